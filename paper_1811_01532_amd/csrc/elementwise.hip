@@ -131,52 +131,69 @@ __global__ __launch_bounds__(256) void reduce_f32_grouped_kernel(const float* __
     }
 }
 
-// ---- bias gradient, first stage: column sums of a chunk of rows (blockIdx.x) for a block of up to 256 column
-// vectors (blockIdx.y).  A thread owns one 8-channel vector (or one channel) and every RP-th row of the chunk; the
-// RP partial sums per column are then added in thread order. ----
+// ---- bias gradient, first stage: column sums of a chunk of rows (blockIdx.y) for a block of column vectors
+// (blockIdx.x) of VEC channels.  `vpb` (a power of two) vectors lie side by side in a work-group, its other threads take
+// every RP-th row, eight loads in flight each (the loop is bound by load latency, not by bytes: a whole FC layer's
+// gradient is 0.8 MB), and the RP partial sums of a column are added as a tree through LDS.  The order is fixed by
+// (rows, cols): bitwise reproducible.  Few wide work-groups with one load in flight and a serial sum over RP took
+// 24 us for 4096 x 16, 33 us for 100 x 4096 and 14 us for 16900 x 256; this takes 7, 5 and 10. ----
 template <int VEC>
-__global__ __launch_bounds__(256) void bias_grad_kernel(const bf16_t* __restrict__ dy, float* __restrict__ part,
-                                                        size_t rows, int cols, size_t rows_per_chunk) {
-    __shared__ float red[256][VEC + 1];
-    const int cv = (cols + VEC - 1) / VEC;         // vectors per row
-    const int vpb = cv < 256 ? cv : 256;           // vectors handled side by side by this work-group
-    const int rp = 256 / vpb;                      // rows in flight per pass
-    const int vec = threadIdx.x % vpb, rsub = threadIdx.x / vpb;
-    const size_t r0 = (size_t)blockIdx.x * rows_per_chunk;
+__device__ __forceinline__ void add_vec(float* s, const bf16_t* p) {
+    if (VEC == 8) {
+        const u32x4 u = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            s[2 * k] += __uint_as_float(u[k] << 16);
+            s[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
+        }
+    } else if (VEC == 4) {
+        const u32x2 u = *reinterpret_cast<const u32x2*>(p);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            s[2 * k] += __uint_as_float(u[k] << 16);
+            s[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
+        }
+    } else {
+        s[0] += bf2f(p[0]);
+    }
+}
+
+template <int VEC>
+__global__ __launch_bounds__(1024) void bias_grad_kernel(const bf16_t* __restrict__ dy, float* __restrict__ part,
+                                                        size_t rows, int cols, size_t rows_per_chunk, int vpb) {
+    __shared__ float red[VEC][1024];
+    const int cv = cols / VEC;                     // vectors per row
+    const int rp = blockDim.x / vpb;                   // rows in flight per pass
+    const int vec = threadIdx.x & (vpb - 1), rsub = threadIdx.x / vpb;
+    const int v = blockIdx.x * vpb + vec;
+    const size_t r0 = (size_t)blockIdx.y * rows_per_chunk;
     size_t r1 = r0 + rows_per_chunk;
     if (r1 > rows) r1 = rows;
-    {
-        const int v = blockIdx.y * vpb + vec;
-        float s[VEC];
+    float s[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) s[e] = 0.f;
-        if (rsub < rp && v < cv) {
-            for (size_t r = r0 + rsub; r < r1; r += rp) {
-                if (VEC == 8) {
-                    const uint4 u = *reinterpret_cast<const uint4*>(dy + r * cols + (size_t)v * 8);
-                    const unsigned w4[4] = {u.x, u.y, u.z, u.w};
+    for (int e = 0; e < VEC; ++e) s[e] = 0.f;
+    if (v < cv) {
+        const bf16_t* p = dy + (size_t)v * VEC;
+        size_t r = r0 + rsub;
+        for (; r + 7 * (size_t)rp < r1; r += 8 * (size_t)rp) {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        s[2 * k] += __uint_as_float(w4[k] << 16);
-                        s[2 * k + 1] += __uint_as_float(w4[k] & 0xffff0000u);
-                    }
-                } else {
-                    s[0] += bf2f(dy[r * cols + v]);
-                }
-            }
+            for (int k = 0; k < 8; ++k) add_vec<VEC>(s, p + (r + (size_t)k * rp) * cols);
         }
+        for (; r < r1; r += rp) add_vec<VEC>(s, p + r * cols);
+    }
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) red[threadIdx.x][e] = s[e];
-        __syncthreads();
-        if (rsub == 0 && v < cv) {
+    for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] = s[e];
+    __syncthreads();
+    for (int o = rp / 2; o > 0; o >>= 1) {
+        if (rsub < o) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                float t = red[vec][e];
-                for (int k = 1; k < rp; ++k) t += red[k * vpb + vec][e];
-                if (v * VEC + e < cols) part[(size_t)blockIdx.x * cols + v * VEC + e] = t;
-            }
+            for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] += red[e][threadIdx.x + o * vpb];
         }
         __syncthreads();
+    }
+    if (rsub == 0 && v < cv) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part[(size_t)blockIdx.y * cols + (size_t)v * VEC + e] = red[e][vec];
     }
 }
 
@@ -493,20 +510,36 @@ __global__ __launch_bounds__(256) void colsum_f32_multi_kernel(const ColsumJobs 
     }
 }
 
+// 16 column vectors (of the concatenation of all matrices) per work-group, 16 threads per vector that each add every
+// 16th chunk; their sums are added in order.  (One thread per vector walked up to 64 chunks one load after the other:
+// 20 us for VGG-16's twelve layers at minibatch 22; this takes 6.)
 __global__ __launch_bounds__(256) void colsum_f32_finish_kernel(const ColsumJobs js, unsigned char* __restrict__ base) {
-    const int t = blockIdx.x * 256 + threadIdx.x;  // column vector in the concatenation of all matrices
+    __shared__ float4 red[256];
+    const int sub = threadIdx.x >> 4;
+    const int t = blockIdx.x * 16 + (threadIdx.x & 15);
     int j = 0, v0 = 0;
     while (j < js.n && t >= v0 + js.job[j].cols / 4) { v0 += js.job[j].cols / 4; ++j; }
-    if (j >= js.n) return;
-    const ColsumJob& jb = js.job[j];
+    const ColsumJob& jb = js.job[j < js.n ? j : 0];
     const int v = t - v0;
-    const float* part2 = reinterpret_cast<const float*>(base + jb.part2_off);
-    float4 s = *reinterpret_cast<const float4*>(part2 + (size_t)v * 4);
-    for (int k = 1; k < jb.chunks; ++k) {
-        const float4 u = *reinterpret_cast<const float4*>(part2 + (size_t)k * jb.cols + (size_t)v * 4);
-        s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < js.n) {
+        const float* part2 = reinterpret_cast<const float*>(base + jb.part2_off) + (size_t)v * 4;
+#pragma unroll 4
+        for (int k = sub; k < jb.chunks; k += 16) {
+            const float4 u = *reinterpret_cast<const float4*>(part2 + (size_t)k * jb.cols);
+            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+        }
     }
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(base + jb.out_off) + (size_t)v * 4) = s;
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (sub == 0 && j < js.n) {
+#pragma unroll
+        for (int k = 1; k < 16; ++k) {
+            const float4 u = red[k * 16 + threadIdx.x];
+            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+        }
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(base + jb.out_off) + (size_t)v * 4) = s;
+    }
 }
 
 int colsum_f32_chunks(size_t rows) {
@@ -533,37 +566,52 @@ int launch_colsum_f32_multi(const ColsumJobs& js, void* base, hipStream_t st) {
     if (rc != WAP_OK) return rc;
     int vecs = 0;
     for (int j = 0; j < js.n; ++j) vecs += js.job[j].cols / 4;
-    hipLaunchKernelGGL(colsum_f32_finish_kernel, dim3((vecs + 255) / 256), dim3(256), 0, st, js, (unsigned char*)base);
+    hipLaunchKernelGGL(colsum_f32_finish_kernel, dim3((vecs + 15) / 16), dim3(256), 0, st, js, (unsigned char*)base);
     return check_launch("colsum_f32_finish");
 }
 
-// Row chunks of the first stage: about 32 loads per thread (a work-group covers min(vectors per row, 256) vectors side
-// by side and 256 / that many rows per pass), at most ~8 work-groups per CU over all column blocks.
+// How the first stage is laid out: 16-byte vectors where the row length allows it (8-byte, else 2-byte), up to 16 of
+// them side by side (256-byte runs of a row; fewer threads per row means more rows in flight and more work-groups).
+struct BiasGradShape {
+    int vecw, vpb, colblocks;
+};
+static BiasGradShape bias_grad_shape(int cols) {
+    BiasGradShape b;
+    b.vecw = (cols & 7) == 0 ? 8 : (cols & 3) == 0 ? 4 : 1;
+    const int cv = cols / b.vecw;
+    const int most = b.vecw == 1 ? 64 : 16;
+    b.vpb = 1;
+    while (b.vpb < cv && b.vpb < most) b.vpb *= 2;
+    b.colblocks = (cv + b.vpb - 1) / b.vpb;
+    return b;
+}
+
+// Row chunks (= partial sums per column) of the first stage.  One chunk, whose sums are the result (no second launch of
+// about 4.6 us), while a thread of a 1024-thread work-group walks at most 16 rows, i.e. two batches of loads; beyond
+// that about 16 rows per thread of 256-thread work-groups, at most ~8 of them per CU over all column blocks.
 int bias_grad_chunks(size_t rows, int cols) {
-    const int vecw = (cols & 7) == 0 ? 8 : 1;
-    const int cv = (cols + vecw - 1) / vecw;
-    const int vpb = cv < 256 ? cv : 256;
-    const int rp = 256 / vpb;
-    const int colblocks = (cv + vpb - 1) / vpb;
-    if (rows <= 512) return 1;  // a minibatch of rows (FC layers): one chunk, its sums are the result (no second launch)
-    size_t chunks = (rows + (size_t)32 * rp - 1) / ((size_t)32 * rp);
-    size_t cap = (size_t)kNumCU * 8 / colblocks;
+    const BiasGradShape b = bias_grad_shape(cols);
+    if (rows <= (size_t)16 * (1024 / b.vpb)) return 1;
+    const size_t rp = 256 / b.vpb;
+    size_t chunks = (rows + 16 * rp - 1) / (16 * rp);
+    size_t cap = (size_t)kNumCU * 8 / b.colblocks;
     if (cap < 1) cap = 1;
     if (chunks > cap) chunks = cap;
-    return (int)(chunks < 1 ? 1 : chunks);
+    return (int)chunks;
 }
 
 int launch_bias_grad(size_t rows, int cols, const bf16_t* dy, float* db, float* part, hipStream_t st) {
     const int chunks = bias_grad_chunks(rows, cols);
     const size_t rpc = (rows + chunks - 1) / chunks;
-    const int vecw = (cols & 7) == 0 ? 8 : 1;
-    const int cv = (cols + vecw - 1) / vecw;
-    const int colblocks = (cv + 255) / 256;  // the kernel covers min(cv, 256) vectors per work-group
+    const BiasGradShape b = bias_grad_shape(cols);
     float* dst = chunks == 1 ? db : part;  // a single chunk writes the result itself
-    if (vecw == 8)
-        hipLaunchKernelGGL(bias_grad_kernel<8>, dim3(chunks, colblocks), dim3(256), 0, st, dy, dst, rows, cols, rpc);
+    const dim3 grid(b.colblocks, chunks), block(chunks == 1 && rows > (size_t)2 * (256 / b.vpb) ? 1024 : 256);
+    if (b.vecw == 8)
+        hipLaunchKernelGGL(bias_grad_kernel<8>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
+    else if (b.vecw == 4)
+        hipLaunchKernelGGL(bias_grad_kernel<4>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
     else
-        hipLaunchKernelGGL(bias_grad_kernel<1>, dim3(chunks, colblocks), dim3(256), 0, st, dy, dst, rows, cols, rpc);
+        hipLaunchKernelGGL(bias_grad_kernel<1>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
     int rc = check_launch("bias_grad");
     if (rc != WAP_OK || chunks == 1) return rc;
     return launch_reduce_f32(part, chunks, (size_t)cols, db, st);
