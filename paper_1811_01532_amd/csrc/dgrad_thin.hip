@@ -1,36 +1,44 @@
 // Data gradient of a convolution whose INPUT has very few channels (the 3-channel image of the first layer):
 //   dx[n,h,w,c] = sum over (k,r,s) of dy[n,p,q,k] * w[k,r,s,c]   with p*stride_h - pad_h + r = h, q likewise,
-// the backward half of t_c (Eq. 1) of the first "primary" node of Section 3.2.2.  As a matrix product it has 3
-// (at most 4) output columns, so an MFMA tile would be nine-tenths padding and the pass is bound by reading dy once;
-// it runs on the vector ALUs instead:
-//   * a wavefront owns 64 pixels of one image row that share their phase (w mod stride_w), so all of them visit the
-//     same filter taps, as eight groups of eight neighbouring pixels; lane (pixel i of the group, channel chunk j)
-//     fetches 16 bytes = channels 8j..8j+7 of dy at its pixel, so a group's load is one contiguous run of dy
-//     (neighbouring pixels of a phase read neighbouring dy pixels) and nothing is fetched twice per tap;
-//   * the lane keeps the weights of its eight channels for the current tap in registers (fp32 copy laid out
-//     [tap][k][4] by a small packing kernel) and accumulates its partial sums of the <= 4 output channels for
-//     each of the eight groups; at the end the eight chunk lanes of a pixel are added with a fixed butterfly
-//     (bitwise reproducible) and one lane stores the pixel as bf16;
-//   * positions the forward pass never reads come out as exact zeros (no tap is valid there).
-// With a stride above one only the taps with (h + pad - r) mod stride = 0 exist for a given row / phase; the loops
-// step through exactly those.
+// the backward half of t_c (Eq. 1) of the first "primary" node of Section 3.2.2.
+//
+// As a product with one row per image pixel it has 3 (at most 4) columns, nine tenths of an MFMA tile would be padding.
+// Turned around it is a good one: z[p,q][(r,s,c)] = sum over k of dy[p,q,k] * w[k,r,s,c] has one row per dy pixel and
+// R*S*C columns (27 of 32 for a 3x3 filter), its operand dy is read as it lies in memory, and dx is the sum of the R*S
+// values of z that land on a pixel.  z never leaves the LDS:
+//   * a work-group (4 wavefronts) owns TH x TW pixels of dx; the filter is walked in groups of rows (and of taps of a
+//     row, and of 64 channels) whose columns fit up to four 32-column blocks, e.g. the whole 3x3 filter in one block;
+//   * for each group the wavefronts make z for the dy pixels under the tile, 32 pixels at a time: the pixel fragments
+//     come straight from global memory (16 bytes of a pixel per lane, neighbouring pixels adjacent), the weight fragments
+//     from the LDS, where the work-group put them in fragment order; out-of-image pixels load zeros;
+//   * then each thread adds up the values of its PX pixels: for a stride above one only the taps that meet the pixel's
+//     row and column phase.  The order of all sums is fixed: bitwise reproducible.
+// Bound by reading dy once (plus the tiles' halo, from L2) for 3 x 3 filters: 64 channels at 224 x 224, minibatch 24
+// (154 MB) 262 us on the vector ALUs (each dy element read once per tap, three multiply-adds each), now 44 us, 3.7 TB/s;
+// for large strided filters by the latency of the groups' load - product - sum phases: 11 x 11 / 4 at minibatch 32 299 to
+// 72 us (weights gathered with branches around the loads instead of out-of-range offsets: 123 us; one filter row per
+// group: 131 us).
 #include "wap_internal.h"
 
 namespace wap {
 
 namespace {
 
-constexpr int NT = 64;
+constexpr int NT = 256;
+constexpr int KC = 64;  // dy channels per pass: four MFMA reduction steps
 
 struct ThinArgs {
     const bf16_t* dy;   // [N][IH][IW][K]
-    const float* wp;    // packed weights [R*S][K][4] (column c of tap (r,s), zero beyond Ncols), forward tap order
+    const bf16_t* w;    // [K][R][S][C]
     bf16_t* dx;         // [N][OH][OW][C]
-    int N, IH, IW, K, OH, OW, C, R, S, sh, sw, ph, pw;  // ph / pw: the forward pass's padding
-    unsigned dy_bytes, wp_bytes;  // both below 2 GiB (host)
-    int cols;           // ceil(OW / sw): pixels of one phase in a row
-    int colblocks;      // ceil(cols / 64)
-    FastDiv dCB, dSW, dOH;
+    int N, IH, IW, K, OH, OW, R, S, sh, sw, ph, pw;  // ph / pw: the forward pass's padding
+    unsigned dy_bytes;       // below 2 GiB (host)
+    int rg, sg;              // filter rows / taps of a row per group
+    int zh, zw, zgroups;     // dy rows / columns under a tile for one group, 32-pixel groups of them
+    int zp;                  // floats per z row: the columns rounded up to an odd number of 16-byte units (all banks)
+    int tiles_w, tiles;      // tiles per row of dx, in all
+    FastDiv dTW, dTI, dZW, dSH, dSW;   // division by tiles per row, tiles per image, zw, the strides
+    int tiles_img;
 };
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -38,91 +46,161 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     return __builtin_bit_cast(unsigned short, b);
 }
 
-// fp32 copy of the weights in the order the gradient kernel walks them: wp[(r*S+s)*K + k][c], c < 4
-__global__ void dgrad_thin_pack_kernel(const bf16_t* __restrict__ w, float* __restrict__ wp, int K, int RS, int C) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;  // (tap, k)
-    if (i >= RS * K) return;
-    const int tap = i / K, k = i - tap * K;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    const bf16_t* src = w + ((size_t)k * RS + tap) * C;
-    float* f = reinterpret_cast<float*>(&v);
-    for (int c = 0; c < C; ++c) f[c] = __uint_as_float((unsigned)src[c] << 16);
-    reinterpret_cast<float4*>(wp)[i] = v;
-}
+// smallest integer >= a / b for any a, b >= 1
+__device__ __forceinline__ int ceil_div(int a, int b) { return a >= 0 ? (a + b - 1) / b : -((-a) / b); }
 
+// C: channels of dx; NB: 32-column blocks of z; PX: pixels per thread (a tile is 8 x 32 for one, 16 x 64 for four)
+template <int C, int NB, int PX>
 __global__ __launch_bounds__(NT) void dgrad_thin_kernel(const ThinArgs a) {
-    // block -> (image n, row h, phase of w, block of 64 columns of that phase): all uniform
-    int b = blockIdx.x;
-    const int cb = b - (int)fdiv((uint32_t)b, a.dCB) * a.colblocks;
-    b = (int)fdiv((uint32_t)b, a.dCB);
-    const int phase = b - (int)fdiv((uint32_t)b, a.dSW) * a.sw;
-    b = (int)fdiv((uint32_t)b, a.dSW);
-    const int h = b - (int)fdiv((uint32_t)b, a.dOH) * a.OH;
-    const int n = (int)fdiv((uint32_t)b, a.dOH);
-    const int lane = threadIdx.x, pi = lane >> 3, kc = lane & 7;  // pixel within a group, channel chunk
-
+    constexpr int TH = PX == 1 ? 8 : 16, TW = PX == 1 ? 32 : 64;
+    constexpr int WF = NB * (KC / 16) * 64;  // 16-byte weight fragments of a group
+    extern __shared__ __align__(16) unsigned char smem[];
+    u32x4* const wf = reinterpret_cast<u32x4*>(smem);
+    float* const z = reinterpret_cast<float*>(smem + WF * 16);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ngr = (a.R + a.rg - 1) / a.rg, ngs = (a.S + a.sg - 1) / a.sg, nkc = (a.K + KC - 1) / KC;
+    const int ngroups = ngr * ngs * nkc;
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.dy), 0, (int)a.dy_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcW =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, (int)a.wp_bytes, 0x00020000);
-    float acc[8][4];
-#pragma unroll
-    for (int gi = 0; gi < 8; ++gi)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[gi][c] = 0.f;
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.w), 0, (int)((unsigned)a.K * a.R * a.S * C * 2u), 0x00020000);
 
-    // taps with h + ph - r = p * sh: r = r0, r0 + sh, ...
-    const int r0 = (h + a.ph) % a.sh, s0 = (phase + a.pw) % a.sw;
-    for (int r = r0; r < a.R; r += a.sh) {
-        const int p = (h + a.ph - r) / a.sh;
-        if (h + a.ph - r < 0 || p >= a.IH) continue;  // uniform
-        for (int s = s0; s < a.S; s += a.sw) {
-            for (int k0 = 0; k0 < a.K; k0 += 64) {     // 64 channels per pass: chunk kc holds k0 + 8 kc .. + 7
-                const int kk = k0 + kc * 8;
-                // this lane's weights for the tap (out of range beyond K: zeros)
-                f32x4 wv[8];
-                const unsigned woff = kk < a.K ? (unsigned)(((r * a.S + s) * a.K + kk) * 16) : 0x80000000u;
+    bool weights_in = false;
+    for (int tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
+        const int n = (int)fdiv((uint32_t)tile, a.dTI);
+        const int ti = tile - n * a.tiles_img;
+        const int th = (int)fdiv((uint32_t)ti, a.dTW);
+        const int h0 = th * TH, w0 = (ti - th * a.tiles_w) * TW;
+        float acc[PX][C];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    wv[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrcW, woff + (unsigned)e * 16u, 0, 0));
+        for (int i = 0; i < PX; ++i)
 #pragma unroll
-                for (int gi = 0; gi < 8; ++gi) {
-                    const int j = cb * 64 + gi * 8 + pi;   // index within the phase
-                    const int wq = phase + j * a.sw;       // the pixel's column
-                    const int t = wq + a.pw - s;           // a multiple of sw
-                    const int q = t / a.sw;
-                    const bool ok = j < a.cols && wq < a.OW && t >= 0 && q < a.IW && kk < a.K;
-                    // lanes without a pixel read from beyond the buffer's range: zeros, no branch around the load
-                    const unsigned src = ok ? (unsigned)(((n * a.IH + p) * a.IW + q) * a.K + kk) * 2u : 0x80000000u;
-                    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, src, 0, 0);
+            for (int c = 0; c < C; ++c) acc[i][c] = 0.f;
+        // a pixel's row h meets the taps r = rf + sh * i at the dy rows hd - i, its column the taps sf + sw * j at wd - j
+        int rf[PX], hd[PX], sf[PX], wd[PX];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float g = __uint_as_float((e & 1) ? (v[e >> 1] & 0xffff0000u) : (v[e >> 1] << 16));
+        for (int i = 0; i < PX; ++i) {
+            const int pix = tid + i * NT;
+            const int hp = h0 + pix / TW + a.ph, wp = w0 + pix % TW + a.pw;
+            hd[i] = (int)fdiv((uint32_t)hp, a.dSH);
+            rf[i] = hp - hd[i] * a.sh;
+            wd[i] = (int)fdiv((uint32_t)wp, a.dSW);
+            sf[i] = wp - wd[i] * a.sw;
+        }
+
+        for (int grp = 0; grp < ngroups; ++grp) {
+            const int k0 = (grp % nkc) * KC;
+            const int s0 = (grp / nkc % ngs) * a.sg, r0 = grp / (nkc * ngs) * a.rg;
+            const int rg = a.R - r0 < a.rg ? a.R - r0 : a.rg, sg = a.S - s0 < a.sg ? a.S - s0 : a.sg;
+            // ---- weights of the group in fragment order: [block][reduction step][lane][8 channels], zero beyond ----
+            if (ngroups > 1 || !weights_in) {
+                unsigned short* const wl = reinterpret_cast<unsigned short*>(smem);
+                // a thread keeps its column, so that neighbouring threads read runs of w; all its loads are in flight
+                constexpr int KSTEP = NT / (NB * 32);
+                const int col = tid % (NB * 32), kt = tid / (NB * 32);
+                const int r = col / (sg * C);
+                const bool in = r < rg;
+                const unsigned row = (unsigned)(a.R * a.S * C) * 2u;
+                const unsigned src = (unsigned)(k0 + kt) * row + (unsigned)((r0 + r) * (a.S * C) + s0 * C + (col - r * (sg * C))) * 2u;
+                unsigned short v[KC / KSTEP];
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) acc[gi][c] = __builtin_fmaf(g, wv[e][c], acc[gi][c]);
+                for (int i = 0; i < KC / KSTEP; ++i)
+                    v[i] = __builtin_amdgcn_raw_buffer_load_b16(
+                        rsrcW, in && k0 + kt + i * KSTEP < a.K ? src + (unsigned)(i * KSTEP) * row : 0x80000000u, 0, 0);
+#pragma unroll
+                for (int i = 0; i < KC / KSTEP; ++i) {
+                    const int k = kt + i * KSTEP;
+                    // lane = column within the block + 32 * (half of the 16-deep step)
+                    wl[((((col >> 5) * (KC / 16) + (k >> 4)) * 64) + (col & 31) + ((k >> 3) & 1) * 32) * 8 + (k & 7)] = v[i];
+                }
+                weights_in = true;
+            }
+            __syncthreads();  // weights in place; the previous group's z is read
+            // ---- z for the dy pixels under the tile ----
+            const int p_lo = ceil_div(h0 + a.ph - (r0 + rg - 1), a.sh), q_lo = ceil_div(w0 + a.pw - (s0 + sg - 1), a.sw);
+            for (int g = wave; g < a.zgroups; g += NT / 64) {
+                const int px = g * 32 + (lane & 31);
+                const int pr = (int)fdiv((uint32_t)px, a.dZW), pc = px - pr * a.zw;
+                const int p = p_lo + pr, q = q_lo + pc;
+                const bool in = pr < a.zh && (unsigned)p < (unsigned)a.IH && (unsigned)q < (unsigned)a.IW;
+                const int kk = k0 + (lane >> 5) * 8;
+                const unsigned base = (unsigned)(((n * a.IH + p) * a.IW + q) * a.K + kk) * 2u;
+                bf16x8 fd[KC / 16];
+#pragma unroll
+                for (int ks = 0; ks < KC / 16; ++ks)  // outside the image or beyond K: beyond the buffer, i.e. zeros
+                    fd[ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rsrc, in && kk + ks * 16 < a.K ? base + ks * 32u : 0x80000000u, 0, 0));
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    f32x16 d;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) d[e] = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < KC / 16; ++ks)
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, wf[(b * (KC / 16) + ks) * 64 + lane]), fd[ks], d, 0, 0, 0);
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const int col = b * 32 + q4 * 8 + (lane >> 5) * 4;
+                        if (col < a.zp)
+                            *reinterpret_cast<float4*>(z + px * a.zp + col) =
+                                make_float4(d[q4 * 4], d[q4 * 4 + 1], d[q4 * 4 + 2], d[q4 * 4 + 3]);
+                    }
+                }
+            }
+            __syncthreads();
+            // ---- the taps of the group that land on this thread's pixels ----
+            const int ri = r0 / a.sh, rb = r0 - ri * a.sh, sj = s0 / a.sw, sb = s0 - sj * a.sw;
+#pragma unroll
+            for (int i = 0; i < PX; ++i) {
+                const int j0 = sj + (sf[i] < sb ? 1 : 0);
+                const int s_first = sf[i] + a.sw * j0;
+                int k = ri + (rf[i] < rb ? 1 : 0);
+                for (int r = rf[i] + a.sh * k; r < r0 + rg; r += a.sh, ++k) {
+                    const float* src = z + ((hd[i] - k - p_lo) * a.zw + wd[i] - j0 - q_lo) * a.zp + ((r - r0) * sg + s_first - s0) * C;
+                    for (int s = s_first; s < s0 + sg; s += a.sw) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) acc[i][c] += src[c];
+                        src += a.sw * C - a.zp;  // the next tap of this phase meets the dy pixel to the left
                     }
                 }
             }
         }
-    }
-    // add the eight chunk lanes of every pixel (lanes 8 i .. 8 i + 7) in a fixed butterfly; lane 8 i stores
 #pragma unroll
-    for (int gi = 0; gi < 8; ++gi) {
+        for (int i = 0; i < PX; ++i) {
+            const int pix = tid + i * NT;
+            const int h = h0 + pix / TW, wq = w0 + pix % TW;
+            if (h < a.OH && wq < a.OW) {
+                bf16_t* dst = a.dx + ((size_t)(n * a.OH + h) * a.OW + wq) * C;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float v = acc[gi][c];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            acc[gi][c] = v;
-        }
-        const int j = cb * 64 + gi * 8 + pi;
-        const int wq = phase + j * a.sw;
-        if (kc == 0 && j < a.cols && wq < a.OW) {
-            bf16_t* dst = a.dx + ((size_t)(n * a.OH + h) * a.OW + wq) * a.C;
-            for (int c = 0; c < a.C; ++c) dst[c] = f2bf(acc[gi][c]);
+                for (int c = 0; c < C; ++c) dst[c] = f2bf(acc[i][c]);
+            }
         }
     }
+}
+
+template <int C, int NB, int PX>
+int launch_one(const ThinArgs& a, size_t smem, hipStream_t st) {
+    auto kfn = dgrad_thin_kernel<C, NB, PX>;
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           160 * 1024);
+        if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+        attr_done = true;
+    }
+    // as many work-groups as are resident at once (by LDS); they walk the tiles, so the weights are put in place once
+    const int per_cu = (int)(160 * 1024 / smem);
+    const int most = kNumCU * (per_cu < 6 ? per_cu : 6);
+    hipLaunchKernelGGL(kfn, dim3(a.tiles < most ? a.tiles : most), dim3(NT), smem, st, a);
+    return check_launch("dgrad_thin");
+}
+
+template <int C, int PX>
+int launch_c(const ThinArgs& a, int cols, size_t smem, hipStream_t st) {
+    if (cols <= 32) return launch_one<C, 1, PX>(a, smem, st);
+    if (cols <= 64) return launch_one<C, 2, PX>(a, smem, st);
+    return launch_one<C, 4, PX>(a, smem, st);
 }
 
 }  // namespace
@@ -130,39 +208,55 @@ __global__ __launch_bounds__(NT) void dgrad_thin_kernel(const ThinArgs a) {
 // g: the data-gradient geometry (rows = input pixels, gathered tensor = dy, Ncols = input channels of the layer)
 bool dgrad_thin_supported(const GemmGeom& g) {
     if (g.Ncols > 4 || (g.IC % 8) != 0 || g.mul_h != 1 || g.mul_w != 1) return false;
-    if ((double)(g.M / ((long)g.OH * g.OW)) * g.IH * g.IW * g.IC * 2.0 >= 2147483648.0) return false;  // 32-bit dy offsets
-    const long blocks = (long)(g.M / g.OW) * g.div_w * (((g.OW + g.div_w - 1) / g.div_w + NT - 1) / NT);
-    return blocks < (1L << 31);
+    // 32-bit byte offsets into dy and w
+    return (double)(g.M / ((long)g.OH * g.OW)) * g.IH * g.IW * g.IC * 2.0 < 2147483648.0 &&
+           (double)g.Kred * g.Ncols * 2.0 < 2147483648.0;
 }
-size_t dgrad_thin_ws_bytes(const GemmGeom& g) { return (size_t)g.R * g.S * g.IC * 4 * sizeof(float); }
 
-int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, void* ws, hipStream_t st) {
+int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st) {
     if (!dgrad_thin_supported(g)) return set_error(WAP_EINVAL, "internal: thin data-gradient kernel not applicable");
-    const int RS = g.R * g.S, K = g.IC;
-    hipLaunchKernelGGL(dgrad_thin_pack_kernel, dim3((RS * K + 255) / 256), dim3(256), 0, st, w, reinterpret_cast<float*>(ws),
-                       K, RS, g.Ncols);
-    int rc = check_launch("dgrad_thin_pack");
-    if (rc != WAP_OK) return rc;
+    const int C = g.Ncols;
     ThinArgs a;
     a.dy = dy;
-    a.wp = reinterpret_cast<const float*>(ws);
+    a.w = w;
     a.dx = dx;
-    a.wp_bytes = (unsigned)dgrad_thin_ws_bytes(g);
-    a.dy_bytes = (unsigned)((size_t)(g.M / (g.OH * g.OW)) * g.IH * g.IW * g.IC * 2);
     a.N = g.M / (g.OH * g.OW);
-    a.IH = g.IH; a.IW = g.IW; a.K = K;
-    a.OH = g.OH; a.OW = g.OW; a.C = g.Ncols;
+    a.dy_bytes = (unsigned)((size_t)a.N * g.IH * g.IW * g.IC * 2);
+    a.IH = g.IH; a.IW = g.IW; a.K = g.IC;
+    a.OH = g.OH; a.OW = g.OW;
     a.R = g.R; a.S = g.S;
     a.sh = g.div_h; a.sw = g.div_w;
     a.ph = g.R - 1 - g.pad_h; a.pw = g.S - 1 - g.pad_w;  // the geometry carries the flipped-filter padding
-    a.cols = (g.OW + a.sw - 1) / a.sw;
-    a.colblocks = (a.cols + NT - 1) / NT;
-    a.dCB = make_fastdiv((uint32_t)a.colblocks);
+    // Strided both ways, a tile of 8 x 32 pixels lies over a handful of dy pixels: four times the pixels, less halo.
+    const int px = a.sh > 1 && a.sw > 1 ? 4 : 1;
+    const int TH = px == 1 ? 8 : 16, TW = px == 1 ? 32 : 64;
+    // Groups: the fewest (each costs two barriers and a round of loads) whose columns fit four blocks and whose z leaves
+    // room for two work-groups per CU; rows beyond 16 taps go in pieces, which bounds z by 105 KB.
+    a.sg = a.S < 16 ? a.S : 16;
+    a.zw = (TW - 1 + a.sg - 1) / a.sw + 1;
+    size_t z_bytes = 0;
+    for (int n = 1; n <= a.R; ++n) {
+        a.rg = a.sg == a.S ? (a.R + n - 1) / n : 1;
+        a.zh = (TH - 1 + a.rg - 1) / a.sh + 1;
+        a.zgroups = (a.zh * a.zw + 31) / 32;
+        a.zp = (a.rg * a.sg * C + 3) / 4 * 4;
+        if ((a.zp & 4) == 0) a.zp += 4;
+        z_bytes = (size_t)a.zgroups * 32 * a.zp * sizeof(float);
+        if (a.rg == 1 || (a.rg * a.sg * C <= 128 && z_bytes <= 56 * 1024)) break;
+    }
+    const int cols = a.rg * a.sg * C;
+    a.tiles_w = (a.OW + TW - 1) / TW;
+    a.tiles_img = a.tiles_w * ((a.OH + TH - 1) / TH);
+    a.tiles = a.N * a.tiles_img;
+    a.dTW = make_fastdiv((uint32_t)a.tiles_w);
+    a.dTI = make_fastdiv((uint32_t)a.tiles_img);
+    a.dZW = make_fastdiv((uint32_t)a.zw);
+    a.dSH = make_fastdiv((uint32_t)a.sh);
     a.dSW = make_fastdiv((uint32_t)a.sw);
-    a.dOH = make_fastdiv((uint32_t)a.OH);
-    const long blocks = (long)a.N * a.OH * a.sw * a.colblocks;
-    hipLaunchKernelGGL(dgrad_thin_kernel, dim3((unsigned)blocks), dim3(NT), 0, st, a);
-    return check_launch("dgrad_thin");
+    const size_t smem = (size_t)(cols <= 32 ? 1 : cols <= 64 ? 2 : 4) * (KC / 16) * 1024 + z_bytes;
+#define WAP_DISPATCH(C) (px == 1 ? launch_c<C, 1>(a, cols, smem, st) : launch_c<C, 4>(a, cols, smem, st))
+    return C == 1 ? WAP_DISPATCH(1) : C == 2 ? WAP_DISPATCH(2) : C == 3 ? WAP_DISPATCH(3) : WAP_DISPATCH(4);
+#undef WAP_DISPATCH
 }
 
 }  // namespace wap

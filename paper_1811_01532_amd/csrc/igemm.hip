@@ -408,9 +408,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
         return p;
     }
     if (b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 9) && dgrad_thin_supported(g)) {
-        p.cfg = 9;  // at most four output columns (gradient w.r.t. a 3-channel image): vector-ALU kernel
+        p.cfg = 9;  // at most four output columns (gradient w.r.t. a 3-channel image)
         p.nsplit = 1;
-        p.ws_bytes = dgrad_thin_ws_bytes(g);
+        p.ws_bytes = 0;
         return p;
     }
     int mode = classify_mode(g, b_tr);
@@ -476,7 +476,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
         return launch_relu_bwd(out, relu_mask, out, (size_t)g.M * g.Ncols, st);
     }
     if (plan.cfg == 8) return launch_conv_c3_fwd(g, A, Bw, bias, relu, out, st);
-    if (plan.cfg == 9) return launch_dgrad_thin(g, A, Bw, out, ws, st);
+    if (plan.cfg == 9) return launch_dgrad_thin(g, A, Bw, out, st);
     KArgs ka;
     ka.A = A;
     ka.Bw = Bw;

@@ -29,3 +29,30 @@ def test_bias_grad_layout_edges(orc, rows, cols):
     # fp32 sums of `rows` values of magnitude one: the error grows like sqrt(rows) * 2^-24 of their scale sqrt(rows)
     scale = max(np.abs(ref).max(), np.sqrt(rows))
     assert np.max(np.abs(gu.host_f64(db[:cols]) - ref)) <= 1e-5 * scale
+
+
+# gradient w.r.t. an image of 1 .. 4 channels: maps one pixel over / under the 8 x 32 and 16 x 64 tiles, strides in one or
+# both directions, filters in one group, in several (rows, and taps of rows longer than 16), several passes of 64 channels
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad", [
+    (2, 8, 32, 3, 64, 3, 3, 1, 1), (1, 9, 33, 3, 64, 3, 3, 1, 1), (3, 7, 31, 3, 8, 3, 3, 1, 0), (1, 17, 20, 1, 72, 5, 5, 1, 2),
+    (1, 16, 64, 3, 64, 11, 11, 4, 2), (2, 33, 65, 3, 96, 11, 11, 4, 2), (1, 40, 37, 3, 136, 7, 7, 2, 3),
+    (1, 12, 50, 2, 16, 3, 5, (1, 2), (1, 2)), (1, 13, 40, 4, 40, 4, 3, (2, 1), (0, 1)), (1, 31, 34, 3, 24, 3, 3, 3, 1),
+    (1, 10, 60, 4, 16, 2, 19, 1, (1, 9)), (1, 20, 70, 3, 32, 18, 18, 2, 5), (2, 5, 5, 1, 8, 1, 1, 1, 0), (1, 30, 41, 1, 16, 20, 1, 1, (3, 0)),
+])
+def test_image_gradient_edges(orc, N, H, W, C, K, R, S, stride, pad):
+    import paper_1811_01532_amd as wap
+    st = (stride, stride) if isinstance(stride, int) else stride
+    pd = (pad, pad) if isinstance(pad, int) else pad
+    print(f"[case] image gradient {(N, H, W, C, K, R, S, st, pd)}", flush=True)
+    P, Q = si.out_dim(H, pd[0], R, st[0]), si.out_dim(W, pd[1], S, st[1])
+    gb, wb = si.normal_bf16(si.rng(440, H * W + K), (N, P, Q, K)), si.he_weight_bf16(si.rng(441, R * S + C), (K, R, S, C))
+    d = wap.conv_desc(N, H, W, C, K, R, S, st, pd)
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_DATA) == "dgrad_thin_kernel"
+    dx = torch.full((N * H * W * C + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wap.wap_conv2d_bwd_data(d, gu.dev_bf16(gb), gu.dev_bf16(wb), dx,
+                            gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)))
+    torch.cuda.synchronize()
+    assert torch.isnan(dx[N * H * W * C:]).all()
+    ref = orc.conv2d_bwd_data(orc.bf16_bits_to_f64(gb), orc.bf16_bits_to_f64(wb), (N, H, W, C), st, pd)
+    e = gu.rel_err(gu.host_f64(dx[:N * H * W * C]).reshape(N, H, W, C), ref)
+    assert e <= gu.TOL_BF16_OUT, e           # one bf16 rounding of an fp32 sum
