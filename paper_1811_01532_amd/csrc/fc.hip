@@ -1,0 +1,336 @@
+// Fully-connected layers at small minibatches (Section 3.2.2 "primary" nodes; the forward and the data half of the
+// backward part of t_c in Eq. 1): y[B][out] = x[B][in] * Wt[out][in]^T and dx[B][in] = dy[B][out] * Wt[out][in].  Both
+// are bound by reading Wt once, so the kernels are built as streams of Wt, not as tiles of a product:
+//   * Wt goes from memory straight into the MFMA operand registers, never through the LDS: every byte of it is used by
+//     one wavefront only.  The batch operand (L2-resident) is loaded beside it in the same layout.
+//   * The reduction is divided over the wavefronts of ONE work-group, step by step in turn, so that the work-group as a
+//     whole walks contiguous runs of Wt; the partial results meet in the LDS, are added in a fixed order (bitwise
+//     reproducible) and leave with bias / ReLU / the ReLU derivative of the layer below applied.  The generic kernel
+//     divides it over work-groups: fp32 partial sums through memory and a second launch of 5 .. 7 us.
+//   * Every load of the next steps is issued before the products of the present ones, in two register sets.
+//   * Row lengths that are no multiple of 8 are read with unaligned loads, the last vector moved back to end with the row.
+// Forward (up to 16 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt), 16 wavefronts.
+// Data gradient: the reduction runs over the rows of Wt.  A lane loads CPL neighbouring columns of eight rows and turns
+// the 8 x CPL block around in registers (byte permutes); a work-group owns 16 * CPL columns, 8 wavefronts.
+#include "wap_internal.h"
+
+namespace wap {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+struct FcArgs {
+    const bf16_t* act;   // x [B][in] (forward) or dy [B][out] (data gradient)
+    const bf16_t* w;     // [out][in]
+    const float* bias;   // forward
+    const bf16_t* mask;  // data gradient: dx = mask > 0 ? dx : 0
+    void* res;           // bf16 result, or fp32 partial sums [split][B][out]
+    int B, in, out;
+    int relu, partial, steps_per_split;
+};
+
+__device__ __forceinline__ unsigned short f2bf(float f) {
+    __bf16 b = (__bf16)f;  // round to nearest even
+    return __builtin_bit_cast(unsigned short, b);
+}
+
+__device__ __forceinline__ int xcd_remap(int bid, int total) {
+    int per = total / kNumXCD, rem = total % kNumXCD;
+    int xcd = bid % kNumXCD, idx = bid / kNumXCD;
+    return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+}
+
+constexpr unsigned kNowhere = 0x80000000u;  // beyond every buffer here (all below 2 GiB): loads zeros
+
+__device__ __forceinline__ bf16x8 ldb128(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+constexpr int FW_WAVES = 16;
+
+// VEC8: rows are 16-byte aligned (in % 8 == 0)
+template <bool VEC8>
+__global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
+    constexpr int U = 4;  // 32-deep steps per register set
+    __shared__ f32x4_t red[FW_WAVES][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = lane & 15, kg = lane >> 4;
+    const int o0 = blockIdx.x * 16;
+    const int orows = a.out - o0 < 16 ? a.out - o0 : 16;
+    const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(a.w + (size_t)o0 * a.in), 0, orows * a.in * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rX =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.act), 0, a.B * a.in * 2, 0x00020000);
+    const unsigned off = (unsigned)row * (unsigned)a.in * 2u;  // rows beyond the matrix lie beyond its buffer
+    const int first = blockIdx.y * a.steps_per_split;
+    const int steps = (a.in + 31) / 32;
+    const int last = first + a.steps_per_split < steps ? first + a.steps_per_split : steps;
+
+    bf16x8 fw[2][U], fx[2][U];
+    auto load = [&](int set, int st) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = st + u * FW_WAVES;
+            int k = s * 32 + kg * 8;
+            const bool ok = s < last && k < a.in;
+            if (!VEC8 && k > a.in - 8) k = a.in - 8;  // the row's last vector, moved back to end with the row
+            fw[set][u] = ldb128(rW, ok ? off + (unsigned)k * 2u : kNowhere);
+            fx[set][u] = ldb128(rX, ok ? off + (unsigned)k * 2u : kNowhere);
+        }
+    };
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](int set, int st) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!VEC8) {  // a vector that was moved back repeats elements of its neighbour
+                const int k = (st + u * FW_WAVES) * 32 + kg * 8;
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (e < k - (a.in - 8)) fx[set][u][e] = (__bf16)0.f;
+            }
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][u], fx[set][u], acc, 0, 0, 0);
+        }
+    };
+    constexpr int STRIDE = U * FW_WAVES;
+    int st = first + wave;
+    load(0, st);
+    while (true) {
+        load(1, st + STRIDE);
+        __builtin_amdgcn_sched_barrier(0);  // the scheduler would move the loads down to their uses
+        mul(0, st);
+        st += STRIDE;
+        if (st >= last) break;  // uniform in the wavefront; a set loaded beyond the range holds zeros and is dropped
+        load(0, st + STRIDE);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(1, st);
+        st += STRIDE;
+        if (st >= last) break;
+    }
+
+    // lane: batch row lane & 15, output features (lane >> 4) * 4 .. + 3
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (tid >= 64) return;
+    f32x4_t s = red[0][lane];
+#pragma unroll
+    for (int w = 1; w < FW_WAVES; ++w) s += red[w][lane];
+    const int o = o0 + kg * 4;
+    if (row >= a.B) return;
+    const size_t e0 = (size_t)row * a.out + o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (o + e >= a.out) continue;
+        if (a.partial) {
+            reinterpret_cast<float*>(a.res)[(size_t)blockIdx.y * a.B * a.out + e0 + e] = s[e];
+        } else {
+            float v = a.bias ? s[e] + a.bias[o + e] : s[e];
+            if (a.relu) v = v > 0.f ? v : 0.f;
+            reinterpret_cast<bf16_t*>(a.res)[e0 + e] = f2bf(v);
+        }
+    }
+}
+
+constexpr int DX_WAVES = 8;
+
+// NB: blocks of 16 batch rows; CPL: columns of Wt per lane (a work-group owns 16 * CPL); VEC8: out % 8 == 0
+template <int NB, int CPL, bool VEC8>
+__global__ __launch_bounds__(64 * DX_WAVES) void fc_dx_kernel(const FcArgs a) {
+    constexpr int U = NB * CPL <= 4 ? 2 : 1;  // 32-deep steps per register set
+    __shared__ f32x4_t red[DX_WAVES][CPL][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int il = lane & 15, og = lane >> 4;
+    // neighbours in memory share an L2; the last work-group is moved back to end with the row (it repeats columns of its
+    // neighbour, bit for bit)
+    int i0 = xcd_remap(blockIdx.x, gridDim.x) * 16 * CPL;
+    if (i0 > a.in - 16 * CPL) i0 = a.in - 16 * CPL;
+    const int col = i0 + il * CPL;
+    const __amdgpu_buffer_rsrc_t rW =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.w), 0, (int)((unsigned)a.out * (unsigned)a.in * 2u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rG =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.act), 0, a.B * a.out * 2, 0x00020000);
+    const unsigned rowb = (unsigned)a.in * 2u;
+    const int steps = (a.out + 31) / 32;
+
+    unsigned fw[2][U][8][CPL / 2];  // eight rows of Wt, CPL columns
+    bf16x8 fg[2][U][NB];
+    auto load1 = [&](int set, int u, int s) {
+        const int o = s * 32 + og * 8;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int bi = b * 16 + il;
+            const int oo = !VEC8 && o > a.out - 8 ? a.out - 8 : o;  // the row's last vector, moved back to end with the row
+            fg[set][u][b] = ldb128(rG, o < a.out && bi < a.B ? (unsigned)(bi * a.out + oo) * 2u : kNowhere);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const unsigned off = o + j < a.out ? (unsigned)(o + j) * rowb + (unsigned)col * 2u : kNowhere;
+            if (CPL == 4) {
+                const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rW, off, 0, 0));
+                fw[set][u][j][0] = v[0];
+                fw[set][u][j][CPL / 2 - 1] = v[1];
+            } else {
+                fw[set][u][j][0] = __builtin_amdgcn_raw_buffer_load_b32(rW, off, 0, 0);
+            }
+        }
+    };
+    auto load = [&](int set, int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load1(set, u, s + u * DX_WAVES);
+    };
+    f32x4_t acc[CPL][NB];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[c][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto mul1 = [&](int set, int u, int s) {
+        if (!VEC8) {  // a vector that was moved back: its elements d, d + 1, ... to the front, zeros behind
+            const int d = s * 32 + og * 8 - (a.out - 8);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                u32x4 v = __builtin_bit_cast(u32x4, fg[set][u][b]);
+                if (d & 4) v = u32x4{v[2], v[3], 0u, 0u};
+                if (d & 2) v = u32x4{v[1], v[2], v[3], 0u};
+                if (d & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+                if (d > 0) fg[set][u][b] = __builtin_bit_cast(bf16x8, v);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            u32x4 v;  // column c of the eight rows
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                v[d] = __builtin_amdgcn_perm(fw[set][u][2 * d + 1][c >> 1], fw[set][u][2 * d][c >> 1],
+                                             (c & 1) ? 0x07060302u : 0x05040100u);
+            const bf16x8 wv = __builtin_bit_cast(bf16x8, v);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                acc[c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, fg[set][u][b], acc[c][b], 0, 0, 0);
+        }
+    };
+    auto mul = [&](int set, int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) mul1(set, u, s + u * DX_WAVES);
+    };
+    constexpr int STRIDE = U * DX_WAVES;
+    int st = wave;
+    load(0, st);
+    while (true) {
+        load(1, st + STRIDE);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(0, st);
+        st += STRIDE;
+        if (st >= steps) break;
+        load(0, st + STRIDE);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(1, st);
+        st += STRIDE;
+        if (st >= steps) break;
+    }
+
+    // lane: batch row lane & 15; accumulator element e of column block c is column ((lane >> 4) * 4 + e) * CPL + c, so a
+    // lane holds 4 * CPL neighbouring columns, staged as CPL groups of four
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int h = 0; h < CPL; ++h) {
+            f32x4_t v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = acc[(h * 4 + t) % CPL][b][(h * 4 + t) / CPL];
+            red[wave][h][lane] = v;
+        }
+        __syncthreads();
+        if (tid < 64 * CPL) {
+            const int h = tid >> 6;
+            f32x4_t s = red[0][h][lane];
+#pragma unroll
+            for (int w = 1; w < DX_WAVES; ++w) s += red[w][h][lane];
+            const int bi = b * 16 + il, i = i0 + og * 4 * CPL + h * 4;
+            if (bi < a.B) {
+                const size_t e = (size_t)bi * a.in + i;
+                if (a.mask) {
+                    u32x2 m;
+                    __builtin_memcpy(&m, a.mask + e, 8);  // rows need not be 8-byte aligned
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float y = __uint_as_float((t & 1) ? m[t >> 1] & 0xffff0000u : m[t >> 1] << 16);
+                        s[t] = y > 0.f ? s[t] : 0.f;
+                    }
+                }
+                u32x2 pk = {(unsigned)f2bf(s[0]) | ((unsigned)f2bf(s[1]) << 16),
+                            (unsigned)f2bf(s[2]) | ((unsigned)f2bf(s[3]) << 16)};
+                __builtin_memcpy(reinterpret_cast<bf16_t*>(a.res) + e, &pk, 8);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// a fully-connected product: one pixel per image, one tap
+bool is_fc(const GemmGeom& g) {
+    return g.IH == 1 && g.IW == 1 && g.OH == 1 && g.OW == 1 && g.R == 1 && g.S == 1 && g.pad_h == 0 && g.pad_w == 0;
+}
+bool below_2g(double elems) { return elems * 2.0 < 2147483648.0; }
+
+}  // namespace
+
+// Every work-group reads the whole batch operand, through an L2 path that carries about 8.6 TB/s: with one block of 16
+// rows that is as much traffic as Wt itself, with more it outweighs Wt, and the generic kernel's tiles (64 x 256, split
+// reduction) are faster: 4096 x 9216 at 8 / 32 / 64 rows 17.3 / 29 / 44 us here, 21.9 / 22.2 / 24.5 us there;
+// 4096 x 4096 at 8 rows 8.8 against 14.2, 4096 x 25088 39.4 against 39.3.
+bool fc_fwd_supported(const GemmGeom& g) {
+    return is_fc(g) && g.M <= 16 && g.IC >= 8 && below_2g(16.0 * g.IC);
+}
+// The same for the data gradient, whose work-groups share the batch operand among 64 (or 32) columns: up to 32 rows, and
+// where the reduction is short (both kernels wait more than they stream) up to 128.  This kernel / the generic one in
+// us: 9216 columns x 4096 rows of Wt at 8 / 32 / 64 batch rows 15.2 / 19.4 / 26.9 and 21.9 / 23.4 / 26.0; 4096 x 4096
+// 10.7 / 15.5 / 22.1 and 14.3 / 17 / 19.3; 25088 x 4096 at 8 / 22 / 64 33.7 / 38.1 / 51.3 and 45.0 / 45.2 / 48.7;
+// 4096 x 1000 at 64 / 100 8.1 / 9.6 and 14.2 / 16.3.
+bool fc_dx_supported(const GemmGeom& g) {
+    return is_fc(g) && (g.M <= 32 || (g.M <= 128 && g.IC <= 1024)) && g.Ncols >= 64 && g.IC >= 8 &&
+           below_2g((double)g.IC * g.Ncols) && below_2g((double)g.M * g.IC);
+}
+
+// Where the output features alone would leave most CUs without work, the reduction is also divided over work-groups, as
+// long as each still streams 128 KB of Wt (below that the launch that adds the parts costs more than it saves).
+int fc_fwd_nsplit(const GemmGeom& g) {
+    const int groups = (g.Ncols + 15) / 16;
+    const double bytes = 32.0 * g.IC;
+    int n = kNumCU / groups;
+    if (n > (int)(bytes / (128 * 1024))) n = (int)(bytes / (128 * 1024));
+    return n < 1 ? 1 : n;
+}
+
+int launch_fc_fwd(const GemmGeom& g, int nsplit, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
+                  hipStream_t st) {
+    FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0};
+    a.steps_per_split = ((g.IC + 31) / 32 + nsplit - 1) / nsplit;
+    const dim3 grid((g.Ncols + 15) / 16, nsplit), block(64 * FW_WAVES);
+    if ((g.IC % 8) == 0) hipLaunchKernelGGL(fc_fwd_kernel<true>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(fc_fwd_kernel<false>, grid, block, 0, st, a);
+    return check_launch("fc_fwd");
+}
+
+namespace {
+template <int CPL, bool VEC8>
+int launch_dx(const FcArgs& a, hipStream_t st) {
+    const dim3 grid((a.in + 16 * CPL - 1) / (16 * CPL)), block(64 * DX_WAVES);
+    if (a.B <= 16) hipLaunchKernelGGL((fc_dx_kernel<1, CPL, VEC8>), grid, block, 0, st, a);
+    else if (a.B <= 32) hipLaunchKernelGGL((fc_dx_kernel<2, CPL, VEC8>), grid, block, 0, st, a);
+    else if (a.B <= 64) hipLaunchKernelGGL((fc_dx_kernel<4, CPL, VEC8>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fc_dx_kernel<8, 2, VEC8>), grid, block, 0, st, a);
+    return check_launch("fc_dx");
+}
+}  // namespace
+
+// Four columns per lane read whole 128-byte lines of a row.  Where that gives fewer than 96 work-groups (4096 columns at
+// 8 rows: 12.7 us), or the sums of more than 64 batch rows would not fit the registers, two columns per lane (10.7 us;
+// the other half of the line comes from the L2).  9216 columns: 15.2 us with four, 22.4 us with two.
+int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st) {
+    const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0};
+    const bool wide = g.Ncols >= 96 * 64 && g.M <= 64, vec8 = (g.IC % 8) == 0;
+    if (wide) return vec8 ? launch_dx<4, true>(a, st) : launch_dx<4, false>(a, st);
+    return vec8 ? launch_dx<2, true>(a, st) : launch_dx<2, false>(a, st);
+}
+
+}  // namespace wap

@@ -413,6 +413,15 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
         p.ws_bytes = 0;
         return p;
     }
+    if (g_force_fwd_cfg < 0 && (b_tr ? fc_dx_supported(g) : fc_fwd_supported(g))) {
+        p.cfg = b_tr ? 11 : 10;
+        p.nsplit = b_tr ? 1 : g_force_nsplit >= 1 ? g_force_nsplit : fc_fwd_nsplit(g);
+        const int steps = (g.IC + 31) / 32;
+        if (p.nsplit > steps) p.nsplit = steps;
+        p.nsplit = (steps + (steps + p.nsplit - 1) / p.nsplit - 1) / ((steps + p.nsplit - 1) / p.nsplit);  // none empty
+        p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * g.M * g.Ncols * sizeof(float) : 0;
+        return p;
+    }
     int mode = classify_mode(g, b_tr);
     int ktiles = (g.Kred + BK - 1) / BK;
     auto tiles = [&](int c) {
@@ -477,6 +486,14 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     }
     if (plan.cfg == 8) return launch_conv_c3_fwd(g, A, Bw, bias, relu, out, st);
     if (plan.cfg == 9) return launch_dgrad_thin(g, A, Bw, out, st);
+    if (plan.cfg == 10) {
+        int rc10 = launch_fc_fwd(g, plan.nsplit, A, Bw, bias, relu, plan.nsplit > 1 ? ws : (void*)out, st);
+        if (rc10 != WAP_OK || plan.nsplit == 1) return rc10;
+        if (ev_mid) (void)hipEventRecord(ev_mid, st);
+        return launch_reduce_bf16(reinterpret_cast<const float*>(ws), plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias,
+                                  relu, out, st);
+    }
+    if (plan.cfg == 11) return launch_fc_dx(g, A, Bw, relu_mask, out, st);
     KArgs ka;
     ka.A = A;
     ka.Bw = Bw;
@@ -568,7 +585,7 @@ int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
     return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g) : 0;
 }
 bool fwd_like_fuses_mask(const GemmGeom& g, const GemmPlan& plan) {
-    return (plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0;
+    return ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11;
 }
 // Label of the kernel instantiation a plan launches (matches the demangled kernel name).
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool) {
@@ -577,6 +594,8 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 7) return tile2d_kernel_name(g, unpool);
     if (plan.cfg == 8) return conv_c3_fwd_kernel_name(g);
     if (plan.cfg == 9) return "dgrad_thin_kernel";
+    if (plan.cfg == 10) return "fc_fwd_kernel";
+    if (plan.cfg == 11) return "fc_dx_kernel";
     static const char* names[5][2][3] = {
         {{"igemm_kernel<256,256,2,4,false,0>", "", ""}, {"igemm_kernel<256,256,2,4,true,0>", "", ""}},
         {{"igemm_kernel<128,128,2,2,false,0>", "igemm_kernel<128,128,2,2,false,1>", "igemm_kernel<128,128,2,2,false,2>"},

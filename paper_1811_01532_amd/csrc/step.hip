@@ -424,7 +424,14 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     for (int i = 2; i >= 0; --i) {
         std::string nm = lname(nconv + i);
         size_t elems = (size_t)B * fds[i].out_features;
-        if (kFcs[i].relu) {
+        // the data gradient of the layer above applies this layer's ReLU derivative where its kernel can
+        Op& above = p->ops.back();
+        if (kFcs[i].relu && !keep && above.kind == OP_FC_DX && fwd_like_fuses_mask(above.gg, above.gp)) {
+            above.has_mask = true;
+            above.t3 = fc_y[i];
+            above.name += "+relu_bwd";
+            above.bytes += 2.0 * elems;
+        } else if (kFcs[i].relu) {
             Op op;
             op.kind = OP_RELU_BWD; op.name = nm + ".relu_bwd";
             op.n = elems;

@@ -174,6 +174,15 @@ int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_
 bool dgrad_thin_supported(const GemmGeom& g);
 int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st);
 
+// fully-connected products with few rows as streams of the weights (fc.hip); geometries of geom_fc_fwd / geom_fc_dx
+bool fc_fwd_supported(const GemmGeom& g);
+bool fc_dx_supported(const GemmGeom& g);
+int fc_fwd_nsplit(const GemmGeom& g);
+// out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
+int launch_fc_fwd(const GemmGeom& g, int nsplit, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
+                  hipStream_t st);
+int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
+
 // weights-in-registers large-tile kernel (conv_wreg.hip)
 bool wreg_supported(const GemmGeom& g);
 inline size_t wreg_wt_bytes(const GemmGeom& g) { return (size_t)((g.Ncols + 31) / 32) * 32 * g.Kred * 2; }  // packed copy

@@ -56,3 +56,37 @@ def test_image_gradient_edges(orc, N, H, W, C, K, R, S, stride, pad):
     ref = orc.conv2d_bwd_data(orc.bf16_bits_to_f64(gb), orc.bf16_bits_to_f64(wb), (N, H, W, C), st, pd)
     e = gu.rel_err(gu.host_f64(dx[:N * H * W * C]).reshape(N, H, W, C), ref)
     assert e <= gu.TOL_BF16_OUT, e           # one bf16 rounding of an fp32 sum
+
+
+# fully-connected products as streams of the weights: one to eight blocks of 16 rows and one row over / under, features
+# that end inside a 16-row block, reductions shorter than one step of all wavefronts, longer, ragged (% 32, % 8, odd),
+# divided over work-groups (few features, long rows), two and four columns per lane, a last work-group moved back,
+# and the first shapes beyond the limits
+@pytest.mark.parametrize("B,n_in,n_out", [
+    (1, 8, 1), (16, 40, 17), (17, 512, 16), (32, 520, 33), (33, 4096, 500), (64, 4104, 125), (65, 1024, 130), (96, 4096, 500),
+    (128, 2048, 1000), (128, 2051, 1023), (8, 25088, 40), (50, 16392, 24), (64, 12288, 72), (3, 12301, 20), (129, 256, 40),
+    (5, 67, 9), (16, 64, 8), (16, 9, 7), (32, 6145, 1031), (33, 6144, 1032), (16, 16391, 50), (64, 65, 1024)])
+def test_fc_stream_edges(orc, B, n_in, n_out):
+    import paper_1811_01532_amd as wap
+    print(f"[case] fc stream {(B, n_in, n_out)}", flush=True)
+    xb, Wb = si.normal_bf16(si.rng(450, B + n_in), (B, n_in)), si.he_weight_bf16(si.rng(451, n_in + n_out), (n_out, n_in))
+    gb = si.normal_bf16(si.rng(452, B + n_out), (B, n_out))
+    bias = si.rng(453, n_out).standard_normal(n_out).astype(np.float32)
+    x64, W64, g64 = orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(Wb), orc.bf16_bits_to_f64(gb)
+    xd, Wd, gd = gu.dev_bf16(xb), gu.dev_bf16(Wb), gu.dev_bf16(gb)
+    for relu in (False, True):
+        d = wap.fc_desc(B, n_in, n_out, relu=relu)
+        ws = gu.workspace(max(wap.wap_fc_workspace_bytes(d, p) for p in (0, 1, 2)))
+        y = torch.full((B * n_out + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        wap.wap_fc_fwd(d, xd, Wd, torch.from_numpy(bias).cuda() if relu else None, y, ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(y[B * n_out:]).all()
+        ref = orc.fc_fwd(x64, W64, bias=bias.astype(np.float64) if relu else None, relu=relu)
+        e = gu.rel_err(gu.host_f64(y[:B * n_out]).reshape(B, n_out), ref)
+        assert e <= gu.TOL_BF16_OUT, e
+    dx = torch.full((B * n_in + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wap.wap_fc_bwd(d, xd, Wd, gd, dx, None, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(dx[B * n_in:]).all()
+    e = gu.rel_err(gu.host_f64(dx[:B * n_in]).reshape(B, n_in), orc.fc_bwd_data(g64, W64))
+    assert e <= gu.TOL_BF16_OUT, e
