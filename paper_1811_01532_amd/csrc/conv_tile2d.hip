@@ -48,6 +48,8 @@ struct TArgs {
     bf16_t* pool_y;      // optional: 2x2 / stride-2 max-pool of the output tile ...
     uint8_t* pool_am;    // ... and the position r*2+s of the first maximum of every window
     float* colsum;       // optional: [tiles_m][Ncols] column sums of this tile's stored (masked) rows, for a bias gradient
+    float* part;         // split reduction: fp32 partial sums [nsplit][M][Ncols], no epilogue here (flat tiles only)
+    int nsplit, slices_per_split;  // 32-channel slices of the reduction that one work-group walks
     GemmGeom g;
     int tiles_x, tiles_y, tiles_img, tiles_m, tiles_n;
     int RWB, buf_bytes;  // LDS byte stride of a patch row, bytes of one patch buffer
@@ -118,7 +120,12 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     const int pg = wave % PG, cg = wave / PG;  // pixel group, channel group
     constexpr int BN = 32 * FN * CG;
 
-    int logical = xcd_remap(blockIdx.x, a.tiles_m * a.tiles_n);
+    int logical = xcd_remap(blockIdx.x, a.tiles_m * a.tiles_n * (FLAT ? a.nsplit : 1));
+    int split = 0;
+    if (FLAT) {
+        split = logical / (a.tiles_m * a.tiles_n);  // slowest: an XCD's work-groups share the weights of few splits
+        logical -= split * (a.tiles_m * a.tiles_n);
+    }
     const int tn = logical % a.tiles_n;
     const int tm = logical / a.tiles_n;
     const int img = (int)fdiv((uint32_t)tm, a.dTimg);
@@ -148,7 +155,8 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     const int r_lo = FLAT ? rflat(m0) : 0;
     const int patch_len = FLAT ? rflat(m_last) + (g.R - 1) * a.RW + (g.S - 1) + 1 - r_lo : a.patch_len;
     const int RS = g.R * g.S;
-    const int ncs = g.IC / BK;
+    const int cs0 = FLAT ? split * a.slices_per_split : 0;  // slices [cs0, ncs) of this work-group (never empty)
+    const int ncs = FLAT && cs0 + a.slices_per_split < g.IC / BK ? cs0 + a.slices_per_split : g.IC / BK;
 
     const __amdgpu_buffer_rsrc_t rsrcA =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.A), 0, (int)a.a_bytes, 0x00020000);
@@ -316,9 +324,9 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     //   otherwise: a tap loop with two sets, the new one copied over the current one at the end of every tap.
     constexpr int NSET = T9 ? 3 : 2;
     bf16x8 w[NSET][2][FN];
-    issue_patch(0);
+    issue_patch(cs0);
 #pragma unroll
-    for (int u = 0; u + 1 < NSET; ++u) load_w(0, u, w[u]);
+    for (int u = 0; u + 1 < NSET; ++u) load_w(cs0, u, w[u]);
     store_patch(smem);
     __syncthreads();
     // Fragment reads run one reduction step ahead of the MFMAs that consume them, in place: right after the MFMA that
@@ -353,9 +361,9 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
         }
     };
 
-    for (int cs = 0; cs < ncs; ++cs) {
-        const unsigned char* cur = smem + (cs & 1) * a.buf_bytes;
-        unsigned char* nxt = smem + ((cs + 1) & 1) * a.buf_bytes;
+    for (int cs = cs0; cs < ncs; ++cs) {
+        const unsigned char* cur = smem + ((cs - cs0) & 1) * a.buf_bytes;
+        unsigned char* nxt = smem + ((cs - cs0 + 1) & 1) * a.buf_bytes;
         const int csn = cs + 1 < ncs ? cs + 1 : cs;  // the next slice, clamped
         __builtin_amdgcn_s_setprio(1);
         if constexpr (T9) {
@@ -440,6 +448,23 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
             tap_body(RS - 1, std::true_type{});
         }
         __builtin_amdgcn_s_setprio(0);
+    }
+
+    // ---- split reduction: the accumulators as they lie, four consecutive channels of a pixel per store ----
+    if (FLAT && a.part) {
+        float* const po = a.part + (size_t)split * g.M * g.Ncols;
+#pragma unroll
+        for (int j = 0; j < FM; ++j) {
+            const int m = m0 + (pg * FM + j) * 32 + (lane & 31);
+            if (m > m_last) continue;
+#pragma unroll
+            for (int i = 0; i < FN; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(po + (size_t)m * g.Ncols + n0 + cg * 32 * FN + i * 32 + q * 8 + (lane >> 5) * 4) =
+                        make_float4(acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]);
+        }
+        return;
     }
 
     // ---- epilogue: bias / ReLU / bf16, transposed through LDS (the patch buffers are dead) so that every global
@@ -565,7 +590,7 @@ int launch_tile2d_w(const TArgs& ta, size_t smem, hipStream_t st) {
         if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
         attr_done = true;
     }
-    hipLaunchKernelGGL(kfn, dim3(ta.tiles_m * ta.tiles_n), dim3(NT), smem, st, ta);
+    hipLaunchKernelGGL(kfn, dim3(ta.tiles_m * ta.tiles_n * ta.nsplit), dim3(NT), smem, st, ta);
     return check_launch("conv_tile2d");
 }
 // straight-line 3x3 slices with the three-set weight ring for one-block wavefronts, else the tap loop
@@ -675,8 +700,18 @@ bool flat64_wins_small_batch(const GemmGeom& g) {
     const double t_flat = floor_s > flops / 900e12 ? floor_s : flops / 900e12;
     return t_flat < 0.85 * t_generic;
 }
+// The flat tilings a split reduction runs on: 64 or 224 pixels x 128 channels, 192 pixels x 64 channels.
+TileCfg split_cfg(const GemmGeom& g, int tile) {
+    TileCfg c = {1, 0, 0, tile == kTileSplit192 ? 3 : 2, 0, 0, 0, tile == kTileSplit224 ? 7 : 2};
+    const bool v3 = c.variant == 3;
+    if ((g.Ncols % (v3 ? 64 : 128)) != 0 || max_flat_patch(g, tile_pixels(c)) > (v3 ? MAX_PATCH_FLAT64 : MAX_PATCH_FLAT) ||
+        !lds_layout(g, &c))
+        c.fn = 0;
+    return c;
+}
 // Tile shape for this geometry (width must divide the map, patch must fit), fn = 0 if none.
-TileCfg tile_cfg(const GemmGeom& g) {
+TileCfg tile_cfg(const GemmGeom& g, int tile = 0) {
+    if (tile) return split_cfg(g, tile);
     TileCfg none = {0, 0, 0, 0, 0, 0, 0, 0};
     TileCfg c = none;
     if ((g.Ncols % 64) != 0) return none;
@@ -726,13 +761,13 @@ TileCfg tile_cfg(const GemmGeom& g) {
 }  // namespace
 
 // 0 = not applicable, otherwise FN (32-channel blocks per wavefront)
-int tile2d_supported(const GemmGeom& g) {
+int tile2d_supported(const GemmGeom& g, int tile) {
     if ((g.IC % BK) != 0 || g.div_h != 1 || g.div_w != 1 || g.mul_h != 1 || g.mul_w != 1) return 0;
     if (g.R * g.S < 2) return 0;
     long a_elems = (long)(g.M / ((long)g.OH * g.OW)) * g.IH * g.IW * g.IC;
     if (a_elems * 2 >= (1L << 31)) return 0;
-    if (tile64_width(g)) return 1;  // 64 output channels on a map that 256-pixel tiles divide: conv_tile64.hip
-    return tile_cfg(g).fn;
+    if (!tile && tile64_width(g)) return 1;  // 64 output channels on a map that 256-pixel tiles divide: conv_tile64.hip
+    return tile_cfg(g, tile).fn;
 }
 
 // Shapes on which this kernel measured faster than conv_patch.hip: thin outputs on 256-pixel 2-D tiles, and the
@@ -756,9 +791,34 @@ bool tile2d_preferred(const GemmGeom& g) {
     return wgs >= kNumCU * 3 / 4;
 }
 
-const char* tile2d_kernel_name(const GemmGeom& g, bool unpool) {
-    if (tile64_width(g)) return tile64_kernel_name(g, unpool);
-    const TileCfg c = tile_cfg(g);
+// How to divide the reduction of a layer too small to fill the chip: number of splits (1: don't) and the flat tiling.
+// `generic`: the alternative is the tap-by-tap kernel, which splits its reduction as well but gathers every activation
+// once per tap (7 to 12 us slower at every size measured, e.g. 512 -> 512 channels on 14 x 14 at minibatch 8 32.4 -> 22.2,
+// 256 -> 256 on 13 x 13 at 8 19.0 -> 13.4, 384 -> 256 at 1 15.6 -> 10.2 us).  Otherwise it is an unsplit tile of this
+// kernel: a slice of a 3x3 filter takes a work-group about 2.2 us, the partial sums and their reduction about 9, so the
+// split has to save 10 (384 -> 192 on 13 x 13 at 32 24.5 -> 22.7; 64 outputs of a 5x5 filter at 16 / 32 / 64 47 / 49 /
+// 53 -> 27 / 36 / 44 us; 128 -> 64 on 56 x 56, four slices, would lose: 12.0 -> 15.7).
+// Work-groups: just under one per CU for 3x3 filters (more splits only add partial sums: 384 -> 256 at 8 176 / 264
+// work-groups 14.8 / 15.9 us), two per CU for larger filters, whose work per partial sum is higher.
+int tile2d_split(const GemmGeom& g, bool generic, int* tile) {
+    const int slices = g.IC / BK;
+    if ((g.IC % BK) != 0 || slices < 2 || g.R * g.S < 2 || (g.Ncols % 64) != 0) return 1;
+    *tile = (g.Ncols % 128) == 0 ? kTileSplit64 : kTileSplit192;
+    const long tiles = *tile == kTileSplit64 ? (long)((g.M + 63) / 64) * (g.Ncols / 128) : (long)((g.M + 191) / 192) * (g.Ncols / 64);
+    const long target = g.R * g.S > 9 ? 2 * kNumCU : kNumCU * 27 / 32;
+    long s = target / tiles;
+    if (generic && s < 2 && tiles <= kNumCU * 3 / 4) s = 2;
+    if (s > slices) s = slices;
+    if (s < 2) return 1;
+    const long per = (slices + s - 1) / s;
+    s = (slices + per - 1) / per;  // none empty
+    if (!generic && slices * (g.R * g.S / 9.0) * 2.2 * (1.0 - 1.0 / s) < 10.0) return 1;
+    return tile2d_supported(g, *tile) ? (int)s : 1;
+}
+
+const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
+    if (!tile && tile64_width(g)) return tile64_kernel_name(g, unpool);
+    const TileCfg c = tile_cfg(g, tile);
     const int u = unpool ? 1 : 0, t9 = (g.R == 3 && g.S == 3) ? 1 : 0;
     static const char* n1[2][2] = {{"conv_tile2d_kernel<1,28,7,1,false,false>", "conv_tile2d_kernel<1,28,7,1,false,true>"},
                                    {"conv_tile2d_kernel<1,28,7,1,true,false>", "conv_tile2d_kernel<1,28,7,1,true,true>"}};
@@ -780,7 +840,8 @@ const char* tile2d_kernel_name(const GemmGeom& g, bool unpool) {
 }
 
 // can the patch loader take the input operand pooled (2x2 / stride 2, whole windows) plus the argmax?
-bool tile2d_fuses_unpool(const GemmGeom& g) {
+bool tile2d_fuses_unpool(const GemmGeom& g, int tile) {
+    if (tile) return (g.IH % 2) == 0 && (g.IW % 2) == 0;
     if (tile64_width(g)) return tile64_fuses_unpool(g);
     if (!tile2d_supported(g) || (g.IH % 2) != 0 || (g.IW % 2) != 0) return false;
     const TileCfg c = tile_cfg(g);
@@ -808,22 +869,27 @@ bool tile2d_fuses_pool(const GemmGeom& g) {
 
 int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out,
                   hipStream_t st, const bf16_t* mask, bf16_t* pool_y, uint8_t* pool_am, const uint8_t* unpool_am,
-                  float* colsum) {
+                  float* colsum, int tile, int nsplit, float* part) {
     if (colsum && pool_y) return set_error(WAP_EINVAL, "internal: column sums and the fused pool share the staging area");
-    if (tile64_width(g)) return launch_tile64(g, A, Wp, bias, relu, out, st, mask, pool_y, pool_am, unpool_am, colsum);
+    if (!tile && tile64_width(g)) return launch_tile64(g, A, Wp, bias, relu, out, st, mask, pool_y, pool_am, unpool_am, colsum);
     TArgs ta = {};
     ta.colsum = colsum;
     ta.mask = mask;
-    if (unpool_am && !tile2d_fuses_unpool(g))
+    if (unpool_am && !tile2d_fuses_unpool(g, tile))
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this shape");
     ta.up_am = unpool_am;
     if ((pool_y || pool_am) && !(pool_y && pool_am && tile2d_fuses_pool(g)))
         return set_error(WAP_EINVAL, "internal: fused pooling not available for this shape");
-    if (!out && !pool_y) return set_error(WAP_EINVAL, "internal: no output");
+    if (!out && !pool_y && !part) return set_error(WAP_EINVAL, "internal: no output");
+    if ((tile != 0) != (part != nullptr)) return set_error(WAP_EINVAL, "internal: split tiles write partial sums, others do not");
     ta.pool_y = pool_y;
     ta.pool_am = pool_am;
-    if (!tile2d_supported(g)) return set_error(WAP_EINVAL, "internal: 2-D tile kernel not applicable");
-    const TileCfg c = tile_cfg(g);
+    if (!tile2d_supported(g, tile)) return set_error(WAP_EINVAL, "internal: 2-D tile kernel not applicable");
+    const TileCfg c = tile_cfg(g, tile);
+    ta.part = part;
+    ta.nsplit = part ? nsplit : 1;
+    ta.slices_per_split = (g.IC / BK + ta.nsplit - 1) / ta.nsplit;
+    if ((long)(ta.nsplit - 1) * ta.slices_per_split >= g.IC / BK) return set_error(WAP_EINVAL, "internal: empty reduction split");
     ta.A = A;
     ta.Wp = reinterpret_cast<const bf16_t*>(Wp);
     ta.bias = bias;

@@ -24,39 +24,89 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     return __builtin_bit_cast(unsigned short, b);
 }
 
-// ---- out[i] = bf16(act(bias[i % ncols] + sum_s part[s][i])) , summed in split order ----
-__global__ void reduce_bf16_kernel(const float* __restrict__ part, int nsplit, size_t elems, int ncols,
-                                   const float* __restrict__ bias, int relu, bf16_t* __restrict__ out) {
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    if ((ncols & 3) == 0) {
-        size_t n4 = elems / 4;
-        for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-            float4 s = reinterpret_cast<const float4*>(part)[i];
-            for (int k = 1; k < nsplit; ++k) {
-                float4 t = reinterpret_cast<const float4*>(part + (size_t)k * elems)[i];
+// ---- out[r][c] = bf16(act(bias[c] + sum_k part[k][r][c])), summed in split order; with `mask`, zeroed where the mask is
+// not positive (ReLU derivative of the layer below); with `colsum`, also the column sums of what is stored, one partial
+// row per work-group row range (the bias gradient of that layer).  Bound by the launch and the latency of the loads: the
+// partial sums of a layer small enough to be split are a few MB that the caches still hold.  A thread owns 16 bytes of a
+// row, `vpb` (a power of two) threads lie side by side, four splits are in flight.  The separate mask and column-sum
+// passes that this replaces took 5 us each at 1568 x 512. ----
+__global__ __launch_bounds__(256) void reduce_bf16_kernel(const float* __restrict__ part, int nsplit, int rows, int ncols,
+                                                          const float* __restrict__ bias, int relu,
+                                                          const bf16_t* __restrict__ mask, bf16_t* __restrict__ out,
+                                                          float* __restrict__ colsum, int vpb, int colblocks,
+                                                          int rows_per_block) {
+    __shared__ float4 red[256];
+    const int rb = blockIdx.x / colblocks, cb = blockIdx.x - rb * colblocks;
+    const int vec = threadIdx.x & (vpb - 1), rsub = threadIdx.x / vpb, rp = 256 / vpb;
+    const int c = (cb * vpb + vec) * 4;
+    const size_t elems = (size_t)rows * ncols;
+    float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < ncols) {
+        float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (bias) bv = make_float4(bias[c], bias[c + 1], bias[c + 2], bias[c + 3]);
+        const int r1 = (rb + 1) * rows_per_block < rows ? (rb + 1) * rows_per_block : rows;
+        for (int r = rb * rows_per_block + rsub; r < r1; r += rp) {
+            const size_t o = (size_t)r * ncols + c;
+            const float* p = part + o;
+            uint2 mk = make_uint2(0u, 0u);
+            if (mask) mk = *reinterpret_cast<const uint2*>(mask + o);
+            float4 s = *reinterpret_cast<const float4*>(p);
+            int k = 1;
+            for (; k + 3 < nsplit; k += 4) {
+                const float4 t0 = *reinterpret_cast<const float4*>(p + (size_t)k * elems);
+                const float4 t1 = *reinterpret_cast<const float4*>(p + (size_t)(k + 1) * elems);
+                const float4 t2 = *reinterpret_cast<const float4*>(p + (size_t)(k + 2) * elems);
+                const float4 t3 = *reinterpret_cast<const float4*>(p + (size_t)(k + 3) * elems);
+                s.x += t0.x; s.y += t0.y; s.z += t0.z; s.w += t0.w;
+                s.x += t1.x; s.y += t1.y; s.z += t1.z; s.w += t1.w;
+                s.x += t2.x; s.y += t2.y; s.z += t2.z; s.w += t2.w;
+                s.x += t3.x; s.y += t3.y; s.z += t3.z; s.w += t3.w;
+            }
+            for (; k < nsplit; ++k) {
+                const float4 t = *reinterpret_cast<const float4*>(p + (size_t)k * elems);
                 s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
             }
-            if (bias) {
-                int c = (int)((i * 4) % (size_t)ncols);
-                s.x += bias[c]; s.y += bias[c + 1]; s.z += bias[c + 2]; s.w += bias[c + 3];
-            }
+            if (bias) { s.x += bv.x; s.y += bv.y; s.z += bv.z; s.w += bv.w; }
             if (relu) {
                 s.x = s.x > 0.f ? s.x : 0.f; s.y = s.y > 0.f ? s.y : 0.f;
                 s.z = s.z > 0.f ? s.z : 0.f; s.w = s.w > 0.f ? s.w : 0.f;
             }
-            uint2 pk;
-            pk.x = (unsigned)f2bf(s.x) | ((unsigned)f2bf(s.y) << 16);
-            pk.y = (unsigned)f2bf(s.z) | ((unsigned)f2bf(s.w) << 16);
-            reinterpret_cast<uint2*>(out)[i] = pk;
+            unsigned short h0 = f2bf(s.x), h1 = f2bf(s.y), h2 = f2bf(s.z), h3 = f2bf(s.w);
+            if (mask) {
+                h0 = __uint_as_float(mk.x << 16) > 0.f ? h0 : 0;
+                h1 = __uint_as_float(mk.x & 0xffff0000u) > 0.f ? h1 : 0;
+                h2 = __uint_as_float(mk.y << 16) > 0.f ? h2 : 0;
+                h3 = __uint_as_float(mk.y & 0xffff0000u) > 0.f ? h3 : 0;
+            }
+            *reinterpret_cast<uint2*>(out + o) = make_uint2((unsigned)h0 | ((unsigned)h1 << 16), (unsigned)h2 | ((unsigned)h3 << 16));
+            cs.x += bf2f(h0); cs.y += bf2f(h1); cs.z += bf2f(h2); cs.w += bf2f(h3);
         }
-    } else {
-        for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < elems; i += stride) {
-            float s = part[i];
-            for (int k = 1; k < nsplit; ++k) s += part[(size_t)k * elems + i];
-            if (bias) s += bias[i % (size_t)ncols];
-            if (relu) s = s > 0.f ? s : 0.f;
-            out[i] = f2bf(s);
+    }
+    if (colsum) {  // the row slots of a column as a tree through LDS: order fixed by the shape
+        red[threadIdx.x] = cs;
+        __syncthreads();
+        for (int o = rp / 2; o > 0; o >>= 1) {
+            if (rsub < o) {
+                const float4 t = red[threadIdx.x + o * vpb];
+                cs.x += t.x; cs.y += t.y; cs.z += t.z; cs.w += t.w;
+                red[threadIdx.x] = cs;
+            }
+            __syncthreads();
         }
+        if (rsub == 0 && c < ncols) *reinterpret_cast<float4*>(colsum + (size_t)rb * ncols + c) = cs;
+    }
+}
+
+// the same for row lengths that are no multiple of 4, element by element
+__global__ void reduce_bf16_scalar_kernel(const float* __restrict__ part, int nsplit, size_t elems, int ncols,
+                                          const float* __restrict__ bias, int relu, bf16_t* __restrict__ out) {
+    size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < elems; i += stride) {
+        float s = part[i];
+        for (int k = 1; k < nsplit; ++k) s += part[(size_t)k * elems + i];
+        if (bias) s += bias[i % (size_t)ncols];
+        if (relu) s = s > 0.f ? s : 0.f;
+        out[i] = f2bf(s);
     }
 }
 
@@ -440,10 +490,37 @@ __global__ void fill_kernel(bf16_t* p, size_t n, uint32_t seed) {
 
 }  // namespace
 
+// Threads side by side in a row: the largest power of two up to 64 that divides the row into whole vectors, unless that
+// falls below 16 (then the smallest that covers the row, some threads of the last column block idle).
+static int reduce_vpb(int ncols) {
+    const int cv = ncols / 4;
+    int vpb = 64;
+    while (vpb > 16 && cv % vpb != 0) vpb /= 2;
+    if (cv % vpb != 0 || cv < 16) {
+        vpb = 1;
+        while (vpb < cv && vpb < 64) vpb *= 2;
+    }
+    return vpb;
+}
+// rows of one work-group: one per thread, four where column sums are wanted (fewer partial rows to add up later)
+static int reduce_rows_per_block(int ncols, bool colsum) { return 256 / reduce_vpb(ncols) * (colsum ? 4 : 1); }
+int reduce_bf16_colsum_rows(int rows, int ncols) {
+    const int rpb = reduce_rows_per_block(ncols, true);
+    return (ncols & 3) == 0 ? (rows + rpb - 1) / rpb : 0;
+}
+
 int launch_reduce_bf16(const float* part, int nsplit, size_t elems, int ncols, const float* bias,
-                       bool relu, bf16_t* out, hipStream_t st) {
-    hipLaunchKernelGGL(reduce_bf16_kernel, dim3(grid_for(elems / 4 + 1)), dim3(kThreads), 0, st, part,
-                       nsplit, elems, ncols, bias, relu ? 1 : 0, out);
+                       bool relu, bf16_t* out, hipStream_t st, const bf16_t* mask, float* colsum) {
+    if ((ncols & 3) != 0) {
+        if (mask || colsum) return set_error(WAP_EINVAL, "internal: split reduction with a mask needs rows of whole 16-byte vectors");
+        hipLaunchKernelGGL(reduce_bf16_scalar_kernel, dim3(grid_for(elems)), dim3(kThreads), 0, st, part, nsplit, elems, ncols,
+                           bias, relu ? 1 : 0, out);
+        return check_launch("reduce_bf16_scalar");
+    }
+    const int rows = (int)(elems / ncols), vpb = reduce_vpb(ncols), rpb = reduce_rows_per_block(ncols, colsum != nullptr);
+    const int colblocks = (ncols / 4 + vpb - 1) / vpb;
+    hipLaunchKernelGGL(reduce_bf16_kernel, dim3((unsigned)((rows + rpb - 1) / rpb) * colblocks), dim3(256), 0, st, part, nsplit, rows,
+                       ncols, bias, relu ? 1 : 0, mask, out, colsum, vpb, colblocks, rpb);
     return check_launch("reduce_bf16");
 }
 

@@ -461,6 +461,24 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
     if (g_force_fwd_cfg < 0 && tile2d_preferred(g)) cfg = 7;
     if (cfg == 7 && !tile2d_supported(g)) cfg = 1;
     if (cfg == 6 || cfg == 7) nsplit = 1;
+    // Reductions split over channel slices of the patch kernel.  A forward layer that pools in its epilogue stays whole,
+    // and one whose partial sums would take it past the static scratch keeps the plan it had.
+    if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 6 || cfg == 7)) {
+        int tile = 0;
+        const bool pools = !b_tr && cfg == 7 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
+        const int sp = pools ? 1 : tile2d_split(g, cfg < 6, &tile);
+        if (sp > 1 && (b_tr || (size_t)sp * g.M * g.Ncols * sizeof(float) + wreg_wt_bytes(g) <= WAP_STATIC_SCRATCH_BYTES)) {
+            cfg = 7;
+            p.tile = tile;
+            nsplit = sp;
+        }
+    } else if (g_force_fwd_cfg >= 12 && g_force_fwd_cfg <= 14 && g_force_nsplit >= 2 && g_force_nsplit <= g.IC / 32 &&
+               tile2d_supported(g, g_force_fwd_cfg - 11)) {
+        cfg = 7;
+        p.tile = g_force_fwd_cfg - 11;
+        const int slices = g.IC / 32, per = (slices + g_force_nsplit - 1) / g_force_nsplit;
+        nsplit = (slices + per - 1) / per;
+    }
     p.cfg = cfg;
     p.nsplit = nsplit;
     p.ws_bytes = nsplit > 1 ? (size_t)nsplit * g.M * g.Ncols * sizeof(float) : 0;
@@ -516,6 +534,14 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
             wp = ws;
         }
         if (ev_packed) (void)hipEventRecord(ev_packed, st);
+        if (plan.cfg == 7 && plan.nsplit > 1) {
+            float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + wreg_wt_bytes(g));
+            int rc7 = launch_tile2d(g, A, wp, nullptr, false, nullptr, st, nullptr, nullptr, nullptr, unpool_am, nullptr, plan.tile,
+                                    plan.nsplit, part);
+            if (rc7 != WAP_OK) return rc7;
+            if (ev_mid) (void)hipEventRecord(ev_mid, st);
+            return launch_reduce_bf16(part, plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st, relu_mask, colsum);
+        }
         return plan.cfg == 6 ? launch_patch(g, A, wp, bias, relu, out, st, relu_mask)
                              : launch_tile2d(g, A, wp, bias, relu, out, st, relu_mask, pool_y, pool_am, unpool_am, colsum);
     }
@@ -532,7 +558,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
         if (ev_mid) (void)hipEventRecord(ev_mid, st);
         if (ka.partial)
             return launch_reduce_bf16(reinterpret_cast<const float*>(part), plan.nsplit, (size_t)g.M * g.Ncols,
-                                      g.Ncols, bias, relu, out, st);
+                                      g.Ncols, bias, relu, out, st, relu_mask, colsum);
         return WAP_OK;
     }
     size_t smem = smem_bytes(c, b_tr);
@@ -569,7 +595,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     if (ev_mid) (void)hipEventRecord(ev_mid, st);
     if (ka.partial)
         return launch_reduce_bf16(reinterpret_cast<const float*>(ws), plan.nsplit,
-                                  (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st);
+                                  (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st, relu_mask, colsum);
     return WAP_OK;
 }
 
@@ -578,20 +604,22 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
 namespace wap {
 bool fwd_like_packs_weights(const GemmPlan& plan) { return plan.cfg == 5 || plan.cfg == 6 || plan.cfg == 7; }
 bool fwd_like_fuses_pool(const GemmGeom& g, const GemmPlan& plan) {
-    return plan.cfg == 7 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
+    return plan.cfg == 7 && plan.nsplit == 1 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
 }
-bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) { return plan.cfg == 7 && tile2d_fuses_unpool(g); }
+bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) { return plan.cfg == 7 && tile2d_fuses_unpool(g, plan.tile); }
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
+    if (plan.nsplit > 1 && plan.cfg != 10) return reduce_bf16_colsum_rows(g.M, g.Ncols);
     return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g) : 0;
 }
 bool fwd_like_fuses_mask(const GemmGeom& g, const GemmPlan& plan) {
+    if (plan.nsplit > 1 && plan.cfg != 10) return (g.Ncols % 4) == 0;  // by the kernel that adds up the splits
     return ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11;
 }
 // Label of the kernel instantiation a plan launches (matches the demangled kernel name).
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool) {
     if (plan.cfg == 5) return "conv_wreg_kernel";
     if (plan.cfg == 6) return patch_kernel_name(g);
-    if (plan.cfg == 7) return tile2d_kernel_name(g, unpool);
+    if (plan.cfg == 7) return tile2d_kernel_name(g, unpool, plan.tile);
     if (plan.cfg == 8) return conv_c3_fwd_kernel_name(g);
     if (plan.cfg == 9) return "dgrad_thin_kernel";
     if (plan.cfg == 10) return "fc_fwd_kernel";

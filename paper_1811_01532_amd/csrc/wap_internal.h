@@ -92,7 +92,9 @@ struct GemmPlan {
     int cfg;     // tile configuration id
     int nsplit;  // reduction splits (1 = direct epilogue)
     size_t ws_bytes;
+    int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own
 };
+constexpr int kTileSplit64 = 1, kTileSplit224 = 2, kTileSplit192 = 3;
 
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred
@@ -219,23 +221,27 @@ int launch_tile64(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
 
 // stride-1 convolution with double-buffered 32-channel patch slices: 2-D, strip and flat tiles (conv_tile2d.hip;
 // it hands the shapes of conv_tile64.hip on to that kernel)
-int tile2d_supported(const GemmGeom& g);
+int tile2d_supported(const GemmGeom& g, int tile = 0);
 bool tile2d_preferred(const GemmGeom& g);
-const char* tile2d_kernel_name(const GemmGeom& g, bool unpool);
+int tile2d_split(const GemmGeom& g, bool generic, int* tile);
+const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile = 0);
 int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out,
                   hipStream_t st, const bf16_t* mask = nullptr, bf16_t* pool_y = nullptr, uint8_t* pool_am = nullptr,
                   const uint8_t* unpool_am = nullptr,
-                  float* colsum = nullptr);  // [tile2d_colsum_rows][Ncols] column sums of the stored (masked) output
+                  float* colsum = nullptr,  // [tile2d_colsum_rows][Ncols] column sums of the stored (masked) output
+                  int tile = 0, int nsplit = 1, float* part = nullptr);  // split reduction: partial sums only
 int tile2d_colsum_rows(const GemmGeom& g);
 bool tile2d_fuses_pool(const GemmGeom& g);
-bool tile2d_fuses_unpool(const GemmGeom& g);
+bool tile2d_fuses_unpool(const GemmGeom& g, int tile = 0);
 
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool = false);
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan);
 
 // split-reduction epilogues (fixed summation order)
+// mask / colsum (ncols % 4 == 0): as in launch_fwd_like, reduce_bf16_colsum_rows() partial rows of column sums
 int launch_reduce_bf16(const float* part, int nsplit, size_t elems, int ncols, const float* bias,
-                       bool relu, bf16_t* out, hipStream_t st);
+                       bool relu, bf16_t* out, hipStream_t st, const bf16_t* mask = nullptr, float* colsum = nullptr);
+int reduce_bf16_colsum_rows(int rows, int ncols);
 // with `sgd`, the sums update the parameters (see SgdFuse) instead of being stored; `out` is then unused
 int launch_reduce_f32(const float* part, int nsplit, size_t elems, float* out, hipStream_t st,
                       const SgdFuse* sgd = nullptr);

@@ -91,6 +91,18 @@ CASES = [
     ("c3_strided_wgrad_11x11_s4_k64", (5, 64, 72, 3, 64, 11, 11, 4, 2), (-1, -1, -1)),
     ("c3_strided_wgrad_7x7_s4_k32", (6, 50, 96, 3, 32, 7, 7, 4, 2), (-1, -1, -1)),
     ("c3_strided_wgrad_5x9_rect_stride_2_4_pad_1_0", (8, 30, 64, 3, 64, 5, 9, (2, 4), (1, 0)), (-1, -1, -1)),
+    # patch kernel with the reduction divided over channel slices: chosen from the shape, uneven splits, a layer smaller
+    # than one tile, straddled images, each flat tiling, pooled dy; and the reduction's mask / ragged columns behind the
+    # generic kernel (36 and 72 channels in vectors, 10 element by element)
+    ("tile2d_split_auto_w13", (4, 13, 13, 384, 256, 3, 3, 1, 1), (-1, -1, -1)),
+    ("tile2d_split_64x128_uneven", (2, 13, 13, 256, 128, 3, 3, 1, 1), (12, -1, 3)),
+    ("tile2d_split_64x128_one_slice_each_unpool", (3, 14, 14, 128, 128, 3, 3, 1, 1), (12, -1, 4)),
+    ("tile2d_split_224x128", (2, 20, 20, 128, 256, 3, 3, 1, 1), (13, -1, 2)),
+    ("tile2d_split_192x64_5x5", (1, 27, 27, 64, 192, 5, 5, 1, 2), (14, -1, 2)),
+    ("tile2d_split_192x64_under_one_tile", (1, 7, 9, 128, 64, 3, 3, 1, 1), (14, -1, 3)),
+    ("split_mask_c36", (2, 9, 9, 36, 64, 3, 3, 1, 1), (1, -1, 3)),
+    ("split_mask_c72", (1, 21, 20, 72, 64, 3, 3, 1, 1), (1, -1, 6)),
+    ("split_mask_c10", (2, 9, 9, 10, 64, 3, 3, 1, 1), (1, -1, 3)),
 ]
 
 
