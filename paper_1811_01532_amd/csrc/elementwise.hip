@@ -268,114 +268,214 @@ __global__ void relu_bwd_kernel(const bf16_t* __restrict__ dy, const bf16_t* __r
         dx[i] = (bf2f(y[i]) > 0.f) ? dy[i] : (bf16_t)0;
 }
 
-// ---- max-pool forward: VEC channels per thread ----
-template <int VEC>
-__global__ void maxpool_fwd_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
-                                   uint8_t* __restrict__ am, int N, int H, int W, int C, int P, int Q,
-                                   int win, int st) {
-    const int CV = C / VEC;
-    size_t total = (size_t)N * P * Q * CV;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        int cv = (int)(i % CV);
-        size_t t = i / CV;
-        int q = (int)(t % Q); t /= Q;
-        int p = (int)(t % P);
-        int n = (int)(t / P);
-        float best[VEC];
-        unsigned short bestbits[VEC];
-        uint8_t bi[VEC];
+// ---- max-pool forward: VEC channels of one window per thread, the window's loads issued together.  Bound by the input
+// stream; index arithmetic in 64 bits (a software division per coordinate) held it to 2.2 TB/s: 100 x 55 x 55 x 64,
+// window 3, 23.8 -> 12.4 us. ----
+struct PoolArgs {
+    int H, W, C, P, Q, st;
+    uint32_t items;        // threads' work items
+    FastDiv dCV, dX, dY;   // item -> channel vector, x, y, image: divisions by vectors per pixel, items per row, rows
+};
+
+template <int VEC, int WIN>
+__global__ void maxpool_fwd_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, uint8_t* __restrict__ am,
+                                   const PoolArgs a) {
+    const uint32_t CV = a.C / VEC;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
+        uint32_t t = fdiv(i, a.dCV);
+        const uint32_t cv = i - t * CV;
+        const uint32_t t2 = fdiv(t, a.dX);
+        const int q = (int)(t - t2 * a.Q);
+        const uint32_t n = fdiv(t2, a.dY);
+        const int p = (int)(t2 - n * a.P);
+        const bf16_t* src = x + (((size_t)n * a.H + (size_t)p * a.st) * a.W + (size_t)q * a.st) * a.C + (size_t)cv * VEC;
+        u32x4 v8[WIN * WIN];
+        unsigned short v1[WIN * WIN];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { best[e] = 0.f; bestbits[e] = 0; bi[e] = 255; }
-        for (int r = 0; r < win; ++r)
-            for (int s = 0; s < win; ++s) {
-                const bf16_t* src = x + (((size_t)n * H + p * st + r) * W + q * st + s) * C + (size_t)cv * VEC;
-                unsigned short v[VEC];
-                if (VEC == 8) {
-                    uint4 u = *reinterpret_cast<const uint4*>(src);
-                    v[0] = u.x & 0xffff; v[1] = u.x >> 16; v[2] = u.y & 0xffff; v[3] = u.y >> 16;
-                    v[4] = u.z & 0xffff; v[5] = u.z >> 16; v[6] = u.w & 0xffff; v[7] = u.w >> 16;
-                } else {
-                    v[0] = src[0];
-                }
+        for (int k = 0; k < WIN * WIN; ++k) {
+            const bf16_t* s = src + ((size_t)(k / WIN) * a.W + k % WIN) * a.C;
+            if (VEC == 8) v8[k] = *reinterpret_cast<const u32x4*>(s);
+            else v1[k] = *s;
+        }
+        unsigned best[VEC];  // as fp32 bits
+        unsigned bi[VEC];
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    float f = bf2f(v[e]);
-                    if (bi[e] == 255 || f > best[e]) { best[e] = f; bestbits[e] = v[e]; bi[e] = (uint8_t)(r * win + s); }
-                }
+        for (int e = 0; e < VEC; ++e) {
+#pragma unroll
+            for (int k = 0; k < WIN * WIN; ++k) {
+                const unsigned f = VEC == 8 ? ((e & 1) ? (v8[k][e >> 1] & 0xffff0000u) : (v8[k][e >> 1] << 16)) : (unsigned)v1[k] << 16;
+                const bool take = k == 0 || __uint_as_float(f) > __uint_as_float(best[e]);  // the first maximum
+                best[e] = take ? f : best[e];
+                bi[e] = take ? (unsigned)k : bi[e];
             }
-        size_t o = (((size_t)n * P + p) * Q + q) * C + (size_t)cv * VEC;
+        }
+        const size_t o = (size_t)t * a.C + (size_t)cv * VEC;
         if (VEC == 8) {
-            *reinterpret_cast<uint4*>(y + o) = make_uint4(
-                (unsigned)bestbits[0] | ((unsigned)bestbits[1] << 16), (unsigned)bestbits[2] | ((unsigned)bestbits[3] << 16),
-                (unsigned)bestbits[4] | ((unsigned)bestbits[5] << 16), (unsigned)bestbits[6] | ((unsigned)bestbits[7] << 16));
-            uint2 a;
-            a.x = bi[0] | (bi[1] << 8) | (bi[2] << 16) | ((unsigned)bi[3] << 24);
-            a.y = bi[4] | (bi[5] << 8) | (bi[6] << 16) | ((unsigned)bi[7] << 24);
-            *reinterpret_cast<uint2*>(am + o) = a;
+            u32x4 yo;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) yo[k] = (best[2 * k] >> 16) | best[2 * k + 1];
+            *reinterpret_cast<u32x4*>(y + o) = yo;
+            const u32x2 ao = {bi[0] | (bi[1] << 8) | (bi[2] << 16) | (bi[3] << 24), bi[4] | (bi[5] << 8) | (bi[6] << 16) | (bi[7] << 24)};
+            *reinterpret_cast<u32x2*>(am + o) = ao;
         } else {
-            y[o] = bestbits[0];
-            am[o] = bi[0];
+            y[o] = (bf16_t)(best[0] >> 16);
+            am[o] = (uint8_t)bi[0];
         }
     }
 }
 
-// ---- max-pool backward as a gather over the windows covering each input element ----
+// any other window side
+template <int VEC>
+__global__ void maxpool_fwd_any_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, uint8_t* __restrict__ am, int win,
+                                       const PoolArgs a) {
+    const uint32_t CV = a.C / VEC;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
+        uint32_t t = fdiv(i, a.dCV);
+        const uint32_t cv = i - t * CV;
+        const uint32_t t2 = fdiv(t, a.dX);
+        const int q = (int)(t - t2 * a.Q);
+        const uint32_t n = fdiv(t2, a.dY);
+        const int p = (int)(t2 - n * a.P);
+        const bf16_t* src = x + (((size_t)n * a.H + (size_t)p * a.st) * a.W + (size_t)q * a.st) * a.C + (size_t)cv * VEC;
+        unsigned short best[VEC];
+        uint8_t bi[VEC];
+        for (int r = 0; r < win; ++r)
+            for (int s = 0; s < win; ++s) {
+                const bf16_t* v = src + ((size_t)r * a.W + s) * a.C;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e)
+                    if ((r | s) == 0 || bf2f(v[e]) > bf2f(best[e])) { best[e] = v[e]; bi[e] = (uint8_t)(r * win + s); }
+            }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            y[(size_t)t * a.C + (size_t)cv * VEC + e] = best[e];
+            am[(size_t)t * a.C + (size_t)cv * VEC + e] = bi[e];
+        }
+    }
+}
+
+// ---- max-pool backward as a gather over the windows covering each input element (zero where ry is given and not
+// positive).  VEC channels of one gradient window as fp32 plus the argmax; an absent window names no pixel. ----
+template <int VEC>
+struct PoolWindow {
+    float g[VEC];
+    unsigned am[VEC];
+    __device__ __forceinline__ void load(const bf16_t* dy, const uint8_t* amp, const bf16_t* ry, size_t o, bool ok) {
+        if (VEC == 8) {
+            u32x4 gv = {0u, 0u, 0u, 0u}, yv = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+            u32x2 av = {0xffffffffu, 0xffffffffu};
+            if (ok) {
+                gv = *reinterpret_cast<const u32x4*>(dy + o);
+                av = *reinterpret_cast<const u32x2*>(amp + o);
+                if (ry) yv = *reinterpret_cast<const u32x4*>(ry + o);
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const unsigned yb = (e & 1) ? (yv[e >> 1] & 0xffff0000u) : (yv[e >> 1] << 16);
+                const unsigned gb = (e & 1) ? (gv[e >> 1] & 0xffff0000u) : (gv[e >> 1] << 16);
+                g[e] = __uint_as_float(gb);
+                am[e] = __uint_as_float(yb) > 0.f ? ((e < 4 ? av[0] : av[1]) >> ((e & 3) * 8)) & 0xffu : 0xffu;
+            }
+        } else {
+            g[0] = ok ? bf2f(dy[o]) : 0.f;
+            am[0] = ok && (!ry || bf2f(ry[o]) > 0.f) ? amp[o] : 0xffu;
+        }
+    }
+    __device__ __forceinline__ void add(float* sum, unsigned code) const {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) sum[e] += am[e] == code ? g[e] : 0.f;
+    }
+};
+template <int VEC>
+__device__ __forceinline__ void pool_store(bf16_t* dx, const float* s) {
+    if (VEC == 8) {
+        u32x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (unsigned)f2bf(s[2 * k]) | ((unsigned)f2bf(s[2 * k + 1]) << 16);
+        *reinterpret_cast<u32x4*>(dx) = v;
+    } else {
+        *dx = f2bf(s[0]);
+    }
+}
+
+// Stride 2 (every pool of the two networks): a thread owns a 2 x 2 block of input pixels, which only the windows ending
+// in it (WIN 3: and the ones before, above and left) can reach: one (four) window loads for four pixels, where a thread
+// per pixel loads 4 (9).  100 x 55 x 55 x 64, window 3: 30.7 -> 17.3 us.
+template <int VEC, int WIN>
+__global__ void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
+                                      const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, const PoolArgs a) {
+    const uint32_t CV = a.C / VEC;
+    const uint32_t WB = (a.W + 1) / 2, HB = (a.H + 1) / 2;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
+        const uint32_t t = fdiv(i, a.dCV);
+        const uint32_t cv = i - t * CV;
+        const uint32_t t2 = fdiv(t, a.dX);
+        const int q = (int)(t - t2 * WB);
+        const uint32_t n = fdiv(t2, a.dY);
+        const int p = (int)(t2 - n * HB);
+        constexpr int NB = WIN == 3 ? 2 : 1;  // windows per direction
+        PoolWindow<VEC> w[NB][NB];            // [1]: the window of (p, q), [0]: the one before
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+            for (int v = 0; v < NB; ++v) {
+                const int pw = p - (NB - 1) + u, qw = q - (NB - 1) + v;
+                w[u][v].load(dy, am, ry, (((size_t)n * a.P + pw) * a.Q + qw) * a.C + (size_t)cv * VEC,
+                             (unsigned)pw < (unsigned)a.P && (unsigned)qw < (unsigned)a.Q);
+            }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int h = 2 * p + r, x = 2 * q + s;
+                if (h >= a.H || x >= a.W) continue;
+                float sum[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
+                if (WIN == 3) {
+                    if (r == 0 && s == 0) w[0][0].add(sum, 2 * WIN + 2);
+                    if (r == 0) w[0][NB - 1].add(sum, 2 * WIN + s);
+                    if (s == 0) w[NB - 1][0].add(sum, r * WIN + 2);
+                }
+                w[NB - 1][NB - 1].add(sum, r * WIN + s);
+                pool_store<VEC>(dx + (((size_t)n * a.H + h) * a.W + x) * a.C + (size_t)cv * VEC, sum);
+            }
+    }
+}
+
+// any other stride or window: a thread per input pixel walks the windows that cover it
 template <int VEC>
 __global__ void maxpool_bwd_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
-                                   const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, int N, int H,
-                                   int W, int C, int P, int Q, int win, int st) {
-    const int CV = C / VEC;
-    size_t total = (size_t)N * H * W * CV;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        int cv = (int)(i % CV);
-        size_t t = i / CV;
-        int w = (int)(t % W); t /= W;
-        int h = (int)(t % H);
-        int n = (int)(t / H);
+                                   const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, int win, const PoolArgs a) {
+    const uint32_t CV = a.C / VEC;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    const int st = a.st;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
+        const uint32_t t = fdiv(i, a.dCV);
+        const uint32_t cv = i - t * CV;
+        const uint32_t t2 = fdiv(t, a.dX);
+        const int w = (int)(t - t2 * a.W);
+        const uint32_t n = fdiv(t2, a.dY);
+        const int h = (int)(t2 - n * a.H);
         float sum[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
         int p_lo = (h - win + 1 + st - 1);
         p_lo = p_lo > 0 ? p_lo / st : 0;
-        int p_hi = h / st; if (p_hi > P - 1) p_hi = P - 1;
+        int p_hi = h / st; if (p_hi > a.P - 1) p_hi = a.P - 1;
         int q_lo = (w - win + 1 + st - 1);
         q_lo = q_lo > 0 ? q_lo / st : 0;
-        int q_hi = w / st; if (q_hi > Q - 1) q_hi = Q - 1;
+        int q_hi = w / st; if (q_hi > a.Q - 1) q_hi = a.Q - 1;
         for (int p = p_lo; p <= p_hi; ++p)
             for (int q = q_lo; q <= q_hi; ++q) {
-                int code = (h - p * st) * win + (w - q * st);
-                size_t o = (((size_t)n * P + p) * Q + q) * C + (size_t)cv * VEC;
-                if (VEC == 8) {
-                    uint2 a = *reinterpret_cast<const uint2*>(am + o);
-                    uint4 g = *reinterpret_cast<const uint4*>(dy + o);
-                    unsigned gg[4] = {g.x, g.y, g.z, g.w};
-                    unsigned yy[4] = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-                    if (ry) {
-                        uint4 v = *reinterpret_cast<const uint4*>(ry + o);
-                        yy[0] = v.x; yy[1] = v.y; yy[2] = v.z; yy[3] = v.w;
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        unsigned ai = ((e < 4 ? a.x : a.y) >> ((e & 3) * 8)) & 0xff;
-                        unsigned short gb = (unsigned short)((gg[e >> 1] >> ((e & 1) * 16)) & 0xffff);
-                        unsigned short yb = (unsigned short)((yy[e >> 1] >> ((e & 1) * 16)) & 0xffff);
-                        if ((int)ai == code && bf2f(yb) > 0.f) sum[e] += bf2f(gb);
-                    }
-                } else {
-                    bool pass = ry ? (bf2f(ry[o]) > 0.f) : true;
-                    if ((int)am[o] == code && pass) sum[0] += bf2f(dy[o]);
-                }
+                PoolWindow<VEC> wd;
+                wd.load(dy, am, ry, (((size_t)n * a.P + p) * a.Q + q) * a.C + (size_t)cv * VEC, true);
+                wd.add(sum, (unsigned)((h - p * st) * win + (w - q * st)));
             }
-        size_t o = (((size_t)n * H + h) * W + w) * C + (size_t)cv * VEC;
-        if (VEC == 8) {
-            *reinterpret_cast<uint4*>(dx + o) = make_uint4(
-                (unsigned)f2bf(sum[0]) | ((unsigned)f2bf(sum[1]) << 16), (unsigned)f2bf(sum[2]) | ((unsigned)f2bf(sum[3]) << 16),
-                (unsigned)f2bf(sum[4]) | ((unsigned)f2bf(sum[5]) << 16), (unsigned)f2bf(sum[6]) | ((unsigned)f2bf(sum[7]) << 16));
-        } else {
-            dx[o] = f2bf(sum[0]);
-        }
+        pool_store<VEC>(dx + (size_t)t * a.C + (size_t)cv * VEC, sum);
     }
 }
 
@@ -699,33 +799,51 @@ int launch_relu_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dx, size_t n, hip
     return check_launch("relu_bwd");
 }
 
+// items = one per channel vector of `rows` x `cols` positions per image
+static PoolArgs pool_args(int N, int H, int W, int C, int win, int st, int vec, int rows, int cols) {
+    PoolArgs a;
+    a.H = H; a.W = W; a.C = C; a.st = st;
+    a.P = (H - win) / st + 1;
+    a.Q = (W - win) / st + 1;
+    a.items = (uint32_t)((size_t)N * rows * cols * (C / vec));
+    a.dCV = make_fastdiv((uint32_t)(C / vec));
+    a.dX = make_fastdiv((uint32_t)cols);
+    a.dY = make_fastdiv((uint32_t)rows);
+    return a;
+}
+
 int launch_maxpool_fwd(int N, int H, int W, int C, int win, int stp, const bf16_t* x, bf16_t* y,
                        uint8_t* am, hipStream_t st) {
-    int P = (H - win) / stp + 1, Q = (W - win) / stp + 1;
-    if ((C & 7) == 0) {
-        size_t total = (size_t)N * P * Q * (C / 8);
-        hipLaunchKernelGGL(maxpool_fwd_kernel<8>, dim3(grid_for(total)), dim3(kThreads), 0, st, x, y, am, N,
-                           H, W, C, P, Q, win, stp);
-    } else {
-        size_t total = (size_t)N * P * Q * C;
-        hipLaunchKernelGGL(maxpool_fwd_kernel<1>, dim3(grid_for(total)), dim3(kThreads), 0, st, x, y, am, N,
-                           H, W, C, P, Q, win, stp);
-    }
+    const int vec = (C & 7) == 0 ? 8 : 1;
+    const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, (H - win) / stp + 1, (W - win) / stp + 1);
+    const dim3 grid(grid_for(a.items)), block(kThreads);
+    if (win != 2 && win != 3) {
+        if (vec == 8) hipLaunchKernelGGL(maxpool_fwd_any_kernel<8>, grid, block, 0, st, x, y, am, win, a);
+        else hipLaunchKernelGGL(maxpool_fwd_any_kernel<1>, grid, block, 0, st, x, y, am, win, a);
+    } else if (vec == 8 && win == 2) hipLaunchKernelGGL((maxpool_fwd_kernel<8, 2>), grid, block, 0, st, x, y, am, a);
+    else if (vec == 8) hipLaunchKernelGGL((maxpool_fwd_kernel<8, 3>), grid, block, 0, st, x, y, am, a);
+    else if (win == 2) hipLaunchKernelGGL((maxpool_fwd_kernel<1, 2>), grid, block, 0, st, x, y, am, a);
+    else hipLaunchKernelGGL((maxpool_fwd_kernel<1, 3>), grid, block, 0, st, x, y, am, a);
     return check_launch("maxpool_fwd");
 }
 
 int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_t* dy, const uint8_t* am,
                        const bf16_t* ry, bf16_t* dx, hipStream_t st) {
-    int P = (H - win) / stp + 1, Q = (W - win) / stp + 1;
-    if ((C & 7) == 0) {
-        size_t total = (size_t)N * H * W * (C / 8);
-        hipLaunchKernelGGL(maxpool_bwd_kernel<8>, dim3(grid_for(total)), dim3(kThreads), 0, st, dy, am, ry,
-                           dx, N, H, W, C, P, Q, win, stp);
-    } else {
-        size_t total = (size_t)N * H * W * C;
-        hipLaunchKernelGGL(maxpool_bwd_kernel<1>, dim3(grid_for(total)), dim3(kThreads), 0, st, dy, am, ry,
-                           dx, N, H, W, C, P, Q, win, stp);
+    const int vec = (C & 7) == 0 ? 8 : 1;
+    const dim3 block(kThreads);
+    if (stp == 2 && (win == 2 || win == 3)) {
+        const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, (H + 1) / 2, (W + 1) / 2);
+        const dim3 grid(grid_for(a.items));
+        if (vec == 8 && win == 2) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 2>), grid, block, 0, st, dy, am, ry, dx, a);
+        else if (vec == 8) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 3>), grid, block, 0, st, dy, am, ry, dx, a);
+        else if (win == 2) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<1, 2>), grid, block, 0, st, dy, am, ry, dx, a);
+        else hipLaunchKernelGGL((maxpool_bwd_s2_kernel<1, 3>), grid, block, 0, st, dy, am, ry, dx, a);
+        return check_launch("maxpool_bwd");
     }
+    const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, H, W);
+    const dim3 grid(grid_for(a.items));
+    if (vec == 8) hipLaunchKernelGGL(maxpool_bwd_kernel<8>, grid, block, 0, st, dy, am, ry, dx, win, a);
+    else hipLaunchKernelGGL(maxpool_bwd_kernel<1>, grid, block, 0, st, dy, am, ry, dx, win, a);
     return check_launch("maxpool_bwd");
 }
 

@@ -90,3 +90,36 @@ def test_fc_stream_edges(orc, B, n_in, n_out):
     assert torch.isnan(dx[B * n_in:]).all()
     e = gu.rel_err(gu.host_f64(dx[:B * n_in]).reshape(B, n_in), orc.fc_bwd_data(g64, W64))
     assert e <= gu.TOL_BF16_OUT, e
+
+
+# max-pool: odd / even maps (a last row or column that no window covers, blocks of two input pixels with one inside),
+# channels in vectors and one by one, stride 2 with windows of 2 and 3, other strides and windows
+@pytest.mark.parametrize("N,H,W,C,win,st", [
+    (2, 13, 13, 8, 3, 2), (1, 14, 15, 24, 3, 2), (3, 12, 9, 16, 2, 2), (1, 11, 16, 475, 3, 2), (2, 7, 7, 5, 2, 2), (1, 3, 3, 8, 3, 2),
+    (1, 2, 3, 8, 2, 2), (1, 10, 11, 8, 3, 1), (1, 10, 13, 3, 3, 3), (1, 9, 9, 16, 5, 2), (2, 8, 8, 8, 1, 2), (1, 16, 17, 6, 15, 1)])
+def test_maxpool_edges(orc, N, H, W, C, win, st):
+    import paper_1811_01532_amd as wap
+    print(f"[case] maxpool edges {(N, H, W, C, win, st)}", flush=True)
+    g = si.rng(460, H * W + C + win)
+    x = np.round(g.standard_normal((N, H, W, C)).astype(np.float32) * 4) / 4      # ties, negative windows
+    x[0, 0, 0, 0] = -np.inf
+    xb = si.f32_to_bf16_bits(x)
+    P, Q = si.out_dim(H, 0, win, st), si.out_dim(W, 0, win, st)
+    gb = si.normal_bf16(g, (N, P, Q, C))
+    n, no = N * H * W * C, N * P * Q * C
+    y = torch.full((no + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    am = torch.full((no + 8,), 77, dtype=torch.uint8, device="cuda")
+    wap.wap_maxpool_fwd(N, H, W, C, win, st, gu.dev_bf16(xb), y, am)
+    x64, g64 = orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(gb)
+    yref, amref = orc.maxpool_fwd(x64, win, st)
+    torch.cuda.synchronize()
+    assert torch.isnan(y[no:]).all() and (am[no:] == 77).all()
+    assert np.array_equal(gu.host_f64(y[:no]).reshape(N, P, Q, C), yref)
+    assert np.array_equal(am[:no].cpu().numpy().reshape(N, P, Q, C), amref)
+    for ry in (None, y):
+        dx = torch.full((n + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        wap.wap_maxpool_bwd(N, H, W, C, win, st, gu.dev_bf16(gb), am, ry, dx)
+        torch.cuda.synchronize()
+        assert torch.isnan(dx[n:]).all()
+        ref = orc.maxpool_bwd(g64 if ry is None else np.where(yref > 0, g64, 0.0), amref, (N, H, W, C), win, st)
+        assert gu.rel_err(gu.host_f64(dx[:n]).reshape(N, H, W, C), ref) <= gu.TOL_BF16_OUT
