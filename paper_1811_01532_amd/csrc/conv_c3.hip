@@ -828,7 +828,10 @@ size_t c3_general_smem(const GemmGeom& g) {
 
 bool conv_c3_fwd_supported(const GemmGeom& g) {
     if (g.IC != 3 || g.div_h != 1 || g.div_w != 1 || (g.Ncols != 32 && g.Ncols != 64)) return false;
-    return c3_special(g) || c3_fwd_strided(g) || c3_general_smem(g) <= 64 * 1024;
+    if (c3_special(g)) return true;
+    if (c3_fwd_strided(g)) return g_force_fwd_cfg == 8 || !conv_thin_fwd_few_tiles(g);
+    // the gather serves what is left: patches too large to stage (conv_thin.hip)
+    return c3_general_smem(g) <= 64 * 1024 && (g_force_fwd_cfg == 8 || !conv_thin_fwd_supported(g));
 }
 const char* conv_c3_fwd_kernel_name(const GemmGeom& g) {
     if (c3_rows(g)) return g.Ncols == 64 ? "conv_c3_fwd_rows_kernel<2>" : "conv_c3_fwd_rows_kernel<1>";
@@ -922,7 +925,7 @@ int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, cons
 
 // (A gather-based general-filter weight gradient, lanes indexing the columns k, was tried and dropped: every lane
 // touches a different cache line.  Large filters at horizontal stride 4 use the rows-in-LDS kernel above; all other
-// first-layer shapes fall to the generic kernel.)
+// first-layer shapes go to conv_thin.hip.)
 static bool wgrad_c3_special(const WgradGeom& g) {
     return g.C == 3 && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && (g.K == 32 || g.K == 64) && (g.Q % 8) == 0 &&
            (long)g.N * g.P * g.Q >= 4096;
@@ -931,7 +934,9 @@ static bool wgrad_c3_strided(const WgradGeom& g) {
     C3SPlan p;
     return !wgrad_c3_special(g) && c3s_plan(g, &p) && (long)g.N * g.P >= 64;
 }
-bool wgrad_c3_supported(const WgradGeom& g) { return wgrad_c3_special(g) || wgrad_c3_strided(g); }
+bool wgrad_c3_supported(const WgradGeom& g) {
+    return wgrad_c3_special(g) || (wgrad_c3_strided(g) && (g_force_wgrad_cfg == 4 || !wgrad_thin_few_tiles(g)));
+}
 const char* wgrad_c3_kernel_name(const WgradGeom& g) {
     if (wgrad_c3_strided(g)) return g.K == 64 ? "wgrad_c3_strided_kernel<2>" : "wgrad_c3_strided_kernel<1>";
     return g.K == 64 ? "wgrad_c3_kernel<2>" : "wgrad_c3_kernel<1>";

@@ -407,6 +407,12 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
         p.ws_bytes = 0;
         return p;
     }
+    if (!b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 15) && conv_thin_fwd_supported(g)) {
+        p.cfg = 15;
+        p.nsplit = 1;
+        p.ws_bytes = 0;
+        return p;
+    }
     if (b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 9) && dgrad_thin_supported(g)) {
         p.cfg = 9;  // at most four output columns (gradient w.r.t. a 3-channel image)
         p.nsplit = 1;
@@ -503,6 +509,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
         return launch_relu_bwd(out, relu_mask, out, (size_t)g.M * g.Ncols, st);
     }
     if (plan.cfg == 8) return launch_conv_c3_fwd(g, A, Bw, bias, relu, out, st);
+    if (plan.cfg == 15) return launch_conv_thin_fwd(g, A, Bw, bias, relu, out, st);
     if (plan.cfg == 9) return launch_dgrad_thin(g, A, Bw, out, st);
     if (plan.cfg == 10) {
         int rc10 = launch_fc_fwd(g, plan.nsplit, A, Bw, bias, relu, plan.nsplit > 1 ? ws : (void*)out, st);
@@ -624,6 +631,7 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 9) return "dgrad_thin_kernel";
     if (plan.cfg == 10) return "fc_fwd_kernel";
     if (plan.cfg == 11) return "fc_dx_kernel";
+    if (plan.cfg == 15) return "conv_thin_fwd_kernel";
     static const char* names[5][2][3] = {
         {{"igemm_kernel<256,256,2,4,false,0>", "", ""}, {"igemm_kernel<256,256,2,4,true,0>", "", ""}},
         {{"igemm_kernel<128,128,2,2,false,0>", "igemm_kernel<128,128,2,2,false,1>", "igemm_kernel<128,128,2,2,false,2>"},

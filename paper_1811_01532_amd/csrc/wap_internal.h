@@ -172,6 +172,16 @@ const char* wgrad_c3_kernel_name(const WgradGeom& g);
 int wgrad_c3_nsplit(const WgradGeom& g);
 int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* part, hipStream_t st);
 
+// 1 .. 4 input channels, any filter and stride, output channels a multiple of 8 (conv_thin.hip)
+bool conv_thin_fwd_supported(const GemmGeom& g);
+bool conv_thin_fwd_few_tiles(const GemmGeom& g);  // ... and preferred to the kernel for horizontal strides of 4
+int launch_conv_thin_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y,
+                         hipStream_t st);
+bool wgrad_thin_supported(const WgradGeom& g);
+bool wgrad_thin_few_tiles(const WgradGeom& g);
+int wgrad_thin_nsplit(const WgradGeom& g);
+int launch_wgrad_thin(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* part, hipStream_t st);
+
 // data gradient with at most four output columns (dgrad_thin.hip); g = data-gradient geometry
 bool dgrad_thin_supported(const GemmGeom& g);
 int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st);

@@ -335,6 +335,12 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
         p.ws_bytes = (size_t)p.nsplit * g.K * Kred * sizeof(float);  // always reduced from per-work-group partials
         return p;
     }
+    if ((g_force_wgrad_cfg < 0 || g_force_wgrad_cfg == 7) && wgrad_thin_supported(g)) {
+        p.cfg = 7;
+        p.nsplit = wgrad_thin_nsplit(g);
+        p.ws_bytes = (size_t)p.nsplit * g.K * Kred * sizeof(float);
+        return p;
+    }
     // (5 / 6: the patch kernel with two / one dy blocks per wavefront, for the tests)
     if ((g_force_wgrad_cfg < 0 || g_force_wgrad_cfg == 3 || g_force_wgrad_cfg == 5 || g_force_wgrad_cfg == 6) && mode == 0 &&
         wgrad_patch_supported(g)) {
@@ -387,8 +393,9 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
     wa.dPQ = make_fastdiv((uint32_t)(g.P * g.Q));
     wa.dQ = make_fastdiv((uint32_t)g.Q);
     wa.out = plan.nsplit > 1 ? reinterpret_cast<float*>(ws) : dw;
-    if (plan.cfg == 4) {
-        int rc4 = launch_wgrad_c3(g, plan.nsplit, x, dy, reinterpret_cast<float*>(ws), st);
+    if (plan.cfg == 4 || plan.cfg == 7) {
+        int rc4 = plan.cfg == 4 ? launch_wgrad_c3(g, plan.nsplit, x, dy, reinterpret_cast<float*>(ws), st)
+                                : launch_wgrad_thin(g, plan.nsplit, x, dy, reinterpret_cast<float*>(ws), st);
         if (rc4 != WAP_OK) return rc4;
         if (ev_mid) (void)hipEventRecord(ev_mid, st);
         return launch_reduce_f32(reinterpret_cast<const float*>(ws), plan.nsplit, (size_t)g.K * wa.Kred, dw, st, sgd);
@@ -431,13 +438,14 @@ bool wgrad_fuses_unpool(const WgradGeom& g, const WgradPlan& plan) {
 // first-layer kernels always reduce), or the epilogue of an unsplit generic product whose accumulator rows are
 // 16-byte groups of parameters.
 bool wgrad_fuses_sgd(const WgradGeom& g, const WgradPlan& plan) {
-    if (plan.cfg == 4 || plan.nsplit > 1) return true;
+    if (plan.cfg == 4 || plan.cfg == 7 || plan.nsplit > 1) return true;
     return plan.cfg < 3 && ((g.R * g.S * g.C) & 3) == 0;
 }
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan) { return wgrad_kernel_name(g, plan, false); }
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool unpool) {
     if (plan.cfg == 3) return wgrad_patch_kernel_name(g, unpool);
     if (plan.cfg == 4) return wgrad_c3_kernel_name(g);
+    if (plan.cfg == 7) return "wgrad_thin_kernel";
     static const char* names[3][2] = {
         {"wgrad_kernel<256,256,2,4,0>", ""},
         {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>"},

@@ -103,6 +103,10 @@ CASES = [
     ("split_mask_c36", (2, 9, 9, 36, 64, 3, 3, 1, 1), (1, -1, 3)),
     ("split_mask_c72", (1, 21, 20, 72, 64, 3, 3, 1, 1), (1, -1, 6)),
     ("split_mask_c10", (2, 9, 9, 10, 64, 3, 3, 1, 1), (1, -1, 3)),
+    # the specialised first-layer kernels on shapes that the few-channel kernels take by themselves
+    ("c3_general_forced_5x5_s2_k32", (9, 63, 61, 3, 32, 5, 5, 2, 2), (8, 4, -1)),
+    ("c3_strided_forced_11x11_s4_k64", (4, 131, 136, 3, 64, 11, 11, 4, 2), (8, 4, -1)),
+    ("c3_strided_forced_5x9_rect_stride_2_4_pad_1_0", (8, 30, 64, 3, 64, 5, 9, (2, 4), (1, 0)), (8, 4, -1)),
 ]
 
 

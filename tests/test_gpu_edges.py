@@ -123,3 +123,58 @@ def test_maxpool_edges(orc, N, H, W, C, win, st):
         assert torch.isnan(dx[n:]).all()
         ref = orc.maxpool_bwd(g64 if ry is None else np.where(yref > 0, g64, 0.0), amref, (N, H, W, C), win, st)
         assert gu.rel_err(gu.host_f64(dx[:n]).reshape(N, H, W, C), ref) <= gu.TOL_BF16_OUT
+
+
+# few input channels (1 .. 4): one tile and ragged ones in both directions, filters with an even and an odd side, one to
+# sixteen blocks of filter taps, strides and pads in one or both directions, output channels in one block, a part of one,
+# several and divided over work-groups, an odd number of elements per image row; several tiles per work-group
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad", [
+    (1, 4, 32, 3, 16, 3, 3, 1, 1), (2, 9, 33, 3, 8, 3, 3, 1, 1), (1, 11, 31, 3, 96, 3, 3, 1, 0), (1, 13, 29, 1, 24, 5, 5, 2, 2),
+    (2, 35, 35, 3, 40, 11, 11, 4, 2), (1, 47, 47, 3, 96, 7, 7, 2, 3), (1, 12, 50, 2, 16, 3, 5, (1, 2), (1, 2)),
+    (1, 13, 40, 4, 40, 4, 3, (2, 1), (0, 1)), (3, 31, 34, 3, 72, 3, 3, 3, 1), (1, 10, 60, 4, 16, 2, 19, 1, (1, 9)),
+    (1, 30, 41, 1, 128, 20, 1, 1, (3, 0)), (1, 5, 5, 3, 200, 1, 2, 1, 0), (40, 60, 70, 3, 16, 3, 3, 1, 1), (1, 3, 200, 3, 32, 1, 9, 1, (0, 4))])
+def test_few_channel_edges(orc, N, H, W, C, K, R, S, stride, pad):
+    import paper_1811_01532_amd as wap
+    st = (stride, stride) if isinstance(stride, int) else stride
+    pd = (pad, pad) if isinstance(pad, int) else pad
+    print(f"[case] few channels {(N, H, W, C, K, R, S, st, pd)}", flush=True)
+    P, Q = si.out_dim(H, pd[0], R, st[0]), si.out_dim(W, pd[1], S, st[1])
+    xb, wb = si.normal_bf16(si.rng(470, H * W + K), (N, H, W, C)), si.he_weight_bf16(si.rng(471, R * S + C), (K, R, S, C))
+    gb = si.normal_bf16(si.rng(472, H * W + K), (N, P, Q, K))
+    bias = si.rng(473, K).standard_normal(K).astype(np.float32)
+    x64, w64, g64 = orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(wb), orc.bf16_bits_to_f64(gb)
+    xd, ny, nw = gu.dev_bf16(xb), N * P * Q * K, K * R * S * C
+    wap.lib().wap_debug_force(15, 7, -1)
+    try:
+        for relu in (False, True):
+            d = wap.conv_desc(N, H, W, C, K, R, S, st, pd, relu=relu)
+            assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_FWD) == "conv_thin_fwd_kernel"
+            y = torch.full((ny + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            wap.wap_conv2d_fwd(d, xd, gu.dev_bf16(wb), torch.from_numpy(bias).cuda() if relu else None, y, None)
+            torch.cuda.synchronize()
+            assert torch.isnan(y[ny:]).all()
+            ref = orc.conv2d_fwd(x64, w64, st, pd, bias=bias.astype(np.float64) if relu else None, relu=relu)
+            assert gu.rel_err(gu.host_f64(y[:ny]).reshape(N, P, Q, K), ref) <= gu.TOL_BF16_OUT
+        assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT) == "wgrad_thin_kernel"
+        dw = torch.full((nw + 8,), float("nan"), dtype=torch.float32, device="cuda")
+        wap.wap_conv2d_bwd_weight(d, xd, gu.dev_bf16(gb), dw, gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
+        torch.cuda.synchronize()
+        assert torch.isnan(dw[nw:]).all()
+        ref = orc.conv2d_bwd_weight(x64, g64, (K, R, S, C), st, pd)
+        assert gu.rel_err(gu.host_f64(dw[:nw]).reshape(K, R, S, C), ref) <= gu.TOL_F32_OUT
+        # an infinite pixel reaches exactly the outputs and the weight taps whose receptive field holds it
+        xi = x64.copy()
+        xi[0, H // 2, W - 1, C - 1] = np.inf
+        xid = xd.clone().reshape(N, H, W, C)
+        xid[0, H // 2, W - 1, C - 1] = float("inf")
+        wap.wap_conv2d_fwd(d, xid, gu.dev_bf16(np.where(wb == 0, 0x3f80, wb).astype(np.uint16)), None, y, None)
+        wap.wap_conv2d_bwd_weight(d, xid, torch.ones(N, P, Q, K, dtype=torch.bfloat16, device="cuda"), dw,
+                                  gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
+        torch.cuda.synchronize()
+        touched = orc.conv2d_fwd((~np.isfinite(xi)).astype(np.float64), np.ones((1, R, S, C)), st, pd)[..., 0] > 0
+        d0 = gu.host_f64(y[:ny]).reshape(N, P, Q, K)
+        assert np.isfinite(d0[~touched]).all()
+        taps = orc.conv2d_bwd_weight((~np.isfinite(xi)).astype(np.float64), np.ones((N, P, Q, 1)), (1, R, S, C), st, pd)[0] > 0
+        assert np.array_equal(~np.isfinite(gu.host_f64(dw[:nw]).reshape(K, R, S, C)), np.broadcast_to(taps, (K, R, S, C)))
+    finally:
+        wap.lib().wap_debug_force(-1, -1, -1)
