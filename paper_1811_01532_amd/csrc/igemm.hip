@@ -17,6 +17,8 @@
 //   * channel-contiguous weight tiles (data gradient) are transposed on the way out of LDS with
 //     ds_read_b64_tr_b16 instead of a separate transpose pass over the weights;
 //   * blockIdx is remapped so that each XCD (own L2) works on a contiguous range of tiles.
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -26,6 +28,15 @@ namespace {
 constexpr int BK = 64;
 constexpr int A_PITCH = (BK + 8) * 2;  // bytes per LDS row of a reduction-contiguous tile
 
+// One phase of a strided data gradient: the output pixels whose coordinates leave the same remainders (oh0, ow0) modulo
+// the strides.  Only the filter taps r0, r0 + stride, ... meet a dy element there, so a phase is an ordinary stride-1
+// product of its own, with R x S of the taps.
+constexpr int kMaxPhases = 16;
+struct Phase {
+    int R, S, r0, s0, OH, OW, pad_h, pad_w, oh0, ow0, M;
+    int tile0;  // first row tile
+};
+
 struct KArgs {
     const bf16_t* A;
     const bf16_t* Bw;
@@ -34,6 +45,8 @@ struct KArgs {
     GemmGeom g;
     int tiles_m, tiles_n, nsplit, ktiles, ktiles_per_split;
     int relu, partial;
+    int nphase;
+    Phase ph[kMaxPhases];
 };
 
 __device__ __forceinline__ int xcd_remap(int bid, int total) {
@@ -63,7 +76,10 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
 // MODE 0: fast  -- channel counts multiples of 64 / 8, unit tap divisor, 16-byte loads, one tap per tile
 // MODE 1: vec   -- channel counts multiples of 8, any geometry
 // MODE 2: scalar-- anything (2-byte loads)
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE>
+// PHASE: data gradient of a strided convolution, the row tiles grouped by phase (a.ph): a tap between dy elements costs
+// nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x 57 x 57, 200 -> 72 channels, 3x3
+// stride 2: block forward and backward 141 -> 103 us)
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE, bool PHASE>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KArgs a) {
     constexpr int NT = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -81,20 +97,38 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
 
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const GemmGeom& g = a.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
 
     const int total = a.tiles_m * a.tiles_n * a.nsplit;
-    int logical = xcd_remap(blockIdx.x, total);
+    // (phases differ in work: neighbouring work-groups go to different XCDs there)
+    int logical = PHASE ? (int)blockIdx.x : xcd_remap(blockIdx.x, total);
     const int tn = logical % a.tiles_n;
     logical /= a.tiles_n;
-    const int tm = logical % a.tiles_m;
+    int tm = logical % a.tiles_m;
     const int split = logical / a.tiles_m;
+    GemmGeom gp;
+    int r0 = 0, s0 = 0, oh0 = 0, ow0 = 0;
+    int ktiles = a.ktiles, kps = a.ktiles_per_split;
+    if (PHASE) {
+        int c = 0;
+        while (c + 1 < a.nphase && tm >= a.ph[c + 1].tile0) ++c;
+        const Phase& p = a.ph[c];
+        tm -= p.tile0;
+        gp = a.g;
+        gp.R = p.R; gp.S = p.S; gp.OH = p.OH; gp.OW = p.OW; gp.M = p.M;
+        gp.pad_h = p.pad_h; gp.pad_w = p.pad_w;
+        gp.mul_h = gp.mul_w = gp.div_h = gp.div_w = 1;
+        gp.Kred = p.R * p.S * gp.IC;
+        r0 = p.r0; s0 = p.s0; oh0 = p.oh0; ow0 = p.ow0;
+        ktiles = (gp.Kred + BK - 1) / BK;
+        kps = (ktiles + a.nsplit - 1) / a.nsplit;
+    }
+    const GemmGeom& g = PHASE ? gp : a.g;
     const int m0 = tm * BM, n0 = tn * BN;
-    const int kt_begin = split * a.ktiles_per_split;
-    int kt_end = kt_begin + a.ktiles_per_split;
-    if (kt_end > a.ktiles) kt_end = a.ktiles;
+    const int kt_begin = split * kps;
+    int kt_end = kt_begin + kps;
+    if (kt_end > ktiles) kt_end = ktiles;
 
     // ---- per-thread row state of the gathered operand ----
     const int a_vec = tid & 7, a_row0 = tid >> 3;
@@ -122,7 +156,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
     const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block);
 
     auto tap_ok = [&](int th, int tw, int& ih, int& iw) -> bool {
-        if (MODE == 0) {
+        if (MODE == 0 || PHASE) {
             ih = th;
             iw = tw;
             return (unsigned)th < (unsigned)g.IH && (unsigned)tw < (unsigned)g.IW;
@@ -207,7 +241,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
                 int tap = (MODE == 0) ? kk0 / g.IC : kk / g.IC;  // one tap per tile in the fast mode
                 int k = kk - tap * g.IC;
                 int r = tap / g.S, s = tap - r * g.S;
-                int rowoff = ((k * g.R + (g.R - 1 - r)) * g.S + (g.S - 1 - s)) * g.Ncols;
+                if (PHASE) { r = r0 + r * a.g.div_h; s = s0 + s * a.g.div_w; }
+                int rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
                 if (MODE <= 1) {
                     bool ok = kk < g.Kred && n < g.Ncols;
                     rb[i] = ld16(ok ? a.Bw + (rowoff + n) : zero_src);
@@ -305,8 +340,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
     const bool vec4 = (g.Ncols & 3) == 0;
 #pragma unroll
     for (int j = 0; j < FM; ++j) {
-        const int m = m0 + wm * WM + j * 32 + (lane & 31);
+        int m = m0 + wm * WM + j * 32 + (lane & 31);
         if (m >= g.M) continue;
+        if (PHASE) {  // back to the pixel of the whole map
+            const int t = m / g.OW, ow = m - t * g.OW;
+            const int n = t / g.OH, oh = t - n * g.OH;
+            m = (n * a.g.OH + oh * a.g.div_h + oh0) * a.g.OW + ow * a.g.div_w + ow0;
+        }
 #pragma unroll
         for (int i = 0; i < FN; ++i) {
 #pragma unroll
@@ -317,7 +357,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = acc[i][j][q * 4 + e];
                 if (a.partial) {
-                    float* o = reinterpret_cast<float*>(a.out) + ((size_t)split * g.M + m) * g.Ncols + n;
+                    float* o = reinterpret_cast<float*>(a.out) + ((size_t)split * a.g.M + m) * g.Ncols + n;
                     if (vec4) {
                         *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
                     } else {
@@ -374,9 +414,9 @@ size_t smem_bytes(const Cfg& c, bool b_tr) {
     return 2 * (a + b);
 }
 
-template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE>
+template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE, bool PHASE = false>
 int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
-    auto kfn = igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE>;
+    auto kfn = igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE, PHASE>;
     static std::atomic<bool> attr_done{false};  // one attribute call per instantiation
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
@@ -389,12 +429,45 @@ int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
     return check_launch("igemm");
 }
 
+bool phased(const GemmGeom& g, bool b_tr) { return b_tr && g.div_h * g.div_w > 1 && g.div_h * g.div_w <= kMaxPhases; }
+
 int classify_mode(const GemmGeom& g, bool b_tr) {
     bool vec_a = (g.IC % 8) == 0;
     bool vec_b = b_tr ? (g.Ncols % 8) == 0 : (g.Kred % 8) == 0;
     if (!(vec_a && vec_b)) return 2;
-    if ((g.IC % BK) == 0 && g.div_h == 1 && g.div_w == 1) return 0;
+    if ((g.IC % BK) == 0 && ((g.div_h == 1 && g.div_w == 1) || phased(g, b_tr))) return 0;
     return 1;
+}
+
+// The phases of a strided data gradient, those with the most taps first (the longest work-groups start first); returns the
+// row tiles of bm pixels in all.
+int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
+    int n = 0;
+    const int images = g.M / (g.OH * g.OW);
+    for (int a = 0; a < g.div_h; ++a)
+        for (int b = 0; b < g.div_w; ++b) {
+            Phase p;
+            p.oh0 = a; p.ow0 = b;
+            p.OH = (g.OH - a + g.div_h - 1) / g.div_h;
+            p.OW = (g.OW - b + g.div_w - 1) / g.div_w;
+            if (a >= g.OH || b >= g.OW) continue;
+            p.r0 = ((g.pad_h - a) % g.div_h + g.div_h) % g.div_h;
+            p.s0 = ((g.pad_w - b) % g.div_w + g.div_w) % g.div_w;
+            p.R = p.r0 < g.R ? (g.R - 1 - p.r0) / g.div_h + 1 : 0;
+            p.S = p.s0 < g.S ? (g.S - 1 - p.s0) / g.div_w + 1 : 0;
+            p.pad_h = (g.pad_h - a - p.r0) / g.div_h;  // exact
+            p.pad_w = (g.pad_w - b - p.s0) / g.div_w;
+            p.M = images * p.OH * p.OW;
+            ph[n++] = p;
+        }
+    std::stable_sort(ph, ph + n, [](const Phase& x, const Phase& y) { return x.R * x.S > y.R * y.S; });
+    int tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        ph[i].tile0 = tiles;
+        tiles += (ph[i].M + bm - 1) / bm;
+    }
+    *nphase = n;
+    return tiles;
 }
 
 }  // namespace
@@ -430,11 +503,13 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
     }
     int mode = classify_mode(g, b_tr);
     int ktiles = (g.Kred + BK - 1) / BK;
+    const bool ph = phased(g, b_tr);
+    if (ph) ktiles = (ktiles + g.div_h * g.div_w - 1) / (g.div_h * g.div_w);  // of the average phase
     auto tiles = [&](int c) {
         return (long)((g.M + kCfgs[c].BM - 1) / kCfgs[c].BM) * ((g.Ncols + kCfgs[c].BN - 1) / kCfgs[c].BN);
     };
     int cfg;
-    if (mode != 0) {
+    if (mode != 0 || (ph && g.Ncols > 64)) {
         cfg = 1;
     } else if (g.Ncols <= 64) {
         cfg = 3;
@@ -445,7 +520,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
     } else {
         cfg = 1;
     }
-    if (g_force_fwd_cfg >= 0 && g_force_fwd_cfg < 8 && (mode == 0 || g_force_fwd_cfg == 1)) cfg = g_force_fwd_cfg;
+    if (g_force_fwd_cfg >= 0 && g_force_fwd_cfg < 8 && (mode == 0 || g_force_fwd_cfg == 1) &&
+        (!ph || g_force_fwd_cfg == 1 || g_force_fwd_cfg == 3))
+        cfg = g_force_fwd_cfg;
     long t = tiles(cfg);
     int nsplit = 1;
     // split the reduction when the tiles alone leave most CUs idle
@@ -571,6 +648,21 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     size_t smem = smem_bytes(c, b_tr);
     int mode = classify_mode(g, b_tr);
     int rc;
+    ka.nphase = 0;
+    if (phased(g, b_tr)) {
+        ka.tiles_m = make_phases(g, c.BM, ka.ph, &ka.nphase);
+        if (plan.cfg == 3 && mode == 0) rc = launch_one<256, 64, 4, 1, true, 0, true>(ka, smem, st);
+        else if (plan.cfg != 1) return set_error(WAP_EINVAL, "internal: strided data gradient on an unsuitable tile");
+        else if (mode == 0) rc = launch_one<128, 128, 2, 2, true, 0, true>(ka, smem, st);
+        else if (mode == 1) rc = launch_one<128, 128, 2, 2, true, 1, true>(ka, smem, st);
+        else rc = launch_one<128, 128, 2, 2, true, 2, true>(ka, smem, st);
+        if (rc != WAP_OK) return rc;
+        if (ev_mid) (void)hipEventRecord(ev_mid, st);
+        if (ka.partial)
+            return launch_reduce_bf16(reinterpret_cast<const float*>(ws), plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias, relu,
+                                      out, st, relu_mask, colsum);
+        return WAP_OK;
+    }
 #define WAP_DISPATCH(BM, BN, WMv, WNv)                                                     \
     (b_tr ? (mode == 0 ? launch_one<BM, BN, WMv, WNv, true, 0>(ka, smem, st)                \
                        : mode == 1 ? launch_one<BM, BN, WMv, WNv, true, 1>(ka, smem, st)    \
@@ -632,13 +724,18 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 10) return "fc_fwd_kernel";
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
+    if (phased(g, b_tr)) {
+        static const char* phase_names[2][3] = {{"igemm_kernel<128,128,2,2,true,0,true>", "igemm_kernel<128,128,2,2,true,1,true>", "igemm_kernel<128,128,2,2,true,2,true>"},
+                                                {"igemm_kernel<256,64,4,1,true,0,true>", "", ""}};
+        return phase_names[plan.cfg == 3 ? 1 : 0][classify_mode(g, b_tr)];
+    }
     static const char* names[5][2][3] = {
-        {{"igemm_kernel<256,256,2,4,false,0>", "", ""}, {"igemm_kernel<256,256,2,4,true,0>", "", ""}},
-        {{"igemm_kernel<128,128,2,2,false,0>", "igemm_kernel<128,128,2,2,false,1>", "igemm_kernel<128,128,2,2,false,2>"},
-         {"igemm_kernel<128,128,2,2,true,0>", "igemm_kernel<128,128,2,2,true,1>", "igemm_kernel<128,128,2,2,true,2>"}},
-        {{"igemm_kernel<64,256,1,4,false,0>", "", ""}, {"igemm_kernel<64,256,1,4,true,0>", "", ""}},
-        {{"igemm_kernel<256,64,4,1,false,0>", "", ""}, {"igemm_kernel<256,64,4,1,true,0>", "", ""}},
-        {{"igemm_kernel<256,256,2,2,false,0>", "", ""}, {"igemm_kernel<256,256,2,2,true,0>", "", ""}},
+        {{"igemm_kernel<256,256,2,4,false,0,false>", "", ""}, {"igemm_kernel<256,256,2,4,true,0,false>", "", ""}},
+        {{"igemm_kernel<128,128,2,2,false,0,false>", "igemm_kernel<128,128,2,2,false,1,false>", "igemm_kernel<128,128,2,2,false,2,false>"},
+         {"igemm_kernel<128,128,2,2,true,0,false>", "igemm_kernel<128,128,2,2,true,1,false>", "igemm_kernel<128,128,2,2,true,2,false>"}},
+        {{"igemm_kernel<64,256,1,4,false,0,false>", "", ""}, {"igemm_kernel<64,256,1,4,true,0,false>", "", ""}},
+        {{"igemm_kernel<256,64,4,1,false,0,false>", "", ""}, {"igemm_kernel<256,64,4,1,true,0,false>", "", ""}},
+        {{"igemm_kernel<256,256,2,2,false,0,false>", "", ""}, {"igemm_kernel<256,256,2,2,true,0,false>", "", ""}},
     };
     return names[plan.cfg][b_tr ? 1 : 0][classify_mode(g, b_tr)];
 }

@@ -178,3 +178,40 @@ def test_few_channel_edges(orc, N, H, W, C, K, R, S, stride, pad):
         assert np.array_equal(~np.isfinite(gu.host_f64(dw[:nw]).reshape(K, R, S, C)), np.broadcast_to(taps, (K, R, S, C)))
     finally:
         wap.lib().wap_debug_force(-1, -1, -1)
+
+
+# strided data gradients, one product per phase of the stride: maps that end inside a phase, strides in one or both
+# directions, phases without a tap (1x1 filter), more stride than filter, 64 channels or fewer (thin tile), channels in
+# vectors and odd, the reduction divided over work-groups, with the ReLU derivative of the layer below, and a stride with
+# more phases than the kernel takes
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad,nsplit", [
+    (2, 17, 19, 64, 64, 3, 3, 2, 1, -1), (1, 21, 18, 128, 64, 3, 3, 2, 1, -1), (1, 57, 57, 72, 200, 3, 3, 2, 1, -1),
+    (2, 14, 15, 24, 40, 1, 1, 2, 0, -1), (1, 12, 13, 40, 64, 5, 5, 2, 2, 2), (1, 16, 11, 16, 24, 4, 3, (2, 1), (1, 0), -1),
+    (1, 15, 15, 12, 64, 2, 2, 3, 0, -1), (1, 20, 23, 32, 128, 3, 3, 4, 1, 3), (1, 9, 9, 13, 17, 3, 3, 2, 1, -1),
+    (1, 24, 24, 16, 32, 5, 5, 5, 2, -1), (1, 2, 3, 64, 64, 3, 3, 3, 1, -1)])
+def test_strided_data_gradient_phases(orc, N, H, W, C, K, R, S, stride, pad, nsplit):
+    import paper_1811_01532_amd as wap
+    st = (stride, stride) if isinstance(stride, int) else stride
+    pd = (pad, pad) if isinstance(pad, int) else pad
+    print(f"[case] strided data gradient {(N, H, W, C, K, R, S, st, pd, nsplit)}", flush=True)
+    P, Q = si.out_dim(H, pd[0], R, st[0]), si.out_dim(W, pd[1], S, st[1])
+    gb, wb = si.normal_bf16(si.rng(480, H * W + K), (N, P, Q, K)), si.he_weight_bf16(si.rng(481, R * S + C), (K, R, S, C))
+    xb = si.normal_bf16(si.rng(482, H * W + C), (N, H, W, C))
+    d = wap.conv_desc(N, H, W, C, K, R, S, st, pd)
+    n = N * H * W * C
+    ref = orc.conv2d_bwd_data(orc.bf16_bits_to_f64(gb), orc.bf16_bits_to_f64(wb), (N, H, W, C), st, pd)
+    wap.lib().wap_debug_force(-1, -1, nsplit)
+    try:
+        ws = gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA))
+        for mask in (False, True):
+            dx = torch.full((n + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            if mask:
+                wap.wap_conv2d_bwd_data_relu(d, gu.dev_bf16(gb), gu.dev_bf16(wb), gu.dev_bf16(xb), dx, ws)
+            else:
+                wap.wap_conv2d_bwd_data(d, gu.dev_bf16(gb), gu.dev_bf16(wb), dx, ws)
+            torch.cuda.synchronize()
+            assert torch.isnan(dx[n:]).all()
+            want = np.where(orc.bf16_bits_to_f64(xb) > 0, ref, 0.0) if mask else ref
+            assert gu.rel_err(gu.host_f64(dx[:n]).reshape(N, H, W, C), want) <= gu.TOL_BF16_OUT
+    finally:
+        wap.lib().wap_debug_force(-1, -1, -1)
