@@ -18,6 +18,7 @@
 //     ds_read_b64_tr_b16 instead of a separate transpose pass over the weights;
 //   * blockIdx is remapped so that each XCD (own L2) works on a contiguous range of tiles.
 #include <algorithm>
+#include <type_traits>
 
 #include "wap_internal.h"
 
@@ -45,6 +46,12 @@ struct KArgs {
     GemmGeom g;
     int tiles_m, tiles_n, nsplit, ktiles, ktiles_per_split;
     int relu, partial;
+    int ICp;      // MODE 2: channels rounded up to 8, the reduction's length per tap (no group of 8 crosses a tap)
+    FastDiv dICp;
+};
+// (apart, so that the other launches do not carry the phases in their arguments: with them a short product, 302 x 256 ->
+// 25088, took 35 instead of 22 us)
+struct KPhaseArgs : KArgs {
     int nphase;
     Phase ph[kMaxPhases];
 };
@@ -75,12 +82,15 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
 
 // MODE 0: fast  -- channel counts multiples of 64 / 8, unit tap divisor, 16-byte loads, one tap per tile
 // MODE 1: vec   -- channel counts multiples of 8, any geometry
-// MODE 2: scalar-- anything (2-byte loads)
+// MODE 2: odd   -- any channel counts of at least 8: unaligned 16-byte loads, every tap's channels rounded up to a multiple
+//                  of 8 in the reduction (element by element, as MODE 3 does it, 288 x 4096 -> 3373 took 253 us for dx)
+// MODE 3: scalar-- anything (2-byte loads)
 // PHASE: data gradient of a strided convolution, the row tiles grouped by phase (a.ph): a tap between dy elements costs
 // nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x 57 x 57, 200 -> 72 channels, 3x3
 // stride 2: block forward and backward 141 -> 103 us)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE, bool PHASE>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KArgs a) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
+    const std::conditional_t<PHASE, KPhaseArgs, KArgs> a) {
     constexpr int NT = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int FM = WM / 32, FN = WN / 32;
@@ -110,7 +120,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
     GemmGeom gp;
     int r0 = 0, s0 = 0, oh0 = 0, ow0 = 0;
     int ktiles = a.ktiles, kps = a.ktiles_per_split;
-    if (PHASE) {
+    if constexpr (PHASE) {
         int c = 0;
         while (c + 1 < a.nphase && tm >= a.ph[c + 1].tile0) ++c;
         const Phase& p = a.ph[c];
@@ -119,7 +129,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
         gp.R = p.R; gp.S = p.S; gp.OH = p.OH; gp.OW = p.OW; gp.M = p.M;
         gp.pad_h = p.pad_h; gp.pad_w = p.pad_w;
         gp.mul_h = gp.mul_w = gp.div_h = gp.div_w = 1;
-        gp.Kred = p.R * p.S * gp.IC;
+        gp.Kred = p.R * p.S * (MODE == 2 ? a.ICp : gp.IC);
         r0 = p.r0; s0 = p.s0; oh0 = p.oh0; ow0 = p.ow0;
         ktiles = (gp.Kred + BK - 1) / BK;
         kps = (ktiles + a.nsplit - 1) / a.nsplit;
@@ -175,18 +185,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
         const int RS = g.R * g.S;
         const int kk0 = (MODE == 0) ? ((kt % RS) * g.IC + (kt / RS) * BK) : kt * BK;
         // ---------- gathered operand ----------
-        if (MODE <= 1) {
+        if (MODE <= 2) {
+            const int tapk = MODE == 2 ? a.ICp : g.IC;
             int kk = (MODE == 0) ? kk0 : kk0 + a_vec * 8;
-            int tap = kk / g.IC;
-            int c = kk - tap * g.IC + ((MODE == 0) ? a_vec * 8 : 0);
+            int tap = MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;
+            int c = kk - tap * tapk + ((MODE == 0) ? a_vec * 8 : 0);
             int r = tap / g.S, s = tap - r * g.S;
-            bool kok = (MODE == 0) ? true : (kk < g.Kred);
+            bool kok = (MODE == 0) ? true : tap < g.R * g.S;
+            const int over = MODE == 2 && c + 8 > g.IC ? c + 8 - g.IC : 0;
 #pragma unroll
             for (int i = 0; i < A_PASSES; ++i) {
                 int ih, iw;
                 bool ok = tap_ok(hb[i] + r, wb[i] + s, ih, iw) && kok;
-                int off = abase[i] + (ih * g.IW + iw) * g.IC + c;
-                ra[i] = ld16(ok ? a.A + off : zero_src);
+                int off = abase[i] + (ih * g.IW + iw) * g.IC + c - over;
+                if (MODE == 2) ra[i] = shift_down8(load8_unaligned(ok ? a.A + off : zero_src), over);
+                else ra[i] = ld16(ok ? a.A + off : zero_src);
             }
         } else {
             int rr[8], ss[8], cc[8];
@@ -216,10 +229,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
         if (!B_TR) {
             // Bw[n][kk]: LDS row = output channel, 8 vectors of 8 reduction elements per row
             int kk = kk0 + b_vec * 8;
+            int over = 0;
+            if (MODE == 2) {  // to the position in the unpadded row
+                const int tap = (int)fdiv((uint32_t)kk, a.dICp), c = kk - tap * a.ICp;
+                over = c + 8 > g.IC ? c + 8 - g.IC : 0;
+                kk = tap < g.R * g.S ? tap * g.IC + c - over : g.Kred;
+            }
 #pragma unroll
             for (int i = 0; i < B_PASSES; ++i) {
                 int n = n0 + b_row0 + i * B_RPP;
-                if (MODE <= 1) {
+                if (MODE == 2) {
+                    const bool ok = n < g.Ncols && kk < g.Kred;
+                    rb[i] = shift_down8(load8_unaligned(ok ? a.Bw + (n * g.Kred + kk) : zero_src), over);
+                } else if (MODE <= 1) {
                     bool ok = n < g.Ncols && kk < g.Kred;
                     rb[i] = ld16(ok ? a.Bw + (n * g.Kred + kk) : zero_src);
                 } else {
@@ -235,15 +257,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KAr
         } else {
             // Bw[k][R-1-r][S-1-s][n]: LDS row = reduction index (r,s,k), BN/8 vectors of 8 channels
             int n = n0 + b_vec * 8;
+            const int over = MODE == 2 && n + 8 > g.Ncols ? n + 8 - g.Ncols : 0;
 #pragma unroll
             for (int i = 0; i < B_PASSES; ++i) {
                 int kk = kk0 + b_row0 + i * B_RPP;
-                int tap = (MODE == 0) ? kk0 / g.IC : kk / g.IC;  // one tap per tile in the fast mode
-                int k = kk - tap * g.IC;
+                const int tapk = MODE == 2 ? a.ICp : g.IC;
+                int tap = (MODE == 0) ? kk0 / tapk : MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;  // one tap per tile in the fast mode
+                int k = kk - tap * tapk;
                 int r = tap / g.S, s = tap - r * g.S;
                 if (PHASE) { r = r0 + r * a.g.div_h; s = s0 + s * a.g.div_w; }
                 int rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
-                if (MODE <= 1) {
+                if (MODE == 2) {
+                    const bool ok = tap < g.R * g.S && k < g.IC && over < 8;
+                    rb[i] = shift_down8(load8_unaligned(ok ? a.Bw + (rowoff + n - over) : zero_src), over < 8 ? over : 0);
+                } else if (MODE <= 1) {
                     bool ok = kk < g.Kred && n < g.Ncols;
                     rb[i] = ld16(ok ? a.Bw + (rowoff + n) : zero_src);
                 } else {
@@ -415,7 +442,7 @@ size_t smem_bytes(const Cfg& c, bool b_tr) {
 }
 
 template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE, bool PHASE = false>
-int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
+int launch_one(const std::conditional_t<PHASE, KPhaseArgs, KArgs>& ka, size_t smem, hipStream_t st) {
     auto kfn = igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE, PHASE>;
     static std::atomic<bool> attr_done{false};  // one attribute call per instantiation
     if (!attr_done) {
@@ -429,12 +456,16 @@ int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
     return check_launch("igemm");
 }
 
-bool phased(const GemmGeom& g, bool b_tr) { return b_tr && g.div_h * g.div_w > 1 && g.div_h * g.div_w <= kMaxPhases; }
+// (A 1x1 filter has one tap to skip and pays for writing every pixel's row apart from its neighbours': 64 <- 128 channels on
+// 56 x 56 14.0 against 11.4 us.  3x3: 64 <- 64 on 112 x 112 27 against 52 us, 16 <- 64 on 64 x 64 11.7 against 27.)
+bool phased(const GemmGeom& g, bool b_tr) {
+    return b_tr && g.R * g.S > 1 && g.div_h * g.div_w > 1 && g.div_h * g.div_w <= kMaxPhases;
+}
 
 int classify_mode(const GemmGeom& g, bool b_tr) {
     bool vec_a = (g.IC % 8) == 0;
     bool vec_b = b_tr ? (g.Ncols % 8) == 0 : (g.Kred % 8) == 0;
-    if (!(vec_a && vec_b)) return 2;
+    if (!(vec_a && vec_b)) return g.IC >= 8 && (!b_tr || g.Ncols >= 8) ? 2 : 3;
     if ((g.IC % BK) == 0 && ((g.div_h == 1 && g.div_w == 1) || phased(g, b_tr))) return 0;
     return 1;
 }
@@ -502,7 +533,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
         return p;
     }
     int mode = classify_mode(g, b_tr);
-    int ktiles = (g.Kred + BK - 1) / BK;
+    int ktiles = ((mode == 2 ? g.R * g.S * ((g.IC + 7) / 8 * 8) : g.Kred) + BK - 1) / BK;
     const bool ph = phased(g, b_tr);
     if (ph) ktiles = (ktiles + g.div_h * g.div_w - 1) / (g.div_h * g.div_w);  // of the average phase
     auto tiles = [&](int c) {
@@ -603,7 +634,10 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     const Cfg& c = kCfgs[plan.cfg < 5 ? plan.cfg : 0];
     ka.tiles_m = (g.M + c.BM - 1) / c.BM;
     ka.tiles_n = (g.Ncols + c.BN - 1) / c.BN;
-    ka.ktiles = (g.Kred + BK - 1) / BK;
+    const bool odd = plan.cfg == 1 && classify_mode(g, b_tr) == 2;
+    ka.ICp = (g.IC + 7) / 8 * 8;
+    ka.dICp = make_fastdiv((uint32_t)ka.ICp);
+    ka.ktiles = ((odd ? g.R * g.S * ka.ICp : g.Kred) + BK - 1) / BK;
     ka.nsplit = plan.nsplit;
     ka.ktiles_per_split = (ka.ktiles + plan.nsplit - 1) / plan.nsplit;
     ka.partial = plan.nsplit > 1;
@@ -648,14 +682,16 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     size_t smem = smem_bytes(c, b_tr);
     int mode = classify_mode(g, b_tr);
     int rc;
-    ka.nphase = 0;
     if (phased(g, b_tr)) {
-        ka.tiles_m = make_phases(g, c.BM, ka.ph, &ka.nphase);
-        if (plan.cfg == 3 && mode == 0) rc = launch_one<256, 64, 4, 1, true, 0, true>(ka, smem, st);
+        KPhaseArgs kp;
+        static_cast<KArgs&>(kp) = ka;
+        kp.tiles_m = make_phases(g, c.BM, kp.ph, &kp.nphase);
+        if (plan.cfg == 3 && mode == 0) rc = launch_one<256, 64, 4, 1, true, 0, true>(kp, smem, st);
         else if (plan.cfg != 1) return set_error(WAP_EINVAL, "internal: strided data gradient on an unsuitable tile");
-        else if (mode == 0) rc = launch_one<128, 128, 2, 2, true, 0, true>(ka, smem, st);
-        else if (mode == 1) rc = launch_one<128, 128, 2, 2, true, 1, true>(ka, smem, st);
-        else rc = launch_one<128, 128, 2, 2, true, 2, true>(ka, smem, st);
+        else if (mode == 0) rc = launch_one<128, 128, 2, 2, true, 0, true>(kp, smem, st);
+        else if (mode == 1) rc = launch_one<128, 128, 2, 2, true, 1, true>(kp, smem, st);
+        else if (mode == 2) rc = launch_one<128, 128, 2, 2, true, 2, true>(kp, smem, st);
+        else rc = launch_one<128, 128, 2, 2, true, 3, true>(kp, smem, st);
         if (rc != WAP_OK) return rc;
         if (ev_mid) (void)hipEventRecord(ev_mid, st);
         if (ka.partial)
@@ -666,10 +702,12 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
 #define WAP_DISPATCH(BM, BN, WMv, WNv)                                                     \
     (b_tr ? (mode == 0 ? launch_one<BM, BN, WMv, WNv, true, 0>(ka, smem, st)                \
                        : mode == 1 ? launch_one<BM, BN, WMv, WNv, true, 1>(ka, smem, st)    \
-                                   : launch_one<BM, BN, WMv, WNv, true, 2>(ka, smem, st))   \
+                       : mode == 2 ? launch_one<BM, BN, WMv, WNv, true, 2>(ka, smem, st)    \
+                                   : launch_one<BM, BN, WMv, WNv, true, 3>(ka, smem, st))   \
           : (mode == 0 ? launch_one<BM, BN, WMv, WNv, false, 0>(ka, smem, st)               \
                        : mode == 1 ? launch_one<BM, BN, WMv, WNv, false, 1>(ka, smem, st)   \
-                                   : launch_one<BM, BN, WMv, WNv, false, 2>(ka, smem, st)))
+                       : mode == 2 ? launch_one<BM, BN, WMv, WNv, false, 2>(ka, smem, st)   \
+                                   : launch_one<BM, BN, WMv, WNv, false, 3>(ka, smem, st)))
     if (plan.cfg == 0) {
         if (mode != 0) return set_error(WAP_EINVAL, "internal: large tile needs the fast mode");
         rc = b_tr ? launch_one<256, 256, 2, 4, true, 0>(ka, smem, st)
@@ -725,17 +763,19 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
     if (phased(g, b_tr)) {
-        static const char* phase_names[2][3] = {{"igemm_kernel<128,128,2,2,true,0,true>", "igemm_kernel<128,128,2,2,true,1,true>", "igemm_kernel<128,128,2,2,true,2,true>"},
-                                                {"igemm_kernel<256,64,4,1,true,0,true>", "", ""}};
-        return phase_names[plan.cfg == 3 ? 1 : 0][classify_mode(g, b_tr)];
+        static const char* phase_names[4] = {"igemm_kernel<128,128,2,2,true,0,true>", "igemm_kernel<128,128,2,2,true,1,true>",
+                                             "igemm_kernel<128,128,2,2,true,2,true>", "igemm_kernel<128,128,2,2,true,3,true>"};
+        return plan.cfg == 3 ? "igemm_kernel<256,64,4,1,true,0,true>" : phase_names[classify_mode(g, b_tr)];
     }
-    static const char* names[5][2][3] = {
-        {{"igemm_kernel<256,256,2,4,false,0,false>", "", ""}, {"igemm_kernel<256,256,2,4,true,0,false>", "", ""}},
-        {{"igemm_kernel<128,128,2,2,false,0,false>", "igemm_kernel<128,128,2,2,false,1,false>", "igemm_kernel<128,128,2,2,false,2,false>"},
-         {"igemm_kernel<128,128,2,2,true,0,false>", "igemm_kernel<128,128,2,2,true,1,false>", "igemm_kernel<128,128,2,2,true,2,false>"}},
-        {{"igemm_kernel<64,256,1,4,false,0,false>", "", ""}, {"igemm_kernel<64,256,1,4,true,0,false>", "", ""}},
-        {{"igemm_kernel<256,64,4,1,false,0,false>", "", ""}, {"igemm_kernel<256,64,4,1,true,0,false>", "", ""}},
-        {{"igemm_kernel<256,256,2,2,false,0,false>", "", ""}, {"igemm_kernel<256,256,2,2,true,0,false>", "", ""}},
+    static const char* names[5][2][4] = {
+        {{"igemm_kernel<256,256,2,4,false,0,false>"}, {"igemm_kernel<256,256,2,4,true,0,false>"}},
+        {{"igemm_kernel<128,128,2,2,false,0,false>", "igemm_kernel<128,128,2,2,false,1,false>",
+          "igemm_kernel<128,128,2,2,false,2,false>", "igemm_kernel<128,128,2,2,false,3,false>"},
+         {"igemm_kernel<128,128,2,2,true,0,false>", "igemm_kernel<128,128,2,2,true,1,false>",
+          "igemm_kernel<128,128,2,2,true,2,false>", "igemm_kernel<128,128,2,2,true,3,false>"}},
+        {{"igemm_kernel<64,256,1,4,false,0,false>"}, {"igemm_kernel<64,256,1,4,true,0,false>"}},
+        {{"igemm_kernel<256,64,4,1,false,0,false>"}, {"igemm_kernel<256,64,4,1,true,0,false>"}},
+        {{"igemm_kernel<256,256,2,2,false,0,false>"}, {"igemm_kernel<256,256,2,2,true,0,false>"}},
     };
     return names[plan.cfg][b_tr ? 1 : 0][classify_mode(g, b_tr)];
 }

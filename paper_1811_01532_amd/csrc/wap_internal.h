@@ -36,6 +36,21 @@ inline FastDiv make_fastdiv(uint32_t d) {
 }
 __device__ __forceinline__ uint32_t fdiv(uint32_t x, FastDiv f) { return (__umulhi(x, f.mul) + x) >> f.shift; }
 
+// ---- rows whose length is no multiple of 8 elements: eight consecutive elements by one 16-byte load at any 2-byte address
+// (global memory takes unaligned vector loads).  The last, partial group of a row of `len` >= 8 elements is loaded where it
+// still lies inside the row, `over` = how many of its elements are past the end, and moved down by that many, zeros behind. ----
+__device__ __forceinline__ u32x4 load8_unaligned(const bf16_t* p) {
+    u32x4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+__device__ __forceinline__ u32x4 shift_down8(u32x4 v, int over) {
+    if (over & 4) v = u32x4{v[2], v[3], 0u, 0u};
+    if (over & 2) v = u32x4{v[1], v[2], v[3], 0u};
+    if (over & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+    return v;
+}
+
 constexpr double kPeakBf16Tflops = 2516.6;  // 256 CU x 4096 FLOP/clk x 2.4 GHz
 constexpr double kPeakHbmGBs = 8000.0;
 constexpr int kNumCU = 256;

@@ -27,6 +27,8 @@ struct WArgs {
     WgradGeom g;
     int Kred, Mred;
     int tiles_c, tiles_k, nsplit, ktiles, ktiles_per_split;
+    int Cp;      // MODE 1: channels rounded up to 8, the columns per tap (no group of 8 crosses a tap)
+    FastDiv dCp;
     FastDiv dPQ, dQ;
     SgdFuse sgd;  // w32 != NULL (unsplit reduction, Kred % 4 == 0 only): update the parameters instead of storing dW
 };
@@ -58,7 +60,9 @@ __device__ __forceinline__ bf16x8 tr_frag(const unsigned char* tile, int pitch, 
     return __builtin_bit_cast(bf16x8, both);
 }
 
-// MODE 0: C % 8 == 0 and K % 8 == 0 (16-byte loads); MODE 1: anything (2-byte loads)
+// MODE 0: C % 8 == 0 and K % 8 == 0 (16-byte loads); MODE 1: C and K of at least 8 (unaligned 16-byte loads, every tap's
+// channels rounded up to a multiple of 8 columns; element by element, as MODE 2 does it, 195 x 4096 -> 250 took 23 us);
+// MODE 2: anything (2-byte loads)
 template <int TC, int TK, int WAVES_C, int WAVES_K, int MODE>
 __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WArgs a) {
     constexpr int NT = 64 * WAVES_C * WAVES_K;
@@ -92,12 +96,20 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
     // ---- fixed per-thread column decode of the x operand ----
     const int x_vec = tid % XV, x_row0 = tid / XV;
     const int d_vec = tid % DV, d_row0 = tid / DV;
-    constexpr int NE = (MODE == 0) ? 1 : 8;
+    constexpr int NE = (MODE <= 1) ? 1 : 8;
     int xr[NE], xs[NE], xc[NE];
+    int x_over = 0;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
         int col = col0 + x_vec * 8 + e;
-        if (col < a.Kred) {
+        if (MODE == 1) {
+            const int tap = (int)fdiv((uint32_t)col, a.dCp);
+            int c = col - tap * a.Cp;
+            x_over = c + 8 > g.C ? c + 8 - g.C : 0;
+            xc[e] = c - x_over;
+            xr[e] = tap < g.R * g.S ? tap / g.S : -(1 << 20);
+            xs[e] = tap - tap / g.S * g.S;
+        } else if (col < a.Kred) {
             int tap = col / g.C;
             xc[e] = col - tap * g.C;
             xr[e] = tap / g.S;
@@ -109,6 +121,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         }
     }
     const int ko_d = ko0 + d_vec * 8;
+    const int d_over = MODE == 1 && ko_d + 8 > g.K ? ko_d + 8 - g.K : 0;  // 8 and more: no channel of this group exists
 
     u32x4 rx[X_PASSES], rd[D_PASSES];
     const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block_w);
@@ -126,11 +139,12 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
             int q = rem - p * g.Q;
             int hb = p * g.sh - g.ph, wb = q * g.sw - g.pw;
             int base = n * g.H * g.W * g.C;
-            if (MODE == 0) {
+            if (MODE <= 1) {
                 int h = hb + xr[0], w = wb + xs[0];
                 bool ok = pok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
                 int off = base + (h * g.W + w) * g.C + xc[0];
-                rx[i] = ld16(ok ? a.x + off : zero_src);
+                if (MODE == 1) rx[i] = shift_down8(load8_unaligned(ok ? a.x + off : zero_src), x_over);
+                else rx[i] = ld16(ok ? a.x + off : zero_src);
             } else {
                 unsigned short h16[8];
 #pragma unroll
@@ -147,7 +161,10 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         for (int i = 0; i < D_PASSES; ++i) {
             int pix = pix0 + d_row0 + i * D_RPP;
             bool pok = pix < a.Mred;
-            if (MODE == 0) {
+            if (MODE == 1) {
+                const bool ok = pok && d_over < 8;
+                rd[i] = shift_down8(load8_unaligned(ok ? a.dy + ((size_t)pix * g.K + ko_d - d_over) : zero_src), d_over < 8 ? d_over : 0);
+            } else if (MODE == 0) {
                 bool ok = pok && ko_d < g.K;
                 rd[i] = ld16(ok ? a.dy + ((size_t)pix * g.K + ko_d) : zero_src);
             } else {
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         }
     }
 
-    const bool vec4 = (a.Kred & 3) == 0;
+    const bool vec4 = (a.Kred & 3) == 0 && (MODE != 1 || a.Cp == g.C);
     float* outp = a.out + (size_t)split * g.K * a.Kred;
     if (vec4) {
         // A lane of the MFMA accumulator holds 16-byte groups of 32 different output rows, so a direct store touches
@@ -275,10 +292,25 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         for (int i = 0; i < FC; ++i) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int col = col0 + wc * WC + i * 32 + q * 8 + (lane >> 5) * 4;
+                int col = col0 + wc * WC + i * 32 + q * 8 + (lane >> 5) * 4;
+                int ncol = a.Kred - col;  // columns of this group that exist
+                if (MODE == 1) {
+                    const int tap = (int)fdiv((uint32_t)col, a.dCp), c = col - tap * a.Cp;
+                    ncol = tap < g.R * g.S ? g.C - c : 0;
+                    col = tap * g.C + c;
+                }
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (col + e < a.Kred) outp[(size_t)ko * a.Kred + col + e] = acc[i][j][q * 4 + e];
+                for (int e = 0; e < 4; ++e) {
+                    if (e >= ncol) continue;
+                    const size_t o = (size_t)ko * a.Kred + col + e;
+                    if (a.sgd.w32) {
+                        const float w = sgd_apply(a.sgd.w32[o], acc[i][j][q * 4 + e], a.sgd.lr);
+                        a.sgd.w32[o] = w;
+                        a.sgd.wb[o] = __builtin_bit_cast(unsigned short, (__bf16)w);
+                    } else {
+                        outp[o] = acc[i][j][q * 4 + e];
+                    }
+                }
             }
         }
     }
@@ -310,7 +342,11 @@ int launch_one(const WArgs& wa, size_t smem, hipStream_t st) {
     return check_launch("wgrad");
 }
 
-int classify_mode(const WgradGeom& g) { return ((g.C % 8) == 0 && (g.K % 8) == 0) ? 0 : 1; }
+int classify_mode(const WgradGeom& g) {
+    if ((g.C % 8) == 0 && (g.K % 8) == 0) return 0;
+    return g.C >= 8 && g.K >= 8 ? 1 : 2;
+}
+int padded_cols(const WgradGeom& g) { return classify_mode(g) == 1 ? g.R * g.S * ((g.C + 7) / 8 * 8) : g.R * g.S * g.C; }
 
 }  // namespace
 
@@ -352,7 +388,7 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
         return p;
     }
     const Cfg& c = kCfgs[cfg];
-    long tiles = (long)((Kred + c.TC - 1) / c.TC) * ((g.K + c.TK - 1) / c.TK);
+    long tiles = (long)((padded_cols(g) + c.TC - 1) / c.TC) * ((g.K + c.TK - 1) / c.TK);
     int ktiles = (int)((Mred + BK - 1) / BK);
     long want = (2L * kNumCU + tiles - 1) / tiles;
     long maxs = ktiles / 4;
@@ -385,7 +421,9 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
     wa.Kred = g.R * g.S * g.C;
     wa.Mred = g.N * g.P * g.Q;
     const Cfg& c = kCfgs[plan.cfg < 3 ? plan.cfg : 0];
-    wa.tiles_c = (wa.Kred + c.TC - 1) / c.TC;
+    wa.Cp = (g.C + 7) / 8 * 8;
+    wa.dCp = make_fastdiv((uint32_t)wa.Cp);
+    wa.tiles_c = (padded_cols(g) + c.TC - 1) / c.TC;
     wa.tiles_k = (g.K + c.TK - 1) / c.TK;
     wa.ktiles = (wa.Mred + BK - 1) / BK;
     wa.nsplit = plan.nsplit;
@@ -415,7 +453,9 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
         if (mode != 0) return set_error(WAP_EINVAL, "internal: large wgrad tile needs 16-byte loads");
         rc = launch_one<256, 256, 2, 4, 0>(wa, smem, st);
     } else if (plan.cfg == 1) {
-        rc = mode == 0 ? launch_one<128, 128, 2, 2, 0>(wa, smem, st) : launch_one<128, 128, 2, 2, 1>(wa, smem, st);
+        rc = mode == 0   ? launch_one<128, 128, 2, 2, 0>(wa, smem, st)
+             : mode == 1 ? launch_one<128, 128, 2, 2, 1>(wa, smem, st)
+                         : launch_one<128, 128, 2, 2, 2>(wa, smem, st);
     } else {
         if (mode != 0) return set_error(WAP_EINVAL, "internal: channel-thin wgrad tile needs 16-byte loads");
         rc = launch_one<256, 64, 4, 1, 0>(wa, smem, st);
@@ -446,10 +486,10 @@ const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool un
     if (plan.cfg == 3) return wgrad_patch_kernel_name(g, unpool);
     if (plan.cfg == 4) return wgrad_c3_kernel_name(g);
     if (plan.cfg == 7) return "wgrad_thin_kernel";
-    static const char* names[3][2] = {
-        {"wgrad_kernel<256,256,2,4,0>", ""},
-        {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>"},
-        {"wgrad_kernel<256,64,4,1,0>", ""},
+    static const char* names[3][3] = {
+        {"wgrad_kernel<256,256,2,4,0>", "", ""},
+        {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>", "wgrad_kernel<128,128,2,2,2>"},
+        {"wgrad_kernel<256,64,4,1,0>", "", ""},
     };
     return names[plan.cfg][classify_mode(g)];
 }

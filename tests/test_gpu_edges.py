@@ -215,3 +215,70 @@ def test_strided_data_gradient_phases(orc, N, H, W, C, K, R, S, stride, pad, nsp
             assert gu.rel_err(gu.host_f64(dx[:n]).reshape(N, H, W, C), want) <= gu.TOL_BF16_OUT
     finally:
         wap.lib().wap_debug_force(-1, -1, -1)
+
+
+# channel counts that are no multiple of 8, from 8 (the least for unaligned 16-byte loads) up: every remainder, one group and
+# many, tiles that end inside a group, one pass only odd, each with the update fused behind the weight gradient, and channel
+# counts below 8 (element by element)
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad,nsplit", [
+    (1, 9, 8, 9, 8, 3, 3, 1, 1, -1), (2, 7, 7, 15, 23, 3, 3, 1, 1, -1), (1, 6, 5, 12, 20, 3, 3, 1, 1, 1), (1, 13, 11, 119, 64, 3, 3, 1, 1, -1),
+    (1, 10, 10, 64, 475, 1, 1, 1, 0, -1), (1, 9, 9, 13, 17, 3, 3, 2, 1, -1), (1, 8, 8, 8, 10, 3, 3, 1, 1, 2), (1, 5, 5, 11, 8, 2, 2, 1, 0, -1),
+    (1, 6, 6, 137, 131, 3, 3, 1, 1, 3), (3, 5, 4, 14, 129, 1, 3, 1, (0, 1), -1), (1, 6, 7, 7, 18, 3, 3, 1, 1, -1), (1, 6, 7, 18, 5, 3, 3, 1, 1, -1)])
+def test_odd_channel_edges(orc, N, H, W, C, K, R, S, stride, pad, nsplit):
+    import paper_1811_01532_amd as wap
+    st = (stride, stride) if isinstance(stride, int) else stride
+    pd = (pad, pad) if isinstance(pad, int) else pad
+    print(f"[case] odd channels {(N, H, W, C, K, R, S, st, pd, nsplit)}", flush=True)
+    P, Q = si.out_dim(H, pd[0], R, st[0]), si.out_dim(W, pd[1], S, st[1])
+    xb, wb = si.normal_bf16(si.rng(490, H * W + C), (N, H, W, C)), si.he_weight_bf16(si.rng(491, R * S + C), (K, R, S, C))
+    gb = si.normal_bf16(si.rng(492, H * W + K), (N, P, Q, K))
+    x64, w64, g64 = orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(wb), orc.bf16_bits_to_f64(gb)
+    xd, wd, gd = gu.dev_bf16(xb), gu.dev_bf16(wb), gu.dev_bf16(gb)
+    d = wap.conv_desc(N, H, W, C, K, R, S, st, pd)
+    nx, ny, nw = N * H * W * C, N * P * Q * K, K * R * S * C
+    wap.lib().wap_debug_force(-1, -1, nsplit)
+    try:
+        ws = gu.workspace(max(wap.wap_conv2d_workspace_bytes(d, p) for p in (0, 1, 2)))
+        y = torch.full((ny + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dx = torch.full((nx + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dw = torch.full((nw + 8,), float("nan"), dtype=torch.float32, device="cuda")
+        wap.wap_conv2d_fwd(d, xd, wd, None, y, ws)
+        wap.wap_conv2d_bwd_data(d, gd, wd, dx, ws)
+        wap.wap_conv2d_bwd_weight(d, xd, gd, dw, ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(y[ny:]).all() and torch.isnan(dx[nx:]).all() and torch.isnan(dw[nw:]).all()
+        assert gu.rel_err(gu.host_f64(y[:ny]).reshape(N, P, Q, K), orc.conv2d_fwd(x64, w64, st, pd)) <= gu.TOL_BF16_OUT
+        assert gu.rel_err(gu.host_f64(dx[:nx]).reshape(N, H, W, C), orc.conv2d_bwd_data(g64, w64, (N, H, W, C), st, pd)) <= gu.TOL_BF16_OUT
+        assert gu.rel_err(gu.host_f64(dw[:nw]).reshape(K, R, S, C), orc.conv2d_bwd_weight(x64, g64, (K, R, S, C), st, pd)) <= gu.TOL_F32_OUT
+        w32 = torch.arange(nw, dtype=torch.float32, device="cuda") / nw
+        want = torch.empty_like(w32).copy_(w32)
+        wbf, wbf_want = torch.zeros(nw, dtype=torch.bfloat16, device="cuda"), torch.zeros(nw, dtype=torch.bfloat16, device="cuda")
+        wap.wap_sgd_update(nw, want, dw[:nw].clone(), 0.5, wbf_want)
+        wap.wap_conv2d_bwd_weight_sgd(d, xd, gd, w32, wbf, 0.5, torch.empty(nw, dtype=torch.float32, device="cuda"), ws)
+        torch.cuda.synchronize()
+        assert torch.equal(w32, want) and torch.equal(wbf, wbf_want)
+    finally:
+        wap.lib().wap_debug_force(-1, -1, -1)
+
+
+# the same for fully-connected layers beyond the streaming kernels: odd rows of x, of the weights and of dy
+@pytest.mark.parametrize("B,n_in,n_out", [(130, 67, 9), (200, 255, 250), (129, 257, 40), (288, 96, 333), (150, 8, 11), (140, 300, 8)])
+def test_odd_fc_edges(orc, B, n_in, n_out):
+    import paper_1811_01532_amd as wap
+    print(f"[case] odd fc {(B, n_in, n_out)}", flush=True)
+    xb, Wb = si.normal_bf16(si.rng(500, B + n_in), (B, n_in)), si.he_weight_bf16(si.rng(501, n_in + n_out), (n_out, n_in))
+    gb = si.normal_bf16(si.rng(502, B + n_out), (B, n_out))
+    x64, W64, g64 = orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(Wb), orc.bf16_bits_to_f64(gb)
+    d = wap.fc_desc(B, n_in, n_out, relu=False)
+    ws = gu.workspace(max(wap.wap_fc_workspace_bytes(d, p) for p in (0, 1, 2)))
+    y = torch.full((B * n_out + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dx = torch.full((B * n_in + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dw = torch.full((n_out * n_in + 8,), float("nan"), dtype=torch.float32, device="cuda")
+    xd, Wd, gd = gu.dev_bf16(xb), gu.dev_bf16(Wb), gu.dev_bf16(gb)
+    wap.wap_fc_fwd(d, xd, Wd, None, y, ws)
+    wap.wap_fc_bwd(d, xd, Wd, gd, dx, dw, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(y[B * n_out:]).all() and torch.isnan(dx[B * n_in:]).all() and torch.isnan(dw[n_out * n_in:]).all()
+    assert gu.rel_err(gu.host_f64(y[:B * n_out]).reshape(B, n_out), orc.fc_fwd(x64, W64)) <= gu.TOL_BF16_OUT
+    assert gu.rel_err(gu.host_f64(dx[:B * n_in]).reshape(B, n_in), orc.fc_bwd_data(g64, W64)) <= gu.TOL_BF16_OUT
+    assert gu.rel_err(gu.host_f64(dw[:n_out * n_in]).reshape(n_out, n_in), g64.T @ x64) <= gu.TOL_F32_OUT
