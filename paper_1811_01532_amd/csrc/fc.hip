@@ -285,9 +285,9 @@ bool fc_fwd_supported(const GemmGeom& g) {
 // where the reduction is short (both kernels wait more than they stream) up to 128.  This kernel / the generic one in
 // us: 9216 columns x 4096 rows of Wt at 8 / 32 / 64 batch rows 15.2 / 19.4 / 26.9 and 21.9 / 23.4 / 26.0; 4096 x 4096
 // 10.7 / 15.5 / 22.1 and 14.3 / 17 / 19.3; 25088 x 4096 at 8 / 22 / 64 33.7 / 38.1 / 51.3 and 45.0 / 45.2 / 48.7;
-// 4096 x 1000 at 64 / 100 8.1 / 9.6 and 14.2 / 16.3.
+// 4096 x 1000 at 64 / 100 8.1 / 9.6 and 14.2 / 16.3; 25088 x 512 at 64 / 100 17.7 / 32 and 18.2 / 17.
 bool fc_dx_supported(const GemmGeom& g) {
-    return is_fc(g) && (g.M <= 32 || (g.M <= 128 && g.IC <= 1024)) && g.Ncols >= 64 && g.IC >= 8 &&
+    return is_fc(g) && (g.M <= 32 || (g.M <= 128 && g.IC <= 1024 && (g.M <= 64 || g.Ncols <= 8192))) && g.Ncols >= 64 && g.IC >= 8 &&
            below_2g((double)g.IC * g.Ncols) && below_2g((double)g.M * g.IC);
 }
 
