@@ -473,6 +473,20 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     constexpr int OPITCH = BN * 2 + 16;  // bytes per pixel row in the staging buffer
     constexpr int VPR = BN / 8;          // 16-byte vectors per pixel row
     constexpr int RPP = NT / VPR;        // pixel rows stored per pass
+    constexpr int NR = BM / RPP;
+    static_assert(NR * RPP == BM, "whole passes");
+    // The mask of this thread's rows is fetched before the accumulators are converted: fetched row by row between the
+    // stores (which the compiler may not move it over) every row waited for memory, 14 times per 224-pixel tile.
+    u32x4 mk[NR];
+    auto out_pixel = [&](int row) { return FLAT ? m0 + row : (img * g.OH + oh0 + row / TWD) * g.OW + ow0 + row % TWD; };
+    if (a.mask) {
+#pragma unroll
+        for (int it = 0; it < NR; ++it) {
+            int m = out_pixel(tid / VPR + it * RPP);
+            if (FLAT && m > m_last) m = m_last;  // never stored
+            mk[it] = *reinterpret_cast<const u32x4*>(a.mask + (size_t)m * g.Ncols + n0 + (tid % VPR) * 8);
+        }
+    }
     __syncthreads();  // the last readers of the patch are done
 #pragma unroll
     for (int j = 0; j < FM; ++j) {
@@ -500,13 +514,14 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     }
     __syncthreads();
     float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // column sums over this thread's rows (its 8 channels)
-    for (int row = tid / VPR; row < BM; row += RPP) {
-        const int idx = row;
-        const int m = FLAT ? m0 + idx : (img * g.OH + oh0 + idx / TWD) * g.OW + ow0 + idx % TWD;
+#pragma unroll
+    for (int it = 0; it < NR; ++it) {
+        const int row = tid / VPR + it * RPP;
+        const int m = out_pixel(row);
         if (FLAT && m > m_last) continue;
         u32x4 vv = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + (tid % VPR) * 16);
         const size_t o = (size_t)m * g.Ncols + n0 + (tid % VPR) * 8;
-        if (a.mask) vv = relu_mask8(vv, *reinterpret_cast<const u32x4*>(a.mask + o));
+        if (a.mask) vv = relu_mask8(vv, mk[it]);
         if (a.out) *reinterpret_cast<u32x4*>(a.out + o) = vv;
         if (a.colsum) {
 #pragma unroll

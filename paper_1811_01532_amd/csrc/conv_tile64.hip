@@ -294,6 +294,17 @@ __global__ __launch_bounds__(NT, 3) void conv_tile64_kernel(const T64Args a) {
     constexpr int VPR = BN / 8;          // 16-byte vectors per pixel row
     constexpr int RPP = NT / VPR;        // pixel rows stored per pass
     static_assert(BM * OPITCH <= MAX_PATCH * PITCH, "the staged tile must fit the patch area");
+    constexpr int NR = BM / RPP;
+    static_assert(NR * RPP == BM, "whole passes");
+    // The mask of this thread's rows is fetched before the accumulators are converted: fetched row by row between the
+    // stores (which the compiler may not move it over) every row waited for memory, 8 times per tile.
+    u32x4 mk[NR];
+    auto out_pixel = [&](int row) { return (img * g.OH + oh0 + row / TW) * g.OW + ow0 + row % TW; };
+    if (a.mask) {
+#pragma unroll
+        for (int it = 0; it < NR; ++it)
+            mk[it] = *reinterpret_cast<const u32x4*>(a.mask + (size_t)out_pixel(tid / VPR + it * RPP) * BN + (tid % VPR) * 8);
+    }
     __syncthreads();  // the last readers of the patch are done
     // bias and ReLU are decided once for the whole tile (four straight-line variants), not per register group
     auto stage_tile = [&](auto bias_tag, auto relu_tag) {
@@ -331,11 +342,12 @@ __global__ __launch_bounds__(NT, 3) void conv_tile64_kernel(const T64Args a) {
     __syncthreads();
     float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // column sums over this thread's rows (its 8 channels)
     if (a.out || a.colsum)  // (pooled output only: nothing to store per pixel)
-    for (int row = tid / VPR; row < BM; row += RPP) {
-        const int m = (img * g.OH + oh0 + row / TW) * g.OW + ow0 + row % TW;
+#pragma unroll
+    for (int it = 0; it < NR; ++it) {
+        const int row = tid / VPR + it * RPP;
         u32x4 vv = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + (tid % VPR) * 16);
-        const size_t o = (size_t)m * BN + (tid % VPR) * 8;
-        if (a.mask) vv = relu_mask8(vv, *reinterpret_cast<const u32x4*>(a.mask + o));
+        const size_t o = (size_t)out_pixel(row) * BN + (tid % VPR) * 8;
+        if (a.mask) vv = relu_mask8(vv, mk[it]);
         if (a.out) *reinterpret_cast<u32x4*>(a.out + o) = vv;
         if (a.colsum) {
 #pragma unroll
