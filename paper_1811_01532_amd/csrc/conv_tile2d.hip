@@ -23,6 +23,7 @@
 // Serves the "primary" convolution nodes of Section 3.2.2 (forward and backward halves of t_c, Eq. 1).
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "wap_internal.h"
 
@@ -100,11 +101,17 @@ __device__ __forceinline__ u32x4 unpool_select8(u32x4 v, u32x2 am, unsigned code
     return v;
 }
 
+template <typename F, int... T>
+__device__ __forceinline__ void each_tap(F& f, std::integer_sequence<int, T...>) {
+    (f(std::integral_constant<int, T>{}), ...);
+}
+
 // FN: 32-channel blocks per wavefront; TW: tile width in pixels; FM: 32-pixel fragments per wavefront;
 // PG: wavefronts along the pixels (4 / PG along the channels).  Tile = 32*FM*PG pixels x 32*FN*(4/PG) channels.
 // TW = 0: flat tiles, 32*FM*PG consecutive output pixels in raster order (they may straddle rows and images;
 // the patch is then a run of the zero-padded image in raster order).  UP: pooled input operand.
-template <int FN, int TW, int FM, int PG, bool UP, bool T9>
+// ST: filter side of the straight-line slice body (3 or 5), 0 = tap loop.
+template <int FN, int TW, int FM, int PG, bool UP, int ST>
 __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     constexpr bool FLAT = (TW == 0);
     constexpr int BM = 32 * FM * PG;
@@ -316,13 +323,16 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     // load may stay in flight before its wavefront needs it, and a wavefront's loads return in order, so the first
     // weight load issued after the patch loads of the next slice drags those along: with sets filled one tap ahead
     // the patch latency (first touch: HBM or the memory-side cache) would be exposed once per slice.
-    //   T9 (3x3 filters, one channel block per wavefront): the nine taps of a slice are straight-line code, the sets
-    //   a ring of three filled two taps ahead that rotates without copies, the patch loads go out right behind the
-    //   weight loads of tap 0 (three taps until a younger weight load is needed) and reach LDS after tap 7.  No branch
-    //   in the slice body: the loads / stores / barrier of a slice beyond the last are issued anyway (clamped to the
-    //   last slice, written to the idle buffer), so the compiler's counter waits are exact.
+    //   ST (square filters of 3 or 5 taps a side): the taps of a slice are straight-line code, the sets a ring of ST that
+    //   is filled ST - 1 taps ahead and rotates without copies (ST divides the taps, so every slice starts at the same set),
+    //   the patch loads go out right behind the weight loads of tap 0 (ST taps until a younger weight load is needed) and
+    //   reach LDS after three quarters of the taps (3x3: after tap 7).  No branch in the slice body: the loads / stores /
+    //   barrier of a slice beyond the last are issued anyway (clamped to the last slice, written to the idle buffer), so
+    //   the compiler's counter waits are exact.
     //   otherwise: a tap loop with two sets, the new one copied over the current one at the end of every tap.
-    constexpr int NSET = T9 ? 3 : 2;
+    constexpr int NSET = ST ? ST : 2;
+    constexpr int STD = ST ? ST : 1, RSC = STD * STD;
+    constexpr int STORE_TAP = ST == 3 ? 7 : RSC * 3 / 4;
     bf16x8 w[NSET][2][FN];
     issue_patch(cs0);
 #pragma unroll
@@ -366,22 +376,22 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
         unsigned char* nxt = smem + ((cs - cs0 + 1) & 1) * a.buf_bytes;
         const int csn = cs + 1 < ncs ? cs + 1 : cs;  // the next slice, clamped
         __builtin_amdgcn_s_setprio(1);
-        if constexpr (T9) {
-            auto tap9 = [&](auto tap_tag) {
+        if constexpr (ST != 0) {
+            auto tap = [&](auto tap_tag) {
                 constexpr int T = decltype(tap_tag)::value;
-                constexpr int U = T % 3;
-                constexpr int PT = (T + 2) % 9;           // the tap whose weights are fetched now
-                const int tapoff = (T / 3) * a.RWB + (T % 3) * PITCH;
-                const int tapoff1 = ((T + 1) / 3) * a.RWB + ((T + 1) % 3) * PITCH;
+                constexpr int U = T % NSET;
+                constexpr int PT = (T + NSET - 1) % RSC;  // the tap whose weights are fetched now
+                const int tapoff = (T / STD) * a.RWB + (T % STD) * PITCH;
+                const int tapoff1 = ((T + 1) / STD) * a.RWB + ((T + 1) % STD) * PITCH;
                 __builtin_amdgcn_sched_barrier(0);
-                load_w(T + 2 >= 9 ? csn : cs, PT, w[(U + 2) % 3]);
+                load_w(T + NSET - 1 >= RSC ? csn : cs, PT, w[(U + NSET - 1) % NSET]);
                 if (T == 0) issue_patch(csn);
                 step(w[U][0], cur, tapoff + 32, true);
                 if (T == 0) pin_step(std::integral_constant<int, 2 * FN + (UP ? 2 : 1) * NRP>{});
                 else pin_step(std::integral_constant<int, 2 * FN>{});
                 __builtin_amdgcn_sched_barrier(0);
-                if (T == 8) {
-                    // every wavefront has written its share of the next slice (after tap 7; the LDS pipe executes a
+                if (T == RSC - 1) {
+                    // every wavefront has written its share of the next slice (after tap STORE_TAP; the LDS pipe executes a
                     // wavefront's operations in order and fragment reads issued after those writes have returned) and
                     // nobody reads the buffer that slice c+2 will overwrite before this point again
                     __builtin_amdgcn_s_barrier();
@@ -392,20 +402,12 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
                 }
                 pin_step(std::integral_constant<int, 0>{});
                 __builtin_amdgcn_sched_barrier(0);
-                if (T == 7) {
+                if (T == STORE_TAP) {
                     store_patch(nxt);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
-            tap9(std::integral_constant<int, 0>{});
-            tap9(std::integral_constant<int, 1>{});
-            tap9(std::integral_constant<int, 2>{});
-            tap9(std::integral_constant<int, 3>{});
-            tap9(std::integral_constant<int, 4>{});
-            tap9(std::integral_constant<int, 5>{});
-            tap9(std::integral_constant<int, 6>{});
-            tap9(std::integral_constant<int, 7>{});
-            tap9(std::integral_constant<int, 8>{});
+            each_tap(tap, std::make_integer_sequence<int, RSC>{});
         } else {
             const bool has_next = cs + 1 < ncs;
             if (has_next) issue_patch(cs + 1);
@@ -595,9 +597,9 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     }
 }
 
-template <int FN, int TW, int FM, int PG, bool UP, bool T9>
+template <int FN, int TW, int FM, int PG, bool UP, int ST>
 int launch_tile2d_w(const TArgs& ta, size_t smem, hipStream_t st) {
-    auto kfn = conv_tile2d_kernel<FN, TW, FM, PG, UP, T9>;
+    auto kfn = conv_tile2d_kernel<FN, TW, FM, PG, UP, ST>;
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
@@ -608,12 +610,17 @@ int launch_tile2d_w(const TArgs& ta, size_t smem, hipStream_t st) {
     hipLaunchKernelGGL(kfn, dim3(ta.tiles_m * ta.tiles_n * ta.nsplit), dim3(NT), smem, st, ta);
     return check_launch("conv_tile2d");
 }
-// straight-line 3x3 slices with the three-set weight ring for one-block wavefronts, else the tap loop
+// straight-line 3x3 slices; 5x5 ones on the flat 192 x 64 tiles (the tilings such layers get); else the tap loop
+constexpr int tile2d_st(int tw, int pg, bool up, int R, int S) {
+    return R == 3 && S == 3 ? 3 : R == 5 && S == 5 && tw == 0 && pg == 2 && !up ? 5 : 0;
+}
 template <int FN, int TW, int FM, int PG, bool UP>
 int launch_tile2d_u(const TArgs& ta, size_t smem, hipStream_t st) {
-    constexpr bool CAN9 = true;
-    if (CAN9 && ta.g.R == 3 && ta.g.S == 3) return launch_tile2d_w<FN, TW, FM, PG, UP, CAN9>(ta, smem, st);
-    return launch_tile2d_w<FN, TW, FM, PG, UP, false>(ta, smem, st);
+    const int side = tile2d_st(TW, PG, UP, ta.g.R, ta.g.S);
+    if (side == 3) return launch_tile2d_w<FN, TW, FM, PG, UP, 3>(ta, smem, st);
+    if constexpr (tile2d_st(TW, PG, UP, 5, 5) == 5)
+        if (side == 5) return launch_tile2d_w<FN, TW, FM, PG, UP, 5>(ta, smem, st);
+    return launch_tile2d_w<FN, TW, FM, PG, UP, 0>(ta, smem, st);
 }
 template <int FN, int TW, int FM, int PG>
 int launch_tile2d_t(const TArgs& ta, size_t smem, hipStream_t st) {
@@ -835,22 +842,23 @@ const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
     if (!tile && tile64_width(g)) return tile64_kernel_name(g, unpool);
     const TileCfg c = tile_cfg(g, tile);
     const int u = unpool ? 1 : 0, t9 = (g.R == 3 && g.S == 3) ? 1 : 0;
-    static const char* n1[2][2] = {{"conv_tile2d_kernel<1,28,7,1,false,false>", "conv_tile2d_kernel<1,28,7,1,false,true>"},
-                                   {"conv_tile2d_kernel<1,28,7,1,true,false>", "conv_tile2d_kernel<1,28,7,1,true,true>"}};
-    static const char* n2[2][2] = {{"conv_tile2d_kernel<1,0,7,1,false,false>", "conv_tile2d_kernel<1,0,7,1,false,true>"},
-                                   {"conv_tile2d_kernel<1,0,7,1,true,false>", "conv_tile2d_kernel<1,0,7,1,true,true>"}};
-    static const char* n3[2][2] = {{"conv_tile2d_kernel<1,0,3,2,false,false>", "conv_tile2d_kernel<1,0,3,2,false,true>"},
-                                   {"conv_tile2d_kernel<1,0,3,2,true,false>", "conv_tile2d_kernel<1,0,3,2,true,true>"}};
-    static const char* n22[2][2] = {{"conv_tile2d_kernel<1,0,2,1,false,false>", "conv_tile2d_kernel<1,0,2,1,false,true>"},
-                                    {"conv_tile2d_kernel<1,0,2,1,true,false>", "conv_tile2d_kernel<1,0,2,1,true,true>"}};
+    static const char* n1[2][2] = {{"conv_tile2d_kernel<1,28,7,1,false,0>", "conv_tile2d_kernel<1,28,7,1,false,3>"},
+                                   {"conv_tile2d_kernel<1,28,7,1,true,0>", "conv_tile2d_kernel<1,28,7,1,true,3>"}};
+    static const char* n2[2][2] = {{"conv_tile2d_kernel<1,0,7,1,false,0>", "conv_tile2d_kernel<1,0,7,1,false,3>"},
+                                   {"conv_tile2d_kernel<1,0,7,1,true,0>", "conv_tile2d_kernel<1,0,7,1,true,3>"}};
+    static const char* n3[2][2] = {{"conv_tile2d_kernel<1,0,3,2,false,0>", "conv_tile2d_kernel<1,0,3,2,false,3>"},
+                                   {"conv_tile2d_kernel<1,0,3,2,true,0>", "conv_tile2d_kernel<1,0,3,2,true,3>"}};
+    static const char* n22[2][2] = {{"conv_tile2d_kernel<1,0,2,1,false,0>", "conv_tile2d_kernel<1,0,2,1,false,3>"},
+                                    {"conv_tile2d_kernel<1,0,2,1,true,0>", "conv_tile2d_kernel<1,0,2,1,true,3>"}};
     if (c.variant == 1) return n1[u][t9];
     if (c.variant == 2) return c.fm == 7 ? n2[u][t9] : n22[u][t9];
+    if (c.variant == 3 && tile2d_st(0, 2, unpool, g.R, g.S) == 5) return "conv_tile2d_kernel<1,0,3,2,false,5>";
     if (c.variant == 3) return n3[u][t9];
     static const char* names[2][2][3] = {
-        {{"conv_tile2d_kernel<2,32,4,2,false,false>", "conv_tile2d_kernel<2,16,4,2,false,false>", "conv_tile2d_kernel<2,8,4,2,false,false>"},
-         {"conv_tile2d_kernel<2,32,4,2,false,true>", "conv_tile2d_kernel<2,16,4,2,false,true>", "conv_tile2d_kernel<2,8,4,2,false,true>"}},
-        {{"conv_tile2d_kernel<2,32,4,2,true,false>", "conv_tile2d_kernel<2,16,4,2,true,false>", "conv_tile2d_kernel<2,8,4,2,true,false>"},
-         {"conv_tile2d_kernel<2,32,4,2,true,true>", "conv_tile2d_kernel<2,16,4,2,true,true>", "conv_tile2d_kernel<2,8,4,2,true,true>"}}};
+        {{"conv_tile2d_kernel<2,32,4,2,false,0>", "conv_tile2d_kernel<2,16,4,2,false,0>", "conv_tile2d_kernel<2,8,4,2,false,0>"},
+         {"conv_tile2d_kernel<2,32,4,2,false,3>", "conv_tile2d_kernel<2,16,4,2,false,3>", "conv_tile2d_kernel<2,8,4,2,false,3>"}},
+        {{"conv_tile2d_kernel<2,32,4,2,true,0>", "conv_tile2d_kernel<2,16,4,2,true,0>", "conv_tile2d_kernel<2,8,4,2,true,0>"},
+         {"conv_tile2d_kernel<2,32,4,2,true,3>", "conv_tile2d_kernel<2,16,4,2,true,3>", "conv_tile2d_kernel<2,8,4,2,true,3>"}}};
     return names[u][t9][c.tw == 32 ? 0 : c.tw == 16 ? 1 : 2];
 }
 
