@@ -503,7 +503,7 @@ int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
 
 }  // namespace
 
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
     GemmPlan p;
     if (!b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 8) && conv_c3_fwd_supported(g)) {
         p.cfg = 8;
@@ -580,7 +580,10 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr) {
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 6 || cfg == 7)) {
         int tile = 0;
         const bool pools = !b_tr && cfg == 7 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
-        const int sp = pools ? 1 : tile2d_split(g, cfg < 6, &tile);
+        // (below some 0.2 GFLOP the packing launch costs more than the better kernel saves: 128 -> 128 channels on 4 x 12 x 12,
+        // forward and backward 53 us without and 58 with)
+        const bool worth = cfg == 7 || prepacked || 2.0 * g.M * g.Ncols * g.Kred >= 1.9e8;
+        const int sp = pools || !worth ? 1 : tile2d_split(g, cfg < 6, &tile);
         if (sp > 1 && (b_tr || (size_t)sp * g.M * g.Ncols * sizeof(float) + wreg_wt_bytes(g) <= WAP_STATIC_SCRATCH_BYTES)) {
             cfg = 7;
             p.tile = tile;

@@ -289,7 +289,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
                              size_t w, size_t o) {
         Op op;
         op.kind = kind; op.name = name; op.gg = g; op.b_tr = b_tr; op.relu = relu;
-        op.gp = plan_fwd_like(g, b_tr);
+        op.gp = plan_fwd_like(g, b_tr, true);
         op.kernel = fwd_like_kernel_name(g, b_tr, op.gp);
         op.flops = 2.0 * g.M * (double)g.Ncols * g.Kred;
         op.bytes = 2.0 * ((double)B * g.IH * g.IW * g.IC + (double)g.Kred * g.Ncols + (double)g.M * g.Ncols);
@@ -468,7 +468,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
             const WgradGeom wgm = geom_conv_wgrad(d);
             const GemmGeom dgm = geom_conv_dgrad(d);
             unpool = wgrad_fuses_unpool(wgm, plan_wgrad(wgm)) &&
-                     (i == 0 || fwd_like_fuses_unpool(dgm, plan_fwd_like(dgm, true)));
+                     (i == 0 || fwd_like_fuses_unpool(dgm, plan_fwd_like(dgm, true, true)));
         }
         if (unpool) {
             Op& prod = p->ops.back();  // the data gradient of the layer above (conv or fc6): it wrote g_cur

@@ -114,7 +114,8 @@ constexpr int kTileSplit64 = 1, kTileSplit224 = 2, kTileSplit192 = 3;
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred
 //  TR : Bw[k][R-1-r][S-1-s][n]  (data gradient: reduction (r,s,k), k innermost): n contiguous
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr);
+// prepacked: the caller keeps the weights in packed order (a step plan); else a packing launch in front is part of the price
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked = false);
 int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf16_t* A,
                     const bf16_t* Bw, const float* bias, bool relu, bf16_t* out, void* ws,
                     hipStream_t st, hipEvent_t ev_mid = nullptr,  // ev_mid: recorded between kernel and split epilogue

@@ -361,8 +361,11 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
     else if (g.K >= 192 && Kred >= 256) {
         // A short reduction over a large output (the FC layers at training minibatches) is bound by the epilogue's
         // stores: smaller tiles put several work-groups on a CU, whose store phases then overlap.
+        // So does a layer of little work, whose few large tiles leave CUs idle or split the reduction thin (64 -> 192 channels,
+        // 5x5 on 27 x 27 at 4 images 26.0 -> 19.6 us, at 8 30.2 -> 25.5, 256 -> 320 on 13 x 13 at 4 28.0 -> 23.0; from about
+        // 6 GFLOP on the large tiles win: 14 GFLOP 56 against 61).
         const long small_tiles = (long)((Kred + 127) / 128) * ((g.K + 127) / 128);
-        cfg = (Mred <= 256 && small_tiles >= kNumCU) ? 1 : 0;
+        cfg = (Mred <= 256 && small_tiles >= kNumCU) || 2.0 * Mred * g.K * Kred < 6e9 ? 1 : 0;
     } else cfg = 1;
     if (g_force_wgrad_cfg >= 0 && g_force_wgrad_cfg < 3 && (mode == 0 || g_force_wgrad_cfg == 1)) cfg = g_force_wgrad_cfg;
     if ((g_force_wgrad_cfg < 0 || g_force_wgrad_cfg == 4) && wgrad_c3_supported(g)) {

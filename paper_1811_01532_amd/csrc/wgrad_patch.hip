@@ -1,4 +1,4 @@
-// Weight gradient of a stride-1 3x3 convolution with the input PATCH resident in LDS (gfx950):
+// Weight gradient of a stride-1 3x3 or 5x5 convolution with the input PATCH resident in LDS (gfx950):
 //   dw[k][(r,s,c)] = sum over pixels (n,p,q) of dy[n,p,q,k] * x[n, p-ph+r, q-pw+s, c]
 // (backward half of t_c in Eq. 1; the output is the weight-sized tensor whose aggregation cost the
 // platform model of Section 3.2.3 prices).
@@ -13,6 +13,9 @@
 // multiple of 4 (at least 16) columns whose surplus pixels carry dy = 0.
 //   * 12 wavefronts, three per SIMD whatever the dispatcher's placement: wavefront (r, cb, kh) owns filter
 //     row r, the 32-channel half cb of the x slice and FD 32-channel blocks of dy: 3 taps x FD tiles;
+//     (5x5: ten wavefronts (r, cb) with 5 taps each and ONE 32-channel block of dy per work-group: two would need 160
+//     accumulator registers beside three wavefronts per SIMD.  64 -> 192 channels on 27 x 27, generic kernel / this one
+//     with their reductions, us: at 32 images 56 / 42, at 100 106 / 74; 64 -> 64 on 56 x 56 at 32 82 / 46);
 //   * one work-group per CU.  LDS holds two tile buffers: while the wavefronts run the MFMAs of tile i out
 //     of one buffer, their global loads of tile i+2 are in flight and tile i+1 (already in registers) is
 //     written to the other buffer, so a tile costs one barrier and no exposed load or store phase;
@@ -32,11 +35,11 @@ namespace wap {
 
 namespace {
 
-constexpr int NT = 768;       // 12 wavefronts
+constexpr int wavefronts(int rf) { return rf == 3 ? 12 : 10; }
 constexpr int XPITCH = 192;   // LDS bytes per patch pixel: 64 channels + 64 bytes, so that the 4 rows x 64 bytes a
                               // half-wavefront touches in one transposing read fall into 4 disjoint bank groups
 constexpr int DCAP = 128;     // most dy rows (virtual pixels) per tile: 8 reduction steps of 16
-constexpr int PVMAX = 3;      // most wavefront loads of the patch per wavefront and tile: 36 per work-group
+constexpr int pv_max(int rf) { return rf == 3 ? 3 : 4; }  // most wavefront loads of the patch per wavefront and tile
 constexpr unsigned OOB = 0x80000000u;  // both tensors are below 2 GiB (checked on the host)
 constexpr size_t LDS_BYTES = 160 * 1024;
 
@@ -46,8 +49,8 @@ constexpr size_t LDS_BYTES = 160 * 1024;
 //   MODE 1: virtual tile width 32, a step is half a tile row;
 //   MODE 2: any virtual width that is a multiple of 4, tile height 4, a step is a block of 4 rows x 4 columns.
 template <int MODE> struct StepMap;
-template <> struct StepMap<0> { static constexpr int VW = 16, PWP = 18; };
-template <> struct StepMap<1> { static constexpr int VW = 32, PWP = 34; };
+template <> struct StepMap<0> { static constexpr int VW = 16; };
+template <> struct StepMap<1> { static constexpr int VW = 32; };
 
 struct WPArgs {
     const bf16_t* x;
@@ -96,24 +99,27 @@ __device__ __forceinline__ u32x4 unpool_select8(u32x4 v, u32x2 am, unsigned code
 }
 
 // FD: 32-channel dy blocks per wavefront; the work-group covers 64 * FD output channels.  UP: dy arrives pooled.
-// NK: reduction steps per tile (tile pixels / 16).
-template <int FD, bool UP, int MODE, int NK>
-__global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
-    constexpr int KO = 64 * FD;             // output channels per work-group
-    constexpr int DPITCH = KO * 2 + 64;     // same bank argument as XPITCH
+// NK: reduction steps per tile (tile pixels / 16).  RF: filter side; 5 with FD = 1 only, a work-group then covers 32
+// output channels.
+template <int FD, bool UP, int MODE, int NK, int RF>
+__global__ __launch_bounds__(64 * wavefronts(RF), 3) void wgrad_patch_kernel(const WPArgs a) {
+    static_assert(RF == 3 || (RF == 5 && FD == 1 && !UP), "5x5: one dy block, full-size dy");
+    constexpr int NW = wavefronts(RF);
+    constexpr int KO = RF == 3 ? 64 * FD : 32;             // output channels per work-group
+    constexpr int DPITCH = RF == 3 ? KO * 2 + 64 : 192;    // same bank argument as XPITCH
     constexpr int DVP = KO / 8;             // 16-byte vectors per dy pixel
     constexpr int PPW = 64 / DVP;           // dy pixels (UP: pooling windows) one wavefront load covers
-    // wavefront loads per wavefront and tile: 12 wavefronts share (tile rows + 2) x segments loads of the patch and
+    // wavefront loads per wavefront and tile: the wavefronts share (tile rows + RF - 1) x segments loads of the patch and
     // tile rows x segments loads of dy (pooled dy: one)
     constexpr int TVW = MODE == 0 ? 16 : MODE == 1 ? 32 : 4 * NK, TTH = NK * 16 / TVW;
-    constexpr int PV = ((TTH + 2) * ((TVW + 2 + 7) / 8) + 11) / 12;
-    constexpr int DV = UP ? 1 : (TTH * ((TVW + PPW - 1) / PPW) + 11) / 12;
-    static_assert(PV <= PVMAX && DV <= 3, "tile too large for the loader");
+    constexpr int PV = ((TTH + RF - 1) * ((TVW + RF - 1 + 7) / 8) + NW - 1) / NW;
+    constexpr int DV = UP ? 1 : (TTH * ((TVW + PPW - 1) / PPW) + NW - 1) / NW;
+    static_assert(PV <= pv_max(RF) && DV <= 3, "tile too large for the loader");
     extern __shared__ __align__(16) unsigned char smem[];
     const WgradGeom& g = a.g;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: everything derived from it stays scalar
-    const int r = wave >> 2, cb = (wave >> 1) & 1, kh = wave & 1;
+    const int r = RF == 3 ? wave >> 2 : wave >> 1, cb = RF == 3 ? (wave >> 1) & 1 : wave & 1, kh = RF == 3 ? wave & 1 : 0;
 
     const int total = a.ncombo * a.nsplit;
     const int logical = xcd_remap(blockIdx.x, total);
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
     // constant offset and one comparison of its pixel against the row's valid columns.  The last segment of a row
     // is moved back so that it ends with the row: it then repeats a few pixels of its neighbour (both write the
     // same bytes to the same LDS address), and no lane ever falls outside its row.  Wavefront w takes the loads
-    // w, w + 12, w + 24 of the tile. ----
+    // w, w + NW, w + 2 NW, ... of the tile. ----
     auto seg_start = [](int seg, int per, int row_len) {  // first pixel of segment seg of a row of row_len >= per pixels
         const int p0 = seg * per;
         return p0 + per > row_len ? row_len - per : p0;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
         const int xbase = (((img * g.H + ih0) * g.W + iw0) * g.C + c0) * 2;  // first patch pixel (may lie before the tensor)
 #pragma unroll
         for (int i = 0; i < PV; ++i) {
-            const int j = wave + 12 * i;
+            const int j = wave + NW * i;
             const int py = (int)fdiv((uint32_t)j, a.dNSEG), px0 = seg_start(j - py * a.NSEG, 8, a.PWp);
             // columns of the segment that lie inside the image
             const int lo = -(iw0 + px0);
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
             const int dbase = (((img * g.P + oh0) * g.Q + ow0) * g.K + ko0) * 2;
 #pragma unroll
             for (int i = 0; i < DV; ++i) {
-                const int j = wave + 12 * i;
+                const int j = wave + NW * i;
                 const int ty = (int)fdiv((uint32_t)j, a.dDSEG), tx0 = seg_start(j - ty * a.DSEG, PPW, a.VW);
                 const bool ok = j < a.NDL && oh0 + ty < g.P && tx0 + lp < a.TWr;
                 const unsigned soff = (unsigned)(dbase + (ty * g.Q + tx0) * g.K * 2);
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
         unsigned char* sD = sX + a.d_off;
 #pragma unroll
         for (int i = 0; i < PV; ++i) {
-            const int j = wave + 12 * i;
+            const int j = wave + NW * i;
             const int py = (int)fdiv((uint32_t)j, a.dNSEG), px0 = seg_start(j - py * a.NSEG, 8, a.PWp);
             if (j < a.NXL) *reinterpret_cast<u32x4*>(sX + (py * a.PWp + px0) * XPITCH + xs) = rp[i];
         }
@@ -214,16 +220,16 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
         } else {
 #pragma unroll
             for (int i = 0; i < DV; ++i) {
-                const int j = wave + 12 * i;
+                const int j = wave + NW * i;
                 const int ty = (int)fdiv((uint32_t)j, a.dDSEG), tx0 = seg_start(j - ty * a.DSEG, PPW, a.VW);
                 if (j < a.NDL) *reinterpret_cast<u32x4*>(sD + (ty * a.VW + tx0) * DPITCH + dsl) = rd[i];
             }
         }
     };
 
-    f32x16 acc[3][FD];  // [tap s of filter row r][32-channel block of dy]
+    f32x16 acc[RF][FD];  // [tap s of filter row r][32-channel block of dy]
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
+    for (int s = 0; s < RF; ++s)
 #pragma unroll
         for (int kb = 0; kb < FD; ++kb)
 #pragma unroll
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
     const int chunk = (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
     // LDS offsets of the lane's first pixel in step 0: patch (tap s = 0 of filter row r) and dy; the second pixel
     // (kl + 4) lies at a compile-time distance (MODE 2: one tile row further, and the tile is 4 * NK columns wide)
-    constexpr int XB = MODE == 2 ? (4 * NK + 2) * XPITCH : 4 * XPITCH;
+    constexpr int XB = MODE == 2 ? (4 * NK + RF - 1) * XPITCH : 4 * XPITCH;
     constexpr int DB = MODE == 2 ? 4 * NK * DPITCH : 4 * DPITCH;
     int xa, da;
     if (MODE == 2) {     // pixel i of a step = row i / 4, column i % 4 of the block
@@ -254,7 +260,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
     // lockstep: without the overlap inside a wavefront all of them wait for LDS at the same time.)  The tile's only
     // barrier sits in the LAST step, in front of the reads that fetch step 0 of the next tile from the other
     // buffer, so the pipeline never drains. ----
-    bf16x8 fd[FD], fx[3];  // dy fragments (one per 32-channel block), patch fragments (one per tap s)
+    bf16x8 fd[FD], fx[RF];  // dy fragments (one per 32-channel block), patch fragments (one per tap s)
     bf16x8 fdn[1];         // FD == 1 only: the single dy fragment is used by every MFMA of a step, so the next one gets registers of its own
     auto read_d = [&](bf16x8& f, int kb, const unsigned char* sB, int dO) {
         f = tr_pair(sB + da + dO + kb * 64, sB + da + dO + DB + kb * 64);
@@ -263,8 +269,8 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
         fx[s] = tr_pair(sB + xa + xo + s * XPITCH, sB + xa + xo + XB + s * XPITCH);
     };
     auto step_x = [](int ks) {  // compile-time distance of step ks from step 0 in the patch
-        return MODE == 0 ? ks * StepMap<0>::PWP * XPITCH
-             : MODE == 1 ? ((ks >> 1) * StepMap<1>::PWP + (ks & 1) * 16) * XPITCH : ks * 4 * XPITCH;
+        return MODE == 0 ? ks * (StepMap<0>::VW + RF - 1) * XPITCH
+             : MODE == 1 ? ((ks >> 1) * (StepMap<1>::VW + RF - 1) + (ks & 1) * 16) * XPITCH : ks * 4 * XPITCH;
     };
     auto step_d = [](int ks) { return (MODE == 2 ? ks * 4 : ks * 16) * DPITCH; };  // ... and in the dy tile
     auto tile_barrier = [&]() {
@@ -277,7 +283,25 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
     auto mma = [&](int s, int kb, const bf16x8& d) {
         acc[s][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[s], d, acc[s][kb], 0, 0, 0);
     };
-    auto tile_steps = [&](const unsigned char* sB, const unsigned char* sN) {
+    // 5x5: x of a surplus pixel (a tile's virtual columns, rows past the map) is zeroed in front of its product, for its
+    // zero dy would not cancel an infinity.  Lane element e is pixel (lane / 32) * 8 + e of the step.
+    auto pixel_mask = [&](int ks, int rows) {
+        u32x4 m;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            unsigned w = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int p = (lane >> 5) * 8 + 2 * k + h;
+                const int row = MODE == 2 ? p >> 2 : MODE == 1 ? ks >> 1 : ks;
+                const int col = MODE == 2 ? 4 * ks + (p & 3) : MODE == 1 ? (ks & 1) * 16 + p : p;
+                if (row < rows && col < a.TWr) w |= h ? 0xffff0000u : 0xffffu;
+            }
+            m[k] = w;
+        }
+        return m;
+    };
+    auto tile_steps = [&](const unsigned char* sB, const unsigned char* sN, int rows) {
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
             const bool last = ks == NK - 1;
@@ -303,8 +327,15 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
                 if (last) tile_barrier();
                 read_d((ks & 1) ? fd[0] : fdn[0], 0, src, dO);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (RF == 5) {
+                    if (rows < a.TH || (MODE == 2 ? 4 * ks + 4 : MODE == 1 ? (ks & 1) * 16 + 16 : 16) > a.TWr) {
+                        const u32x4 m = pixel_mask(ks, rows);
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
+                        for (int s = 0; s < RF; ++s) fx[s] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, fx[s]) & m);
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < RF; ++s) {
                     mma(s, 0, (ks & 1) ? fdn[0] : fd[0]);
                     read_x(s, src, xo);
                     __builtin_amdgcn_sched_barrier(0);
@@ -323,7 +354,7 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
 #pragma unroll
     for (int kb = 0; kb < FD; ++kb) read_d(fd[kb], kb, smem, 0);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) read_x(s, smem, 0);
+    for (int s = 0; s < RF; ++s) read_x(s, smem, 0);
     for (int t = t0; t < t1; ++t) {
         const int buf = (t - t0) & 1;
         // tile t+1 (in registers since the previous iteration) -> the other buffer, whose last readers finished
@@ -332,7 +363,13 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
         if (t + 2 < t1) load_tile(t + 2);
         const unsigned char* sB = smem + buf * a.buf_bytes;
         const unsigned char* sN = smem + (buf ^ 1) * a.buf_bytes;
-        tile_steps(sB, sN);
+        int rows = a.TH;
+        if (RF == 5) {  // rows of this tile inside the map
+            const int rem = t - (int)fdiv((uint32_t)t, a.dTimg) * a.tiles_img;
+            const int left = g.P - (int)fdiv((uint32_t)rem, a.dTx) * a.TH;
+            rows = left < rows ? left : rows;
+        }
+        tile_steps(sB, sN, rows);
     }
 
     // ---- epilogue: a lane holds 4 consecutive input channels of one output channel per register quad ----
@@ -341,10 +378,10 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
     for (int kb = 0; kb < FD; ++kb) {
         const int ko = ko0 + kh * (FD * 32) + kb * 32 + (lane & 31);
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
+        for (int s = 0; s < RF; ++s)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int col = (r * 3 + s) * g.C + c0 + cb * 32 + q * 8 + (lane >> 5) * 4;
+                const int col = (r * RF + s) * g.C + c0 + cb * 32 + q * 8 + (lane >> 5) * 4;
                 *reinterpret_cast<float4*>(outp + (size_t)ko * a.Kred + col) =
                     make_float4(acc[s][kb][q * 4 + 0], acc[s][kb][q * 4 + 1], acc[s][kb][q * 4 + 2], acc[s][kb][q * 4 + 3]);
             }
@@ -353,15 +390,16 @@ __global__ __launch_bounds__(NT, 3) void wgrad_patch_kernel(const WPArgs a) {
 
 struct TileShape {
     int TH, TWr, VW, mode;
-    int nseg() const { return (VW + 2 + 7) / 8; }        // 8-pixel segments per patch row
+    int nseg(int rf) const { return (VW + rf - 1 + 7) / 8; }  // 8-pixel segments per patch row
     int nk() const { return TH * VW / 16; }
 };
 
 bool choose_tile_fd(const WgradGeom& g, int fd, struct TileShape* out);
 int fd_for(const WgradGeom& g);
-size_t buf_bytes_for(int fd, const TileShape& ts) {
-    return (size_t)(ts.TH + 2) * (ts.VW + 2) * XPITCH + (size_t)ts.TH * ts.VW * (fd * 128 + 64);
+size_t buf_bytes_for(int fd, const TileShape& ts, int rf) {
+    return (size_t)(ts.TH + rf - 1) * (ts.VW + rf - 1) * XPITCH + (size_t)ts.TH * ts.VW * (rf == 3 ? fd * 128 + 64 : 192);
 }
+int ko_for(const WgradGeom& g, int fd) { return g.R == 3 ? 64 * fd : 32; }  // output channels per work-group
 
 // Most real pixels per tile (the tile height need not divide the map: the last tile row of an image is then partly
 // masked) among the tiles the kernel's three step maps cover and whose two LDS buffers fit; then the least padding.
@@ -375,8 +413,8 @@ bool choose_tile_fd(const WgradGeom& g, int fd, TileShape* out) {
         for (int th = 1; th <= g.P; ++th) {
             if ((mode == 2 && th != 4) || (mode == 1 && th != 4) || (mode == 0 && th != 7 && th != 8)) continue;
             const TileShape ts{th, twr, vw, mode};
-            if (th * vw > DCAP || (th + 2) * ts.nseg() > 12 * PVMAX) break;
-            if (2 * buf_bytes_for(fd, ts) > LDS_BYTES) break;
+            if (th * vw > DCAP || (th + g.R - 1) * ts.nseg(g.R) > wavefronts(g.R) * pv_max(g.R)) break;
+            if (2 * buf_bytes_for(fd, ts, g.R) > LDS_BYTES) break;
             const int tiles_y = (g.P + th - 1) / th;
             // real pixels per tile first, then the least padding, then even tiles (whole pooling windows)
             long score = ((long)g.P * twr * 1024 / tiles_y + (1023 - th * (vw - twr))) * 2 + ((th % 2) == 0 && (twr % 2) == 0 ? 1 : 0);
@@ -396,7 +434,7 @@ bool choose_tile_fd(const WgradGeom& g, int fd, TileShape* out) {
 // Measured on whole steps with the limit at 8 / 16 / 28 tiles: VGG-16 -5.1 / -5.1 / -5.2 % at b = 8, -2.2 / -3.4 / -3.6 %
 // at 16, -0.9 / -1.0 / -1.3 % at 32, 0 / 0 / -0.5 % at 64; the AlexNet-style step -2 .. -3 % at b = 8 .. 64.
 int fd_for(const WgradGeom& g) {
-    if ((g.K % 128) != 0 || g_force_wgrad_cfg == 6) return 1;
+    if (g.R != 3 || (g.K % 128) != 0 || g_force_wgrad_cfg == 6) return 1;
     if (g_force_wgrad_cfg == 5) return 2;
     TileShape ts;
     if (!choose_tile_fd(g, 2, &ts)) return 1;
@@ -409,11 +447,18 @@ bool choose_tile(const WgradGeom& g, TileShape* out) { return choose_tile_fd(g, 
 }  // namespace
 
 bool wgrad_patch_supported(const WgradGeom& g) {
-    if (g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1) return false;
-    if ((g.C % 64) != 0 || (g.K % 64) != 0) return false;
+    if (g.R != g.S || (g.R != 3 && g.R != 5) || g.sh != 1 || g.sw != 1) return false;
+    if ((g.C % 64) != 0 || (g.K % (g.R == 3 ? 64 : 32)) != 0) return false;
     if ((size_t)g.N * g.H * g.W * g.C * 2 >= (1ull << 31) || (size_t)g.N * g.P * g.Q * g.K * 2 >= (1ull << 31)) return false;
     TileShape ts;
     if (!choose_tile(g, &ts)) return false;
+    // 5x5: the prologue and the partial sums of one work-group per CU take about 18 us whatever the layer, the generic kernel
+    // overtakes it below some 8 GFLOP (27 x 27, 64 -> 192: 4.3 / 17 GFLOP 31.6 against 25.5 and 41.6 against 56.5 us; 14 x 14,
+    // 128 -> 128: 5.1 / 16 GFLOP 34 against 28 and 46 against 53; 28 x 28, 512 -> 64: 5.1 / 10 GFLOP 32 against 35 and 36
+    // against 54).  (A single split could not apply the update by itself.)
+    if (g.R == 5 && (wgrad_patch_nsplit(g) < 2 ||
+                     (g_force_wgrad_cfg != 3 && 2.0 * g.N * g.P * g.Q * g.K * g.C * 25.0 < 8e9)))
+        return false;
     return ts.TH * ts.TWr >= 64;  // tiny tiles: the generic kernel is no worse
 }
 
@@ -431,16 +476,20 @@ int variant_of(const TileShape& ts) {
 
 const char* wgrad_patch_kernel_name(const WgradGeom& g, bool unpool) {
     static const char* names[2][2][kNumVariants] = {
-        {{"wgrad_patch_kernel<1,false,0,7>", "wgrad_patch_kernel<1,false,0,8>", "wgrad_patch_kernel<1,false,1,8>",
-          "wgrad_patch_kernel<1,false,2,5>", "wgrad_patch_kernel<1,false,2,6>", "wgrad_patch_kernel<1,false,2,7>"},
-         {"wgrad_patch_kernel<1,true,0,7>", "wgrad_patch_kernel<1,true,0,8>", "wgrad_patch_kernel<1,true,1,8>",
-          "wgrad_patch_kernel<1,true,2,5>", "wgrad_patch_kernel<1,true,2,6>", "wgrad_patch_kernel<1,true,2,7>"}},
-        {{"wgrad_patch_kernel<2,false,0,7>", "wgrad_patch_kernel<2,false,0,8>", "wgrad_patch_kernel<2,false,1,8>",
-          "wgrad_patch_kernel<2,false,2,5>", "wgrad_patch_kernel<2,false,2,6>", "wgrad_patch_kernel<2,false,2,7>"},
-         {"wgrad_patch_kernel<2,true,0,7>", "wgrad_patch_kernel<2,true,0,8>", "wgrad_patch_kernel<2,true,1,8>",
-          "wgrad_patch_kernel<2,true,2,5>", "wgrad_patch_kernel<2,true,2,6>", "wgrad_patch_kernel<2,true,2,7>"}}};
+        {{"wgrad_patch_kernel<1,false,0,7,3>", "wgrad_patch_kernel<1,false,0,8,3>", "wgrad_patch_kernel<1,false,1,8,3>",
+          "wgrad_patch_kernel<1,false,2,5,3>", "wgrad_patch_kernel<1,false,2,6,3>", "wgrad_patch_kernel<1,false,2,7,3>"},
+         {"wgrad_patch_kernel<1,true,0,7,3>", "wgrad_patch_kernel<1,true,0,8,3>", "wgrad_patch_kernel<1,true,1,8,3>",
+          "wgrad_patch_kernel<1,true,2,5,3>", "wgrad_patch_kernel<1,true,2,6,3>", "wgrad_patch_kernel<1,true,2,7,3>"}},
+        {{"wgrad_patch_kernel<2,false,0,7,3>", "wgrad_patch_kernel<2,false,0,8,3>", "wgrad_patch_kernel<2,false,1,8,3>",
+          "wgrad_patch_kernel<2,false,2,5,3>", "wgrad_patch_kernel<2,false,2,6,3>", "wgrad_patch_kernel<2,false,2,7,3>"},
+         {"wgrad_patch_kernel<2,true,0,7,3>", "wgrad_patch_kernel<2,true,0,8,3>", "wgrad_patch_kernel<2,true,1,8,3>",
+          "wgrad_patch_kernel<2,true,2,5,3>", "wgrad_patch_kernel<2,true,2,6,3>", "wgrad_patch_kernel<2,true,2,7,3>"}}};
+    static const char* names5[kNumVariants] = {"wgrad_patch_kernel<1,false,0,7,5>", "wgrad_patch_kernel<1,false,0,8,5>",
+                                               "wgrad_patch_kernel<1,false,1,8,5>", "wgrad_patch_kernel<1,false,2,5,5>",
+                                               "wgrad_patch_kernel<1,false,2,6,5>", "wgrad_patch_kernel<1,false,2,7,5>"};
     TileShape ts;
     if (!choose_tile(g, &ts) || variant_of(ts) < 0) return "wgrad_patch_kernel";
+    if (g.R == 5) return names5[variant_of(ts)];
     return names[fd_for(g) - 1][unpool ? 1 : 0][variant_of(ts)];
 }
 
@@ -452,16 +501,16 @@ static int unpool_loads(const WgradGeom& g, const TileShape& ts) {
 }
 bool wgrad_patch_fuses_unpool(const WgradGeom& g) {
     TileShape ts;
-    if (!wgrad_patch_supported(g) || (g.P % 2) != 0 || (g.Q % 2) != 0 || !choose_tile(g, &ts)) return false;
+    if (g.R != 3 || !wgrad_patch_supported(g) || (g.P % 2) != 0 || (g.Q % 2) != 0 || !choose_tile(g, &ts)) return false;
     if ((ts.TH % 2) != 0 || (ts.TWr % 2) != 0) return false;  // windows must not straddle tiles
-    return unpool_loads(g, ts) <= NT / 64;
+    return unpool_loads(g, ts) <= wavefronts(3);
 }
 
 int wgrad_patch_nsplit(const WgradGeom& g) {
     TileShape ts;
     if (!choose_tile(g, &ts)) return 1;
     const long tiles = (long)g.N * ((g.P + ts.TH - 1) / ts.TH) * (g.Q / ts.TWr);
-    const long ncombo = (long)(g.K / (64 * fd_for(g))) * (g.C / 64);
+    const long ncombo = (long)(g.K / ko_for(g, fd_for(g))) * (g.C / 64);
     long want = kNumCU / ncombo;  // one resident work-group per CU, one round (never a second, nearly empty one)
     if (want < 1) want = 1;
     if (want > tiles) want = tiles;
@@ -470,20 +519,21 @@ int wgrad_patch_nsplit(const WgradGeom& g) {
 }
 
 namespace {
-template <int FD, bool UP>
+template <int FD, bool UP, int RF>
 const void* variant_fn(int v) {
     switch (v) {
-        case 0: return (const void*)wgrad_patch_kernel<FD, UP, 0, 7>;
-        case 1: return (const void*)wgrad_patch_kernel<FD, UP, 0, 8>;
-        case 2: return (const void*)wgrad_patch_kernel<FD, UP, 1, 8>;
-        case 3: return (const void*)wgrad_patch_kernel<FD, UP, 2, 5>;
-        case 4: return (const void*)wgrad_patch_kernel<FD, UP, 2, 6>;
-        default: return (const void*)wgrad_patch_kernel<FD, UP, 2, 7>;
+        case 0: return (const void*)wgrad_patch_kernel<FD, UP, 0, 7, RF>;
+        case 1: return (const void*)wgrad_patch_kernel<FD, UP, 0, 8, RF>;
+        case 2: return (const void*)wgrad_patch_kernel<FD, UP, 1, 8, RF>;
+        case 3: return (const void*)wgrad_patch_kernel<FD, UP, 2, 5, RF>;
+        case 4: return (const void*)wgrad_patch_kernel<FD, UP, 2, 6, RF>;
+        default: return (const void*)wgrad_patch_kernel<FD, UP, 2, 7, RF>;
     }
 }
-const void* kernel_fn(int fd, bool up, int v) {
-    if (fd == 1) return up ? variant_fn<1, true>(v) : variant_fn<1, false>(v);
-    return up ? variant_fn<2, true>(v) : variant_fn<2, false>(v);
+const void* kernel_fn(int fd, bool up, int v, int rf) {
+    if (rf == 5) return variant_fn<1, false, 5>(v);
+    if (fd == 1) return up ? variant_fn<1, true, 3>(v) : variant_fn<1, false, 3>(v);
+    return up ? variant_fn<2, true, 3>(v) : variant_fn<2, false, 3>(v);
 }
 }  // namespace
 
@@ -495,8 +545,8 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
         return set_error(WAP_EINVAL, "internal: patch weight-gradient kernel not applicable");
     if (unpool_am && !wgrad_patch_fuses_unpool(g))
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this shape");
-    const int fd = fd_for(g);
-    const int ppw = fd == 2 ? 4 : 8;
+    const int fd = fd_for(g), rf = g.R, nw = wavefronts(rf);
+    const int ppw = 512 / ko_for(g, fd);
     wa.am = unpool_am;
     wa.P2 = g.P / 2;
     wa.Q2 = g.Q / 2;
@@ -508,10 +558,10 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
     wa.TH = ts.TH;
     wa.TWr = ts.TWr;
     wa.VW = ts.VW;
-    wa.PWp = ts.VW + 2;
+    wa.PWp = ts.VW + rf - 1;
     wa.nk = ts.nk();
-    wa.NSEG = ts.nseg();
-    wa.NXL = (ts.TH + 2) * wa.NSEG;
+    wa.NSEG = ts.nseg(rf);
+    wa.NXL = (ts.TH + rf - 1) * wa.NSEG;
     if (unpool_am) {
         wa.DSEG = (ts.VW / 2 + ppw - 1) / ppw;
         wa.NDL = unpool_loads(g, ts);
@@ -520,19 +570,20 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
         wa.NDL = ts.TH * wa.DSEG;
     }
     // what the kernel's fixed loop counts and compile-time step distances assume
-    const bool fits = variant_of(ts) >= 0 && wa.nk <= DCAP / 16 && wa.NXL <= 12 * PVMAX && wa.NDL <= (unpool_am ? 12 : 12 * (fd == 2 ? 3 : 2)) &&
+    const bool fits = variant_of(ts) >= 0 && wa.nk <= DCAP / 16 && wa.NXL <= nw * pv_max(rf) &&
+                      wa.NDL <= (unpool_am ? nw : nw * (rf == 5 ? 1 : fd == 2 ? 3 : 2)) &&
                       ts.VW >= 16 && (ts.mode != 0 || ts.VW == StepMap<0>::VW) && (ts.mode != 1 || ts.VW == StepMap<1>::VW) &&
                       (ts.mode != 2 || (ts.TH == 4 && ts.VW == 4 * wa.nk));
     if (!fits) return set_error(WAP_EINVAL, "internal: patch weight-gradient tile outside the kernel's step maps");
     wa.tiles_x = g.Q / ts.TWr;
     wa.tiles_img = wa.tiles_x * ((g.P + ts.TH - 1) / ts.TH);
     wa.tiles_total = wa.tiles_img * g.N;
-    wa.kgroups = g.K / (64 * fd);
+    wa.kgroups = g.K / ko_for(g, fd);
     wa.ncombo = wa.kgroups * (g.C / 64);
     wa.nsplit = nsplit;
     wa.tiles_per_split = (wa.tiles_total + nsplit - 1) / nsplit;
-    wa.d_off = (ts.TH + 2) * wa.PWp * XPITCH;
-    wa.buf_bytes = (int)buf_bytes_for(fd, ts);
+    wa.d_off = (ts.TH + rf - 1) * wa.PWp * XPITCH;
+    wa.buf_bytes = (int)buf_bytes_for(fd, ts, rf);
     wa.x_bytes = (unsigned)((size_t)g.N * g.H * g.W * g.C * 2);
     wa.dy_bytes = (unsigned)((size_t)g.N * g.P * g.Q * g.K * 2 / (unpool_am ? 4 : 1));
     wa.dNSEG = make_fastdiv((uint32_t)wa.NSEG);
@@ -543,16 +594,16 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
     if (smem > LDS_BYTES) return set_error(WAP_EINVAL, "internal: patch weight-gradient tile does not fit LDS");
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
-        for (int f = 1; f <= 2; ++f)
-            for (int u = 0; u < 2; ++u)
-                for (int v = 0; v < kNumVariants; ++v) {
-                    hipError_t e = hipFuncSetAttribute(kernel_fn(f, u != 0, v), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-                    if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
-                }
+        for (int k = 0; k < 5 * kNumVariants; ++k) {  // 3x3: one / two blocks, full-size / pooled dy; 5x5
+            const int kind = k / kNumVariants;
+            const void* f = kind == 4 ? kernel_fn(1, false, k % kNumVariants, 5) : kernel_fn(1 + kind / 2, (kind & 1) != 0, k % kNumVariants, 3);
+            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+            if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+        }
         attr_done = true;
     }
     void* kargs[] = {(void*)&wa};
-    hipError_t le = hipLaunchKernel(kernel_fn(fd, unpool_am != nullptr, variant_of(ts)), dim3(wa.ncombo * nsplit), dim3(NT), kargs, smem, st);
+    hipError_t le = hipLaunchKernel(kernel_fn(fd, unpool_am != nullptr, variant_of(ts), rf), dim3(wa.ncombo * nsplit), dim3(64 * nw), kargs, smem, st);
     if (le != hipSuccess) return set_error(WAP_EHIP, "wgrad_patch launch: %s", hipGetErrorString(le));
     return check_launch("wgrad_patch");
 }

@@ -103,6 +103,16 @@ CASES = [
     ("split_mask_c36", (2, 9, 9, 36, 64, 3, 3, 1, 1), (1, -1, 3)),
     ("split_mask_c72", (1, 21, 20, 72, 64, 3, 3, 1, 1), (1, -1, 6)),
     ("split_mask_c10", (2, 9, 9, 10, 64, 3, 3, 1, 1), (1, -1, 3)),
+    # patch weight gradient of 5x5 filters: every step map (27-wide maps masked to 28, 16, 32, 20 and 24 columns, rows past
+    # the map), 32 output channels and several blocks, uneven splits, pad 0; one tile only stays with the generic kernel
+    ("wgrad_patch_5x5_w27_k192", (3, 27, 27, 64, 192, 5, 5, 1, 2), (-1, 3, -1)),
+    ("wgrad_patch_5x5_w28_k32_c128", (2, 28, 28, 128, 32, 5, 5, 1, 2), (-1, 3, 5)),
+    ("wgrad_patch_5x5_rows16_x7_w14", (3, 14, 14, 64, 64, 5, 5, 1, 2), (-1, 3, -1)),
+    ("wgrad_patch_5x5_rows16_x8_w16_pad0", (2, 20, 20, 64, 32, 5, 5, 1, 0), (-1, 3, -1)),
+    ("wgrad_patch_5x5_halfrows_w31_ragged", (2, 9, 31, 64, 96, 5, 5, 1, 2), (-1, 3, -1)),
+    ("wgrad_patch_5x5_blocks_w20", (2, 10, 20, 64, 32, 5, 5, 1, 2), (-1, 3, -1)),
+    ("wgrad_patch_5x5_blocks_w24", (1, 12, 24, 64, 64, 5, 5, 1, 2), (-1, 3, -1)),
+    ("wgrad_5x5_one_tile", (1, 8, 8, 64, 32, 5, 5, 1, 2), (-1, -1, -1)),
     # the specialised first-layer kernels on shapes that the few-channel kernels take by themselves
     ("c3_general_forced_5x5_s2_k32", (9, 63, 61, 3, 32, 5, 5, 2, 2), (8, 4, -1)),
     ("c3_strided_forced_11x11_s4_k64", (4, 131, 136, 3, 64, 11, 11, 4, 2), (8, 4, -1)),

@@ -282,3 +282,26 @@ def test_odd_fc_edges(orc, B, n_in, n_out):
     assert gu.rel_err(gu.host_f64(y[:B * n_out]).reshape(B, n_out), orc.fc_fwd(x64, W64)) <= gu.TOL_BF16_OUT
     assert gu.rel_err(gu.host_f64(dx[:B * n_in]).reshape(B, n_in), orc.fc_bwd_data(g64, W64)) <= gu.TOL_BF16_OUT
     assert gu.rel_err(gu.host_f64(dw[:n_out * n_in]).reshape(n_out, n_in), g64.T @ x64) <= gu.TOL_F32_OUT
+
+
+# 5x5 weight gradient on maps whose tiles hold surplus columns and rows: an infinite pixel reaches exactly the taps whose
+# receptive field holds it
+@pytest.mark.parametrize("H,W,yx", [(27, 27, (26, 26)), (27, 27, (25, 3)), (13, 14, (12, 13)), (9, 31, (8, 30))])
+def test_wgrad_5x5_infinite_pixel(orc, H, W, yx):
+    import paper_1811_01532_amd as wap
+    print(f"[case] 5x5 weight gradient, infinite pixel {(H, W, yx)}", flush=True)
+    N, C, K = 2, 64, 32
+    d = wap.conv_desc(N, H, W, C, K, 5, 5, 1, 2)
+    wap.lib().wap_debug_force(-1, 3, -1)
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch_kernel")
+    x = torch.ones((N, H, W, C), dtype=torch.bfloat16, device="cuda")
+    x[1, yx[0], yx[1], 5] = float("inf")
+    dw = torch.zeros((K, 5, 5, C), dtype=torch.float32, device="cuda")
+    wap.wap_conv2d_bwd_weight(d, x, torch.ones((N, H, W, K), dtype=torch.bfloat16, device="cuda"), dw,
+                              gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
+    wap.lib().wap_debug_force(-1, -1, -1)
+    torch.cuda.synchronize()
+    hot = np.zeros((N, H, W, C))
+    hot[1, yx[0], yx[1], 5] = 1.0
+    taps = orc.conv2d_bwd_weight(hot, np.ones((N, H, W, 1)), (1, 5, 5, C), (1, 1), (2, 2))[0] > 0
+    assert np.array_equal(~np.isfinite(gu.host_f64(dw)), np.broadcast_to(taps, (K, 5, 5, C)))
