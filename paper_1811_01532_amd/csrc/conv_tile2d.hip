@@ -112,7 +112,7 @@ __device__ __forceinline__ void each_tap(F& f, std::integer_sequence<int, T...>)
 // the patch is then a run of the zero-padded image in raster order).  UP: pooled input operand.
 // ST: filter side of the straight-line slice body (3 or 5), 0 = tap loop.
 template <int FN, int TW, int FM, int PG, bool UP, int ST>
-__global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
+__device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     constexpr bool FLAT = (TW == 0);
     constexpr int BM = 32 * FM * PG;
     constexpr int CG = 4 / PG;
@@ -597,10 +597,17 @@ __global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
     }
 }
 
-template <int FN, int TW, int FM, int PG, bool UP, int ST>
-int launch_tile2d_w(const TArgs& ta, size_t smem, hipStream_t st) {
-    auto kfn = conv_tile2d_kernel<FN, TW, FM, PG, UP, ST>;
-    static std::atomic<bool> attr_done{false};
+template <int FN, int TW, int FM, int PG, bool UP, bool T9>
+__global__ __launch_bounds__(NT, 2) void conv_tile2d_kernel(const TArgs a) {
+    conv_tile2d_body<FN, TW, FM, PG, UP, T9 ? 3 : 0>(a);
+}
+template <int FN, int TW, int FM, int PG>
+__global__ __launch_bounds__(NT, 2) void conv_tile2d_5x5_kernel(const TArgs a) {
+    conv_tile2d_body<FN, TW, FM, PG, false, 5>(a);
+}
+
+template <typename F>
+int launch_tile2d_k(F kfn, std::atomic<bool>& attr_done, const TArgs& ta, size_t smem, hipStream_t st) {
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_CAP);
@@ -616,11 +623,12 @@ constexpr int tile2d_st(int tw, int pg, bool up, int R, int S) {
 }
 template <int FN, int TW, int FM, int PG, bool UP>
 int launch_tile2d_u(const TArgs& ta, size_t smem, hipStream_t st) {
+    static std::atomic<bool> done9{false}, done5{false}, done{false};
     const int side = tile2d_st(TW, PG, UP, ta.g.R, ta.g.S);
-    if (side == 3) return launch_tile2d_w<FN, TW, FM, PG, UP, 3>(ta, smem, st);
+    if (side == 3) return launch_tile2d_k(conv_tile2d_kernel<FN, TW, FM, PG, UP, true>, done9, ta, smem, st);
     if constexpr (tile2d_st(TW, PG, UP, 5, 5) == 5)
-        if (side == 5) return launch_tile2d_w<FN, TW, FM, PG, UP, 5>(ta, smem, st);
-    return launch_tile2d_w<FN, TW, FM, PG, UP, 0>(ta, smem, st);
+        if (side == 5) return launch_tile2d_k(conv_tile2d_5x5_kernel<FN, TW, FM, PG>, done5, ta, smem, st);
+    return launch_tile2d_k(conv_tile2d_kernel<FN, TW, FM, PG, UP, false>, done, ta, smem, st);
 }
 template <int FN, int TW, int FM, int PG>
 int launch_tile2d_t(const TArgs& ta, size_t smem, hipStream_t st) {
@@ -842,23 +850,23 @@ const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
     if (!tile && tile64_width(g)) return tile64_kernel_name(g, unpool);
     const TileCfg c = tile_cfg(g, tile);
     const int u = unpool ? 1 : 0, t9 = (g.R == 3 && g.S == 3) ? 1 : 0;
-    static const char* n1[2][2] = {{"conv_tile2d_kernel<1,28,7,1,false,0>", "conv_tile2d_kernel<1,28,7,1,false,3>"},
-                                   {"conv_tile2d_kernel<1,28,7,1,true,0>", "conv_tile2d_kernel<1,28,7,1,true,3>"}};
-    static const char* n2[2][2] = {{"conv_tile2d_kernel<1,0,7,1,false,0>", "conv_tile2d_kernel<1,0,7,1,false,3>"},
-                                   {"conv_tile2d_kernel<1,0,7,1,true,0>", "conv_tile2d_kernel<1,0,7,1,true,3>"}};
-    static const char* n3[2][2] = {{"conv_tile2d_kernel<1,0,3,2,false,0>", "conv_tile2d_kernel<1,0,3,2,false,3>"},
-                                   {"conv_tile2d_kernel<1,0,3,2,true,0>", "conv_tile2d_kernel<1,0,3,2,true,3>"}};
-    static const char* n22[2][2] = {{"conv_tile2d_kernel<1,0,2,1,false,0>", "conv_tile2d_kernel<1,0,2,1,false,3>"},
-                                    {"conv_tile2d_kernel<1,0,2,1,true,0>", "conv_tile2d_kernel<1,0,2,1,true,3>"}};
+    static const char* n1[2][2] = {{"conv_tile2d_kernel<1,28,7,1,false,false>", "conv_tile2d_kernel<1,28,7,1,false,true>"},
+                                   {"conv_tile2d_kernel<1,28,7,1,true,false>", "conv_tile2d_kernel<1,28,7,1,true,true>"}};
+    static const char* n2[2][2] = {{"conv_tile2d_kernel<1,0,7,1,false,false>", "conv_tile2d_kernel<1,0,7,1,false,true>"},
+                                   {"conv_tile2d_kernel<1,0,7,1,true,false>", "conv_tile2d_kernel<1,0,7,1,true,true>"}};
+    static const char* n3[2][2] = {{"conv_tile2d_kernel<1,0,3,2,false,false>", "conv_tile2d_kernel<1,0,3,2,false,true>"},
+                                   {"conv_tile2d_kernel<1,0,3,2,true,false>", "conv_tile2d_kernel<1,0,3,2,true,true>"}};
+    static const char* n22[2][2] = {{"conv_tile2d_kernel<1,0,2,1,false,false>", "conv_tile2d_kernel<1,0,2,1,false,true>"},
+                                    {"conv_tile2d_kernel<1,0,2,1,true,false>", "conv_tile2d_kernel<1,0,2,1,true,true>"}};
     if (c.variant == 1) return n1[u][t9];
     if (c.variant == 2) return c.fm == 7 ? n2[u][t9] : n22[u][t9];
-    if (c.variant == 3 && tile2d_st(0, 2, unpool, g.R, g.S) == 5) return "conv_tile2d_kernel<1,0,3,2,false,5>";
+    if (c.variant == 3 && tile2d_st(0, 2, unpool, g.R, g.S) == 5) return "conv_tile2d_5x5_kernel<1,0,3,2>";
     if (c.variant == 3) return n3[u][t9];
     static const char* names[2][2][3] = {
-        {{"conv_tile2d_kernel<2,32,4,2,false,0>", "conv_tile2d_kernel<2,16,4,2,false,0>", "conv_tile2d_kernel<2,8,4,2,false,0>"},
-         {"conv_tile2d_kernel<2,32,4,2,false,3>", "conv_tile2d_kernel<2,16,4,2,false,3>", "conv_tile2d_kernel<2,8,4,2,false,3>"}},
-        {{"conv_tile2d_kernel<2,32,4,2,true,0>", "conv_tile2d_kernel<2,16,4,2,true,0>", "conv_tile2d_kernel<2,8,4,2,true,0>"},
-         {"conv_tile2d_kernel<2,32,4,2,true,3>", "conv_tile2d_kernel<2,16,4,2,true,3>", "conv_tile2d_kernel<2,8,4,2,true,3>"}}};
+        {{"conv_tile2d_kernel<2,32,4,2,false,false>", "conv_tile2d_kernel<2,16,4,2,false,false>", "conv_tile2d_kernel<2,8,4,2,false,false>"},
+         {"conv_tile2d_kernel<2,32,4,2,false,true>", "conv_tile2d_kernel<2,16,4,2,false,true>", "conv_tile2d_kernel<2,8,4,2,false,true>"}},
+        {{"conv_tile2d_kernel<2,32,4,2,true,false>", "conv_tile2d_kernel<2,16,4,2,true,false>", "conv_tile2d_kernel<2,8,4,2,true,false>"},
+         {"conv_tile2d_kernel<2,32,4,2,true,true>", "conv_tile2d_kernel<2,16,4,2,true,true>", "conv_tile2d_kernel<2,8,4,2,true,true>"}}};
     return names[u][t9][c.tw == 32 ? 0 : c.tw == 16 ? 1 : 2];
 }
 

@@ -89,8 +89,7 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
 // nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x 57 x 57, 200 -> 72 channels, 3x3
 // stride 2: block forward and backward 141 -> 103 us)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE, bool PHASE>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
-    const std::conditional_t<PHASE, KPhaseArgs, KArgs> a) {
+__device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhaseArgs, KArgs>& a) {
     constexpr int NT = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int FM = WM / 32, FN = WN / 32;
@@ -420,6 +419,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
     }
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KArgs a) {
+    igemm_body<BM, BN, WAVES_M, WAVES_N, B_TR, MODE, false>(a);
+}
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_phase_kernel(const KPhaseArgs a) {
+    igemm_body<BM, BN, WAVES_M, WAVES_N, true, MODE, true>(a);
+}
+
 // ---- tile configurations ----
 struct Cfg {
     int BM, BN, NT;
@@ -441,10 +449,8 @@ size_t smem_bytes(const Cfg& c, bool b_tr) {
     return 2 * (a + b);
 }
 
-template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE, bool PHASE = false>
-int launch_one(const std::conditional_t<PHASE, KPhaseArgs, KArgs>& ka, size_t smem, hipStream_t st) {
-    auto kfn = igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE, PHASE>;
-    static std::atomic<bool> attr_done{false};  // one attribute call per instantiation
+template <typename F, typename A>
+int launch_any(F kfn, std::atomic<bool>& attr_done, const A& ka, int threads, size_t smem, hipStream_t st) {
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -452,8 +458,18 @@ int launch_one(const std::conditional_t<PHASE, KPhaseArgs, KArgs>& ka, size_t sm
         attr_done = true;
     }
     int total = ka.tiles_m * ka.tiles_n * ka.nsplit;
-    hipLaunchKernelGGL(kfn, dim3(total), dim3(64 * WMv * WNv), smem, st, ka);
+    hipLaunchKernelGGL(kfn, dim3(total), dim3(threads), smem, st, ka);
     return check_launch("igemm");
+}
+template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE>
+int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
+    static std::atomic<bool> attr_done{false};  // one attribute call per instantiation
+    return launch_any(igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
+}
+template <int BM, int BN, int WMv, int WNv, int MODE>
+int launch_phase(const KPhaseArgs& ka, size_t smem, hipStream_t st) {
+    static std::atomic<bool> attr_done{false};
+    return launch_any(igemm_phase_kernel<BM, BN, WMv, WNv, MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
 }
 
 // (A 1x1 filter has one tap to skip and pays for writing every pixel's row apart from its neighbours': 64 <- 128 channels on
@@ -689,12 +705,12 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
         KPhaseArgs kp;
         static_cast<KArgs&>(kp) = ka;
         kp.tiles_m = make_phases(g, c.BM, kp.ph, &kp.nphase);
-        if (plan.cfg == 3 && mode == 0) rc = launch_one<256, 64, 4, 1, true, 0, true>(kp, smem, st);
+        if (plan.cfg == 3 && mode == 0) rc = launch_phase<256, 64, 4, 1, 0>(kp, smem, st);
         else if (plan.cfg != 1) return set_error(WAP_EINVAL, "internal: strided data gradient on an unsuitable tile");
-        else if (mode == 0) rc = launch_one<128, 128, 2, 2, true, 0, true>(kp, smem, st);
-        else if (mode == 1) rc = launch_one<128, 128, 2, 2, true, 1, true>(kp, smem, st);
-        else if (mode == 2) rc = launch_one<128, 128, 2, 2, true, 2, true>(kp, smem, st);
-        else rc = launch_one<128, 128, 2, 2, true, 3, true>(kp, smem, st);
+        else if (mode == 0) rc = launch_phase<128, 128, 2, 2, 0>(kp, smem, st);
+        else if (mode == 1) rc = launch_phase<128, 128, 2, 2, 1>(kp, smem, st);
+        else if (mode == 2) rc = launch_phase<128, 128, 2, 2, 2>(kp, smem, st);
+        else rc = launch_phase<128, 128, 2, 2, 3>(kp, smem, st);
         if (rc != WAP_OK) return rc;
         if (ev_mid) (void)hipEventRecord(ev_mid, st);
         if (ka.partial)
@@ -766,19 +782,19 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
     if (phased(g, b_tr)) {
-        static const char* phase_names[4] = {"igemm_kernel<128,128,2,2,true,0,true>", "igemm_kernel<128,128,2,2,true,1,true>",
-                                             "igemm_kernel<128,128,2,2,true,2,true>", "igemm_kernel<128,128,2,2,true,3,true>"};
-        return plan.cfg == 3 ? "igemm_kernel<256,64,4,1,true,0,true>" : phase_names[classify_mode(g, b_tr)];
+        static const char* phase_names[4] = {"igemm_phase_kernel<128,128,2,2,0>", "igemm_phase_kernel<128,128,2,2,1>",
+                                             "igemm_phase_kernel<128,128,2,2,2>", "igemm_phase_kernel<128,128,2,2,3>"};
+        return plan.cfg == 3 ? "igemm_phase_kernel<256,64,4,1,0>" : phase_names[classify_mode(g, b_tr)];
     }
     static const char* names[5][2][4] = {
-        {{"igemm_kernel<256,256,2,4,false,0,false>"}, {"igemm_kernel<256,256,2,4,true,0,false>"}},
-        {{"igemm_kernel<128,128,2,2,false,0,false>", "igemm_kernel<128,128,2,2,false,1,false>",
-          "igemm_kernel<128,128,2,2,false,2,false>", "igemm_kernel<128,128,2,2,false,3,false>"},
-         {"igemm_kernel<128,128,2,2,true,0,false>", "igemm_kernel<128,128,2,2,true,1,false>",
-          "igemm_kernel<128,128,2,2,true,2,false>", "igemm_kernel<128,128,2,2,true,3,false>"}},
-        {{"igemm_kernel<64,256,1,4,false,0,false>"}, {"igemm_kernel<64,256,1,4,true,0,false>"}},
-        {{"igemm_kernel<256,64,4,1,false,0,false>"}, {"igemm_kernel<256,64,4,1,true,0,false>"}},
-        {{"igemm_kernel<256,256,2,2,false,0,false>"}, {"igemm_kernel<256,256,2,2,true,0,false>"}},
+        {{"igemm_kernel<256,256,2,4,false,0>"}, {"igemm_kernel<256,256,2,4,true,0>"}},
+        {{"igemm_kernel<128,128,2,2,false,0>", "igemm_kernel<128,128,2,2,false,1>",
+          "igemm_kernel<128,128,2,2,false,2>", "igemm_kernel<128,128,2,2,false,3>"},
+         {"igemm_kernel<128,128,2,2,true,0>", "igemm_kernel<128,128,2,2,true,1>",
+          "igemm_kernel<128,128,2,2,true,2>", "igemm_kernel<128,128,2,2,true,3>"}},
+        {{"igemm_kernel<64,256,1,4,false,0>"}, {"igemm_kernel<64,256,1,4,true,0>"}},
+        {{"igemm_kernel<256,64,4,1,false,0>"}, {"igemm_kernel<256,64,4,1,true,0>"}},
+        {{"igemm_kernel<256,256,2,2,false,0>"}, {"igemm_kernel<256,256,2,2,true,0>"}},
     };
     return names[plan.cfg][b_tr ? 1 : 0][classify_mode(g, b_tr)];
 }

@@ -102,7 +102,7 @@ __device__ __forceinline__ u32x4 unpool_select8(u32x4 v, u32x2 am, unsigned code
 // NK: reduction steps per tile (tile pixels / 16).  RF: filter side; 5 with FD = 1 only, a work-group then covers 32
 // output channels.
 template <int FD, bool UP, int MODE, int NK, int RF>
-__global__ __launch_bounds__(64 * wavefronts(RF), 3) void wgrad_patch_kernel(const WPArgs a) {
+__device__ __forceinline__ void wgrad_patch_body(const WPArgs& a) {
     static_assert(RF == 3 || (RF == 5 && FD == 1 && !UP), "5x5: one dy block, full-size dy");
     constexpr int NW = wavefronts(RF);
     constexpr int KO = RF == 3 ? 64 * FD : 32;             // output channels per work-group
@@ -388,6 +388,15 @@ __global__ __launch_bounds__(64 * wavefronts(RF), 3) void wgrad_patch_kernel(con
     }
 }
 
+template <int FD, bool UP, int MODE, int NK>
+__global__ __launch_bounds__(64 * wavefronts(3), 3) void wgrad_patch_kernel(const WPArgs a) {
+    wgrad_patch_body<FD, UP, MODE, NK, 3>(a);
+}
+template <int MODE, int NK>
+__global__ __launch_bounds__(64 * wavefronts(5), 3) void wgrad_patch5_kernel(const WPArgs a) {
+    wgrad_patch_body<1, false, MODE, NK, 5>(a);
+}
+
 struct TileShape {
     int TH, TWr, VW, mode;
     int nseg(int rf) const { return (VW + rf - 1 + 7) / 8; }  // 8-pixel segments per patch row
@@ -476,17 +485,17 @@ int variant_of(const TileShape& ts) {
 
 const char* wgrad_patch_kernel_name(const WgradGeom& g, bool unpool) {
     static const char* names[2][2][kNumVariants] = {
-        {{"wgrad_patch_kernel<1,false,0,7,3>", "wgrad_patch_kernel<1,false,0,8,3>", "wgrad_patch_kernel<1,false,1,8,3>",
-          "wgrad_patch_kernel<1,false,2,5,3>", "wgrad_patch_kernel<1,false,2,6,3>", "wgrad_patch_kernel<1,false,2,7,3>"},
-         {"wgrad_patch_kernel<1,true,0,7,3>", "wgrad_patch_kernel<1,true,0,8,3>", "wgrad_patch_kernel<1,true,1,8,3>",
-          "wgrad_patch_kernel<1,true,2,5,3>", "wgrad_patch_kernel<1,true,2,6,3>", "wgrad_patch_kernel<1,true,2,7,3>"}},
-        {{"wgrad_patch_kernel<2,false,0,7,3>", "wgrad_patch_kernel<2,false,0,8,3>", "wgrad_patch_kernel<2,false,1,8,3>",
-          "wgrad_patch_kernel<2,false,2,5,3>", "wgrad_patch_kernel<2,false,2,6,3>", "wgrad_patch_kernel<2,false,2,7,3>"},
-         {"wgrad_patch_kernel<2,true,0,7,3>", "wgrad_patch_kernel<2,true,0,8,3>", "wgrad_patch_kernel<2,true,1,8,3>",
-          "wgrad_patch_kernel<2,true,2,5,3>", "wgrad_patch_kernel<2,true,2,6,3>", "wgrad_patch_kernel<2,true,2,7,3>"}}};
-    static const char* names5[kNumVariants] = {"wgrad_patch_kernel<1,false,0,7,5>", "wgrad_patch_kernel<1,false,0,8,5>",
-                                               "wgrad_patch_kernel<1,false,1,8,5>", "wgrad_patch_kernel<1,false,2,5,5>",
-                                               "wgrad_patch_kernel<1,false,2,6,5>", "wgrad_patch_kernel<1,false,2,7,5>"};
+        {{"wgrad_patch_kernel<1,false,0,7>", "wgrad_patch_kernel<1,false,0,8>", "wgrad_patch_kernel<1,false,1,8>",
+          "wgrad_patch_kernel<1,false,2,5>", "wgrad_patch_kernel<1,false,2,6>", "wgrad_patch_kernel<1,false,2,7>"},
+         {"wgrad_patch_kernel<1,true,0,7>", "wgrad_patch_kernel<1,true,0,8>", "wgrad_patch_kernel<1,true,1,8>",
+          "wgrad_patch_kernel<1,true,2,5>", "wgrad_patch_kernel<1,true,2,6>", "wgrad_patch_kernel<1,true,2,7>"}},
+        {{"wgrad_patch_kernel<2,false,0,7>", "wgrad_patch_kernel<2,false,0,8>", "wgrad_patch_kernel<2,false,1,8>",
+          "wgrad_patch_kernel<2,false,2,5>", "wgrad_patch_kernel<2,false,2,6>", "wgrad_patch_kernel<2,false,2,7>"},
+         {"wgrad_patch_kernel<2,true,0,7>", "wgrad_patch_kernel<2,true,0,8>", "wgrad_patch_kernel<2,true,1,8>",
+          "wgrad_patch_kernel<2,true,2,5>", "wgrad_patch_kernel<2,true,2,6>", "wgrad_patch_kernel<2,true,2,7>"}}};
+    static const char* names5[kNumVariants] = {"wgrad_patch5_kernel<0,7>", "wgrad_patch5_kernel<0,8>",
+                                               "wgrad_patch5_kernel<1,8>", "wgrad_patch5_kernel<2,5>",
+                                               "wgrad_patch5_kernel<2,6>", "wgrad_patch5_kernel<2,7>"};
     TileShape ts;
     if (!choose_tile(g, &ts) || variant_of(ts) < 0) return "wgrad_patch_kernel";
     if (g.R == 5) return names5[variant_of(ts)];
@@ -519,21 +528,31 @@ int wgrad_patch_nsplit(const WgradGeom& g) {
 }
 
 namespace {
-template <int FD, bool UP, int RF>
+template <int FD, bool UP>
 const void* variant_fn(int v) {
     switch (v) {
-        case 0: return (const void*)wgrad_patch_kernel<FD, UP, 0, 7, RF>;
-        case 1: return (const void*)wgrad_patch_kernel<FD, UP, 0, 8, RF>;
-        case 2: return (const void*)wgrad_patch_kernel<FD, UP, 1, 8, RF>;
-        case 3: return (const void*)wgrad_patch_kernel<FD, UP, 2, 5, RF>;
-        case 4: return (const void*)wgrad_patch_kernel<FD, UP, 2, 6, RF>;
-        default: return (const void*)wgrad_patch_kernel<FD, UP, 2, 7, RF>;
+        case 0: return (const void*)wgrad_patch_kernel<FD, UP, 0, 7>;
+        case 1: return (const void*)wgrad_patch_kernel<FD, UP, 0, 8>;
+        case 2: return (const void*)wgrad_patch_kernel<FD, UP, 1, 8>;
+        case 3: return (const void*)wgrad_patch_kernel<FD, UP, 2, 5>;
+        case 4: return (const void*)wgrad_patch_kernel<FD, UP, 2, 6>;
+        default: return (const void*)wgrad_patch_kernel<FD, UP, 2, 7>;
+    }
+}
+const void* variant5_fn(int v) {
+    switch (v) {
+        case 0: return (const void*)wgrad_patch5_kernel<0, 7>;
+        case 1: return (const void*)wgrad_patch5_kernel<0, 8>;
+        case 2: return (const void*)wgrad_patch5_kernel<1, 8>;
+        case 3: return (const void*)wgrad_patch5_kernel<2, 5>;
+        case 4: return (const void*)wgrad_patch5_kernel<2, 6>;
+        default: return (const void*)wgrad_patch5_kernel<2, 7>;
     }
 }
 const void* kernel_fn(int fd, bool up, int v, int rf) {
-    if (rf == 5) return variant_fn<1, false, 5>(v);
-    if (fd == 1) return up ? variant_fn<1, true, 3>(v) : variant_fn<1, false, 3>(v);
-    return up ? variant_fn<2, true, 3>(v) : variant_fn<2, false, 3>(v);
+    if (rf == 5) return variant5_fn(v);
+    if (fd == 1) return up ? variant_fn<1, true>(v) : variant_fn<1, false>(v);
+    return up ? variant_fn<2, true>(v) : variant_fn<2, false>(v);
 }
 }  // namespace
 

@@ -293,7 +293,7 @@ def test_wgrad_5x5_infinite_pixel(orc, H, W, yx):
     N, C, K = 2, 64, 32
     d = wap.conv_desc(N, H, W, C, K, 5, 5, 1, 2)
     wap.lib().wap_debug_force(-1, 3, -1)
-    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch_kernel")
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch5_kernel")
     x = torch.ones((N, H, W, C), dtype=torch.bfloat16, device="cuda")
     x[1, yx[0], yx[1], 5] = float("inf")
     dw = torch.zeros((K, 5, 5, C), dtype=torch.float32, device="cuda")
