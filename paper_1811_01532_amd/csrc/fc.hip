@@ -83,11 +83,12 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
     auto mul = [&](int set, int st) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (!VEC8) {  // a vector that was moved back repeats elements of its neighbour
+            if (!VEC8) {  // a vector that was moved back repeats elements of its neighbour: zeros on both sides, for a
+                          // zero activation does not cancel an infinite weight
                 const int k = (st + u * FW_WAVES) * 32 + kg * 8;
 #pragma unroll
                 for (int e = 0; e < 7; ++e)
-                    if (e < k - (a.in - 8)) fx[set][u][e] = (__bf16)0.f;
+                    if (e < k - (a.in - 8)) fx[set][u][e] = fw[set][u][e] = (__bf16)0.f;
             }
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][u], fx[set][u], acc, 0, 0, 0);
         }

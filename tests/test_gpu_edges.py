@@ -92,6 +92,31 @@ def test_fc_stream_edges(orc, B, n_in, n_out):
     assert e <= gu.TOL_BF16_OUT, e
 
 
+# rows of Wt that are no multiple of 8: an infinite weight among the elements that the row's last vector shares with its
+# neighbour, in the last vector's own elements and in front of both reaches exactly its own feature, as +-infinity
+@pytest.mark.parametrize("B,n_in,n_out", [(5, 67, 9), (16, 9, 7), (1, 8199, 20), (16, 16391, 50), (3, 1020, 17)])
+def test_fc_stream_infinite_weight(orc, B, n_in, n_out):
+    import paper_1811_01532_amd as wap
+    assert wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD) == "fc_fwd_kernel"
+    x = orc.bf16_bits_to_f64(si.normal_bf16(si.rng(455, B + n_in), (B, n_in)))
+    x[x == 0] = 1.0
+    W = orc.bf16_bits_to_f64(si.he_weight_bf16(si.rng(456, n_in + n_out), (n_out, n_in)))
+    tail = n_in % 8
+    for i, col in enumerate(sorted({0, n_in - 8, n_in - tail - 1, n_in - tail, n_in - 1})):
+        W[i, col] = np.inf if i % 2 else -np.inf
+    xd, Wd = (gu.dev_bf16(si.f32_to_bf16_bits(t.astype(np.float32))) for t in (x, W))
+    for relu in (False, True):
+        print(f"[case] fc stream, infinite weight {(B, n_in, n_out, relu)}", flush=True)
+        d = wap.fc_desc(B, n_in, n_out, relu=relu)
+        y = torch.zeros((B, n_out), dtype=torch.bfloat16, device="cuda")
+        wap.wap_fc_fwd(d, xd, Wd, None, y, gu.workspace(wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD)))
+        torch.cuda.synchronize()
+        ref, got = orc.fc_fwd(x, W, relu=relu), gu.host_f64(y)
+        inf = np.isinf(ref)
+        assert inf.any() and np.array_equal(got[inf], ref[inf])
+        assert gu.rel_err(np.where(inf, 0.0, got), np.where(inf, 0.0, ref)) <= gu.TOL_BF16_OUT
+
+
 # max-pool: odd / even maps (a last row or column that no window covers, blocks of two input pixels with one inside),
 # channels in vectors and one by one, stride 2 with windows of 2 and 3, other strides and windows
 @pytest.mark.parametrize("N,H,W,C,win,st", [
