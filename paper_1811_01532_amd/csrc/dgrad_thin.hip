@@ -153,12 +153,15 @@ __global__ __launch_bounds__(NT) void dgrad_thin_kernel(const ThinArgs a) {
             const int ri = r0 / a.sh, rb = r0 - ri * a.sh, sj = s0 / a.sw, sb = s0 - sj * a.sw;
 #pragma unroll
             for (int i = 0; i < PX; ++i) {
-                const int j0 = sj + (sf[i] < sb ? 1 : 0);
-                const int s_first = sf[i] + a.sw * j0;
-                int k = ri + (rf[i] < rb ? 1 : 0);
-                for (int r = rf[i] + a.sh * k; r < r0 + rg; r += a.sh, ++k) {
+                // only taps whose dy pixel (hd - k, wd - j) lies in the image: its z is made of zeros beyond, which do not
+                // cancel an infinite weight
+                const int j0 = max(sj + (sf[i] < sb ? 1 : 0), wd[i] - a.IW + 1);
+                const int s_first = sf[i] + a.sw * j0, s_end = min(s0 + sg, sf[i] + a.sw * wd[i] + 1);
+                int k = max(ri + (rf[i] < rb ? 1 : 0), hd[i] - a.IH + 1);
+                const int r_end = min(r0 + rg, rf[i] + a.sh * hd[i] + 1);
+                for (int r = rf[i] + a.sh * k; r < r_end; r += a.sh, ++k) {
                     const float* src = z + ((hd[i] - k - p_lo) * a.zw + wd[i] - j0 - q_lo) * a.zp + ((r - r0) * sg + s_first - s0) * C;
-                    for (int s = s_first; s < s0 + sg; s += a.sw) {
+                    for (int s = s_first; s < s_end; s += a.sw) {
 #pragma unroll
                         for (int c = 0; c < C; ++c) acc[i][c] += src[c];
                         src += a.sw * C - a.zp;  // the next tap of this phase meets the dy pixel to the left

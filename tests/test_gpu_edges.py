@@ -58,6 +58,33 @@ def test_image_gradient_edges(orc, N, H, W, C, K, R, S, stride, pad):
     assert e <= gu.TOL_BF16_OUT, e           # one bf16 rounding of an fp32 sum
 
 
+# an infinite weight reaches exactly the pixels that meet its tap at a dy pixel of the image, not those whose tap lies beyond
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad", [
+    (1, 9, 33, 3, 64, 3, 3, 1, 1), (2, 7, 31, 3, 8, 3, 3, 1, 0), (1, 17, 20, 1, 72, 5, 5, 1, 2), (1, 33, 65, 3, 96, 11, 11, 4, 2),
+    (1, 40, 37, 3, 136, 7, 7, 2, 3), (1, 13, 40, 4, 40, 4, 3, (2, 1), (0, 1)), (1, 31, 34, 3, 24, 3, 3, 3, 1),
+    (1, 10, 60, 4, 16, 2, 19, 1, (1, 9)), (1, 20, 70, 3, 32, 18, 18, 2, 5)])
+def test_image_gradient_infinite_weight(orc, N, H, W, C, K, R, S, stride, pad):
+    import paper_1811_01532_amd as wap
+    st = (stride, stride) if isinstance(stride, int) else stride
+    pd = (pad, pad) if isinstance(pad, int) else pad
+    P, Q = si.out_dim(H, pd[0], R, st[0]), si.out_dim(W, pd[1], S, st[1])
+    d = wap.conv_desc(N, H, W, C, K, R, S, st, pd)
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_DATA) == "dgrad_thin_kernel"
+    dy = torch.ones((N, P, Q, K), dtype=torch.bfloat16, device="cuda")
+    ones = np.ones((N, P, Q, K))
+    for r, s in ((0, 0), (R - 1, S - 1), (R // 2, 0), (0, S - 1)):
+        print(f"[case] image gradient, infinite weight {(N, H, W, C, K, R, S, st, pd, r, s)}", flush=True)
+        w, hot = torch.ones((K, R, S, C), dtype=torch.bfloat16, device="cuda"), np.zeros((K, R, S, C))
+        w[K - 1, r, s, C - 1] = float("inf")
+        hot[K - 1, r, s, C - 1] = 1.0
+        dx = torch.zeros((N, H, W, C), dtype=torch.bfloat16, device="cuda")
+        wap.wap_conv2d_bwd_data(d, dy, w, dx, gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)))
+        torch.cuda.synchronize()
+        got = gu.host_f64(dx)
+        touched = orc.conv2d_bwd_data(ones, hot, (N, H, W, C), st, pd) > 0
+        assert touched.any() and np.array_equal(np.isposinf(got), touched) and np.isfinite(got[~touched]).all()
+
+
 # fully-connected products as streams of the weights: one to eight blocks of 16 rows and one row over / under, features
 # that end inside a 16-row block, reductions shorter than one step of all wavefronts, longer, ragged (% 32, % 8, odd),
 # divided over work-groups (few features, long rows), two and four columns per lane, a last work-group moved back,
