@@ -475,7 +475,8 @@ int launch_phase(const KPhaseArgs& ka, size_t smem, hipStream_t st) {
 // (A 1x1 filter has one tap to skip and pays for writing every pixel's row apart from its neighbours': 64 <- 128 channels on
 // 56 x 56 14.0 against 11.4 us.  3x3: 64 <- 64 on 112 x 112 27 against 52 us, 16 <- 64 on 64 x 64 11.7 against 27.)
 bool phased(const GemmGeom& g, bool b_tr) {
-    return b_tr && g.R * g.S > 1 && g.div_h * g.div_w > 1 && g.div_h * g.div_w <= kMaxPhases;
+    const long phases = (long)g.div_h * g.div_w;  // strides may be as large as an int holds
+    return b_tr && g.R * g.S > 1 && phases > 1 && phases <= kMaxPhases;
 }
 
 int classify_mode(const GemmGeom& g, bool b_tr) {

@@ -208,6 +208,18 @@ def test_wide_maps_leave_the_16bit_coordinate_kernel(wap):
     assert wap.wap_conv2d_kernel_name(wap.conv_desc(64, 28, 28, 512, 512, 3, 3, 1, 1), wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch")
 
 
+def test_phases_of_a_strided_data_gradient_are_counted_in_64_bits(wap):
+    """A data gradient is divided into stride_h * stride_w products where these are few.  Strides are bounded by int32
+    only: a product that wraps to a small number must not pass for few phases (the phase table has a fixed length)."""
+    def name(stride):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(1, 8, 8, 16, 16, 3, 3, stride, 1), wap.WAP_PASS_BWD_DATA)
+    assert (3 * 1431655767) % 2 ** 32 == 5 and (65537 * 65535) % 2 ** 32 == 2 ** 32 - 1
+    plain = name((1, 1))
+    assert name((2, 2)) != plain                      # four phases
+    for stride in ((3, 1431655767), (1431655767, 3), (65537, 65535), (65536, 65536), (2147483647, 2147483647), (5, 5)):
+        assert name(stride) == plain, stride
+
+
 def test_patch_weight_gradient_tile_and_step_map_per_layer(wap):
     """Host-side plan of the patch weight-gradient kernel <FD, UP, step map, steps per tile>: block steps on the
     28-wide tiles of conv2_x .. conv4_x need no padded pixel, 14- and 13-wide maps run 7-row tiles of width 16,
