@@ -382,11 +382,12 @@ ThinShape shape_of(const GemmGeom& g) {
 }
 ThinShape shape_of(const WgradGeom& g) { return {g.H, g.W, g.C, g.K, g.P, g.Q, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.N}; }
 long thin_tiles(const ThinShape& s) { return (long)s.N * ((s.OH + TR - 1) / TR) * ((s.OW + TW - 1) / TW); }
-int thin_xw(const ThinShape& s) { return (TW - 1) * s.sw + (s.S + 1) / 2 * 2; }
-int thin_rows(const ThinShape& s) { return (TR - 1) * s.sh + s.R; }
-long thin_npx(const ThinShape& s) { return (long)thin_rows(s) * thin_xw(s); }
-int thin_nv(const ThinShape& s) { return (thin_xw(s) * s.C + 7 + 7) / 8; }  // up to seven elements in front of the patch
-size_t thin_patch_smem(const ThinShape& s) { return (size_t)(thin_npx(s) + 1) / 2 * 16 + (size_t)thin_rows(s) * thin_nv(s) * 16; }
+// (in 64 bits: strides are bounded by int32 only)
+long thin_xw(const ThinShape& s) { return (long)(TW - 1) * s.sw + (s.S + 1) / 2 * 2; }
+long thin_rows(const ThinShape& s) { return (long)(TR - 1) * s.sh + s.R; }
+long thin_npx(const ThinShape& s) { return thin_rows(s) * thin_xw(s); }
+long thin_nv(const ThinShape& s) { return (thin_xw(s) * s.C + 7 + 7) / 8; }  // up to seven elements in front of the patch
+size_t thin_patch_smem(const ThinShape& s) { return (size_t)((thin_npx(s) + 1) / 2 * 16 + thin_rows(s) * thin_nv(s) * 16); }
 size_t thin_fwd_smem(const ThinShape& s, int fb) {
     const size_t ksteps = ((size_t)s.R * ((s.S + 1) / 2) + 1) / 2;
     return ksteps * fb * 1024 + (size_t)4 * 32 * (fb * 64 + 16) + thin_patch_smem(s);
@@ -395,8 +396,11 @@ size_t thin_wgrad_smem(const ThinShape& s, int fb) {
     return std::max((size_t)TR * TW * (fb * 64 + 64) + thin_patch_smem(s), (size_t)4 * 32 * 33 * sizeof(float));
 }
 bool thin_shape_ok(const ThinShape& s) {
-    return s.C >= 1 && s.C <= 4 && s.K % 8 == 0 && s.R * s.S >= 2 && (long)thin_rows(s) * thin_nv(s) <= XV * NT &&
-           thin_patch_smem(s) <= 80 * 1024 && thin_tiles(s) < (1L << 30);
+    // (the stride bound keeps the products below in 64 bits, the LDS bounds are far tighter; the last bound: the vectors of
+    // a patch may reach behind the tensor, their offsets stay below 2^31)
+    return s.C >= 1 && s.C <= 4 && s.K % 8 == 0 && s.R * s.S >= 2 && s.sh < 4096 && s.sw < 4096 &&
+           thin_rows(s) * thin_nv(s) <= XV * NT && thin_patch_smem(s) <= 80 * 1024 && thin_tiles(s) < (1L << 30) &&
+           (long)s.N * s.H * s.W * s.C <= 2147483647L - XV * NT * 8;
 }
 // Channel blocks per work-group: all of a thin layer's, so that the patch is staged once, as long as two work-groups per
 // CU fit; one each where the tiles alone do not put two work-groups on every CU.
@@ -422,13 +426,13 @@ ThinArgs thin_args(const ThinShape& s) {
     a.G = (s.S + 1) / 2;
     a.ksteps = (s.R * a.G + 1) / 2;
     a.NB = (s.R * s.S + 7) / 8;
-    a.xw = thin_xw(s);
+    a.xw = (int)thin_xw(s);
     a.npx = (int)thin_npx(s);
     a.dTX = make_fastdiv((uint32_t)a.tiles_x);
     a.dTY = make_fastdiv((uint32_t)a.tiles_y);
     a.dXW = make_fastdiv((uint32_t)a.xw);
-    a.nv = thin_nv(s);
-    a.nvec = thin_rows(s) * a.nv;
+    a.nv = (int)thin_nv(s);
+    a.nvec = (int)thin_rows(s) * a.nv;
     a.rpitch = a.nv * 16;
     a.x_elems = (int)((long)s.N * s.H * s.W * s.C);
     a.dNV = make_fastdiv((uint32_t)a.nv);

@@ -220,6 +220,17 @@ def test_phases_of_a_strided_data_gradient_are_counted_in_64_bits(wap):
         assert name(stride) == plain, stride
 
 
+def test_few_channel_kernels_refuse_strides_whose_patch_size_wraps(wap):
+    """The patch of a tile is 31 * stride + filter pixels wide: a stride for which this wraps to a small number in 32 bits
+    must not be planned onto the kernels that stage the patch in LDS."""
+    assert (31 * 138547333) % 2 ** 32 == 27 and (3 * 1431655766) % 2 ** 32 == 2
+    for stride in ((1, 138547333), (1431655766, 1), (1431655766, 138547333), (2147483647, 2147483647)):
+        d = wap.conv_desc(2, 6, 9, 3, 16, 3, 3, stride, 1)
+        assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_FWD).startswith("igemm_kernel"), stride
+        assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_kernel"), stride
+    assert wap.wap_conv2d_kernel_name(wap.conv_desc(2, 6, 9, 3, 16, 3, 3, 2, 1), wap.WAP_PASS_FWD) == "conv_thin_fwd_kernel"
+
+
 def test_patch_weight_gradient_tile_and_step_map_per_layer(wap):
     """Host-side plan of the patch weight-gradient kernel <FD, UP, step map, steps per tile>: block steps on the
     28-wide tiles of conv2_x .. conv4_x need no padded pixel, 14- and 13-wide maps run 7-row tiles of width 16,
