@@ -18,6 +18,8 @@
 // for large strided filters by the latency of the groups' load - product - sum phases: 11 x 11 / 4 at minibatch 32 299 to
 // 72 us (weights gathered with branches around the loads instead of out-of-range offsets: 123 us; one filter row per
 // group: 131 us).
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -228,7 +230,9 @@ int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16
     a.IH = g.IH; a.IW = g.IW; a.K = g.IC;
     a.OH = g.OH; a.OW = g.OW;
     a.R = g.R; a.S = g.S;
-    a.sh = g.div_h; a.sw = g.div_w;
+    // (with one row (column) of dy every stride past the map means the same; a larger one would wrap the tap counters)
+    a.sh = g.IH == 1 ? (int)std::min<long>(g.div_h, (long)g.OH + g.R) : g.div_h;
+    a.sw = g.IW == 1 ? (int)std::min<long>(g.div_w, (long)g.OW + g.S) : g.div_w;
     a.ph = g.R - 1 - g.pad_h; a.pw = g.S - 1 - g.pad_w;  // the geometry carries the flipped-filter padding
     // Strided both ways, a tile of 8 x 32 pixels lies over a handful of dy pixels: four times the pixels, less halo.
     const int px = a.sh > 1 && a.sw > 1 ? 4 : 1;

@@ -58,6 +58,25 @@ def test_image_gradient_edges(orc, N, H, W, C, K, R, S, stride, pad):
     assert e <= gu.TOL_BF16_OUT, e           # one bf16 rounding of an fp32 sum
 
 
+# one row or column of dy: strides up to the largest int mean the same as one past the map
+@pytest.mark.parametrize("stride", [(12, 20), (2147483647, 2147483647), (2147483646, 1), (1, 2000000000)])
+def test_image_gradient_huge_strides(orc, stride):
+    import paper_1811_01532_amd as wap
+    N, H, W, C, K, R, S, pad = 2, 6, 9, 3, 16, 3, 3, (1, 1)
+    print(f"[case] image gradient, stride {stride}", flush=True)
+    P, Q = si.out_dim(H, 1, R, stride[0]), si.out_dim(W, 1, S, stride[1])
+    gb, wb = si.normal_bf16(si.rng(445, P * Q), (N, P, Q, K)), si.he_weight_bf16(si.rng(446, 0), (K, R, S, C))
+    d = wap.conv_desc(N, H, W, C, K, R, S, stride, pad)
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_DATA) == "dgrad_thin_kernel"
+    dx = torch.full((N, H, W, C), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wap.wap_conv2d_bwd_data(d, gu.dev_bf16(gb), gu.dev_bf16(wb), dx,
+                            gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)))
+    torch.cuda.synchronize()
+    same = tuple(min(s, 20) for s in stride)
+    ref = orc.conv2d_bwd_data(orc.bf16_bits_to_f64(gb), orc.bf16_bits_to_f64(wb), (N, H, W, C), same, pad)
+    assert gu.rel_err(gu.host_f64(dx), ref) <= gu.TOL_BF16_OUT
+
+
 # an infinite weight reaches exactly the pixels that meet its tap at a dy pixel of the image, not those whose tap lies beyond
 @pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad", [
     (1, 9, 33, 3, 64, 3, 3, 1, 1), (2, 7, 31, 3, 8, 3, 3, 1, 0), (1, 17, 20, 1, 72, 5, 5, 1, 2), (1, 33, 65, 3, 96, 11, 11, 4, 2),
