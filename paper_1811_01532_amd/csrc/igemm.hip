@@ -482,7 +482,10 @@ bool phased(const GemmGeom& g, bool b_tr) {
 int classify_mode(const GemmGeom& g, bool b_tr) {
     bool vec_a = (g.IC % 8) == 0;
     bool vec_b = b_tr ? (g.Ncols % 8) == 0 : (g.Kred % 8) == 0;
-    if (!(vec_a && vec_b)) return g.IC >= 8 && (!b_tr || g.Ncols >= 8) ? 2 : 3;
+    if (!(vec_a && vec_b)) {
+        const long padded = (long)g.R * g.S * ((g.IC + 7L) / 8 * 8);  // the reduction of mode 2, counted in int
+        return g.IC >= 8 && (!b_tr || g.Ncols >= 8) && padded <= 2147483647L - BK ? 2 : 3;
+    }
     if ((g.IC % BK) == 0 && ((g.div_h == 1 && g.div_w == 1) || phased(g, b_tr))) return 0;
     return 1;
 }

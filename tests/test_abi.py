@@ -220,6 +220,15 @@ def test_phases_of_a_strided_data_gradient_are_counted_in_64_bits(wap):
         assert name(stride) == plain, stride
 
 
+def test_odd_channel_reduction_that_passes_int32_stays_element_by_element(wap):
+    """Odd channel counts are rounded up to a multiple of 8 per filter tap; where that takes the reduction past int32 the
+    kernel that counts the taps' own channels remains."""
+    fits, wraps = (wap.conv_desc(1, 1, 1, C, 1, 255, 255, 1, 127) for C in (33017, 33025))
+    assert 255 * 255 * 33024 < 2 ** 31 - 64 < 255 * 255 * 33032 and 255 * 255 * 33025 < 2 ** 31
+    assert wap.wap_conv2d_kernel_name(fits, wap.WAP_PASS_FWD) == "igemm_kernel<128,128,2,2,false,2>"
+    assert wap.wap_conv2d_kernel_name(wraps, wap.WAP_PASS_FWD) == "igemm_kernel<128,128,2,2,false,3>"
+
+
 def test_few_channel_kernels_refuse_strides_whose_patch_size_wraps(wap):
     """The patch of a tile is 31 * stride + filter pixels wide: a stride for which this wraps to a small number in 32 bits
     must not be planned onto the kernels that stage the patch in LDS."""
