@@ -85,11 +85,17 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
 // MODE 2: odd   -- any channel counts of at least 8: unaligned 16-byte loads, every tap's channels rounded up to a multiple
 //                  of 8 in the reduction (element by element, as MODE 3 does it, 288 x 4096 -> 3373 took 253 us for dx)
 // MODE 3: scalar-- anything (2-byte loads)
-// PHASE: data gradient of a strided convolution, the row tiles grouped by phase (a.ph): a tap between dy elements costs
-// nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x 57 x 57, 200 -> 72 channels, 3x3
-// stride 2: block forward and backward 141 -> 103 us)
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE, bool PHASE>
-__device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhaseArgs, KArgs>& a) {
+// VARIANT: the mode, plus 4 for PHASE: data gradient of a strided convolution, the row tiles grouped by phase (a.ph): a tap
+// between dy elements costs nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x
+// 57 x 57, 200 -> 72 channels, 3x3 stride 2: block forward and backward 141 -> 103 us)
+// (One kernel, not two around a shared device function: behind that call the compiler no longer hoisted the argument loads
+// and address arithmetic of modes 0 and 1, 200 instructions more, 29 x 50 x 50 x 192 -> 248 at stride 2 37.1 against 41.5 us,
+// 1024 -> 4096 at 17 rows 9.6 against 11.1.  For the same reason their expressions name a.g only where a phase needs it.)
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int VARIANT>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
+    const std::conditional_t<(VARIANT >= 4), KPhaseArgs, KArgs> a) {
+    constexpr bool PHASE = VARIANT >= 4;
+    constexpr int MODE = VARIANT & 3;
     constexpr int NT = 64 * WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int FM = WM / 32, FN = WN / 32;
@@ -190,7 +196,7 @@ __device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhas
             int tap = MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;
             int c = kk - tap * tapk + ((MODE == 0) ? a_vec * 8 : 0);
             int r = tap / g.S, s = tap - r * g.S;
-            bool kok = (MODE == 0) ? true : tap < g.R * g.S;
+            bool kok = MODE == 0 ? true : MODE == 2 ? tap < g.R * g.S : kk < g.Kred;
             const int over = MODE == 2 && c + 8 > g.IC ? c + 8 - g.IC : 0;
 #pragma unroll
             for (int i = 0; i < A_PASSES; ++i) {
@@ -260,12 +266,17 @@ __device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhas
 #pragma unroll
             for (int i = 0; i < B_PASSES; ++i) {
                 int kk = kk0 + b_row0 + i * B_RPP;
-                const int tapk = MODE == 2 ? a.ICp : g.IC;
-                int tap = (MODE == 0) ? kk0 / tapk : MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;  // one tap per tile in the fast mode
-                int k = kk - tap * tapk;
+                int tap = MODE == 0 ? kk0 / g.IC : MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / g.IC;  // one tap per tile in the fast mode
+                int k = kk - tap * (MODE == 2 ? a.ICp : g.IC);
                 int r = tap / g.S, s = tap - r * g.S;
-                if (PHASE) { r = r0 + r * a.g.div_h; s = s0 + s * a.g.div_w; }
-                int rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
+                int rowoff;
+                if (PHASE) {
+                    r = r0 + r * a.g.div_h;
+                    s = s0 + s * a.g.div_w;
+                    rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
+                } else {
+                    rowoff = ((k * g.R + (g.R - 1 - r)) * g.S + (g.S - 1 - s)) * g.Ncols;
+                }
                 if (MODE == 2) {
                     const bool ok = tap < g.R * g.S && k < g.IC && over < 8;
                     rb[i] = shift_down8(load8_unaligned(ok ? a.Bw + (rowoff + n - over) : zero_src), over < 8 ? over : 0);
@@ -406,8 +417,10 @@ __device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhas
 #pragma unroll
                     for (int e = 0; e < 4; ++e) hb16[e] = f2bf(v[e]);
                     if (vec4) {
-                        *reinterpret_cast<uint2*>(o) = make_uint2((unsigned)hb16[0] | ((unsigned)hb16[1] << 16),
-                                                                  (unsigned)hb16[2] | ((unsigned)hb16[3] << 16));
+                        // (one vector: as a pair of words the second was merged with the element stores below, three
+                        // stores for one, the strided data gradients 20 to 40 % slower)
+                        *reinterpret_cast<u32x2*>(o) = u32x2{(unsigned)hb16[0] | ((unsigned)hb16[1] << 16),
+                                                             (unsigned)hb16[2] | ((unsigned)hb16[3] << 16)};
                     } else {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
@@ -417,15 +430,6 @@ __device__ __forceinline__ void igemm_body(const std::conditional_t<PHASE, KPhas
             }
         }
     }
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int MODE>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(const KArgs a) {
-    igemm_body<BM, BN, WAVES_M, WAVES_N, B_TR, MODE, false>(a);
-}
-template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_phase_kernel(const KPhaseArgs a) {
-    igemm_body<BM, BN, WAVES_M, WAVES_N, true, MODE, true>(a);
 }
 
 // ---- tile configurations ----
@@ -469,7 +473,7 @@ int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
 template <int BM, int BN, int WMv, int WNv, int MODE>
 int launch_phase(const KPhaseArgs& ka, size_t smem, hipStream_t st) {
     static std::atomic<bool> attr_done{false};
-    return launch_any(igemm_phase_kernel<BM, BN, WMv, WNv, MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
+    return launch_any(igemm_kernel<BM, BN, WMv, WNv, true, 4 + MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
 }
 
 // (A 1x1 filter has one tap to skip and pays for writing every pixel's row apart from its neighbours': 64 <- 128 channels on
@@ -786,9 +790,9 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
     if (phased(g, b_tr)) {
-        static const char* phase_names[4] = {"igemm_phase_kernel<128,128,2,2,0>", "igemm_phase_kernel<128,128,2,2,1>",
-                                             "igemm_phase_kernel<128,128,2,2,2>", "igemm_phase_kernel<128,128,2,2,3>"};
-        return plan.cfg == 3 ? "igemm_phase_kernel<256,64,4,1,0>" : phase_names[classify_mode(g, b_tr)];
+        static const char* phase_names[4] = {"igemm_kernel<128,128,2,2,true,4>", "igemm_kernel<128,128,2,2,true,5>",
+                                             "igemm_kernel<128,128,2,2,true,6>", "igemm_kernel<128,128,2,2,true,7>"};
+        return plan.cfg == 3 ? "igemm_kernel<256,64,4,1,true,4>" : phase_names[classify_mode(g, b_tr)];
     }
     static const char* names[5][2][4] = {
         {{"igemm_kernel<256,256,2,4,false,0>"}, {"igemm_kernel<256,256,2,4,true,0>"}},
