@@ -292,24 +292,26 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         for (int i = 0; i < FC; ++i) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                int col = col0 + wc * WC + i * 32 + q * 8 + (lane >> 5) * 4;
-                int ncol = a.Kred - col;  // columns of this group that exist
-                if (MODE == 1) {
+                const int col = col0 + wc * WC + i * 32 + q * 8 + (lane >> 5) * 4;
+                if constexpr (MODE == 1) {
                     const int tap = (int)fdiv((uint32_t)col, a.dCp), c = col - tap * a.Cp;
-                    ncol = tap < g.R * g.S ? g.C - c : 0;
-                    col = tap * g.C + c;
-                }
+                    const int ncol = tap < g.R * g.S ? g.C - c : 0;  // columns of this group that exist
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (e >= ncol) continue;
-                    const size_t o = (size_t)ko * a.Kred + col + e;
-                    if (a.sgd.w32) {
-                        const float w = sgd_apply(a.sgd.w32[o], acc[i][j][q * 4 + e], a.sgd.lr);
-                        a.sgd.w32[o] = w;
-                        a.sgd.wb[o] = __builtin_bit_cast(unsigned short, (__bf16)w);
-                    } else {
-                        outp[o] = acc[i][j][q * 4 + e];
+                    for (int e = 0; e < 4; ++e) {
+                        if (e >= ncol) continue;
+                        const size_t o = (size_t)ko * a.Kred + tap * g.C + c + e;
+                        if (a.sgd.w32) {
+                            const float w = sgd_apply(a.sgd.w32[o], acc[i][j][q * 4 + e], a.sgd.lr);
+                            a.sgd.w32[o] = w;
+                            a.sgd.wb[o] = __builtin_bit_cast(unsigned short, (__bf16)w);
+                        } else {
+                            outp[o] = acc[i][j][q * 4 + e];
+                        }
                     }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < a.Kred) outp[(size_t)ko * a.Kred + col + e] = acc[i][j][q * 4 + e];
                 }
             }
         }
