@@ -277,19 +277,46 @@ bool below_2g(double elems) { return elems * 2.0 < 2147483648.0; }
 
 // Every work-group reads the whole batch operand, through an L2 path that carries about 8.6 TB/s: with one block of 16
 // rows that is as much traffic as Wt itself, with more it outweighs Wt, and the generic kernel's tiles (64 x 256, split
-// reduction) are faster: 4096 x 9216 at 8 / 32 / 64 rows 17.3 / 29 / 44 us here, 21.9 / 22.2 / 24.5 us there;
-// 4096 x 4096 at 8 rows 8.8 against 14.2, 4096 x 25088 39.4 against 39.3.
+// reduction) are faster.  Up to 4096 features, one work-group per CU, this kernel is ahead (9216 -> 4096 at 8 rows 17.2
+// us against 21.6; 4096 -> 1000 8.6 against 12.2) until the long rows of Wt outlast what the generic one spends on its
+// second launch: 25088 -> 4096 at 2 / 8 / 16 rows 32.9 / 38.9 / 47.0 against 39.4, 16384 -> 4096 26.6 / 28.9 / 33.2 against
+// 28.  Beyond that it runs in rounds of work-groups, each with a start of 3 us, which pays only while the reduction is long
+// enough to be split there and short enough here: 64 -> 25088 17 against 4.5, 64 -> 6000 6.2 against 4.4, 512 -> 8192 7.1
+// against 8.7, 2048 -> 8192 10.4 against 11.4, 4096 -> 9216 23.3 against 19.4.  Rows that are no multiple of 64, which
+// the generic kernel loads more slowly, move that line: 600 -> 10000 8.7 against 10.1, 1000 -> 25088 20.0 against 19.6.
 bool fc_fwd_supported(const GemmGeom& g) {
-    return is_fc(g) && g.M <= 16 && g.IC >= 8 && below_2g(16.0 * g.IC);
+    if (!is_fc(g) || g.M > 16 || g.IC < 8 || !below_2g(16.0 * g.IC)) return false;
+    const bool quick = (g.IC % 64) == 0;  // the generic kernel's fast mode
+    if (g.Ncols <= 4096) return !quick || g.M <= 6 || (double)g.IC * g.Ncols <= 50e6;
+    return quick ? g.Ncols <= 8192 && g.IC >= 256 && g.IC <= 2048 : 25.0 * g.IC >= g.Ncols;
 }
 // The same for the data gradient, whose work-groups share the batch operand among 64 (or 32) columns: up to 32 rows, and
-// where the reduction is short (both kernels wait more than they stream) up to 128.  This kernel / the generic one in
-// us: 9216 columns x 4096 rows of Wt at 8 / 32 / 64 batch rows 15.2 / 19.4 / 26.9 and 21.9 / 23.4 / 26.0; 4096 x 4096
-// 10.7 / 15.5 / 22.1 and 14.3 / 17 / 19.3; 25088 x 4096 at 8 / 22 / 64 33.7 / 38.1 / 51.3 and 45.0 / 45.2 / 48.7;
-// 4096 x 1000 at 64 / 100 8.1 / 9.6 and 14.2 / 16.3; 25088 x 512 at 64 / 100 17.7 / 32 and 18.2 / 17.
+// where the reduction is short (both kernels wait more than they stream) up to 128.  A work-group walks all rows of Wt with
+// eight wavefronts, so few columns or many rows of Wt leave it waiting, most of all when Wt comes from memory and not
+// from the 256 MB cache.  This kernel / the generic one in us, Wt cached (from memory), at 8 / 16 / 32 batch rows:
+//   4096 rows of Wt x  4096 columns  10.9 / 12.1 / 15.4 (18.4 / 19.7 / 23.4)   14.3 / 15.5 / 16.7 (17.1 / 16.9 / 17.9)
+//                      9216          15.6 / 16.5 / 18.9 (25.5 / 27.1 / 30.3)   21.1 / 21.3 / 22.7 (25.2 / 25.4 / 26.6)
+//                     25088          35.0 / 36.7 / 40.2 (50.4 / 53.4 / 60.4)   44.6 / 45.1 / 46.5 (58.9 / 60.5 / 62.0)
+//   8192             x   512         10.8 / 13.0 / 20.1 (19.7 / 22.0 / 27.6)   17.7 / 17.8 / 18.5 (18.2 / 18.4 / 19.1)
+//                      8192          26.9 / 28.4 / 32.7 (43.4 / 46.4 / 52.2)   28.7 / 28.7 / 29.8 (34.3 / 34.2 / 35.6)
+//  25088             x   512         28.1 / 41.8 / 82.9 (93 / 105 / 127)       27.9 / 28.3 / 28.0 (30.3 / 30.7 / 30.2)
+//   1000             x  4096         4.0 / 3.9 / 4.6 (4.8 / 5.1 / 6.0)         10.2 / 10.6 / 11.4 (11.1 / 11.2 / 12.0)
+//                      at 64 / 100 / 128 rows 5.9 / 9.6 / 10.1                 13.7 / 16.0 / 18.2
+//   1024             x   512         at 64 / 100 / 128 rows 7.1 / 10.7 / 12.1  11.4 / 10.7 / 11.2
+// The lines are drawn where the two times' geometric mean (cached, from memory) crosses.  The generic kernel is slower
+// where it cannot load whole 64-channel slices (10000 x 9216 at 16 rows 36.7 against 70) and more so with odd rows
+// (8192 x 4551 24 against 70), and the lines lie further out there.
 bool fc_dx_supported(const GemmGeom& g) {
-    return is_fc(g) && (g.M <= 32 || (g.M <= 128 && g.IC <= 1024 && (g.M <= 64 || g.Ncols <= 8192))) && g.Ncols >= 64 && g.IC >= 8 &&
-           below_2g((double)g.IC * g.Ncols) && below_2g((double)g.M * g.IC);
+    if (!is_fc(g) || g.M > 128 || g.Ncols < 64 || g.IC < 8 || !below_2g((double)g.IC * g.Ncols) || !below_2g((double)g.M * g.IC))
+        return false;
+    const bool odd = (g.IC % 8) != 0 || (g.Ncols % 8) != 0, quick = !odd && (g.IC % 64) == 0;
+    if (g.M > 32)
+        return g.IC <= 1024 && (g.M <= 64 || g.Ncols <= 8192) && (!quick || g.M <= 80 || g.IC <= 768 || g.Ncols > 1024);
+    if (odd) return g.IC <= 4096 || g.Ncols >= 2048 || (g.IC <= 8192 && g.M <= 16);
+    if (!quick)
+        return g.IC <= 4096 || (g.IC <= 12288 && g.Ncols >= 6144) || (g.IC <= 6144 && (g.M <= 16 || g.Ncols <= 1024));
+    if (g.IC <= 4096) return g.M <= 16 || g.IC <= 2048 || g.Ncols <= 2048 || g.Ncols >= 9216;
+    return g.IC <= 8192 && (g.Ncols >= 12288 || (g.M <= 16 && g.Ncols <= 512));
 }
 
 // Where the output features alone would leave most CUs without work, the reduction is also divided over work-groups, as

@@ -220,6 +220,26 @@ def test_phases_of_a_strided_data_gradient_are_counted_in_64_bits(wap):
         assert name(stride) == plain, stride
 
 
+def test_streamed_fully_connected_products_by_shape(wap):
+    """Which fully-connected products are streams of the weights: where the streams ran in rounds of work-groups or waited on
+    one long row of them (few columns, many rows of Wt, long rows at many batch rows), the tiles are planned."""
+    def fwd(B, n_in, n_out):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD) == "fc_fwd_kernel"
+
+    def dx(B, n_in, n_out):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_BWD_DATA) == "fc_dx_kernel"
+    for B, i, o in ((1, 64, 1000), (16, 9216, 4096), (2, 25088, 4096), (16, 4096, 1000), (16, 2048, 8192), (8, 600, 10000), (16, 4551, 4096)):
+        assert fwd(B, i, o), (B, i, o)
+    for B, i, o in ((17, 4096, 1000), (16, 25088, 4096), (1, 64, 25088), (16, 64, 4112), (8, 4096, 9216), (2, 512, 25088), (8, 67, 25088)):
+        assert not fwd(B, i, o), (B, i, o)
+    for B, i, o in ((16, 4096, 4096), (32, 9216, 4096), (32, 25088, 4096), (128, 4096, 1000), (64, 1024, 1024), (80, 512, 1024),
+                    (16, 512, 8192), (32, 4096, 2048), (8, 16384, 8192), (32, 9216, 10000), (32, 4551, 8192)):
+        assert dx(B, i, o), (B, i, o)
+    for B, i, o in ((17, 4096, 4096), (32, 512, 25088), (4, 64, 25088), (8, 8192, 8192), (17, 512, 8192), (128, 512, 1024),
+                    (32, 4096, 9216), (16, 4096, 10000), (8, 501, 25088), (33, 4096, 4096)):
+        assert not dx(B, i, o), (B, i, o)
+
+
 def test_odd_channel_reduction_that_passes_int32_stays_element_by_element(wap):
     """Odd channel counts are rounded up to a multiple of 8 per filter tap; where that takes the reduction past int32 the
     kernel that counts the taps' own channels remains."""
