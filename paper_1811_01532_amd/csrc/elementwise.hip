@@ -28,17 +28,18 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
 // not positive (ReLU derivative of the layer below); with `colsum`, also the column sums of what is stored, one partial
 // row per work-group row range (the bias gradient of that layer).  Bound by the launch and the latency of the loads: the
 // partial sums of a layer small enough to be split are a few MB that the caches still hold.  A thread owns 16 bytes of a
-// row, `vpb` (a power of two) threads lie side by side, four splits are in flight.  The separate mask and column-sum
-// passes that this replaces took 5 us each at 1568 x 512. ----
+// row, `vpb` (a power of two) threads lie side by side, U splits are in flight, the last batch with its absent splits
+// loaded from the last one and left out (a loop over them waited for each: 2.9 us without, 3.8 with, 400 x 128 in 4 splits;
+// 96 x 1000 in 32 4.9 us, 9.7 with a load at a time).  The separate mask and column-sum passes that this replaces took 5 us
+// each at 1568 x 512. ----
+template <int U, bool COLSUM>
 __global__ __launch_bounds__(256) void reduce_bf16_kernel(const float* __restrict__ part, int nsplit, int rows, int ncols,
                                                           const float* __restrict__ bias, int relu,
                                                           const bf16_t* __restrict__ mask, bf16_t* __restrict__ out,
-                                                          float* __restrict__ colsum, int vpb, int colblocks,
-                                                          int rows_per_block) {
-    __shared__ float4 red[256];
-    const int rb = blockIdx.x / colblocks, cb = blockIdx.x - rb * colblocks;
-    const int vec = threadIdx.x & (vpb - 1), rsub = threadIdx.x / vpb, rp = 256 / vpb;
-    const int c = (cb * vpb + vec) * 4;
+                                                          float* __restrict__ colsum, int log_vpb, int rows_per_block) {
+    const int rb = blockIdx.y, vpb = 1 << log_vpb;
+    const int vec = threadIdx.x & (vpb - 1), rsub = threadIdx.x >> log_vpb, rp = 256 >> log_vpb;
+    const int c = ((int)blockIdx.x * vpb + vec) * 4;
     const size_t elems = (size_t)rows * ncols;
     float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c < ncols) {
@@ -50,21 +51,16 @@ __global__ __launch_bounds__(256) void reduce_bf16_kernel(const float* __restric
             const float* p = part + o;
             uint2 mk = make_uint2(0u, 0u);
             if (mask) mk = *reinterpret_cast<const uint2*>(mask + o);
-            float4 s = *reinterpret_cast<const float4*>(p);
-            int k = 1;
-            for (; k + 3 < nsplit; k += 4) {
-                const float4 t0 = *reinterpret_cast<const float4*>(p + (size_t)k * elems);
-                const float4 t1 = *reinterpret_cast<const float4*>(p + (size_t)(k + 1) * elems);
-                const float4 t2 = *reinterpret_cast<const float4*>(p + (size_t)(k + 2) * elems);
-                const float4 t3 = *reinterpret_cast<const float4*>(p + (size_t)(k + 3) * elems);
-                s.x += t0.x; s.y += t0.y; s.z += t0.z; s.w += t0.w;
-                s.x += t1.x; s.y += t1.y; s.z += t1.z; s.w += t1.w;
-                s.x += t2.x; s.y += t2.y; s.z += t2.z; s.w += t2.w;
-                s.x += t3.x; s.y += t3.y; s.z += t3.z; s.w += t3.w;
-            }
-            for (; k < nsplit; ++k) {
-                const float4 t = *reinterpret_cast<const float4*>(p + (size_t)k * elems);
-                s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int k = 0; k < nsplit; k += U) {
+                float4 t[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] = *reinterpret_cast<const float4*>(p + (size_t)(k + u < nsplit ? k + u : nsplit - 1) * elems);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (k + u == 0) s = t[0];
+                    else if (k + u < nsplit) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+                }
             }
             if (bias) { s.x += bv.x; s.y += bv.y; s.z += bv.z; s.w += bv.w; }
             if (relu) {
@@ -79,10 +75,12 @@ __global__ __launch_bounds__(256) void reduce_bf16_kernel(const float* __restric
                 h3 = __uint_as_float(mk.y & 0xffff0000u) > 0.f ? h3 : 0;
             }
             *reinterpret_cast<uint2*>(out + o) = make_uint2((unsigned)h0 | ((unsigned)h1 << 16), (unsigned)h2 | ((unsigned)h3 << 16));
+            if (!COLSUM) break;  // one row per thread
             cs.x += bf2f(h0); cs.y += bf2f(h1); cs.z += bf2f(h2); cs.w += bf2f(h3);
         }
     }
-    if (colsum) {  // the row slots of a column as a tree through LDS: order fixed by the shape
+    if constexpr (COLSUM) {  // the row slots of a column as a tree through LDS: order fixed by the shape
+        __shared__ float4 red[256];
         red[threadIdx.x] = cs;
         __syncthreads();
         for (int o = rp / 2; o > 0; o >>= 1) {
@@ -619,8 +617,17 @@ int launch_reduce_bf16(const float* part, int nsplit, size_t elems, int ncols, c
     }
     const int rows = (int)(elems / ncols), vpb = reduce_vpb(ncols), rpb = reduce_rows_per_block(ncols, colsum != nullptr);
     const int colblocks = (ncols / 4 + vpb - 1) / vpb;
-    hipLaunchKernelGGL(reduce_bf16_kernel, dim3((unsigned)((rows + rpb - 1) / rpb) * colblocks), dim3(256), 0, st, part, nsplit, rows,
-                       ncols, bias, relu ? 1 : 0, mask, out, colsum, vpb, colblocks, rpb);
+    int log_vpb = 0;
+    while ((1 << log_vpb) < vpb) ++log_vpb;
+    // (a split product has at most 192 tiles of 256 rows: fewer than 65536 row blocks)
+    const dim3 grid((unsigned)colblocks, (unsigned)((rows + rpb - 1) / rpb));
+#define WAP_REDUCE(U)                                                                                                        \
+    hipLaunchKernelGGL((colsum ? reduce_bf16_kernel<U, true> : reduce_bf16_kernel<U, false>), grid, dim3(256), 0, st, part, \
+                       nsplit, rows, ncols, bias, relu ? 1 : 0, mask, out, colsum, log_vpb, rpb)
+    if (nsplit <= 2) WAP_REDUCE(2);
+    else if (nsplit <= 4) WAP_REDUCE(4);
+    else WAP_REDUCE(8);
+#undef WAP_REDUCE
     return check_launch("reduce_bf16");
 }
 
