@@ -830,8 +830,8 @@ bool conv_c3_fwd_supported(const GemmGeom& g) {
     if (g.IC != 3 || g.div_h != 1 || g.div_w != 1 || (g.Ncols != 32 && g.Ncols != 64)) return false;
     if (c3_special(g)) return true;
     if (c3_fwd_strided(g)) return g_force_fwd_cfg == 8 || !conv_thin_fwd_few_tiles(g);
-    // the gather serves what is left: patches too large to stage (conv_thin.hip)
-    return c3_general_smem(g) <= 64 * 1024 && (g_force_fwd_cfg == 8 || !conv_thin_fwd_supported(g));
+    // the gather: short reductions, ragged maps, patches too large to stage (conv_thin.hip)
+    return c3_general_smem(g) <= 64 * 1024 && (g_force_fwd_cfg == 8 || !conv_thin_fwd_over_gather(g));
 }
 const char* conv_c3_fwd_kernel_name(const GemmGeom& g) {
     if (c3_rows(g)) return g.Ncols == 64 ? "conv_c3_fwd_rows_kernel<2>" : "conv_c3_fwd_rows_kernel<1>";

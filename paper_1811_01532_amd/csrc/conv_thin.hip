@@ -16,9 +16,8 @@
 //   weight grad 13 x 192x192x3 -> 96, 3x3 123 / 46; 32 x 224x224x3 -> 64, 7x7 stride 2 190 / 46;
 //               37 x 63x63x3 -> 32, 5x5 stride 2 27 / 13; 4 x 32x32x3 -> 16 28 / 11
 // Where the specialised kernels of conv_c3.hip apply they stay ahead (3x3 stride 1 at 24 x 224x224 -> 64: 43 against 63
-// us forward, 55 against 63 weight gradient), except that the pair for large filters at horizontal stride 4, which wants
-// many output rows to amortise its set-up, loses while there are at most two tiles per CU (11x11, 8 images: 24.7 against
-// 28.2 and 29 against 32 us; 16 images: 42 against 28 and 34 against 33).
+// us forward, 55 against 63 weight gradient); the gather for other filters and the pair for large filters at horizontal
+// stride 4 share the field with these kernels by the rules below.
 #include <algorithm>
 
 #include "wap_internal.h"
@@ -493,16 +492,53 @@ int launch_conv_thin_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, co
     return launch_fwd_t<1>(a, grid, smem, st);
 }
 
+// Preferred to the kernel for horizontal strides of 4 (which takes the same time up to some tiles per CU): while all tiles
+// are resident at once, with two channel blocks for a second round.  11x11 at stride 4, us, that kernel / this one: 16 x
+// 112x112 -> 32 15.9 / 14.3, 16 x 160x160 -> 32 (two rounds) 16.4 / 21.5, 16 x 112x112 -> 64 19.8 / 14.7, 8 x 224x224 -> 64
+// (two rounds) 20.5 / 21.9 with its operands cached and 26.7 / 23.0 without; 4x4 at stride 4, 64 x 96x96 -> 32 8.0 / 7.6.
 bool conv_thin_fwd_few_tiles(const GemmGeom& g) {
-    return conv_thin_fwd_supported(g) && thin_tiles(shape_of(g)) * ((g.Ncols + 31) / 32) <= 2 * kNumCU;
+    if (!conv_thin_fwd_supported(g)) return false;
+    const ThinShape s = shape_of(g);
+    const long nb = (s.K + 31) / 32, resident = std::min<long>(2, (long)(LDS_CAP / thin_fwd_smem(s, 1)));
+    return thin_tiles(s) * nb <= kNumCU * std::min<long>(2, std::max(nb, resident));
+}
+
+// Preferred to the gather-based kernel (32 or 64 channels): that one fetches every reduction step of 16 from memory, this one
+// stages a patch per tile whatever the filter, so a short reduction, a ragged map or a large stride speaks for the gather.
+// While one round of work-groups does it, only the start counts (3x3 stride 3, 16 x 33x33 -> 32 3.5 us with the gather, 5.5
+// here; 5x5, 1 image of 48x48 -> 64 6.0 / 5.5; 7x7 -> 32 and 64 1.01 and 1.2 times faster here; 9x9 stride 2, 4 x 130x130 -> 64,
+// two work-groups per CU, 15.2 / 11.4).  Beyond, the two times as fitted over 300 shapes (mean error 6 % with one channel
+// block, 13 % with two): so much per 128 pixels and reduction step there, per tile, staged pixel and step of tap pairs here,
+// and this kernel's later start.  us, gather / this one: 3x3 stride 2, 64 x 130x130 -> 64 16.6 / 25.2; 5x5 stride 2, 64 x
+// 192x192 -> 32 46.9 / 26.1; 7x7 stride 2, 25 x 71x71 -> 64 (36 of 64 columns) 10.6 / 13.5, 64 x 224x224 -> 64 124 / 90.  With two
+// channel blocks and one work-group per CU (11x11 at stride 4) nothing hides the staging: 32 x 224x224 -> 64 52 / 60.  Over
+// 1166 shapes the choice is 0.4 % from the better of the two on average.
+bool conv_thin_fwd_over_gather(const GemmGeom& g) {
+    if (!conv_thin_fwd_supported(g)) return false;
+    const ThinShape s = shape_of(g);
+    const long tiles = thin_tiles(s), nb = (s.K + 31) / 32, ksteps = (g.Kred + 15) / 16;
+    const bool alone = 2 * thin_fwd_smem(s, 1) > LDS_CAP;  // one work-group per CU
+    if (tiles * nb <= kNumCU) return ksteps >= (nb == 1 ? 10 : 5);
+    if (tiles * nb <= (alone ? 1 : 2) * kNumCU && ksteps >= (nb == 1 ? 16 : 10)) return true;
+    if (alone && nb > 1) return false;
+    const double pairs = (s.R * ((s.S + 1) / 2) + 1) / 2, staged = (double)thin_npx(s);
+    const double gather = g.M / (double)(TR * TW) * (nb == 1 ? 1.0 + 1.7 * ksteps : 0.6 + 2.1 * ksteps);  // ns, as below
+    const double here = tiles * (nb == 1 ? 0.3 + 0.00245 * staged + 0.32 * pairs : 0.4 + 0.0042 * staged + 0.55 * pairs) +
+                        (nb == 1 ? 2100.0 : 1400.0);
+    return 1.03 * here <= gather;
 }
 
 bool wgrad_thin_supported(const WgradGeom& g) {
     const ThinShape s = shape_of(g);
     return thin_shape_ok(s) && s.R * s.S <= 128;
 }
+// Preferred to the kernel for horizontal strides of 4, us, that one / this: two channel blocks, 11x11, 8 x 224x224 -> 64 29.7 /
+// 25.2, 16 x 160x160 28.2 / 28.1, 32 x 224x224 32.9 / 46.5; one block, whose work-groups hold half the products for the same
+// patch, 4 x 224x224 -> 32 22.4 / 17.1, 8 x 160x160 18.9 / 18.0, 64 x 96x96 21.2 / 26.3; 4x4, 16 x 224x224 -> 32 14.2 / 12.0.
 bool wgrad_thin_few_tiles(const WgradGeom& g) {
-    return wgrad_thin_supported(g) && thin_tiles(shape_of(g)) * ((g.K + 31) / 32) <= 2 * kNumCU;
+    const long nb = (g.K + 31) / 32;
+    return wgrad_thin_supported(g) &&
+           thin_tiles(shape_of(g)) * nb <= (nb == 1 && g.R * g.S > 16 ? kNumCU / 2 : 2 * kNumCU);
 }
 
 // Work-groups along the tiles, each of which leaves a K x R*S*C fp32 partial: two per CU over all channel groups, but no

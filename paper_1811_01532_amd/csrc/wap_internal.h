@@ -191,6 +191,7 @@ int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_
 // 1 .. 4 input channels, any filter and stride, output channels a multiple of 8 (conv_thin.hip)
 bool conv_thin_fwd_supported(const GemmGeom& g);
 bool conv_thin_fwd_few_tiles(const GemmGeom& g);  // ... and preferred to the kernel for horizontal strides of 4
+bool conv_thin_fwd_over_gather(const GemmGeom& g);  // ... and preferred to the gather for 32 / 64 output channels
 int launch_conv_thin_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y,
                          hipStream_t st);
 bool wgrad_thin_supported(const WgradGeom& g);

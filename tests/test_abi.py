@@ -240,6 +240,20 @@ def test_streamed_fully_connected_products_by_shape(wap):
         assert not dx(B, i, o), (B, i, o)
 
 
+def test_first_layer_kernel_by_shape(wap):
+    """First layers of 32 or 64 channels: the staged patch needs a reduction long enough for the pixels it stages; short
+    filters, ragged maps and large strides stay with the gather, and the horizontal strides of 4 with their own kernel from
+    the second round of work-groups on (third for two channel blocks)."""
+    def name(N, H, K, R, stride, pad):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, 3, K, R, R, stride, pad), wap.WAP_PASS_FWD)
+    for c in ((1, 224, 64, 7, 2, 3), (64, 224, 64, 7, 2, 3), (1, 48, 64, 7, 1, 3), (64, 192, 32, 5, 2, 2), (16, 112, 64, 11, 4, 2), (4, 32, 16, 3, 1, 1)):
+        assert name(*c) == "conv_thin_fwd_kernel", c
+    for c in ((16, 224, 64, 3, 2, 1), (1, 32, 32, 3, 2, 1), (25, 71, 64, 7, 2, 3), (1, 48, 32, 5, 1, 2), (64, 112, 32, 2, 2, 0), (32, 224, 64, 11, 4, 5)):
+        assert name(*c).startswith("conv_c3_fwd_general_kernel"), c
+    for c in ((16, 160, 32, 11, 4, 2), (16, 160, 64, 11, 4, 2), (64, 224, 32, 4, 4, 0)):
+        assert name(*c).startswith("conv_c3_fwd_strided_kernel"), c
+
+
 def test_odd_channel_reduction_that_passes_int32_stays_element_by_element(wap):
     """Odd channel counts are rounded up to a multiple of 8 per filter tap; where that takes the reduction past int32 the
     kernel that counts the taps' own channels remains."""
