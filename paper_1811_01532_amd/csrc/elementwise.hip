@@ -2,6 +2,8 @@
 // max-pool forward / backward, softmax cross-entropy, SGD, casts.  These are the "auxiliary
 // computation nodes" of Section 3.2.2 and the weight update of Section 3.2.3; all are streaming
 // kernels with 16-byte accesses where the shape allows and a grid sized to cover the chip.
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -138,110 +140,135 @@ __global__ void reduce_f32_kernel(const float* __restrict__ part, int nsplit, si
     }
 }
 
-// Many splits of a small tensor: G groups of threads each add the splits k = g, g + G, g + 2G, ... of one
-// 16-byte column in increasing k (four independent loads in flight), then the G partial sums are added in
-// group order through LDS.  The summation tree is fixed by (nsplit, G), so results are bitwise reproducible.
-template <int G>
+// Many splits of a small tensor: G groups of threads each add the splits k = g, g + G, g + 2G, ... of one 16-byte column
+// (V = float4; one element where the tensor is no multiple of four) in increasing k (four independent loads in flight), then
+// the G partial sums are added in group order through LDS.  The summation tree is fixed by (nsplit, G), so results are bitwise
+// reproducible.  (A thread per element that walks all splits takes 0.2 us for each: the bias gradient of 50176 x 33 in 784
+// chunks 176 us.)
+__device__ __forceinline__ void acc4(float4& s, const float4& t) { s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; }
+__device__ __forceinline__ void acc4(float& s, float t) { s += t; }
+template <int G, typename V>
 __global__ __launch_bounds__(256) void reduce_f32_grouped_kernel(const float* __restrict__ part, int nsplit, size_t elems,
                                                                float* __restrict__ out, const SgdFuse sgd) {
-    constexpr int COLS = 256 / G;
-    __shared__ float4 sm[G][COLS];
+    constexpr int COLS = 256 / G, VEC = sizeof(V) / sizeof(float);
+    __shared__ V sm[G][COLS];
     const int col = threadIdx.x % COLS, grp = threadIdx.x / COLS;
-    const size_t n4 = elems / 4;
+    const size_t nv = elems / VEC;
     const size_t i = (size_t)blockIdx.x * COLS + col;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < n4) {
-        const float4* p = reinterpret_cast<const float4*>(part) + i;
+    V s = {};
+    if (i < nv) {
+        const V* p = reinterpret_cast<const V*>(part) + i;
         int k = grp;
         for (; k + 3 * G < nsplit; k += 4 * G) {
-            float4 t0 = p[(size_t)k * n4], t1 = p[(size_t)(k + G) * n4], t2 = p[(size_t)(k + 2 * G) * n4],
-                   t3 = p[(size_t)(k + 3 * G) * n4];
-            s.x += t0.x; s.y += t0.y; s.z += t0.z; s.w += t0.w;
-            s.x += t1.x; s.y += t1.y; s.z += t1.z; s.w += t1.w;
-            s.x += t2.x; s.y += t2.y; s.z += t2.z; s.w += t2.w;
-            s.x += t3.x; s.y += t3.y; s.z += t3.z; s.w += t3.w;
+            const V t0 = p[(size_t)k * nv], t1 = p[(size_t)(k + G) * nv], t2 = p[(size_t)(k + 2 * G) * nv],
+                    t3 = p[(size_t)(k + 3 * G) * nv];
+            acc4(s, t0); acc4(s, t1); acc4(s, t2); acc4(s, t3);
         }
-        for (; k < nsplit; k += G) {
-            float4 t = p[(size_t)k * n4];
-            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-        }
+        for (; k < nsplit; k += G) acc4(s, p[(size_t)k * nv]);
     }
     sm[grp][col] = s;
     __syncthreads();
-    if (grp == 0 && i < n4) {
+    if (grp == 0 && i < nv) {
 #pragma unroll
-        for (int g2 = 1; g2 < G; ++g2) {
-            float4 t = sm[g2][col];
-            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+        for (int g2 = 1; g2 < G; ++g2) acc4(s, sm[g2][col]);
+        if constexpr (VEC == 4) {
+            if (sgd.w32) sgd_apply4(sgd.w32 + i * 4, sgd.wb + i * 4, sgd.lr, s.x, s.y, s.z, s.w);
+            else reinterpret_cast<float4*>(out)[i] = s;
+        } else if (sgd.w32) {
+            const float a = sgd_apply(sgd.w32[i], s, sgd.lr);
+            sgd.w32[i] = a;
+            sgd.wb[i] = f2bf(a);
+        } else {
+            out[i] = s;
         }
-        if (sgd.w32) sgd_apply4(sgd.w32 + i * 4, sgd.wb + i * 4, sgd.lr, s.x, s.y, s.z, s.w);
-        else reinterpret_cast<float4*>(out)[i] = s;
     }
 }
 
 // ---- bias gradient, first stage: column sums of a chunk of rows (blockIdx.y) for a block of column vectors
-// (blockIdx.x) of VEC channels.  `vpb` (a power of two) vectors lie side by side in a work-group, its other threads take
-// every RP-th row, eight loads in flight each (the loop is bound by load latency, not by bytes: a whole FC layer's
-// gradient is 0.8 MB), and the RP partial sums of a column are added as a tree through LDS.  The order is fixed by
-// (rows, cols): bitwise reproducible.  Few wide work-groups with one load in flight and a serial sum over RP took
-// 24 us for 4096 x 16, 33 us for 100 x 4096 and 14 us for 16900 x 256; this takes 7, 5 and 10. ----
+// (blockIdx.x) of VEC channels.  `vpb` vectors lie side by side in a work-group, `rp` rows below each other (its threads
+// cover whole rows, or runs of them, whatever their length), eight loads in flight each (the loop is bound by load latency,
+// not by bytes: a whole FC layer's gradient is 0.8 MB; the last batch loads its absent rows from the last one and leaves
+// them out), and the rp partial sums of a column are added as a tree through LDS.  The order is fixed by (rows, cols):
+// bitwise reproducible.  Few wide work-groups with one load in flight and a serial sum over rp took 17 us for 100 x 4096, 18
+// for 67600 x 256 and 55 for 50176 x 33; this takes 3.2, 9.2 and 6.2. ----
+template <int VEC> struct BiasVec;
+template <> struct BiasVec<8> { using type = u32x4; };
+template <> struct BiasVec<4> { using type = u32x2; };
+template <> struct BiasVec<1> { using type = bf16_t; };
 template <int VEC>
-__device__ __forceinline__ void add_vec(float* s, const bf16_t* p) {
-    if (VEC == 8) {
-        const u32x4 u = *reinterpret_cast<const u32x4*>(p);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            s[2 * k] += __uint_as_float(u[k] << 16);
-            s[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
-        }
-    } else if (VEC == 4) {
-        const u32x2 u = *reinterpret_cast<const u32x2*>(p);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            s[2 * k] += __uint_as_float(u[k] << 16);
-            s[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
-        }
+__device__ __forceinline__ void add_vec(float* s, const typename BiasVec<VEC>::type u) {
+    if constexpr (VEC == 1) {
+        s[0] += bf2f(u);
     } else {
-        s[0] += bf2f(p[0]);
+#pragma unroll
+        for (int k = 0; k < VEC / 2; ++k) {
+            s[2 * k] += __uint_as_float(u[k] << 16);
+            s[2 * k + 1] += __uint_as_float(u[k] & 0xffff0000u);
+        }
     }
 }
 
 template <int VEC>
 __global__ __launch_bounds__(1024) void bias_grad_kernel(const bf16_t* __restrict__ dy, float* __restrict__ part,
-                                                        size_t rows, int cols, size_t rows_per_chunk, int vpb) {
+                                                        uint32_t rows, uint32_t cols, uint32_t rows_per_chunk, int vpb, int rp) {
+    using V = typename BiasVec<VEC>::type;
     __shared__ float red[VEC][1024];
-    const int cv = cols / VEC;                     // vectors per row
-    const int rp = blockDim.x / vpb;                   // rows in flight per pass
-    const int vec = threadIdx.x & (vpb - 1), rsub = threadIdx.x / vpb;
+    const int cv = (int)(cols / VEC);              // vectors per row
+    const int rsub = threadIdx.x / vpb, vec = threadIdx.x - rsub * vpb;
     const int v = blockIdx.x * vpb + vec;
-    const size_t r0 = (size_t)blockIdx.y * rows_per_chunk;
-    size_t r1 = r0 + rows_per_chunk;
-    if (r1 > rows) r1 = rows;
+    // (32-bit offsets: a tensor has at most 2^31 - 1 elements)
+    const uint32_t r0 = blockIdx.y * rows_per_chunk, r1 = r0 + rows_per_chunk < rows ? r0 + rows_per_chunk : rows;
     float s[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) s[e] = 0.f;
-    if (v < cv) {
+    if (v < cv && rsub < rp) {
         const bf16_t* p = dy + (size_t)v * VEC;
-        size_t r = r0 + rsub;
-        for (; r + 7 * (size_t)rp < r1; r += 8 * (size_t)rp) {
+        for (uint32_t r = r0 + rsub; r < r1; r += 8u * rp) {
+            V t[8];
+            if (r + 7u * rp < r1) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) add_vec<VEC>(s, p + (r + (size_t)k * rp) * cols);
+                for (int k = 0; k < 8; ++k) t[k] = *reinterpret_cast<const V*>(p + (r + (uint32_t)k * rp) * cols);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) add_vec<VEC>(s, t[k]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const uint32_t rk = r + (uint32_t)k * rp;
+                    t[k] = *reinterpret_cast<const V*>(p + (rk < r1 ? rk : r1 - 1) * cols);
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (r + (uint32_t)k * rp < r1) add_vec<VEC>(s, t[k]);
+            }
         }
-        for (; r < r1; r += rp) add_vec<VEC>(s, p + r * cols);
     }
+    if (rp > 1) {  // (uniform)
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] = s[e];
-    __syncthreads();
-    for (int o = rp / 2; o > 0; o >>= 1) {
-        if (rsub < o) {
+        for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] = s[e];
+        for (int n = rp; n > 1;) {  // four rows into one: half the barriers of a tree of pairs
+            const int h = (n + 3) >> 2;
+            __syncthreads();
+            if (rsub < h) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] += red[e][threadIdx.x + o * vpb];
+                for (int q = 1; q < 4; ++q)
+                    if (rsub + q * h < n) {
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) s[e] += red[e][threadIdx.x + q * h * vpb];
+                    }
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) red[e][threadIdx.x] = s[e];
+            }
+            n = h;
         }
-        __syncthreads();
     }
     if (rsub == 0 && v < cv) {
+        float* o = part + (size_t)blockIdx.y * cols + (size_t)v * VEC;
+        if constexpr (VEC == 1) {
+            *o = s[0];
+        } else {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) part[(size_t)blockIdx.y * cols + (size_t)v * VEC + e] = red[e][vec];
+            for (int e = 0; e < VEC; e += 4) *reinterpret_cast<float4*>(o + e) = make_float4(s[e], s[e + 1], s[e + 2], s[e + 3]);
+        }
     }
 }
 
@@ -634,15 +661,16 @@ int launch_reduce_bf16(const float* part, int nsplit, size_t elems, int ncols, c
 int launch_reduce_f32(const float* part, int nsplit, size_t elems, float* out, hipStream_t st, const SgdFuse* sgdp) {
     SgdFuse sgd = {nullptr, nullptr, 0.f};
     if (sgdp) sgd = *sgdp;
-    if ((elems & 3) == 0 && nsplit >= 8) {
-        const size_t n4 = elems / 4;
-        if (nsplit >= 64) {
-            hipLaunchKernelGGL(reduce_f32_grouped_kernel<32>, dim3((unsigned)((n4 + 7) / 8)), dim3(256), 0, st, part, nsplit,
-                               elems, out, sgd);
-        } else {
-            hipLaunchKernelGGL(reduce_f32_grouped_kernel<8>, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, st, part, nsplit,
-                               elems, out, sgd);
-        }
+    if (nsplit >= 8) {
+        const bool vec = (elems & 3) == 0;
+        const size_t nv = vec ? elems / 4 : elems;
+#define WAP_GROUPED(G, V) \
+    hipLaunchKernelGGL((reduce_f32_grouped_kernel<G, V>), dim3((unsigned)((nv + 256 / G - 1) / (256 / G))), dim3(256), 0, st, part, nsplit, elems, out, sgd)
+        if (nsplit >= 64 && vec) WAP_GROUPED(32, float4);
+        else if (nsplit >= 64 && elems <= 4096) WAP_GROUPED(32, float);  // (rows of 32 bytes)
+        else if (vec) WAP_GROUPED(8, float4);
+        else WAP_GROUPED(8, float);
+#undef WAP_GROUPED
         return check_launch("reduce_f32_grouped");
     }
     hipLaunchKernelGGL(reduce_f32_kernel, dim3(grid_for(elems / 4 + 1)), dim3(kThreads), 0, st, part,
@@ -754,51 +782,57 @@ int launch_colsum_f32_multi(const ColsumJobs& js, void* base, hipStream_t st) {
     return check_launch("colsum_f32_finish");
 }
 
-// How the first stage is laid out: 16-byte vectors where the row length allows it (8-byte, else 2-byte), up to 16 of
-// them side by side (256-byte runs of a row; fewer threads per row means more rows in flight and more work-groups).
+// How the first stage is laid out: 16-byte vectors where the row length allows it (8-byte, else 2-byte).  A few rows are
+// summed in one chunk, whose sums are the result (no second launch of about 4.6 us): up to 512 rows, and
+// while a thread of a 1024-thread work-group walks at most 16 rows, i.e. two batches of loads.  Up to 16 vectors (64 elements)
+// lie side by side: 256-byte runs of a row, fewer threads per row mean more rows in flight and more work-groups.  More rows
+// are divided into chunks of 16 rows per thread of 256-thread work-groups.  Rows that are no whole 128-byte lines go to a
+// work-group in one piece there, 32 rows per thread: narrower blocks fetch their border lines twice, from two L2s (50176 x 1000
+// 28.5 us in 256-byte runs, 21.6 in whole rows; 802816 x 200 80 and 59; 12544 x 500, where the fetches hide, 7.0 and 7.6).
 struct BiasGradShape {
-    int vecw, vpb, colblocks;
+    int vecw, vpb, colblocks, chunks, rp;
+    size_t rpc;  // rows per chunk
 };
-static BiasGradShape bias_grad_shape(int cols) {
+static BiasGradShape bias_grad_shape(size_t rows, int cols) {
     BiasGradShape b;
     b.vecw = (cols & 7) == 0 ? 8 : (cols & 3) == 0 ? 4 : 1;
     const int cv = cols / b.vecw;
-    const int most = b.vecw == 1 ? 64 : 16;
-    b.vpb = 1;
-    while (b.vpb < cv && b.vpb < most) b.vpb *= 2;
-    b.colblocks = (cv + b.vpb - 1) / b.vpb;
+    auto blocks = [&](int most) {
+        b.colblocks = (cv + most - 1) / most;
+        b.vpb = (cv + b.colblocks - 1) / b.colblocks;
+    };
+    blocks(b.vecw == 1 ? 64 : 16);
+    b.chunks = 1;
+    b.rpc = rows;
+    b.rp = 1024 / b.vpb;
+    if (rows > 512 && rows > (size_t)16 * b.rp) {
+        const bool lines = (cols & 63) == 0;
+        if (!lines) blocks(b.vecw == 1 ? 256 : 128);
+        b.rp = 256 / b.vpb;
+        const size_t per = (size_t)(lines ? 16 : 32) * b.rp;
+        size_t cap = (size_t)kNumCU * 8 / b.colblocks;  // at most ~8 work-groups per CU
+        if (cap < 1) cap = 1;
+        b.chunks = (int)std::min((rows + per - 1) / per, cap);
+        b.rpc = (rows + b.chunks - 1) / b.chunks;
+    }
+    b.rp = (int)std::min<size_t>((size_t)b.rp, (b.rpc + 7) / 8);  // one batch of loads is enough: a shorter tree
     return b;
 }
-
-// Row chunks (= partial sums per column) of the first stage.  One chunk, whose sums are the result (no second launch of
-// about 4.6 us), while a thread of a 1024-thread work-group walks at most 16 rows, i.e. two batches of loads; beyond
-// that about 16 rows per thread of 256-thread work-groups, at most ~8 of them per CU over all column blocks.
-int bias_grad_chunks(size_t rows, int cols) {
-    const BiasGradShape b = bias_grad_shape(cols);
-    if (rows <= (size_t)16 * (1024 / b.vpb)) return 1;
-    const size_t rp = 256 / b.vpb;
-    size_t chunks = (rows + 16 * rp - 1) / (16 * rp);
-    size_t cap = (size_t)kNumCU * 8 / b.colblocks;
-    if (cap < 1) cap = 1;
-    if (chunks > cap) chunks = cap;
-    return (int)chunks;
-}
+int bias_grad_chunks(size_t rows, int cols) { return bias_grad_shape(rows, cols).chunks; }
 
 int launch_bias_grad(size_t rows, int cols, const bf16_t* dy, float* db, float* part, hipStream_t st) {
-    const int chunks = bias_grad_chunks(rows, cols);
-    const size_t rpc = (rows + chunks - 1) / chunks;
-    const BiasGradShape b = bias_grad_shape(cols);
-    float* dst = chunks == 1 ? db : part;  // a single chunk writes the result itself
-    const dim3 grid(b.colblocks, chunks), block(chunks == 1 && rows > (size_t)2 * (256 / b.vpb) ? 1024 : 256);
+    const BiasGradShape b = bias_grad_shape(rows, cols);
+    float* dst = b.chunks == 1 ? db : part;  // a single chunk writes the result itself
+    const dim3 grid(b.colblocks, b.chunks), block((b.vpb * b.rp + 63) / 64 * 64);
     if (b.vecw == 8)
-        hipLaunchKernelGGL(bias_grad_kernel<8>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
+        hipLaunchKernelGGL(bias_grad_kernel<8>, grid, block, 0, st, dy, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)b.rpc, b.vpb, b.rp);
     else if (b.vecw == 4)
-        hipLaunchKernelGGL(bias_grad_kernel<4>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
+        hipLaunchKernelGGL(bias_grad_kernel<4>, grid, block, 0, st, dy, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)b.rpc, b.vpb, b.rp);
     else
-        hipLaunchKernelGGL(bias_grad_kernel<1>, grid, block, 0, st, dy, dst, rows, cols, rpc, b.vpb);
+        hipLaunchKernelGGL(bias_grad_kernel<1>, grid, block, 0, st, dy, dst, (uint32_t)rows, (uint32_t)cols, (uint32_t)b.rpc, b.vpb, b.rp);
     int rc = check_launch("bias_grad");
-    if (rc != WAP_OK || chunks == 1) return rc;
-    return launch_reduce_f32(part, chunks, (size_t)cols, db, st);
+    if (rc != WAP_OK || b.chunks == 1) return rc;
+    return launch_reduce_f32(part, b.chunks, (size_t)cols, db, st);
 }
 
 int launch_relu_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dx, size_t n, hipStream_t st) {

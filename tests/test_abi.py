@@ -254,6 +254,13 @@ def test_first_layer_kernel_by_shape(wap):
         assert name(*c).startswith("conv_c3_fwd_strided_kernel"), c
 
 
+def test_bias_gradient_of_up_to_512_rows_is_one_chunk(wap):
+    """A minibatch of rows is summed in one launch, whatever the number of columns: the workspace query is one row of sums."""
+    for cols in (1, 3, 33, 64, 125, 475, 500, 1000, 4096, 9999):
+        for rows in (1, 64, 257, 512):
+            assert wap.wap_bias_grad_workspace_bytes(rows, cols) == cols * 4, (rows, cols)
+
+
 def test_odd_channel_reduction_that_passes_int32_stays_element_by_element(wap):
     """Odd channel counts are rounded up to a multiple of 8 per filter tap; where that takes the reduction past int32 the
     kernel that counts the taps' own channels remains."""

@@ -10,11 +10,14 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 
+# (rows that are no whole 128-byte lines also in chunks: whole rows side by side, odd numbers of them below each other, chunk
+# sums added by groups of splits for any number of columns)
 # rows around the limit of one row chunk (16 per thread of 1024: 1024 with 16 vectors side by side, 8192 with two, 256
 # with 64 scalars) and of the small work-group (two rows per thread of 256), 16- / 8- / 2-byte vectors, column blocks
 # with a ragged end
 @pytest.mark.parametrize("rows,cols", [(1024, 128), (1025, 128), (8192, 16), (8193, 16), (32, 500), (33, 500), (3, 4),
-                                       (256, 125), (257, 125), (70, 3), (100, 4096), (2000, 136)])
+                                       (256, 125), (257, 125), (70, 3), (100, 4096), (2000, 136), (1, 12), (9, 500), (512, 475), (513, 475), (513, 72),
+                                       (6000, 33), (20000, 17), (3001, 1000), (40000, 3), (2049, 2051), (5000, 1)])
 def test_bias_grad_layout_edges(orc, rows, cols):
     import paper_1811_01532_amd as wap
     print(f"[case] bias_grad edges rows={rows} cols={cols}", flush=True)
