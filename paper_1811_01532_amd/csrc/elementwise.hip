@@ -302,6 +302,22 @@ struct PoolArgs {
     FastDiv dCV, dX, dY;   // item -> channel vector, x, y, image: divisions by vectors per pixel, items per row, rows
 };
 
+// VEC maxima (fp32 bits) and their window positions at element o
+template <int VEC>
+__device__ __forceinline__ void pool_store_max(bf16_t* y, uint8_t* am, size_t o, const unsigned* best, const unsigned* bi) {
+    if constexpr (VEC == 8) {
+        u32x4 yo;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) yo[k] = (best[2 * k] >> 16) | best[2 * k + 1];
+        *reinterpret_cast<u32x4*>(y + o) = yo;
+        const u32x2 ao = {bi[0] | (bi[1] << 8) | (bi[2] << 16) | (bi[3] << 24), bi[4] | (bi[5] << 8) | (bi[6] << 16) | (bi[7] << 24)};
+        *reinterpret_cast<u32x2*>(am + o) = ao;
+    } else {
+        y[o] = (bf16_t)(best[0] >> 16);
+        am[o] = (uint8_t)bi[0];
+    }
+}
+
 template <int VEC, int WIN>
 __global__ void maxpool_fwd_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, uint8_t* __restrict__ am,
                                    const PoolArgs a) {
@@ -335,22 +351,11 @@ __global__ void maxpool_fwd_kernel(const bf16_t* __restrict__ x, bf16_t* __restr
                 bi[e] = take ? (unsigned)k : bi[e];
             }
         }
-        const size_t o = (size_t)t * a.C + (size_t)cv * VEC;
-        if (VEC == 8) {
-            u32x4 yo;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) yo[k] = (best[2 * k] >> 16) | best[2 * k + 1];
-            *reinterpret_cast<u32x4*>(y + o) = yo;
-            const u32x2 ao = {bi[0] | (bi[1] << 8) | (bi[2] << 16) | (bi[3] << 24), bi[4] | (bi[5] << 8) | (bi[6] << 16) | (bi[7] << 24)};
-            *reinterpret_cast<u32x2*>(am + o) = ao;
-        } else {
-            y[o] = (bf16_t)(best[0] >> 16);
-            am[o] = (uint8_t)bi[0];
-        }
+        pool_store_max<VEC>(y, am, (size_t)t * a.C + (size_t)cv * VEC, best, bi);
     }
 }
 
-// any other window side
+// any other window side (VEC channels by one load, as above: element by element 8 x 40 x 40 x 64, window 5, took 21 us for 12)
 template <int VEC>
 __global__ void maxpool_fwd_any_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, uint8_t* __restrict__ am, int win,
                                        const PoolArgs a) {
@@ -364,20 +369,26 @@ __global__ void maxpool_fwd_any_kernel(const bf16_t* __restrict__ x, bf16_t* __r
         const uint32_t n = fdiv(t2, a.dY);
         const int p = (int)(t2 - n * a.P);
         const bf16_t* src = x + (((size_t)n * a.H + (size_t)p * a.st) * a.W + (size_t)q * a.st) * a.C + (size_t)cv * VEC;
-        unsigned short best[VEC];
-        uint8_t bi[VEC];
+        unsigned best[VEC], bi[VEC];  // best: as fp32 bits
         for (int r = 0; r < win; ++r)
-            for (int s = 0; s < win; ++s) {
-                const bf16_t* v = src + ((size_t)r * a.W + s) * a.C;
+            for (int q2 = 0; q2 < win; ++q2) {
+                const bf16_t* x1 = src + ((size_t)r * a.W + q2) * a.C;
+                unsigned f[VEC];
+                if constexpr (VEC == 8) {
+                    const u32x4 u = *reinterpret_cast<const u32x4*>(x1);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    if ((r | s) == 0 || bf2f(v[e]) > bf2f(best[e])) { best[e] = v[e]; bi[e] = (uint8_t)(r * win + s); }
+                    for (int e = 0; e < VEC; ++e) f[e] = (e & 1) ? u[e >> 1] & 0xffff0000u : u[e >> 1] << 16;
+                } else {
+                    f[0] = (unsigned)*x1 << 16;
+                }
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const bool take = (r | q2) == 0 || __uint_as_float(f[e]) > __uint_as_float(best[e]);
+                    best[e] = take ? f[e] : best[e];
+                    bi[e] = take ? (unsigned)(r * win + q2) : bi[e];
+                }
             }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            y[(size_t)t * a.C + (size_t)cv * VEC + e] = best[e];
-            am[(size_t)t * a.C + (size_t)cv * VEC + e] = bi[e];
-        }
+        pool_store_max<VEC>(y, am, (size_t)t * a.C + (size_t)cv * VEC, best, bi);
     }
 }
 
