@@ -9,7 +9,7 @@ extern "C" {
 #endif
 
 /* Process-wide and NOT thread safe (plain globals read while a plan is made): force the tile configuration of
- * the forward-type kernels (0..9; 12 / 13 / 14: the patch kernel's flat 64 x 128 / 224 x 128 / 192 x 64 tiles with
+ * the forward-type kernels (0..9; 12 / 14: the patch kernel's flat 64 x 128 / 192 x 64 tiles with
  * the reduction in nsplit >= 2 parts; 15: the few-channel kernel), of the weight-gradient kernel (0..4; 7: the
  * few-channel kernel; 5 / 6: the patch kernel with two / one
  * 32-channel dy blocks per wavefront) and the number of reduction splits;

@@ -114,6 +114,7 @@ __device__ __forceinline__ void each_tap(F& f, std::integer_sequence<int, T...>)
 template <int FN, int TW, int FM, int PG, bool UP, int ST>
 __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     constexpr bool FLAT = (TW == 0);
+    constexpr bool SPLIT = FLAT && FM < 7;  // may walk a part of the reduction (the 224-pixel tiles have no register left for it)
     constexpr int BM = 32 * FM * PG;
     constexpr int CG = 4 / PG;
     constexpr int TWD = FLAT ? 1 : TW;  // divisor that is never zero
@@ -127,9 +128,9 @@ __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     const int pg = wave % PG, cg = wave / PG;  // pixel group, channel group
     constexpr int BN = 32 * FN * CG;
 
-    int logical = xcd_remap(blockIdx.x, a.tiles_m * a.tiles_n * (FLAT ? a.nsplit : 1));
+    int logical = xcd_remap(blockIdx.x, a.tiles_m * a.tiles_n * (SPLIT ? a.nsplit : 1));
     int split = 0;
-    if (FLAT) {
+    if (SPLIT) {
         split = logical / (a.tiles_m * a.tiles_n);  // slowest: an XCD's work-groups share the weights of few splits
         logical -= split * (a.tiles_m * a.tiles_n);
     }
@@ -162,8 +163,8 @@ __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     const int r_lo = FLAT ? rflat(m0) : 0;
     const int patch_len = FLAT ? rflat(m_last) + (g.R - 1) * a.RW + (g.S - 1) + 1 - r_lo : a.patch_len;
     const int RS = g.R * g.S;
-    const int cs0 = FLAT ? split * a.slices_per_split : 0;  // slices [cs0, ncs) of this work-group (never empty)
-    const int ncs = FLAT && cs0 + a.slices_per_split < g.IC / BK ? cs0 + a.slices_per_split : g.IC / BK;
+    const int cs0 = SPLIT ? split * a.slices_per_split : 0;  // slices [cs0, ncs) of this work-group (never empty)
+    const int ncs = SPLIT && cs0 + a.slices_per_split < g.IC / BK ? cs0 + a.slices_per_split : g.IC / BK;
 
     const __amdgpu_buffer_rsrc_t rsrcA =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.A), 0, (int)a.a_bytes, 0x00020000);
@@ -453,7 +454,7 @@ __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     }
 
     // ---- split reduction: the accumulators as they lie, four consecutive channels of a pixel per store ----
-    if (FLAT && a.part) {
+    if (SPLIT && a.part) {
         float* const po = a.part + (size_t)split * g.M * g.Ncols;
 #pragma unroll
         for (int j = 0; j < FM; ++j) {
@@ -730,10 +731,10 @@ bool flat64_wins_small_batch(const GemmGeom& g) {
     const double t_flat = floor_s > flops / 900e12 ? floor_s : flops / 900e12;
     return t_flat < 0.85 * t_generic;
 }
-// The flat tilings a split reduction runs on: 64 or 224 pixels x 128 channels, 192 pixels x 64 channels.
+// The flat tilings a split reduction runs on: 64 pixels x 128 channels or 192 pixels x 64 channels.
 TileCfg split_cfg(const GemmGeom& g, int tile) {
-    TileCfg c = {1, 0, 0, tile == kTileSplit192 ? 3 : 2, 0, 0, 0, tile == kTileSplit224 ? 7 : 2};
-    const bool v3 = c.variant == 3;
+    const bool v3 = tile == kTileSplit192;
+    TileCfg c = {1, 0, 0, v3 ? 3 : 2, 0, 0, 0, 2};
     if ((g.Ncols % (v3 ? 64 : 128)) != 0 || max_flat_patch(g, tile_pixels(c)) > (v3 ? MAX_PATCH_FLAT64 : MAX_PATCH_FLAT) ||
         !lds_layout(g, &c))
         c.fn = 0;

@@ -613,7 +613,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
             p.tile = tile;
             nsplit = sp;
         }
-    } else if (g_force_fwd_cfg >= 12 && g_force_fwd_cfg <= 14 && g_force_nsplit >= 2 && g_force_nsplit <= g.IC / 32 &&
+    } else if ((g_force_fwd_cfg == 12 || g_force_fwd_cfg == 14) && g_force_nsplit >= 2 && g_force_nsplit <= g.IC / 32 &&
                tile2d_supported(g, g_force_fwd_cfg - 11)) {
         cfg = 7;
         p.tile = g_force_fwd_cfg - 11;

@@ -109,7 +109,7 @@ struct GemmPlan {
     size_t ws_bytes;
     int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own
 };
-constexpr int kTileSplit64 = 1, kTileSplit224 = 2, kTileSplit192 = 3;
+constexpr int kTileSplit64 = 1, kTileSplit192 = 3;
 
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred

@@ -97,7 +97,7 @@ CASES = [
     ("tile2d_split_auto_w13", (4, 13, 13, 384, 256, 3, 3, 1, 1), (-1, -1, -1)),
     ("tile2d_split_64x128_uneven", (2, 13, 13, 256, 128, 3, 3, 1, 1), (12, -1, 3)),
     ("tile2d_split_64x128_one_slice_each_unpool", (3, 14, 14, 128, 128, 3, 3, 1, 1), (12, -1, 4)),
-    ("tile2d_split_224x128", (2, 20, 20, 128, 256, 3, 3, 1, 1), (13, -1, 2)),
+    ("tile2d_split_64x128_two_column_tiles", (2, 20, 20, 128, 256, 3, 3, 1, 1), (12, -1, 2)),
     ("tile2d_split_192x64_5x5", (1, 27, 27, 64, 192, 5, 5, 1, 2), (14, -1, 2)),
     ("tile2d_split_192x64_under_one_tile", (1, 7, 9, 128, 64, 3, 3, 1, 1), (14, -1, 3)),
     ("split_mask_c36", (2, 9, 9, 36, 64, 3, 3, 1, 1), (1, -1, 3)),
