@@ -346,7 +346,8 @@ int launch_dx(const FcArgs& a, hipStream_t st) {
     if (a.B <= 16) hipLaunchKernelGGL((fc_dx_kernel<1, CPL, VEC8>), grid, block, 0, st, a);
     else if (a.B <= 32) hipLaunchKernelGGL((fc_dx_kernel<2, CPL, VEC8>), grid, block, 0, st, a);
     else if (a.B <= 64) hipLaunchKernelGGL((fc_dx_kernel<4, CPL, VEC8>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fc_dx_kernel<8, 2, VEC8>), grid, block, 0, st, a);
+    else if constexpr (CPL == 2) hipLaunchKernelGGL((fc_dx_kernel<8, 2, VEC8>), grid, block, 0, st, a);
+    else return set_error(WAP_EINVAL, "internal: more than 64 batch rows need two columns per lane");
     return check_launch("fc_dx");
 }
 }  // namespace

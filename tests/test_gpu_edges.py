@@ -141,6 +141,26 @@ def test_fc_stream_edges(orc, B, n_in, n_out):
     assert e <= gu.TOL_BF16_OUT, e
 
 
+# the data-gradient stream with the ReLU derivative of the layer below: a 1x1 convolution on a 1x1 map, rows of dx and of the
+# mask at every alignment, the last work-group moved back (columns that no work-group divides), two and four columns per lane
+@pytest.mark.parametrize("N,C,K", [(20, 67, 41), (3, 64, 8), (32, 4551, 40), (16, 6147, 33), (65, 6145, 24), (128, 101, 1000)])
+def test_fc_stream_masked_data_gradient(orc, N, C, K):
+    import paper_1811_01532_amd as wap
+    print(f"[case] masked data-gradient stream {(N, C, K)}", flush=True)
+    d = wap.conv_desc(N, 1, 1, C, K, 1, 1, 1, 0)
+    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_DATA) == "fc_dx_kernel"
+    gb, wb = si.normal_bf16(si.rng(457, N + K), (N, 1, 1, K)), si.he_weight_bf16(si.rng(458, C + K), (K, 1, 1, C))
+    xb = si.normal_bf16(si.rng(459, N + C), (N, 1, 1, C))
+    dx = torch.full((N * C + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wap.wap_conv2d_bwd_data_relu(d, gu.dev_bf16(gb), gu.dev_bf16(wb), gu.dev_bf16(xb), dx,
+                                 gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)))
+    torch.cuda.synchronize()
+    assert torch.isnan(dx[N * C:]).all()
+    ref = orc.conv2d_bwd_data(orc.bf16_bits_to_f64(gb), orc.bf16_bits_to_f64(wb), (N, 1, 1, C), (1, 1), (0, 0))
+    want = np.where(orc.bf16_bits_to_f64(xb) > 0, ref, 0.0)
+    assert gu.rel_err(gu.host_f64(dx[:N * C]).reshape(N, 1, 1, C), want) <= gu.TOL_BF16_OUT
+
+
 # rows of Wt that are no multiple of 8: an infinite weight among the elements that the row's last vector shares with its
 # neighbour, in the last vector's own elements and in front of both reaches exactly its own feature, as +-infinity
 @pytest.mark.parametrize("B,n_in,n_out", [(5, 67, 9), (16, 9, 7), (1, 8199, 20), (16, 16391, 50), (3, 1020, 17)])
@@ -206,7 +226,11 @@ def test_maxpool_edges(orc, N, H, W, C, win, st):
     (1, 4, 32, 3, 16, 3, 3, 1, 1), (2, 9, 33, 3, 8, 3, 3, 1, 1), (1, 11, 31, 3, 96, 3, 3, 1, 0), (1, 13, 29, 1, 24, 5, 5, 2, 2),
     (2, 35, 35, 3, 40, 11, 11, 4, 2), (1, 47, 47, 3, 96, 7, 7, 2, 3), (1, 12, 50, 2, 16, 3, 5, (1, 2), (1, 2)),
     (1, 13, 40, 4, 40, 4, 3, (2, 1), (0, 1)), (3, 31, 34, 3, 72, 3, 3, 3, 1), (1, 10, 60, 4, 16, 2, 19, 1, (1, 9)),
-    (1, 30, 41, 1, 128, 20, 1, 1, (3, 0)), (1, 5, 5, 3, 200, 1, 2, 1, 0), (40, 60, 70, 3, 16, 3, 3, 1, 1), (1, 3, 200, 3, 32, 1, 9, 1, (0, 4))])
+    (1, 30, 41, 1, 128, 20, 1, 1, (3, 0)), (1, 5, 5, 3, 200, 1, 2, 1, 0), (40, 60, 70, 3, 16, 3, 3, 1, 1), (1, 3, 200, 3, 32, 1, 9, 1, (0, 4)),
+    # 768 tiles: two and three channel blocks per work-group in the forward kernel (from 512), the third partly filled; two
+    # and three blocks in the weight gradient with three or four and five to eight blocks of filter taps
+    (16, 62, 66, 3, 64, 3, 3, 1, 1), (16, 62, 66, 3, 72, 3, 3, 1, 1), (2, 30, 33, 3, 96, 5, 5, 1, 2), (2, 30, 33, 3, 64, 5, 5, 1, 2),
+    (1, 30, 33, 3, 64, 7, 7, 1, 3)])
 def test_few_channel_edges(orc, N, H, W, C, K, R, S, stride, pad):
     import paper_1811_01532_amd as wap
     st = (stride, stride) if isinstance(stride, int) else stride
@@ -367,13 +391,15 @@ def test_wgrad_5x5_infinite_pixel(orc, H, W, yx):
     N, C, K = 2, 64, 32
     d = wap.conv_desc(N, H, W, C, K, 5, 5, 1, 2)
     wap.lib().wap_debug_force(-1, 3, -1)
-    assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch5_kernel")
-    x = torch.ones((N, H, W, C), dtype=torch.bfloat16, device="cuda")
-    x[1, yx[0], yx[1], 5] = float("inf")
-    dw = torch.zeros((K, 5, 5, C), dtype=torch.float32, device="cuda")
-    wap.wap_conv2d_bwd_weight(d, x, torch.ones((N, H, W, K), dtype=torch.bfloat16, device="cuda"), dw,
-                              gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
-    wap.lib().wap_debug_force(-1, -1, -1)
+    try:
+        assert wap.wap_conv2d_kernel_name(d, wap.WAP_PASS_BWD_WEIGHT).startswith("wgrad_patch5_kernel")
+        x = torch.ones((N, H, W, C), dtype=torch.bfloat16, device="cuda")
+        x[1, yx[0], yx[1], 5] = float("inf")
+        dw = torch.zeros((K, 5, 5, C), dtype=torch.float32, device="cuda")
+        wap.wap_conv2d_bwd_weight(d, x, torch.ones((N, H, W, K), dtype=torch.bfloat16, device="cuda"), dw,
+                                  gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
+    finally:
+        wap.lib().wap_debug_force(-1, -1, -1)
     torch.cuda.synchronize()
     hot = np.zeros((N, H, W, C))
     hot[1, yx[0], yx[1], 5] = 1.0
