@@ -835,6 +835,17 @@ int tile2d_split(const GemmGeom& g, bool generic, int* tile) {
     const int slices = g.IC / BK;
     if ((g.IC % BK) != 0 || slices < 2 || g.R * g.S < 2 || (g.Ncols % 64) != 0) return 1;
     *tile = (g.Ncols % 128) == 0 ? kTileSplit64 : kTileSplit192;
+    // Against the tap-by-tap kernel (whose plan splits too), 1100 layers of 0.04 to 20 GFLOP, that kernel's time over this one's
+    // with its packing: with straight-line taps 3x3 0.98 .. 1.30 and 5x5 on 192 x 64 tiles 0.96 .. 1.40; with the taps in a loop 2x2
+    // 0.71 .. 0.98 up to two slices and mostly 1.0 .. 1.19 beyond, 5x5 on 64 x 128 tiles 0.64 .. 0.9 where the grid is small or few rows
+    // pay for the packing, else 0.93 .. 1.52 (2704 x 128 x 128 17 us against 20, 5408 x 256 x 256 41 against 63) and 1.1 .. 1.3 with
+    // sixteen slices, 7x7 0.48 .. 1.07.  The lines below are 0.5 % off the better of the two in the mean, 10 % at worst (5x5 and up).
+    const int side = tile2d_st(0, *tile == kTileSplit192 ? 2 : 1, false, g.R, g.S), taps = g.R * g.S;
+    if (generic && side == 0) {
+        const bool wins = taps <= 9 ? slices * taps >= 16
+                                    : taps <= 25 && (slices >= 16 || (g.M >= 600 && 2.0 * g.M * g.Ncols * g.Kred >= 1e9));
+        if (!wins) return 1;
+    }
     const long tiles = *tile == kTileSplit64 ? (long)((g.M + 63) / 64) * (g.Ncols / 128) : (long)((g.M + 191) / 192) * (g.Ncols / 64);
     const long target = g.R * g.S > 9 ? 2 * kNumCU : kNumCU * 27 / 32;
     long s = target / tiles;
