@@ -274,6 +274,14 @@ def test_split_patch_kernel_by_filter_and_work(wap):
         assert fwd(*c).startswith("igemm_kernel"), c
 
 
+def test_profile_times_the_kernels_of_a_step(wap):
+    """A step packs its weights once, so 4 x 6 x 6 x 256 -> 256 runs on eight slices of the patch kernel there, and the
+    per-layer table sizes its scratch for that plan: packed weights and eight parts of y, beside x, y (twice), dx, w and dw."""
+    y, w = 4 * 6 * 6 * 256, 256 * 9 * 256
+    need = wap.wap_profile_scratch_bytes(0, wap.conv_desc(4, 6, 6, 256, 256, 3, 3, 1, 1), [4])
+    assert need >= (4 * 2 * y + 2 * w + 4 * w) + (2 * w + 8 * 4 * y), need
+
+
 def test_odd_channel_reduction_that_passes_int32_stays_element_by_element(wap):
     """Odd channel counts are rounded up to a multiple of 8 per filter tap; where that takes the reduction past int32 the
     kernel that counts the taps' own channels remains."""
