@@ -604,11 +604,12 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 6 || cfg == 7)) {
         int tile = 0;
         const bool pools = !b_tr && cfg == 7 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
-        // (A single call packs its weights in front, a launch more.  Called one by one, layers of little work wait for the host,
-        // 5.5 us for every launch of a Python caller: 3x3 layers of 128 .. 512 channels, forward and backward, us without / with the
-        // split: 0.2 GFLOP 42 / 50, 0.46 45 / 50, 0.6 49.5 / 49.4, 0.8 52 / 50, 1.6 59 / 53, 1.9 62 / 56; one AlexNet-style image
-        // forward 104 / 108, four 118 / 112.  As a graph the split is 3 to 20 % ahead from 0.04 GFLOP on.)
-        const bool worth = cfg == 7 || prepacked || 2.0 * g.M * g.Ncols * g.Kred >= 6e8;
+        // (A single call packs its weights in front, a launch more.  As a graph the split is 3 to 20 % ahead from 0.04 GFLOP on all
+        // the same; called one by one, a layer of little work waits for the host, 4 us for every launch of a Python caller.  3x3
+        // layers of 128 .. 512 channels, forward and both gradients, us without / with the split in both passes: 0.2 GFLOP 41 / 49,
+        // 0.46 45 / 50, 0.6 49.5 / 49.4, 0.8 52 / 50, 1.6 59 / 53.  A forward pass runs ahead of the GPU earlier: AlexNet-style layers of
+        // 0.2 .. 0.45 GFLOP, one image 115 / 113, two 116 / 113.)
+        const bool worth = cfg == 7 || prepacked || 2.0 * g.M * g.Ncols * g.Kred >= (b_tr ? 6e8 : 1.9e8);
         const int sp = pools || !worth ? 1 : tile2d_split(g, cfg < 6, &tile);
         if (sp > 1 && (b_tr || (size_t)sp * g.M * g.Ncols * sizeof(float) + wreg_wt_bytes(g) <= WAP_STATIC_SCRATCH_BYTES)) {
             cfg = 7;

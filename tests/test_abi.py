@@ -263,14 +263,16 @@ def test_bias_gradient_of_up_to_512_rows_is_one_chunk(wap):
 
 def test_split_patch_kernel_by_filter_and_work(wap):
     """Small layers whose reduction is divided over slices of the patch kernel: with straight-line taps (3x3, 5x5 on 64-channel
-    tiles) or a few in a loop, and from 0.6 GFLOP where the weights are packed for the one call."""
-    def fwd(N, H, C, K, R, pad):
-        return wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, C, K, R, R, 1, pad), wap.WAP_PASS_FWD)
+    tiles) or a few in a loop, and from 0.19 (forward) or 0.6 GFLOP (data gradient) where the weights are packed for the one call."""
+    def fwd(N, H, C, K, R, pad, what=wap.WAP_PASS_FWD):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, C, K, R, R, 1, pad), what)
     assert fwd(4, 13, 256, 256, 3, 1) == "conv_tile2d_kernel<1,0,2,1,false,true>"       # 0.8 GFLOP
     assert fwd(2, 27, 64, 192, 5, 2) == "conv_tile2d_5x5_kernel<1,0,3,2>"
     assert fwd(4, 13, 512, 256, 2, 0) == "conv_tile2d_kernel<1,0,2,1,false,false>"
     assert fwd(32, 9, 128, 128, 5, 2) == "conv_tile2d_kernel<1,0,2,1,false,false>"      # 2592 rows, 2 GFLOP
-    for c in ((1, 13, 256, 256, 3, 1), (2, 14, 256, 512, 5, 2), (4, 12, 128, 128, 3, 1), (4, 13, 128, 128, 5, 2), (4, 13, 128, 64, 7, 3), (4, 13, 128, 128, 7, 3)):
+    assert fwd(1, 13, 256, 256, 3, 1) == "conv_tile2d_kernel<1,0,2,1,false,true>"       # 0.2 GFLOP: in the forward pass only
+    assert fwd(1, 13, 256, 256, 3, 1, wap.WAP_PASS_BWD_DATA).startswith("igemm_kernel")
+    for c in ((2, 14, 256, 512, 5, 2), (4, 12, 128, 128, 3, 1), (4, 13, 128, 128, 5, 2), (4, 13, 128, 64, 7, 3), (4, 13, 128, 128, 7, 3)):
         assert fwd(*c).startswith("igemm_kernel"), c
 
 
