@@ -924,8 +924,8 @@ int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, cons
 }
 
 // (A gather-based general-filter weight gradient, lanes indexing the columns k, was tried and dropped: every lane
-// touches a different cache line.  Large filters at horizontal stride 4 use the rows-in-LDS kernel above; all other
-// first-layer shapes go to conv_thin.hip.)
+// touches a different cache line.  Large filters at horizontal stride 4 use the rows-in-LDS kernel above where
+// there are enough of them; all other first-layer shapes go to conv_thin.hip.)
 static bool wgrad_c3_special(const WgradGeom& g) {
     return g.C == 3 && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && (g.K == 32 || g.K == 64) && (g.Q % 8) == 0 &&
            (long)g.N * g.P * g.Q >= 4096;

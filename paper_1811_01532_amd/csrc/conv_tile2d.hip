@@ -824,8 +824,8 @@ bool tile2d_preferred(const GemmGeom& g) {
 
 // How to divide the reduction of a layer too small to fill the chip: number of splits (1: don't) and the flat tiling.
 // `generic`: the alternative is the tap-by-tap kernel, which splits its reduction as well but gathers every activation
-// once per tap (7 to 12 us slower at every size measured, e.g. 512 -> 512 channels on 14 x 14 at minibatch 8 32.4 -> 22.2,
-// 256 -> 256 on 13 x 13 at 8 19.0 -> 13.4, 384 -> 256 at 1 15.6 -> 10.2 us).  Otherwise it is an unsplit tile of this
+// once per tap (3x3, weights packed before: 512 -> 512 channels on 14 x 14 at minibatch 8 32.4 -> 22.2, 256 -> 256 on 13 x 13
+// at 8 19.0 -> 13.4, 384 -> 256 at 1 15.6 -> 10.2 us; other filters below).  Otherwise it is an unsplit tile of this
 // kernel: a slice of a 3x3 filter takes a work-group about 2.2 us, the partial sums and their reduction about 9, so the
 // split has to save 10 (384 -> 192 on 13 x 13 at 32 24.5 -> 22.7; 64 outputs of a 5x5 filter at 16 / 32 / 64 47 / 49 /
 // 53 -> 27 / 36 / 44 us; 128 -> 64 on 56 x 56, four slices, would lose: 12.0 -> 15.7).
