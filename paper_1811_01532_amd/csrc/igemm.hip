@@ -7,11 +7,17 @@
 // forward / backward halves of t_c in Eq. 1).
 //
 // Design for CDNA4:
+// Bound by what a work-group does one thing after the other (12 x 57 x 57 x 72 -> 200, 3x3 stride 2, 158 work-groups of 11
+// reduction tiles: addresses 0.6 us, first loads 1.5, 0.64 a tile, epilogue 1.4; with the address divisions and the loads of one
+// tile ahead of four wavefronts' products, 0.93 a tile and 21.5 us for the call; this 12.8).
 //   * block tile BM x BN x 64, 64-wide wavefronts each owning a (BM/WAVES_M) x (BN/WAVES_N)
 //     sub-tile built from v_mfma_f32_32x32x16_bf16; the weight fragment is the MFMA "A" operand so
 //     that each lane ends up with 4 consecutive output channels of one pixel (8-byte bf16 stores);
-//   * operands staged through LDS, two stages; the next tile's global loads are issued before the
-//     current tile's MFMAs and written to the other stage afterwards (one barrier per tile);
+//   * operands staged through LDS, two stages, up to four more tiles in flight in registers; the step of a tile is one basic
+//     block (no branch around a load or in the walk over the taps), so that address arithmetic, loads and LDS writes issue
+//     between the MFMAs (one barrier per tile);
+//   * where the grid leaves a CU one work-group, eight wavefronts share its tile, two for every sub-tile: each takes half of
+//     the reduction steps and the sums meet in the LDS;
 //   * LDS rows padded (144 B for reduction-contiguous tiles, +64 B for channel-contiguous tiles) so
 //     ds_read_b128 / ds_read_b64_tr_b16 fragment reads are bank-conflict free;
 //   * channel-contiguous weight tiles (data gradient) are transposed on the way out of LDS with
@@ -29,6 +35,12 @@ namespace {
 constexpr int BK = 64;
 constexpr int A_PITCH = (BK + 8) * 2;  // bytes per LDS row of a reduction-contiguous tile
 
+// Wavefronts that share a sub-tile and divide every reduction tile between them; their sums meet in the LDS at the end.  Two
+// where a CU has one work-group (wavefronts of the same SIMD then cover each other's LDS and MFMA latency: 0.85 -> 0.64 us a
+// tile); a grid of more than one work-group per CU has that from its neighbours, two of four wavefronts each (32 x 28 x 28,
+// 512 <- 128 channels, 1x1: 17.1 us, 21.5 with eight wavefronts each in half the registers).
+constexpr int waves_k(int bm, int bn, int variant) { return bm * bn <= 128 * 128 && !(variant & 8) ? 2 : 1; }
+
 // One phase of a strided data gradient: the output pixels whose coordinates leave the same remainders (oh0, ow0) modulo
 // the strides.  Only the filter taps r0, r0 + stride, ... meet a dy element there, so a phase is an ordinary stride-1
 // product of its own, with R x S of the taps.
@@ -36,18 +48,22 @@ constexpr int kMaxPhases = 16;
 struct Phase {
     int R, S, r0, s0, OH, OW, pad_h, pad_w, oh0, ow0, M;
     int tile0;  // first row tile
+    FastDiv dOW, dOH;
 };
 
 struct KArgs {
     const bf16_t* A;
     const bf16_t* Bw;
     const float* bias;
+    const bf16_t* mask;  // out = mask > 0 ? out : 0 (unsplit reductions)
     void* out;
     GemmGeom g;
     int tiles_m, tiles_n, nsplit, ktiles, ktiles_per_split;
     int relu, partial;
+    unsigned a_bytes, b_bytes;  // of the operands
     int ICp;      // MODE 2: channels rounded up to 8, the reduction's length per tap (no group of 8 crosses a tap)
     FastDiv dICp;
+    FastDiv dOW, dOH;  // row -> pixel (a phase has its own)
 };
 // (apart, so that the other launches do not carry the phases in their arguments: with them a short product, 302 x 256 ->
 // 25088, took 35 instead of 22 us)
@@ -62,11 +78,11 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
-__device__ __forceinline__ u32x4 ld16(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
-
-// Out-of-image taps and tile tails load from this zero block instead of being masked after the load:
-// the loaded registers then have no consumer until the LDS store that follows the MFMAs, so the
-// global-load latency overlaps the current tile's compute.
+// Out-of-image taps and tile tails load from beyond the buffer, which yields zeros and costs no access: the loaded
+// registers then have no consumer until the LDS store, so the latency overlaps the compute of the tiles before.  (As loads of
+// a block of zeros they all met in one L2 channel.)
+constexpr unsigned kNowhere = 0xfffffff0u;  // operands of the modes 0 .. 2 end before (classify_mode)
+// the same element by element
 __device__ __align__(16) unsigned int g_zero_block[4] = {0u, 0u, 0u, 0u};
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -85,18 +101,18 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
 // MODE 2: odd   -- any channel counts of at least 8: unaligned 16-byte loads, every tap's channels rounded up to a multiple
 //                  of 8 in the reduction (element by element, as MODE 3 does it, 288 x 4096 -> 3373 took 253 us for dx)
 // MODE 3: scalar-- anything (2-byte loads)
-// VARIANT: the mode, plus 4 for PHASE: data gradient of a strided convolution, the row tiles grouped by phase (a.ph): a tap
+// VARIANT: the mode, plus 8 where the grid has more than one work-group per CU (waves_k); plus 4 for PHASE: data gradient of a
+// strided convolution, the row tiles grouped by phase (a.ph): a tap
 // between dy elements costs nothing, where the unphased product multiplies stride_h * stride_w times as many zeros (12 x
 // 57 x 57, 200 -> 72 channels, 3x3 stride 2: block forward and backward 141 -> 103 us)
-// (One kernel, not two around a shared device function: behind that call the compiler no longer hoisted the argument loads
-// and address arithmetic of modes 0 and 1, 200 instructions more, 29 x 50 x 50 x 192 -> 248 at stride 2 37.1 against 41.5 us,
-// 1024 -> 4096 at 17 rows 9.6 against 11.1.  For the same reason their expressions name a.g only where a phase needs it.)
+// (One kernel, not two around a shared device function, behind whose call the compiler did not hoist the argument loads.)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool B_TR, int VARIANT>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
-    const std::conditional_t<(VARIANT >= 4), KPhaseArgs, KArgs> a) {
-    constexpr bool PHASE = VARIANT >= 4;
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * waves_k(BM, BN, VARIANT), (VARIANT & 8) ? 2 : 1) void igemm_kernel(
+    const std::conditional_t<(VARIANT & 4) != 0, KPhaseArgs, KArgs> a) {
+    constexpr bool PHASE = (VARIANT & 4) != 0;
     constexpr int MODE = VARIANT & 3;
-    constexpr int NT = 64 * WAVES_M * WAVES_N;
+    constexpr int WAVES_K = waves_k(BM, BN, VARIANT);
+    constexpr int NT = 64 * WAVES_M * WAVES_N * WAVES_K;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int FM = WM / 32, FN = WN / 32;
     constexpr int A_RPP = NT / 8, A_PASSES = BM / A_RPP;
@@ -109,11 +125,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
     constexpr int B_BYTES = B_ROWS * B_PITCH;
     constexpr int STAGE = A_BYTES + B_BYTES;
     static_assert(A_PASSES >= 1 && B_PASSES >= 1, "tile too small for the block");
+    // Register sets for tiles in flight.  Four for the square tile (100 x 9216 -> 4096 22.6 us, 24.4 with two); the long ones, whose
+    // loads take most of the memory's rate, start earlier with two (64 x 4096 -> 4096 18.4 us, 20.8 with four).
+    constexpr int SETS = WAVES_K == 2 && MODE < 3 && BM == BN ? 4 : BM * BN <= 128 * 128 ? 2 : 1;
 
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+    const int wm = wave % WAVES_M, wn = wave / WAVES_M % WAVES_N, wk = wave / (WAVES_M * WAVES_N);
 
     const int total = a.tiles_m * a.tiles_n * a.nsplit;
     // (phases differ in work: neighbouring work-groups go to different XCDs there)
@@ -125,6 +144,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
     GemmGeom gp;
     int r0 = 0, s0 = 0, oh0 = 0, ow0 = 0;
     int ktiles = a.ktiles, kps = a.ktiles_per_split;
+    FastDiv dOW = a.dOW, dOH = a.dOH;
     if constexpr (PHASE) {
         int c = 0;
         while (c + 1 < a.nphase && tm >= a.ph[c + 1].tile0) ++c;
@@ -135,6 +155,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
         gp.pad_h = p.pad_h; gp.pad_w = p.pad_w;
         gp.mul_h = gp.mul_w = gp.div_h = gp.div_w = 1;
         gp.Kred = p.R * p.S * (MODE == 2 ? a.ICp : gp.IC);
+        dOW = p.dOW; dOH = p.dOH;
         r0 = p.r0; s0 = p.s0; oh0 = p.oh0; ow0 = p.ow0;
         ktiles = (gp.Kred + BK - 1) / BK;
         kps = (ktiles + a.nsplit - 1) / a.nsplit;
@@ -146,19 +167,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
     if (kt_end > ktiles) kt_end = ktiles;
 
     // ---- per-thread row state of the gathered operand ----
+    const bool unit = MODE == 0 || PHASE || !B_TR || (g.div_h == 1 && g.div_w == 1);  // taps of neighbouring steps are neighbours in memory
     const int a_vec = tid & 7, a_row0 = tid >> 3;
-    int hb[A_PASSES], wb[A_PASSES], abase[A_PASSES];
+    int hb[A_PASSES], wb[A_PASSES], abase[A_PASSES];  // unit: abase is the element of tap (0, 0), which may lie outside
 #pragma unroll
     for (int i = 0; i < A_PASSES; ++i) {
         int m = m0 + a_row0 + i * A_RPP;
         if (m < g.M) {
-            int ow = m % g.OW;
-            int t = m / g.OW;
-            int oh = t % g.OH;
-            int n = t / g.OH;
+            const int t = (int)fdiv((uint32_t)m, dOW), ow = m - t * g.OW;
+            const int n = (int)fdiv((uint32_t)t, dOH), oh = t - n * g.OH;
             hb[i] = oh * g.mul_h - g.pad_h;
             wb[i] = ow * g.mul_w - g.pad_w;
             abase[i] = n * g.IH * g.IW * g.IC;
+            if (unit) abase[i] += (hb[i] * g.IW + wb[i]) * g.IC;
         } else {
             hb[i] = -(1 << 28);
             wb[i] = -(1 << 28);
@@ -166,47 +187,144 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
         }
     }
     const int b_vec = tid % B_VPR, b_row0 = tid / B_VPR;
-
-    u32x4 ra[A_PASSES], rb[B_PASSES];
-    const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block);
-
-    auto tap_ok = [&](int th, int tw, int& ih, int& iw) -> bool {
-        if (MODE == 0 || PHASE) {
-            ih = th;
-            iw = tw;
-            return (unsigned)th < (unsigned)g.IH && (unsigned)tw < (unsigned)g.IW;
-        } else {
-            if (th < 0 || tw < 0) return false;
-            ih = th / g.div_h;
-            iw = tw / g.div_w;
-            return (ih * g.div_h == th) && (iw * g.div_w == tw) && ih < g.IH && iw < g.IW;
-        }
+    const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block);  // MODE 3
+    const __amdgpu_buffer_rsrc_t rsrcA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.A), 0, (int)a.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.Bw), 0, (int)a.b_bytes, 0x00020000);
+    auto ld8 = [](__amdgpu_buffer_rsrc_t r, bool ok, int off, unsigned past) {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, (ok ? (unsigned)off * 2u : kNowhere) | past, 0, 0);
     };
 
-    auto load_global = [&](int kt) {
-        // Fast mode walks the reduction channel-slice-major (all filter taps of one 64-channel slice
-        // before the next slice): the 9 (or 25) shifted re-reads of the same input pixels then happen
-        // in consecutive tiles and hit in L2 instead of going back to HBM.
+    // ---- walk over the reduction tiles: from an offset of the work-group's own, wrapping.  Work-groups running at the same
+    // time then read different channel slices and filter taps, which spreads their requests over the L2 channels instead of
+    // hammering the same few.  The fast mode walks channel-slice-major (all filter taps of one 64-channel slice before the
+    // next slice): the 9 (or 25) shifted re-reads of the same input pixels then happen in consecutive tiles and hit in L2
+    // instead of going back to HBM. ----
+    const int nkt = kt_end - kt_begin;
+    int cur = kt_begin + (nkt > 0 ? (int)(((unsigned)blockIdx.x / kNumXCD * 5u) % (unsigned)nkt) : 0);  // next tile to load
+    int loaded = 0;                                                                                     // tiles loaded so far
+    // MODE 0: tap and channel slice of that tile, and of the walk's first one
+    int wr = 0, ws = 0, wc = 0, br = 0, bs = 0, bc = 0;
+    if (MODE == 0 && nkt > 0) {
         const int RS = g.R * g.S;
-        const int kk0 = (MODE == 0) ? ((kt % RS) * g.IC + (kt / RS) * BK) : kt * BK;
-        // ---------- gathered operand ----------
-        if (MODE <= 2) {
-            const int tapk = MODE == 2 ? a.ICp : g.IC;
-            int kk = (MODE == 0) ? kk0 : kk0 + a_vec * 8;
-            int tap = MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;
-            int c = kk - tap * tapk + ((MODE == 0) ? a_vec * 8 : 0);
-            int r = tap / g.S, s = tap - r * g.S;
-            bool kok = MODE == 0 ? true : MODE == 2 ? tap < g.R * g.S : kk < g.Kred;
-            const int over = MODE == 2 && c + 8 > g.IC ? c + 8 - g.IC : 0;
+        wc = cur / RS; ws = cur - wc * RS; wr = ws / g.S; ws -= wr * g.S; wc *= BK;
+        bc = kt_begin / RS; bs = kt_begin - bc * RS; br = bs / g.S; bs -= br * g.S; bc *= BK;
+    }
+    // MODE 1, 2: lane l holds the decoded group of eight reduction elements l % 8 of the l / 8-th of the next eight tiles;
+    // the loads fetch theirs from there.  (Divisions for every tile and pass took more time than the products: 12 x 57 x 57 x 72
+    // -> 200, 3x3 stride 2, 27.8 us with them.)
+    int t_rs = 0, t_c = 0, t_a = 0, t_b = 0;  // tap r | s << 8 | elements moved back << 16, -1: past the end; channel; offsets
+    auto decode = [&]() {
+        int kt = cur + (lane >> 3);
+        while (kt >= kt_end) kt -= nkt;  // (lanes past the walk's end decode tiles again)
+        const int kk = kt * BK + (lane & 7) * 8;
+        const int tapk = MODE == 2 ? a.ICp : g.IC;
+        const int tap = MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / tapk;
+        int c = kk - tap * tapk;
+        const int r = tap / g.S, s = tap - r * g.S;
+        if (B_TR) {  // (channel c of the group is its first reduction row here, whatever the row's length)
+            const int rf = PHASE ? r0 + r * a.g.div_h : r, sf = PHASE ? s0 + s * a.g.div_w : s;
+            t_b = ((c * a.g.R + (a.g.R - 1 - rf)) * a.g.S + (a.g.S - 1 - sf)) * g.Ncols;
+        }
+        t_c = c;
+        const int over = MODE == 2 && c + 8 > g.IC ? c + 8 - g.IC : 0;
+        c -= over;
+        t_a = (r * g.IW + s) * g.IC + c;
+        if (!B_TR) t_b = tap * g.IC + c;
+        t_rs = tap < g.R * g.S ? r | (s << 8) | (over << 16) : -1;
+    };
+    auto beyond = [](int rs) { return (unsigned)(rs >> 31) & kNowhere; };
+    auto from_lane = [](int v, int src) { return __builtin_amdgcn_ds_bpermute(src * 4, v); };
+
+    auto load_global = [&](u32x4 (&ra)[A_PASSES], u32x4 (&rb)[B_PASSES]) {
+        // past the walk's end: nothing (the loop's loads are unconditional, see there; a condition would become a branch)
+        const unsigned past = loaded < nkt ? 0u : kNowhere;
+        if constexpr (MODE == 0) {
+            const int adelta = (wr * g.IW + ws) * g.IC + wc + a_vec * 8;
 #pragma unroll
             for (int i = 0; i < A_PASSES; ++i) {
-                int ih, iw;
-                bool ok = tap_ok(hb[i] + r, wb[i] + s, ih, iw) && kok;
-                int off = abase[i] + (ih * g.IW + iw) * g.IC + c - over;
-                if (MODE == 2) ra[i] = shift_down8(load8_unaligned(ok ? a.A + off : zero_src), over);
-                else ra[i] = ld16(ok ? a.A + off : zero_src);
+                const bool ok = (unsigned)(hb[i] + wr) < (unsigned)g.IH && (unsigned)(wb[i] + ws) < (unsigned)g.IW;
+                ra[i] = ld8(rsrcA, ok, abase[i] + adelta, past);
             }
+            if (!B_TR) {
+                // Bw[n][kk]: LDS row = output channel, 8 vectors of 8 reduction elements per row
+                const int kk = (wr * g.S + ws) * g.IC + wc + b_vec * 8;
+#pragma unroll
+                for (int i = 0; i < B_PASSES; ++i) {
+                    const int n = n0 + b_row0 + i * B_RPP;
+                    rb[i] = ld8(rsrcB, n < g.Ncols, n * g.Kred + kk, past);
+                }
+            } else {
+                // Bw[k][R-1-r][S-1-s][n]: LDS row = reduction index k of one tap, BN/8 vectors of 8 channels
+                const int rf = PHASE ? r0 + wr * a.g.div_h : wr, sf = PHASE ? s0 + ws * a.g.div_w : ws;
+                const int n = n0 + b_vec * 8, tapoff = (a.g.R - 1 - rf) * a.g.S + (a.g.S - 1 - sf);
+#pragma unroll
+                for (int i = 0; i < B_PASSES; ++i) {
+                    const int k = wc + b_row0 + i * B_RPP;
+                    rb[i] = ld8(rsrcB, n < g.Ncols, (k * a.g.R * a.g.S + tapoff) * g.Ncols + n, past);
+                }
+            }
+            const bool row = ws + 1 == g.S, slice = row && wr + 1 == g.R, wrap = cur + 1 == kt_end;
+            cur = wrap ? kt_begin : cur + 1;
+            wc = wrap ? bc : slice ? wc + BK : wc;
+            wr = wrap ? br : slice ? 0 : row ? wr + 1 : wr;
+            ws = wrap ? bs : row ? 0 : ws + 1;
+            ++loaded;
+        } else if constexpr (MODE <= 2) {
+            if ((loaded & 7) == 0) decode();
+            const int src0 = (loaded & 7) * 8;
+            // ---------- gathered operand ----------
+            {
+                const int rs = from_lane(t_rs, src0 + a_vec), ad = from_lane(t_a, src0 + a_vec);
+                const int r = rs & 255, s = (rs >> 8) & 255, over = (rs >> 16) & 7;
+                const unsigned none = beyond(rs) | past;
+                const int c = unit ? 0 : from_lane(t_c, src0 + a_vec) - over;
+#pragma unroll
+                for (int i = 0; i < A_PASSES; ++i) {
+                    const int th = hb[i] + r, tw = wb[i] + s;
+                    bool ok;
+                    int off;
+                    if (unit) {
+                        ok = (unsigned)th < (unsigned)g.IH && (unsigned)tw < (unsigned)g.IW;
+                        off = abase[i] + ad;
+                    } else {
+                        const int ih = th / g.div_h, iw = tw / g.div_w;
+                        ok = th >= 0 && tw >= 0 && ih * g.div_h == th && iw * g.div_w == tw && ih < g.IH && iw < g.IW;
+                        off = abase[i] + (ih * g.IW + iw) * g.IC + c;
+                    }
+                    ra[i] = ld8(rsrcA, ok, off, none);
+                    if (MODE == 2) ra[i] = shift_down8(ra[i], over);
+                }
+            }
+            // ---------- weight operand ----------
+            if (!B_TR) {
+                const int rs = from_lane(t_rs, src0 + b_vec), kk = from_lane(t_b, src0 + b_vec), over = (rs >> 16) & 7;
+                const unsigned none = beyond(rs) | past;
+#pragma unroll
+                for (int i = 0; i < B_PASSES; ++i) {
+                    const int n = n0 + b_row0 + i * B_RPP;
+                    rb[i] = ld8(rsrcB, n < g.Ncols, n * g.Kred + kk, none);
+                    if (MODE == 2) rb[i] = shift_down8(rb[i], over);
+                }
+            } else {
+                // LDS row = reduction index (r,s,k): row j of the group's eight is its channel c + j
+                const int n = n0 + b_vec * 8;
+                const int nover = MODE == 2 && n + 8 > g.Ncols ? n + 8 - g.Ncols : 0;
+#pragma unroll
+                for (int i = 0; i < B_PASSES; ++i) {
+                    const int row = b_row0 + i * B_RPP, src = src0 + (row >> 3), j = row & 7;
+                    const int rs = from_lane(t_rs, src);
+                    const int off = from_lane(t_b, src) + j * a.g.R * a.g.S * g.Ncols + n - nover;
+                    const unsigned none = beyond(rs) | past;
+                    if (MODE == 2) rb[i] = shift_down8(ld8(rsrcB, j + ((rs >> 16) & 7) < 8 && nover < 8, off, none), nover < 8 ? nover : 0);
+                    else rb[i] = ld8(rsrcB, n < g.Ncols, off, none);
+                }
+            }
+            ++loaded;
+            if (++cur == kt_end) cur = kt_begin;
         } else {
+            const int kk0 = past ? ktiles * BK : cur * BK;
+            if (++cur == kt_end) cur = kt_begin;
+            ++loaded;
             int rr[8], ss[8], cc[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -222,34 +340,26 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
                 unsigned short h16[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    int ih, iw;
-                    bool ok = tap_ok(hb[i] + rr[e], wb[i] + ss[e], ih, iw);
-                    int off = abase[i] + (ih * g.IW + iw) * g.IC + cc[e];
+                    const int th = hb[i] + rr[e], tw = wb[i] + ss[e];
+                    bool ok;
+                    int off;
+                    if (unit) {
+                        ok = (unsigned)th < (unsigned)g.IH && (unsigned)tw < (unsigned)g.IW;
+                        off = abase[i] + (rr[e] * g.IW + ss[e]) * g.IC + cc[e];
+                    } else {
+                        const int ih = th / g.div_h, iw = tw / g.div_w;
+                        ok = th >= 0 && tw >= 0 && ih * g.div_h == th && iw * g.div_w == tw && ih < g.IH && iw < g.IW;
+                        off = abase[i] + (ih * g.IW + iw) * g.IC + cc[e];
+                    }
                     h16[e] = *(ok ? a.A + off : zero_src);
                 }
                 ra[i] = pack8(h16);
             }
-        }
-        // ---------- weight operand ----------
-        if (!B_TR) {
-            // Bw[n][kk]: LDS row = output channel, 8 vectors of 8 reduction elements per row
-            int kk = kk0 + b_vec * 8;
-            int over = 0;
-            if (MODE == 2) {  // to the position in the unpadded row
-                const int tap = (int)fdiv((uint32_t)kk, a.dICp), c = kk - tap * a.ICp;
-                over = c + 8 > g.IC ? c + 8 - g.IC : 0;
-                kk = tap < g.R * g.S ? tap * g.IC + c - over : g.Kred;
-            }
+            if (!B_TR) {
+                int kk = kk0 + b_vec * 8;
 #pragma unroll
-            for (int i = 0; i < B_PASSES; ++i) {
-                int n = n0 + b_row0 + i * B_RPP;
-                if (MODE == 2) {
-                    const bool ok = n < g.Ncols && kk < g.Kred;
-                    rb[i] = shift_down8(load8_unaligned(ok ? a.Bw + (n * g.Kred + kk) : zero_src), over);
-                } else if (MODE <= 1) {
-                    bool ok = n < g.Ncols && kk < g.Kred;
-                    rb[i] = ld16(ok ? a.Bw + (n * g.Kred + kk) : zero_src);
-                } else {
+                for (int i = 0; i < B_PASSES; ++i) {
+                    int n = n0 + b_row0 + i * B_RPP;
                     unsigned short h16[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -258,32 +368,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
                     }
                     rb[i] = pack8(h16);
                 }
-            }
-        } else {
-            // Bw[k][R-1-r][S-1-s][n]: LDS row = reduction index (r,s,k), BN/8 vectors of 8 channels
-            int n = n0 + b_vec * 8;
-            const int over = MODE == 2 && n + 8 > g.Ncols ? n + 8 - g.Ncols : 0;
+            } else {
+                int n = n0 + b_vec * 8;
 #pragma unroll
-            for (int i = 0; i < B_PASSES; ++i) {
-                int kk = kk0 + b_row0 + i * B_RPP;
-                int tap = MODE == 0 ? kk0 / g.IC : MODE == 2 ? (int)fdiv((uint32_t)kk, a.dICp) : kk / g.IC;  // one tap per tile in the fast mode
-                int k = kk - tap * (MODE == 2 ? a.ICp : g.IC);
-                int r = tap / g.S, s = tap - r * g.S;
-                int rowoff;
-                if (PHASE) {
-                    r = r0 + r * a.g.div_h;
-                    s = s0 + s * a.g.div_w;
-                    rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
-                } else {
-                    rowoff = ((k * g.R + (g.R - 1 - r)) * g.S + (g.S - 1 - s)) * g.Ncols;
-                }
-                if (MODE == 2) {
-                    const bool ok = tap < g.R * g.S && k < g.IC && over < 8;
-                    rb[i] = shift_down8(load8_unaligned(ok ? a.Bw + (rowoff + n - over) : zero_src), over < 8 ? over : 0);
-                } else if (MODE <= 1) {
-                    bool ok = kk < g.Kred && n < g.Ncols;
-                    rb[i] = ld16(ok ? a.Bw + (rowoff + n) : zero_src);
-                } else {
+                for (int i = 0; i < B_PASSES; ++i) {
+                    int kk = kk0 + b_row0 + i * B_RPP;
+                    int tap = kk / g.IC;
+                    int k = kk - tap * g.IC;
+                    int r = tap / g.S, s = tap - r * g.S;
+                    if (PHASE) {
+                        r = r0 + r * a.g.div_h;
+                        s = s0 + s * a.g.div_w;
+                    }
+                    const int rowoff = ((k * a.g.R + (a.g.R - 1 - r)) * a.g.S + (a.g.S - 1 - s)) * g.Ncols;
                     unsigned short h16[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -296,7 +393,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
         }
     };
 
-    auto store_lds = [&](int stage) {
+    auto store_lds = [&](int stage, const u32x4 (&ra)[A_PASSES], const u32x4 (&rb)[B_PASSES]) {
         unsigned char* sA = smem + stage * STAGE;
         unsigned char* sB = sA + A_BYTES;
 #pragma unroll
@@ -319,7 +416,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
         const unsigned char* sA = smem + stage * STAGE;
         const unsigned char* sB = sA + A_BYTES;
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
+        for (int k2 = 0; k2 < BK / 16 / WAVES_K; ++k2) {
+            const int ks = wk * (BK / 16 / WAVES_K) + k2;
             bf16x8 fa[FM], fw[FN];
 #pragma unroll
             for (int j = 0; j < FM; ++j) {
@@ -351,58 +449,136 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
         }
     };
 
-    if (kt_begin < kt_end) {
-        // Each work-group starts its walk over the reduction tiles at a different offset (and wraps):
-        // work-groups running at the same time then read different channel slices and filter taps,
-        // which spreads their requests over the L2 channels instead of hammering the same few.
-        const int nkt = kt_end - kt_begin;
-        int cur = kt_begin + (int)(((unsigned)blockIdx.x / kNumXCD * 5u) % (unsigned)nkt);
-        load_global(cur);
-        store_lds(0);
+    // Tile it is in the LDS, tile it + 1 in one register set, and (where two sets fit) tile it + 2 in flight in the other: few
+    // work-groups share a CU where this kernel is used, so one tile's loads do not cover the latency of the next.  The loads are
+    // unconditional, or the compiler could not tell how many are in flight and would wait for all of them.
+    if (nkt > 0) {
+        u32x4 ra[SETS][A_PASSES], rb[SETS][B_PASSES];
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) load_global(ra[i], rb[i]);
+        store_lds(0, ra[0], rb[0]);
+        load_global(ra[0], rb[0]);
         __syncthreads();
-        for (int it = 0; it < nkt; ++it) {
-            const int stage = it & 1;
-            const bool more = (it + 1 < nkt);
-            int nxt = cur + 1;
-            if (nxt == kt_end) nxt = kt_begin;
-            if (more) load_global(nxt);
+        auto step = [&](int stage, u32x4 (&xa)[A_PASSES], u32x4 (&xb)[B_PASSES]) {
+            store_lds(stage ^ 1, xa, xb);
+            load_global(xa, xb);
             compute(stage);
-            if (more) store_lds(stage ^ 1);
             __syncthreads();
-            cur = nxt;
+        };
+        constexpr int U = SETS < 2 ? 2 : SETS;
+        int it = 0;
+        for (; it + U <= nkt; it += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
         }
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u)
+            if (it + u < nkt) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
     }
 
-    // ---- epilogue: lane holds 4 consecutive channels of one pixel per register quad ----
-    const bool vec4 = (g.Ncols & 3) == 0;
+    // ---- the halves of the reduction meet: each wavefront keeps every WAVES_K-th pixel block of its sub-tile ----
+    if constexpr (WAVES_K == 2) {
+        static_assert(FM % 2 == 0 && WAVES_M * WAVES_N * 2 * (FM / 2) * FN * 4096 <= 2 * STAGE, "does not fit the operand tiles");
+        unsigned char* const mine = smem + wave * ((FM / 2) * FN * 4096) + lane * 16;
+        unsigned char* const theirs = smem + (wave ^ (WAVES_M * WAVES_N)) * ((FM / 2) * FN * 4096) + lane * 16;
 #pragma unroll
-    for (int j = 0; j < FM; ++j) {
-        int m = m0 + wm * WM + j * 32 + (lane & 31);
-        if (m >= g.M) continue;
-        if (PHASE) {  // back to the pixel of the whole map
-            const int t = m / g.OW, ow = m - t * g.OW;
-            const int n = t / g.OH, oh = t - n * g.OH;
-            m = (n * a.g.OH + oh * a.g.div_h + oh0) * a.g.OW + ow * a.g.div_w + ow0;
-        }
+        for (int i = 0; i < FN; ++i)
 #pragma unroll
-        for (int i = 0; i < FN; ++i) {
+            for (int j = 0; j < FM / 2; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = n0 + wn * WN + i * 32 + q * 8 + (lane >> 5) * 4;
-                if (n >= g.Ncols) continue;
-                float v[4];
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4*>(mine + ((i * (FM / 2) + j) * 4 + q) * 1024) =
+                        wk == 0 ? f32x4{acc[i][j + FM / 2][q * 4], acc[i][j + FM / 2][q * 4 + 1], acc[i][j + FM / 2][q * 4 + 2], acc[i][j + FM / 2][q * 4 + 3]}
+                                : f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+        __syncthreads();
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][q * 4 + e];
-                if (a.partial) {
-                    float* o = reinterpret_cast<float*>(a.out) + ((size_t)split * a.g.M + m) * g.Ncols + n;
-                    if (vec4) {
-                        *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+        for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM / 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(theirs + ((i * (FM / 2) + j) * 4 + q) * 1024);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)  // (the first half's sum first in both)
+                        acc[i][j][q * 4 + e] = wk == 0 ? acc[i][j][q * 4 + e] + v[e] : v[e] + acc[i][j + FM / 2][q * 4 + e];
+                }
+    }
+
+    // ---- epilogue.  A lane holds 4 consecutive channels of one pixel per register quad; a wavefront turns its blocks of 32
+    // pixels around in LDS of its own, 16-byte groups exchanged within a row against bank conflicts, so that whole runs of
+    // channels leave in 16-byte stores (8-byte stores to 32 rows each: 32 x 28 x 28, 512 <- 128 channels, 1x1, 21.0 us against 17.1;
+    // partial sums in 32-byte runs: 4 x 14 x 14 x 512 -> 512, 1x1, 13.5 against 11.3). ----
+    constexpr int JN = FM / WAVES_K, WNC = FN * 32;         // blocks of this wavefront, channels of a block
+    constexpr int EP = 32 * WNC * 4;                        // bytes, as fp32
+    static_assert((NT / 64) * EP <= 2 * STAGE || BM * BN > 128 * 128, "epilogue staging does not fit the operand tiles");
+    if constexpr (WAVES_K == 2) __syncthreads();            // (the exchanged halves have been read)
+    unsigned char* const ep = smem + wave * EP;
+    const int l32 = lane & 31, half = lane >> 5;
+    const int nw = n0 + wn * WNC;                           // first channel of the wavefront
+#pragma unroll
+    for (int j = 0; j < JN; ++j) {
+        const int mw = m0 + wm * WM + (wk * JN + j) * 32;   // first pixel of the block
+        auto row_of = [&](int p) {                          // output row of the block's pixel p
+            int m = mw + p;
+            if (PHASE) {  // back to the pixel of the whole map
+                const int t = (int)fdiv((uint32_t)m, dOW), ow = m - t * g.OW;
+                const int n = (int)fdiv((uint32_t)t, dOH), oh = t - n * g.OH;
+                m = (n * a.g.OH + oh * a.g.div_h + oh0) * a.g.OW + ow * a.g.div_w + ow0;
+            }
+            return m;
+        };
+        if (a.partial) {
+            constexpr int CH = WNC / 4;  // 16-byte groups per pixel
+#pragma unroll
+            for (int i = 0; i < FN; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = i * 8 + q * 2 + half;
+                    *reinterpret_cast<f32x4*>(ep + l32 * (WNC * 4) + (c ^ (l32 & 15)) * 16) =
+                        f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+                }
+            __builtin_amdgcn_wave_barrier();  // LDS operations of one wavefront complete in order
+#pragma unroll
+            for (int it = 0; it < CH / 2; ++it) {
+                const int v = it * 64 + lane, p = v / CH, c = v % CH, n = nw + c * 4;
+                const f32x4 x = *reinterpret_cast<const f32x4*>(ep + p * (WNC * 4) + (c ^ (p & 15)) * 16);
+                if (mw + p >= g.M || n >= g.Ncols) continue;
+                float* o = reinterpret_cast<float*>(a.out) + ((size_t)split * a.g.M + row_of(p)) * g.Ncols + n;
+                if (n + 4 <= g.Ncols) {
+                    __builtin_memcpy(o, &x, 16);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (n + e < g.Ncols) o[e] = x[e];
+                }
+            }
+        } else {
+            constexpr int CH = WNC / 8;
+            u32x4 mk[CH / 2];  // mask of the rows to be stored, fetched ahead
+            if (a.mask) {
+#pragma unroll
+                for (int it = 0; it < CH / 2; ++it) {
+                    const int v = it * 64 + lane, p = v / CH, n = nw + v % CH * 8;
+                    mk[it] = u32x4{0u, 0u, 0u, 0u};
+                    if (mw + p >= g.M || n >= g.Ncols) continue;
+                    const bf16_t* src = a.mask + (size_t)row_of(p) * g.Ncols + n;
+                    if (n + 8 <= g.Ncols) {
+                        mk[it] = load8_unaligned(src);
                     } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < g.Ncols) o[e] = v[e];
+                        for (int e = 0; e < 7; ++e)
+                            if (n + e < g.Ncols) mk[it][e >> 1] |= (unsigned)src[e] << (16 * (e & 1));
                     }
-                } else {
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < FN; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc[i][j][q * 4 + e];
+                    const int n = nw + i * 32 + q * 8 + half * 4;
                     if (a.bias) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
@@ -412,23 +588,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_kernel(
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
                     }
-                    bf16_t* o = reinterpret_cast<bf16_t*>(a.out) + (size_t)m * g.Ncols + n;
-                    unsigned short hb16[4];
+                    const int c = i * 4 + q;
+                    *reinterpret_cast<u32x2*>(ep + l32 * (WNC * 2) + (c ^ (l32 & 7)) * 16 + half * 8) =
+                        u32x2{(unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16)};
+                }
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) hb16[e] = f2bf(v[e]);
-                    if (vec4) {
-                        // (one vector: as a pair of words the second was merged with the element stores below, three
-                        // stores for one, the strided data gradients 20 to 40 % slower)
-                        *reinterpret_cast<u32x2*>(o) = u32x2{(unsigned)hb16[0] | ((unsigned)hb16[1] << 16),
-                                                             (unsigned)hb16[2] | ((unsigned)hb16[3] << 16)};
-                    } else {
+            for (int it = 0; it < CH / 2; ++it) {
+                const int v = it * 64 + lane, p = v / CH, c = v % CH, n = nw + c * 8;
+                u32x4 x = *reinterpret_cast<const u32x4*>(ep + p * (WNC * 2) + (c ^ (p & 7)) * 16);
+                if (a.mask) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < g.Ncols) o[e] = hb16[e];
-                    }
+                    for (int k = 0; k < 4; ++k)
+                        x[k] &= (__uint_as_float(mk[it][k] << 16) > 0.f ? 0xffffu : 0u) |
+                                (__uint_as_float(mk[it][k] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u);
+                }
+                if (mw + p >= g.M || n >= g.Ncols) continue;
+                bf16_t* o = reinterpret_cast<bf16_t*>(a.out) + (size_t)row_of(p) * g.Ncols + n;
+                if (n + 8 <= g.Ncols) {
+                    __builtin_memcpy(o, &x, 16);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 7; ++e)
+                        if (n + e < g.Ncols) o[e] = (bf16_t)(x[e >> 1] >> (16 * (e & 1)));
                 }
             }
         }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -453,6 +639,8 @@ size_t smem_bytes(const Cfg& c, bool b_tr) {
     return 2 * (a + b);
 }
 
+bool dense_grid(long groups) { return groups > kNumCU; }
+
 template <typename F, typename A>
 int launch_any(F kfn, std::atomic<bool>& attr_done, const A& ka, int threads, size_t smem, hipStream_t st) {
     if (!attr_done) {
@@ -467,13 +655,19 @@ int launch_any(F kfn, std::atomic<bool>& attr_done, const A& ka, int threads, si
 }
 template <int BM, int BN, int WMv, int WNv, bool B_TR, int MODE>
 int launch_one(const KArgs& ka, size_t smem, hipStream_t st) {
-    static std::atomic<bool> attr_done{false};  // one attribute call per instantiation
-    return launch_any(igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
+    static std::atomic<bool> attr_done{false}, attr_done2{false};  // one attribute call per instantiation
+    constexpr int dense = BM * BN <= 128 * 128 && MODE < 3 ? 8 + MODE : MODE;
+    if (dense != MODE && dense_grid((long)ka.tiles_m * ka.tiles_n * ka.nsplit))
+        return launch_any(igemm_kernel<BM, BN, WMv, WNv, B_TR, dense>, attr_done2, ka, 64 * WMv * WNv * waves_k(BM, BN, dense), smem, st);
+    return launch_any(igemm_kernel<BM, BN, WMv, WNv, B_TR, MODE>, attr_done, ka, 64 * WMv * WNv * waves_k(BM, BN, MODE), smem, st);
 }
 template <int BM, int BN, int WMv, int WNv, int MODE>
 int launch_phase(const KPhaseArgs& ka, size_t smem, hipStream_t st) {
-    static std::atomic<bool> attr_done{false};
-    return launch_any(igemm_kernel<BM, BN, WMv, WNv, true, 4 + MODE>, attr_done, ka, 64 * WMv * WNv, smem, st);
+    static std::atomic<bool> attr_done{false}, attr_done2{false};
+    constexpr int dense = MODE < 3 ? 12 + MODE : 4 + MODE;
+    if (MODE < 3 && dense_grid((long)ka.tiles_m * ka.tiles_n * ka.nsplit))
+        return launch_any(igemm_kernel<BM, BN, WMv, WNv, true, dense>, attr_done2, ka, 64 * WMv * WNv * waves_k(BM, BN, dense), smem, st);
+    return launch_any(igemm_kernel<BM, BN, WMv, WNv, true, 4 + MODE>, attr_done, ka, 64 * WMv * WNv * waves_k(BM, BN, MODE), smem, st);
 }
 
 // (A 1x1 filter has one tap to skip and pays for writing every pixel's row apart from its neighbours': 64 <- 128 channels on
@@ -484,6 +678,8 @@ bool phased(const GemmGeom& g, bool b_tr) {
 }
 
 int classify_mode(const GemmGeom& g, bool b_tr) {
+    const size_t most = 2147483647u - 63;  // elements of an operand whose last 16 bytes lie below kNowhere
+    if ((size_t)(g.M / (g.OH * g.OW)) * g.IH * g.IW * g.IC > most || (size_t)g.Kred * g.Ncols > most) return 3;
     bool vec_a = (g.IC % 8) == 0;
     bool vec_b = b_tr ? (g.Ncols % 8) == 0 : (g.Kred % 8) == 0;
     if (!(vec_a && vec_b)) {
@@ -513,6 +709,8 @@ int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
             p.pad_h = (g.pad_h - a - p.r0) / g.div_h;  // exact
             p.pad_w = (g.pad_w - b - p.s0) / g.div_w;
             p.M = images * p.OH * p.OW;
+            p.dOW = make_fastdiv((uint32_t)p.OW);
+            p.dOH = make_fastdiv((uint32_t)p.OH);
             ph[n++] = p;
         }
     std::stable_sort(ph, ph + n, [](const Phase& x, const Phase& y) { return x.R * x.S > y.R * y.S; });
@@ -666,12 +864,17 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     ka.tiles_n = (g.Ncols + c.BN - 1) / c.BN;
     const bool odd = plan.cfg == 1 && classify_mode(g, b_tr) == 2;
     ka.ICp = (g.IC + 7) / 8 * 8;
+    ka.a_bytes = (unsigned)((size_t)(g.M / (g.OH * g.OW)) * g.IH * g.IW * g.IC * 2);
+    ka.b_bytes = (unsigned)((size_t)g.Kred * g.Ncols * 2);
     ka.dICp = make_fastdiv((uint32_t)ka.ICp);
+    ka.dOW = make_fastdiv((uint32_t)g.OW);
+    ka.dOH = make_fastdiv((uint32_t)g.OH);
     ka.ktiles = ((odd ? g.R * g.S * ka.ICp : g.Kred) + BK - 1) / BK;
     ka.nsplit = plan.nsplit;
     ka.ktiles_per_split = (ka.ktiles + plan.nsplit - 1) / plan.nsplit;
     ka.partial = plan.nsplit > 1;
     ka.bias = ka.partial ? nullptr : bias;
+    ka.mask = ka.partial ? nullptr : relu_mask;
     ka.relu = ka.partial ? 0 : (relu ? 1 : 0);
     ka.out = ka.partial ? ws : (void*)out;
     if (plan.cfg == 6 || plan.cfg == 7) {
@@ -780,7 +983,7 @@ int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
 }
 bool fwd_like_fuses_mask(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return (g.Ncols % 4) == 0;  // by the kernel that adds up the splits
-    return ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11;
+    return plan.cfg < 5 || ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11;
 }
 // Label of the kernel instantiation a plan launches (matches the demangled kernel name).
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool) {
@@ -792,21 +995,23 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 10) return "fc_fwd_kernel";
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
-    if (phased(g, b_tr)) {
-        static const char* phase_names[4] = {"igemm_kernel<128,128,2,2,true,4>", "igemm_kernel<128,128,2,2,true,5>",
-                                             "igemm_kernel<128,128,2,2,true,6>", "igemm_kernel<128,128,2,2,true,7>"};
-        return plan.cfg == 3 ? "igemm_kernel<256,64,4,1,true,4>" : phase_names[classify_mode(g, b_tr)];
-    }
-    static const char* names[5][2][4] = {
-        {{"igemm_kernel<256,256,2,4,false,0>"}, {"igemm_kernel<256,256,2,4,true,0>"}},
-        {{"igemm_kernel<128,128,2,2,false,0>", "igemm_kernel<128,128,2,2,false,1>",
-          "igemm_kernel<128,128,2,2,false,2>", "igemm_kernel<128,128,2,2,false,3>"},
-         {"igemm_kernel<128,128,2,2,true,0>", "igemm_kernel<128,128,2,2,true,1>",
-          "igemm_kernel<128,128,2,2,true,2>", "igemm_kernel<128,128,2,2,true,3>"}},
-        {{"igemm_kernel<64,256,1,4,false,0>"}, {"igemm_kernel<64,256,1,4,true,0>"}},
-        {{"igemm_kernel<256,64,4,1,false,0>"}, {"igemm_kernel<256,64,4,1,true,0>"}},
-        {{"igemm_kernel<256,256,2,2,false,0>"}, {"igemm_kernel<256,256,2,2,true,0>"}},
+    const int mode = classify_mode(g, b_tr);
+    const Cfg& c = kCfgs[plan.cfg];
+    Phase ph[kMaxPhases];
+    int nphase;
+    const long tm = phased(g, b_tr) ? make_phases(g, c.BM, ph, &nphase) : (g.M + c.BM - 1) / c.BM;
+    const bool dense = mode < 3 && plan.cfg >= 1 && plan.cfg <= 3 && dense_grid(tm * ((g.Ncols + c.BN - 1) / c.BN) * plan.nsplit);
+    const int variant = mode + (phased(g, b_tr) ? 4 : 0) + (dense ? 8 : 0);
+#define WAP_IG(T, V) "igemm_kernel<" T "," V ">"
+#define WAP_IG16(T) {WAP_IG(T, "0"), WAP_IG(T, "1"), WAP_IG(T, "2"), WAP_IG(T, "3"), WAP_IG(T, "4"), WAP_IG(T, "5"), WAP_IG(T, "6"), WAP_IG(T, "7"), \
+                     WAP_IG(T, "8"), WAP_IG(T, "9"), WAP_IG(T, "10"), WAP_IG(T, "11"), WAP_IG(T, "12"), WAP_IG(T, "13"), WAP_IG(T, "14"), WAP_IG(T, "15")}
+    static const char* names[5][2][16] = {
+        {WAP_IG16("256,256,2,4,false"), WAP_IG16("256,256,2,4,true")}, {WAP_IG16("128,128,2,2,false"), WAP_IG16("128,128,2,2,true")},
+        {WAP_IG16("64,256,1,4,false"), WAP_IG16("64,256,1,4,true")},   {WAP_IG16("256,64,4,1,false"), WAP_IG16("256,64,4,1,true")},
+        {WAP_IG16("256,256,2,2,false"), WAP_IG16("256,256,2,2,true")},
     };
-    return names[plan.cfg][b_tr ? 1 : 0][classify_mode(g, b_tr)];
+#undef WAP_IG16
+#undef WAP_IG
+    return names[plan.cfg][b_tr ? 1 : 0][variant];
 }
 }  // namespace wap
