@@ -178,6 +178,26 @@ const char* wgrad_patch_kernel_name(const WgradGeom& g, bool unpool);
 int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* out, hipStream_t st,
                        const uint8_t* unpool_am = nullptr);
 
+// Several such layers of a step as one launch and one more for their sums (wgrad_patch.hip).
+constexpr int kMaxWgradGroup = 6;
+struct WgradGroup {
+    int n = 0, per = 0;  // layers; tiles per work-group
+    WgradGeom g[kMaxWgradGroup];
+};
+struct WgradGroupPtrs {
+    const bf16_t *x, *dy;
+    const uint8_t* unpool_am;  // of all layers of a group or of none
+    float* dw;                 // the gradient is stored here, or (w32 != NULL) applied to the parameters
+    float* w32;
+    bf16_t* wb;
+};
+int wgrad_group_variant(const WgradGeom& g);  // layers with the same number may share a group; -1: none may
+long wgrad_group_units(const WgradGeom& g);   // tiles of all its blocks
+int wgrad_group_per(const long* units, int n);
+size_t wgrad_group_ws_bytes(const WgradGroup& wg);
+const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool);
+int launch_wgrad_group(const WgradGroup& wg, const WgradGroupPtrs* ptrs, float lr, void* ws, hipStream_t st, hipEvent_t ev_mid = nullptr);
+
 // 3-input-channel 3x3 stride-1 first layer (conv_c3.hip)
 bool conv_c3_fwd_supported(const GemmGeom& g);
 const char* conv_c3_fwd_kernel_name(const GemmGeom& g);

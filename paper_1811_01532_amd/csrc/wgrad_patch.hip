@@ -35,6 +35,7 @@ namespace wap {
 
 namespace {
 
+constexpr int block_ko(int fd, int rf) { return rf == 3 ? 64 * fd : 32; }  // output channels per work-group
 constexpr int wavefronts(int rf) { return rf == 3 ? 12 : 10; }
 constexpr int XPITCH = 192;   // LDS bytes per patch pixel: 64 channels + 64 bytes, so that the 4 rows x 64 bytes a
                               // half-wavefront touches in one transposing read fall into 4 disjoint bank groups
@@ -101,11 +102,13 @@ __device__ __forceinline__ u32x4 unpool_select8(u32x4 v, u32x2 am, unsigned code
 // FD: 32-channel dy blocks per wavefront; the work-group covers 64 * FD output channels.  UP: dy arrives pooled.
 // NK: reduction steps per tile (tile pixels / 16).  RF: filter side; 5 with FD = 1 only, a work-group then covers 32
 // output channels.
+// Computes output channels ko0 .. and input channels c0 .. over the tiles t0 .. t1 - 1; element (k, tap, c) of the block goes to
+// outp[k * ldk + tap * ldt + c].
 template <int FD, bool UP, int MODE, int NK, int RF>
-__device__ __forceinline__ void wgrad_patch_body(const WPArgs& a) {
+__device__ __forceinline__ void wgrad_patch_body(const WPArgs& a, int ko0, int c0, int t0, int t1, float* outp, int ldk, int ldt) {
     static_assert(RF == 3 || (RF == 5 && FD == 1 && !UP), "5x5: one dy block, full-size dy");
     constexpr int NW = wavefronts(RF);
-    constexpr int KO = RF == 3 ? 64 * FD : 32;             // output channels per work-group
+    constexpr int KO = block_ko(FD, RF);                   // output channels per work-group
     constexpr int DPITCH = RF == 3 ? KO * 2 + 64 : 192;    // same bank argument as XPITCH
     constexpr int DVP = KO / 8;             // 16-byte vectors per dy pixel
     constexpr int PPW = 64 / DVP;           // dy pixels (UP: pooling windows) one wavefront load covers
@@ -120,14 +123,6 @@ __device__ __forceinline__ void wgrad_patch_body(const WPArgs& a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: everything derived from it stays scalar
     const int r = RF == 3 ? wave >> 2 : wave >> 1, cb = RF == 3 ? (wave >> 1) & 1 : wave & 1, kh = RF == 3 ? wave & 1 : 0;
-
-    const int total = a.ncombo * a.nsplit;
-    const int logical = xcd_remap(blockIdx.x, total);
-    const int combo = logical % a.ncombo, split = logical / a.ncombo;
-    const int ko0 = (combo % a.kgroups) * KO, c0 = (combo / a.kgroups) * 64;
-    const int t0 = split * a.tiles_per_split;
-    int t1 = t0 + a.tiles_per_split;
-    if (t1 > a.tiles_total) t1 = a.tiles_total;
 
     const __amdgpu_buffer_rsrc_t rsrcX =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x), 0, (int)a.x_bytes, 0x00020000);
@@ -373,28 +368,128 @@ __device__ __forceinline__ void wgrad_patch_body(const WPArgs& a) {
     }
 
     // ---- epilogue: a lane holds 4 consecutive input channels of one output channel per register quad ----
-    float* outp = a.out + (size_t)split * g.K * a.Kred;
 #pragma unroll
     for (int kb = 0; kb < FD; ++kb) {
-        const int ko = ko0 + kh * (FD * 32) + kb * 32 + (lane & 31);
+        const int ko = kh * (FD * 32) + kb * 32 + (lane & 31);
 #pragma unroll
         for (int s = 0; s < RF; ++s)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int col = (r * RF + s) * g.C + c0 + cb * 32 + q * 8 + (lane >> 5) * 4;
-                *reinterpret_cast<float4*>(outp + (size_t)ko * a.Kred + col) =
+                const int col = (r * RF + s) * ldt + cb * 32 + q * 8 + (lane >> 5) * 4;
+                *reinterpret_cast<float4*>(outp + (size_t)ko * ldk + col) =
                     make_float4(acc[s][kb][q * 4 + 0], acc[s][kb][q * 4 + 1], acc[s][kb][q * 4 + 2], acc[s][kb][q * 4 + 3]);
             }
     }
 }
 
+template <int FD, bool UP, int MODE, int NK, int RF>
+__device__ __forceinline__ void wgrad_patch_split(const WPArgs& a) {
+    const int logical = xcd_remap(blockIdx.x, a.ncombo * a.nsplit);
+    const int combo = logical % a.ncombo, split = logical / a.ncombo;
+    const int ko0 = (combo % a.kgroups) * block_ko(FD, RF), c0 = (combo / a.kgroups) * 64;
+    const int t0 = split * a.tiles_per_split;
+    int t1 = t0 + a.tiles_per_split;
+    if (t1 > a.tiles_total) t1 = a.tiles_total;
+    wgrad_patch_body<FD, UP, MODE, NK, RF>(a, ko0, c0, t0, t1, a.out + (size_t)split * a.g.K * a.Kred + (size_t)ko0 * a.Kred + c0,
+                                           a.Kred, a.g.C);
+}
 template <int FD, bool UP, int MODE, int NK>
 __global__ __launch_bounds__(64 * wavefronts(3), 3) void wgrad_patch_kernel(const WPArgs a) {
-    wgrad_patch_body<FD, UP, MODE, NK, 3>(a);
+    wgrad_patch_split<FD, UP, MODE, NK, 3>(a);
 }
 template <int MODE, int NK>
 __global__ __launch_bounds__(64 * wavefronts(5), 3) void wgrad_patch5_kernel(const WPArgs a) {
-    wgrad_patch_body<1, false, MODE, NK, 5>(a);
+    wgrad_patch_split<1, false, MODE, NK, 5>(a);
+}
+
+// ---- several layers of a step in one launch.  Alone, a layer of little work pays for its share of the chip: one work-group per
+// CU means a few tiles each, then 38 MB of partial sums written and read back and a launch for them (VGG-16 at 8 images, conv5_1
+// .. 3: 3 x (19.4 + 13.3) us; so 44.3 + 24.6, the sums at 5.4 TB/s; the AlexNet-style conv3 .. 5 71 -> 32).  Here the blocks of all layers of a group are laid end to end, block after block the tiles of
+// its reduction, and cut into equal runs of `per` tiles, one run per work-group (a run never spans two layers, so a layer's sums
+// depend on `per` and its shape only).  A run that reaches over the end of a block goes on with the next one; every (run,
+// block) pair leaves a partial tile in a slot of its own, number run + block of the layer, and a second launch adds up the few
+// slots of each block, for all layers, in run order. ----
+constexpr int kSlotFloats = 64 * 9 * 64;  // 64 output channels x nine taps x 64 input channels
+struct WGroupArgs {
+    int njobs, per;
+    int first[kMaxWgradGroup + 1];  // first work-group of each layer
+    int slot0[kMaxWgradGroup];
+    float* part;
+    WPArgs job[kMaxWgradGroup];
+};
+template <bool UP, int MODE, int NK>
+__global__ __launch_bounds__(64 * wavefronts(3), 3) void wgrad_patch_group_kernel(const WGroupArgs ga) {
+    int j = 0;
+    while (j + 1 < ga.njobs && (int)blockIdx.x >= ga.first[j + 1]) ++j;
+    const WPArgs& a = ga.job[j];
+    const int run = xcd_remap((int)blockIdx.x - ga.first[j], ga.first[j + 1] - ga.first[j]);
+    int u = run * ga.per;
+    int end = u + ga.per;
+    if (end > a.ncombo * a.tiles_total) end = a.ncombo * a.tiles_total;
+    while (u < end) {  // at most `per` trips: a block has at least one tile
+        const int combo = u / a.tiles_total, t0 = u - combo * a.tiles_total;
+        int t1 = t0 + end - u;
+        if (t1 > a.tiles_total) t1 = a.tiles_total;
+        wgrad_patch_body<1, UP, MODE, NK, 3>(a, (combo % a.kgroups) * 64, (combo / a.kgroups) * 64, t0, t1,
+                                             ga.part + (size_t)(ga.slot0[j] + run + combo) * kSlotFloats, 9 * 64, 64);
+        u += t1 - t0;
+        __syncthreads();  // the tile buffers may be overwritten
+    }
+}
+
+// The sums of a group: a thread owns 16 bytes of a layer's dw, `spread` (1 or 8) threads share them, each every spread-th slot
+// (a block cut into hundreds of runs is a small layer's: 16 KB of dw, walked slot by slot 0.2 us each), whose sums are added in
+// order through LDS.
+struct WGroupSum {
+    int K, C, Kred, kgroups, tiles, runs, slot0, spread;
+    FastDiv dRow, dC;   // by Kred / 4, C
+    float* out;
+    SgdFuse sgd;
+};
+struct WGroupSumArgs {
+    int njobs, per;
+    int first[kMaxWgradGroup + 1];  // first work-group of each layer
+    const float* part;
+    WGroupSum job[kMaxWgradGroup];
+};
+__global__ __launch_bounds__(256) void wgrad_group_sum_kernel(const WGroupSumArgs ga) {
+    __shared__ float4 sm[256];
+    int j = 0;
+    while (j + 1 < ga.njobs && (int)blockIdx.x >= ga.first[j + 1]) ++j;
+    const WGroupSum& a = ga.job[j];
+    const int cols = 256 / a.spread, col = threadIdx.x % cols, grp = threadIdx.x / cols;
+    const int v = ((int)blockIdx.x - ga.first[j]) * cols + col;
+    const bool ok = v < a.K * (a.Kred / 4);
+    const int ko = (int)fdiv((uint32_t)(ok ? v : 0), a.dRow);
+    const int e = ((ok ? v : 0) - ko * (a.Kred / 4)) * 4;
+    const int tap = (int)fdiv((uint32_t)e, a.dC), c = e - tap * a.C;
+    const int combo = ko / 64 + c / 64 * a.kgroups;
+    const int r0 = combo * a.tiles / ga.per, r1 = ((combo + 1) * a.tiles - 1) / ga.per;  // runs that hold a part of the block
+    const float* src = ga.part + (size_t)(a.slot0 + combo) * kSlotFloats + (ko % 64) * (9 * 64) + tap * 64 + c % 64;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r = r0 + grp; r <= r1; r += 4 * a.spread) {
+        float4 t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int rk = r + k * a.spread;
+            t[k] = *reinterpret_cast<const float4*>(src + (size_t)(rk <= r1 ? rk : r1) * kSlotFloats);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (r + k * a.spread <= r1) { s.x += t[k].x; s.y += t[k].y; s.z += t[k].z; s.w += t[k].w; }
+    }
+    if (a.spread > 1) {  // (uniform)
+        sm[threadIdx.x] = s;
+        __syncthreads();
+        if (grp == 0)
+            for (int k = 1; k < a.spread; ++k) {
+                const float4 t = sm[k * cols + col];
+                s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+            }
+    }
+    if (grp != 0 || !ok) return;
+    if (a.sgd.w32) sgd_apply4(a.sgd.w32 + (size_t)v * 4, a.sgd.wb + (size_t)v * 4, a.sgd.lr, s.x, s.y, s.z, s.w);
+    else *reinterpret_cast<float4*>(a.out + (size_t)v * 4) = s;
 }
 
 struct TileShape {
@@ -408,7 +503,7 @@ int fd_for(const WgradGeom& g);
 size_t buf_bytes_for(int fd, const TileShape& ts, int rf) {
     return (size_t)(ts.TH + rf - 1) * (ts.VW + rf - 1) * XPITCH + (size_t)ts.TH * ts.VW * (rf == 3 ? fd * 128 + 64 : 192);
 }
-int ko_for(const WgradGeom& g, int fd) { return g.R == 3 ? 64 * fd : 32; }  // output channels per work-group
+int ko_for(const WgradGeom& g, int fd) { return block_ko(fd, g.R); }
 
 // Most real pixels per tile (the tile height need not divide the map: the last tile row of an image is then partly
 // masked) among the tiles the kernel's three step maps cover and whose two LDS buffers fit; then the least padding.
@@ -556,9 +651,9 @@ const void* kernel_fn(int fd, bool up, int v, int rf) {
 }
 }  // namespace
 
-int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* out, hipStream_t st,
-                       const uint8_t* unpool_am) {
-    WPArgs wa;
+static int patch_args(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* out, const uint8_t* unpool_am, WPArgs* args,
+                      int* variant) {
+    WPArgs& wa = *args;
     TileShape ts;
     if (!wgrad_patch_supported(g) || !choose_tile(g, &ts))
         return set_error(WAP_EINVAL, "internal: patch weight-gradient kernel not applicable");
@@ -609,8 +704,19 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
     wa.dDSEG = make_fastdiv((uint32_t)wa.DSEG);
     wa.dTimg = make_fastdiv((uint32_t)wa.tiles_img);
     wa.dTx = make_fastdiv((uint32_t)wa.tiles_x);
+    *variant = variant_of(ts);
+    if (2 * (size_t)wa.buf_bytes > LDS_BYTES) return set_error(WAP_EINVAL, "internal: patch weight-gradient tile does not fit LDS");
+    return WAP_OK;
+}
+
+int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* out, hipStream_t st,
+                       const uint8_t* unpool_am) {
+    WPArgs wa;
+    int variant;
+    int rc = patch_args(g, nsplit, x, dy, out, unpool_am, &wa, &variant);
+    if (rc != WAP_OK) return rc;
+    const int fd = fd_for(g), rf = g.R;
     const size_t smem = 2 * (size_t)wa.buf_bytes;
-    if (smem > LDS_BYTES) return set_error(WAP_EINVAL, "internal: patch weight-gradient tile does not fit LDS");
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
         for (int k = 0; k < 5 * kNumVariants; ++k) {  // 3x3: one / two blocks, full-size / pooled dy; 5x5
@@ -622,9 +728,116 @@ int launch_wgrad_patch(const WgradGeom& g, int nsplit, const bf16_t* x, const bf
         attr_done = true;
     }
     void* kargs[] = {(void*)&wa};
-    hipError_t le = hipLaunchKernel(kernel_fn(fd, unpool_am != nullptr, variant_of(ts), rf), dim3(wa.ncombo * nsplit), dim3(64 * nw), kargs, smem, st);
+    hipError_t le = hipLaunchKernel(kernel_fn(fd, unpool_am != nullptr, variant, rf), dim3(wa.ncombo * nsplit), dim3(64 * wavefronts(rf)), kargs, smem, st);
     if (le != hipSuccess) return set_error(WAP_EHIP, "wgrad_patch launch: %s", hipGetErrorString(le));
     return check_launch("wgrad_patch");
+}
+
+// ---- groups of layers (a step's) ----
+// Layers of little work (one 32-channel dy block per wavefront) that run on the same instantiation may share a launch.
+int wgrad_group_variant(const WgradGeom& g) {
+    TileShape ts;
+    if (g.R != 3 || plan_wgrad(g).cfg != 3 || fd_for(g) != 1 || !choose_tile(g, &ts)) return -1;
+    return variant_of(ts);
+}
+long wgrad_group_units(const WgradGeom& g) {
+    TileShape ts;
+    if (!choose_tile(g, &ts)) return 0;
+    return (long)g.N * ((g.P + ts.TH - 1) / ts.TH) * (g.Q / ts.TWr) * (g.K / 64) * (g.C / 64);
+}
+// Least tiles per work-group with which the layers (their units) need no more than one work-group per CU.
+int wgrad_group_per(const long* units, int n) {
+    long total = 0;
+    for (int i = 0; i < n; ++i) total += units[i];
+    for (long per = (total + kNumCU - 1) / kNumCU;; ++per) {
+        long groups = 0;
+        for (int i = 0; i < n; ++i) groups += (units[i] + per - 1) / per;
+        if (groups <= kNumCU || per >= total) return (int)per;
+    }
+}
+size_t wgrad_group_ws_bytes(const WgradGroup& wg) {
+    size_t slots = 0;
+    for (int i = 0; i < wg.n; ++i) slots += (wgrad_group_units(wg.g[i]) + wg.per - 1) / wg.per + (size_t)(wg.g[i].K / 64) * (wg.g[i].C / 64);
+    return slots * kSlotFloats * sizeof(float);
+}
+const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool) {
+    static const char* names[2][kNumVariants] = {
+        {"wgrad_patch_group_kernel<false,0,7>", "wgrad_patch_group_kernel<false,0,8>", "wgrad_patch_group_kernel<false,1,8>",
+         "wgrad_patch_group_kernel<false,2,5>", "wgrad_patch_group_kernel<false,2,6>", "wgrad_patch_group_kernel<false,2,7>"},
+        {"wgrad_patch_group_kernel<true,0,7>", "wgrad_patch_group_kernel<true,0,8>", "wgrad_patch_group_kernel<true,1,8>",
+         "wgrad_patch_group_kernel<true,2,5>", "wgrad_patch_group_kernel<true,2,6>", "wgrad_patch_group_kernel<true,2,7>"}};
+    const int v = wgrad_group_variant(wg.g[0]);
+    return v < 0 ? "wgrad_patch_group_kernel" : names[unpool ? 1 : 0][v];
+}
+namespace {
+template <bool UP>
+const void* group_fn(int v) {
+    switch (v) {
+        case 0: return (const void*)wgrad_patch_group_kernel<UP, 0, 7>;
+        case 1: return (const void*)wgrad_patch_group_kernel<UP, 0, 8>;
+        case 2: return (const void*)wgrad_patch_group_kernel<UP, 1, 8>;
+        case 3: return (const void*)wgrad_patch_group_kernel<UP, 2, 5>;
+        case 4: return (const void*)wgrad_patch_group_kernel<UP, 2, 6>;
+        default: return (const void*)wgrad_patch_group_kernel<UP, 2, 7>;
+    }
+}
+}  // namespace
+
+int launch_wgrad_group(const WgradGroup& wg, const WgradGroupPtrs* ptrs, float lr, void* ws, hipStream_t st, hipEvent_t ev_mid) {
+    WGroupArgs ga;
+    WGroupSumArgs gs;
+    if (wg.n < 1 || wg.n > kMaxWgradGroup || wg.per < 1) return set_error(WAP_EINVAL, "internal: bad group of weight gradients");
+    ga.njobs = gs.njobs = wg.n;
+    ga.per = gs.per = wg.per;
+    ga.part = reinterpret_cast<float*>(ws);
+    gs.part = ga.part;
+    ga.first[0] = gs.first[0] = 0;
+    int variant = -1, slots = 0, smem = 0;
+    for (int i = 0; i < wg.n; ++i) {
+        const WgradGeom& g = wg.g[i];
+        const WgradGroupPtrs& p = ptrs[i];
+        WPArgs& wa = ga.job[i];
+        int v;
+        int rc = patch_args(g, 1, p.x, p.dy, nullptr, p.unpool_am, &wa, &v);
+        if (rc != WAP_OK) return rc;
+        if (fd_for(g) != 1 || g.R != 3 || (variant >= 0 && v != variant) || (p.unpool_am != nullptr) != (ptrs[0].unpool_am != nullptr) ||
+            (long)wa.ncombo * wa.tiles_total > 2147483647L - wg.per || (long)g.K * wa.Kred / 4 > 2147483647L)
+            return set_error(WAP_EINVAL, "internal: weight gradients of different kernels in one group");
+        variant = v;
+        smem = 2 * wa.buf_bytes > smem ? 2 * wa.buf_bytes : smem;
+        const int runs = (wa.ncombo * wa.tiles_total + wg.per - 1) / wg.per;
+        ga.first[i + 1] = ga.first[i] + runs;
+        ga.slot0[i] = slots;
+        WGroupSum& js = gs.job[i];
+        js.K = g.K; js.C = g.C; js.Kred = wa.Kred; js.kgroups = wa.kgroups; js.tiles = wa.tiles_total; js.runs = runs; js.slot0 = slots;
+        js.spread = wa.tiles_total / wg.per >= 8 ? 8 : 1;
+        js.dRow = make_fastdiv((uint32_t)(wa.Kred / 4));
+        js.dC = make_fastdiv((uint32_t)g.C);
+        js.out = p.dw;
+        js.sgd = SgdFuse{p.w32, p.wb, lr};
+        const int cols = 256 / js.spread;
+        gs.first[i + 1] = gs.first[i] + (g.K * (wa.Kred / 4) + cols - 1) / cols;
+        slots += runs + wa.ncombo;
+    }
+    const bool up = ptrs[0].unpool_am != nullptr;
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done) {
+        for (int k = 0; k < 2 * kNumVariants; ++k) {
+            hipError_t e = hipFuncSetAttribute(k < kNumVariants ? group_fn<false>(k) : group_fn<true>(k - kNumVariants),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+            if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+        }
+        attr_done = true;
+    }
+    void* kargs[] = {(void*)&ga};
+    hipError_t le = hipLaunchKernel(up ? group_fn<true>(variant) : group_fn<false>(variant), dim3(ga.first[wg.n]), dim3(64 * wavefronts(3)),
+                                    kargs, smem, st);
+    if (le != hipSuccess) return set_error(WAP_EHIP, "wgrad_patch_group launch: %s", hipGetErrorString(le));
+    int rc = check_launch("wgrad_patch_group");
+    if (rc != WAP_OK) return rc;
+    if (ev_mid) (void)hipEventRecord(ev_mid, st);
+    hipLaunchKernelGGL(wgrad_group_sum_kernel, dim3(gs.first[wg.n]), dim3(256), 0, st, gs);
+    return check_launch("wgrad_group_sum");
 }
 
 }  // namespace wap
