@@ -29,6 +29,7 @@ struct WArgs {
     int tiles_c, tiles_k, nsplit, ktiles, ktiles_per_split;
     int Cp;      // MODE 1: channels rounded up to 8, the columns per tap (no group of 8 crosses a tap)
     FastDiv dCp;
+    unsigned x_bytes, dy_bytes;
     FastDiv dPQ, dQ;
     SgdFuse sgd;  // w32 != NULL (unsplit reduction, Kred % 4 == 0 only): update the parameters instead of storing dW
 };
@@ -39,7 +40,8 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
-// Masked-out elements load from this zero block (no select after the load, see igemm.hip).
+// Masked-out elements load from beyond the buffer (no access, zeros), element by element from a zero block.
+constexpr unsigned kNowhere = 0xfffffff0u;  // operands of the modes 0 and 1 end before (classify_mode)
 __device__ __align__(16) unsigned int g_zero_block_w[4] = {0u, 0u, 0u, 0u};
 
 __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
@@ -47,8 +49,6 @@ __device__ __forceinline__ u32x4 pack8(const unsigned short* h) {
                (unsigned)h[4] | ((unsigned)h[5] << 16), (unsigned)h[6] | ((unsigned)h[7] << 16)};
     return v;
 }
-
-__device__ __forceinline__ u32x4 ld16(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 
 __device__ __forceinline__ bf16x8 tr_frag(const unsigned char* tile, int pitch, int colbase, int ks, int lane) {
     int col = colbase + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
@@ -63,9 +63,13 @@ __device__ __forceinline__ bf16x8 tr_frag(const unsigned char* tile, int pitch, 
 // MODE 0: C % 8 == 0 and K % 8 == 0 (16-byte loads); MODE 1: C and K of at least 8 (unaligned 16-byte loads, every tap's
 // channels rounded up to a multiple of 8 columns; element by element, as MODE 2 does it, 195 x 4096 -> 250 took 23 us);
 // MODE 2: anything (2-byte loads)
-template <int TC, int TK, int WAVES_C, int WAVES_K, int MODE>
-__global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WArgs a) {
-    constexpr int NT = 64 * WAVES_C * WAVES_K;
+// VARIANT: the mode, plus 4 where the grid leaves a CU one work-group: two wavefronts for every sub-tile, each with half of the
+// reduction steps (their sums meet in the LDS), and more tiles in flight, as in igemm.hip.
+template <int TC, int TK, int WAVES_C, int WAVES_K, int VARIANT>
+__global__ __launch_bounds__(64 * WAVES_C * WAVES_K * (VARIANT >= 4 ? 2 : 1), VARIANT >= 4 || TC * TK > 128 * 128 ? 1 : 2) void wgrad_kernel(const WArgs a) {
+    constexpr int MODE = VARIANT & 3, HALVES = VARIANT >= 4 ? 2 : 1;
+    constexpr int NT = 64 * WAVES_C * WAVES_K * HALVES;
+    constexpr int SETS = HALVES == 2 ? 4 : 1;  // register sets for tiles in flight
     constexpr int WC = TC / WAVES_C, WK = TK / WAVES_K;
     constexpr int FC = WC / 32, FK = WK / 32;
     constexpr int X_PITCH = TC * 2 + 64, D_PITCH = TK * 2 + 64;
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
 
     const WgradGeom& g = a.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wc = wave % WAVES_C, wk = wave / WAVES_C;
+    const int wc = wave % WAVES_C, wk = HALVES == 1 ? wave / WAVES_C : wave / WAVES_C % WAVES_K, hf = HALVES == 1 ? 0 : wave / (WAVES_C * WAVES_K);
 
     const int total = a.tiles_c * a.tiles_k * a.nsplit;
     int logical = xcd_remap(blockIdx.x, total);
@@ -123,16 +127,23 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
     const int ko_d = ko0 + d_vec * 8;
     const int d_over = MODE == 1 && ko_d + 8 > g.K ? ko_d + 8 - g.K : 0;  // 8 and more: no channel of this group exists
 
-    u32x4 rx[X_PASSES], rd[D_PASSES];
-    const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block_w);
+    const bf16_t* zero_src = reinterpret_cast<const bf16_t*>(g_zero_block_w);  // MODE 2
+    const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x), 0, (int)a.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcD = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.dy), 0, (int)a.dy_bytes, 0x00020000);
+    auto ld8 = [](__amdgpu_buffer_rsrc_t r, bool ok, unsigned off) {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, ok ? off * 2u : kNowhere, 0, 0);
+    };
 
-    auto load_global = [&](int kt) {
-        const int pix0 = kt * BK;
+    // (tiles past kt_end load nothing: no pixel there is below mend)
+    const uint32_t mend = kt_end < a.ktiles ? (uint32_t)kt_end * BK : (uint32_t)a.Mred;
+    int nxt = kt_begin;  // next tile to load
+    auto load_global = [&](u32x4 (&rx)[X_PASSES], u32x4 (&rd)[D_PASSES]) {
+        const uint32_t pix0 = (uint32_t)nxt++ * BK;
 #pragma unroll
         for (int i = 0; i < X_PASSES; ++i) {
-            int pix = pix0 + x_row0 + i * X_RPP;
-            bool pok = pix < a.Mred;
-            uint32_t upix = pok ? (uint32_t)pix : 0u;
+            const uint32_t pix = pix0 + x_row0 + i * X_RPP;
+            const bool pok = pix < mend;
+            const uint32_t upix = pok ? pix : 0u;
             int n = (int)fdiv(upix, a.dPQ);
             int rem = (int)upix - n * (g.P * g.Q);
             int p = (int)fdiv((uint32_t)rem, a.dQ);
@@ -143,8 +154,8 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
                 int h = hb + xr[0], w = wb + xs[0];
                 bool ok = pok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
                 int off = base + (h * g.W + w) * g.C + xc[0];
-                if (MODE == 1) rx[i] = shift_down8(load8_unaligned(ok ? a.x + off : zero_src), x_over);
-                else rx[i] = ld16(ok ? a.x + off : zero_src);
+                rx[i] = ld8(rsrcX, ok, (unsigned)off);
+                if (MODE == 1) rx[i] = shift_down8(rx[i], x_over);
             } else {
                 unsigned short h16[8];
 #pragma unroll
@@ -159,14 +170,12 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         }
 #pragma unroll
         for (int i = 0; i < D_PASSES; ++i) {
-            int pix = pix0 + d_row0 + i * D_RPP;
-            bool pok = pix < a.Mred;
+            const uint32_t pix = pix0 + d_row0 + i * D_RPP;
+            const bool pok = pix < mend;
             if (MODE == 1) {
-                const bool ok = pok && d_over < 8;
-                rd[i] = shift_down8(load8_unaligned(ok ? a.dy + ((size_t)pix * g.K + ko_d - d_over) : zero_src), d_over < 8 ? d_over : 0);
+                rd[i] = shift_down8(ld8(rsrcD, pok && d_over < 8, pix * g.K + ko_d - d_over), d_over < 8 ? d_over : 0);
             } else if (MODE == 0) {
-                bool ok = pok && ko_d < g.K;
-                rd[i] = ld16(ok ? a.dy + ((size_t)pix * g.K + ko_d) : zero_src);
+                rd[i] = ld8(rsrcD, pok && ko_d < g.K, pix * g.K + ko_d);
             } else {
                 unsigned short h16[8];
 #pragma unroll
@@ -179,7 +188,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         }
     };
 
-    auto store_lds = [&](int stage) {
+    auto store_lds = [&](int stage, const u32x4 (&rx)[X_PASSES], const u32x4 (&rd)[D_PASSES]) {
         unsigned char* sX = smem + stage * STAGE;
         unsigned char* sD = sX + X_BYTES;
 #pragma unroll
@@ -202,7 +211,8 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         const unsigned char* sX = smem + stage * STAGE;
         const unsigned char* sD = sX + X_BYTES;
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
+        for (int k2 = 0; k2 < BK / 16 / HALVES; ++k2) {
+            const int ks = hf * (BK / 16 / HALVES) + k2;
             bf16x8 fx[FC], fd[FK];
 #pragma unroll
             for (int i = 0; i < FC; ++i) fx[i] = tr_frag(sX, X_PITCH, wc * WC + i * 32, ks, lane);
@@ -216,19 +226,71 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         }
     };
 
-    if (kt_begin < kt_end) {
-        load_global(kt_begin);
-        store_lds(0);
-        __syncthreads();
-        for (int kt = kt_begin; kt < kt_end; ++kt) {
-            const int stage = (kt - kt_begin) & 1;
-            const bool more = (kt + 1 < kt_end);
-            if (more) load_global(kt + 1);
-            compute(stage);
-            if (more) store_lds(stage ^ 1);
+    const int nkt = kt_end - kt_begin;
+    if (nkt > 0) {  // tile it in the LDS, the next SETS in registers or in flight; loads unconditional, see igemm.hip
+        u32x4 rx[SETS][X_PASSES], rd[SETS][D_PASSES];
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) load_global(rx[i], rd[i]);
+        // nothing is stored or loaded behind the last tile (the largest tiles have no registers for a second copy of the products)
+        constexpr int LAST = TC * TK > 128 * 128 ? 0 : 1;
+        store_lds(0, rx[0], rd[0]);
+        int it = 0;
+        if (nkt > 1 || LAST == 0) {
+            load_global(rx[0], rd[0]);
+            __syncthreads();
+            auto step = [&](int stage, u32x4 (&xx)[X_PASSES], u32x4 (&xd)[D_PASSES]) {
+                store_lds(stage ^ 1, xx, xd);
+                load_global(xx, xd);
+                compute(stage);
+                __syncthreads();
+            };
+            constexpr int U = SETS < 2 ? 2 : SETS;
+            for (; it + U + LAST <= nkt; it += U) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) step(u & 1, rx[(u + 1) % SETS], rd[(u + 1) % SETS]);
+            }
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (it + u + LAST < nkt) step(u & 1, rx[(u + 1) % SETS], rd[(u + 1) % SETS]);
+        } else {
+            __syncthreads();
+        }
+        if constexpr (LAST == 1) {
+            compute((nkt - 1) & 1);
             __syncthreads();
         }
     }
+
+    // the halves of the reduction meet: each wavefront keeps half of the dy blocks of its sub-tile
+    constexpr int FKK = FK / HALVES;
+    if constexpr (HALVES == 2) {
+        static_assert(FK % 2 == 0 && (NT / 64) * FC * FKK * 4096 <= 2 * STAGE, "does not fit the operand tiles");
+        unsigned char* const mine = smem + wave * (FC * FKK * 4096) + lane * 16;
+        unsigned char* const theirs = smem + (wave ^ (WAVES_C * WAVES_K)) * (FC * FKK * 4096) + lane * 16;
+#pragma unroll
+        for (int i = 0; i < FC; ++i)
+#pragma unroll
+            for (int j = 0; j < FKK; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4*>(mine + ((i * FKK + j) * 4 + q) * 1024) =
+                        hf == 0 ? f32x4{acc[i][j + FKK][q * 4], acc[i][j + FKK][q * 4 + 1], acc[i][j + FKK][q * 4 + 2], acc[i][j + FKK][q * 4 + 3]}
+                                : f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < FC; ++i)
+#pragma unroll
+            for (int j = 0; j < FKK; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(theirs + ((i * FKK + j) * 4 + q) * 1024);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)  // (the first half's sum first in both)
+                        acc[i][j][q * 4 + e] = hf == 0 ? acc[i][j][q * 4 + e] + v[e] : v[e] + acc[i][j + FKK][q * 4 + e];
+                }
+        __syncthreads();
+    }
+    const int jb = hf * FKK;  // first dy block kept
 
     const bool vec4 = (a.Kred & 3) == 0 && (MODE != 1 || a.Cp == g.C);
     float* outp = a.out + (size_t)split * g.K * a.Kred;
@@ -244,11 +306,11 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         const int r_rd = lane >> 4, c_rd = (lane & 15) * 4;
         const bool fused = a.sgd.w32 != nullptr;
 #pragma unroll
-        for (int j = 0; j < FK; ++j) {
+        for (int j = 0; j < FKK; ++j) {
 #pragma unroll
             for (int ih = 0; ih < FC / 2; ++ih) {
                 const int col = col0 + wc * WC + ih * 64 + c_rd;
-                const int row0 = ko0 + wk * WK + j * 32 + r_rd;
+                const int row0 = ko0 + wk * WK + (jb + j) * 32 + r_rd;
                 float4 old[8];
                 if (fused) {
 #pragma unroll
@@ -285,8 +347,8 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K) void wgrad_kernel(const WAr
         return;
     }
 #pragma unroll
-    for (int j = 0; j < FK; ++j) {
-        const int ko = ko0 + wk * WK + j * 32 + (lane & 31);
+    for (int j = 0; j < FKK; ++j) {
+        const int ko = ko0 + wk * WK + (jb + j) * 32 + (lane & 31);
         if (ko >= g.K) continue;
 #pragma unroll
         for (int i = 0; i < FC; ++i) {
@@ -329,9 +391,9 @@ constexpr Cfg kCfgs[] = {
 
 size_t smem_bytes(const Cfg& c) { return 2 * ((size_t)BK * (c.TC * 2 + 64) + (size_t)BK * (c.TK * 2 + 64)); }
 
-template <int TC, int TK, int WCv, int WKv, int MODE>
-int launch_one(const WArgs& wa, size_t smem, hipStream_t st) {
-    auto kfn = wgrad_kernel<TC, TK, WCv, WKv, MODE>;
+template <int TC, int TK, int WCv, int WKv, int VARIANT>
+int launch_variant(const WArgs& wa, size_t smem, hipStream_t st) {
+    auto kfn = wgrad_kernel<TC, TK, WCv, WKv, VARIANT>;
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
@@ -340,11 +402,21 @@ int launch_one(const WArgs& wa, size_t smem, hipStream_t st) {
         attr_done = true;
     }
     int total = wa.tiles_c * wa.tiles_k * wa.nsplit;
-    hipLaunchKernelGGL(kfn, dim3(total), dim3(64 * WCv * WKv), smem, st, wa);
+    hipLaunchKernelGGL(kfn, dim3(total), dim3(64 * WCv * WKv * (VARIANT >= 4 ? 2 : 1)), smem, st, wa);
     return check_launch("wgrad");
+}
+// (walks of one or two tiles gain nothing that pays for adding up the halves: 40 x 3000 -> 700 7.6 us, 9.6 so)
+bool halves(long groups, int tiles) { return groups <= kNumCU && tiles >= 3; }
+template <int TC, int TK, int WCv, int WKv, int MODE>
+int launch_one(const WArgs& wa, size_t smem, hipStream_t st) {
+    constexpr int lone = TC * TK <= 128 * 128 && MODE < 2 ? 4 + MODE : MODE;
+    return halves((long)wa.tiles_c * wa.tiles_k * wa.nsplit, wa.ktiles_per_split) ? launch_variant<TC, TK, WCv, WKv, lone>(wa, smem, st)
+                                                                 : launch_variant<TC, TK, WCv, WKv, MODE>(wa, smem, st);
 }
 
 int classify_mode(const WgradGeom& g) {
+    const size_t most = 2147483647u - 63;  // elements of an operand whose last 16 bytes lie below kNowhere
+    if ((size_t)g.N * g.H * g.W * g.C > most || (size_t)g.N * g.P * g.Q * g.K > most) return 2;
     if ((g.C % 8) == 0 && (g.K % 8) == 0) return 0;
     return g.C >= 8 && g.K >= 8 ? 1 : 2;
 }
@@ -395,7 +467,9 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
     const Cfg& c = kCfgs[cfg];
     long tiles = (long)((padded_cols(g) + c.TC - 1) / c.TC) * ((g.K + c.TK - 1) / c.TK);
     int ktiles = (int)((Mred + BK - 1) / BK);
-    long want = (2L * kNumCU + tiles - 1) / tiles;
+    // about one work-group per CU, as fast with its eight wavefronts as two of four and with half the partial sums (24 x 27 x 27 x
+    // 119 -> 200 49 us, 60 with two work-groups per CU; 16 x 80 x 80 x 48 -> 24, 5x5, 39.6 and 56)
+    long want = tiles < kNumCU ? kNumCU / tiles : 1;
     long maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
     int nsplit = (int)(want < maxs ? want : maxs);
@@ -433,6 +507,8 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
     wa.ktiles = (wa.Mred + BK - 1) / BK;
     wa.nsplit = plan.nsplit;
     wa.ktiles_per_split = (wa.ktiles + plan.nsplit - 1) / plan.nsplit;
+    wa.x_bytes = (unsigned)((size_t)g.N * g.H * g.W * g.C * 2);
+    wa.dy_bytes = (unsigned)((size_t)wa.Mred * g.K * 2);
     wa.dPQ = make_fastdiv((uint32_t)(g.P * g.Q));
     wa.dQ = make_fastdiv((uint32_t)g.Q);
     wa.out = plan.nsplit > 1 ? reinterpret_cast<float*>(ws) : dw;
@@ -491,11 +567,15 @@ const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool un
     if (plan.cfg == 3) return wgrad_patch_kernel_name(g, unpool);
     if (plan.cfg == 4) return wgrad_c3_kernel_name(g);
     if (plan.cfg == 7) return "wgrad_thin_kernel";
-    static const char* names[3][3] = {
-        {"wgrad_kernel<256,256,2,4,0>", "", ""},
-        {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>", "wgrad_kernel<128,128,2,2,2>"},
-        {"wgrad_kernel<256,64,4,1,0>", "", ""},
+    static const char* names[3][6] = {
+        {"wgrad_kernel<256,256,2,4,0>", "", "", "wgrad_kernel<256,256,2,4,0>", "", ""},
+        {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>", "wgrad_kernel<128,128,2,2,2>", "wgrad_kernel<128,128,2,2,4>",
+         "wgrad_kernel<128,128,2,2,5>", "wgrad_kernel<128,128,2,2,2>"},
+        {"wgrad_kernel<256,64,4,1,0>", "", "", "wgrad_kernel<256,64,4,1,4>", "", ""},
     };
-    return names[plan.cfg][classify_mode(g)];
+    const Cfg& c = kCfgs[plan.cfg];
+    const long groups = (long)((padded_cols(g) + c.TC - 1) / c.TC) * ((g.K + c.TK - 1) / c.TK) * plan.nsplit;
+    const int ktiles = (int)(((long)g.N * g.P * g.Q + BK - 1) / BK);
+    return names[plan.cfg][classify_mode(g) + (halves(groups, (ktiles + plan.nsplit - 1) / plan.nsplit) ? 3 : 0)];
 }
 }  // namespace wap

@@ -78,3 +78,28 @@ def test_fully_connected(orc, B, n_in, n_out):
     torch.cuda.synchronize()
     assert gu.rel_err(gu.host_f64(y), x64 @ w64.T) <= gu.TOL_BF16_OUT
     assert gu.rel_err(gu.host_f64(dx), g64 @ w64) <= gu.TOL_BF16_OUT
+
+
+# weight gradient: pixels of 1 .. 9 reduction tiles unsplit and split, both wavefront arrangements, a last tile of one pixel,
+# channels in eights, odd and single, columns behind the last tap
+@pytest.mark.parametrize("case", [
+    (1, 7, 7, 512, 512, 3, 3, 1, 1), (1, 13, 5, 128, 136, 1, 1, 1, 0), (1, 16, 12, 128, 128, 1, 1, 1, 0), (5, 13, 13, 40, 72, 3, 3, 2, 1),
+    (2, 16, 18, 24, 40, 5, 5, 1, 2), (3, 19, 17, 37, 43, 3, 3, 1, 1), (1, 9, 9, 9, 257, 3, 3, (2, 1), 1), (4, 20, 20, 64, 64, 3, 3, 2, 1),
+    (1, 23, 1, 600, 700, 1, 1, 1, 0), (65, 1, 1, 264, 4100, 1, 1, 1, 0), (193, 1, 1, 520, 301, 1, 1, 1, 0), (1, 8, 8, 5, 6, 3, 3, 1, 1),
+    (12, 27, 27, 96, 256, 5, 5, 1, 2),
+])
+def test_weight_gradient(orc, case):
+    import paper_1811_01532_amd as wap
+    N, H, W, C, K, R, S, stride, pad = case
+    st = (stride, stride) if isinstance(stride, int) else stride
+    print(f"[case] wgrad {case}", flush=True)
+    P, Q = si.out_dim(H, pad, R, st[0]), si.out_dim(W, pad, S, st[1])
+    xb, gb = si.normal_bf16(si.rng(930, H * W + C), (N, H, W, C)), si.normal_bf16(si.rng(931, P * Q + K), (N, P, Q, K))
+    d = wap.conv_desc(N, H, W, C, K, R, S, st, (pad, pad))
+    n = K * R * S * C
+    dw = torch.full((n + 4,), float("nan"), dtype=torch.float32, device="cuda")
+    wap.wap_conv2d_bwd_weight(d, gu.dev_bf16(xb), gu.dev_bf16(gb), dw, gu.workspace(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)))
+    torch.cuda.synchronize()
+    assert torch.isnan(dw[n:]).all()
+    ref = orc.conv2d_bwd_weight(orc.bf16_bits_to_f64(xb), orc.bf16_bits_to_f64(gb), (K, R, S, C), st, (pad, pad))
+    assert gu.rel_err(gu.host_f64(dw[:n]).reshape(ref.shape), ref) <= gu.TOL_F32_OUT
