@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * waves_k(BM, BN, VARIANT), 
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M % WAVES_N, wk = wave / (WAVES_M * WAVES_N);
+    const int wm = wave % WAVES_M, wn = WAVES_K == 1 ? wave / WAVES_M : wave / WAVES_M % WAVES_N, wk = WAVES_K == 1 ? 0 : wave / (WAVES_M * WAVES_N);
 
     const int total = a.tiles_m * a.tiles_n * a.nsplit;
     // (phases differ in work: neighbouring work-groups go to different XCDs there)
@@ -456,24 +456,34 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * waves_k(BM, BN, VARIANT), 
         u32x4 ra[SETS][A_PASSES], rb[SETS][B_PASSES];
 #pragma unroll
         for (int i = 0; i < SETS; ++i) load_global(ra[i], rb[i]);
+        // nothing is stored or loaded behind the last tile (the largest tiles have no registers for a second copy of the products)
+        constexpr int LAST = BM * BN > 128 * 128 ? 0 : 1;
         store_lds(0, ra[0], rb[0]);
-        load_global(ra[0], rb[0]);
-        __syncthreads();
-        auto step = [&](int stage, u32x4 (&xa)[A_PASSES], u32x4 (&xb)[B_PASSES]) {
-            store_lds(stage ^ 1, xa, xb);
-            load_global(xa, xb);
-            compute(stage);
-            __syncthreads();
-        };
-        constexpr int U = SETS < 2 ? 2 : SETS;
         int it = 0;
-        for (; it + U <= nkt; it += U) {
+        if (nkt > 1 || LAST == 0) {
+            load_global(ra[0], rb[0]);
+            __syncthreads();
+            auto step = [&](int stage, u32x4 (&xa)[A_PASSES], u32x4 (&xb)[B_PASSES]) {
+                store_lds(stage ^ 1, xa, xb);
+                load_global(xa, xb);
+                compute(stage);
+                __syncthreads();
+            };
+            constexpr int U = SETS < 2 ? 2 : SETS;
+            for (; it + U + LAST <= nkt; it += U) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
+                for (int u = 0; u < U; ++u) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
+            }
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (it + u + LAST < nkt) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
+        } else {
+            __syncthreads();
         }
-#pragma unroll
-        for (int u = 0; u < U - 1; ++u)
-            if (it + u < nkt) step(u & 1, ra[(u + 1) % SETS], rb[(u + 1) % SETS]);
+        if constexpr (LAST == 1) {
+            compute((nkt - 1) & 1);
+            __syncthreads();
+        }
     }
 
     // ---- the halves of the reduction meet: each wavefront keeps every WAVES_K-th pixel block of its sub-tile ----
