@@ -328,7 +328,9 @@ int wap_step_arena_bytes(const wap_step_plan* p, size_t* bytes_out);
 int wap_step_num_tensors(const wap_step_plan* p);
 int wap_step_tensor(const wap_step_plan* p, int32_t index, const char** name, size_t* offset,
                     size_t* bytes);
-/* Enqueues one full step on `stream`: no allocation, no synchronisation. */
+/* Enqueues one full step on `stream`: no device memory allocated, no synchronisation.  Small steps run a part of the
+ * backward pass on a stream of the library's own that is forked from `stream` and joined with it by events, so that work
+ * enqueued on `stream` afterwards follows the whole step; under stream capture everything stays on `stream`. */
 int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* stream);
 /* The same step as one HIP graph: wap_step_graph_capture records the launch list for this arena on `stream`
  * (stream capture; nothing executes) and instantiates it, replacing any graph captured before;

@@ -1,10 +1,12 @@
 // One replica's whole training step as a precomputed host-side launch list: forward, loss,
 // backward, SGD (what each per-GPU partial graph of Section 3.1 executes between two gradient
 // aggregations; its duration is the sum over layers of t_c in Eq. 1).  The plan owns no device
-// memory: every tensor lives at a fixed offset of one caller-provided arena, all launches go to
-// one stream, nothing allocates or synchronises in wap_step_run.
+// memory: every tensor lives at a fixed offset of one caller-provided arena.  Launches go to the caller's
+// stream, those of a small step's fully-connected weight gradients to a second one that is forked from it and joined with it
+// by events (take_side); nothing allocates device memory or synchronises in wap_step_run.
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -46,6 +48,7 @@ struct Op {
     bool fuse_sgd = false;  // weight gradient that applies the SGD update itself (fp32 master weights at t6, bf16 copy at
                             // t7); it runs after the layer's data gradient, which still needs the old weights
     size_t t6 = 0, t7 = 0;
+    bool beside = false;    // may run beside the operations behind it, up to the plan's join
     bool colsum = false;    // data gradient whose epilogue also leaves per-tile column sums of its (masked) output at t8:
                             // the bias gradient of the layer below, finished by the OP_BIAS_FINISH operation behind it
     size_t t8 = 0;
@@ -79,10 +82,71 @@ const ConvL kVggConvs[] = {
 };
 const FcL kFcs[] = {{"fc6", 4096, true}, {"fc7", 4096, true}, {"fc8", 1000, false}};
 
+// ---- a second stream for the operations that may run beside others ----
+// Streams and events are kept for the process: a plan's first step would pay for them.  A run takes a set of its own for as
+// long as it enqueues; one that is given back may still have work in flight, which the next user's work simply follows.
+struct Side {
+    int device;
+    hipStream_t stream;
+    hipEvent_t fork, join;
+};
+constexpr size_t kMaxSides = 16;  // kept; runs beyond that many at a time use one stream
+std::mutex g_side_mutex;
+std::vector<Side*> g_sides_free;
+size_t g_sides = 0;
+
+// nullptr: run on one stream (capturing, a stream of another device than the current one, or nothing to be had)
+Side* take_side(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = -1;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (st) {
+        hipDevice_t sdev = -1;
+        if (hipStreamGetDevice(st, &sdev) != hipSuccess || sdev != dev) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+    }
+    std::lock_guard<std::mutex> lock(g_side_mutex);
+    for (size_t i = 0; i < g_sides_free.size(); ++i)
+        if (g_sides_free[i]->device == dev) {
+            Side* s = g_sides_free[i];
+            g_sides_free.erase(g_sides_free.begin() + i);
+            return s;
+        }
+    if (g_sides >= kMaxSides) return nullptr;
+    Side* s = new Side{dev, nullptr, nullptr, nullptr};
+    if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&s->join, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        if (s->fork) (void)hipEventDestroy(s->fork);
+        if (s->stream) (void)hipStreamDestroy(s->stream);
+        delete s;
+        return nullptr;
+    }
+    ++g_sides;
+    return s;
+}
+void give_side(Side* s) {
+    std::lock_guard<std::mutex> lock(g_side_mutex);
+    g_sides_free.push_back(s);
+}
+
 // Most tiles per work-group of a group of weight gradients: beyond, the partial sums that a group saves weigh little and the
 // gradients it defers have left the caches (VGG-16 at 22 images 0.996 of the ungrouped step's speed at 64, 1.004 at 48; at 8
 // images, at most 43 tiles, 1.044; AlexNet-style at 8 / 32 / 100 images 1.08 / 1.05 / 1.02).
 constexpr int kMaxGroupTiles = 48;
+
+// Which steps run their fully-connected weight gradients beside the convolutions: those whose convolutions leave the chip
+// waiting, while the gradients stay one reduction tile deep and the update rides on them.  One stream / two, us: AlexNet-style
+// at 4 / 16 / 32 / 48 / 64 images 432 / 402, 532 / 507, 606 / 590, 665 / 641, 726 / 721, VGG-16 at 3 / 8 / 12 images 1187 / 1155,
+// 1602 / 1570, 2003 / 1987; gradients stored for an exchange, 20 and 60 images 694 / 693, 868 / 875; VGG-16 at 22 no gain.
+constexpr double kForkFlops = 1.2e12;
+constexpr int kForkRows = 64;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -96,6 +160,8 @@ struct wap_step_plan {
     float lr = 0.01f;
     int B = 0, classes = 1000;
     size_t ws_off = 0, ws_bytes = 0;
+    size_t ws2_off = 0;                      // workspace of the operations that run beside others
+    bool forks = false;                      // the list has such operations, one run of them
     size_t n_params = 0;
     size_t w32_off = 0, dw_off = 0, wb_off = 0;
     mutable std::vector<hipEvent_t> events;  // cached by wap_step_time
@@ -123,8 +189,8 @@ struct wap_step_plan {
 namespace {
 
 int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_t st, hipEvent_t ev_mid = nullptr,
-           hipEvent_t ev_packed = nullptr) {
-    void* ws = base + p->ws_off;
+           hipEvent_t ev_packed = nullptr, bool beside = false) {
+    void* ws = base + (op.beside ? p->ws2_off : p->ws_off);
     switch (op.kind) {
         case OP_PACK:
             return launch_pack_weights_multi(p->packjobs, base, st);
@@ -145,7 +211,8 @@ int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_
             const SgdFuse sgd = {(float*)(base + op.t6), (bf16_t*)(base + op.t7), p->lr};
             return launch_wgrad(op.wg, op.wp, (const bf16_t*)(base + op.t0), (const bf16_t*)(base + op.t1),
                                 (float*)(base + op.t2), ws, st, ev_mid,
-                                op.unpool ? (const uint8_t*)(base + op.t3) : nullptr, op.fuse_sgd ? &sgd : nullptr);
+                                op.unpool ? (const uint8_t*)(base + op.t3) : nullptr, op.fuse_sgd ? &sgd : nullptr,
+                                beside ? kNumCU : 0);  // (one work-group per CU: a grid that fills the chip lets nothing in beside it)
         }
         case OP_WGRAD_GROUP: {
             const WgradGroup& wg = p->groups[op.group];
@@ -304,6 +371,13 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         return off;
     };
 
+    double step_flops = 0;
+    for (int i = 0; i < nconv; ++i) {
+        const GemmGeom g = geom_conv_fwd(cds[i]);
+        step_flops += (i == 0 ? 4.0 : 6.0) * g.M * (double)g.Ncols * g.Kred;
+    }
+    for (int i = 0; i < 3; ++i) step_flops += 6.0 * B * (double)fds[i].in_features * fds[i].out_features;
+
     // ---- weight gradients that share a launch at the end of the backward pass ----
     // Where both backward kernels of a layer can route the gradient of its 2x2-pooled output (see below); by shape alone, so that
     // the kept-gradients layout, which does not route, groups the same layers and gets the same sums.
@@ -340,11 +414,16 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         for (const auto& l : group_layers)
             for (int i : l) grouped[i] = true;
     }
-    // the gradient a grouped layer reads has to last until then: a buffer of its own
+    // Where the fully-connected weight gradients run beside the rest of the backward pass (below), the generic weight gradients,
+    // whose work-groups need a CU to themselves, go to the end as well.
+    const bool forks = fuse_update && B <= kForkRows && step_flops < kForkFlops;
+    std::vector<bool> late(nconv, false);
+    for (int i = 0; i < nconv; ++i) late[i] = grouped[i] || (forks && plan_wgrad(geom_conv_wgrad(cds[i])).cfg < 3);
+    // the gradient such a layer reads has to last until then: a buffer of its own
     auto grad_for = [&](const std::string& name, size_t elems, bool lasting) -> size_t {
         return lasting && !keep ? p->add(name, elems * 2) : new_grad(name, elems);
     };
-    auto reads_incoming = [&](int i) { return grouped[i] && (!convs[i].pool_win || (routes[i] && !keep)); };  // dy is what arrives from above
+    auto reads_incoming = [&](int i) { return late[i] && (!convs[i].pool_win || (routes[i] && !keep)); };  // dy is what arrives from above
 
     size_t ws_need = 0;
     auto push_fwd_like = [&](OpKind kind, const std::string& name, const GemmGeom& g, bool b_tr, bool relu, size_t a,
@@ -473,7 +552,9 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     p->flops = flops;
 
     // ---- loss ----
-    size_t g_cur = new_grad("g.fc8.y", (size_t)B * 1000);
+    // The fully-connected weight gradients (with their updates) may run beside the convolutions' backward pass: they stream the
+    // weights, most of a small step's bytes, while the convolutions wait for latency or compute.
+    size_t g_cur = forks ? p->add("g.fc8.y", (size_t)B * 1000 * 2) : new_grad("g.fc8.y", (size_t)B * 1000);
     {
         Op op;
         op.kind = OP_SOFTMAX; op.name = "softmax_xent";
@@ -511,7 +592,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (!keep) gsel = (g_cur == gbuf[0]) ? 1 : 0;
         std::string in_name = i > 0 ? "g." + lname(nconv + i - 1) + ".y"
                                     : "g." + lname(nconv - 1) + (convs[nconv - 1].pool_win ? ".pool.y" : ".y");
-        size_t g_in = grad_for(in_name, (size_t)B * fds[i].in_features, i == 0 && reads_incoming(nconv - 1));
+        size_t g_in = grad_for(in_name, (size_t)B * fds[i].in_features, i == 0 ? reads_incoming(nconv - 1) : forks);
         push_fwd_like(OP_FC_DX, nm + ".dx", geom_fc_dx(fds[i]), true, false, g_cur, p->wb_off + poff[nconv + i] * 2, g_in);
         g_cur = g_in;
     }
@@ -539,7 +620,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
             op.kind = OP_POOL_BWD; op.name = nm + ".pool_relu_bwd";
             op.N = B; op.H = gf.OH; op.W = gf.OW; op.C = d.K; op.win = convs[i].pool_win; op.st = convs[i].pool_st;
             op.t0 = g_cur; op.t1 = pool_am[i]; op.t2 = pool_y[i];
-            op.t3 = grad_for("gm." + nm + ".y", conv_y_elems[i], grouped[i]);
+            op.t3 = grad_for("gm." + nm + ".y", conv_y_elems[i], late[i]);
             op.kernel = "maxpool_bwd_kernel";
             op.bytes = 2.0 * conv_y_elems[i] + 5.0 * pool_y_elems[i];
             p->ops.push_back(op);
@@ -638,6 +719,11 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (need > ws_need) ws_need = need;
         p->groups.push_back(wg);
     }
+    for (int i = nconv - 1; i >= 0; --i) {
+            if (!late[i] || grouped[i]) continue;
+            auto it = std::find_if(p->ops.begin(), p->ops.end(), [&](const Op& o) { return o.kind == OP_CONV_WGRAD && o.C == i; });
+            std::rotate(it, it + 1, p->ops.end());
+        }
 
     // ---- update ----
     // A weight gradient that applies its own update moves behind its layer's data gradient (the next data-gradient
@@ -649,6 +735,25 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         while (j < p->ops.size() && p->ops[j].kind != OP_FC_DX && p->ops[j].kind != OP_CONV_DGRAD) ++j;
         if (j == p->ops.size()) continue;  // first layer: no data gradient
         std::rotate(p->ops.begin() + i, p->ops.begin() + i + 1, p->ops.begin() + j + 1);
+    }
+    // ---- the operations to run beside: behind the last of the fully-connected data gradients, in one run ----
+    size_t ws2_need = 0;
+    if (forks) {
+        std::vector<Op> side;
+        for (size_t i = 0; i < p->ops.size();) {
+            if (p->ops[i].kind == OP_FC_DW) {
+                side.push_back(p->ops[i]);
+                p->ops.erase(p->ops.begin() + i);
+            } else ++i;
+        }
+        size_t at = p->ops.size();
+        while (at > 0 && p->ops[at - 1].kind != OP_FC_DX) --at;
+        for (Op& op : side) {
+            op.beside = true;
+            if (op.wp.ws_bytes > ws2_need) ws2_need = op.wp.ws_bytes;
+        }
+        p->ops.insert(p->ops.begin() + at, side.begin(), side.end());
+        p->forks = true;
     }
     // the remaining parameters (gradients stored by their kernels, biases) are updated by one pass per gap
     {
@@ -679,6 +784,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     }
     p->ws_bytes = ws_need;
     p->ws_off = p->add("workspace", ws_need ? ws_need : 256);
+    if (forks) p->ws2_off = p->add("workspace2", ws2_need ? ws2_need : 256);
     *out = p;
     return WAP_OK;
 }
@@ -722,10 +828,31 @@ int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* 
     int rc = check_arena(p, arena, arena_bytes);
     if (rc != WAP_OK) return rc;
     unsigned char* base = (unsigned char*)arena;
-    for (const Op& op : p->ops) {
-        rc = run_op(p, op, base, (hipStream_t)stream);
-        if (rc != WAP_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    Side* side = p->forks ? take_side(st) : nullptr;
+    bool forked = false;
+    for (size_t i = 0; i < p->ops.size() && rc == WAP_OK; ++i) {
+        const Op& op = p->ops[i];
+        if (side && op.kind == OP_SGD && forked) {  // updates parameters whose gradients the side may still be writing
+            if (hipStreamWaitEvent(st, side->join, 0) != hipSuccess) rc = set_error(WAP_EHIP, "step: hipStreamWaitEvent failed");
+            forked = false;
+        }
+        if (rc != WAP_OK) break;
+        if (side && op.beside) {
+            if (!p->ops[i - 1].beside && (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess))
+                rc = set_error(WAP_EHIP, "step: fork failed");
+            if (rc == WAP_OK) rc = run_op(p, op, base, side->stream, nullptr, nullptr, true);
+            // (recorded behind every one of them, so that whatever was enqueued is joined)
+            if (hipEventRecord(side->join, side->stream) != hipSuccess && rc == WAP_OK) rc = set_error(WAP_EHIP, "step: hipEventRecord failed");
+            forked = true;
+        } else {
+            rc = run_op(p, op, base, st);
+        }
     }
+    if (side && forked && hipStreamWaitEvent(st, side->join, 0) != hipSuccess && rc == WAP_OK)
+        rc = set_error(WAP_EHIP, "step: join failed");
+    if (side) give_side(side);
+    if (rc != WAP_OK) return rc;
     p->ran_once = true;
     return WAP_OK;
 }

@@ -163,9 +163,10 @@ WgradPlan plan_wgrad(const WgradGeom& g);
 // argmax; only where wgrad_fuses_unpool() says so.
 // sgd: apply the update to the parameters instead of storing dW (dw may then be NULL); only where wgrad_fuses_sgd()
 // says so.
+// max_groups: most work-groups of a generic kernel's grid, which then walk the tiles (0: one for every tile).
 int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, const bf16_t* dy,
                  float* dw, void* ws, hipStream_t st, hipEvent_t ev_mid = nullptr, const uint8_t* unpool_am = nullptr,
-                 const SgdFuse* sgd = nullptr);
+                 const SgdFuse* sgd = nullptr, int max_groups = 0);
 bool wgrad_fuses_unpool(const WgradGeom& g, const WgradPlan& plan);
 bool wgrad_fuses_sgd(const WgradGeom& g, const WgradPlan& plan);
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool unpool);

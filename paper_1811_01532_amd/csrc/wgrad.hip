@@ -30,6 +30,7 @@ struct WArgs {
     int Cp;      // MODE 1: channels rounded up to 8, the columns per tap (no group of 8 crosses a tap)
     FastDiv dCp;
     unsigned x_bytes, dy_bytes;
+    int max_groups;  // host side: most work-groups of the grid (0: one per tile)
     FastDiv dPQ, dQ;
     SgdFuse sgd;  // w32 != NULL (unsplit reduction, Kred % 4 == 0 only): update the parameters instead of storing dW
 };
@@ -87,7 +88,9 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K * (VARIANT >= 4 ? 2 : 1), VA
     const int wc = wave % WAVES_C, wk = HALVES == 1 ? wave / WAVES_C : wave / WAVES_C % WAVES_K, hf = HALVES == 1 ? 0 : wave / (WAVES_C * WAVES_K);
 
     const int total = a.tiles_c * a.tiles_k * a.nsplit;
-    int logical = xcd_remap(blockIdx.x, total);
+    // (a grid of fewer work-groups than tiles walks them; see launch_wgrad's max_groups)
+    for (int bid = blockIdx.x; bid < total; bid += gridDim.x) {
+    int logical = xcd_remap(bid, total);
     const int tc = logical % a.tiles_c;
     logical /= a.tiles_c;
     const int tk = logical % a.tiles_k;
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K * (VARIANT >= 4 ? 2 : 1), VA
         // With a parameter block the old master weights are fetched before the block goes through LDS.
         static_assert(FC % 2 == 0, "the epilogue stages 64 columns at a time");
         constexpr int EP_PITCH = 64 * 4 + 16;  // rows 16 bytes apart modulo the bank width: both phases conflict-free
-        static_assert((NT / 64) * 32 * EP_PITCH <= 2 * STAGE, "epilogue staging does not fit the operand tiles");
+        static_assert((NT / 64) * 32 * EP_PITCH <= (TC * TK == 128 * 128 && HALVES == 1 ? 1 : 2) * STAGE, "epilogue staging does not fit the operand tiles");
         unsigned char* const ep = smem + wave * (32 * EP_PITCH);
         const int r_rd = lane >> 4, c_rd = (lane & 15) * 4;
         const bool fused = a.sgd.w32 != nullptr;
@@ -344,8 +347,7 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K * (VARIANT >= 4 ? 2 : 1), VA
                 __builtin_amdgcn_wave_barrier();
             }
         }
-        return;
-    }
+    } else {
 #pragma unroll
     for (int j = 0; j < FKK; ++j) {
         const int ko = ko0 + wk * WK + (jb + j) * 32 + (lane & 31);
@@ -378,6 +380,9 @@ __global__ __launch_bounds__(64 * WAVES_C * WAVES_K * (VARIANT >= 4 ? 2 : 1), VA
             }
         }
     }
+    }
+    __syncthreads();  // the tiles in the LDS may be overwritten
+    }
 }
 
 struct Cfg {
@@ -402,6 +407,7 @@ int launch_variant(const WArgs& wa, size_t smem, hipStream_t st) {
         attr_done = true;
     }
     int total = wa.tiles_c * wa.tiles_k * wa.nsplit;
+    if (wa.max_groups > 0 && total > wa.max_groups) total = wa.max_groups;
     hipLaunchKernelGGL(kfn, dim3(total), dim3(64 * WCv * WKv * (VARIANT >= 4 ? 2 : 1)), smem, st, wa);
     return check_launch("wgrad");
 }
@@ -486,7 +492,7 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
 
 int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, const bf16_t* dy,
                  float* dw, void* ws, hipStream_t st, hipEvent_t ev_mid, const uint8_t* unpool_am,
-                 const SgdFuse* sgd) {
+                 const SgdFuse* sgd, int max_groups) {
     if (unpool_am && !wgrad_fuses_unpool(g, plan))
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this weight gradient");
     if (sgd && !wgrad_fuses_sgd(g, plan))
@@ -494,6 +500,7 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
     WArgs wa;
     wa.sgd = SgdFuse{nullptr, nullptr, 0.f};
     if (sgd && plan.nsplit == 1) wa.sgd = *sgd;  // split reductions apply the update in the reduction kernel
+    wa.max_groups = max_groups;
     wa.x = x;
     wa.dy = dy;
     wa.g = g;
@@ -528,6 +535,7 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
         return WAP_OK;
     }
     size_t smem = smem_bytes(c);
+    if (plan.cfg == 1 && wa.ktiles_per_split == 1) smem /= 2;  // one tile: one stage (which holds the epilogue's blocks as well)
     int mode = classify_mode(g);
     int rc;
     if (plan.cfg == 0) {
