@@ -245,7 +245,7 @@ struct PackJob {
 constexpr int kMaxPackJobs = 32;
 struct PackJobs {
     int n;
-    size_t first[kMaxPackJobs + 1];  // first 16-byte vector of each job in the concatenated index space
+    unsigned first[kMaxPackJobs + 1];  // first group (conv_wreg.hip) of each job in the concatenated index space
     PackJob job[kMaxPackJobs];
 };
 void pack_jobs_add(PackJobs& js, const GemmGeom& g, bool flip, size_t w_off, size_t out_off);
