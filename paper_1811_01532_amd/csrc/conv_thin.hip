@@ -135,9 +135,11 @@ __global__ __launch_bounds__(NT, 2) void conv_thin_fwd_kernel(const ThinArgs a) 
     constexpr int VPR = FB * 4;  // 16-byte vectors per output pixel
     extern __shared__ __align__(16) unsigned char smem_t[];
     unsigned char* const sW = smem_t;                                    // [ksteps][FB][64 lanes][16 bytes]
-    unsigned char* const sO = sW + (size_t)a.ksteps * FB * 1024;          // one strip of 32 pixels per wavefront
-    unsigned char* const sX = sO + 4 * 32 * OPITCH;
+    unsigned char* const sX = sW + (size_t)a.ksteps * FB * 1024;
     unsigned char* const sR = sX + (size_t)(a.npx + 1) / 2 * 16;
+    // One strip of 32 pixels per wavefront, where the raw patch lay until it was widened.  Apart from it, an 11x11 filter's
+    // work-group took more than half of a CU's LDS: 8 x 224x224x3 -> 64 at stride 4 25.7 us in a step, 20.4 with two a CU.
+    unsigned char* const sO = sR;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
     const int ch0 = blockIdx.y * 32 * FB;
@@ -387,9 +389,15 @@ long thin_rows(const ThinShape& s) { return (long)(TR - 1) * s.sh + s.R; }
 long thin_npx(const ThinShape& s) { return thin_rows(s) * thin_xw(s); }
 long thin_nv(const ThinShape& s) { return (thin_xw(s) * s.C + 7 + 7) / 8; }  // up to seven elements in front of the patch
 size_t thin_patch_smem(const ThinShape& s) { return (size_t)((thin_npx(s) + 1) / 2 * 16 + thin_rows(s) * thin_nv(s) * 16); }
-size_t thin_fwd_smem(const ThinShape& s, int fb) {
+size_t thin_fwd_strips(int fb) { return (size_t)4 * 32 * (fb * 64 + 16); }
+// What the choice between kernels goes by: its lines were fitted with the strips apart from the raw patch, where fewer
+// work-groups are resident.
+size_t thin_fwd_apart(const ThinShape& s, int fb) {
     const size_t ksteps = ((size_t)s.R * ((s.S + 1) / 2) + 1) / 2;
-    return ksteps * fb * 1024 + (size_t)4 * 32 * (fb * 64 + 16) + thin_patch_smem(s);
+    return ksteps * fb * 1024 + thin_fwd_strips(fb) + thin_patch_smem(s);
+}
+size_t thin_fwd_smem(const ThinShape& s, int fb) {
+    return thin_fwd_apart(s, fb) - std::min(thin_fwd_strips(fb), (size_t)(thin_rows(s) * thin_nv(s) * 16));
 }
 size_t thin_wgrad_smem(const ThinShape& s, int fb) {
     return std::max((size_t)TR * TW * (fb * 64 + 64) + thin_patch_smem(s), (size_t)4 * 32 * 33 * sizeof(float));
@@ -406,7 +414,7 @@ bool thin_shape_ok(const ThinShape& s) {
 int thin_fwd_fb(const ThinShape& s) {
     const int nb = (s.K + 31) / 32;
     for (int fb : {3, 2})
-        if (nb % fb == 0 && thin_tiles(s) * (nb / fb) >= 2 * kNumCU && thin_fwd_smem(s, fb) <= LDS_CAP / 2) return fb;
+        if (nb % fb == 0 && thin_tiles(s) * (nb / fb) >= 2 * kNumCU && thin_fwd_apart(s, fb) <= LDS_CAP / 2) return fb;
     return 1;
 }
 int thin_wgrad_fb(const ThinShape& s) {
@@ -472,7 +480,7 @@ int launch_wgrad_t(const ThinArgs& a, dim3 grid, size_t smem, hipStream_t st) {
 bool conv_thin_fwd_supported(const GemmGeom& g) {
     if (g.div_h != 1 || g.div_w != 1) return false;
     const ThinShape s = shape_of(g);
-    return thin_shape_ok(s) && thin_fwd_smem(s, 1) <= LDS_CAP;
+    return thin_shape_ok(s) && thin_fwd_apart(s, 1) <= LDS_CAP;
 }
 
 int launch_conv_thin_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y,
@@ -499,7 +507,7 @@ int launch_conv_thin_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, co
 bool conv_thin_fwd_few_tiles(const GemmGeom& g) {
     if (!conv_thin_fwd_supported(g)) return false;
     const ThinShape s = shape_of(g);
-    const long nb = (s.K + 31) / 32, resident = std::min<long>(2, (long)(LDS_CAP / thin_fwd_smem(s, 1)));
+    const long nb = (s.K + 31) / 32, resident = std::min<long>(2, (long)(LDS_CAP / thin_fwd_apart(s, 1)));
     return thin_tiles(s) * nb <= kNumCU * std::min<long>(2, std::max(nb, resident));
 }
 
@@ -517,7 +525,7 @@ bool conv_thin_fwd_over_gather(const GemmGeom& g) {
     if (!conv_thin_fwd_supported(g)) return false;
     const ThinShape s = shape_of(g);
     const long tiles = thin_tiles(s), nb = (s.K + 31) / 32, ksteps = (g.Kred + 15) / 16;
-    const bool alone = 2 * thin_fwd_smem(s, 1) > LDS_CAP;  // one work-group per CU
+    const bool alone = 2 * thin_fwd_apart(s, 1) > LDS_CAP;  // one work-group per CU
     if (tiles * nb <= kNumCU) return ksteps >= (nb == 1 ? 10 : 5);
     if (tiles * nb <= (alone ? 1 : 2) * kNumCU && ksteps >= (nb == 1 ? 16 : 10)) return true;
     if (alone && nb > 1) return false;
