@@ -550,12 +550,13 @@ bool wgrad_thin_few_tiles(const WgradGeom& g) {
 }
 
 // Work-groups along the tiles, each of which leaves a K x R*S*C fp32 partial: two per CU over all channel groups, but no
-// more than 16 MB of partial sums together.
+// more than 24 MB of partial sums together (11x11, 8 x 224x224 -> 64, whose work-groups then have one tile instead of two: 24.1 us
+// with 16 MB, its sums 4.8; 19.7 and 6.0 with 24).
 int wgrad_thin_nsplit(const WgradGeom& g) {
     const ThinShape s = shape_of(g);
     const int fb = thin_wgrad_fb(s), groups = (s.K + 32 * fb - 1) / (32 * fb);
     const long bytes = (long)s.K * s.R * s.S * s.C * 4;
-    const long cap = std::max<long>(1, std::min<long>(2 * kNumCU / groups, (16L << 20) / bytes));
+    const long cap = std::max<long>(1, std::min<long>(2 * kNumCU / groups, (24L << 20) / bytes));
     const long tiles = thin_tiles(s);
     if (tiles <= cap) return (int)tiles;
     const long per = (tiles + cap - 1) / cap;  // the same number of tiles for (nearly) every work-group
