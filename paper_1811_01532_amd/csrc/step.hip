@@ -83,20 +83,40 @@ const ConvL kVggConvs[] = {
 const FcL kFcs[] = {{"fc6", 4096, true}, {"fc7", 4096, true}, {"fc8", 1000, false}};
 
 // ---- a second stream for the operations that may run beside others ----
-// Streams and events are kept for the process: a plan's first step would pay for them.  A run takes a set of its own for as
-// long as it enqueues; one that is given back may still have work in flight, which the next user's work simply follows.
+// Streams and events are kept for the process: a plan's first step would pay for them.  A run holds a set of its own while it
+// enqueues; a set that is given back may still have work in flight, and whoever takes it next waits for that work.  So a
+// set goes only to a run that waits for it anyway, one on the same arena (two runs that write the same memory are ordered
+// by whoever owns it), or to any run once its work is done; streams that have nothing to do with each other stay independent.
 struct Side {
-    int device;
-    hipStream_t stream;
-    hipEvent_t fork, join;
+    int device = -1;  // -1: nothing created yet
+    bool taken = false;
+    const void* arena = nullptr;
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
 };
-constexpr size_t kMaxSides = 16;  // kept; runs beyond that many at a time use one stream
+constexpr int kMaxSides = 16;  // kept; runs beyond that many at a time use one stream
 std::mutex g_side_mutex;
-std::vector<Side*> g_sides_free;
-size_t g_sides = 0;
+Side g_sides[kMaxSides];
+
+bool make_side(Side* s, int dev) {
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+    if (hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) != hipSuccess || hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        if (fork) (void)hipEventDestroy(fork);
+        if (stream) (void)hipStreamDestroy(stream);
+        return false;
+    }
+    s->device = dev;
+    s->stream = stream;
+    s->fork = fork;
+    s->join = join;
+    return true;
+}
 
 // nullptr: run on one stream (capturing, a stream of another device than the current one, or nothing to be had)
-Side* take_side(hipStream_t st) {
+Side* take_side(hipStream_t st, const void* arena) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     int dev = -1;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess) {
@@ -111,29 +131,30 @@ Side* take_side(hipStream_t st) {
         }
     }
     std::lock_guard<std::mutex> lock(g_side_mutex);
-    for (size_t i = 0; i < g_sides_free.size(); ++i)
-        if (g_sides_free[i]->device == dev) {
-            Side* s = g_sides_free[i];
-            g_sides_free.erase(g_sides_free.begin() + i);
-            return s;
-        }
-    if (g_sides >= kMaxSides) return nullptr;
-    Side* s = new Side{dev, nullptr, nullptr, nullptr};
-    if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&s->join, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        if (s->fork) (void)hipEventDestroy(s->fork);
-        if (s->stream) (void)hipStreamDestroy(s->stream);
-        delete s;
-        return nullptr;
+    Side* found = nullptr;
+    for (Side& s : g_sides)
+        if (s.device == dev && !s.taken && s.arena == arena) found = &s;
+    if (!found) {
+        // (another thread's capture may forbid a thread in the ordinary mode to ask after an event or to create a stream)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        for (Side& s : g_sides)
+            if (!found && s.device == dev && !s.taken && hipEventQuery(s.join) == hipSuccess) found = &s;
+        for (Side& s : g_sides)
+            if (!found && s.device < 0 && make_side(&s, dev)) found = &s;
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        (void)hipGetLastError();  // hipErrorNotReady
     }
-    ++g_sides;
-    return s;
+    if (found) {
+        found->taken = true;
+        found->arena = arena;
+    }
+    return found;
 }
-void give_side(Side* s) {
+// whole: everything enqueued on it lies before its join (a set of which that is not known is not used again)
+void give_side(Side* s, bool whole) {
     std::lock_guard<std::mutex> lock(g_side_mutex);
-    g_sides_free.push_back(s);
+    s->taken = !whole;
 }
 
 // Most tiles per work-group of a group of weight gradients: beyond, the partial sums that a group saves weigh little and the
@@ -829,8 +850,8 @@ int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* 
     if (rc != WAP_OK) return rc;
     unsigned char* base = (unsigned char*)arena;
     hipStream_t st = (hipStream_t)stream;
-    Side* side = p->forks ? take_side(st) : nullptr;
-    bool forked = false;
+    Side* side = p->forks ? take_side(st, arena) : nullptr;
+    bool forked = false, whole = true;
     for (size_t i = 0; i < p->ops.size() && rc == WAP_OK; ++i) {
         const Op& op = p->ops[i];
         if (side && op.kind == OP_SGD && forked) {  // updates parameters whose gradients the side may still be writing
@@ -843,7 +864,8 @@ int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* 
                 rc = set_error(WAP_EHIP, "step: fork failed");
             if (rc == WAP_OK) rc = run_op(p, op, base, side->stream, nullptr, nullptr, true);
             // (recorded behind every one of them, so that whatever was enqueued is joined)
-            if (hipEventRecord(side->join, side->stream) != hipSuccess && rc == WAP_OK) rc = set_error(WAP_EHIP, "step: hipEventRecord failed");
+            whole = hipEventRecord(side->join, side->stream) == hipSuccess;
+            if (!whole && rc == WAP_OK) rc = set_error(WAP_EHIP, "step: hipEventRecord failed");
             forked = true;
         } else {
             rc = run_op(p, op, base, st);
@@ -851,7 +873,7 @@ int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* 
     }
     if (side && forked && hipStreamWaitEvent(st, side->join, 0) != hipSuccess && rc == WAP_OK)
         rc = set_error(WAP_EHIP, "step: join failed");
-    if (side) give_side(side);
+    if (side) give_side(side, whole);
     if (rc != WAP_OK) return rc;
     p->ran_once = true;
     return WAP_OK;

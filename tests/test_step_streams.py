@@ -1,0 +1,47 @@
+"""Which streams a step with a second stream uses, seen from the library's calls to the runtime (no GPU)."""
+import pytest
+
+from tests import recorded
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    return recorded.build(tmp_path_factory.mktemp("recorder"))
+
+
+def _sides(calls, *callers):
+    """For every step of the recorded calls, in order, the stream beside the caller's (None: one stream)."""
+    steps = []
+    for c in recorded.launches(calls):
+        if c.kernel.find("pack_weights_multi") >= 0:
+            steps.append(set())
+        steps[-1].add(c.stream)
+    return [next(iter(s - set(callers)), None) for s in steps]
+
+
+RUNS = """
+plan = wap.StepPlan("alexnet", 8)
+n = plan.arena_bytes()
+rec.recorder_hold({hold})
+for arena, stream in {runs}:
+    plan.run(Mem(n, (1 + arena) << 40), stream=stream)
+"""
+
+
+def test_steps_on_independent_streams_share_no_second_stream_in_flight(so):
+    """Each of three streams waits for its own work only, whatever is in flight on the others; one arena's steps, which wait
+    for each other anyway, keep theirs."""
+    calls = recorded.run(so, RUNS.format(hold=1, runs=[(0, 0x10), (1, 0x20), (2, 0x30), (0, 0x10), (1, 0x20), (0, 0x20)]))
+    a, b, c, a2, b2, a3 = _sides(calls, "0x10", "0x20", "0x30")
+    assert None not in (a, b, c) and len({a, b, c}) == 3
+    assert (a2, b2, a3) == (a, b, a)
+
+
+def test_a_second_stream_whose_work_is_done_is_used_again(so):
+    a, b, c = _sides(recorded.run(so, RUNS.format(hold=0, runs=[(0, 0x10), (1, 0x20), (2, 0x30)])), "0x10", "0x20", "0x30")
+    assert a is not None and a == b == c
+
+
+def test_more_steps_in_flight_than_second_streams_use_one_stream(so):
+    sides = _sides(recorded.run(so, RUNS.format(hold=1, runs=[(i, 0x10) for i in range(18)])), "0x10")
+    assert len(set(sides[:16])) == 16 and sides[16:] == [None, None]
