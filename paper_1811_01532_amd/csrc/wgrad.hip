@@ -402,7 +402,8 @@ int launch_variant(const WArgs& wa, size_t smem, hipStream_t st) {
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)smem_bytes({TC, TK, 0}));  // the most any launch takes, not this one's
         if (e != hipSuccess) return set_error(WAP_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
         attr_done = true;
     }
