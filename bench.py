@@ -99,6 +99,12 @@ def init_step(plan, buf, net, B, image, torch, wap, recipe):
 LR = 0.001
 
 
+def launch_of(kernel):
+    """(kernel, whether another operation launches it) of an operation's kernel label."""
+    name, _, shared = kernel.partition(" (shared)")
+    return name, kernel != name
+
+
 def time_plain_steps(plan, buf, steps, warmup, torch):
     for _ in range(warmup):
         plan.run(buf)
@@ -268,15 +274,17 @@ def main():
                                                               "flops": 0.0, "bytes": 0.0})
                 k0["launches"] += 1
                 k0["us"] += up
-            k = kern_.setdefault(kernel, {"kernel": kernel, "launches": 0, "us": 0.0, "flops": 0.0, "bytes": 0.0})
-            k["launches"] += 1
+            name_, shared = launch_of(kernel)
+            k = kern_.setdefault(name_, {"kernel": name_, "launches": 0, "us": 0.0, "flops": 0.0, "bytes": 0.0})
+            k["launches"] += not shared
             k["us"] += u
             k["flops"] += fl
             k["bytes"] += by
             if ue > 0:   # split-reduction epilogue kernel of this operation, timed on its own
-                ek = "reduce_f32*_kernel" if kernel.startswith("wgrad") else "reduce_bf16_kernel"
+                ek = ("wgrad_group_sum_kernel" if kernel.startswith("wgrad_patch_group") else
+                      "reduce_f32*_kernel" if kernel.startswith("wgrad") else "reduce_bf16_kernel")
                 k2 = kern_.setdefault(ek, {"kernel": ek, "launches": 0, "us": 0.0, "flops": 0.0, "bytes": 0.0})
-                k2["launches"] += 1
+                k2["launches"] += not shared
                 k2["us"] += ue
         return kern_
 
@@ -284,7 +292,7 @@ def main():
     klist = sorted(kern.values(), key=lambda k: -k["us"])
     # the dominant kernel is chosen among the operations' main kernels (the split-reduction epilogues and the weight
     # repacking are listed in the breakdown, but carry no algorithmic FLOP / byte count of their own to price)
-    main_kernels = {kernel for (_, kernel, _, _) in ops}
+    main_kernels = {launch_of(kernel)[0] for (_, kernel, _, _) in ops}
     dom_entry = next(k for k in klist if k["kernel"] in main_kernels)
     dom_name = dom_entry["kernel"]
     step_us_all_events = sum(k["us"] for k in klist)
@@ -292,7 +300,7 @@ def main():
     # Timed region: exactly K steps back to back on the stream, one synchronisation on each side, HIP event
     # pairs only around the launches of the dominant kernel (the full instrumentation costs two event records
     # per operation, about 0.5 ms per step, and would be charged to the step).
-    mask = [kernel == dom_name for (_, kernel, _, _) in ops]
+    mask = [launch_of(kernel)[0] == dom_name for (_, kernel, _, _) in ops]
     # W warm-up steps immediately in front of the timed region (the clock needs about four steps to settle after
     # any idle gap; the host-side bookkeeping above is such a gap)
     for _ in range(a.warmup):

@@ -347,6 +347,9 @@ double wap_step_flops(const wap_step_plan* p);
 int wap_step_num_ops(const wap_step_plan* p);
 /* Operation `index` of the launch list: its name (e.g. "conv3_2.wgrad"), the kernel instantiation
  * it launches, and its algorithmic FLOPs and bytes (operands read once, outputs written once).
+ * The weight gradients of several small layers may share one launch: they follow each other in the list, each with
+ * its own FLOPs and bytes, the first launches it and all others carry " (shared)" behind the kernel's name; the
+ * timing entry points divide the launch's time among them by FLOPs.
  * Strings are owned by the plan. */
 int wap_step_op_info(const wap_step_plan* p, int32_t index, const char** name, const char** kernel,
                      double* flops, double* bytes);

@@ -735,7 +735,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         const size_t at = p->ops.size() - layers.size();
         p->ops[at].kind = OP_WGRAD_GROUP;
         p->ops[at].group = (int)p->groups.size();
-        for (size_t k = at; k < p->ops.size(); ++k) p->ops[k].kernel = wgrad_group_kernel_name(wg, p->ops[k].unpool);
+        for (size_t k = at; k < p->ops.size(); ++k) p->ops[k].kernel = wgrad_group_kernel_name(wg, p->ops[k].unpool, k == at);
         const size_t need = wgrad_group_ws_bytes(wg);
         if (need > ws_need) ws_need = need;
         p->groups.push_back(wg);
@@ -963,6 +963,15 @@ int wap_step_time_sampled(const wap_step_plan* p, void* arena, size_t arena_byte
         if (hipEventCreate(&e) != hipSuccess) return set_error(WAP_EHIP, "hipEventCreate failed");
         p->events.push_back(e);
     }
+    // a shared launch is timed where one of its operations is asked for
+    auto asked = [&](size_t i) { return !op_mask || op_mask[i]; };
+    auto bracket = [&](size_t i) {
+        const Op& op = p->ops[i];
+        if (op.kind == OP_WGRAD_MEMBER) return false;
+        bool any = asked(i);
+        for (int k = 1; op.kind == OP_WGRAD_GROUP && k < p->groups[op.group].n; ++k) any = any || asked(i + k);
+        return any;
+    };
     auto has_epilogue = [&](const Op& op) {
         switch (op.kind) {
             case OP_CONV_FWD: case OP_FC_FWD: case OP_CONV_DGRAD: case OP_FC_DX: return op.gp.nsplit > 1;
@@ -981,7 +990,7 @@ int wap_step_time_sampled(const wap_step_plan* p, void* arena, size_t arena_byte
     for (int s = 0; s < steps && rc == WAP_OK; ++s)
         for (size_t i = 0; i < n && rc == WAP_OK; ++i) {
             hipEvent_t* ev = &p->events[4 * ((size_t)(s / every) * n + i)];
-            if ((s % every) != 0 || (op_mask && !op_mask[i])) {
+            if ((s % every) != 0 || !bracket(i)) {
                 rc = run_op(p, p->ops[i], base, st, nullptr);
                 continue;
             }
@@ -997,9 +1006,12 @@ int wap_step_time_sampled(const wap_step_plan* p, void* arena, size_t arena_byte
         double sum = 0, sum_epi = 0;
         const bool epi = has_epilogue(p->ops[i]);
         if (us_prologue_out) us_prologue_out[i] = 0.f;
-        if (op_mask && !op_mask[i]) {
+        if (p->ops[i].kind == OP_WGRAD_MEMBER) continue;  // filled in with its group's first
+        if (!bracket(i)) {
             us_out[i] = 0.f;
             us_epilogue_out[i] = 0.f;
+            if (p->ops[i].kind == OP_WGRAD_GROUP)
+                for (int k = 1; k < p->groups[p->ops[i].group].n; ++k) us_out[i + k] = us_epilogue_out[i + k] = 0.f;
             continue;
         }
         const bool pro = has_prologue(p->ops[i]);
@@ -1026,6 +1038,16 @@ int wap_step_time_sampled(const wap_step_plan* p, void* arena, size_t arena_byte
         if (us_prologue_out) us_prologue_out[i] = (float)(sum_pro * 1000.0 / timed);
         us_out[i] = (float)(sum * 1000.0 / timed);
         us_epilogue_out[i] = (float)(sum_epi * 1000.0 / timed);
+        if (p->ops[i].kind == OP_WGRAD_GROUP) {
+            const int members = p->groups[p->ops[i].group].n;
+            double flops = 0;
+            for (int k = 0; k < members; ++k) flops += p->ops[i + k].flops;
+            for (int k = members - 1; k >= 0; --k) {  // (the first last: it holds the whole)
+                const double share = asked(i + k) ? p->ops[i + k].flops / flops : 0.0;
+                us_out[i + k] = (float)(us_out[i] * share);
+                us_epilogue_out[i + k] = (float)(us_epilogue_out[i] * share);
+            }
+        }
     }
     return WAP_OK;
 }

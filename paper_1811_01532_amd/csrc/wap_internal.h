@@ -196,7 +196,7 @@ int wgrad_group_variant(const WgradGeom& g);  // layers with the same number may
 long wgrad_group_units(const WgradGeom& g);   // tiles of all its blocks
 int wgrad_group_per(const long* units, int n);
 size_t wgrad_group_ws_bytes(const WgradGroup& wg);
-const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool);
+const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool, bool first);  // first: of the group's operations
 int launch_wgrad_group(const WgradGroup& wg, const WgradGroupPtrs* ptrs, float lr, void* ws, hipStream_t st, hipEvent_t ev_mid = nullptr);
 
 // 3-input-channel 3x3 stride-1 first layer (conv_c3.hip)

@@ -760,14 +760,14 @@ size_t wgrad_group_ws_bytes(const WgradGroup& wg) {
     for (int i = 0; i < wg.n; ++i) slots += (wgrad_group_units(wg.g[i]) + wg.per - 1) / wg.per + (size_t)(wg.g[i].K / 64) * (wg.g[i].C / 64);
     return slots * kSlotFloats * sizeof(float);
 }
-const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool) {
-    static const char* names[2][kNumVariants] = {
-        {"wgrad_patch_group_kernel<false,0,7>", "wgrad_patch_group_kernel<false,0,8>", "wgrad_patch_group_kernel<false,1,8>",
-         "wgrad_patch_group_kernel<false,2,5>", "wgrad_patch_group_kernel<false,2,6>", "wgrad_patch_group_kernel<false,2,7>"},
-        {"wgrad_patch_group_kernel<true,0,7>", "wgrad_patch_group_kernel<true,0,8>", "wgrad_patch_group_kernel<true,1,8>",
-         "wgrad_patch_group_kernel<true,2,5>", "wgrad_patch_group_kernel<true,2,6>", "wgrad_patch_group_kernel<true,2,7>"}};
+const char* wgrad_group_kernel_name(const WgradGroup& wg, bool unpool, bool first) {
+#define WAP_WG(U, V) {"wgrad_patch_group_kernel<" U "," V ">", "wgrad_patch_group_kernel<" U "," V "> (shared)"}
+#define WAP_WG6(U) {WAP_WG(U, "0,7"), WAP_WG(U, "0,8"), WAP_WG(U, "1,8"), WAP_WG(U, "2,5"), WAP_WG(U, "2,6"), WAP_WG(U, "2,7")}
+    static const char* names[2][kNumVariants][2] = {WAP_WG6("false"), WAP_WG6("true")};
+#undef WAP_WG6
+#undef WAP_WG
     const int v = wgrad_group_variant(wg.g[0]);
-    return v < 0 ? "wgrad_patch_group_kernel" : names[unpool ? 1 : 0][v];
+    return v < 0 ? "wgrad_patch_group_kernel" : names[unpool ? 1 : 0][v][first ? 0 : 1];
 }
 namespace {
 template <bool UP>

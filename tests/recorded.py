@@ -1,5 +1,6 @@
 """What the library asks of the HIP runtime, seen without a GPU: a piece of Python run in a process of its own in which
 tests/hip_recorder.cpp stands in for the runtime."""
+import ast
 import collections
 import os
 import subprocess
@@ -39,11 +40,15 @@ def build(folder):
     return so
 
 
-def run(so, code):
+def run(so, code, printed=None):
     """The calls that `code` (with `wap`, `Mem` and `rec` at hand) makes, as lists of words: launch kernel stream smem limit,
-    stream handle, record stream, wait stream."""
+    stream handle, record stream, wait stream.  What it prints, a word and a value a line, goes to printed[word]."""
     r = subprocess.run([sys.executable, "-c", PRELUDE + code + EPILOGUE, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
+    for line in r.stdout.splitlines():
+        if printed is not None and not line.startswith("# "):
+            word, value = line.split(" ", 1)
+            printed.setdefault(word, []).append(ast.literal_eval(value))
     return [line[2:].split() for line in r.stdout.splitlines() if line.startswith("# ")]
 
 
