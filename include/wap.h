@@ -353,12 +353,13 @@ int wap_step_num_ops(const wap_step_plan* p);
  * Strings are owned by the plan. */
 int wap_step_op_info(const wap_step_plan* p, int32_t index, const char** name, const char** kernel,
                      double* flops, double* bytes);
-/* Runs `steps` steps back to back with a HIP event pair around every operation (events are created
+/* Runs `steps` steps, as wap_step_run does, back to back with a HIP event pair around every operation (events are created
  * on first use and cached in the plan); fills us_out[num_ops] with the mean duration in microseconds
  * of each operation's main kernel and us_epilogue_out[num_ops] with that of its split-reduction
  * epilogue kernel (0 where the operation has none).  The weight-repacking kernel that precedes some
- * convolution kernels is outside both (see wap_step_time_masked).  Synchronises the stream once, at
- * the end. */
+ * convolution kernels is outside both (see wap_step_time_masked).  Where a part of the step runs beside
+ * another on a second stream, either takes the longer for it and the durations add up to more than the step's.
+ * Synchronises the stream once, at the end. */
 int wap_step_time(const wap_step_plan* p, void* arena, size_t arena_bytes, void* stream, int32_t steps,
                   float* us_out, float* us_epilogue_out);
 /* The same with events only around the operations whose op_mask[index] is non-zero (host array of

@@ -270,6 +270,36 @@ int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_
     return set_error(WAP_EINVAL, "internal: unknown op");
 }
 
+// Enqueues every operation of the list through launch(index, stream, beside): on `st`, or, those that may run beside others, on
+// the side's stream (side == nullptr: on `st` as well).  *whole: see give_side.
+template <typename F>
+int run_list(const wap_step_plan* p, hipStream_t st, Side* side, bool* whole, F&& launch) {
+    int rc = WAP_OK;
+    bool forked = false;
+    for (size_t i = 0; i < p->ops.size() && rc == WAP_OK; ++i) {
+        const Op& op = p->ops[i];
+        if (side && op.kind == OP_SGD && forked) {  // updates parameters whose gradients the side may still be writing
+            if (hipStreamWaitEvent(st, side->join, 0) != hipSuccess) rc = set_error(WAP_EHIP, "step: hipStreamWaitEvent failed");
+            forked = false;
+        }
+        if (rc != WAP_OK) break;
+        if (side && op.beside) {
+            if (!p->ops[i - 1].beside && (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess))
+                rc = set_error(WAP_EHIP, "step: fork failed");
+            if (rc == WAP_OK) rc = launch(i, side->stream, true);
+            // (recorded behind every one of them, so that whatever was enqueued is joined)
+            *whole = hipEventRecord(side->join, side->stream) == hipSuccess;
+            if (!*whole && rc == WAP_OK) rc = set_error(WAP_EHIP, "step: hipEventRecord failed");
+            forked = true;
+        } else {
+            rc = launch(i, st, false);
+        }
+    }
+    if (side && forked && hipStreamWaitEvent(st, side->join, 0) != hipSuccess && rc == WAP_OK)
+        rc = set_error(WAP_EHIP, "step: join failed");
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -854,28 +884,8 @@ int wap_step_run(const wap_step_plan* p, void* arena, size_t arena_bytes, void* 
     unsigned char* base = (unsigned char*)arena;
     hipStream_t st = (hipStream_t)stream;
     Side* side = p->forks ? take_side(st, arena) : nullptr;
-    bool forked = false, whole = true;
-    for (size_t i = 0; i < p->ops.size() && rc == WAP_OK; ++i) {
-        const Op& op = p->ops[i];
-        if (side && op.kind == OP_SGD && forked) {  // updates parameters whose gradients the side may still be writing
-            if (hipStreamWaitEvent(st, side->join, 0) != hipSuccess) rc = set_error(WAP_EHIP, "step: hipStreamWaitEvent failed");
-            forked = false;
-        }
-        if (rc != WAP_OK) break;
-        if (side && op.beside) {
-            if (!p->ops[i - 1].beside && (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess))
-                rc = set_error(WAP_EHIP, "step: fork failed");
-            if (rc == WAP_OK) rc = run_op(p, op, base, side->stream, nullptr, nullptr, true);
-            // (recorded behind every one of them, so that whatever was enqueued is joined)
-            whole = hipEventRecord(side->join, side->stream) == hipSuccess;
-            if (!whole && rc == WAP_OK) rc = set_error(WAP_EHIP, "step: hipEventRecord failed");
-            forked = true;
-        } else {
-            rc = run_op(p, op, base, st);
-        }
-    }
-    if (side && forked && hipStreamWaitEvent(st, side->join, 0) != hipSuccess && rc == WAP_OK)
-        rc = set_error(WAP_EHIP, "step: join failed");
+    bool whole = true;
+    rc = run_list(p, st, side, &whole, [&](size_t i, hipStream_t s, bool beside) { return run_op(p, p->ops[i], base, s, nullptr, nullptr, beside); });
     if (side) give_side(side, whole);
     if (rc != WAP_OK) return rc;
     p->ran_once = true;
@@ -987,18 +997,19 @@ int wap_step_time_sampled(const wap_step_plan* p, void* arena, size_t arena_byte
             default: return false;
         }
     };
+    Side* side = p->forks ? take_side(st, arena) : nullptr;
+    bool whole = true;
     for (int s = 0; s < steps && rc == WAP_OK; ++s)
-        for (size_t i = 0; i < n && rc == WAP_OK; ++i) {
+        rc = run_list(p, st, side, &whole, [&](size_t i, hipStream_t on, bool beside) {
+            const Op& op = p->ops[i];
             hipEvent_t* ev = &p->events[4 * ((size_t)(s / every) * n + i)];
-            if ((s % every) != 0 || !bracket(i)) {
-                rc = run_op(p, p->ops[i], base, st, nullptr);
-                continue;
-            }
-            (void)hipEventRecord(ev[0], st);
-            rc = run_op(p, p->ops[i], base, st, has_epilogue(p->ops[i]) ? ev[2] : nullptr,
-                        has_prologue(p->ops[i]) ? ev[3] : nullptr);
-            (void)hipEventRecord(ev[1], st);
-        }
+            if ((s % every) != 0 || !bracket(i)) return run_op(p, op, base, on, nullptr, nullptr, beside);
+            (void)hipEventRecord(ev[0], on);
+            const int r = run_op(p, op, base, on, has_epilogue(op) ? ev[2] : nullptr, has_prologue(op) ? ev[3] : nullptr, beside);
+            (void)hipEventRecord(ev[1], on);
+            return r;
+        });
+    if (side) give_side(side, whole);
     hipError_t e = hipStreamSynchronize(st);
     if (rc == WAP_OK && e != hipSuccess) rc = set_error(WAP_EHIP, "step: %s", hipGetErrorString(e));
     if (rc != WAP_OK) return rc;

@@ -45,3 +45,20 @@ def test_a_second_stream_whose_work_is_done_is_used_again(so):
 def test_more_steps_in_flight_than_second_streams_use_one_stream(so):
     sides = _sides(recorded.run(so, RUNS.format(hold=1, runs=[(i, 0x10) for i in range(18)])), "0x10")
     assert len(set(sides[:16])) == 16 and sides[16:] == [None, None]
+
+
+@pytest.mark.parametrize("net,mb,flags,forks", [("alexnet", 8, 0, True), ("vgg16", 8, 2, True), ("alexnet", 64, 0, True), ("alexnet", 65, 0, False),
+                                                ("alexnet", 8, 4, False), ("vgg16", 22, 0, False)])
+def test_timed_steps_are_the_steps_that_run(so, net, mb, flags, forks):
+    """The same launches on the same streams, with a mask or without."""
+    calls = recorded.launches(recorded.run(so, f"""
+plan = wap.StepPlan("{net}", {mb}, flags={flags})
+assert ("workspace2" in plan.tensors()) == {forks}
+mem = Mem(plan.arena_bytes())
+plan.run(mem, stream=0x10)
+plan.time(mem, stream=0x10)
+plan.time(mem, stream=0x10, op_mask=[i % 3 == 0 for i in range(plan.num_ops())])
+"""))
+    n = len(calls) // 3
+    assert calls[:n] == calls[n:2 * n] == calls[2 * n:]
+    assert len({c.stream for c in calls}) == (2 if forks else 1)
