@@ -1,5 +1,5 @@
-"""Steps whose fully-connected weight gradients run on a second stream beside the convolutions: the same weights as on one
-stream (the timing entry point and a captured graph run the list on one), with several runs in flight at once."""
+"""Steps whose fully-connected weight gradients run on a second stream beside the convolutions (which launches do: test_step_streams.py):
+the same weights as on one stream, as a captured graph runs the list, with several runs in flight at once."""
 import threading
 
 import pytest
@@ -15,9 +15,12 @@ def _params(plan, buf):
     return buf[off:off + nb].clone()
 
 
-@pytest.mark.parametrize("net,B,image,flags", [("alexnet", 2, 131, 0), ("alexnet", 64, 67, 2), ("vgg16", 3, 64, 0), ("alexnet", 65, 67, 0), ("alexnet", 3, 67, 6)])
-def test_beside_is_bitwise_the_same(orc, net, B, image, flags):
+# (more rows than the limit, and stored gradients: the list has one stream anyway)
+@pytest.mark.parametrize("net,B,image,flags,forks", [("alexnet", 2, 131, 0, True), ("alexnet", 64, 67, 2, True), ("vgg16", 3, 64, 0, True),
+                                                     ("alexnet", 5, 67, 2, True), ("alexnet", 65, 67, 0, False), ("alexnet", 3, 67, 6, False)])
+def test_beside_is_bitwise_the_same(orc, net, B, image, flags, forks):
     plan, ar, *_ = _setup(net, B, image, flags, 560)
+    assert ("workspace2" in plan.tensors()) == forks
     print(f"[case] step beside {net} B={B} image={image} flags={flags}", flush=True)
     start = ar.buf.clone()
     for _ in range(3):
@@ -44,6 +47,7 @@ def test_runs_of_one_plan_from_several_threads(orc):
     """One plan, four arenas, a thread and a stream each, more runs in flight than one after the other: every arena ends as a
     run by itself leaves it."""
     plan, ar, *_ = _setup("alexnet", 4, 131, 0, 561)
+    assert "workspace2" in plan.tensors()
     print("[case] step beside, four threads", flush=True)
     arenas = [ar.buf.clone() for _ in range(4)]
     for _ in range(6):
