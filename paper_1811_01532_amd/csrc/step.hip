@@ -86,11 +86,14 @@ const FcL kFcs[] = {{"fc6", 4096, true}, {"fc7", 4096, true}, {"fc8", 1000, fals
 // Streams and events are kept for the process: a plan's first step would pay for them.  A run holds a set of its own while it
 // enqueues; a set that is given back may still have work in flight, and whoever takes it next waits for that work.  So a
 // set goes only to a run that waits for it anyway, one on the same arena (two runs that write the same memory are ordered
-// by whoever owns it), or to any run once its work is done; streams that have nothing to do with each other stay independent.
+// by whoever owns it) or like the last on the default stream (which is never another one), or to any run once its work is
+// done; streams that have nothing to do with each other stay independent.  (With a set for each arena of the default stream
+// three arenas in turn took 437 instead of 432 us, AlexNet-style at 8 images.)
 struct Side {
     int device = -1;  // -1: nothing created yet
     bool taken = false;
-    const void* arena = nullptr;
+    const void* arena = nullptr;    // of the last run
+    bool on_default = false;        // the last run's stream was the default stream
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };
@@ -133,7 +136,7 @@ Side* take_side(hipStream_t st, const void* arena) {
     std::lock_guard<std::mutex> lock(g_side_mutex);
     Side* found = nullptr;
     for (Side& s : g_sides)
-        if (s.device == dev && !s.taken && s.arena == arena) found = &s;
+        if (s.device == dev && !s.taken && (s.arena == arena || (!st && s.on_default))) found = &s;
     if (!found) {
         // (another thread's capture may forbid a thread in the ordinary mode to ask after an event or to create a stream)
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -148,6 +151,7 @@ Side* take_side(hipStream_t st, const void* arena) {
     if (found) {
         found->taken = true;
         found->arena = arena;
+        found->on_default = !st;
     }
     return found;
 }
@@ -166,6 +170,8 @@ constexpr int kMaxGroupTiles = 48;
 // waiting, while the gradients stay one reduction tile deep and the update rides on them.  One stream / two, us: AlexNet-style
 // at 4 / 16 / 32 / 48 / 64 images 432 / 402, 532 / 507, 606 / 590, 665 / 641, 726 / 721, VGG-16 at 3 / 8 / 12 images 1187 / 1155,
 // 1602 / 1570, 2003 / 1987; gradients stored for an exchange, 20 and 60 images 694 / 693, 868 / 875; VGG-16 at 22 no gain.
+// (On one of six streams of a caller the second stream gained nothing, as if both had the same hardware queue: AlexNet-style at 8
+// 478 against 421 on the others and 456 as a captured one-stream graph, VGG-16 at 8 1587 / 1507 / 1578.)
 constexpr double kForkFlops = 1.2e12;
 constexpr int kForkRows = 64;
 
@@ -770,11 +776,12 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (need > ws_need) ws_need = need;
         p->groups.push_back(wg);
     }
+    // ... and the late ones that are in no group
     for (int i = nconv - 1; i >= 0; --i) {
-            if (!late[i] || grouped[i]) continue;
-            auto it = std::find_if(p->ops.begin(), p->ops.end(), [&](const Op& o) { return o.kind == OP_CONV_WGRAD && o.C == i; });
-            std::rotate(it, it + 1, p->ops.end());
-        }
+        if (!late[i] || grouped[i]) continue;
+        auto it = std::find_if(p->ops.begin(), p->ops.end(), [&](const Op& o) { return o.kind == OP_CONV_WGRAD && o.C == i; });
+        std::rotate(it, it + 1, p->ops.end());
+    }
 
     // ---- update ----
     // A weight gradient that applies its own update moves behind its layer's data gradient (the next data-gradient

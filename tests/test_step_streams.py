@@ -37,6 +37,12 @@ def test_steps_on_independent_streams_share_no_second_stream_in_flight(so):
     assert (a2, b2, a3) == (a, b, a)
 
 
+def test_steps_on_the_default_stream_share_one(so):
+    """Whatever their arenas: they follow each other anyway.  A step on another stream has another."""
+    a, b, c, d = _sides(recorded.run(so, RUNS.format(hold=1, runs=[(0, 0), (1, 0), (2, 0x20), (3, 0)])), "(nil)", "0x20")
+    assert a is not None and a == b == d and c not in (None, a)
+
+
 def test_a_second_stream_whose_work_is_done_is_used_again(so):
     a, b, c = _sides(recorded.run(so, RUNS.format(hold=0, runs=[(0, 0x10), (1, 0x20), (2, 0x30)])), "0x10", "0x20", "0x30")
     assert a is not None and a == b == c
