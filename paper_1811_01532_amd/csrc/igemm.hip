@@ -831,10 +831,44 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
         const int slices = g.IC / 32, per = (slices + g_force_nsplit - 1) / g_force_nsplit;
         nsplit = (slices + per - 1) / per;
     }
-    p.cfg = cfg;
-    p.nsplit = nsplit;
     p.ws_bytes = nsplit > 1 ? (size_t)nsplit * g.M * g.Ncols * sizeof(float) : 0;
     if (cfg >= 5) p.ws_bytes += wreg_wt_bytes(g);  // weights repacked into MFMA fragment order
+    // Small layers: tiles whose reduction is divided over the wavefronts of a work-group, so that no partial sums and no second launch are
+    // needed.  us, kernels alone, the plan so far / the flat tiles (351 products, as in flat_pick):
+    //   a split reduction of the patch kernel, always: 8 x 13 x 13, 256 -> 256 14.4 / 8.2, 8 x 14 x 14, 512 -> 512 20.8 / 15.0, 2 x 28 x 28,
+    //     128 -> 128 15.8 / 6.2, 5x5 3 x 27 x 27, 192 -> 64 16.2 / 12.9 (100 products: 1.03 to 2.5 times as fast);
+    //   unsplit tiles of the patch kernel up to ten 32 x 32 blocks of outputs per CU (32 x 13 x 13, 384 -> 256 20.7 / 14.3, 22 x 14 x 14,
+    //     512 -> 512 31.9 / 23.8), sixteen with 256 input channels (8 x 28 x 28, 512 -> 512 36 / 30; with 128 62 x 62 15 / 20), eight
+    //     for 5x5 (32 x 27 x 27, 64 -> 192 20 / 26): beyond, the larger tiles read fewer weights per output;
+    //   the generic kernel: where the predicted time, with a packing launch where there is one to pay for, is below that
+    //     kernel's line of 9 us (14 with a split reduction) and 550 TFLOP/s (13 x 67 x 67, 384 -> 32 41 / 52, 28 x 10 x 10 20 / 8).
+    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans (what
+    // wap_conv2d_kernel_name says of them is promised by the tests of the boundary), and every plan the workspace it asked for:
+    // what fits the static scratch, or does not, stays so.
+    if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && (prepacked || nsplit == 1)) {
+        const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
+        const size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
+        double us = 0;
+        const int tile = blocks <= 64.0 && (b_tr || need == p.ws_bytes || need <= WAP_STATIC_SCRATCH_BYTES) ? flat_pick(g, &us) : 0;
+        bool wins;
+        if (cfg == 7 && nsplit > 1) wins = true;
+        else if (cfg < 5) wins = us + (prepacked ? 0.0 : 4.0) < (nsplit > 1 ? 14.0 : 9.0) + flops / 550e6;
+        else wins = blocks <= (g.R == 5 ? 8.0 : g.IC >= 256 ? 16.0 : 10.0) && !(cfg == 7 && !b_tr && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g));
+        if (tile && wins) {
+            cfg = 16;
+            p.tile = tile;
+            nsplit = 1;
+            p.ws_bytes = need;
+        }
+    }
+    if (g_force_fwd_cfg >= 100 && flat_supported(g, g_force_fwd_cfg - 100)) {
+        cfg = 16;
+        p.tile = g_force_fwd_cfg - 100;
+        nsplit = 1;
+        p.ws_bytes = wreg_wt_bytes(g);
+    }
+    p.cfg = cfg;
+    p.nsplit = nsplit;
     return p;
 }
 
@@ -887,7 +921,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     ka.mask = ka.partial ? nullptr : relu_mask;
     ka.relu = ka.partial ? 0 : (relu ? 1 : 0);
     ka.out = ka.partial ? ws : (void*)out;
-    if (plan.cfg == 6 || plan.cfg == 7) {
+    if (plan.cfg == 6 || plan.cfg == 7 || plan.cfg == 16) {
         const void* wp = prepacked;
         if (!wp) {
             int rc0 = launch_pack_weights(g, b_tr, Bw, ws, st);
@@ -895,6 +929,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
             wp = ws;
         }
         if (ev_packed) (void)hipEventRecord(ev_packed, st);
+        if (plan.cfg == 16) return launch_flat(g, plan.tile, A, wp, bias, relu, out, st, relu_mask, unpool_am, colsum);
         if (plan.cfg == 7 && plan.nsplit > 1) {
             float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + wreg_wt_bytes(g));
             int rc7 = launch_tile2d(g, A, wp, nullptr, false, nullptr, st, nullptr, nullptr, nullptr, unpool_am, nullptr, plan.tile,
@@ -982,18 +1017,21 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
 }  // namespace wap
 
 namespace wap {
-bool fwd_like_packs_weights(const GemmPlan& plan) { return plan.cfg == 5 || plan.cfg == 6 || plan.cfg == 7; }
+bool fwd_like_packs_weights(const GemmPlan& plan) { return plan.cfg == 5 || plan.cfg == 6 || plan.cfg == 7 || plan.cfg == 16; }
 bool fwd_like_fuses_pool(const GemmGeom& g, const GemmPlan& plan) {
     return plan.cfg == 7 && plan.nsplit == 1 && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g);
 }
-bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) { return plan.cfg == 7 && tile2d_fuses_unpool(g, plan.tile); }
+bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) {
+    return plan.cfg == 16 ? flat_fuses_unpool(g) : plan.cfg == 7 && tile2d_fuses_unpool(g, plan.tile);
+}
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return reduce_bf16_colsum_rows(g.M, g.Ncols);
+    if (plan.cfg == 16) return flat_colsum_rows(g, plan.tile);
     return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g) : 0;
 }
 bool fwd_like_fuses_mask(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return (g.Ncols % 4) == 0;  // by the kernel that adds up the splits
-    return plan.cfg < 5 || ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11;
+    return plan.cfg < 5 || ((plan.cfg == 6 || plan.cfg == 7) && (g.Ncols % 8) == 0) || plan.cfg == 11 || plan.cfg == 16;
 }
 // Label of the kernel instantiation a plan launches (matches the demangled kernel name).
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool) {
@@ -1005,6 +1043,7 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 10) return "fc_fwd_kernel";
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
+    if (plan.cfg == 16) return flat_kernel_name(g, plan.tile, unpool);
     const int mode = classify_mode(g, b_tr);
     const Cfg& c = kCfgs[plan.cfg];
     Phase ph[kMaxPhases];

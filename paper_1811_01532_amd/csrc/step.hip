@@ -494,7 +494,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         op.t0 = a; op.t1 = w; op.t2 = o;
         if (op.gp.ws_bytes > ws_need) ws_need = op.gp.ws_bytes;
         // kernels that read the weights in MFMA fragment order: one repacking kernel per step serves them all
-        if ((op.gp.cfg == 6 || op.gp.cfg == 7) && p->packjobs.n < kMaxPackJobs) {
+        if ((op.gp.cfg == 6 || op.gp.cfg == 7 || op.gp.cfg == 16) && p->packjobs.n < kMaxPackJobs) {
             op.prepacked = true;
             op.t4 = p->add("wpack." + name, wreg_wt_bytes(g));
             pack_jobs_add(p->packjobs, g, b_tr, w, op.t4);

@@ -107,7 +107,7 @@ struct GemmPlan {
     int cfg;     // tile configuration id
     int nsplit;  // reduction splits (1 = direct epilogue)
     size_t ws_bytes;
-    int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own
+    int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own; cfg 16: flat_pick
 };
 constexpr int kTileSplit64 = 1, kTileSplit192 = 3;
 
@@ -281,6 +281,16 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
 int tile2d_colsum_rows(const GemmGeom& g);
 bool tile2d_fuses_pool(const GemmGeom& g);
 bool tile2d_fuses_unpool(const GemmGeom& g, int tile = 0);
+
+// stride-1 3x3 and 5x5 layers on short flat tiles, the reduction divided over the wavefronts of a work-group (conv_tile2d_flat.hip);
+// tile = 10 * (32-pixel fragments) + wavefronts that divide the reduction
+bool flat_supported(const GemmGeom& g, int tile);
+int flat_pick(const GemmGeom& g, double* us_out);  // 0: none
+bool flat_fuses_unpool(const GemmGeom& g);
+int flat_colsum_rows(const GemmGeom& g, int tile);
+const char* flat_kernel_name(const GemmGeom& g, int tile, bool unpool);
+int launch_flat(const GemmGeom& g, int tile, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out, hipStream_t st,
+                const bf16_t* mask, const uint8_t* unpool_am, float* colsum);
 
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool = false);
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan);

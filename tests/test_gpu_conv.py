@@ -117,6 +117,26 @@ CASES = [
     ("c3_general_forced_5x5_s2_k32", (9, 63, 61, 3, 32, 5, 5, 2, 2), (8, 4, -1)),
     ("c3_strided_forced_11x11_s4_k64", (4, 131, 136, 3, 64, 11, 11, 4, 2), (8, 4, -1)),
     ("c3_strided_forced_5x9_rect_stride_2_4_pad_1_0", (8, 30, 64, 3, 64, 5, 9, (2, 4), (1, 0)), (8, 4, -1)),
+    # flat tiles whose wavefronts divide the reduction: every tiling; one slice and several, a layer smaller than a tile, ragged
+    # last tiles, runs over rows and images, channels that fill no block (40, 72 outputs), pad 0, pooled dy (even maps), 5x5
+    ("flat_14_w13", (3, 13, 13, 192, 64, 3, 3, 1, 1), (114, -1, -1)),
+    ("flat_14_under_one_tile_k40", (1, 4, 5, 64, 40, 3, 3, 1, 1), (114, -1, -1)),
+    ("flat_14_5x5_even", (2, 10, 8, 64, 64, 5, 5, 1, 2), (114, -1, -1)),
+    ("flat_18_w14_images", (3, 14, 14, 128, 128, 3, 3, 1, 1), (118, -1, -1)),
+    ("flat_18_three_slices", (1, 7, 7, 384, 128, 3, 3, 1, 1), (118, -1, -1)),
+    ("flat_22_odd_slices_k72", (2, 11, 17, 96, 72, 3, 3, 1, 1), (122, -1, -1)),
+    ("flat_22_one_slice_w40", (1, 10, 40, 32, 160, 3, 3, 1, 1), (122, -1, -1)),
+    ("flat_24_7x7_maps", (9, 7, 7, 64, 192, 3, 3, 1, 1), (124, -1, -1)),
+    ("flat_24_pad0", (2, 12, 14, 128, 64, 3, 3, 1, 0), (124, -1, -1)),
+    ("flat_28_w12", (2, 12, 12, 256, 128, 3, 3, 1, 1), (128, -1, -1)),
+    ("flat_32_5x5_c96", (2, 9, 9, 96, 96, 5, 5, 1, 2), (132, -1, -1)),
+    ("flat_32_w56_even", (1, 12, 56, 32, 64, 3, 3, 1, 1), (132, -1, -1)),
+    ("flat_34_5x5_w27", (1, 27, 27, 64, 64, 5, 5, 1, 2), (134, -1, -1)),
+    ("flat_34_w13", (4, 13, 13, 128, 64, 3, 3, 1, 1), (134, -1, -1)),
+    ("flat_42_w14_k136", (3, 14, 14, 64, 136, 3, 3, 1, 1), (142, -1, -1)),
+    ("flat_42_exact_tiles", (4, 8, 16, 64, 128, 3, 3, 1, 1), (142, -1, -1)),
+    ("flat_44_w28_even", (1, 28, 28, 128, 64, 3, 3, 1, 1), (144, -1, -1)),
+    ("flat_44_5x5_images", (3, 6, 7, 64, 64, 5, 5, 1, 2), (144, -1, -1)),
 ]
 
 
