@@ -233,6 +233,10 @@ int launch_fc_fwd(const GemmGeom& g, int nsplit, const bf16_t* x, const bf16_t* 
                   hipStream_t st);
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
 
+// fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups: as launch_wgrad
+bool fc_dw_supported(const WgradGeom& g);
+int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, hipStream_t st);
+
 // weights-in-registers large-tile kernel (conv_wreg.hip)
 bool wreg_supported(const GemmGeom& g);
 inline size_t wreg_wt_bytes(const GemmGeom& g) { return (size_t)((g.Ncols + 31) / 32) * 32 * g.Kred * 2; }  // packed copy

@@ -471,6 +471,12 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
         p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * g.K * Kred * sizeof(float) : 0;
         return p;
     }
+    if (g_force_wgrad_cfg < 0 && g_force_nsplit < 0 && fc_dw_supported(g)) {
+        p.cfg = 8;
+        p.nsplit = 1;
+        p.ws_bytes = 0;
+        return p;
+    }
     const Cfg& c = kCfgs[cfg];
     long tiles = (long)((padded_cols(g) + c.TC - 1) / c.TC) * ((g.K + c.TK - 1) / c.TK);
     int ktiles = (int)((Mred + BK - 1) / BK);
@@ -498,6 +504,7 @@ int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, con
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this weight gradient");
     if (sgd && !wgrad_fuses_sgd(g, plan))
         return set_error(WAP_EINVAL, "internal: fused SGD update not available for this weight gradient");
+    if (plan.cfg == 8) return launch_fc_dw(g, x, dy, dw, sgd, max_groups, st);
     WArgs wa;
     wa.sgd = SgdFuse{nullptr, nullptr, 0.f};
     if (sgd && plan.nsplit == 1) wa.sgd = *sgd;  // split reductions apply the update in the reduction kernel
@@ -568,7 +575,7 @@ bool wgrad_fuses_unpool(const WgradGeom& g, const WgradPlan& plan) {
 // first-layer kernels always reduce), or the epilogue of an unsplit generic product whose accumulator rows are
 // 16-byte groups of parameters.
 bool wgrad_fuses_sgd(const WgradGeom& g, const WgradPlan& plan) {
-    if (plan.cfg == 4 || plan.cfg == 7 || plan.nsplit > 1) return true;
+    if (plan.cfg == 4 || plan.cfg == 7 || plan.cfg == 8 || plan.nsplit > 1) return true;
     return plan.cfg < 3 && ((g.R * g.S * g.C) & 3) == 0;
 }
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan) { return wgrad_kernel_name(g, plan, false); }
@@ -576,6 +583,7 @@ const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool un
     if (plan.cfg == 3) return wgrad_patch_kernel_name(g, unpool);
     if (plan.cfg == 4) return wgrad_c3_kernel_name(g);
     if (plan.cfg == 7) return "wgrad_thin_kernel";
+    if (plan.cfg == 8) return "fc_dw_kernel";
     static const char* names[3][6] = {
         {"wgrad_kernel<256,256,2,4,0>", "", "", "wgrad_kernel<256,256,2,4,0>", "", ""},
         {"wgrad_kernel<128,128,2,2,0>", "wgrad_kernel<128,128,2,2,1>", "wgrad_kernel<128,128,2,2,2>", "wgrad_kernel<128,128,2,2,4>",
