@@ -204,6 +204,10 @@ bool conv_c3_fwd_supported(const GemmGeom& g);
 const char* conv_c3_fwd_kernel_name(const GemmGeom& g);
 int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y,
                        hipStream_t st);
+// ... 11x11 at stride 4, groups of output rows (conv_c3_rows.hip)
+bool conv_c3_rows_supported(const GemmGeom& g);
+const char* conv_c3_rows_kernel_name(const GemmGeom& g);
+int launch_conv_c3_rows(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y, hipStream_t st);
 bool wgrad_c3_supported(const WgradGeom& g);
 const char* wgrad_c3_kernel_name(const WgradGeom& g);
 int wgrad_c3_nsplit(const WgradGeom& g);

@@ -137,6 +137,14 @@ CASES = [
     ("flat_42_exact_tiles", (4, 8, 16, 64, 128, 3, 3, 1, 1), (142, -1, -1)),
     ("flat_44_w28_even", (1, 28, 28, 128, 64, 3, 3, 1, 1), (144, -1, -1)),
     ("flat_44_5x5_images", (3, 6, 7, 64, 64, 5, 5, 1, 2), (144, -1, -1)),
+    # 11x11 at stride 4 by groups of 1, 2 and 4 output rows: rows that end in the middle of a vector, a last group cut short, wide
+    # and no borders, an image lower than the filter, the narrowest and the widest map
+    ("c3_groups_1_w138", (2, 19, 138, 3, 64, 11, 11, 4, 2), (-1, -1, -1)),
+    ("c3_groups_1_w139_no_border_k32", (1, 30, 140, 3, 32, 11, 11, 4, 0), (-1, -1, -1)),
+    ("c3_groups_1_low_image_wide_border", (2, 9, 130, 3, 32, 11, 11, 4, (5, 8)), (-1, -1, -1)),
+    ("c3_groups_2_w226", (20, 107, 226, 3, 64, 11, 11, 4, 2), (-1, -1, -1)),
+    ("c3_groups_4_k32_cut_short", (110, 55, 136, 3, 32, 11, 11, 4, 2), (-1, -1, -1)),
+    ("c3_groups_4_k64", (130, 51, 138, 3, 64, 11, 11, 4, (1, 4)), (-1, -1, -1)),
 ]
 
 
