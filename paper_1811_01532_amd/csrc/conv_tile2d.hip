@@ -41,7 +41,7 @@ constexpr size_t LDS_CAP = 160 * 1024;
 
 struct TArgs {
     const bf16_t* A;
-    const bf16_t* Wp;  // packed weights
+    const bf16_t* Wp;  // packed weights (see wo)
     const float* bias;
     const bf16_t* mask;  // optional: out = mask > 0 ? out : 0
     const uint8_t* up_am;  // UP: argmax (r * 2 + s) per pooling window; A is then N x IH/2 x IW/2 x IC
@@ -61,6 +61,7 @@ struct TArgs {
     int PH;              // flat tiles: padded image height
     int relu;
     unsigned a_bytes, w_bytes;
+    WOrder wo;           // the tiles of small layers: where a weight lies
     FastDiv dTimg, dTx;
     FastDiv dOHW, dOW;   // flat tiles
     int UW, units;       // UP, 2-D tiles: pooling windows per patch row, windows per patch
@@ -264,22 +265,20 @@ __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
         }
     }
 
-    // ---- weights: packed [channel block of 32][reduction step of 16][lane][8] ----
-    const unsigned ksteps = (unsigned)g.Kred / 16u;
+    // ---- weights: packed [channel block of 32][reduction step of 16][lane][8]; small layers' tiles take them unpacked as well ----
+    const WOrder wo = SPLIT ? a.wo : w_packed(g.Kred);
     unsigned wrow[FN];
 #pragma unroll
-    for (int i = 0; i < FN; ++i) {
-        unsigned blk = (unsigned)(n0 + cg * 32 * FN + i * 32) / 32u;
-        wrow[i] = (blk * ksteps * 64u + (unsigned)lane) * 16u;
-    }
+    for (int i = 0; i < FN; ++i)
+        wrow[i] = (unsigned)(n0 + cg * 32 * FN + i * 32) / 32u * wo.block + (unsigned)(lane & 31) * wo.row + (unsigned)(lane >> 5) * wo.half;
     auto load_w = [&](int cs, int tap, bf16x8 (&wd)[2][FN]) {
-        const unsigned koff = ((unsigned)(tap * g.IC + cs * BK) / 16u) * 1024u;
+        const unsigned koff = (unsigned)(tap * g.IC + cs * BK) / 16u * wo.step;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int i = 0; i < FN; ++i)
                 wd[ks][i] = __builtin_bit_cast(
-                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrcW, wrow[i] + koff + (unsigned)ks * 1024u, 0, 0));
+                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrcW, wrow[i] + koff + (unsigned)ks * wo.step, 0, 0));
     };
 
     // ---- patch slice: global -> registers (issue), registers -> LDS buffer (store) ----
@@ -912,7 +911,7 @@ bool tile2d_fuses_pool(const GemmGeom& g) {
 
 int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out,
                   hipStream_t st, const bf16_t* mask, bf16_t* pool_y, uint8_t* pool_am, const uint8_t* unpool_am,
-                  float* colsum, int tile, int nsplit, float* part) {
+                  float* colsum, int tile, int nsplit, float* part, bool w_raw) {
     if (colsum && pool_y) return set_error(WAP_EINVAL, "internal: column sums and the fused pool share the staging area");
     if (!tile && tile64_width(g)) return launch_tile64(g, A, Wp, bias, relu, out, st, mask, pool_y, pool_am, unpool_am, colsum);
     TArgs ta = {};
@@ -966,7 +965,9 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
     }
     ta.relu = relu ? 1 : 0;
     ta.a_bytes = (unsigned)((size_t)(g.M / (g.OH * g.OW)) * g.IH * g.IW * g.IC * 2 / (unpool_am ? 4 : 1));
-    ta.w_bytes = (unsigned)wreg_wt_bytes(g);
+    if (w_raw && !part) return set_error(WAP_EINVAL, "internal: only split tiles take unpacked weights");
+    ta.wo = w_raw ? w_unpacked(g.Kred) : w_packed(g.Kred);
+    ta.w_bytes = w_raw ? (unsigned)((size_t)g.Ncols * g.Kred * 2) : (unsigned)wreg_wt_bytes(g);
     ta.dTimg = make_fastdiv((uint32_t)ta.tiles_img);
     ta.dTx = make_fastdiv((uint32_t)ta.tiles_x);
     ta.dRW = make_fastdiv((uint32_t)ta.RW);

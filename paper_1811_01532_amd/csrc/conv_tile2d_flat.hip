@@ -30,7 +30,7 @@ constexpr size_t LDS_CAP = 160 * 1024;
 
 struct FlatArgs {
     const bf16_t* A;
-    const bf16_t* Wp;      // packed weights
+    const bf16_t* Wp;      // packed weights, or the tensor itself (see wo)
     const float* bias;
     const bf16_t* mask;    // optional: out = mask > 0 ? out : 0
     const uint8_t* up_am;  // UP: argmax (r * 2 + s) per pooling window; A is then N x IH/2 x IW/2 x IC
@@ -43,6 +43,7 @@ struct FlatArgs {
     FastDiv dRW, dRPHW, dOHW, dOW;
     int relu;
     unsigned a_bytes, w_bytes;
+    WOrder wo;
 };
 
 __device__ __forceinline__ int xcd_remap(int bid, int total) {
@@ -134,11 +135,11 @@ __global__ __launch_bounds__(NT, FM <= 2 && KS <= 4 && ST == 3 && !UP ? 4 : 2) v
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(UP ? a.up_am : nullptr), 0, UP ? (int)(a.a_bytes / 2) : 0, 0x00020000);
     constexpr unsigned OOB = 0x80000000u;  // both operands are below 2 GiB (checked on the host)
 
-    // ---- weights: packed [channel block of 32][reduction step of 16][lane][8] ----
-    const unsigned wrow = ((unsigned)(tn * CB + cg) * ((unsigned)g.Kred / 16u) + (unsigned)kg) * 1024u + (unsigned)lane * 16u;
-    const unsigned tapstep = (unsigned)g.IC / 16u * 1024u;
+    // ---- weights: packed [channel block of 32][reduction step of 16][lane][8], or [channel][reduction] ----
+    const unsigned wrow = (unsigned)(tn * CB + cg) * a.wo.block + (unsigned)kg * a.wo.step + (unsigned)(lane & 31) * a.wo.row + (unsigned)(lane >> 5) * a.wo.half;
+    const unsigned slicestep = KS * a.wo.step, tapstep = (unsigned)g.IC / 16u * a.wo.step;
     auto load_w = [&](unsigned row, unsigned cs, int tap) {
-        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrcW, row, cs * (KS * 1024u) + (unsigned)tap * tapstep, 0));
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrcW, row, cs * slicestep + (unsigned)tap * tapstep, 0));
     };
     bf16x8 w[NSET];
 #pragma unroll
@@ -468,7 +469,7 @@ const char* flat_kernel_name(const GemmGeom& g, int tile, bool unpool) {
 }
 
 int launch_flat(const GemmGeom& g, int tile, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out, hipStream_t st,
-                const bf16_t* mask, const uint8_t* unpool_am, float* colsum) {
+                const bf16_t* mask, const uint8_t* unpool_am, float* colsum, bool w_raw) {
     if (!flat_supported(g, tile) || (unpool_am && !flat_fuses_unpool(g))) return set_error(WAP_EINVAL, "internal: flat tiles not applicable");
     const FlatCfg c = flat_cfg(g, tile);
     FlatArgs fa = {};
@@ -493,7 +494,8 @@ int launch_flat(const GemmGeom& g, int tile, const bf16_t* A, const void* Wp, co
     fa.dOW = make_fastdiv((uint32_t)g.OW);
     fa.relu = relu ? 1 : 0;
     fa.a_bytes = (unsigned)((size_t)(g.M / (g.OH * g.OW)) * g.IH * g.IW * g.IC * 2 / (unpool_am ? 4 : 1));
-    fa.w_bytes = (unsigned)wreg_wt_bytes(g);
+    fa.wo = w_raw ? w_unpacked(g.Kred) : w_packed(g.Kred);
+    fa.w_bytes = w_raw ? (unsigned)((size_t)g.Ncols * g.Kred * 2) : (unsigned)wreg_wt_bytes(g);
     fa.m_fast = fa.w_bytes > fa.a_bytes;
 #define WAP_FLAT_TILE(FM, KS) \
     if (tile == FM * 10 + KS) return launch_flat_t<FM, KS>(fa, c.smem, st);

@@ -700,6 +700,18 @@ int classify_mode(const GemmGeom& g, bool b_tr) {
     return 1;
 }
 
+// A single forward call whose small tiles take the weights where they lie, without a packing launch (3 us, 10 of host time) in front.  An
+// operand load is then 32 pieces of 32 bytes instead of one run of 1 KB, so the line lies where the tiles read the weights
+// often enough to lose what the launch cost.  us, packed / as they are, by the weights' bytes times the tiles that read them: 7 MB (2 x 13 x 13,
+// 256 -> 256) 10.9 / 9.2, 14 MB (8 x 56 x 56, 64 -> 64) 21.1 / 18.9, 19 MB (4 x 13 x 13, 384 -> 256) 13.2 / 12.3, 22 MB (32 x 20 x 20, 96 -> 64)
+// 14.3 / 12.1, 28 MB (8 x 13 x 13, 192 -> 384) 10.6 / 11.4, 58 MB (56 x 56, 256 -> 256) 12.9 / 13.9, 115 MB (16 x 14 x 14, 512 -> 512) 25.5 / 40.2;
+// 5x5 27 x 27, 64 -> 192 12.2 / 12.9.
+bool reads_unpacked(const GemmGeom& g, bool b_tr, const GemmPlan& plan) {
+    if (b_tr || !(plan.cfg == 16 || (plan.cfg == 7 && plan.nsplit > 1)) || g.R != 3 || g.S != 3) return false;
+    const int pixels = plan.cfg == 16 ? 32 * (plan.tile / 10) : 64 * plan.tile;
+    return (double)((g.M + pixels - 1) / pixels) * g.Ncols * g.Kred * 2.0 <= 24e6;
+}
+
 // The phases of a strided data gradient, those with the most taps first (the longest work-groups start first); returns the
 // row tiles of bm pixels in all.
 int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
@@ -923,17 +935,19 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     ka.out = ka.partial ? ws : (void*)out;
     if (plan.cfg == 6 || plan.cfg == 7 || plan.cfg == 16) {
         const void* wp = prepacked;
+        const bool raw = !prepacked && reads_unpacked(g, b_tr, plan);
+        if (raw) wp = Bw;
         if (!wp) {
             int rc0 = launch_pack_weights(g, b_tr, Bw, ws, st);
             if (rc0 != WAP_OK) return rc0;
             wp = ws;
         }
         if (ev_packed) (void)hipEventRecord(ev_packed, st);
-        if (plan.cfg == 16) return launch_flat(g, plan.tile, A, wp, bias, relu, out, st, relu_mask, unpool_am, colsum);
+        if (plan.cfg == 16) return launch_flat(g, plan.tile, A, wp, bias, relu, out, st, relu_mask, unpool_am, colsum, raw);
         if (plan.cfg == 7 && plan.nsplit > 1) {
             float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + wreg_wt_bytes(g));
             int rc7 = launch_tile2d(g, A, wp, nullptr, false, nullptr, st, nullptr, nullptr, nullptr, unpool_am, nullptr, plan.tile,
-                                    plan.nsplit, part);
+                                    plan.nsplit, part, raw);
             if (rc7 != WAP_OK) return rc7;
             if (ev_mid) (void)hipEventRecord(ev_mid, st);
             return launch_reduce_bf16(part, plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st, relu_mask, colsum);

@@ -109,6 +109,13 @@ struct GemmPlan {
     size_t ws_bytes;
     int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own; cfg 16: flat_pick
 };
+// Where the weights of a forward-type product lie, in bytes: channel blocks of 32, a block's channels, reduction steps of 16 and the two
+// halves of a step.  Packed (pack_weights_kernel): an operand load of a wavefront is one run of 1 KB.
+struct WOrder {
+    unsigned block, row, step, half;
+};
+__host__ __device__ inline WOrder w_packed(int Kred) { return {(unsigned)Kred * 64u, 16u, 1024u, 512u}; }
+__host__ __device__ inline WOrder w_unpacked(int Kred) { return {(unsigned)Kred * 64u, (unsigned)Kred * 2u, 32u, 16u}; }
 constexpr int kTileSplit64 = 1, kTileSplit192 = 3;
 
 // Weight operand addressing.
@@ -285,7 +292,7 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
                   hipStream_t st, const bf16_t* mask = nullptr, bf16_t* pool_y = nullptr, uint8_t* pool_am = nullptr,
                   const uint8_t* unpool_am = nullptr,
                   float* colsum = nullptr,  // [tile2d_colsum_rows][Ncols] column sums of the stored (masked) output
-                  int tile = 0, int nsplit = 1, float* part = nullptr);  // split reduction: partial sums only
+                  int tile = 0, int nsplit = 1, float* part = nullptr, bool w_raw = false);  // split reduction: partial sums only
 int tile2d_colsum_rows(const GemmGeom& g);
 bool tile2d_fuses_pool(const GemmGeom& g);
 bool tile2d_fuses_unpool(const GemmGeom& g, int tile = 0);
@@ -298,7 +305,7 @@ bool flat_fuses_unpool(const GemmGeom& g);
 int flat_colsum_rows(const GemmGeom& g, int tile);
 const char* flat_kernel_name(const GemmGeom& g, int tile, bool unpool);
 int launch_flat(const GemmGeom& g, int tile, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out, hipStream_t st,
-                const bf16_t* mask, const uint8_t* unpool_am, float* colsum);
+                const bf16_t* mask, const uint8_t* unpool_am, float* colsum, bool w_raw);
 
 const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& plan, bool unpool = false);
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan);

@@ -136,6 +136,10 @@ CASES = [
     ("flat_42_w14_k136", (3, 14, 14, 64, 136, 3, 3, 1, 1), (142, -1, -1)),
     ("flat_42_exact_tiles", (4, 8, 16, 64, 128, 3, 3, 1, 1), (142, -1, -1)),
     ("flat_44_w28_even", (1, 28, 28, 128, 64, 3, 3, 1, 1), (144, -1, -1)),
+    # single forward calls on both sides of the line up to which small tiles take the weights unpacked (24 MB of reads)
+    ("split_unpacked_forward_w13", (2, 13, 13, 256, 256, 3, 3, 1, 1), (-1, -1, -1)),
+    ("split_packed_forward_w14", (2, 14, 14, 512, 512, 3, 3, 1, 1), (-1, -1, -1)),
+    ("flat_packed_forward_w28", (3, 28, 28, 256, 256, 3, 3, 1, 1), (-1, -1, -1)),
     ("flat_44_5x5_images", (3, 6, 7, 64, 64, 5, 5, 1, 2), (144, -1, -1)),
     # 11x11 at stride 4 by groups of 1, 2 and 4 output rows: rows that end in the middle of a vector, a last group cut short, wide
     # and no borders, an image lower than the filter, the narrowest and the widest map
