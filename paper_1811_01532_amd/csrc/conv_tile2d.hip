@@ -22,6 +22,7 @@
 // the pixel its argmax names, so the max-pool backward costs no pass over the full-size gradient.
 // Serves the "primary" convolution nodes of Section 3.2.2 (forward and backward halves of t_c, Eq. 1).
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 #include <utility>
 
@@ -115,7 +116,7 @@ __device__ __forceinline__ void each_tap(F& f, std::integer_sequence<int, T...>)
 template <int FN, int TW, int FM, int PG, bool UP, int ST>
 __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     constexpr bool FLAT = (TW == 0);
-    constexpr bool SPLIT = FLAT && FM < 7;  // may walk a part of the reduction (the 224-pixel tiles have no register left for it)
+    constexpr bool SPLIT = FLAT && FM < 4;  // may walk a part of the reduction (the 224-pixel tiles have no register left for it)
     constexpr int BM = 32 * FM * PG;
     constexpr int CG = 4 / PG;
     constexpr int TWD = FLAT ? 1 : TW;  // divisor that is never zero
@@ -617,6 +618,13 @@ int launch_tile2d_k(F kfn, std::atomic<bool>& attr_done, const TArgs& ta, size_t
     hipLaunchKernelGGL(kfn, dim3(ta.tiles_m * ta.tiles_n * ta.nsplit), dim3(NT), smem, st, ta);
     return check_launch("conv_tile2d");
 }
+// flat tiles of FM x 32 pixels x 128 channels, picked to divide a layer evenly (3x3 only)
+template <int FM>
+int launch_tile2d_fill(const TArgs& ta, size_t smem, hipStream_t st) {
+    static std::atomic<bool> done{false}, doneu{false};
+    return ta.up_am ? launch_tile2d_k(conv_tile2d_kernel<1, 0, FM, 1, true, true>, doneu, ta, smem, st)
+                    : launch_tile2d_k(conv_tile2d_kernel<1, 0, FM, 1, false, true>, done, ta, smem, st);
+}
 // straight-line 3x3 slices; 5x5 ones on the flat 192 x 64 tiles (the tilings such layers get); else the tap loop
 constexpr int tile2d_st(int tw, int pg, bool up, int R, int S) {
     return R == 3 && S == 3 ? 3 : R == 5 && S == 5 && tw == 0 && pg == 2 && !up ? 5 : 0;
@@ -644,9 +652,14 @@ struct TileCfg {
                               // 192 pixels x 64 channels (2 x 3 fragments) for thin outputs on maps no 2-D tile divides
     int RWB, buf_bytes;       // LDS layout: byte stride of a patch row, bytes of one patch buffer
     size_t smem;              // dynamic LDS of the launch: two patch buffers, or the staged output tile if larger
-    int fm;                   // variant 2: 32-pixel fragments per wavefront (7 or 2: tiles of 224 or 64 pixels)
+    int fm;                   // variant 2: 32-pixel fragments per wavefront (2 or 4 .. 7: tiles of 64 or 128 .. 224 pixels)
 };
 int tile_pixels(const TileCfg& c) { return c.variant == 3 ? 192 : c.variant == 2 ? 32 * c.fm : c.variant == 1 ? 224 : 256; }
+// Tiles that begin at the same pixel of an image are alike: the first pixel behind all that differ.
+long flat_period(const GemmGeom& g, int bm) {
+    const long OHW = (long)g.OH * g.OW;
+    return std::min((long)g.M, OHW / std::gcd(OHW, (long)bm) * bm);
+}
 // most patch pixels (rows of OW + S - 1) any bm-pixel raster-order tile of this geometry loads
 int max_flat_patch(const GemmGeom& g, int bm) {
     const int PH = g.OH + g.R - 1, PW = g.OW + g.S - 1;
@@ -657,7 +670,8 @@ int max_flat_patch(const GemmGeom& g, int bm) {
         return n * PH * PW + oh * PW + ow;
     };
     long worst = 0;
-    for (long m0 = 0; m0 < g.M; m0 += bm) {
+    const long end = flat_period(g, bm);
+    for (long m0 = 0; m0 < end; m0 += bm) {
         long ml = (m0 + bm <= g.M ? m0 + bm : g.M) - 1;
         long len = pflat(ml) + (long)(g.R - 1) * PW + (g.S - 1) + 1 - pflat(m0);
         if (len > worst) worst = len;
@@ -674,7 +688,8 @@ long max_flat_bytes(const GemmGeom& g, int bm, int rwb) {
         return (n * PH + oh) * rwb + ow * PITCH;
     };
     long worst = 0;
-    for (long m0 = 0; m0 < g.M; m0 += bm) {
+    const long end = flat_period(g, bm);
+    for (long m0 = 0; m0 < end; m0 += bm) {
         long ml = (m0 + bm <= g.M ? m0 + bm : g.M) - 1;
         long len = lbyte(ml) + (long)(g.R - 1) * rwb + (long)(g.S - 1) * PITCH + PITCH - lbyte(m0);
         if (len > worst) worst = len;
@@ -739,8 +754,17 @@ TileCfg split_cfg(const GemmGeom& g, int tile) {
         c.fn = 0;
     return c;
 }
+// Flat tiles of 128 channels and 32 * fm pixels for a whole reduction, 3x3 filters.
+TileCfg fill_cfg(const GemmGeom& g, int fm) {
+    TileCfg c = {1, 0, 0, 2, 0, 0, 0, fm};
+    if (fm < 4 || fm > 6 || g.R != 3 || g.S != 3 || (g.Ncols % 128) != 0 || max_flat_patch(g, 32 * fm) > MAX_PATCH_FLAT || !lds_layout(g, &c) ||
+        c.smem > LDS_CAP / 2)
+        c.fn = 0;
+    return c;
+}
 // Tile shape for this geometry (width must divide the map, patch must fit), fn = 0 if none.
 TileCfg tile_cfg(const GemmGeom& g, int tile = 0) {
+    if (tile >= kTileFill) return fill_cfg(g, tile - kTileFill);
     if (tile) return split_cfg(g, tile);
     TileCfg none = {0, 0, 0, 0, 0, 0, 0, 0};
     TileCfg c = none;
@@ -857,6 +881,31 @@ int tile2d_split(const GemmGeom& g, bool generic, int* tile) {
     return tile2d_supported(g, *tile) ? (int)s : 1;
 }
 
+// The flat tile that divides a layer's pixels most evenly (0: the shape's own).  Two work-groups share a CU, so what counts is how many
+// tiles the fullest CU gets, and every tile costs a start: 224 pixels leave most CUs half the work of the others where they make a
+// few more tiles than CUs.  A 3x3 tile of 512 input channels takes a CU about 6 us for every 32 pixels and 4 beside, alone on its CU 5
+// more (64-pixel tiles 18 in all).  us, packing included, 224 pixels / these: 22 x 28 x 28, 512 -> 512 89.7 / 75.0 (160), 512 -> 256 55.8
+// (64 pixels) / 42.9, 256 -> 512 50.8 / 43.1, 45 x 14 x 14, 512 -> 512 58.1 (64) / 45.2, 11 x 28 x 28 58.4 (64) / 44.4, 45 x 27 x 27, 256 ->
+// 256 50.9 / 42.1, 90 x 27 x 27 75.5 / 69.0 (192).  With less than 8 % to gain nothing is left of it (64 x 28 x 28, 512 -> 512 188 /
+// 186: the clock under matrix load); the 8 x 28 strips of 56-pixel maps lose to the flat tiles whose patch still fits (128 pixels).
+int tile2d_fill(const GemmGeom& g) {
+    if (g.R != 3 || g.S != 3 || (g.Ncols % 128) != 0 || tile64_width(g)) return 0;
+    const TileCfg own = tile_cfg(g);
+    if (own.fn == 0 || own.variant != 2) return 0;
+    auto cost = [&](int fm) {
+        const long groups = (long)((g.M + 32 * fm - 1) / (32 * fm)) * (g.Ncols / 128), n = (groups + kNumCU - 1) / kNumCU;
+        return (double)n * (fm == 2 ? 18 : 6 * fm + 4) + (n == 1 ? 5 : 0);
+    };
+    int best = 0;
+    double least = 0.92 * cost(own.fm);
+    for (int fm : {6, 5, 4})
+        if (cost(fm) < least && fill_cfg(g, fm).fn) {
+            best = fm;
+            least = cost(fm);
+        }
+    return best ? kTileFill + best : 0;
+}
+
 const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
     if (!tile && tile64_width(g)) return tile64_kernel_name(g, unpool);
     const TileCfg c = tile_cfg(g, tile);
@@ -870,7 +919,9 @@ const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
     static const char* n22[2][2] = {{"conv_tile2d_kernel<1,0,2,1,false,false>", "conv_tile2d_kernel<1,0,2,1,false,true>"},
                                     {"conv_tile2d_kernel<1,0,2,1,true,false>", "conv_tile2d_kernel<1,0,2,1,true,true>"}};
     if (c.variant == 1) return n1[u][t9];
-    if (c.variant == 2) return c.fm == 7 ? n2[u][t9] : n22[u][t9];
+    static const char* nf[2][3] = {{"conv_tile2d_kernel<1,0,4,1,false,true>", "conv_tile2d_kernel<1,0,5,1,false,true>", "conv_tile2d_kernel<1,0,6,1,false,true>"},
+                                   {"conv_tile2d_kernel<1,0,4,1,true,true>", "conv_tile2d_kernel<1,0,5,1,true,true>", "conv_tile2d_kernel<1,0,6,1,true,true>"}};
+    if (c.variant == 2) return c.fm == 7 ? n2[u][t9] : c.fm == 2 ? n22[u][t9] : nf[u][c.fm - 4];
     if (c.variant == 3 && tile2d_st(0, 2, unpool, g.R, g.S) == 5) return "conv_tile2d_5x5_kernel<1,0,3,2>";
     if (c.variant == 3) return n3[u][t9];
     static const char* names[2][2][3] = {
@@ -892,9 +943,9 @@ bool tile2d_fuses_unpool(const GemmGeom& g, int tile) {
 }
 
 // partial rows (pixel tiles) the epilogue's column sums come in: [tile2d_colsum_rows][Ncols]
-int tile2d_colsum_rows(const GemmGeom& g) {
-    if (const int tw = tile64_width(g)) return (g.M / (g.OH * g.OW)) * (g.OW / tw) * (g.OH / (256 / tw));
-    const TileCfg c = tile_cfg(g);
+int tile2d_colsum_rows(const GemmGeom& g, int tile) {
+    if (const int tw = tile ? 0 : tile64_width(g)) return (g.M / (g.OH * g.OW)) * (g.OW / tw) * (g.OH / (256 / tw));
+    const TileCfg c = tile_cfg(g, tile);
     if (c.variant >= 2) return (g.M + tile_pixels(c) - 1) / tile_pixels(c);
     return (g.M / (g.OH * g.OW)) * (g.OW / c.tw) * (g.OH / c.th);
 }
@@ -920,10 +971,10 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
     if (unpool_am && !tile2d_fuses_unpool(g, tile))
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this shape");
     ta.up_am = unpool_am;
-    if ((pool_y || pool_am) && !(pool_y && pool_am && tile2d_fuses_pool(g)))
+    if ((pool_y || pool_am) && !(pool_y && pool_am && !tile && tile2d_fuses_pool(g)))
         return set_error(WAP_EINVAL, "internal: fused pooling not available for this shape");
     if (!out && !pool_y && !part) return set_error(WAP_EINVAL, "internal: no output");
-    if ((tile != 0) != (part != nullptr)) return set_error(WAP_EINVAL, "internal: split tiles write partial sums, others do not");
+    if ((tile != 0 && tile < kTileFill) != (part != nullptr)) return set_error(WAP_EINVAL, "internal: split tiles write partial sums, others do not");
     ta.pool_y = pool_y;
     ta.pool_am = pool_am;
     if (!tile2d_supported(g, tile)) return set_error(WAP_EINVAL, "internal: 2-D tile kernel not applicable");
@@ -974,6 +1025,9 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
     const size_t smem = c.smem;
     if (c.variant == 1) return launch_tile2d_t<1, 28, 7, 1>(ta, smem, st);
     if (c.variant == 2 && c.fm == 7) return launch_tile2d_t<1, 0, 7, 1>(ta, smem, st);
+    if (c.variant == 2 && c.fm == 4) return launch_tile2d_fill<4>(ta, smem, st);
+    if (c.variant == 2 && c.fm == 5) return launch_tile2d_fill<5>(ta, smem, st);
+    if (c.variant == 2 && c.fm == 6) return launch_tile2d_fill<6>(ta, smem, st);
     if (c.variant == 2) return launch_tile2d_t<1, 0, 2, 1>(ta, smem, st);
     if (c.variant == 3) return launch_tile2d_t<1, 0, 3, 2>(ta, smem, st);
     const int TW = c.tw;  // 2-D tiles: two channel blocks per wavefront, 128-channel tiles

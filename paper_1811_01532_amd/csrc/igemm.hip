@@ -875,7 +875,14 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
             p.ws_bytes = need;
         }
     }
-    if (g_force_fwd_cfg >= 100 && flat_supported(g, g_force_fwd_cfg - 100)) {
+    // (a launch that pools in its epilogue keeps the 224-pixel tiles, which hold whole row pairs)
+    if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && cfg == 7 && nsplit == 1) p.tile = tile2d_fill(g);
+    if (g_force_fwd_cfg >= 200 && tile2d_supported(g, kTileFill + g_force_fwd_cfg - 200)) {
+        cfg = 7;
+        p.tile = kTileFill + g_force_fwd_cfg - 200;
+        nsplit = 1;
+        p.ws_bytes = wreg_wt_bytes(g);
+    } else if (g_force_fwd_cfg >= 100 && g_force_fwd_cfg < 200 && flat_supported(g, g_force_fwd_cfg - 100)) {
         cfg = 16;
         p.tile = g_force_fwd_cfg - 100;
         nsplit = 1;
@@ -955,7 +962,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
             return launch_reduce_bf16(part, plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st, relu_mask, colsum);
         }
         return plan.cfg == 6 ? launch_patch(g, A, wp, bias, relu, out, st, relu_mask)
-                             : launch_tile2d(g, A, wp, bias, relu, out, st, relu_mask, pool_y, pool_am, unpool_am, colsum);
+                             : launch_tile2d(g, A, wp, bias, relu, out, st, relu_mask, pool_y, pool_am, unpool_am, colsum, pool_y ? 0 : plan.tile);
     }
     if (plan.cfg == 5) {
         // the (small) weight tensor is first repacked into MFMA fragment order (taps flipped and
@@ -1043,7 +1050,7 @@ bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) {
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return reduce_bf16_colsum_rows(g.M, g.Ncols);
     if (plan.cfg == 16) return flat_colsum_rows(g, plan.tile);
-    return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g) : 0;
+    return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g, plan.tile) : 0;
 }
 bool fwd_like_fuses_mask(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return (g.Ncols % 4) == 0;  // by the kernel that adds up the splits

@@ -116,7 +116,7 @@ struct WOrder {
 };
 __host__ __device__ inline WOrder w_packed(int Kred) { return {(unsigned)Kred * 64u, 16u, 1024u, 512u}; }
 __host__ __device__ inline WOrder w_unpacked(int Kred) { return {(unsigned)Kred * 64u, (unsigned)Kred * 2u, 32u, 16u}; }
-constexpr int kTileSplit64 = 1, kTileSplit192 = 3;
+constexpr int kTileSplit64 = 1, kTileSplit192 = 3, kTileFill = 10;  // kTileFill + fm: a whole reduction on flat tiles of 32 * fm pixels
 
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred
@@ -287,13 +287,14 @@ int launch_tile64(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
 int tile2d_supported(const GemmGeom& g, int tile = 0);
 bool tile2d_preferred(const GemmGeom& g);
 int tile2d_split(const GemmGeom& g, bool generic, int* tile);
+int tile2d_fill(const GemmGeom& g);
 const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile = 0);
 int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out,
                   hipStream_t st, const bf16_t* mask = nullptr, bf16_t* pool_y = nullptr, uint8_t* pool_am = nullptr,
                   const uint8_t* unpool_am = nullptr,
                   float* colsum = nullptr,  // [tile2d_colsum_rows][Ncols] column sums of the stored (masked) output
                   int tile = 0, int nsplit = 1, float* part = nullptr, bool w_raw = false);  // split reduction: partial sums only
-int tile2d_colsum_rows(const GemmGeom& g);
+int tile2d_colsum_rows(const GemmGeom& g, int tile = 0);
 bool tile2d_fuses_pool(const GemmGeom& g);
 bool tile2d_fuses_unpool(const GemmGeom& g, int tile = 0);
 

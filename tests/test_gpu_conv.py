@@ -149,6 +149,16 @@ CASES = [
     ("c3_groups_2_w226", (20, 107, 226, 3, 64, 11, 11, 4, 2), (-1, -1, -1)),
     ("c3_groups_4_k32_cut_short", (110, 55, 136, 3, 32, 11, 11, 4, 2), (-1, -1, -1)),
     ("c3_groups_4_k64", (130, 51, 138, 3, 64, 11, 11, 4, (1, 4)), (-1, -1, -1)),
+    # flat 128-channel tiles of 128, 160 and 192 pixels: under one tile, exact tiles, runs over rows and images with a ragged last
+    # tile, several column tiles, pad 0, even maps (pooled dy; the pooling forward call goes to other tiles)
+    ("fill_4_exact_tiles", (2, 8, 16, 128, 128, 3, 3, 1, 1), (204, -1, -1)),
+    ("fill_4_w13_images", (3, 13, 13, 128, 256, 3, 3, 1, 1), (204, -1, -1)),
+    ("fill_5_under_one_tile", (1, 8, 9, 128, 128, 3, 3, 1, 1), (205, -1, -1)),
+    ("fill_5_w28_even", (1, 28, 28, 128, 256, 3, 3, 1, 1), (205, -1, -1)),
+    ("fill_5_w14_images_pad0", (5, 14, 14, 128, 128, 3, 3, 1, 0), (205, -1, -1)),
+    ("fill_6_7x7_images", (9, 7, 7, 256, 128, 3, 3, 1, 1), (206, -1, -1)),
+    ("fill_6_w27", (2, 27, 27, 128, 128, 3, 3, 1, 1), (206, -1, -1)),
+    ("fill_5_picked_w14", (45, 14, 14, 128, 512, 3, 3, 1, 1), (-1, -1, -1)),
 ]
 
 
