@@ -174,6 +174,7 @@ constexpr int kMaxGroupTiles = 48;
 // 478 against 421 on the others and 456 as a captured one-stream graph, VGG-16 at 8 1587 / 1507 / 1578.)
 constexpr double kForkFlops = 1.2e12;
 constexpr int kForkRows = 64;
+constexpr double kLateForkFlops = 0.9e12;  // up to here they begin behind the small maps' data gradients (below)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -796,7 +797,12 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (j == p->ops.size()) continue;  // first layer: no data gradient
         std::rotate(p->ops.begin() + i, p->ops.begin() + i + 1, p->ops.begin() + j + 1);
     }
-    // ---- the operations to run beside: behind the last of the fully-connected data gradients, in one run ----
+    // ---- the operations to run beside: behind the data gradients of the small maps, in one run ----
+    // They take what the memory gives, and small layers' data gradients, which wait for their loads, then take two to four times as long;
+    // what follows (the larger maps, the weight gradients) waits less.  us, right behind the fully-connected data gradients / behind
+    // the data gradients of maps up to 28 x 28 (layer by layer in between it falls and rises): AlexNet-style at 4 / 8 / 16 / 32 / 64
+    // images 374 / 367, 404 / 389, 453 / 433, 526 / 522, 669 / 663, VGG-16 at 3 / 8 1056 / 1033, 1422 / 1403; with more work there is
+    // too little left behind them (at 12, 1.1 TFLOP, 1786 / 1818).
     size_t ws2_need = 0;
     if (forks) {
         std::vector<Op> side;
@@ -808,6 +814,9 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         }
         size_t at = p->ops.size();
         while (at > 0 && p->ops[at - 1].kind != OP_FC_DX) --at;
+        if (flops <= kLateForkFlops)
+            for (size_t k = at; k < p->ops.size(); ++k)
+                if (p->ops[k].kind == OP_CONV_DGRAD && p->ops[k].gg.OH <= 28 && p->ops[k].gg.OW <= 28) at = k + 1;
         for (Op& op : side) {
             op.beside = true;
             if (op.wp.ws_bytes > ws2_need) ws2_need = op.wp.ws_bytes;
