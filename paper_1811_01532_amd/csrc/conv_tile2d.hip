@@ -37,6 +37,7 @@ constexpr int PITCH = 80;            // LDS bytes per padded pixel: 32 channels 
 constexpr int VPP = BK / 8;          // 16-byte vectors per patch pixel
 constexpr int MAX_PATCH = 352;       // padded pixels per 2-D tile patch (>= (tile h + R - 1) * (tile w + S - 1))
 constexpr int MAX_PATCH_FLAT = 384;  // the same for flat (raster-order) 224-pixel tiles, which may straddle rows and images
+constexpr int MAX_PATCH_FILL = 448;       // flat tiles of 160 and 192 pixels (56-wide maps, across images)
 constexpr int MAX_PATCH_FLAT64 = 512;  // flat 192-pixel x 64-channel tiles (5x5 filters on 27-wide maps, across images)
 constexpr size_t LDS_CAP = 160 * 1024;
 
@@ -122,7 +123,7 @@ __device__ __forceinline__ void conv_tile2d_body(const TArgs& a) {
     constexpr int TWD = FLAT ? 1 : TW;  // divisor that is never zero
     constexpr int TH = BM / TWD;
     static_assert(FLAT || TH * TW == BM, "tile width must divide the tile");
-    constexpr int PATCH_ROWS = FLAT ? (PG == 2 ? MAX_PATCH_FLAT64 : MAX_PATCH_FLAT) : MAX_PATCH;  // most patch pixels
+    constexpr int PATCH_ROWS = FLAT ? (PG == 2 ? MAX_PATCH_FLAT64 : FM == 5 || FM == 6 ? MAX_PATCH_FILL : MAX_PATCH_FLAT) : MAX_PATCH;  // most patch pixels
     constexpr int PV = (PATCH_ROWS * VPP + NT - 1) / NT;  // 16-byte patch vectors per thread
     extern __shared__ __align__(16) unsigned char smem[];
     const GemmGeom& g = a.g;
@@ -754,17 +755,20 @@ TileCfg split_cfg(const GemmGeom& g, int tile) {
         c.fn = 0;
     return c;
 }
-// Flat tiles of 128 channels and 32 * fm pixels for a whole reduction, 3x3 filters.
-TileCfg fill_cfg(const GemmGeom& g, int fm) {
+// Tiles of 128 channels for a whole reduction of a 3x3 filter: flat ones of 32 * fm pixels, or (kTileStrips) the 8 x 28 strips.
+TileCfg fill_cfg(const GemmGeom& g, int tile) {
+    const bool strips = tile == kTileStrips;
+    const int fm = tile - kTileFill;
     TileCfg c = {1, 0, 0, 2, 0, 0, 0, fm};
-    if (fm < 4 || fm > 6 || g.R != 3 || g.S != 3 || (g.Ncols % 128) != 0 || max_flat_patch(g, 32 * fm) > MAX_PATCH_FLAT || !lds_layout(g, &c) ||
-        c.smem > LDS_CAP / 2)
-        c.fn = 0;
+    if (strips) c = {1, 28, 8, 1, 0, 0, 0, 0};
+    const bool fits = strips ? (g.OW % 28) == 0 && (g.OH % 8) == 0
+                             : fm >= 4 && fm <= 6 && max_flat_patch(g, 32 * fm) <= (fm == 4 ? MAX_PATCH_FLAT : MAX_PATCH_FILL);
+    if (!fits || g.R != 3 || g.S != 3 || (g.Ncols % 128) != 0 || !lds_layout(g, &c) || c.smem > LDS_CAP / 2) c.fn = 0;
     return c;
 }
 // Tile shape for this geometry (width must divide the map, patch must fit), fn = 0 if none.
 TileCfg tile_cfg(const GemmGeom& g, int tile = 0) {
-    if (tile >= kTileFill) return fill_cfg(g, tile - kTileFill);
+    if (tile >= kTileFill) return fill_cfg(g, tile);
     if (tile) return split_cfg(g, tile);
     TileCfg none = {0, 0, 0, 0, 0, 0, 0, 0};
     TileCfg c = none;
@@ -881,29 +885,37 @@ int tile2d_split(const GemmGeom& g, bool generic, int* tile) {
     return tile2d_supported(g, *tile) ? (int)s : 1;
 }
 
-// The flat tile that divides a layer's pixels most evenly (0: the shape's own).  Two work-groups share a CU, so what counts is how many
+// The tile that divides a layer's pixels most evenly (0: the shape's own).  Two work-groups share a CU, so what counts is how many
 // tiles the fullest CU gets, and every tile costs a start: 224 pixels leave most CUs half the work of the others where they make a
 // few more tiles than CUs.  A 3x3 tile of 512 input channels takes a CU about 6 us for every 32 pixels and 4 beside, alone on its CU 5
 // more (64-pixel tiles 18 in all).  us, packing included, 224 pixels / these: 22 x 28 x 28, 512 -> 512 89.7 / 75.0 (160), 512 -> 256 55.8
 // (64 pixels) / 42.9, 256 -> 512 50.8 / 43.1, 45 x 14 x 14, 512 -> 512 58.1 (64) / 45.2, 11 x 28 x 28 58.4 (64) / 44.4, 45 x 27 x 27, 256 ->
-// 256 50.9 / 42.1, 90 x 27 x 27 75.5 / 69.0 (192).  With less than 8 % to gain nothing is left of it (64 x 28 x 28, 512 -> 512 188 /
-// 186: the clock under matrix load); the 8 x 28 strips of 56-pixel maps lose to the flat tiles whose patch still fits (128 pixels).
+// 256 50.9 / 42.1, 90 x 27 x 27 75.5 / 69.0 (192); strips of 56 x 56 maps / these, 256 -> 256 at 10 / 11 / 14 / 19 / 22 images 50.4 / 39.5
+// (128), 51.4 / 44.1 (160), 54.8 / 52.1 (192), 76.6 / 66.0 (160), 78.2 / 74.5 (192).  With less than 8 % to gain nothing is left of
+// it (64 x 28 x 28, 512 -> 512 188 / 186, 32 x 56 x 56, 256 -> 256 103.7 / 103.2: the clock under matrix load).
+// 256-pixel tiles: the 224-pixel strips where the fullest CU gets no more of them (112 x 112, 128 -> 128 at 3 / 6 / 8 / 11 / 16 / 22 / 32
+// images 22.1 / 21.0, 34.6 / 32.2, 35.7 / 34.5, 49.4 / 46.7, 64.0 / 60.1, 78.2 / 75.6, 106.6 / 103.4; one more tile at 10 39.5 / 45.5, 64 201 / 203).
 int tile2d_fill(const GemmGeom& g) {
     if (g.R != 3 || g.S != 3 || (g.Ncols % 128) != 0 || tile64_width(g)) return 0;
     const TileCfg own = tile_cfg(g);
-    if (own.fn == 0 || own.variant != 2) return 0;
+    if (own.fn == 0 || own.variant > 2) return 0;
+    auto fullest = [&](int pixels) {
+        const long groups = (long)((g.M + pixels - 1) / pixels) * (g.Ncols / 128);
+        return (groups + kNumCU - 1) / kNumCU;
+    };
+    if (own.variant == 0) return fullest(224) == fullest(256) && fill_cfg(g, kTileStrips).fn ? kTileStrips : 0;
     auto cost = [&](int fm) {
-        const long groups = (long)((g.M + 32 * fm - 1) / (32 * fm)) * (g.Ncols / 128), n = (groups + kNumCU - 1) / kNumCU;
+        const long n = fullest(32 * fm);
         return (double)n * (fm == 2 ? 18 : 6 * fm + 4) + (n == 1 ? 5 : 0);
     };
     int best = 0;
-    double least = 0.92 * cost(own.fm);
+    double least = 0.92 * cost(own.variant == 1 ? 7 : own.fm);
     for (int fm : {6, 5, 4})
-        if (cost(fm) < least && fill_cfg(g, fm).fn) {
-            best = fm;
+        if (cost(fm) < least && fill_cfg(g, kTileFill + fm).fn) {
+            best = kTileFill + fm;
             least = cost(fm);
         }
-    return best ? kTileFill + best : 0;
+    return best;
 }
 
 const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile) {
@@ -971,7 +983,7 @@ int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const floa
     if (unpool_am && !tile2d_fuses_unpool(g, tile))
         return set_error(WAP_EINVAL, "internal: fused max-pool backward not available for this shape");
     ta.up_am = unpool_am;
-    if ((pool_y || pool_am) && !(pool_y && pool_am && !tile && tile2d_fuses_pool(g)))
+    if ((pool_y || pool_am) && !(pool_y && pool_am && (!tile || tile == kTileStrips) && tile2d_fuses_pool(g)))
         return set_error(WAP_EINVAL, "internal: fused pooling not available for this shape");
     if (!out && !pool_y && !part) return set_error(WAP_EINVAL, "internal: no output");
     if ((tile != 0 && tile < kTileFill) != (part != nullptr)) return set_error(WAP_EINVAL, "internal: split tiles write partial sums, others do not");

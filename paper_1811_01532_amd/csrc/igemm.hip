@@ -875,7 +875,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
             p.ws_bytes = need;
         }
     }
-    // (a launch that pools in its epilogue keeps the 224-pixel tiles, which hold whole row pairs)
+    // (a launch that pools in its epilogue keeps the tiles that hold whole row pairs)
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && cfg == 7 && nsplit == 1) p.tile = tile2d_fill(g);
     if (g_force_fwd_cfg >= 200 && tile2d_supported(g, kTileFill + g_force_fwd_cfg - 200)) {
         cfg = 7;
@@ -962,7 +962,8 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
             return launch_reduce_bf16(part, plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias, relu, out, st, relu_mask, colsum);
         }
         return plan.cfg == 6 ? launch_patch(g, A, wp, bias, relu, out, st, relu_mask)
-                             : launch_tile2d(g, A, wp, bias, relu, out, st, relu_mask, pool_y, pool_am, unpool_am, colsum, pool_y ? 0 : plan.tile);
+                             : launch_tile2d(g, A, wp, bias, relu, out, st, relu_mask, pool_y, pool_am, unpool_am, colsum,
+                                             pool_y && plan.tile != kTileStrips ? 0 : plan.tile);
     }
     if (plan.cfg == 5) {
         // the (small) weight tensor is first repacked into MFMA fragment order (taps flipped and

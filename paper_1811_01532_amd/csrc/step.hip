@@ -581,7 +581,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (convs[i].pool_win == 2 && convs[i].pool_st == 2 && !keep && fwd_like_fuses_pool(g, p->ops.back().gp)) {
             Op& cf = p->ops.back();
             cf.has_pool = true;
-            cf.gp.tile = 0;  // the tiles that pool
+            if (cf.gp.tile != kTileStrips) cf.gp.tile = 0;  // the tiles that pool
             cf.kernel = fwd_like_kernel_name(g, false, cf.gp);
             cf.t3 = pool_y[i];
             cf.t5 = pool_am[i];

@@ -116,7 +116,7 @@ struct WOrder {
 };
 __host__ __device__ inline WOrder w_packed(int Kred) { return {(unsigned)Kred * 64u, 16u, 1024u, 512u}; }
 __host__ __device__ inline WOrder w_unpacked(int Kred) { return {(unsigned)Kred * 64u, (unsigned)Kred * 2u, 32u, 16u}; }
-constexpr int kTileSplit64 = 1, kTileSplit192 = 3, kTileFill = 10;  // kTileFill + fm: a whole reduction on flat tiles of 32 * fm pixels
+constexpr int kTileSplit64 = 1, kTileSplit192 = 3, kTileFill = 10, kTileStrips = 13;  // kTileFill + 4 .. 6: flat tiles of 32 pixels times that
 
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred

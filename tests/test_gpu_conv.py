@@ -158,6 +158,10 @@ CASES = [
     ("fill_5_w14_images_pad0", (5, 14, 14, 128, 128, 3, 3, 1, 0), (205, -1, -1)),
     ("fill_6_7x7_images", (9, 7, 7, 256, 128, 3, 3, 1, 1), (206, -1, -1)),
     ("fill_6_w27", (2, 27, 27, 128, 128, 3, 3, 1, 1), (206, -1, -1)),
+    ("fill_strips_112", (1, 112, 112, 128, 128, 3, 3, 1, 1), (203, -1, -1)),
+    ("fill_strips_even_w28", (2, 8, 28, 128, 256, 3, 3, 1, 1), (203, -1, -1)),
+    ("fill_5_w56_images", (2, 20, 56, 128, 128, 3, 3, 1, 1), (205, -1, -1)),
+    ("fill_6_w56_images", (2, 28, 56, 128, 128, 3, 3, 1, 1), (206, -1, -1)),
     ("fill_5_picked_w14", (45, 14, 14, 128, 512, 3, 3, 1, 1), (-1, -1, -1)),
 ]
 
