@@ -9,7 +9,7 @@
 //     divides it over work-groups: fp32 partial sums through memory and a second launch of 5 .. 7 us.
 //   * Every load of the next steps is issued before the products of the present ones, in two register sets.
 //   * Row lengths that are no multiple of 8 are read with unaligned loads, the last vector moved back to end with the row.
-// Forward (up to 16 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt), 16 wavefronts.
+// Forward (up to 16 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt) or fewer, 16 wavefronts.
 // Data gradient: the reduction runs over the rows of Wt.  A lane loads CPL neighbouring columns of eight rows and turns
 // the 8 x CPL block around in registers (byte permutes); a work-group owns 16 * CPL columns, 8 wavefronts.
 #include "wap_internal.h"
@@ -28,6 +28,7 @@ struct FcArgs {
     void* res;           // bf16 result, or fp32 partial sums [split][B][out]
     int B, in, out;
     int relu, partial, steps_per_split;
+    int feat;            // forward: output features of a work-group
 };
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -56,8 +57,8 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
     __shared__ f32x4_t red[FW_WAVES][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = lane & 15, kg = lane >> 4;
-    const int o0 = blockIdx.x * 16;
-    const int orows = a.out - o0 < 16 ? a.out - o0 : 16;
+    const int o0 = blockIdx.x * a.feat;
+    const int orows = a.out - o0 < a.feat ? a.out - o0 : a.feat;
     const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t*>(a.w + (size_t)o0 * a.in), 0, orows * a.in * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rX =
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
     const size_t e0 = (size_t)row * a.out + o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        if (o + e >= a.out) continue;
+        if (o + e >= o0 + orows) continue;
         if (a.partial) {
             reinterpret_cast<float*>(a.res)[(size_t)blockIdx.y * a.B * a.out + e0 + e] = s[e];
         } else {
@@ -324,21 +325,33 @@ bool fc_dx_supported(const GemmGeom& g) {
     return g.IC <= 8192 && (g.Ncols >= 12288 || (g.M <= 16 && g.Ncols <= 512));
 }
 
-// Where the output features alone would leave most CUs without work, the reduction is also divided over work-groups, as
-// long as each still streams 128 KB of Wt (below that the launch that adds the parts costs more than it saves).
-int fc_fwd_nsplit(const GemmGeom& g) {
-    const int groups = (g.Ncols + 15) / 16;
-    const double bytes = 32.0 * g.IC;
-    int n = kNumCU / groups;
-    if (n > (int)(bytes / (128 * 1024))) n = (int)(bytes / (128 * 1024));
-    return n < 1 ? 1 : n;
+// How many output features a work-group owns (16, 8 or 4: the rows of the MFMA beyond them are zeros that no load is made for) and over
+// how many work-groups the reduction is divided as well.  A work-group is bound by its CU's way to the L2: it starts in 3.5 us, and
+// every 512-deep step of its 16 wavefronts takes 0.19 and 0.021 more for every row of Wt or of the batch (within 6 % of 13 shapes, 1 to
+// 16 rows); a launch that adds up partial sums takes 2.3 (3.5 where it cannot load vectors).  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
+// memory, 16 features and a division by 128 KB of Wt / this: 4096 -> 1000 7.7 / 9.1 / 10.3, 6.2 / 7.4 / 8.0; 9216 -> 512 10.4 / 11.8 / 13.3, 7.4 /
+// 8.0 / 8.7; 11264 -> 609 11.5 / 13.3 / 15.0, 8.5 / 9.2 / 9.9.
+void fc_fwd_plan(const GemmGeom& g, int* feat, int* nsplit) {
+    const int steps = (g.IC + 16 * 2 * FW_WAVES - 1) / (16 * 2 * FW_WAVES);
+    double least = 0;
+    for (int f : {16, 8, 4})
+        for (int n = 1; n <= 16 && n <= steps; ++n) {
+            const long groups = (long)((g.Ncols + f - 1) / f) * n;
+            if ((f < 16 || n > 1) && groups > kNumCU) break;
+            const double us = 3.5 * ((groups + kNumCU - 1) / kNumCU) + (steps + n - 1) / n * (0.19 + 0.021 * (f + g.M)) + (n > 1 ? (g.Ncols % 4 ? 3.5 : 2.3) + 0.05 * n : 0.0);
+            if (least == 0 || us < 0.97 * least) {
+                least = us;
+                *feat = f;
+                *nsplit = n;
+            }
+        }
 }
 
-int launch_fc_fwd(const GemmGeom& g, int nsplit, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
+int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st) {
-    FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0};
+    FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0, feat};
     a.steps_per_split = ((g.IC + 31) / 32 + nsplit - 1) / nsplit;
-    const dim3 grid((g.Ncols + 15) / 16, nsplit), block(64 * FW_WAVES);
+    const dim3 grid((g.Ncols + a.feat - 1) / a.feat, nsplit), block(64 * FW_WAVES);
     if ((g.IC % 8) == 0) hipLaunchKernelGGL(fc_fwd_kernel<true>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(fc_fwd_kernel<false>, grid, block, 0, st, a);
     return check_launch("fc_fwd");
@@ -361,7 +374,7 @@ int launch_dx(const FcArgs& a, hipStream_t st) {
 // 8 rows: 12.7 us), or the sums of more than 64 batch rows would not fit the registers, two columns per lane (10.7 us;
 // the other half of the line comes from the L2).  9216 columns: 15.2 us with four, 22.4 us with two.
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st) {
-    const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0};
+    const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0, 0};
     const bool wide = g.Ncols >= 96 * 64 && g.M <= 64, vec8 = (g.IC % 8) == 0;
     if (wide) return vec8 ? launch_dx<4, true>(a, st) : launch_dx<4, false>(a, st);
     return vec8 ? launch_dx<2, true>(a, st) : launch_dx<2, false>(a, st);

@@ -769,7 +769,11 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
     }
     if (g_force_fwd_cfg < 0 && (b_tr ? fc_dx_supported(g) : fc_fwd_supported(g))) {
         p.cfg = b_tr ? 11 : 10;
-        p.nsplit = b_tr ? 1 : g_force_nsplit >= 1 ? g_force_nsplit : fc_fwd_nsplit(g);
+        p.nsplit = 1;
+        if (!b_tr) {
+            fc_fwd_plan(g, &p.tile, &p.nsplit);
+            if (g_force_nsplit >= 1) p.nsplit = g_force_nsplit;
+        }
         const int steps = (g.IC + 31) / 32;
         if (p.nsplit > steps) p.nsplit = steps;
         p.nsplit = (steps + (steps + p.nsplit - 1) / p.nsplit - 1) / ((steps + p.nsplit - 1) / p.nsplit);  // none empty
@@ -913,7 +917,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
     if (plan.cfg == 15) return launch_conv_thin_fwd(g, A, Bw, bias, relu, out, st);
     if (plan.cfg == 9) return launch_dgrad_thin(g, A, Bw, out, st);
     if (plan.cfg == 10) {
-        int rc10 = launch_fc_fwd(g, plan.nsplit, A, Bw, bias, relu, plan.nsplit > 1 ? ws : (void*)out, st);
+        int rc10 = launch_fc_fwd(g, plan.nsplit, plan.tile, A, Bw, bias, relu, plan.nsplit > 1 ? ws : (void*)out, st);
         if (rc10 != WAP_OK || plan.nsplit == 1) return rc10;
         if (ev_mid) (void)hipEventRecord(ev_mid, st);
         return launch_reduce_bf16(reinterpret_cast<const float*>(ws), plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias,

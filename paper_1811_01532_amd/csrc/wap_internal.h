@@ -107,7 +107,7 @@ struct GemmPlan {
     int cfg;     // tile configuration id
     int nsplit;  // reduction splits (1 = direct epilogue)
     size_t ws_bytes;
-    int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own; cfg 16: flat_pick
+    int tile = 0;  // conv_tile2d.hip with a split reduction: which flat tiling (kTileSplit*), 0 = the shape's own; cfg 16: flat_pick; cfg 10: output features of a work-group
 };
 // Where the weights of a forward-type product lie, in bytes: channel blocks of 32, a block's channels, reduction steps of 16 and the two
 // halves of a step.  Packed (pack_weights_kernel): an operand load of a wavefront is one run of 1 KB.
@@ -238,9 +238,9 @@ int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16
 // fully-connected products with few rows as streams of the weights (fc.hip); geometries of geom_fc_fwd / geom_fc_dx
 bool fc_fwd_supported(const GemmGeom& g);
 bool fc_dx_supported(const GemmGeom& g);
-int fc_fwd_nsplit(const GemmGeom& g);
+void fc_fwd_plan(const GemmGeom& g, int* feat, int* nsplit);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
-int launch_fc_fwd(const GemmGeom& g, int nsplit, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
+int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
 

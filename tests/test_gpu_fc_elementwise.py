@@ -25,6 +25,13 @@ FC_CASES = [
     # that is not a multiple of four, where the update cannot ride on the gradient kernel
     ("b64_4096_4096_unsplit", 64, 4096, 4096, (-1, -1, -1)),
     ("b16_2050_2048_update_apart", 16, 2050, 2048, (-1, -1, -1)),
+    # forward streams of 4 and 8 output features a work-group and of 16 with the reduction divided: last work-groups that are not
+    # full, odd rows, a last split that is short
+    ("b1_stream_4_features", 1, 4096, 1001, (-1, -1, -1)),
+    ("b3_stream_4_features_odd_rows", 3, 2052, 333, (-1, -1, -1)),
+    ("b16_stream_8_features", 16, 4096, 2042, (-1, -1, -1)),
+    ("b16_stream_split", 16, 9224, 500, (-1, -1, -1)),
+    ("b9_stream_split_odd", 9, 11268, 37, (-1, -1, -1)),
 ]
 
 
