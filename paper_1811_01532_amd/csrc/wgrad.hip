@@ -12,6 +12,8 @@
 // turns each wavefront's blocks around in LDS so that 16 lanes store one 256-byte run of a row.  With
 // a parameter block the epilogue (or the reduction kernel of a split product) applies the SGD update
 // with the finished sums instead of storing them.
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -486,6 +488,14 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
     long maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
     int nsplit = (int)(want < maxs ? want : maxs);
+    // Few tiles and a short reduction fill few CUs with four steps a split: down to two, while the partial sums stay below 4.8 MB.  us, sums
+    // included, four / two: 5 x 24 x 31, 256 -> 64 at stride 2 13.1 / 10.5, 4 x 20 x 20, 160 -> 64 13.5 / 10.9, 8 x 14 x 14, 128 -> 64, 1x1,
+    // 12.9 / 8.8, 2 x 28 x 28, 96 -> 96 11.6 / 10.0; 4.9 and 7.4 MB (27 x 27, 64 -> 192, 5x5) 11.3 / 11.9 and 12.4, one step and 9 MB 12.5 for 10.9.  (What is
+    // whole with four stays whole: the launch that adds up two halves costs 3.)
+    if (nsplit >= 2 && nsplit < want) {
+        const long deeper = std::min({want, ((long)ktiles + 1) / 2, (long)(4.8e6 / (4.0 * g.K * Kred))});
+        if (deeper > nsplit) nsplit = (int)deeper;
+    }
     if (nsplit > 512) nsplit = 512;
     if (tiles >= kNumCU) nsplit = 1;
     if (g_force_nsplit >= 1) nsplit = g_force_nsplit < ktiles ? g_force_nsplit : ktiles;

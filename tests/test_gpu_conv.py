@@ -162,6 +162,8 @@ CASES = [
     ("fill_strips_even_w28", (2, 8, 28, 128, 256, 3, 3, 1, 1), (203, -1, -1)),
     ("fill_5_w56_images", (2, 20, 56, 128, 128, 3, 3, 1, 1), (205, -1, -1)),
     ("fill_6_w56_images", (2, 28, 56, 128, 128, 3, 3, 1, 1), (206, -1, -1)),
+    ("wgrad_two_steps_a_split_s2", (2, 24, 31, 96, 64, 3, 3, 2, 1), (-1, -1, -1)),
+    ("wgrad_two_steps_a_split_1x1", (8, 14, 14, 128, 64, 1, 1, 1, 0), (-1, -1, -1)),
     ("fill_5_picked_w14", (45, 14, 14, 128, 512, 3, 3, 1, 1), (-1, -1, -1)),
 ]
 
