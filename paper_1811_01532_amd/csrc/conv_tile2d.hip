@@ -6,7 +6,8 @@
 // R*S times; weights go from their packed copy straight into MFMA operand registers, one tap ahead.
 //   * tiles: 8 x 32 / 16 x 16 pixels of one image (4 wavefronts = 2 pixel halves x 2 channel halves, 64 or 128
 //     channels), 8 x 28 strips and flat runs of 224 raster-order pixels x 128 channels (4 channel wavefronts; the
-//     runs may straddle rows and images), flat 192 x 64 tiles for thin outputs on maps nothing else divides;
+//     runs may straddle rows and images; 64, 128, 160 or 192 pixels where those fill the CUs more evenly, tile2d_fill),
+//     flat 192 x 64 tiles for thin outputs on maps nothing else divides;
 //   * the patch is DOUBLE buffered: the global loads of slice c+1 are issued when the MFMA loop of slice c starts,
 //     sit in registers for half of the taps and are written to the other buffer in the middle of the loop.  One
 //     barrier per slice, placed in front of the last fragment read of the slice (which already targets the other
