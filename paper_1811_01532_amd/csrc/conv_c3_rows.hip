@@ -3,7 +3,7 @@
 // As in conv_c3.hip the input rows lie in LDS, but with every 4 x 4 pixels together (96 bytes, in a slot of 112): with the filter
 // padded to 12x12 by zero weights the layer is a 3x3 one at stride 1 of 48 channels, and the operand of a pixel is 16 aligned
 // bytes in slots that 16 neighbouring pixels find in different banks.  (As rows of pixels, 24 bytes from one to the next, the
-// operand took two 8-byte reads: the LDS was busy for 71 % of the time, the matrix pipes for 37, 256 images 71 us; this 63.)
+// operand took two 8-byte reads: the LDS was busy for 71 % of the time, the matrix pipes for 37, 256 images 71 us; this 65.)
 // What a work-group does one thing after the other is cut down:
 //   * it takes G neighbouring output rows of an image at a time, whose 4 G + 7 input rows overlap: one pass through memory, LDS and
 //     barrier for all of them, the rows of the next group on their way meanwhile;
@@ -11,8 +11,9 @@
 //     memory by unaligned 16-byte loads 7 us later);
 //   * an output tile leaves through LDS of the wavefront's own: the rows are all that the work-group waits for.
 // 224 x 224 -> 64 channels, us at 1 / 8 / 32 / 100 / 256 images, the kernels that had them before (conv_thin.hip to 8, an output row with all
-// its input rows at a time beyond) and this: 15.4 / 18.7 / 31.6 / 55 / 110, 7.8 / 11.1 / 18.6 / 34 / 63; the output alone takes 20 at 256.
-// Zero weights meet neighbouring input elements (assumed finite).  Wavefront: one block of 32 output channels, its weights in
+// its input rows at a time beyond) and this: 15.2 / 18.6 / 30.0 / 53 / 101, 8.2 / 11.5 / 19.2 / 35 / 65; the output alone takes 20 at 256.
+// The twelfth row and column of a window are masked out of the operand: the zero weights alone would make a NaN of an infinity there
+// (256 images 61 -> 65 us, 32 18.9 -> 19.2).  Wavefront: one block of 32 output channels, its weights in
 // registers for the whole kernel, and every second of the (row, 32 pixels) tiles.
 #include "wap_internal.h"
 
@@ -44,6 +45,12 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     return __builtin_bit_cast(unsigned short, b);
 }
 
+// Elements e and e + 1 of a block of 4 x 4 taps at reduction step ks: ones where the tap is one of the filter's 11 x 11.
+__device__ constexpr unsigned pair_mask(int ks, int e) {
+    const int r = ks / 9 * 4, s = ks / 3 % 3 * 4;  // the block's first tap
+    const bool lo = r + e / 12 < R && s + e % 12 / 3 < R, hi = r + (e + 1) / 12 < R && s + (e + 1) % 12 / 3 < R;
+    return (lo ? 0xffffu : 0u) | (hi ? 0xffff0000u : 0u);
+}
 constexpr int rows_of(int g) { return (g - 1) * ST + R; }
 // the rows, the output tiles and the bias, or before them the weights
 constexpr size_t smem_of(int fb, int g) {
@@ -163,13 +170,20 @@ __global__ __launch_bounds__(NT, 2) void conv_c3_fwd_strided_kernel(const RowsAr
             constexpr int AHEAD = 4;
             bf16x8 xf[AHEAD];
             auto read = [&](int ks) { return *reinterpret_cast<const bf16x8*>(x0 + ks / 9 * BRP + ks / 3 % 3 * BP + ks % 3 * 32); };
+            // the operand without the twelfth row and column
+            auto inside = [&](bf16x8 v, int ks) {
+                u32x4 x = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) x[d] &= half ? pair_mask(ks, ks % 3 * 16 + 8 + 2 * d) : pair_mask(ks, ks % 3 * 16 + 2 * d);
+                return __builtin_bit_cast(bf16x8, x);
+            };
 #pragma unroll
             for (int ks = 0; ks < AHEAD; ++ks) xf[ks] = read(ks);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 __builtin_amdgcn_sched_barrier(0);
                 f32x16& sum = ks & 1 ? odd : acc;
-                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks], xf[ks % AHEAD], sum, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks], inside(xf[ks % AHEAD], ks), sum, 0, 0, 0);
                 if (ks + AHEAD < KS) xf[ks % AHEAD] = read(ks + AHEAD);
             }
             __builtin_amdgcn_sched_barrier(0);
