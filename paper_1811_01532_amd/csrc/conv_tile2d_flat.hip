@@ -408,11 +408,13 @@ int launch_flat_k(F kfn, std::atomic<bool>& attr_done, const FlatArgs& fa, size_
 }
 template <int FM, int KS>
 int launch_flat_t(const FlatArgs& fa, size_t smem, hipStream_t st) {
-    static std::atomic<bool> done3{false}, done3u{false}, done5{false};
+    static std::atomic<bool> done3{false}, done3u{false}, done5{false}, done5u{false};
     if (fa.g.R == 3 && fa.up_am) return launch_flat_k(conv_tile2d_flat_kernel<FM, KS, true, 3>, done3u, fa, smem, st);
     if (fa.g.R == 3) return launch_flat_k(conv_tile2d_flat_kernel<FM, KS, false, 3>, done3, fa, smem, st);
-    if constexpr (KS != 8)
-        if (fa.g.R == 5 && !fa.up_am) return launch_flat_k(conv_tile2d_flat_kernel<FM, KS, false, 5>, done5, fa, smem, st);
+    if constexpr (KS != 8) {
+        if (fa.g.R == 5 && fa.up_am) return launch_flat_k(conv_tile2d_flat_kernel<FM, KS, true, 5>, done5u, fa, smem, st);
+        if (fa.g.R == 5) return launch_flat_k(conv_tile2d_flat_kernel<FM, KS, false, 5>, done5, fa, smem, st);
+    }
     return set_error(WAP_EINVAL, "internal: flat tiles take 3x3 and 5x5 filters");
 }
 }  // namespace
@@ -456,16 +458,18 @@ int flat_pick(const GemmGeom& g, double* us_out) {
     return best;
 }
 
-bool flat_fuses_unpool(const GemmGeom& g) { return g.R == 3 && (g.IH % 2) == 0 && (g.IW % 2) == 0; }
+bool flat_fuses_unpool(const GemmGeom& g) { return (g.IH % 2) == 0 && (g.IW % 2) == 0; }
 int flat_colsum_rows(const GemmGeom& g, int tile) { return (g.M + 32 * (tile / 10) - 1) / (32 * (tile / 10)); }
 
 const char* flat_kernel_name(const GemmGeom& g, int tile, bool unpool) {
-#define WAP_FLAT_KS(FM, KS) {"conv_tile2d_flat_kernel<" #FM "," #KS ",false,3>", "conv_tile2d_flat_kernel<" #FM "," #KS ",true,3>", "conv_tile2d_flat_kernel<" #FM "," #KS ",false,5>"}
+#define WAP_FLAT_ONE(FM, KS, UP, ST) "conv_tile2d_flat_kernel<" #FM "," #KS "," #UP "," #ST ">"
+#define WAP_FLAT_KS(FM, KS) {WAP_FLAT_ONE(FM, KS, false, 3), WAP_FLAT_ONE(FM, KS, true, 3), WAP_FLAT_ONE(FM, KS, false, 5), WAP_FLAT_ONE(FM, KS, true, 5)}
 #define WAP_FLAT(FM) {WAP_FLAT_KS(FM, 2), WAP_FLAT_KS(FM, 4), WAP_FLAT_KS(FM, 8)}
-    static const char* names[4][3][3] = {WAP_FLAT(1), WAP_FLAT(2), WAP_FLAT(3), WAP_FLAT(4)};
+    static const char* names[4][3][4] = {WAP_FLAT(1), WAP_FLAT(2), WAP_FLAT(3), WAP_FLAT(4)};
 #undef WAP_FLAT
 #undef WAP_FLAT_KS
-    return names[tile / 10 - 1][tile % 10 / 4][g.R == 5 ? 2 : unpool ? 1 : 0];
+#undef WAP_FLAT_ONE
+    return names[tile / 10 - 1][tile % 10 / 4][(g.R == 5 ? 2 : 0) + (unpool ? 1 : 0)];
 }
 
 int launch_flat(const GemmGeom& g, int tile, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out, hipStream_t st,

@@ -165,6 +165,14 @@ CASES = [
     ("wgrad_two_steps_a_split_s2", (2, 24, 31, 96, 64, 3, 3, 2, 1), (-1, -1, -1)),
     ("wgrad_two_steps_a_split_1x1", (8, 14, 14, 128, 64, 1, 1, 1, 0), (-1, -1, -1)),
     ("fill_5_picked_w14", (45, 14, 14, 128, 512, 3, 3, 1, 1), (-1, -1, -1)),
+    # 5x5 layers on even maps: the data gradient of every flat tiling routes the gradient of a pooled output itself
+    ("flat_22_5x5_pooled", (2, 12, 14, 64, 64, 5, 5, 1, 2), (122, -1, -1)),
+    ("flat_24_5x5_pooled", (3, 12, 14, 64, 64, 5, 5, 1, 2), (124, -1, -1)),
+    ("flat_32_5x5_pooled_pad0", (2, 10, 16, 64, 96, 5, 5, 1, 0), (132, -1, -1)),
+    ("flat_34_5x5_pooled", (2, 18, 18, 64, 64, 5, 5, 1, 2), (134, -1, -1)),
+    ("flat_42_5x5_pooled", (3, 8, 24, 64, 32, 5, 5, 1, 2), (142, -1, -1)),
+    ("flat_44_5x5_pooled", (3, 12, 12, 128, 64, 5, 5, 1, 2), (144, -1, -1)),
+    ("flat_picked_5x5_pooled", (12, 12, 14, 256, 32, 5, 5, 1, 2), (-1, -1, -1)),
 ]
 
 
