@@ -858,16 +858,23 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
     //     for 5x5 (32 x 27 x 27, 64 -> 192 20 / 26): beyond, the larger tiles read fewer weights per output;
     //   the generic kernel: where the predicted time, with a packing launch where there is one to pay for, is below that
     //     kernel's line of 9 us (14 with a split reduction) and 550 TFLOP/s (13 x 67 x 67, 384 -> 32 41 / 52, 28 x 10 x 10 20 / 8).
-    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, and single data
-    // gradients of the whole-filter patch kernel with a last block of channels that is not full theirs (what wap_conv2d_kernel_name
-    // says of them is promised by the tests; 90 x 90, 64 -> 200 would take 10 instead of 16 us), and every plan the workspace it
-    // asked for: what fits the static scratch, or does not, stays so.
-    const bool promised = !prepacked && (nsplit > 1 || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
-    if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !promised) {
+    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, single data gradients of
+    // the whole-filter patch kernel with a last block of channels that is not full theirs, and every single call the workspace it asked
+    // for: where that was none, only tiles that read the weights where they lie take over (a packed copy would need one).
+    const bool kept = !prepacked && (nsplit > 1 || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
+    if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
-        const size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
+        size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
         double us = 0;
-        const int tile = blocks <= 64.0 && (b_tr || need == p.ws_bytes || need <= WAP_STATIC_SCRATCH_BYTES) ? flat_pick(g, &us) : 0;
+        int tile = blocks <= 64.0 && (b_tr || need == p.ws_bytes || need <= WAP_STATIC_SCRATCH_BYTES) ? flat_pick(g, &us) : 0;
+        if (tile && !prepacked && p.ws_bytes == 0) {
+            GemmPlan flat;
+            flat.cfg = 16;
+            flat.nsplit = 1;
+            flat.ws_bytes = need = 0;
+            flat.tile = tile;
+            if (!reads_unpacked(g, b_tr, flat)) tile = 0;
+        }
         bool wins;
         if (cfg == 7 && nsplit > 1) wins = true;
         else if (cfg < 5) wins = us + (prepacked ? 0.0 : 4.0) < (nsplit > 1 ? 14.0 : 9.0) + flops / 550e6;

@@ -14,3 +14,17 @@ def wap():
 def test_pooled_5x5_data_gradients_need_no_scratch_tensor(wap, N, H, W, C, K, pad):
     """Even 5x5 maps on tiles of whole patches: the gradient of the pooled output is routed while the patch is staged."""
     assert wap.wap_conv2d_bwd_pool2x2_fused(wap.conv_desc(N, H, W, C, K, 5, 5, 1, pad), wap.WAP_PASS_BWD_DATA)
+
+
+# A single call that took no workspace goes on taking none: unsplit products of the generic kernel, whatever other tiles there are.
+NO_WORKSPACE = [
+    ("fwd", (1, 105, 105, 960, 168, 5, 5, 1, 2)), ("fwd", (69, 35, 35, 576, 64, 5, 5, 1, 2)), ("fwd", (27, 60, 60, 64, 96, 3, 3, 1, 1)),
+    ("fwd", (20, 57, 57, 64, 96, 3, 3, 1, 1)), ("fwd", (6, 51, 51, 256, 448, 5, 5, 1, 2)), ("fwd", (7, 68, 68, 64, 96, 3, 3, 1, 1)),
+    ("dx", (15, 37, 37, 96, 256, 3, 3, 1, 1)), ("dx", (2, 40, 49, 1024, 64, 5, 5, 1, 2)), ("dx", (14, 46, 46, 368, 608, 3, 3, 1, 0)),
+    ("dx", (12, 16, 16, 512, 32, 3, 3, 1, 1)), ("dx", (10, 50, 50, 256, 96, 5, 5, 1, 0)),
+]
+
+
+@pytest.mark.parametrize("what,shape", NO_WORKSPACE)
+def test_calls_without_a_workspace_stay_without(wap, what, shape):
+    assert wap.wap_conv2d_workspace_bytes(wap.conv_desc(*shape), wap.WAP_PASS_FWD if what == "fwd" else wap.WAP_PASS_BWD_DATA) == 0
