@@ -771,7 +771,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
         p.cfg = b_tr ? 11 : 10;
         p.nsplit = 1;
         if (!b_tr) {
-            fc_fwd_plan(g, &p.tile, &p.nsplit);
+            fc_fwd_plan(g, prepacked, &p.tile, &p.nsplit);
             if (g_force_nsplit >= 1) p.nsplit = g_force_nsplit;
         }
         const int steps = (g.IC + 31) / 32;

@@ -28,3 +28,10 @@ NO_WORKSPACE = [
 @pytest.mark.parametrize("what,shape", NO_WORKSPACE)
 def test_calls_without_a_workspace_stay_without(wap, what, shape):
     assert wap.wap_conv2d_workspace_bytes(wap.conv_desc(*shape), wap.WAP_PASS_FWD if what == "fwd" else wap.WAP_PASS_BWD_DATA) == 0
+
+
+@pytest.mark.parametrize("B,n_in,n_out", [(12, 4096, 1000), (11, 4096, 512), (10, 7424, 500), (15, 4096, 11), (6, 5184, 1000), (16, 8128, 256), (4, 25088, 2064)])
+def test_fully_connected_calls_without_a_workspace_stay_without(wap, B, n_in, n_out):
+    """Forward streams whose rows of weights are shorter than 256 KB, or with more than 128 work-groups of 16 features."""
+    assert wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD) == "fc_fwd_kernel"
+    assert wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 0
