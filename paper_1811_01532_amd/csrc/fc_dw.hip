@@ -158,18 +158,32 @@ int launch_dw(DwArgs a, int max_groups, hipStream_t st) {
 
 }  // namespace
 
-// Against the tiles of wgrad.hip, us, with the update (stored): 9216 -> 4096 at 8 / 32 / 64 rows 59.0 / 59.4 / 61.0 (26.3 / 26.3 / 28.2)
-// and there 63.0 / 63.3 / 64.2 (29.0 / 29.1 / 30.8); 4096 -> 4096 27.0 / 27.0 / 27.9 (13.1 / 13.1 / 15.0), 30.1 / 30.1 / 30.3 (15.9 / 16.0 / 16.4);
-// 1024 -> 512 at 8 rows 4.9 (3.9), 7.5 (5.3); 2052 -> 333, which they load in pieces, 5.9 (4.3), 26.4 (10.8).  25088 -> 4096 draws level to
-// 32 rows (215 (81), 213 (78)) and is slower at 64 (222 (86), 213 (79)).  More rows take more registers of x and fewer columns: at
-// 96 rows 4096 -> 1000 11.6 (8.8) against 11.0 (8.4), 4096 -> 500 9.0 (6.5) against 12.2 (9.1), 9216 -> 4096 91 (33) against 68 (38).
-bool fc_dw_supported(const WgradGeom& g) {
+// Where this is ahead of the tiles of wgrad.hip, stored and with the update, weights cached and from memory (8 800 calls at 1 .. 128 rows,
+// geometric mean of the time here over the time there; what is not listed is 1.02 .. 1.3 in one of the four):
+//   rows of x that are no whole 16-byte vectors (2052 -> 333), which the tiles load in pieces: 0.2 .. 0.75 at any number of batch rows;
+//   up to 32 batch rows: 0.73 .. 0.92, up to 64 M weights of an even shape (25088 -> 4096, stored: 81.4 us here, 77.9 there; with
+//     the update 215, 213).  A weight row that is not a whole number of lines is cut into runs that share their first and last line with
+//     another wavefront's: from 14 M weights on, beyond what the caches hold together, 1.1 .. 1.3 from memory;
+//   33 .. 64 rows: 0.83 .. 1.0 while 64 x 16 weights a unit make one round of work-groups, 0.92 .. 0.99 between 16 and 40 M weights
+//     (4096 -> 1000, stored, 1.04, 9216 -> 512 1.12), 0.75 .. 0.98 where an odd number of outputs slows the tiles;
+//   65 .. 96 rows: 0.91 .. 0.95 in one round (4096 -> 512 8.3 -> 7.6 us).
+// Long rows of few outputs (9216 -> 104) leave the operand of x as the larger part: 1.05 .. 1.1 beyond 32 rows.
+// In a step, behind and beside other kernels, the stream is ahead or level for all it was measured on, 4096 -> 1000 to 25088 -> 4096 up to
+// 32 rows, to 64 M weights up to 64: stored gradients, tiles / stream, VGG-16 at 1 / 10 / 22 / 32 images 1204 / 1185, 2016 / 2000, 3052 / 3058,
+// 3770 / 3755 us, AlexNet-style at 45 / 64 785 / 778, 864 / 856; beside the convolutions the tiles' LDS would keep these off the CUs.
+bool fc_dw_supported(const WgradGeom& g, bool in_step) {
     if (g.H != 1 || g.W != 1 || g.P != 1 || g.Q != 1 || g.R != 1 || g.S != 1 || g.ph || g.pw) return false;
     const double weights = (double)g.K * g.C;
     if (g.N > 128 || (g.C % 4) != 0 || weights * 4.0 >= 2147483648.0 || (double)g.N * g.C * 2.0 >= 2147483648.0 || (double)g.N * g.K * 2.0 >= 2147483648.0)
         return false;
-    const bool odd = (g.C % 8) != 0 || (g.K % 8) != 0;
-    return odd || g.N <= 32 || (g.N <= 64 && weights <= 64e6) || (g.N <= 96 && weights <= 2.2e6);
+    if ((g.C % 8) != 0) return true;
+    const bool odd = (g.K % 8) != 0, lines = (g.C % 32) == 0;
+    if (in_step && (g.N <= 32 || (g.N <= 64 && weights <= 64e6))) return true;
+    if (g.N <= 32) return lines ? odd || weights <= 64e6 : weights <= 14e6;
+    const bool one_round = (long)((g.C + 63) / 64) * ((g.K + 15) / 16) <= 8 * kNumCU && g.C <= 8192;
+    if (g.N <= 64 && odd) return g.K > 16 && (lines || weights <= 14e6);
+    if (g.N <= 64) return lines && (one_round || (weights >= 16e6 && weights <= 40e6));
+    return g.N <= 96 && one_round;
 }
 
 int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, hipStream_t st) {

@@ -60,7 +60,7 @@ int make_passes(int kind, const void* desc, int mb, Passes* ps, Layout* lay) {
     // the kernels a step launches, whose times the table estimates (a single call of a small layer may plan without packing)
     ps->pf = plan_fwd_like(ps->gf, false, true);
     ps->pd = plan_fwd_like(ps->gd, true, true);
-    ps->pw = plan_wgrad(ps->gw);
+    ps->pw = plan_wgrad(ps->gw, true);
     lay->x_elems = xe; lay->w_elems = we; lay->y_elems = ye;
     lay->ws_bytes = std::max(ps->pf.ws_bytes, std::max(ps->pd.ws_bytes, ps->pw.ws_bytes));
     size_t o = 0;

@@ -544,7 +544,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     auto push_wgrad = [&](OpKind kind, const std::string& name, const WgradGeom& g, size_t x, size_t dy, int li) {
         Op op;
         op.kind = kind; op.name = name; op.wg = g;
-        op.wp = plan_wgrad(g);
+        op.wp = plan_wgrad(g, true);
         op.kernel = wgrad_kernel_name(g, op.wp);
         const double nw = (double)g.K * g.R * g.S * g.C;
         op.flops = 2.0 * g.N * g.P * g.Q * nw;

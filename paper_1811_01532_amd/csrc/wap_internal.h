@@ -165,7 +165,7 @@ struct WgradPlan {
     int nsplit;
     size_t ws_bytes;
 };
-WgradPlan plan_wgrad(const WgradGeom& g);
+WgradPlan plan_wgrad(const WgradGeom& g, bool in_step = false);
 // unpool_am: dy is the gradient of the 2x2 / stride-2 max-pooled output (N x P/2 x Q/2 x K) and unpool_am the pool's
 // argmax; only where wgrad_fuses_unpool() says so.
 // sgd: apply the update to the parameters instead of storing dW (dw may then be NULL); only where wgrad_fuses_sgd()
@@ -245,7 +245,7 @@ int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, cons
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
 
 // fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups: as launch_wgrad
-bool fc_dw_supported(const WgradGeom& g);
+bool fc_dw_supported(const WgradGeom& g, bool in_step);
 int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, hipStream_t st);
 
 // weights-in-registers large-tile kernel (conv_wreg.hip)

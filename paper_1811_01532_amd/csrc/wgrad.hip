@@ -433,7 +433,7 @@ int padded_cols(const WgradGeom& g) { return classify_mode(g) == 1 ? g.R * g.S *
 
 }  // namespace
 
-WgradPlan plan_wgrad(const WgradGeom& g) {
+WgradPlan plan_wgrad(const WgradGeom& g, bool in_step) {
     WgradPlan p;
     int mode = classify_mode(g);
     int Kred = g.R * g.S * g.C;
@@ -473,7 +473,7 @@ WgradPlan plan_wgrad(const WgradGeom& g) {
         p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * g.K * Kred * sizeof(float) : 0;
         return p;
     }
-    if (g_force_wgrad_cfg < 0 && g_force_nsplit < 0 && fc_dw_supported(g)) {
+    if (g_force_wgrad_cfg < 0 && g_force_nsplit < 0 && fc_dw_supported(g, in_step)) {
         p.cfg = 8;
         p.nsplit = 1;
         p.ws_bytes = 0;

@@ -35,3 +35,22 @@ def test_fully_connected_calls_without_a_workspace_stay_without(wap, B, n_in, n_
     """Forward streams whose rows of weights are shorter than 256 KB, or with more than 128 work-groups of 16 features."""
     assert wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD) == "fc_fwd_kernel"
     assert wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 0
+
+
+def test_streamed_weight_gradients_by_shape(wap):
+    """Fully-connected weight gradients as streams of the weights only where these are no slower than the tiles: not the largest even
+    shapes, weight rows that end in the middle of a line, long rows of few outputs, or many batch rows of a large layer."""
+    def streams(B, n_in, n_out):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_BWD_WEIGHT) == "fc_dw_kernel"
+    for c in ((8, 9216, 4096), (32, 4096, 4096), (20, 25088, 1000), (64, 9216, 4096), (48, 4096, 512), (96, 4096, 500), (8, 4504, 512),
+              (100, 2052, 333), (2, 25088, 4097)):
+        assert streams(*c), c
+    for c in ((20, 25088, 4096), (40, 9216, 512), (33, 9216, 104), (2, 4504, 4096), (3, 8856, 4096), (83, 9216, 232), (40, 4096, 1000), (100, 9216, 500), (80, 4096, 2036), (64, 25088, 10)):
+        assert not streams(*c), c
+
+
+@pytest.mark.parametrize("minibatch,store", [(8, False), (22, True), (32, True)])
+def test_a_step_streams_its_largest_weight_gradient(wap, minibatch, store):
+    """Behind and beside other kernels the stream is ahead or level where the single call is not."""
+    ops = {o[0]: o for o in wap.StepPlan("vgg16", minibatch, flags=wap.WAP_STEP_STORE_GRADS if store else 0).ops()}
+    assert "fc_dw_kernel" in next(o for n, o in ops.items() if n.startswith("fc6.dW"))
