@@ -126,6 +126,15 @@ static int check_ptr(const void* p, const char* name) {
     return WAP_OK;
 }
 
+// The plans of single calls.  Convolutions forward: with a workspace of the caller's, without one and on the static array the same
+// kernels, hence the plan that asks for least.  Data gradients and fully-connected forward passes: what the query asks for buys a faster
+// plan, and a call without it runs the lean one.
+static GemmPlan plan_conv_fwd(const GemmGeom& g) { return plan_fwd_like(g, false, false, true); }
+static GemmPlan plan_with_ws(const GemmGeom& g, bool b_tr, const void* ws, size_t ws_bytes) {
+    const GemmPlan p = plan_fwd_like(g, b_tr);
+    return p.ws_bytes && (!ws || ws_bytes < p.ws_bytes) ? plan_fwd_like(g, b_tr, false, true) : p;
+}
+
 static int check_ws(size_t need, void* ws, size_t ws_bytes) {
     if (need == 0) return WAP_OK;
     if (!ws) return set_error(WAP_EWORKSPACE, "workspace is NULL but %zu bytes are needed", need);
@@ -158,7 +167,7 @@ const char* wap_last_error(void) { return g_err; }
 int wap_conv2d_workspace_bytes(const wap_conv_desc* d, int pass, size_t* bytes_out) {
     WAP_TRY(validate_conv(d));
     if (!bytes_out) return set_error(WAP_EINVAL, "bytes_out is NULL");
-    if (pass == WAP_PASS_FWD) *bytes_out = plan_fwd_like(geom_conv_fwd(*d), false).ws_bytes;
+    if (pass == WAP_PASS_FWD) *bytes_out = plan_conv_fwd(geom_conv_fwd(*d)).ws_bytes;
     else if (pass == WAP_PASS_BWD_DATA) *bytes_out = plan_fwd_like(geom_conv_dgrad(*d), true).ws_bytes;
     else if (pass == WAP_PASS_BWD_WEIGHT) *bytes_out = plan_wgrad(geom_conv_wgrad(*d)).ws_bytes;
     else return set_error(WAP_EINVAL, "unknown pass %d", pass);
@@ -170,7 +179,7 @@ int wap_conv2d_kernel_name(const wap_conv_desc* d, int pass, const char** name_o
     if (!name_out) return set_error(WAP_EINVAL, "name_out is NULL");
     if (pass == WAP_PASS_FWD) {
         GemmGeom g = geom_conv_fwd(*d);
-        *name_out = fwd_like_kernel_name(g, false, plan_fwd_like(g, false));
+        *name_out = fwd_like_kernel_name(g, false, plan_conv_fwd(g));
     } else if (pass == WAP_PASS_BWD_DATA) {
         GemmGeom g = geom_conv_dgrad(*d);
         *name_out = fwd_like_kernel_name(g, true, plan_fwd_like(g, true));
@@ -191,7 +200,7 @@ int wap_conv2d_fwd(const wap_conv_desc* d, const void* x, const void* w, const f
     WAP_TRY(check_ptr(y, "y"));
     if (bias && !aligned16(bias)) return set_error(WAP_EINVAL, "bias is not 16-byte aligned");
     GemmGeom g = geom_conv_fwd(*d);
-    GemmPlan p = plan_fwd_like(g, false);
+    GemmPlan p = plan_conv_fwd(g);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     return launch_fwd_like(g, false, p, (const bf16_t*)x, (const bf16_t*)w, bias, (d->flags & WAP_RELU) != 0,
                            (bf16_t*)y, ws, (hipStream_t)stream);
@@ -236,7 +245,7 @@ int wap_conv2d_fwd_static_ws(const wap_conv_desc* d, const void* x, const void* 
     WAP_TRY(check_ptr(y, "y"));
     if (bias && !aligned16(bias)) return set_error(WAP_EINVAL, "bias is not 16-byte aligned");
     GemmGeom g = geom_conv_fwd(*d);
-    GemmPlan p = plan_fwd_like(g, false);
+    GemmPlan p = plan_conv_fwd(g);
     if (p.ws_bytes > (size_t)WAP_STATIC_SCRATCH_BYTES)
         return set_error(WAP_EWORKSPACE, "conv2d_fwd_static_ws: this layer needs %zu bytes of workspace, the static scratch "
                          "holds %zu; use wap_conv2d_fwd with a caller workspace", p.ws_bytes, (size_t)WAP_STATIC_SCRATCH_BYTES);
@@ -250,7 +259,7 @@ int wap_conv2d_fwd_pool2x2_fused(const wap_conv_desc* d, int32_t* fused_out) {
     WAP_TRY(validate_conv(d));
     if (!fused_out) return set_error(WAP_EINVAL, "fwd_pool2x2_fused: NULL argument");
     GemmGeom g = geom_conv_fwd(*d);
-    *fused_out = fwd_like_fuses_pool(g, plan_fwd_like(g, false)) ? 1 : 0;
+    *fused_out = fwd_like_fuses_pool(g, plan_conv_fwd(g)) ? 1 : 0;
     return WAP_OK;
 }
 
@@ -263,7 +272,7 @@ int wap_conv2d_fwd_pool2x2(const wap_conv_desc* d, const void* x, const void* w,
     WAP_TRY(check_ptr(argmax, "argmax"));
     GemmGeom g = geom_conv_fwd(*d);
     if ((g.OH & 1) || (g.OW & 1)) return set_error(WAP_EINVAL, "fwd_pool2x2: output size %dx%d is not even", g.OH, g.OW);
-    GemmPlan p = plan_fwd_like(g, false);
+    GemmPlan p = plan_conv_fwd(g);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     const bool relu = (d->flags & WAP_RELU) != 0;
     if (fwd_like_fuses_pool(g, p))
@@ -283,7 +292,7 @@ int wap_conv2d_bwd_data(const wap_conv_desc* d, const void* dy, const void* w, v
     WAP_TRY(check_ptr(w, "w"));
     WAP_TRY(check_ptr(dx, "dx"));
     GemmGeom g = geom_conv_dgrad(*d);
-    GemmPlan p = plan_fwd_like(g, true);
+    GemmPlan p = plan_with_ws(g, true, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     return launch_fwd_like(g, true, p, (const bf16_t*)dy, (const bf16_t*)w, nullptr, false, (bf16_t*)dx, ws,
                            (hipStream_t)stream);
@@ -297,7 +306,7 @@ int wap_conv2d_bwd_data_relu(const wap_conv_desc* d, const void* dy, const void*
     WAP_TRY(check_ptr(x_act, "x_act"));
     WAP_TRY(check_ptr(dx, "dx"));
     GemmGeom g = geom_conv_dgrad(*d);
-    GemmPlan p = plan_fwd_like(g, true);
+    GemmPlan p = plan_with_ws(g, true, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     return launch_fwd_like(g, true, p, (const bf16_t*)dy, (const bf16_t*)w, nullptr, false, (bf16_t*)dx, ws,
                            (hipStream_t)stream, nullptr, (const bf16_t*)x_act);
@@ -393,7 +402,7 @@ int wap_conv2d_bwd_data_pool2x2(const wap_conv_desc* d, const void* g_pool, cons
     WAP_TRY(check_ptr(dx, "dx"));
     if (x_act && !aligned16(x_act)) return set_error(WAP_EINVAL, "x_act is not 16-byte aligned");
     GemmGeom g = geom_conv_dgrad(*d);
-    GemmPlan p = plan_fwd_like(g, true);
+    GemmPlan p = plan_with_ws(g, true, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     if (fwd_like_fuses_unpool(g, p))
         return launch_fwd_like(g, true, p, (const bf16_t*)g_pool, (const bf16_t*)w, nullptr, false, (bf16_t*)dx, ws,
@@ -440,7 +449,7 @@ int wap_fc_fwd(const wap_fc_desc* d, const void* x, const void* Wt, const float*
     WAP_TRY(check_ptr(y, "y"));
     if (bias && !aligned16(bias)) return set_error(WAP_EINVAL, "bias is not 16-byte aligned");
     GemmGeom g = geom_fc_fwd(*d);
-    GemmPlan p = plan_fwd_like(g, false);
+    GemmPlan p = plan_with_ws(g, false, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     return launch_fwd_like(g, false, p, (const bf16_t*)x, (const bf16_t*)Wt, bias, (d->flags & WAP_RELU) != 0,
                            (bf16_t*)y, ws, (hipStream_t)stream);

@@ -331,10 +331,10 @@ bool fc_dx_supported(const GemmGeom& g) {
 // 16 rows); a launch that adds up partial sums takes 2.3 (3.5 where it cannot load vectors).  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
 // memory, 16 features and a division by 128 KB of Wt / this: 4096 -> 1000 7.7 / 9.1 / 10.3, 6.2 / 7.4 / 8.0; 9216 -> 512 10.4 / 11.8 / 13.3, 7.4 /
 // 8.0 / 8.7; 11264 -> 609 11.5 / 13.3 / 15.0, 8.5 / 9.2 / 9.9.
-// A single call divides the reduction only where it has always needed a workspace, a step's plan (own_ws) wherever it pays.
-void fc_fwd_plan(const GemmGeom& g, bool own_ws, int* feat, int* nsplit) {
+// lean: divided only where rows of 256 KB and few features have always asked for a workspace.
+void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
     const int steps = (g.IC + 16 * 2 * FW_WAVES - 1) / (16 * 2 * FW_WAVES);
-    const int most = own_ws || (g.Ncols <= 2048 && g.IC >= 8192) ? 16 : 1;
+    const int most = !lean || (g.Ncols <= 2048 && g.IC >= 8192) ? 16 : 1;
     double least = 0;
     for (int f : {16, 8, 4})
         for (int n = 1; n <= most && n <= steps; ++n) {

@@ -747,7 +747,7 @@ int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
 
 }  // namespace
 
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) {
     GemmPlan p;
     if (!b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 8) && conv_c3_fwd_supported(g)) {
         p.cfg = 8;
@@ -771,7 +771,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
         p.cfg = b_tr ? 11 : 10;
         p.nsplit = 1;
         if (!b_tr) {
-            fc_fwd_plan(g, prepacked, &p.tile, &p.nsplit);
+            fc_fwd_plan(g, lean, &p.tile, &p.nsplit);
             if (g_force_nsplit >= 1) p.nsplit = g_force_nsplit;
         }
         const int steps = (g.IC + 31) / 32;
@@ -858,9 +858,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
     //     for 5x5 (32 x 27 x 27, 64 -> 192 20 / 26): beyond, the larger tiles read fewer weights per output;
     //   the generic kernel: where the predicted time, with a packing launch where there is one to pay for, is below that
     //     kernel's line of 9 us (14 with a split reduction) and 550 TFLOP/s (13 x 67 x 67, 384 -> 32 41 / 52, 28 x 10 x 10 20 / 8).
-    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, single data gradients of
-    // the whole-filter patch kernel with a last block of channels that is not full theirs, and every single call the workspace it asked
-    // for: where that was none, only tiles that read the weights where they lie take over (a packed copy would need one).
+    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, and single data gradients of
+    // the whole-filter patch kernel with a last block of channels that is not full theirs.  Where a single call needed no workspace, tiles
+    // that read a packed copy of the weights take over only if the caller has one for it (not lean).
     const bool kept = !prepacked && (nsplit > 1 || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
@@ -871,9 +871,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked) {
             GemmPlan flat;
             flat.cfg = 16;
             flat.nsplit = 1;
-            flat.ws_bytes = need = 0;
             flat.tile = tile;
-            if (!reads_unpacked(g, b_tr, flat)) tile = 0;
+            if (reads_unpacked(g, b_tr, flat)) need = 0;
+            else if (lean) tile = 0;
         }
         bool wins;
         if (cfg == 7 && nsplit > 1) wins = true;

@@ -121,8 +121,9 @@ constexpr int kTileSplit64 = 1, kTileSplit192 = 3, kTileFill = 10, kTileStrips =
 // Weight operand addressing.
 //  NT : Bw[n][kk]               (forward conv / FC forward): row pitch Kred
 //  TR : Bw[k][R-1-r][S-1-s][n]  (data gradient: reduction (r,s,k), k innermost): n contiguous
-// prepacked: the caller keeps the weights in packed order (a step plan); else a packing launch in front is part of the price
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked = false);
+// prepacked: the caller keeps the weights in packed order (a step plan); else a packing launch in front is part of the price.
+// lean: a single call that takes no workspace where the generic kernel needs none
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked = false, bool lean = false);
 int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf16_t* A,
                     const bf16_t* Bw, const float* bias, bool relu, bf16_t* out, void* ws,
                     hipStream_t st, hipEvent_t ev_mid = nullptr,  // ev_mid: recorded between kernel and split epilogue
@@ -238,7 +239,7 @@ int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16
 // fully-connected products with few rows as streams of the weights (fc.hip); geometries of geom_fc_fwd / geom_fc_dx
 bool fc_fwd_supported(const GemmGeom& g);
 bool fc_dx_supported(const GemmGeom& g);
-void fc_fwd_plan(const GemmGeom& g, bool own_ws, int* feat, int* nsplit);
+void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);

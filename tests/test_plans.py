@@ -1,6 +1,8 @@
 """CPU-only checks of what a plan promises its caller: which calls need no scratch tensor, which need no workspace."""
 import pytest
 
+from tests import recorded
+
 
 @pytest.fixture(scope="module")
 def wap():
@@ -16,25 +18,56 @@ def test_pooled_5x5_data_gradients_need_no_scratch_tensor(wap, N, H, W, C, K, pa
     assert wap.wap_conv2d_bwd_pool2x2_fused(wap.conv_desc(N, H, W, C, K, 5, 5, 1, pad), wap.WAP_PASS_BWD_DATA)
 
 
-# A single call that took no workspace goes on taking none: unsplit products of the generic kernel, whatever other tiles there are.
-NO_WORKSPACE = [
-    ("fwd", (1, 105, 105, 960, 168, 5, 5, 1, 2)), ("fwd", (69, 35, 35, 576, 64, 5, 5, 1, 2)), ("fwd", (27, 60, 60, 64, 96, 3, 3, 1, 1)),
-    ("fwd", (20, 57, 57, 64, 96, 3, 3, 1, 1)), ("fwd", (6, 51, 51, 256, 448, 5, 5, 1, 2)), ("fwd", (7, 68, 68, 64, 96, 3, 3, 1, 1)),
-    ("dx", (15, 37, 37, 96, 256, 3, 3, 1, 1)), ("dx", (2, 40, 49, 1024, 64, 5, 5, 1, 2)), ("dx", (14, 46, 46, 368, 608, 3, 3, 1, 0)),
-    ("dx", (12, 16, 16, 512, 32, 3, 3, 1, 1)), ("dx", (10, 50, 50, 256, 96, 5, 5, 1, 0)),
-]
+# Calls that took no workspace go on without one: unsplit products of the generic kernel, whatever other tiles there are, and forward streams
+# whose rows of weights are shorter than 256 KB or that have more than 128 work-groups of 16 features.
+FORWARD = [(1, 105, 105, 960, 168, 5, 5, 1, 2), (69, 35, 35, 576, 64, 5, 5, 1, 2), (27, 60, 60, 64, 96, 3, 3, 1, 1),
+           (20, 57, 57, 64, 96, 3, 3, 1, 1), (6, 51, 51, 256, 448, 5, 5, 1, 2), (7, 68, 68, 64, 96, 3, 3, 1, 1), (12, 1, 1, 4096, 1000, 1, 1, 1, 0)]
+BACKWARD = [(15, 37, 37, 96, 256, 3, 3, 1, 1), (2, 40, 49, 1024, 64, 5, 5, 1, 2), (14, 46, 46, 368, 608, 3, 3, 1, 0),
+            (12, 16, 16, 512, 32, 3, 3, 1, 1), (10, 50, 50, 256, 96, 5, 5, 1, 0)]
+FC = [(12, 4096, 1000), (11, 4096, 512), (10, 7424, 500), (15, 4096, 11), (6, 5184, 1000), (16, 8128, 256), (4, 25088, 2064)]
 
 
-@pytest.mark.parametrize("what,shape", NO_WORKSPACE)
-def test_calls_without_a_workspace_stay_without(wap, what, shape):
-    assert wap.wap_conv2d_workspace_bytes(wap.conv_desc(*shape), wap.WAP_PASS_FWD if what == "fwd" else wap.WAP_PASS_BWD_DATA) == 0
+@pytest.mark.parametrize("shape", FORWARD)
+def test_forward_convolutions_ask_for_no_workspace(wap, shape):
+    """With a workspace, without one and on the static array the kernels are the same, so the plan is the one that needs none."""
+    assert wap.wap_conv2d_workspace_bytes(wap.conv_desc(*shape), wap.WAP_PASS_FWD) == 0
 
 
-@pytest.mark.parametrize("B,n_in,n_out", [(12, 4096, 1000), (11, 4096, 512), (10, 7424, 500), (15, 4096, 11), (6, 5184, 1000), (16, 8128, 256), (4, 25088, 2064)])
-def test_fully_connected_calls_without_a_workspace_stay_without(wap, B, n_in, n_out):
-    """Forward streams whose rows of weights are shorter than 256 KB, or with more than 128 work-groups of 16 features."""
-    assert wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD) == "fc_fwd_kernel"
-    assert wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 0
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    return recorded.build(tmp_path_factory.mktemp("recorder"))
+
+
+def test_data_gradients_run_without_a_workspace_and_better_with_it(so):
+    calls = recorded.launches(recorded.run(so, f"""
+m = Mem(1 << 34)
+for shape in {BACKWARD}:
+    d = wap.conv_desc(*shape)
+    wap.wap_conv2d_bwd_data(d, m, m, m, None, stream=0)
+    wap.wap_conv2d_bwd_data_relu(d, m, m, m, m, None, stream=0)
+    if shape[1] % 2 == 0 and shape[2] % 2 == 0 and d.P % 2 == 0:
+        wap.wap_conv2d_bwd_data_pool2x2(d, m, m, m, m, m, m, None, stream=0)
+"""))
+    assert all("igemm_kernel" in c.kernel or "maxpool_bwd" in c.kernel for c in calls), calls
+    calls = recorded.launches(recorded.run(so, f"""
+for shape in {BACKWARD}:
+    d = wap.conv_desc(*shape)
+    m = Mem(1 << 34)
+    wap.wap_conv2d_bwd_data(d, m, m, m, Mem(wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)), stream=0)
+"""))
+    assert sum("conv_tile2d_flat_kernel" in c.kernel for c in calls) >= 2, calls
+
+
+def test_fully_connected_calls_run_without_a_workspace_and_divided_with_it(so):
+    for ws, launches in (("None", 1), ("Mem(need)", 2)):
+        calls = recorded.launches(recorded.run(so, f"""
+for shape in {FC}:
+    d = wap.fc_desc(*shape)
+    m, need = Mem(1 << 34), wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD)
+    wap.wap_fc_fwd(d, m, m, None, m, {ws}, stream=0)
+"""))
+        assert sum("fc_fwd_kernel" in c.kernel for c in calls) == len(FC)
+        assert len(calls) > len(FC) if launches == 2 else len(calls) == len(FC), calls
 
 
 def test_streamed_weight_gradients_by_shape(wap):
