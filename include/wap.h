@@ -24,10 +24,12 @@
  *   - Arguments are validated on the host before any device work: WAP_EINVAL for null
  *     pointers, non-positive sizes, pad >= filter size, misalignment; WAP_EUNSUPPORTED for
  *     sizes whose element counts exceed 2^31-1; WAP_EWORKSPACE when `ws_bytes` is below the
- *     matching *_workspace_bytes query; WAP_EHIP when a launch fails.  wap_last_error() gives
- *     the text of the last failure on the calling thread.
+ *     matching *_workspace_bytes query (or what the call cannot do without, see ws); WAP_EHIP
+ *     when a launch fails.  wap_last_error() gives the text of the last failure on the calling thread.
  *   - `ws` is scratch the caller provides (device memory, 256-byte aligned); it holds split
- *     reduction partials and may be NULL when the query returns 0.
+ *     reduction partials and packed weights and may be NULL when the query returns 0.  Convolution
+ *     data gradients and fully-connected forward passes that can do without what the query asks
+ *     for run a slower plan when it is not there.
  *   - Threads: calls may come from several host threads as long as each uses its own stream and
  *     buffers; one-time kernel attribute set-up is guarded.  wap_last_error() is per thread.
  */

@@ -328,7 +328,7 @@ bool fc_dx_supported(const GemmGeom& g) {
 // How many output features a work-group owns (16, 8 or 4: the rows of the MFMA beyond them are zeros that no load is made for) and over
 // how many work-groups the reduction is divided as well.  A work-group is bound by its CU's way to the L2: it starts in 3.5 us, and
 // every 512-deep step of its 16 wavefronts takes 0.19 and 0.021 more for every row of Wt or of the batch (within 6 % of 13 shapes, 1 to
-// 16 rows); a launch that adds up partial sums takes 2.3 (3.5 where it cannot load vectors).  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
+// 16 rows); a launch that adds up partial sums takes 2.3.  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
 // memory, 16 features and a division by 128 KB of Wt / this: 4096 -> 1000 7.7 / 9.1 / 10.3, 6.2 / 7.4 / 8.0; 9216 -> 512 10.4 / 11.8 / 13.3, 7.4 /
 // 8.0 / 8.7; 11264 -> 609 11.5 / 13.3 / 15.0, 8.5 / 9.2 / 9.9.
 // lean: divided only where rows of 256 KB and few features have always asked for a workspace.
@@ -340,8 +340,8 @@ void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
         for (int n = 1; n <= most && n <= steps; ++n) {
             const long groups = (long)((g.Ncols + f - 1) / f) * n;
             if ((f < 16 || n > 1) && groups > kNumCU) break;
-            const double us = 3.5 * ((groups + kNumCU - 1) / kNumCU) + (steps + n - 1) / n * (0.19 + 0.021 * (f + g.M)) + (n > 1 ? (g.Ncols % 4 ? 3.5 : 2.3) + 0.05 * n : 0.0);
-            if (least == 0 || us < 0.97 * least) {
+            const double us = 3.5 * ((groups + kNumCU - 1) / kNumCU) + (steps + n - 1) / n * (0.19 + 0.021 * (f + g.M)) + (n > 1 ? 2.3 + 0.05 * n : 0.0);
+            if (least == 0 || (us < 0.97 * least && us < least - 0.4)) {
                 least = us;
                 *feat = f;
                 *nsplit = n;

@@ -70,6 +70,12 @@ for shape in {FC}:
         assert len(calls) > len(FC) if launches == 2 else len(calls) == len(FC), calls
 
 
+def test_odd_features_divide_the_reduction_where_the_rows_are_long(wap):
+    """9216 -> 1438 in halves takes 12.6 us, by eight features without a second launch 13.6; short rows gain nothing from fewer features."""
+    for B, n_in, n_out in ((6, 9216, 1438), (5, 9216, 1787), (7, 9216, 1601), (7, 8304, 1653)):
+        assert wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 2 * 4 * B * n_out
+
+
 def test_streamed_weight_gradients_by_shape(wap):
     """Fully-connected weight gradients as streams of the weights only where these are no slower than the tiles: not the largest even
     shapes, weight rows that end in the middle of a line, long rows of few outputs, or many batch rows of a large layer."""
