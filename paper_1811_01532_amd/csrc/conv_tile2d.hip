@@ -850,6 +850,18 @@ bool tile2d_preferred(const GemmGeom& g) {
     return wgs >= kNumCU * 3 / 4;
 }
 
+// pixels and output channels of a work-group's tile
+void tile2d_shape(const GemmGeom& g, int tile, int* pixels, int* channels) {
+    if (!tile && tile64_width(g)) {
+        *pixels = 256;
+        *channels = 64;
+        return;
+    }
+    const TileCfg c = tile_cfg(g, tile);
+    *pixels = tile_pixels(c);
+    *channels = c.variant == 3 ? 64 : c.variant >= 1 ? 128 : 64 * c.fn;
+}
+
 // How to divide the reduction of a layer too small to fill the chip: number of splits (1: don't) and the flat tiling.
 // `generic`: the alternative is the tap-by-tap kernel, which splits its reduction as well but gathers every activation
 // once per tap (3x3, weights packed before: 512 -> 512 channels on 14 x 14 at minibatch 8 32.4 -> 22.2, 256 -> 256 on 13 x 13

@@ -745,6 +745,35 @@ int make_phases(const GemmGeom& g, int bm, Phase* ph, int* nphase) {
     return tiles;
 }
 
+// us that the kernels of a plan take beside which the flat tiles stand: a start, the steps of a work-group's reduction (9 taps of 32
+// channels, or 64 deep in the generic kernel), what a fuller chip and further rounds of work-groups add to each, and the partial sums through
+// memory.  Fitted to 33 000 products with packed weights (3x3 and 5x5, 16 to 1024 channels, maps of 4 to 120 pixels, 1 to 128 images; rms error
+// 4 to 8 %); 0: a tiling that the flat tiles beat wherever they were tried.
+double us_beside_flat(const GemmGeom& g, int cfg, int nsplit, int tile, int ktiles, long tiles) {
+    struct Line { double start, step, fill, round, mb; };
+    static constexpr Line whole192 = {6.3, 0.83, 1.05, 0.69, 0}, split192 = {7.7, 0.84, 0.77, 0, 0.61};
+    static constexpr Line whole64 = {5.35, 0.74, 0.61, 0.46, 0}, split64 = {6.9, 0.65, 0.70, 0.36, 0.54}, loop64 = {10.5, 0.12, 0.92, 0.92, 0.28};
+    static constexpr Line whole_generic = {7.7, 0.38, 0.25, 0.46, 0}, split_generic = {9.7, 0.28, 0.31, 0, 0.49};
+    const Line* l;
+    double steps;
+    if (cfg < 5) {
+        l = nsplit > 1 ? &split_generic : &whole_generic;
+        steps = (ktiles + nsplit - 1) / nsplit;
+    } else {
+        int pixels = 0, channels = 0;
+        if (cfg == 7) tile2d_shape(g, tile, &pixels, &channels);
+        if (channels == 64) l = nsplit > 1 ? &split192 : &whole192;
+        else if (pixels == 64 && g.R == 3) l = nsplit > 1 ? &split64 : &whole64;
+        else if (pixels == 64 && nsplit > 1) l = &loop64;
+        else return 0;
+        steps = (g.IC / 32 + nsplit - 1) / nsplit * (g.R * g.S / 9.0);
+        tiles = (long)((g.M + pixels - 1) / pixels) * (g.Ncols / channels);
+    }
+    const long groups = tiles * nsplit, rounds = (groups + kNumCU - 1) / kNumCU;
+    const double mb = nsplit > 1 ? nsplit * 4e-6 * g.M * g.Ncols : 0;
+    return l->start + steps * (l->step + l->fill * groups / kNumCU + l->round * (rounds - 1)) + l->mb * mb;
+}
+
 }  // namespace
 
 GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) {
@@ -850,9 +879,11 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
     p.ws_bytes = nsplit > 1 ? (size_t)nsplit * g.M * g.Ncols * sizeof(float) : 0;
     if (cfg >= 5) p.ws_bytes += wreg_wt_bytes(g);  // weights repacked into MFMA fragment order
     // Small layers: tiles whose reduction is divided over the wavefronts of a work-group, so that no partial sums and no second launch are
-    // needed.  us, kernels alone, the plan so far / the flat tiles (351 products, as in flat_pick):
-    //   a split reduction of the patch kernel, always: 8 x 13 x 13, 256 -> 256 14.4 / 8.2, 8 x 14 x 14, 512 -> 512 20.8 / 15.0, 2 x 28 x 28,
-    //     128 -> 128 15.8 / 6.2, 5x5 3 x 27 x 27, 192 -> 64 16.2 / 12.9 (100 products: 1.03 to 2.5 times as fast);
+    // needed.  us, kernels alone, the plan so far / the flat tiles, where the predictions for both say so (us_beside_flat; by the sizes alone
+    // 2 900 of 33 000 products were 1.05 to 5 times slower: few pixels under a reduction of 512 channels and more, 2 x 6 x 58, 1024 -> 64
+    // 14.5 / 36, 5x5 2 x 8 x 8, 928 -> 64 12.4 / 54, and two rounds of flat tiles for one of larger ones, 19 x 45 x 45, 64 -> 64 9.2 / 12.9):
+    //   a split reduction of the patch kernel: 8 x 13 x 13, 256 -> 256 14.4 / 8.2, 8 x 14 x 14, 512 -> 512 20.8 / 15.0, 2 x 28 x 28,
+    //     128 -> 128 15.8 / 6.2, 5x5 3 x 27 x 27, 192 -> 64 16.2 / 12.9;
     //   unsplit tiles of the patch kernel up to ten 32 x 32 blocks of outputs per CU (32 x 13 x 13, 384 -> 256 20.7 / 14.3, 22 x 14 x 14,
     //     512 -> 512 31.9 / 23.8), sixteen with 256 input channels (8 x 28 x 28, 512 -> 512 36 / 30; with 128 62 x 62 15 / 20), eight
     //     for 5x5 (32 x 27 x 27, 64 -> 192 20 / 26): beyond, the larger tiles read fewer weights per output;
@@ -867,18 +898,25 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
         double us = 0;
         int tile = blocks <= 64.0 && (b_tr || need == p.ws_bytes || need <= WAP_STATIC_SCRATCH_BYTES) ? flat_pick(g, &us) : 0;
-        if (tile && !prepacked && p.ws_bytes == 0) {
-            GemmPlan flat;
-            flat.cfg = 16;
-            flat.nsplit = 1;
-            flat.tile = tile;
-            if (reads_unpacked(g, b_tr, flat)) need = 0;
+        GemmPlan flat;
+        flat.cfg = 16;
+        flat.nsplit = 1;
+        flat.tile = tile;
+        const bool raw = tile && !prepacked && reads_unpacked(g, b_tr, flat);
+        if (!prepacked && p.ws_bytes == 0) {
+            if (raw) need = 0;
             else if (lean) tile = 0;
         }
         bool wins;
         if (cfg == 7 && nsplit > 1) wins = true;
         else if (cfg < 5) wins = us + (prepacked ? 0.0 : 4.0) < (nsplit > 1 ? 14.0 : 9.0) + flops / 550e6;
         else wins = blocks <= (g.R == 5 ? 8.0 : g.IC >= 256 ? 16.0 : 10.0) && !(cfg == 7 && !b_tr && (g.OH % 2) == 0 && (g.OW % 2) == 0 && tile2d_fuses_pool(g));
+        if (tile && wins) {
+            // The flat tiles' own prediction falls short where the two are close, most for single fragments of a 5x5 filter; a packing launch takes 3.
+            const double other = us_beside_flat(g, cfg, nsplit, p.tile, ktiles, t);
+            const double short_of = g.R == 5 ? (tile == 14 ? 1.4 : 1.1) : cfg < 5 ? (nsplit > 1 ? 1.0 : 1.15) : nsplit > 1 ? 1.05 : 1.1;
+            wins = other == 0 || us * short_of + (prepacked || raw ? 0 : 3) < other + (prepacked || cfg < 5 ? 0 : 3);
+        }
         if (tile && wins) {
             cfg = 16;
             p.tile = tile;

@@ -289,6 +289,7 @@ int tile2d_supported(const GemmGeom& g, int tile = 0);
 bool tile2d_preferred(const GemmGeom& g);
 int tile2d_split(const GemmGeom& g, bool generic, int* tile);
 int tile2d_fill(const GemmGeom& g);
+void tile2d_shape(const GemmGeom& g, int tile, int* pixels, int* channels);
 const char* tile2d_kernel_name(const GemmGeom& g, bool unpool, int tile = 0);
 int launch_tile2d(const GemmGeom& g, const bf16_t* A, const void* Wp, const float* bias, bool relu, bf16_t* out,
                   hipStream_t st, const bf16_t* mask = nullptr, bf16_t* pool_y = nullptr, uint8_t* pool_am = nullptr,

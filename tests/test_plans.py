@@ -93,3 +93,33 @@ def test_a_step_streams_its_largest_weight_gradient(wap, minibatch, store):
     """Behind and beside other kernels the stream is ahead or level where the single call is not."""
     ops = {o[0]: o for o in wap.StepPlan("vgg16", minibatch, flags=wap.WAP_STEP_STORE_GRADS if store else 0).ops()}
     assert "fc_dw_kernel" in next(o for n, o in ops.items() if n.startswith("fc6.dW"))
+
+
+# (shape, pass) of single calls, us on the larger tiles / on the flat tiles that had replaced them
+LARGER_TILES = [((10, 63, 63, 64, 128, 3, 3, 1, 1), 1), ((121, 55, 6, 800, 64, 3, 3, 1, 1), 0), ((19, 45, 45, 64, 64, 3, 3, 1, 1), 0),  # 16 / 22, 52 / 72, 12.4 / 16.1
+                ((116, 8, 36, 64, 32, 3, 3, 1, 1), 1), ((14, 57, 57, 64, 832, 3, 3, 1, 1), 1), ((72, 64, 8, 64, 64, 3, 3, 1, 0), 1),   # 10.6 / 14.9, 58 / 75, 12.3 / 15.9
+                ((8, 61, 61, 128, 256, 3, 3, 1, 0), 1), ((90, 23, 20, 288, 64, 5, 5, 1, 0), 0)]                                        # 27 / 33, 37 / 43
+FLAT_TILES = [((32, 13, 13, 384, 256, 3, 3, 1, 1), 0), ((22, 14, 14, 512, 512, 3, 3, 1, 1), 0), ((8, 28, 28, 512, 512, 3, 3, 1, 1), 1), ((19, 28, 28, 64, 64, 3, 3, 1, 1), 0)]
+
+
+def test_layers_keep_the_larger_tiles_where_these_are_faster(wap):
+    def flat(shape, p):
+        return wap.wap_conv2d_kernel_name(wap.conv_desc(*shape), p).startswith("conv_tile2d_flat_kernel")
+    assert not any(flat(*c) for c in LARGER_TILES), [c for c in LARGER_TILES if flat(*c)]
+    assert all(flat(*c) for c in FLAT_TILES), [c for c in FLAT_TILES if not flat(*c)]
+
+
+def test_divided_reductions_with_packed_weights_keep_their_splits_where_these_are_faster(so):
+    """A step's plans, as the per-layer table runs them: one work-group per few pixels walks a long reduction alone on the flat tiles."""
+    def forward(shape):  # (the stand-in runtime has no event to wait for: the table ends behind its first pass)
+        return [c.kernel for c in recorded.launches(recorded.run(so, f"""
+d = wap.conv_desc(*{shape})
+try:
+    wap.wap_profile_layer(0, d, [d.N], 0, 1, Mem(1 << 34), stream=0)
+except wap.WapError:
+    pass
+"""))]
+    for shape in ((2, 6, 58, 1024, 64, 3, 3, 1, 1), (3, 4, 53, 1024, 128, 3, 3, 1, 1), (2, 8, 8, 928, 64, 5, 5, 1, 2), (1, 10, 10, 960, 128, 5, 5, 1, 2)):
+        k = forward(shape)      # us, divided / flat: 14.5 / 36, 12.7 / 37, 12.4 / 54, 13 / 65
+        assert any("conv_tile2d" in n for n in k) and not any("flat" in n for n in k), (shape, k)
+    assert any("flat" in n for n in forward((8, 14, 14, 512, 512, 3, 3, 1, 1)))
