@@ -906,6 +906,7 @@ int tile2d_split(const GemmGeom& g, bool generic, int* tile) {
 // 256 50.9 / 42.1, 90 x 27 x 27 75.5 / 69.0 (192); strips of 56 x 56 maps / these, 256 -> 256 at 10 / 11 / 14 / 19 / 22 images 50.4 / 39.5
 // (128), 51.4 / 44.1 (160), 54.8 / 52.1 (192), 76.6 / 66.0 (160), 78.2 / 74.5 (192).  With less than 8 % to gain nothing is left of
 // it (64 x 28 x 28, 512 -> 512 188 / 186, 32 x 56 x 56, 256 -> 256 103.7 / 103.2: the clock under matrix load).
+// With one slice of channels a tile is its start: 128 pixels gain nothing on 64 (88 layers 0.98 .. 1.08, 8 x 16 x 26, 32 -> 640 12.4 / 13.1).
 // 256-pixel tiles: the 224-pixel strips where the fullest CU gets no more of them (112 x 112, 128 -> 128 at 3 / 6 / 8 / 11 / 16 / 22 / 32
 // images 22.1 / 21.0, 34.6 / 32.2, 35.7 / 34.5, 49.4 / 46.7, 64.0 / 60.1, 78.2 / 75.6, 106.6 / 103.4; one more tile at 10 39.5 / 45.5, 64 201 / 203).
 int tile2d_fill(const GemmGeom& g) {
@@ -924,7 +925,7 @@ int tile2d_fill(const GemmGeom& g) {
     int best = 0;
     double least = 0.92 * cost(own.variant == 1 ? 7 : own.fm);
     for (int fm : {6, 5, 4})
-        if (cost(fm) < least && fill_cfg(g, kTileFill + fm).fn) {
+        if (!(fm == 4 && own.fm == 2 && g.IC <= 32) && cost(fm) < least && fill_cfg(g, kTileFill + fm).fn) {
             best = kTileFill + fm;
             least = cost(fm);
         }

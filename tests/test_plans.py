@@ -123,3 +123,8 @@ except wap.WapError:
         k = forward(shape)      # us, divided / flat: 14.5 / 36, 12.7 / 37, 12.4 / 54, 13 / 65
         assert any("conv_tile2d" in n for n in k) and not any("flat" in n for n in k), (shape, k)
     assert any("flat" in n for n in forward((8, 14, 14, 512, 512, 3, 3, 1, 1)))
+
+
+@pytest.mark.parametrize("shape", [(6, 106, 10, 384, 32, 3, 3, 1, 1), (59, 28, 6, 256, 32, 3, 3, 1, 1), (13, 14, 14, 1024, 32, 3, 3, 1, 1), (8, 16, 26, 640, 32, 3, 3, 1, 1)])
+def test_one_slice_of_channels_keeps_its_short_tiles(wap, shape):
+    assert wap.wap_conv2d_kernel_name(wap.conv_desc(*shape), wap.WAP_PASS_BWD_DATA) == "conv_tile2d_kernel<1,0,2,1,false,true>"
