@@ -17,6 +17,7 @@
 //     accumulators (AGPRs); the issue order is pinned with sched_group_barrier because a single
 //     wavefront per SIMD has nothing else to hide a bubble.
 // Serves the "primary" convolution nodes of Section 3.2.2 (forward and backward halves of t_c, Eq. 1).
+#include "flat_runs.h"
 #include "wap_internal.h"
 
 namespace wap {
@@ -315,24 +316,6 @@ __global__ __launch_bounds__(NT) void conv_patch_kernel(const PArgs a) {
     }
 }
 
-// largest patch (in padded pixels) any 224-pixel tile of this geometry needs
-int max_patch_len(const GemmGeom& g) {
-    const int PH = g.OH + g.R - 1, PW = g.OW + g.S - 1;
-    const long OHW = (long)g.OH * g.OW;
-    auto pflat = [&](long m) {
-        long n = m / OHW, rem = m - n * OHW;
-        long oh = rem / g.OW, ow = rem - oh * g.OW;
-        return n * PH * PW + oh * PW + ow;
-    };
-    long worst = 0;
-    for (long m0 = 0; m0 < g.M; m0 += BM) {
-        long ml = (m0 + BM <= g.M ? m0 + BM : g.M) - 1;
-        long len = pflat(ml) + (long)(g.R - 1) * PW + (g.S - 1) + 1 - pflat(m0);
-        if (len > worst) worst = len;
-    }
-    return (int)worst;
-}
-
 template <int PV, int FN>
 int launch_patch_t(const PArgs& pa, hipStream_t st) {
     auto kfn = conv_patch_kernel<PV, FN>;
@@ -357,7 +340,7 @@ int patch_supported(const GemmGeom& g) {
     if (g.Ncols < 128 || g.M < BM * 32) return 0;      // thin or tiny shapes stay on the other kernels
     long a_elems = (long)(g.M / ((long)g.OH * g.OW)) * g.IH * g.IW * g.IC;
     if (a_elems * 2 >= (1L << 31)) return 0;
-    int len = max_patch_len(g);
+    const int len = flat_patch(flat_runs(g.M, g.OH, g.OW, BM), g.OW, g.R, g.S);  // largest patch any tile needs
     if (len > 560) return 0;
     return len <= 384 ? 384 : 560;
 }

@@ -23,10 +23,10 @@
 // the pixel its argmax names, so the max-pool backward costs no pass over the full-size gradient.
 // Serves the "primary" convolution nodes of Section 3.2.2 (forward and backward halves of t_c, Eq. 1).
 #include <algorithm>
-#include <numeric>
 #include <type_traits>
 #include <utility>
 
+#include "flat_runs.h"
 #include "wap_internal.h"
 
 namespace wap {
@@ -657,45 +657,13 @@ struct TileCfg {
     int fm;                   // variant 2: 32-pixel fragments per wavefront (2 or 4 .. 7: tiles of 64 or 128 .. 224 pixels)
 };
 int tile_pixels(const TileCfg& c) { return c.variant == 3 ? 192 : c.variant == 2 ? 32 * c.fm : c.variant == 1 ? 224 : 256; }
-// Tiles that begin at the same pixel of an image are alike: the first pixel behind all that differ.
-long flat_period(const GemmGeom& g, int bm) {
-    const long OHW = (long)g.OH * g.OW;
-    return std::min((long)g.M, OHW / std::gcd(OHW, (long)bm) * bm);
-}
-// most patch pixels (rows of OW + S - 1) any bm-pixel raster-order tile of this geometry loads
-int max_flat_patch(const GemmGeom& g, int bm) {
-    const int PH = g.OH + g.R - 1, PW = g.OW + g.S - 1;
-    const long OHW = (long)g.OH * g.OW;
-    auto pflat = [&](long m) {
-        long n = m / OHW, rem = m - n * OHW;
-        long oh = rem / g.OW, ow = rem - oh * g.OW;
-        return n * PH * PW + oh * PW + ow;
-    };
-    long worst = 0;
-    const long end = flat_period(g, bm);
-    for (long m0 = 0; m0 < end; m0 += bm) {
-        long ml = (m0 + bm <= g.M ? m0 + bm : g.M) - 1;
-        long len = pflat(ml) + (long)(g.R - 1) * PW + (g.S - 1) + 1 - pflat(m0);
-        if (len > worst) worst = len;
-    }
-    return (int)worst;
-}
+// most patch pixels any bm-pixel raster-order tile of this geometry loads
+int max_flat_patch(const GemmGeom& g, int bm) { return flat_patch(flat_runs(g.M, g.OH, g.OW, bm), g.OW, g.R, g.S); }
 // most LDS bytes one patch buffer of such a tile spans when patch rows are rwb bytes apart
-long max_flat_bytes(const GemmGeom& g, int bm, int rwb) {
-    const int PH = g.OH + g.R - 1;
-    const long OHW = (long)g.OH * g.OW;
-    auto lbyte = [&](long m) {
-        long n = m / OHW, rem = m - n * OHW;
-        long oh = rem / g.OW, ow = rem - oh * g.OW;
-        return (n * PH + oh) * rwb + ow * PITCH;
-    };
+long max_flat_bytes(const GemmGeom& g, const FlatRuns& f, int rwb) {
     long worst = 0;
-    const long end = flat_period(g, bm);
-    for (long m0 = 0; m0 < end; m0 += bm) {
-        long ml = (m0 + bm <= g.M ? m0 + bm : g.M) - 1;
-        long len = lbyte(ml) + (long)(g.R - 1) * rwb + (long)(g.S - 1) * PITCH + PITCH - lbyte(m0);
-        if (len > worst) worst = len;
-    }
+    for (int i = 0; i < f.n; ++i)
+        worst = std::max(worst, (long)(f.run[i].pixels - 1 + g.S) * PITCH + (long)f.run[i].rows * (rwb - g.OW * PITCH) + (long)(f.run[i].images + 1) * (g.R - 1) * rwb);
     return worst;
 }
 // Row stride that keeps fragments conflict-free across a row wrap: the next row's first pixel must fall into the bank
@@ -711,11 +679,12 @@ bool lds_layout(const GemmGeom& g, TileCfg* c) {
     const int width = flat ? g.OW : c->tw;
     const int dense = (width + g.S - 1) * PITCH;
     const int cands[2] = {(flat || (c->tw != 32)) ? conflict_free_stride(width, g.S) : dense, dense};
+    const FlatRuns runs = flat ? flat_runs(g.M, g.OH, g.OW, bm) : FlatRuns{};
     size_t best = 0;
     for (int pass = 0; pass < 2 && !best; ++pass)            // first two work-groups per CU, then one
         for (int k = 0; k < 2 && !best; ++k) {
             const int rwb = cands[k];
-            const long buf = flat ? max_flat_bytes(g, bm, rwb)
+            const long buf = flat ? max_flat_bytes(g, runs, rwb)
                                   : (long)(c->th + g.R - 2) * rwb + (long)(c->tw + g.S - 1) * PITCH;
             const long bufa = (buf + 15) / 16 * 16;
             const size_t smem = std::max((size_t)(2 * bufa) + 1024, stage);  // + the dump slots of stores without a pixel
