@@ -826,10 +826,12 @@ size_t c3_general_smem(const GemmGeom& g) {
 }
 }  // namespace
 
+// groups of output rows (conv_c3_rows.hip); forced to this file, the kernels here
+static bool c3_row_groups(const GemmGeom& g) { return g_force_fwd_cfg != 8 && conv_c3_rows_supported(g); }
 bool conv_c3_fwd_supported(const GemmGeom& g) {
     if (g.IC != 3 || g.div_h != 1 || g.div_w != 1 || (g.Ncols != 32 && g.Ncols != 64)) return false;
     if (c3_special(g)) return true;
-    if (conv_c3_rows_supported(g)) return true;
+    if (c3_row_groups(g)) return true;
     if (c3_fwd_strided(g)) return g_force_fwd_cfg == 8 || !conv_thin_fwd_few_tiles(g);
     // the gather: short reductions, ragged maps, patches too large to stage (conv_thin.hip)
     return c3_general_smem(g) <= 64 * 1024 && (g_force_fwd_cfg == 8 || !conv_thin_fwd_over_gather(g));
@@ -837,7 +839,7 @@ bool conv_c3_fwd_supported(const GemmGeom& g) {
 const char* conv_c3_fwd_kernel_name(const GemmGeom& g) {
     if (c3_rows(g)) return g.Ncols == 64 ? "conv_c3_fwd_rows_kernel<2>" : "conv_c3_fwd_rows_kernel<1>";
     if (c3_special(g)) return g.Ncols == 64 ? "conv_c3_fwd_kernel<2>" : "conv_c3_fwd_kernel<1>";
-    if (conv_c3_rows_supported(g)) return conv_c3_rows_kernel_name(g);
+    if (c3_row_groups(g)) return conv_c3_rows_kernel_name(g);
     if (c3_fwd_strided(g)) return g.Ncols == 64 ? "conv_c3_fwd_strided_kernel<2>" : "conv_c3_fwd_strided_kernel<1>";
     return g.Ncols == 64 ? "conv_c3_fwd_general_kernel<2>" : "conv_c3_fwd_general_kernel<1>";
 }
@@ -845,7 +847,7 @@ const char* conv_c3_fwd_kernel_name(const GemmGeom& g) {
 int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, bf16_t* y,
                        hipStream_t st) {
     if (!conv_c3_fwd_supported(g)) return set_error(WAP_EINVAL, "internal: 3-channel forward kernel not applicable");
-    if (conv_c3_rows_supported(g)) return launch_conv_c3_rows(g, x, w, bias, relu, y, st);
+    if (c3_row_groups(g)) return launch_conv_c3_rows(g, x, w, bias, relu, y, st);
     if (!c3_special(g) && c3_fwd_strided(g)) {
         C3FPlan p;
         if (!c3f_plan(g, &p)) return set_error(WAP_EINVAL, "internal: strided 3-channel forward plan");

@@ -173,6 +173,14 @@ CASES = [
     ("flat_42_5x5_pooled", (3, 8, 24, 64, 32, 5, 5, 1, 2), (142, -1, -1)),
     ("flat_44_5x5_pooled", (3, 12, 12, 128, 64, 5, 5, 1, 2), (144, -1, -1)),
     ("flat_picked_5x5_pooled", (12, 12, 14, 256, 32, 5, 5, 1, 2), (-1, -1, -1)),
+    # 3x3 on even maps (pooled dy) on the tilings whose other cases have odd ones
+    ("flat_14_even", (2, 12, 14, 64, 64, 3, 3, 1, 1), (114, -1, -1)),
+    ("flat_34_even", (3, 14, 14, 64, 64, 3, 3, 1, 1), (134, -1, -1)),
+    # an output row with all its input rows at a time, which takes what the groups of rows refuse (wider images) and other filters
+    ("c3_strided_forced_11x11_s4_w232_k32", (12, 31, 232, 3, 32, 11, 11, 4, 2), (8, 4, -1)),
+    ("c3_strided_forced_11x11_s4_w232_k64", (12, 31, 232, 3, 64, 11, 11, 4, 2), (8, 4, -1)),
+    ("c3_strided_forced_7x7_s4_k32", (6, 60, 136, 3, 32, 7, 7, 4, 2), (8, 4, -1)),
+    ("c3_strided_forced_7x7_s4_k64", (6, 60, 136, 3, 64, 7, 7, 4, 2), (8, 4, -1)),
 ]
 
 
