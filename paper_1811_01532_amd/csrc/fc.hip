@@ -335,13 +335,14 @@ bool fc_dx_supported(const GemmGeom& g) {
 void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
     const int steps = (g.IC + 16 * 2 * FW_WAVES - 1) / (16 * 2 * FW_WAVES);
     const int most = !lean || (g.Ncols <= 2048 && g.IC >= 8192) ? 16 : 1;
-    double least = 0;
+    double least = 0, whole = 0;  // whole: 16 features, undivided; a gain on it of less than 0.4 is none
     for (int f : {16, 8, 4})
         for (int n = 1; n <= most && n <= steps; ++n) {
             const long groups = (long)((g.Ncols + f - 1) / f) * n;
             if ((f < 16 || n > 1) && groups > kNumCU) break;
             const double us = 3.5 * ((groups + kNumCU - 1) / kNumCU) + (steps + n - 1) / n * (0.19 + 0.021 * (f + g.M)) + (n > 1 ? 2.3 + 0.05 * n : 0.0);
-            if (least == 0 || (us < 0.97 * least && us < least - 0.4)) {
+            if (least == 0 || (us < 0.97 * least && us < whole - 0.4)) {
+                if (least == 0) whole = us;
                 least = us;
                 *feat = f;
                 *nsplit = n;

@@ -128,3 +128,8 @@ except wap.WapError:
 @pytest.mark.parametrize("shape", [(6, 106, 10, 384, 32, 3, 3, 1, 1), (59, 28, 6, 256, 32, 3, 3, 1, 1), (13, 14, 14, 1024, 32, 3, 3, 1, 1), (8, 16, 26, 640, 32, 3, 3, 1, 1)])
 def test_one_slice_of_channels_keeps_its_short_tiles(wap, shape):
     assert wap.wap_conv2d_kernel_name(wap.conv_desc(*shape), wap.WAP_PASS_BWD_DATA) == "conv_tile2d_kernel<1,0,2,1,false,true>"
+
+
+def test_four_features_without_a_second_launch_where_they_fill_the_chip(wap):
+    """4096 -> 1000 at 8 rows: 250 work-groups of four features, 7.4 us, not 252 of sixteen over quarters of the reduction, 9."""
+    assert wap.wap_fc_workspace_bytes(wap.fc_desc(8, 4096, 1000), wap.WAP_PASS_FWD) == 0
