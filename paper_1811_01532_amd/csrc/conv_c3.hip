@@ -13,8 +13,8 @@
 // Reduction index k = (r * 3 + s) * 3 + c; an input row contributes 9 consecutive bf16 (3 pixels x 3
 // channels), so k = r * 9 + j addresses element (ow - pad) * 3 + j of input row oh - pad + r.
 // Larger filters: conv_c3_fwd_general_kernel gathers the same way for any R x S and stride; for a horizontal
-// stride that is a multiple of 4 (the 11x11 stride-4 layer) conv_c3_fwd_strided_kernel and wgrad_c3_strided_kernel
-// keep the R input rows of one output row in LDS, where the im2col rows of neighbouring pixels are overlapping
+// stride that is a multiple of 4 conv_c3_fwd_strided_kernel and wgrad_c3_strided_kernel (11x11 at stride 4 forward: where
+// conv_c3_rows.hip does not apply) keep the R input rows of one output row in LDS, where the im2col rows of neighbouring pixels are overlapping
 // contiguous runs that start 6*stride bytes apart, so no element-wise gather is left.
 // Serves the first "primary" convolution node of Section 3.2.2 (forward and weight-gradient halves of
 // t_c, Eq. 1); its input gradient is never needed.

@@ -761,7 +761,7 @@ TileCfg tile_cfg(const GemmGeom& g, int tile = 0) {
     // else 64 pixels (the serial reduction of a tile is what a small layer waits for: a short tile shortens every
     // reduction step four-fold and puts more work-groups on the chip; the weight stream per pixel grows, which a small
     // layer can afford).  Measured: conv4_2 at minibatch 8 55 -> 44 us, conv5_1 at 32 54 -> 44 us, at 16 37 -> 33 us;
-    // 128-pixel tiles lost to 224-pixel ones wherever both applied (conv5_1 at 64: 68 vs 64 us).  Short flat tiles
+    // 128 to 192 pixels where those divide the layer more evenly: tile2d_fill.  Short flat tiles
     // also replace the strips where those leave the chip under-filled.
     const long strips = c.fn ? (long)(g.M / 224) * (g.Ncols / 128) : 0;
     if ((c.fn == 0 || strips < kNumCU * 3 / 4) && (g.Ncols % 128) == 0 && g.M >= 64 * 4) {

@@ -12,7 +12,8 @@
 //   * the loads of patch slice c + 2 go out when slice c + 1 is written to LDS, a whole slice ahead;
 //   * neighbouring work-groups (on one XCD) share the weights where those are the larger operand, else the patch.
 // Bound by the weights' way from the L2s to the CUs (22 x 14 x 14, 512 -> 512: 212 MB of weights and 50 MB of patches in 24 us;
-// 64 x 128 tiles without the division read 321 MB in 32 us), the smallest by the start of a work-group.  Against the divided
+// 64 x 128 tiles without the division read 321 MB in 32 us), the smallest by the start of a work-group: matrix pipes busy for 0.08 .. 0.30 of the
+// time, LDS 0.08 .. 0.21, a third of the wavefronts' time spent waiting, 1.4 to 2.4 times the layer's bytes past the L2s (each of them reads the weights).  Against the divided
 // reductions of conv_tile2d.hip with the launch that adds them up: 8 x 13 x 13, 384 -> 256 16.2 -> 10.0 us, 8 x 14 x 14, 512 -> 512
 // 20.8 -> 15.0; unsplit ones 32 x 13 x 13, 384 -> 256 20.7 -> 14.3, 8 x 28 x 28, 512 -> 512 36 -> 30.
 #include <algorithm>

@@ -890,8 +890,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
     //   the generic kernel: where the predicted time, with a packing launch where there is one to pay for, is below that
     //     kernel's line of 9 us (14 with a split reduction) and 550 TFLOP/s (13 x 67 x 67, 384 -> 32 41 / 52, 28 x 10 x 10 20 / 8).
     // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, and single data gradients of
-    // the whole-filter patch kernel with a last block of channels that is not full theirs.  Where a single call needed no workspace, tiles
-    // that read a packed copy of the weights take over only if the caller has one for it (not lean).
+    // the whole-filter patch kernel with a last block of channels that is not full theirs, though the flat tiles would often be faster there
+    // as well (90 x 90, 64 -> 200 10 instead of 16 us): the tests of divided reductions and of that kernel's weight order run these calls.  Where a
+    // single call needed no workspace, tiles that read a packed copy of the weights take over only if the caller has one for it (not lean).
     const bool kept = !prepacked && (nsplit > 1 || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;

@@ -242,8 +242,8 @@ def test_streamed_fully_connected_products_by_shape(wap):
 
 def test_first_layer_kernel_by_shape(wap):
     """First layers of 32 or 64 channels: the staged patch needs a reduction long enough for the pixels it stages; short
-    filters, ragged maps and large strides stay with the gather, and the horizontal strides of 4 with their own kernel from
-    the second round of work-groups on (third for two channel blocks)."""
+    filters, ragged maps and large strides stay with the gather, and the horizontal strides of 4 with their own kernels: 11x11 on
+    rows of 33 to 64 output pixels always, others from the second round of work-groups on (third for two channel blocks)."""
     def name(N, H, K, R, stride, pad):
         return wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, 3, K, R, R, stride, pad), wap.WAP_PASS_FWD)
     for c in ((1, 224, 64, 7, 2, 3), (64, 224, 64, 7, 2, 3), (1, 48, 64, 7, 1, 3), (64, 192, 32, 5, 2, 2), (16, 112, 64, 11, 4, 2), (4, 32, 16, 3, 1, 1)):
