@@ -27,9 +27,10 @@
  *     matching *_workspace_bytes query (or what the call cannot do without, see ws); WAP_EHIP
  *     when a launch fails.  wap_last_error() gives the text of the last failure on the calling thread.
  *   - `ws` is scratch the caller provides (device memory, 256-byte aligned); it holds split
- *     reduction partials and packed weights and may be NULL when the query returns 0.  Convolution
- *     data gradients and fully-connected forward passes that can do without what the query asks
- *     for run a slower plan when it is not there.
+ *     reduction partials and packed weights and may be NULL when the query returns 0.  Data
+ *     gradients, weight gradients and fully-connected forward passes that can do with less than
+ *     the query asks for (of the first and the last also with nothing) run a slower plan when
+ *     they are given less.
  *   - Threads: calls may come from several host threads as long as each uses its own stream and
  *     buffers; one-time kernel attribute set-up is guarded.  wap_last_error() is per thread.
  */

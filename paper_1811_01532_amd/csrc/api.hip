@@ -134,6 +134,11 @@ static GemmPlan plan_with_ws(const GemmGeom& g, bool b_tr, const void* ws, size_
     const GemmPlan p = plan_fwd_like(g, b_tr);
     return p.ws_bytes && (!ws || ws_bytes < p.ws_bytes) ? plan_fwd_like(g, b_tr, false, true) : p;
 }
+// Weight gradients: the same, so that a workspace for the largest minibatch serves the smaller ones whose deeper splits would need more.
+static WgradPlan plan_with_ws(const WgradGeom& g, const void* ws, size_t ws_bytes) {
+    const WgradPlan p = plan_wgrad(g);
+    return p.ws_bytes && ws && ws_bytes < p.ws_bytes ? plan_wgrad(g, false, true) : p;
+}
 
 static int check_ws(size_t need, void* ws, size_t ws_bytes) {
     if (need == 0) return WAP_OK;
@@ -319,7 +324,7 @@ int wap_conv2d_bwd_weight(const wap_conv_desc* d, const void* x, const void* dy,
     WAP_TRY(check_ptr(dy, "dy"));
     WAP_TRY(check_ptr(dw, "dw"));
     WgradGeom g = geom_conv_wgrad(*d);
-    WgradPlan p = plan_wgrad(g);
+    WgradPlan p = plan_with_ws(g, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     return launch_wgrad(g, p, (const bf16_t*)x, (const bf16_t*)dy, dw, ws, (hipStream_t)stream);
 }
@@ -330,7 +335,7 @@ static int bwd_weight_sgd(const WgradGeom& g, const void* x, const void* dy, flo
     WAP_TRY(check_ptr(dy, "dy"));
     WAP_TRY(check_ptr(w32, "w32"));
     WAP_TRY(check_ptr(w_bf16, "w_bf16"));
-    WgradPlan p = plan_wgrad(g);
+    WgradPlan p = plan_with_ws(g, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     hipStream_t st = (hipStream_t)stream;
     if (wgrad_fuses_sgd(g, p)) {
@@ -421,7 +426,7 @@ int wap_conv2d_bwd_weight_pool2x2(const wap_conv_desc* d, const void* x, const v
     WAP_TRY(check_ptr(x, "x"));
     WAP_TRY(check_ptr(dw, "dw"));
     WgradGeom g = geom_conv_wgrad(*d);
-    WgradPlan p = plan_wgrad(g);
+    WgradPlan p = plan_with_ws(g, ws, ws_bytes);
     WAP_TRY(check_ws(p.ws_bytes, ws, ws_bytes));
     if (wgrad_fuses_unpool(g, p))
         return launch_wgrad(g, p, (const bf16_t*)x, (const bf16_t*)g_pool, dw, ws, (hipStream_t)stream, nullptr, argmax);
@@ -471,7 +476,7 @@ int wap_fc_bwd(const wap_fc_desc* d, const void* x, const void* Wt, const void* 
     GemmGeom gx = geom_fc_dx(*d);
     GemmPlan px = plan_fwd_like(gx, true);
     WgradGeom gw = geom_fc_dw(*d);
-    WgradPlan pw = plan_wgrad(gw);
+    WgradPlan pw = plan_with_ws(gw, ws, ws_bytes);
     size_t need = 0;
     if (dx) need = px.ws_bytes;
     if (dW && pw.ws_bytes > need) need = pw.ws_bytes;

@@ -12,6 +12,8 @@
 // Forward (up to 16 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt) or fewer, 16 wavefronts.
 // Data gradient: the reduction runs over the rows of Wt.  A lane loads CPL neighbouring columns of eight rows and turns
 // the 8 x CPL block around in registers (byte permutes); a work-group owns 16 * CPL columns, 8 wavefronts.
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -331,10 +333,10 @@ bool fc_dx_supported(const GemmGeom& g) {
 // 16 rows); a launch that adds up partial sums takes 2.3.  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
 // memory, 16 features and a division by 128 KB of Wt / this: 4096 -> 1000 7.7 / 9.1 / 10.3, 6.2 / 7.4 / 8.0; 9216 -> 512 10.4 / 11.8 / 13.3, 7.4 /
 // 8.0 / 8.7; 11264 -> 609 11.5 / 13.3 / 15.0, 8.5 / 9.2 / 9.9.
-// lean: divided only where rows of 256 KB and few features have always asked for a workspace.
+// lean: divided only so far that a work-group of 16 features streams 128 KB of Wt and the work-groups are no more than the CUs.
 void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
     const int steps = (g.IC + 16 * 2 * FW_WAVES - 1) / (16 * 2 * FW_WAVES);
-    const int most = !lean || (g.Ncols <= 2048 && g.IC >= 8192) ? 16 : 1;
+    const int most = lean ? std::max(1, std::min(kNumCU / ((g.Ncols + 15) / 16), g.IC / 4096)) : 16;
     double least = 0, whole = 0;  // whole: 16 features, undivided; a gain on it of less than 0.4 is none
     for (int f : {16, 8, 4})
         for (int n = 1; n <= most && n <= steps; ++n) {

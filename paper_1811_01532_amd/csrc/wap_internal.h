@@ -166,7 +166,7 @@ struct WgradPlan {
     int nsplit;
     size_t ws_bytes;
 };
-WgradPlan plan_wgrad(const WgradGeom& g, bool in_step = false);
+WgradPlan plan_wgrad(const WgradGeom& g, bool in_step = false, bool lean = false);  // lean: at least four reduction steps a split
 // unpool_am: dy is the gradient of the 2x2 / stride-2 max-pooled output (N x P/2 x Q/2 x K) and unpool_am the pool's
 // argmax; only where wgrad_fuses_unpool() says so.
 // sgd: apply the update to the parameters instead of storing dW (dw may then be NULL); only where wgrad_fuses_sgd()

@@ -433,7 +433,7 @@ int padded_cols(const WgradGeom& g) { return classify_mode(g) == 1 ? g.R * g.S *
 
 }  // namespace
 
-WgradPlan plan_wgrad(const WgradGeom& g, bool in_step) {
+WgradPlan plan_wgrad(const WgradGeom& g, bool in_step, bool lean) {
     WgradPlan p;
     int mode = classify_mode(g);
     int Kred = g.R * g.S * g.C;
@@ -493,7 +493,7 @@ WgradPlan plan_wgrad(const WgradGeom& g, bool in_step) {
     // 12.9 / 8.8, 2 x 28 x 28, 96 -> 96 11.6 / 10.0; 4.9 and 7.4 MB (27 x 27, 64 -> 192, 5x5) 11.3 / 11.9 and 12.4, one step and 9 MB 12.5 for 10.9.  (What is
     // whole with four stays whole: the launch that adds up two halves costs 3.  1345 layers of 1x1 to 11x11 filters: 0.81 of the time
     // in the mean, 33 of them 1.02 to 1.06, most where one and a half times the splits make more than 3 MB of sums.)
-    if (nsplit >= 2 && nsplit < want) {
+    if (!lean && nsplit >= 2 && nsplit < want) {
         const long deeper = std::min({want, ((long)ktiles + 1) / 2, (long)(4.8e6 / (4.0 * g.K * Kred))});
         if (deeper > nsplit) nsplit = (int)deeper;
     }

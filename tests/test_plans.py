@@ -133,3 +133,19 @@ def test_one_slice_of_channels_keeps_its_short_tiles(wap, shape):
 def test_four_features_without_a_second_launch_where_they_fill_the_chip(wap):
     """4096 -> 1000 at 8 rows: 250 work-groups of four features, 7.4 us, not 252 of sixteen over quarters of the reduction, 9."""
     assert wap.wap_fc_workspace_bytes(wap.fc_desc(8, 4096, 1000), wap.WAP_PASS_FWD) == 0
+
+
+def test_calls_run_in_the_workspace_they_always_took(so):
+    """One workspace for the largest minibatch serves the smaller ones, whose deeper splits would ask for more: the last, shorter batch."""
+    calls = recorded.launches(recorded.run(so, """
+m = Mem(1 << 34)
+largest = wap.wap_conv2d_workspace_bytes(wap.conv_desc(100, 15, 15, 64, 32, 3, 3, 1, 0), wap.WAP_PASS_BWD_WEIGHT)
+d = wap.conv_desc(64, 15, 15, 64, 32, 3, 3, 1, 0)
+assert largest < wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)
+w = Mem(largest)
+wap.wap_conv2d_bwd_weight(d, m, m, m, w, stream=0)
+wap.wap_conv2d_bwd_weight_sgd(d, m, m, m, m, 0.1, m, w, stream=0)
+wap.wap_fc_fwd(wap.fc_desc(7, 25088, 500), m, m, None, m, Mem(6 * 4 * 7 * 500), stream=0)
+wap.wap_fc_fwd(wap.fc_desc(1, 9216, 512), m, m, None, m, Mem(2 * 4 * 512), stream=0)
+"""))
+    assert sum("wgrad_kernel" in c.kernel for c in calls) == 2 and sum("fc_fwd_kernel" in c.kernel for c in calls) == 2, calls
