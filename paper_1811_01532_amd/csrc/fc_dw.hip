@@ -6,7 +6,11 @@
 //     block take the columns 4 n + c (c = 0 .. 3), so that a lane ends with float4s of the row-major matrix and a wavefront
 //     moves whole 256-byte runs of four rows, with no pass through the LDS;
 //   * a wavefront walks down the rows of its columns; the operand of x stays in registers, the old weights of the next
-//     block are fetched as soon as those of the present one have been used.
+//     block are fetched as soon as those of the present one have been used;
+//   * ONCE: the fp32 matrix, which nothing reads before it would have left the cache, passes it (non-temporal).  The bf16 copy then
+//     stays there for the forward pass, and the cache holds fewer dirty lines that the next reads have to wait for: AlexNet-style
+//     step at 8 / 32 images 395 / 520 -> 362 / 487 us (the copy past the cache as well: 374, 500), three in turn, whose copies the cache
+//     does not hold, 399 / 530 -> 394 / 509; VGG-16 at 8 1383 -> 1369.
 #include "wap_internal.h"
 
 namespace wap {
@@ -28,8 +32,9 @@ struct DwArgs {
 constexpr unsigned kNowhere = 0x80000000u;  // beyond every buffer here (all below 2 GiB): loads zeros, stores nothing
 
 // NB: blocks of 32 batch rows; CB: blocks of 64 columns of a wavefront
-template <int NB, int CB, bool SGD>
+template <int NB, int CB, bool SGD, bool ONCE>
 __global__ __launch_bounds__(256, 2) void fc_dw_kernel(const DwArgs a) {
+    constexpr int NT = ONCE ? 2 : 0;  // cache policy of the buffer accesses: non-temporal
     const int lane = threadIdx.x & 63, n = lane & 15, kg = lane >> 4;
     const unsigned wave = blockIdx.x * 4 + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // units [u0, u1), down the rows of one block of columns after the other (side by side, 2 KB of a row to a work-group, 4096 x 4096
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void fc_dw_kernel(const DwArgs a) {
     auto load_old = [&](int cb, int rb, int c) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            old[c][e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, offset(cb, rb, c, e), 0, 0));
+            old[c][e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, offset(cb, rb, c, e), 0, NT));
     };
 
     int cb = (int)(u0 / (unsigned)a.rowb), rb = (int)(u0 - (unsigned)cb * (unsigned)a.rowb);
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void fc_dw_kernel(const DwArgs a) {
                     }
                     __builtin_amdgcn_raw_buffer_store_b64(pk, rB, off >> 1, 0, 0);
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rW, off, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rW, off, 0, NT);
             }
             if (SGD) load_old(ncb, nrb, c);
             __builtin_amdgcn_sched_barrier(0);
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(256, 2) void fc_dw_kernel(const DwArgs a) {
 }
 
 template <int NB, int CB>
-int launch_dw(DwArgs a, int max_groups, hipStream_t st) {
+int launch_dw(DwArgs a, int max_groups, bool once, hipStream_t st) {
     a.colb = (a.in + 64 * CB - 1) / (64 * CB);
     a.rowb = (a.out + 15) / 16;
     a.units = (unsigned)a.colb * (unsigned)a.rowb;
@@ -151,8 +156,10 @@ int launch_dw(DwArgs a, int max_groups, hipStream_t st) {
     if (groups > 4u * kNumCU) groups = 4u * kNumCU;
     if (max_groups > 0 && groups > (unsigned)max_groups) groups = (unsigned)max_groups;
     a.waves = groups * 4;
-    if (a.w32) hipLaunchKernelGGL((fc_dw_kernel<NB, CB, true>), dim3(groups), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((fc_dw_kernel<NB, CB, false>), dim3(groups), dim3(256), 0, st, a);
+    if (a.w32 && once) hipLaunchKernelGGL((fc_dw_kernel<NB, CB, true, true>), dim3(groups), dim3(256), 0, st, a);
+    else if (a.w32) hipLaunchKernelGGL((fc_dw_kernel<NB, CB, true, false>), dim3(groups), dim3(256), 0, st, a);
+    else if (once) hipLaunchKernelGGL((fc_dw_kernel<NB, CB, false, true>), dim3(groups), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((fc_dw_kernel<NB, CB, false, false>), dim3(groups), dim3(256), 0, st, a);
     return check_launch("fc_dw");
 }
 
@@ -186,7 +193,7 @@ bool fc_dw_supported(const WgradGeom& g, bool in_step) {
     return g.N <= 96 && one_round;
 }
 
-int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, hipStream_t st) {
+int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, bool once, hipStream_t st) {
     DwArgs a = {x, dy, dw, nullptr, nullptr, 0.f, g.N, g.C, g.K, 0, 0, 0u, 0u};
     if (sgd) {
         a.w32 = sgd->w32;
@@ -196,11 +203,11 @@ int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* d
     // Beside the convolutions of a step (max_groups: a work-group per CU), one / two of them per CU: AlexNet-style at 32 images 542 / 544 us,
     // VGG-16 at 3 and 8 1062 / 1083, 1499 / 1508; at 64, where a wavefront's loads of x delay its stream, 718 / 700.  (Half of the
     // CUs: 585, 1146, 1588, 714.)
-    if (g.N <= 32) return launch_dw<1, 2>(a, max_groups, st);
+    if (g.N <= 32) return launch_dw<1, 2>(a, max_groups, once, st);
     max_groups *= 2;
-    if (g.N <= 64) return launch_dw<2, 2>(a, max_groups, st);
-    if (g.N <= 96) return launch_dw<3, 1>(a, max_groups, st);
-    return launch_dw<4, 1>(a, max_groups, st);
+    if (g.N <= 64) return launch_dw<2, 2>(a, max_groups, once, st);
+    if (g.N <= 96) return launch_dw<3, 1>(a, max_groups, once, st);
+    return launch_dw<4, 1>(a, max_groups, once, st);
 }
 
 }  // namespace wap

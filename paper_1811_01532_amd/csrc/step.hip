@@ -191,6 +191,7 @@ struct wap_step_plan {
     size_t ws2_off = 0;                      // workspace of the operations that run beside others
     bool forks = false;                      // the list has such operations, one run of them
     size_t n_params = 0;
+    bool once = false;                       // the parameters pass the cache (beyond_cache): a step touches them once
     size_t w32_off = 0, dw_off = 0, wb_off = 0;
     mutable std::vector<hipEvent_t> events;  // cached by wap_step_time
     std::vector<WgradGroup> groups;
@@ -240,7 +241,8 @@ int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_
             return launch_wgrad(op.wg, op.wp, (const bf16_t*)(base + op.t0), (const bf16_t*)(base + op.t1),
                                 (float*)(base + op.t2), ws, st, ev_mid,
                                 op.unpool ? (const uint8_t*)(base + op.t3) : nullptr, op.fuse_sgd ? &sgd : nullptr,
-                                beside ? kNumCU : 0);  // (one work-group per CU: a grid that fills the chip lets nothing in beside it)
+                                beside ? kNumCU : 0,  // (one work-group per CU: a grid that fills the chip lets nothing in beside it)
+                                p->once);
         }
         case OP_WGRAD_GROUP: {
             const WgradGroup& wg = p->groups[op.group];
@@ -272,7 +274,7 @@ int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_
             return launch_colsum_f32_multi(p->colsumjobs, base, st);
         case OP_SGD:
             return launch_sgd(op.n, (float*)(base + op.t0), (const float*)(base + op.t1), p->lr,
-                              (bf16_t*)(base + op.t2), st);
+                              (bf16_t*)(base + op.t2), p->once, st);
     }
     return set_error(WAP_EINVAL, "internal: unknown op");
 }
@@ -378,6 +380,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
             np += align_up(bcount[i], 64);
         }
     p->n_params = np;
+    p->once = beyond_cache((fuse_update ? 6.0 : 10.0) * np);
     p->w32_off = p->add("params.w32", np * 4);
     p->dw_off = p->add("params.dw", np * 4);
     p->wb_off = p->add("params.w", np * 2);

@@ -55,6 +55,11 @@ constexpr double kPeakBf16Tflops = 2516.6;  // 256 CU x 4096 FLOP/clk x 2.4 GHz
 constexpr double kPeakHbmGBs = 8000.0;
 constexpr int kNumCU = 256;
 constexpr int kNumXCD = 8;
+// Memory that a call or a step passes over once, in bytes: beyond the 256 MiB that the chip caches, what is kept there on the way
+// (non-temporal accesses do not) only drives out what is used again, and its dirty lines are written back when something else is
+// read.  Update of 16.8, 67.1 and 134 M weights (10 bytes each), one 16-byte group a thread, through / past the cache 29, 164, 321 /
+// 35, 127, 250 us.
+inline bool beyond_cache(double bytes) { return bytes > 268435456.0; }
 
 // ---- SGD update fused into the kernel that produces a weight gradient ----
 // Instead of storing dW, the producer applies w32 <- w32 - lr * dW to the fp32 master weights and re-derives the
@@ -172,9 +177,10 @@ WgradPlan plan_wgrad(const WgradGeom& g, bool in_step = false, bool lean = false
 // sgd: apply the update to the parameters instead of storing dW (dw may then be NULL); only where wgrad_fuses_sgd()
 // says so.
 // max_groups: most work-groups of a generic kernel's grid, which then walk the tiles (0: one for every tile).
+// once: the fp32 matrix that an unsplit kernel writes (dw, or the sgd's w32) passes the cache (beyond_cache)
 int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, const bf16_t* dy,
                  float* dw, void* ws, hipStream_t st, hipEvent_t ev_mid = nullptr, const uint8_t* unpool_am = nullptr,
-                 const SgdFuse* sgd = nullptr, int max_groups = 0);
+                 const SgdFuse* sgd = nullptr, int max_groups = 0, bool once = false);
 bool wgrad_fuses_unpool(const WgradGeom& g, const WgradPlan& plan);
 bool wgrad_fuses_sgd(const WgradGeom& g, const WgradPlan& plan);
 const char* wgrad_kernel_name(const WgradGeom& g, const WgradPlan& plan, bool unpool);
@@ -245,9 +251,9 @@ int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, cons
                   hipStream_t st);
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
 
-// fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups: as launch_wgrad
+// fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups, once: as launch_wgrad
 bool fc_dw_supported(const WgradGeom& g, bool in_step);
-int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, hipStream_t st);
+int launch_fc_dw(const WgradGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, const SgdFuse* sgd, int max_groups, bool once, hipStream_t st);
 
 // weights-in-registers large-tile kernel (conv_wreg.hip)
 bool wreg_supported(const GemmGeom& g);
@@ -335,7 +341,7 @@ int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_
                        const bf16_t* ry, bf16_t* dx, hipStream_t st);
 int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labels, float* loss,
                         float* row_loss, bf16_t* dz, hipStream_t st);
-int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, hipStream_t st);
+int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, bool once, hipStream_t st);
 int launch_cast(size_t n, const float* src, bf16_t* dst, hipStream_t st);
 
 // descriptor -> kernel geometry (after validation)

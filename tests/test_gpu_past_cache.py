@@ -1,0 +1,49 @@
+"""GPU: updates on either side of the size from which the parameters pass the cache give the same bits, whole and in pieces."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LINE = 268435456 // 10  # up to this many parameters (fp32, gradient, bf16 copy) fit the cache
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 1023, 1027, LINE, LINE + 1, LINE + 6])
+@pytest.mark.parametrize("copy", [True, False])
+def test_update_whole_and_in_pieces(n, copy):
+    import paper_1811_01532_amd as wap
+    print(f"[case] sgd {n} {copy}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    w, dw = (torch.randn(n + 8, generator=g, device="cuda") for _ in range(2))
+    want = torch.addcmul(w[:n].double(), dw[:n].double(), torch.tensor(-0.1, device="cuda").double()).float()  # fp64: at most a tie apart
+    w2, wb, wb2 = w.clone(), *(torch.full((n + 8,), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    wap.wap_sgd_update(n, w, dw, 0.1, wb if copy else None)
+    piece = (n // 3 + 7) // 8 * 8 + 8
+    for at in range(0, n, piece):
+        m = min(piece, n - at)
+        wap.wap_sgd_update(m, w2[at:at + m], dw[at:at + m], 0.1, wb2[at:at + m] if copy else None)
+    torch.cuda.synchronize()
+    assert torch.equal(w, w2) and torch.equal(wb.view(torch.int16), wb2.view(torch.int16))
+    assert (w[:n] - want).abs().max() <= 2.0 ** -22 * want.abs().max()
+    assert not copy or torch.equal(wb[:n], w[:n].to(torch.bfloat16))
+    assert (wb[n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("B,n_in,n_out", [(5, 11008, 4096), (70, 11008, 4096), (130, 11008, 4096)])  # 45 M parameters, 6 bytes each
+def test_fused_update_past_the_cache(B, n_in, n_out):
+    import paper_1811_01532_amd as wap
+    print(f"[case] fc dW + update {B} x {n_in} -> {n_out}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x, g = torch.randn(B, n_in, generator=gen, device="cuda").bfloat16(), torch.randn(B, n_out, generator=gen, device="cuda").bfloat16()
+    n, d = n_in * n_out, wap.fc_desc(B, n_in, n_out)
+    nws = wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_BWD_WEIGHT)
+    ws = torch.empty(nws + 256, dtype=torch.uint8, device="cuda") if nws else None
+    w32 = torch.randn(n, generator=gen, device="cuda")
+    w2, dw = w32.clone(), torch.empty(n, device="cuda")
+    wb, wb2 = (torch.empty(n, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    assert wap.wap_fc_bwd_weight_sgd_fused(d)
+    wap.wap_fc_bwd_weight_sgd(d, x, g, w32, wb, 0.05, None, ws)
+    wap.wap_fc_bwd(d, x, None, g, None, dw, ws)
+    for at in range(0, n, n // 8):
+        wap.wap_sgd_update(n // 8, w2[at:at + n // 8], dw[at:at + n // 8], 0.05, wb2[at:at + n // 8])
+    torch.cuda.synchronize()
+    assert torch.equal(w32, w2) and torch.equal(wb.view(torch.int16), wb2.view(torch.int16))
