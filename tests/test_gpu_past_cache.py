@@ -1,4 +1,4 @@
-"""GPU: updates on either side of the size from which the parameters pass the cache give the same bits, whole and in pieces."""
+"""GPU: updates and ReLU derivatives on either side of the size from which they pass the cache give the same bits, whole and in pieces."""
 import pytest
 import torch
 
@@ -26,6 +26,22 @@ def test_update_whole_and_in_pieces(n, copy):
     assert (w[:n] - want).abs().max() <= 2.0 ** -22 * want.abs().max()
     assert not copy or torch.equal(wb[:n], w[:n].to(torch.bfloat16))
     assert (wb[n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2049, 268435456 // 6, 268435456 // 6 + 5, 268435456 // 3 + 3])
+def test_relu_derivative(n, in_place):
+    import paper_1811_01532_amd as wap
+    print(f"[case] relu_bwd {n} {in_place}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dy, y = (torch.randn(n + 8, generator=g, device="cuda").bfloat16() for _ in range(2))
+    y[:n:5] = 0.0
+    dx = dy.clone() if in_place else torch.full_like(dy, 7.0)
+    tail = dx[n:].clone()
+    wap.wap_relu_bwd(dx if in_place else dy, y, dx, n)
+    torch.cuda.synchronize()
+    assert torch.equal(dx[:n].view(torch.int16), torch.where(y[:n] > 0, dy[:n], torch.zeros_like(dy[:n])).view(torch.int16))
+    assert torch.equal(dx[n:], tail)
 
 
 @pytest.mark.parametrize("B,n_in,n_out", [(5, 11008, 4096), (70, 11008, 4096), (130, 11008, 4096)])  # 45 M parameters, 6 bytes each
