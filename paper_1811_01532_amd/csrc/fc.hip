@@ -9,7 +9,7 @@
 //     divides it over work-groups: fp32 partial sums through memory and a second launch of 5 .. 7 us.
 //   * Every load of the next steps is issued before the products of the present ones, in two register sets.
 //   * Row lengths that are no multiple of 8 are read with unaligned loads, the last vector moved back to end with the row.
-// Forward (up to 16 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt) or fewer, 16 wavefronts.
+// Forward (up to 64 rows): a work-group owns 16 output features (v_mfma_f32_16x16x32_bf16, 16 rows of Wt) or fewer, 16 wavefronts.
 // Data gradient: the reduction runs over the rows of Wt.  A lane loads CPL neighbouring columns of eight rows and turns
 // the 8 x CPL block around in registers (byte permutes); a work-group owns 16 * CPL columns, 8 wavefronts.
 #include <algorithm>
@@ -52,11 +52,11 @@ __device__ __forceinline__ bf16x8 ldb128(__amdgpu_buffer_rsrc_t r, unsigned off)
 
 constexpr int FW_WAVES = 16;
 
-// VEC8: rows are 16-byte aligned (in % 8 == 0)
-template <bool VEC8>
+// VEC8: rows are 16-byte aligned (in % 8 == 0); NB: blocks of 16 batch rows
+template <bool VEC8, int NB>
 __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
-    constexpr int U = 4;  // 32-deep steps per register set
-    __shared__ f32x4_t red[FW_WAVES][64];
+    constexpr int U = NB == 1 ? 4 : 2;  // 32-deep steps per register set
+    __shared__ f32x4_t red[NB][FW_WAVES][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = lane & 15, kg = lane >> 4;
     const int o0 = blockIdx.x * a.feat;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
     // 24.2 / 16.4, 18.2, 21.1; 4096 -> 4096 9.7, 10.7, 12.4 / 9.2, 9.9, 10.8; 6 x 25088 -> 4096 46.2 / 40.0.  Cached ones 1 to 2 %, short or
     // unaligned rows the same.
     auto step_of = [](int u) { return u / 2 * 2 * FW_WAVES + u % 2; };
-    bf16x8 fw[2][U], fx[2][U];
+    bf16x8 fw[2][U], fx[2][U][NB];
     auto load = [&](int set, int st) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -84,10 +84,13 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
             const bool ok = s < last && k < a.in;
             if (!VEC8 && k > a.in - 8) k = a.in - 8;  // the row's last vector, moved back to end with the row
             fw[set][u] = ldb128(rW, ok ? off + (unsigned)k * 2u : kNowhere);
-            fx[set][u] = ldb128(rX, ok ? off + (unsigned)k * 2u : kNowhere);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) fx[set][u][b] = ldb128(rX, ok ? off + (unsigned)(b * 16 * a.in + k) * 2u : kNowhere);
         }
     };
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto mul = [&](int set, int st) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -96,9 +99,14 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
                 const int k = (st + step_of(u)) * 32 + kg * 8;
 #pragma unroll
                 for (int e = 0; e < 7; ++e)
-                    if (e < k - (a.in - 8)) fx[set][u][e] = fw[set][u][e] = (__bf16)0.f;
+                    if (e < k - (a.in - 8)) {
+                        fw[set][u][e] = (__bf16)0.f;
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) fx[set][u][b][e] = (__bf16)0.f;
+                    }
             }
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][u], fx[set][u], acc, 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][u], fx[set][u][b], acc[b], 0, 0, 0);
         }
     };
     constexpr int STRIDE = U * FW_WAVES;
@@ -117,16 +125,17 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
         if (st >= last) break;
     }
 
-    // lane: batch row lane & 15, output features (lane >> 4) * 4 .. + 3
-    red[wave][lane] = acc;
-    __syncthreads();
-    if (tid >= 64) return;
-    f32x4_t s = red[0][lane];
+    // lane: batch row lane & 15 of the block, output features (lane >> 4) * 4 .. + 3; wavefront b adds up block b
 #pragma unroll
-    for (int w = 1; w < FW_WAVES; ++w) s += red[w][lane];
-    const int o = o0 + kg * 4;
-    if (row >= a.B) return;
-    const size_t e0 = (size_t)row * a.out + o;
+    for (int b = 0; b < NB; ++b) red[b][wave][lane] = acc[b];
+    __syncthreads();
+    if (wave >= NB) return;
+    f32x4_t s = red[wave][0][lane];
+#pragma unroll
+    for (int w = 1; w < FW_WAVES; ++w) s += red[wave][w][lane];
+    const int o = o0 + kg * 4, bi = wave * 16 + row;
+    if (bi >= a.B) return;
+    const size_t e0 = (size_t)bi * a.out + o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (o + e >= o0 + orows) continue;
@@ -292,9 +301,26 @@ bool below_2g(double elems) { return elems * 2.0 < 2147483648.0; }
 // enough to be split there and short enough here: 64 -> 25088 17 against 4.5, 64 -> 6000 6.2 against 4.4, 512 -> 8192 7.1
 // against 8.7, 2048 -> 8192 10.4 against 11.4, 4096 -> 9216 23.3 against 19.4.  Rows that are no multiple of 64, which
 // the generic kernel loads more slowly, move that line: 600 -> 10000 8.7 against 10.1, 1000 -> 25088 20.0 against 19.6.
-bool fc_fwd_supported(const GemmGeom& g) {
-    if (!is_fc(g) || g.M > 16 || g.IC < 8 || !below_2g(16.0 * g.IC)) return false;
+//
+// 17 .. 64 rows: a wavefront multiplies its operand of Wt with two or four blocks of rows.  The batch operand is then most of what a
+// work-group reads, so this is ahead while Wt is small or short (us, tiles of the generic kernel / this, Wt from memory: 32 rows, 4096 -> 1000
+// 12.3 / 8.7, 9216 -> 512 14.6 / 10.5, 1000 -> 2000 9.8 / 5.3, 17 x 4096 -> 4096 14.8 / 12.1; 64 rows, 4096 -> 512 11.3 / 9.4) and far behind
+// where it is large (32 x 9216 -> 4096 21.6 / 31.9, 64 x 25088 -> 4096 46 / 128).  The line is drawn by the two predictions: this kernel's
+// (fc_fwd_plan), and the generic one's, fitted to 253 shapes of 17 .. 64 rows, 200 .. 25000 inputs and 64 .. 12000 outputs, cached and from memory
+// (rms error 12 %): 175 of them come here, all shapes take 0.75 of their time (geometric mean; 0.74 with the better kernel for each) and
+// only unaligned rows of a large Wt were slower (28 x 4387 -> 9504 91 instead of 52): these stay.  Steps, AlexNet-style at 32 and VGG-16 at
+// 22 images, 512.4 / 508.3 and 2783.5 / 2780.4.
+bool fc_fwd_supported(const GemmGeom& g, bool in_step, bool lean) {
+    if (!is_fc(g) || g.M > 64 || g.IC < 8 || !below_2g((double)g.M * g.IC) || !below_2g(16.0 * g.IC)) return false;
     const bool quick = (g.IC % 64) == 0;  // the generic kernel's fast mode
+    if (g.M > 16) {
+        const double k = g.IC, mb = 2e-6 * k * g.Ncols;
+        if ((g.IC % 8) != 0 && mb > 40.0) return false;
+        const double generic = 7.6 + 0.13 * mb + 0.39e-3 * std::min(k, 16384.0) + 0.024 * g.M + (quick ? 0.0 : 0.46 + 0.03 * mb) +
+                               ((g.IC % 8) != 0 || (g.Ncols % 4) != 0 ? 2.0 : 0.0) + ((g.IC % 8) != 0 ? 0.33 * mb : 0.0);
+        int feat, nsplit;
+        return fc_fwd_plan(g, lean, &feat, &nsplit) < 0.95 * generic + (in_step ? 2.0 : 0.0);  // (a step's next kernel waits for the second launch)
+    }
     if (g.Ncols <= 4096) return !quick || g.M <= 6 || (double)g.IC * g.Ncols <= 50e6;
     return quick ? g.Ncols <= 8192 && g.IC >= 256 && g.IC <= 2048 : 25.0 * g.IC >= g.Ncols;
 }
@@ -333,16 +359,21 @@ bool fc_dx_supported(const GemmGeom& g) {
 // 16 rows); a launch that adds up partial sums takes 2.3.  More work-groups than CUs run one after another.  us at 1 / 8 / 16 rows, weights from
 // memory, 16 features and a division by 128 KB of Wt / this: 4096 -> 1000 7.7 / 9.1 / 10.3, 6.2 / 7.4 / 8.0; 9216 -> 512 10.4 / 11.8 / 13.3, 7.4 /
 // 8.0 / 8.7; 11264 -> 609 11.5 / 13.3 / 15.0, 8.5 / 9.2 / 9.9.
-// lean: divided only so far that a work-group of 16 features streams 128 KB of Wt and the work-groups are no more than the CUs.
-void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
+// lean: divided only so far that a work-group of 16 features streams 128 KB of Wt and the work-groups are no more than the CUs; with more than 16
+// rows not at all, for calls of that kind that needed no workspace take none.  More than 16 rows: half as many steps in flight, and a sum of
+// twice or four times as many partial results (fitted to the 253 shapes above).  Returns the predicted us.
+double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
+    const bool rows = g.M > 16;
+    const double start = rows ? 4.2 : 3.5, step = rows ? 0.25 : 0.19, sum = rows ? 3.3 : 2.3;
     const int steps = (g.IC + 16 * 2 * FW_WAVES - 1) / (16 * 2 * FW_WAVES);
-    const int most = lean ? std::max(1, std::min(kNumCU / ((g.Ncols + 15) / 16), g.IC / 4096)) : 16;
+    const int most = lean && rows ? 1 : lean ? std::max(1, std::min(kNumCU / ((g.Ncols + 15) / 16), g.IC / 4096)) : 16;
     double least = 0, whole = 0;  // whole: 16 features, undivided; a gain on it of less than 0.4 is none
     for (int f : {16, 8, 4})
         for (int n = 1; n <= most && n <= steps; ++n) {
             const long groups = (long)((g.Ncols + f - 1) / f) * n;
             if ((f < 16 || n > 1) && groups > kNumCU) break;
-            const double us = 3.5 * ((groups + kNumCU - 1) / kNumCU) + (steps + n - 1) / n * (0.19 + 0.021 * (f + g.M)) + (n > 1 ? 2.3 + 0.05 * n : 0.0);
+            const long rounds = (groups + kNumCU - 1) / kNumCU;
+            const double us = start * rounds + (rows ? rounds : 1) * ((steps + n - 1) / n) * (step + 0.021 * (f + g.M)) + (n > 1 ? sum + 0.05 * n : 0.0);
             if (least == 0 || (us < 0.97 * least && us < whole - 0.4)) {
                 if (least == 0) whole = us;
                 least = us;
@@ -350,16 +381,26 @@ void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
                 *nsplit = n;
             }
         }
+    return least;
 }
+
+namespace {
+template <int NB>
+int launch_fwd(const FcArgs& a, dim3 grid, hipStream_t st) {
+    if ((a.in % 8) == 0) hipLaunchKernelGGL((fc_fwd_kernel<true, NB>), grid, dim3(64 * FW_WAVES), 0, st, a);
+    else hipLaunchKernelGGL((fc_fwd_kernel<false, NB>), grid, dim3(64 * FW_WAVES), 0, st, a);
+    return check_launch("fc_fwd");
+}
+}  // namespace
 
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st) {
     FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0, feat};
     a.steps_per_split = ((g.IC + 31) / 32 + nsplit - 1) / nsplit;
-    const dim3 grid((g.Ncols + a.feat - 1) / a.feat, nsplit), block(64 * FW_WAVES);
-    if ((g.IC % 8) == 0) hipLaunchKernelGGL(fc_fwd_kernel<true>, grid, block, 0, st, a);
-    else hipLaunchKernelGGL(fc_fwd_kernel<false>, grid, block, 0, st, a);
-    return check_launch("fc_fwd");
+    const dim3 grid((g.Ncols + a.feat - 1) / a.feat, nsplit);
+    if (g.M <= 16) return launch_fwd<1>(a, grid, st);
+    if (g.M <= 32) return launch_fwd<2>(a, grid, st);
+    return launch_fwd<4>(a, grid, st);
 }
 
 namespace {

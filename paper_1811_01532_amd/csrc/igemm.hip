@@ -796,7 +796,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         p.ws_bytes = 0;
         return p;
     }
-    if (g_force_fwd_cfg < 0 && (b_tr ? fc_dx_supported(g) : fc_fwd_supported(g))) {
+    if (g_force_fwd_cfg < 0 && (b_tr ? fc_dx_supported(g) : fc_fwd_supported(g, prepacked, lean))) {
         p.cfg = b_tr ? 11 : 10;
         p.nsplit = 1;
         if (!b_tr) {
@@ -1114,7 +1114,7 @@ const char* fwd_like_kernel_name(const GemmGeom& g, bool b_tr, const GemmPlan& p
     if (plan.cfg == 7) return tile2d_kernel_name(g, unpool, plan.tile);
     if (plan.cfg == 8) return conv_c3_fwd_kernel_name(g);
     if (plan.cfg == 9) return "dgrad_thin_kernel";
-    if (plan.cfg == 10) return "fc_fwd_kernel";
+    if (plan.cfg == 10) return g.M <= 16 ? "fc_fwd_kernel" : g.M <= 32 ? "fc_fwd_kernel<2>" : "fc_fwd_kernel<4>";
     if (plan.cfg == 11) return "fc_dx_kernel";
     if (plan.cfg == 15) return "conv_thin_fwd_kernel";
     if (plan.cfg == 16) return flat_kernel_name(g, plan.tile, unpool);

@@ -243,9 +243,9 @@ bool dgrad_thin_supported(const GemmGeom& g);
 int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st);
 
 // fully-connected products with few rows as streams of the weights (fc.hip); geometries of geom_fc_fwd / geom_fc_dx
-bool fc_fwd_supported(const GemmGeom& g);
+bool fc_fwd_supported(const GemmGeom& g, bool in_step, bool lean);
 bool fc_dx_supported(const GemmGeom& g);
-void fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
+double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);

@@ -1,0 +1,42 @@
+"""GPU parity of the fully-connected forward stream with two and four blocks of 16 batch rows: rows around the blocks, whole and partial
+vectors, features that no work-group divides, divided and undivided reductions, with and without a workspace; an infinite weight among the
+elements that a row's last vector shares with its neighbour reaches its own feature alone."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(17, 64, 16), (31, 512, 1000), (32, 4096, 1000), (33, 4096, 500), (48, 1000, 333), (63, 67, 41), (64, 9216, 512), (64, 515, 4096), (20, 1024, 8192),
+         (40, 22000, 80), (64, 8, 9)]
+
+
+@pytest.mark.parametrize("B,n_in,n_out", CASES)
+def test_forward_stream_of_several_row_blocks(orc, B, n_in, n_out):
+    import paper_1811_01532_amd as wap
+    if wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 0:
+        name = wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD)
+        assert name == ("fc_fwd_kernel<2>" if B <= 32 else "fc_fwd_kernel<4>")
+    print(f"[case] fc fwd {B} x {n_in} -> {n_out}", flush=True)
+    x = orc.bf16_bits_to_f64(si.normal_bf16(si.rng(960, B + n_in), (B, n_in)))
+    x[x == 0] = 1.0
+    W = orc.bf16_bits_to_f64(si.he_weight_bf16(si.rng(961, n_in + n_out), (n_out, n_in)))
+    bias = si.rng(962, n_out).standard_normal(n_out).astype(np.float32)
+    for inf in (False, True):
+        if inf:
+            for i, col in enumerate(sorted({0, n_in - 8, n_in - 1 - n_in % 8, n_in - 1})):
+                W[i, col] = np.inf if i % 2 else -np.inf
+        xd, Wd = (gu.dev_bf16(si.f32_to_bf16_bits(t.astype(np.float32))) for t in (x, W))
+        for relu in (False, True):
+            d = wap.fc_desc(B, n_in, n_out, relu=relu)
+            ws = gu.workspace(wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD))
+            ref = orc.fc_fwd(x, W, bias=bias.astype(np.float64), relu=relu)
+            y = torch.full((B * n_out + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            wap.wap_fc_fwd(d, xd, Wd, torch.from_numpy(bias).cuda(), y, ws)
+            torch.cuda.synchronize()
+            got, at = gu.host_f64(y[:B * n_out]).reshape(B, n_out), np.isinf(ref)
+            assert torch.isnan(y[B * n_out:]).all() and np.array_equal(got[at], ref[at]) and (at.any() == inf)
+            assert gu.rel_err(np.where(at, 0.0, got), np.where(at, 0.0, ref)) <= gu.TOL_BF16_OUT
