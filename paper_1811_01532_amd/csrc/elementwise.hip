@@ -435,26 +435,63 @@ struct PoolWindow {
     }
 };
 template <int VEC>
-__device__ __forceinline__ void pool_store(bf16_t* dx, const float* s) {
+__device__ __forceinline__ void pool_store(bf16_t* dx, const float* s, float* cs = nullptr) {  // cs: sums of what is stored
     if (VEC == 8) {
         u32x4 v;
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = (unsigned)f2bf(s[2 * k]) | ((unsigned)f2bf(s[2 * k + 1]) << 16);
         *reinterpret_cast<u32x4*>(dx) = v;
+        if (cs) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                cs[2 * k] += __uint_as_float(v[k] << 16);
+                cs[2 * k + 1] += __uint_as_float(v[k] & 0xffff0000u);
+            }
+        }
     } else {
         *dx = f2bf(s[0]);
     }
 }
 
+// sum of the row losses as a tree of 256, by any number of threads from 128 on: the same order everywhere
+__device__ __forceinline__ void loss_mean(const LossMean m, float* sh) {
+    for (int v = threadIdx.x; v < 256; v += blockDim.x) {
+        float s = 0.f;
+        for (int j = v; j < m.B; j += 256) s += m.row_loss[j];
+        sh[v] = s;
+    }
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *m.loss = sh[0] / (float)m.B;
+}
+
 // Stride 2 (every pool of the two networks): a thread owns a 2 x 2 block of input pixels, which only the windows ending
 // in it (WIN 3: and the ones before, above and left) can reach: one (four) window loads for four pixels, where a thread
 // per pixel loads 4 (9).  100 x 55 x 55 x 64, window 3: 30.7 -> 17.3 us.
-template <int VEC, int WIN>
-__global__ void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
-                                      const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, const PoolArgs a) {
+// COLSUM (work-groups of whole pixels, so that a thread keeps its channels): a row of column sums of what the work-group stores, for the
+// bias gradient of the layer below, which otherwise takes a pass over the tensor and a launch for its partial sums.  The last work-group
+// takes the mean of the row losses where that is asked for: it waits for nothing here, and nothing for it.
+template <int VEC, int WIN, bool COLSUM>
+__global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
+                                                                  const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx,
+                                                                  float* __restrict__ colsum, const LossMean mean, const PoolArgs a) {
+    __shared__ __align__(16) float red[COLSUM ? kThreads * VEC : kThreads];
+    uint32_t groups = gridDim.x;
+    if (mean.loss) {
+        if (blockIdx.x == --groups) {
+            loss_mean(mean, red);
+            return;
+        }
+    }
+    float cs[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) cs[e] = 0.f;
     const uint32_t CV = a.C / VEC;
     const uint32_t WB = (a.W + 1) / 2, HB = (a.H + 1) / 2;
-    const uint32_t stride = gridDim.x * blockDim.x;
+    const uint32_t stride = groups * blockDim.x;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
         const uint32_t t = fdiv(i, a.dCV);
         const uint32_t cv = i - t * CV;
@@ -487,8 +524,36 @@ __global__ void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8
                     if (s == 0) w[NB - 1][0].add(sum, r * WIN + 2);
                 }
                 w[NB - 1][NB - 1].add(sum, r * WIN + s);
-                pool_store<VEC>(dx + (((size_t)n * a.H + h) * a.W + x) * a.C + (size_t)cv * VEC, sum);
+                pool_store<VEC>(dx + (((size_t)n * a.H + h) * a.W + x) * a.C + (size_t)cv * VEC, sum, COLSUM ? cs : nullptr);
             }
+    }
+    if constexpr (COLSUM) {  // the pixels of the work-group in order of a tree: fixed by the shape
+        const uint32_t np = blockDim.x / CV, px = threadIdx.x / CV;
+        f32x4* const mine = reinterpret_cast<f32x4*>(red + threadIdx.x * VEC);
+        auto put = [&]() {
+#pragma unroll
+            for (int q = 0; q < VEC / 4; ++q) mine[q] = f32x4{cs[4 * q], cs[4 * q + 1], cs[4 * q + 2], cs[4 * q + 3]};
+        };
+        put();
+        for (uint32_t h = np; h > 1;) {
+            const uint32_t half = (h + 1) / 2;
+            __syncthreads();
+            if (px < half && px + half < h) {
+#pragma unroll
+                for (int q = 0; q < VEC / 4; ++q) {
+                    const f32x4 o = mine[half * CV * (VEC / 4) + q];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) cs[4 * q + e] += o[e];
+                }
+                put();
+            }
+            h = half;
+        }
+        if (px == 0) {
+#pragma unroll
+            for (int q = 0; q < VEC / 4; ++q)
+                *reinterpret_cast<f32x4*>(colsum + (size_t)blockIdx.x * a.C + threadIdx.x * VEC + 4 * q) = f32x4{cs[4 * q], cs[4 * q + 1], cs[4 * q + 2], cs[4 * q + 3]};
+        }
     }
 }
 
@@ -569,19 +634,9 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const bf16_t* __restr
     if (tid == 0) row_loss[b] = lab_ok ? -(bf2f(zb[lab]) - m - logf(s)) : 0.f;
 }
 
-// fixed-order mean of B row losses (single work-group tree)
-__global__ __launch_bounds__(256) void loss_mean_kernel(const float* __restrict__ row_loss, int B,
-                                                        float* __restrict__ loss) {
-    __shared__ float sh[256];
-    float s = 0.f;
-    for (int j = threadIdx.x; j < B; j += 256) s += row_loss[j];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = sh[0] / (float)B;
+__global__ __launch_bounds__(kThreads) void loss_mean_kernel(const LossMean m) {
+    __shared__ float sh[kThreads];
+    loss_mean(m, sh);
 }
 
 // ---- SGD on fp32 master weights, re-deriving the bf16 compute copy: bound by memory.  One 16-byte group a thread and as many
@@ -727,49 +782,63 @@ int launch_fill_bf16(bf16_t* p, size_t n, uint32_t seed, hipStream_t st) {
     return check_launch("fill");
 }
 
-// ---- fixed-order column sums of fp32 matrices [rows][cols], cols % 4 == 0 (the per-tile partial sums the convolution
-// epilogues leave for the bias gradients), every matrix of a step in one launch.  First stage: a work-group adds one
-// chunk of rows of one matrix, thread (row sub-index, 16-byte column vector) every RP-th row, then the RP partial sums
-// in order.  Second stage: a thread adds the chunks of one column vector in order. ----
-__global__ __launch_bounds__(256) void colsum_f32_multi_kernel(const ColsumJobs js, unsigned char* __restrict__ base) {
+// ---- fixed-order column sums of fp32 or bf16 matrices [rows][cols], cols % 4 == 0 (the per-tile partial sums that other kernels'
+// epilogues leave for the bias gradients, and the gradient of the logits itself), every matrix of a step in one launch.  First stage: a
+// work-group adds a chunk of rows of up to 16 vectors of four columns, a thread every RP-th row, then the RP partial sums in a tree.
+// Second stage: a thread adds the chunks of one column vector in order.  (Rows in one piece, a load at a time and the RP sums one after
+// the other: 15.0 and 8.5 us for the layers of VGG-16 at 22 and of the AlexNet-style network at 100 images; 4.9 and 6.0 so.) ----
+static __host__ __device__ int colsum_vpb(int cols) { return cols / 4 < 16 ? cols / 4 : 16; }
+__global__ __launch_bounds__(256) void colsum_multi_kernel(const ColsumJobs js, unsigned char* __restrict__ base) {
     __shared__ float4 red[256];
     int j = 0;
     while (j + 1 < js.n && (int)blockIdx.x >= js.first[j + 1]) ++j;
     const ColsumJob& jb = js.job[j];
     const int local = (int)blockIdx.x - js.first[j];
-    const int cv = jb.cols / 4;
-    const int vpb = cv < 256 ? cv : 256;
+    const int cv = jb.cols / 4, vpb = colsum_vpb(jb.cols);
     const int colblocks = (cv + vpb - 1) / vpb;
     const int chunk = local / colblocks, cb = local - chunk * colblocks;
     const int rp = 256 / vpb;
     const int vec = threadIdx.x % vpb, rsub = threadIdx.x / vpb;
     const int v = cb * vpb + vec;
-    const float* part = reinterpret_cast<const float*>(base + jb.part_off);
     float* part2 = reinterpret_cast<float*>(base + jb.part2_off);
     const int rpc = (jb.rows + jb.chunks - 1) / jb.chunks;
-    const int r0 = chunk * rpc;
-    const int r1 = r0 + rpc < jb.rows ? r0 + rpc : jb.rows;
+    const int r0 = chunk * rpc, r1 = r0 + rpc < jb.rows ? r0 + rpc : jb.rows;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (rsub < rp && v < cv)
-        for (int r = r0 + rsub; r < r1; r += rp) {
-            const float4 t = *reinterpret_cast<const float4*>(part + (size_t)r * jb.cols + (size_t)v * 4);
-            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    if (rsub < rp && v < cv) {
+        for (int r = r0 + rsub; r < r1; r += 8 * rp) {  // eight loads in flight, absent rows loaded from the last one and left out
+            float4 t[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const size_t o = (size_t)(r + k * rp < r1 ? r + k * rp : r1 - 1) * jb.cols + (size_t)v * 4;
+                if (jb.bf16) {
+                    const uint2 u = *reinterpret_cast<const uint2*>(reinterpret_cast<const bf16_t*>(base + jb.part_off) + o);
+                    t[k] = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+                } else {
+                    t[k] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base + jb.part_off) + o);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (r + k * rp < r1) acc4(s, t[k]);
         }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (rsub == 0 && v < cv) {
-        for (int k = 1; k < rp; ++k) {
-            const float4 t = red[k * vpb + vec];
-            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-        }
-        *reinterpret_cast<float4*>(part2 + (size_t)chunk * jb.cols + (size_t)v * 4) = s;
     }
+    red[threadIdx.x] = s;
+    for (int h = rp; h > 1;) {
+        const int half = (h + 1) / 2;
+        __syncthreads();
+        if (rsub < half && rsub + half < h) {
+            acc4(s, red[threadIdx.x + half * vpb]);
+            red[threadIdx.x] = s;
+        }
+        h = half;
+    }
+    if (rsub == 0 && v < cv) *reinterpret_cast<float4*>(part2 + (size_t)chunk * jb.cols + (size_t)v * 4) = s;
 }
 
 // 16 column vectors (of the concatenation of all matrices) per work-group, 16 threads per vector that each add every
 // 16th chunk; their sums are added in order.  (One thread per vector walked up to 64 chunks one load after the other:
 // 20 us for VGG-16's twelve layers at minibatch 22; this takes 6.)
-__global__ __launch_bounds__(256) void colsum_f32_finish_kernel(const ColsumJobs js, unsigned char* __restrict__ base) {
+__global__ __launch_bounds__(256) void colsum_finish_kernel(const ColsumJobs js, unsigned char* __restrict__ base) {
     __shared__ float4 red[256];
     const int sub = threadIdx.x >> 4;
     const int t = blockIdx.x * 16 + (threadIdx.x & 15);
@@ -798,32 +867,32 @@ __global__ __launch_bounds__(256) void colsum_f32_finish_kernel(const ColsumJobs
     }
 }
 
-int colsum_f32_chunks(size_t rows) {
-    size_t chunks = (rows + 63) / 64;
-    if (chunks > 64) chunks = 64;
-    return (int)(chunks < 1 ? 1 : chunks);
+// up to 64 chunks of at least eight rows a thread
+int colsum_chunks(int rows, int cols) {
+    const int per = 8 * (256 / colsum_vpb(cols));
+    return std::max(1, std::min(64, (rows + per - 1) / per));
 }
 
-int colsum_jobs_add(ColsumJobs& js, int rows, int cols, size_t part_off, size_t part2_off, size_t out_off) {
+int colsum_jobs_add(ColsumJobs& js, int rows, int cols, bool bf16, size_t part_off, size_t part2_off, size_t out_off) {
     if (js.n >= kMaxColsumJobs || (cols & 3) != 0 || rows < 1) return -1;
     ColsumJob& jb = js.job[js.n];
-    jb.rows = rows; jb.cols = cols; jb.chunks = colsum_f32_chunks((size_t)rows);
+    jb.rows = rows; jb.cols = cols; jb.chunks = colsum_chunks(rows, cols); jb.bf16 = bf16 ? 1 : 0;
     jb.part_off = part_off; jb.part2_off = part2_off; jb.out_off = out_off;
-    const int cv = cols / 4, vpb = cv < 256 ? cv : 256;
+    const int cv = cols / 4, vpb = colsum_vpb(cols);
     if (js.n == 0) js.first[0] = 0;
     js.first[js.n + 1] = js.first[js.n] + jb.chunks * ((cv + vpb - 1) / vpb);
     return js.n++;
 }
 
-int launch_colsum_f32_multi(const ColsumJobs& js, void* base, hipStream_t st) {
+int launch_colsum_multi(const ColsumJobs& js, void* base, hipStream_t st) {
     if (js.n < 1) return WAP_OK;
-    hipLaunchKernelGGL(colsum_f32_multi_kernel, dim3(js.first[js.n]), dim3(256), 0, st, js, (unsigned char*)base);
-    int rc = check_launch("colsum_f32_multi");
+    hipLaunchKernelGGL(colsum_multi_kernel, dim3(js.first[js.n]), dim3(256), 0, st, js, (unsigned char*)base);
+    int rc = check_launch("colsum_multi");
     if (rc != WAP_OK) return rc;
     int vecs = 0;
     for (int j = 0; j < js.n; ++j) vecs += js.job[j].cols / 4;
-    hipLaunchKernelGGL(colsum_f32_finish_kernel, dim3((vecs + 15) / 16), dim3(256), 0, st, js, (unsigned char*)base);
-    return check_launch("colsum_f32_finish");
+    hipLaunchKernelGGL(colsum_finish_kernel, dim3((vecs + 15) / 16), dim3(256), 0, st, js, (unsigned char*)base);
+    return check_launch("colsum_finish");
 }
 
 // How the first stage is laid out: 16-byte vectors where the row length allows it (8-byte, else 2-byte).  A few rows are
@@ -917,17 +986,32 @@ int launch_maxpool_fwd(int N, int H, int W, int C, int win, int stp, const bf16_
     return check_launch("maxpool_fwd");
 }
 
+// Two items a thread, so that the partial rows are fewer than the work-groups in flight (100 x 55 x 55 x 64, window 3: 1225 rows).
+static int pool_colsum_threads(int C) { return kThreads / (C / 8) * (C / 8); }
+int maxpool_bwd_colsum_rows(int N, int H, int W, int C, int win, int stp) {
+    if (stp != 2 || (win != 2 && win != 3) || (C & 7) != 0 || C > kThreads * 4) return 0;
+    const size_t items = (size_t)N * ((H + 1) / 2) * ((W + 1) / 2) * (C / 8), per = 2 * pool_colsum_threads(C);
+    return (int)std::min((items + per - 1) / per, (size_t)1 << 22);
+}
+
 int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_t* dy, const uint8_t* am,
-                       const bf16_t* ry, bf16_t* dx, hipStream_t st) {
+                       const bf16_t* ry, bf16_t* dx, hipStream_t st, float* colsum, const LossMean* mean) {
     const int vec = (C & 7) == 0 ? 8 : 1;
     const dim3 block(kThreads);
+    const LossMean lm = mean ? *mean : LossMean{nullptr, nullptr, 0};
+    const int rows = maxpool_bwd_colsum_rows(N, H, W, C, win, stp);
+    if ((colsum || mean) && !rows) return set_error(WAP_EINVAL, "internal: no column sums from this max-pool");
     if (stp == 2 && (win == 2 || win == 3)) {
         const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, (H + 1) / 2, (W + 1) / 2);
-        const dim3 grid(grid_for(a.items));
-        if (vec == 8 && win == 2) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 2>), grid, block, 0, st, dy, am, ry, dx, a);
-        else if (vec == 8) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 3>), grid, block, 0, st, dy, am, ry, dx, a);
-        else if (win == 2) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<1, 2>), grid, block, 0, st, dy, am, ry, dx, a);
-        else hipLaunchKernelGGL((maxpool_bwd_s2_kernel<1, 3>), grid, block, 0, st, dy, am, ry, dx, a);
+        const dim3 grid((colsum ? rows : grid_for(a.items)) + (mean ? 1 : 0));
+#define WAP_POOL(VEC, WIN) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<VEC, WIN, false>), grid, block, 0, st, dy, am, ry, dx, nullptr, lm, a)
+        if (colsum && win == 2) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 2, true>), grid, dim3(pool_colsum_threads(C)), 0, st, dy, am, ry, dx, colsum, lm, a);
+        else if (colsum) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<8, 3, true>), grid, dim3(pool_colsum_threads(C)), 0, st, dy, am, ry, dx, colsum, lm, a);
+        else if (vec == 8 && win == 2) WAP_POOL(8, 2);
+        else if (vec == 8) WAP_POOL(8, 3);
+        else if (win == 2) WAP_POOL(1, 2);
+        else WAP_POOL(1, 3);
+#undef WAP_POOL
         return check_launch("maxpool_bwd");
     }
     const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, H, W);
@@ -941,8 +1025,8 @@ int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labe
                         float* row_loss, bf16_t* dz, hipStream_t st) {
     hipLaunchKernelGGL(softmax_xent_kernel, dim3(B), dim3(256), 0, st, z, labels, B, classes, row_loss, dz);
     int rc = check_launch("softmax_xent");
-    if (rc != WAP_OK) return rc;
-    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, st, row_loss, B, loss);
+    if (rc != WAP_OK || !loss) return rc;
+    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(kThreads), 0, st, LossMean{row_loss, loss, B});
     return check_launch("loss_mean");
 }
 

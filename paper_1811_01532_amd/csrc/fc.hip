@@ -31,6 +31,7 @@ struct FcArgs {
     int B, in, out;
     int relu, partial, steps_per_split;
     int feat;            // forward: output features of a work-group
+    float* colsum;       // data gradient: optional, [in] column sums of the (masked) result
 };
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -246,6 +247,7 @@ __global__ __launch_bounds__(64 * DX_WAVES) void fc_dx_kernel(const FcArgs a) {
         if (st >= steps) break;
     }
 
+    float cs[4] = {0.f, 0.f, 0.f, 0.f};
     // lane: batch row lane & 15; accumulator element e of column block c is column ((lane >> 4) * 4 + e) * CPL + c, so a
     // lane holds 4 * CPL neighbouring columns, staged as CPL groups of four
 #pragma unroll
@@ -278,9 +280,19 @@ __global__ __launch_bounds__(64 * DX_WAVES) void fc_dx_kernel(const FcArgs a) {
                 u32x2 pk = {(unsigned)f2bf(s[0]) | ((unsigned)f2bf(s[1]) << 16),
                             (unsigned)f2bf(s[2]) | ((unsigned)f2bf(s[3]) << 16)};
                 __builtin_memcpy(reinterpret_cast<bf16_t*>(a.res) + e, &pk, 8);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) cs[t] += __uint_as_float((t & 1) ? pk[t >> 1] & 0xffff0000u : pk[t >> 1] << 16);
             }
         }
         __syncthreads();
+    }
+    // the work-group has all rows of its columns: their sums are the bias gradient of the layer below
+    if (a.colsum && tid < 64 * CPL) {
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) cs[t] += __shfl_xor(cs[t], o, 64);
+        if (il == 0) __builtin_memcpy(a.colsum + i0 + og * 4 * CPL + (tid >> 6) * 4, cs, 16);
     }
 }
 
@@ -395,7 +407,7 @@ int launch_fwd(const FcArgs& a, dim3 grid, hipStream_t st) {
 
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st) {
-    FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0, feat};
+    FcArgs a = {x, w, bias, nullptr, out, g.M, g.IC, g.Ncols, relu ? 1 : 0, nsplit > 1 ? 1 : 0, 0, feat, nullptr};
     a.steps_per_split = ((g.IC + 31) / 32 + nsplit - 1) / nsplit;
     const dim3 grid((g.Ncols + a.feat - 1) / a.feat, nsplit);
     if (g.M <= 16) return launch_fwd<1>(a, grid, st);
@@ -419,8 +431,8 @@ int launch_dx(const FcArgs& a, hipStream_t st) {
 // Four columns per lane read whole 128-byte lines of a row.  Where that gives fewer than 96 work-groups (4096 columns at
 // 8 rows: 12.7 us), or the sums of more than 64 batch rows would not fit the registers, two columns per lane (10.7 us;
 // the other half of the line comes from the L2).  9216 columns: 15.2 us with four, 22.4 us with two.
-int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st) {
-    const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0, 0};
+int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, float* colsum, hipStream_t st) {
+    const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0, 0, colsum};
     const bool wide = g.Ncols >= 96 * 64 && g.M <= 64, vec8 = (g.IC % 8) == 0;
     if (wide) return vec8 ? launch_dx<4, true>(a, st) : launch_dx<4, false>(a, st);
     return vec8 ? launch_dx<2, true>(a, st) : launch_dx<2, false>(a, st);

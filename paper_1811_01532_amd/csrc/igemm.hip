@@ -969,7 +969,7 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
         return launch_reduce_bf16(reinterpret_cast<const float*>(ws), plan.nsplit, (size_t)g.M * g.Ncols, g.Ncols, bias,
                                   relu, out, st);
     }
-    if (plan.cfg == 11) return launch_fc_dx(g, A, Bw, relu_mask, out, st);
+    if (plan.cfg == 11) return launch_fc_dx(g, A, Bw, relu_mask, out, colsum, st);
     KArgs ka;
     ka.A = A;
     ka.Bw = Bw;
@@ -1100,6 +1100,7 @@ bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) {
 }
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return reduce_bf16_colsum_rows(g.M, g.Ncols);
+    if (plan.cfg == 11) return 1;
     if (plan.cfg == 16) return flat_colsum_rows(g, plan.tile);
     return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g, plan.tile) : 0;
 }

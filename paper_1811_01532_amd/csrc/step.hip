@@ -49,8 +49,9 @@ struct Op {
                             // t7); it runs after the layer's data gradient, which still needs the old weights
     size_t t6 = 0, t7 = 0;
     bool beside = false;    // may run beside the operations behind it, up to the plan's join
-    bool colsum = false;    // data gradient whose epilogue also leaves per-tile column sums of its (masked) output at t8:
+    bool colsum = false;    // data gradient or max-pool backward that also leaves per-tile column sums of its (masked) output at t8:
                             // the bias gradient of the layer below, finished by the OP_BIAS_FINISH operation behind it
+    bool mean = false;      // softmax or max-pool backward that takes the mean of the row losses (t6) as well (to t7)
     size_t t8 = 0;
     int group = -1;         // OP_WGRAD_GROUP: index of the group; the operands are those of this and the next n - 1 operations
     int N = 0, H = 0, W = 0, C = 0, win = 0, st = 0;  // pooling / softmax shapes
@@ -258,20 +259,22 @@ int run_op(const wap_step_plan* p, const Op& op, unsigned char* base, hipStream_
         case OP_POOL_FWD:
             return launch_maxpool_fwd(op.N, op.H, op.W, op.C, op.win, op.st, (const bf16_t*)(base + op.t0),
                                       (bf16_t*)(base + op.t1), (uint8_t*)(base + op.t2), st);
-        case OP_POOL_BWD:
+        case OP_POOL_BWD: {
+            const LossMean mean = {(const float*)(base + op.t6), (float*)(base + op.t7), p->B};
             return launch_maxpool_bwd(op.N, op.H, op.W, op.C, op.win, op.st, (const bf16_t*)(base + op.t0),
                                       (const uint8_t*)(base + op.t1), (const bf16_t*)(base + op.t2),
-                                      (bf16_t*)(base + op.t3), st);
+                                      (bf16_t*)(base + op.t3), st, op.colsum ? (float*)(base + op.t8) : nullptr, op.mean ? &mean : nullptr);
+        }
         case OP_RELU_BWD:
             return launch_relu_bwd((const bf16_t*)(base + op.t0), (const bf16_t*)(base + op.t1),
                                    (bf16_t*)(base + op.t2), op.n, st);
         case OP_SOFTMAX:
             return launch_softmax_xent(op.N, op.C, (const bf16_t*)(base + op.t0), (const int32_t*)(base + op.t1),
-                                       (float*)(base + op.t2), (float*)(base + op.t3), (bf16_t*)(base + op.t4), st);
+                                       op.mean ? (float*)(base + op.t7) : nullptr, (float*)(base + op.t6), (bf16_t*)(base + op.t4), st);
         case OP_BIAS_GRAD:
             return launch_bias_grad(op.n, op.C, (const bf16_t*)(base + op.t0), (float*)(base + op.t1), (float*)ws, st);
         case OP_BIAS_FINISH:  // the per-tile column sums that the data gradients left -> bias gradients, all layers at once
-            return launch_colsum_f32_multi(p->colsumjobs, base, st);
+            return launch_colsum_multi(p->colsumjobs, base, st);
         case OP_SGD:
             return launch_sgd(op.n, (float*)(base + op.t0), (const float*)(base + op.t1), p->lr,
                               (bf16_t*)(base + op.t2), p->once, st);
@@ -518,21 +521,28 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         if (need > ws_need) ws_need = need;
         p->ops.push_back(op);
     };
-    // The same gradient where the data gradient that produced dy (ReLU derivative applied in its epilogue) can leave
-    // per-tile column sums of what it stores: no pass over dy at all; the (small) partial rows of all such layers are
-    // added up by one operation at the end of the backward pass.
-    struct ColsumReq { size_t op_index; int li, rows, cols; };
+    // The same gradient where the operation that produced dy (a data gradient with the ReLU derivative in its epilogue, a max-pool
+    // backward) can leave per-tile column sums of what it stores: no pass over dy at all; the (small) partial rows of all such
+    // layers are added up by one operation at the end of the backward pass.  A single row is the gradient itself.
+    struct ColsumReq { size_t op_index; int li, rows, cols; };  // op_index: -1 where the rows are the bf16 gradient of the logits
     std::vector<ColsumReq> colsum_reqs;
     auto try_fuse_bias_grad = [&](int li) -> bool {
         if (!with_bias || keep || p->ops.empty() || (int)colsum_reqs.size() >= kMaxColsumJobs) return false;
         Op& prod = p->ops.back();
-        if ((prod.kind != OP_CONV_DGRAD && prod.kind != OP_FC_DX) || !prod.has_mask || prod.has_pool) return false;
-        const int rows = fwd_like_colsum_rows(prod.gg, prod.gp);
-        if (rows == 0 || prod.gg.Ncols != (int)bcount[li] || (prod.gg.Ncols % 4) != 0) return false;
+        int rows = 0, cols = 0;
+        if (prod.kind == OP_POOL_BWD) {
+            rows = maxpool_bwd_colsum_rows(prod.N, prod.H, prod.W, prod.C, prod.win, prod.st);
+            cols = prod.C;
+        } else if ((prod.kind == OP_CONV_DGRAD || prod.kind == OP_FC_DX) && prod.has_mask && !prod.has_pool) {
+            rows = fwd_like_colsum_rows(prod.gg, prod.gp);
+            cols = prod.gg.Ncols;
+        }
+        if (rows == 0 || cols != (int)bcount[li] || (cols % 4) != 0) return false;
         prod.colsum = true;
         prod.name += "+bias_grad";
-        prod.bytes += 4.0 * rows * prod.gg.Ncols;
-        colsum_reqs.push_back({p->ops.size() - 1, li, rows, prod.gg.Ncols});
+        prod.bytes += 4.0 * rows * cols;
+        if (rows == 1) prod.t8 = p->dw_off + boff[li] * 4;
+        else colsum_reqs.push_back({p->ops.size() - 1, li, rows, cols});
         return true;
     };
     auto set_bias = [&](int li) {
@@ -617,12 +627,14 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     // ---- loss ----
     // The fully-connected weight gradients (with their updates) may run beside the convolutions' backward pass: they stream the
     // weights, most of a small step's bytes, while the convolutions wait for latency or compute.
-    size_t g_cur = forks ? p->add("g.fc8.y", (size_t)B * 1000 * 2) : new_grad("g.fc8.y", (size_t)B * 1000);
+    const bool late_sums = with_bias && !keep;  // of the gradient of the logits, with those of the other layers at the end
+    size_t g_cur = forks || late_sums ? p->add("g.fc8.y", (size_t)B * 1000 * 2) : new_grad("g.fc8.y", (size_t)B * 1000);
     {
         Op op;
         op.kind = OP_SOFTMAX; op.name = "softmax_xent";
         op.N = B; op.C = 1000;
-        op.t0 = fc_y[2]; op.t1 = t_labels; op.t2 = t_loss; op.t3 = t_rowloss; op.t4 = g_cur;
+        op.t0 = fc_y[2]; op.t1 = t_labels; op.t4 = g_cur; op.t6 = t_rowloss; op.t7 = t_loss;
+        op.mean = true;
         op.kernel = "softmax_xent_kernel";
         op.bytes = 4.0 * B * 1000;
         p->ops.push_back(op);
@@ -634,11 +646,13 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         size_t elems = (size_t)B * fds[i].out_features;
         // the data gradient of the layer above applies this layer's ReLU derivative where its kernel can
         Op& above = p->ops.back();
+        bool bias_fused = false;
         if (kFcs[i].relu && !keep && above.kind == OP_FC_DX && fwd_like_fuses_mask(above.gg, above.gp)) {
             above.has_mask = true;
             above.t3 = fc_y[i];
             above.name += "+relu_bwd";
             above.bytes += 2.0 * elems;
+            bias_fused = try_fuse_bias_grad(nconv + i);
         } else if (kFcs[i].relu) {
             Op op;
             op.kind = OP_RELU_BWD; op.name = nm + ".relu_bwd";
@@ -651,7 +665,8 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
             g_cur = op.t2;
         }
         push_wgrad(OP_FC_DW, nm + ".dW", geom_fc_dw(fds[i]), fc_in[i], g_cur, nconv + i);
-        push_bias_grad(nconv + i, (size_t)B, g_cur);
+        if (i == 2 && late_sums) colsum_reqs.push_back({(size_t)-1, nconv + i, B, 1000});
+        else if (!bias_fused) push_bias_grad(nconv + i, (size_t)B, g_cur);
         if (!keep) gsel = (g_cur == gbuf[0]) ? 1 : 0;
         std::string in_name = i > 0 ? "g." + lname(nconv + i - 1) + ".y"
                                     : "g." + lname(nconv - 1) + (convs[nconv - 1].pool_win ? ".pool.y" : ".y");
@@ -686,6 +701,13 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
             op.t3 = grad_for("gm." + nm + ".y", conv_y_elems[i], late[i]);
             op.kernel = "maxpool_bwd_kernel";
             op.bytes = 2.0 * conv_y_elems[i] + 5.0 * pool_y_elems[i];
+            // the first of them takes the mean of the row losses (a launch behind the softmax costs every step 4.7 us)
+            auto softmax = std::find_if(p->ops.begin(), p->ops.end(), [](const Op& o) { return o.kind == OP_SOFTMAX; });
+            if (!keep && softmax->mean && maxpool_bwd_colsum_rows(op.N, op.H, op.W, op.C, op.win, op.st) > 0) {
+                softmax->mean = false;
+                op.mean = true;
+                op.t6 = t_rowloss; op.t7 = t_loss;
+            }
             p->ops.push_back(op);
             g_cur = op.t3;
         } else if (!relu_done) {
@@ -701,7 +723,7 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         }
         // bias gradient: from the epilogue of the data gradient that produced g_cur where that kernel can (it applied
         // this layer's ReLU derivative and is the last operation so far), else a pass over g_cur further down
-        const bool bias_fused = (unpool || relu_done) && try_fuse_bias_grad(i);
+        const bool bias_fused = (unpool || relu_done || p->ops.back().kind == OP_POOL_BWD) && try_fuse_bias_grad(i);
         size_t x_in = i == 0 ? t_input : (convs[i - 1].pool_win ? pool_y[i - 1] : conv_y[i - 1]);
         push_wgrad(OP_CONV_WGRAD, nm + ".wgrad", geom_conv_wgrad(d), x_in, g_cur, i);
         if (unpool) {
@@ -746,16 +768,16 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
     if (!colsum_reqs.empty()) {
         double bytes = 0;
         for (const ColsumReq& rq : colsum_reqs) {
-            const size_t part = p->add("bias.colsum." + lname(rq.li), (size_t)rq.rows * rq.cols * sizeof(float));
-            const size_t part2 = p->add("bias.colsum2." + lname(rq.li),
-                                        (size_t)colsum_f32_chunks((size_t)rq.rows) * rq.cols * sizeof(float));
-            p->ops[rq.op_index].t8 = part;
-            colsum_jobs_add(p->colsumjobs, rq.rows, rq.cols, part, part2, p->dw_off + boff[rq.li] * 4);
-            bytes += 4.0 * rq.rows * rq.cols + 4.0 * rq.cols;
+            const bool logits = rq.op_index == (size_t)-1;
+            const size_t part = logits ? p->find("g.fc8.y") : p->add("bias.colsum." + lname(rq.li), (size_t)rq.rows * rq.cols * sizeof(float));
+            const size_t part2 = p->add("bias.colsum2." + lname(rq.li), (size_t)colsum_chunks(rq.rows, rq.cols) * rq.cols * sizeof(float));
+            if (!logits) p->ops[rq.op_index].t8 = part;
+            colsum_jobs_add(p->colsumjobs, rq.rows, rq.cols, logits, part, part2, p->dw_off + boff[rq.li] * 4);
+            bytes += (logits ? 2.0 : 4.0) * rq.rows * rq.cols + 4.0 * rq.cols;
         }
         Op op;
         op.kind = OP_BIAS_FINISH; op.name = "bias_grad_finish";
-        op.kernel = "colsum_f32_multi_kernel";
+        op.kernel = "colsum_multi_kernel";
         op.bytes = bytes;
         p->ops.push_back(op);
     }

@@ -142,10 +142,10 @@ int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf
                     float* colsum = nullptr);            // column sums of the stored output, one partial row per pixel
                                                          // tile (only where fwd_like_colsum_rows > 0; not with pool_y)
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan);  // 0: the plan's kernel cannot emit column sums
-// Fixed-order column sums of fp32 matrices [rows][cols] (cols % 4 == 0), all of a step in one pair of launches; byte
-// offsets are relative to one base pointer; part2 holds colsum_f32_chunks(rows) x cols floats per matrix.
+// Fixed-order column sums of fp32 (or bf16) matrices [rows][cols] (cols % 4 == 0), all of a step in one pair of launches; byte
+// offsets are relative to one base pointer; part2 holds colsum_chunks(rows, cols) x cols floats per matrix.
 struct ColsumJob {
-    int rows, cols, chunks;
+    int rows, cols, chunks, bf16;
     size_t part_off, part2_off, out_off;
 };
 constexpr int kMaxColsumJobs = 24;
@@ -154,9 +154,9 @@ struct ColsumJobs {
     int first[kMaxColsumJobs + 1];  // first work-group of each job in the first-stage grid
     ColsumJob job[kMaxColsumJobs];
 };
-int colsum_f32_chunks(size_t rows);
-int colsum_jobs_add(ColsumJobs& js, int rows, int cols, size_t part_off, size_t part2_off, size_t out_off);  // -1: full / bad
-int launch_colsum_f32_multi(const ColsumJobs& js, void* base, hipStream_t st);
+int colsum_chunks(int rows, int cols);
+int colsum_jobs_add(ColsumJobs& js, int rows, int cols, bool bf16, size_t part_off, size_t part2_off, size_t out_off);  // -1: full / bad
+int launch_colsum_multi(const ColsumJobs& js, void* base, hipStream_t st);
 bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan);
 bool fwd_like_fuses_pool(const GemmGeom& g, const GemmPlan& plan);
 bool fwd_like_packs_weights(const GemmPlan& plan);
@@ -249,7 +249,7 @@ double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);
-int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, hipStream_t st);
+int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, float* colsum, hipStream_t st);
 
 // fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups, once: as launch_wgrad
 bool fc_dw_supported(const WgradGeom& g, bool in_step);
@@ -337,9 +337,17 @@ int bias_grad_chunks(size_t rows, int cols);  // row chunks (= partial sums per 
 int launch_bias_grad(size_t rows, int cols, const bf16_t* dy, float* db, float* part, hipStream_t st);
 int launch_maxpool_fwd(int N, int H, int W, int C, int win, int stp, const bf16_t* x, bf16_t* y,
                        uint8_t* am, hipStream_t st);
+// mean of B row losses in a fixed order, by a work-group of its own behind another kernel's (loss == NULL: none)
+struct LossMean {
+    const float* row_loss;
+    float* loss;
+    int B;
+};
+// colsum: [maxpool_bwd_colsum_rows()][C] column sums of the stored gradient; mean: only where there are such rows
 int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_t* dy, const uint8_t* am,
-                       const bf16_t* ry, bf16_t* dx, hipStream_t st);
-int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labels, float* loss,
+                       const bf16_t* ry, bf16_t* dx, hipStream_t st, float* colsum = nullptr, const LossMean* mean = nullptr);
+int maxpool_bwd_colsum_rows(int N, int H, int W, int C, int win, int stp);  // 0: the kernel has none
+int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labels, float* loss,  // loss == NULL: the rows' alone
                         float* row_loss, bf16_t* dz, hipStream_t st);
 int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, bool once, hipStream_t st);
 int launch_cast(size_t n, const float* src, bf16_t* dst, hipStream_t st);
