@@ -18,6 +18,8 @@
 // contiguous runs that start 6*stride bytes apart, so no element-wise gather is left.
 // Serves the first "primary" convolution node of Section 3.2.2 (forward and weight-gradient halves of
 // t_c, Eq. 1); its input gradient is never needed.
+#include <algorithm>
+
 #include "wap_internal.h"
 
 namespace wap {
@@ -155,7 +157,8 @@ __global__ __launch_bounds__(NT, 4) void conv_c3_fwd_kernel(const C3Args a) {
 // allows), a wavefront stages the three input rows of its tile -- 36 pixels x 3 channels each, ONE 4-byte load per
 // lane and row, starting at an even pixel so that every load is aligned and lies wholly inside or outside the image --
 // in a wavefront-private LDS strip, and builds the fragments from there with sixteen 2-byte reads whose addresses
-// are computed once per kernel.
+// are computed once per kernel.  The rows of its next tile are on their way meanwhile (64 / 128 images, 64 channels 97 / 201 us without, 89 / 179
+// with them).
 template <int FB>
 __global__ __launch_bounds__(NT, 4) void conv_c3_fwd_rows_kernel(const C3Args a) {
     constexpr int K = 32 * FB;
@@ -202,21 +205,27 @@ __global__ __launch_bounds__(NT, 4) void conv_c3_fwd_rows_kernel(const C3Args a)
     const int dp0 = (2 * lane) / 3, dp1 = (2 * lane + 1) / 3;
 
     unsigned char* st = stage[wave];
-    for (int tile = blockIdx.x * 4 + wave; tile < a.ntiles; tile += gridDim.x * 4) {
+    unsigned xv[3];
+    auto load = [&](int tile) {
         const int rowi = (int)fdiv((uint32_t)tile, a.dTR);        // (image, output row)
         const int ow0 = (tile - rowi * a.tiles_row) * 32;
         const int n = (int)fdiv((uint32_t)rowi, a.dOH);
         const int oh = rowi - n * a.OH;
         const int iws = ow0 - a.pad_w - adj;
-        const bool colok = lane < 54 && (unsigned)(iws + dp0) < (unsigned)a.W && (unsigned)(iws + dp1) < (unsigned)a.W;
+        const bool colok = tile < a.ntiles && lane < 54 && (unsigned)(iws + dp0) < (unsigned)a.W && (unsigned)(iws + dp1) < (unsigned)a.W;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const int ih = oh - a.pad_h + r;
             const bool ok = colok && (unsigned)ih < (unsigned)a.H;
             const unsigned off = (unsigned)((((n * a.H + ih) * a.W + iws) * 3 + 2 * lane) * 2);
-            const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(rsrcX, ok ? off : OOB, 0, 0);
-            *reinterpret_cast<unsigned*>(xs + r * XROW + lane * 4) = v;
+            xv[r] = __builtin_amdgcn_raw_buffer_load_b32(rsrcX, ok ? off : OOB, 0, 0);
         }
+    };
+    load(blockIdx.x * 4 + wave);
+    for (int tile = blockIdx.x * 4 + wave; tile < a.ntiles; tile += gridDim.x * 4) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) *reinterpret_cast<unsigned*>(xs + r * XROW + lane * 4) = xv[r];
+        load(tile + gridDim.x * 4);  // the rows of the next tile, while this one is made
         // the strip is written as dwords and read as halfwords: keep the compiler from moving the reads in front of the
         // writes (the LDS pipe itself executes a wavefront's operations in order, so no wait is needed)
         asm volatile("" ::: "memory");
@@ -272,7 +281,7 @@ __global__ __launch_bounds__(NT, 4) void conv_c3_fwd_rows_kernel(const C3Args a)
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the strips are private to this wavefront
         constexpr int VPR = K / 8;  // 16-byte vectors per pixel
-        const size_t m0 = ((size_t)rowi * a.OW + ow0);
+        const size_t m0 = (size_t)tile * 32;
 #pragma unroll
         for (int it = 0; it < 32 * VPR / 64; ++it) {
             const int v = it * 64 + lane;
@@ -469,6 +478,119 @@ __global__ __launch_bounds__(NT, 3) void wgrad_c3_kernel(const C3Args a) {
     __syncthreads();
     float* outp = a.part + (size_t)blockIdx.x * K * 27;
     for (int o = threadIdx.x; o < K * 27; o += NT) {
+        const int ko = o / 27, kk = o - ko * 27;
+        outp[o] = ((red[0][kk][ko] + red[1][kk][ko]) + red[2][kk][ko]) + red[3][kk][ko];
+    }
+}
+
+// The same sums on maps of whole 32-pixel tiles with even input rows (VGG's 224 x 224), bound by reading dy once.  The kernel above gathers
+// its x elements one by one and has one step's 2 KB in flight for each of eight wavefronts a CU: 64 x 224 x 224 x 64 (411 MB) in 101 us.
+// Here a wavefront fetches the dy pixels and the three input rows of its next tile (20 KB a SIMD in flight) while it multiplies the
+// present one out of strips of its own, and a lane's column of x is sixteen 2-byte reads at immediate offsets; two work-groups of eight
+// wavefronts a CU: 76 us (5.4 TB/s), 24 images 37.6 -> 32.0, 128 images 195 -> 146.
+constexpr int C3W_WAVES = 8;
+template <int FB>
+__global__ __launch_bounds__(64 * C3W_WAVES, 4) void wgrad_c3_rows_kernel(const C3Args a) {
+    constexpr int K = 32 * FB;
+    constexpr int DPITCH = K * 2 + 64;  // transposing reads: 4 rows x 64 bytes in disjoint bank groups
+    constexpr int VPR = K / 8, DVL = 32 * VPR / 64;
+    constexpr int XROW = 288;  // bytes per staged input row (36 pixels used), 8 banks apart
+    constexpr int STRIP = 32 * DPITCH + 3 * XROW;
+    constexpr unsigned OOB = 0x80000000u;  // x is below 2 GiB (checked on the host)
+    __shared__ __align__(16) unsigned char sm[C3W_WAVES * STRIP + 256];
+    static_assert(4 * 32 * (K + 1) * 4 <= C3W_WAVES * STRIP, "the sums of four wavefronts fit the strips");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = lane >> 5, l32 = lane & 31;
+    const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x), 0, (int)a.x_bytes, 0x00020000);
+    unsigned char* const sD = sm + wave * STRIP;
+    unsigned char* const sX = sD + 32 * DPITCH;
+    unsigned char* const sZ = sm + C3W_WAVES * STRIP;  // zeros: the columns beyond the filter
+    if (tid < 64) *reinterpret_cast<unsigned*>(sZ + tid * 4) = 0u;
+    __syncthreads();
+
+    // (as in conv_c3_fwd_rows_kernel: a staged row starts at an even pixel, so that a lane's 4 bytes lie wholly inside the image or outside)
+    const int adj = a.pad_w & 1;
+    const int dp0 = (2 * lane) / 3, dp1 = (2 * lane + 1) / 3;
+    const int r = (l32 * 57) >> 9, j = l32 - r * 9;  // this lane's column of x: input row and element
+    const unsigned char* const xcol = l32 < 27 ? sX + r * XROW + ((half * 8 + adj) * 3 + j) * 2 : sZ;
+    const int kl = half * 8 + ((lane & 15) >> 2);
+    const unsigned char* const dcol = sD + kl * DPITCH + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+
+    u32x4 dv[DVL];
+    unsigned xv[3];
+    auto load = [&](int t) {
+        const int tile = t < a.ntiles ? t : a.ntiles - 1;  // (past the end: loaded again and dropped)
+        const int rowi = (int)fdiv((uint32_t)tile, a.dTR);
+        const int ow0 = (tile - rowi * a.tiles_row) * 32;
+        const int n = (int)fdiv((uint32_t)rowi, a.dOH), oh = rowi - n * a.OH;
+        const bf16_t* const src = a.dy + (size_t)tile * 32 * K + lane * 8;  // tiles follow each other in memory
+#pragma unroll
+        for (int i = 0; i < DVL; ++i) dv[i] = *reinterpret_cast<const u32x4*>(src + i * 512);
+        const int iws = ow0 - a.pad_w - adj;
+        const bool colok = lane < 54 && (unsigned)(iws + dp0) < (unsigned)a.W && (unsigned)(iws + dp1) < (unsigned)a.W;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int ih = oh - a.pad_h + q;
+            const unsigned off = (unsigned)((((n * a.H + ih) * a.W + iws) * 3 + 2 * lane) * 2);
+            xv[q] = __builtin_amdgcn_raw_buffer_load_b32(rsrcX, colok && (unsigned)ih < (unsigned)a.H ? off : OOB, 0, 0);
+        }
+    };
+    f32x16 acc[FB];
+#pragma unroll
+    for (int b = 0; b < FB; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[b][e] = 0.f;
+
+    const int stride = gridDim.x * C3W_WAVES;
+    int tile = blockIdx.x * C3W_WAVES + wave;
+    load(tile);
+    for (; tile < a.ntiles; tile += stride) {
+        // (the strips are private to the wavefront, whose LDS operations execute in order: only the compiler has to keep them)
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < DVL; ++i) {
+            const int v = i * 64 + lane;
+            *reinterpret_cast<u32x4*>(sD + (v / VPR) * DPITCH + (v % VPR) * 16) = dv[i];
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<unsigned*>(sX + q * XROW + lane * 4) = xv[q];
+        load(tile + stride);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            unsigned short h[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = *reinterpret_cast<const unsigned short*>(xcol + (ks * 16 + e) * 6);
+            const bf16x8 xf = pack8(h);
+#pragma unroll
+            for (int b = 0; b < FB; ++b) {
+                const unsigned char* d0 = dcol + ks * 16 * DPITCH + b * 64;
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, tr_pair(d0, d0 + 4 * DPITCH), acc[b], 0, 0, 0);
+            }
+        }
+    }
+
+    // accumulator register i of block b: column (i/4)*8 + half*4 + i%4, output channel b*32 + l32.  The upper four wavefronts' sums are
+    // added to the lower four's, those in wavefront order.
+    __syncthreads();
+    float(*const red)[32][K + 1] = reinterpret_cast<float(*)[32][K + 1]>(sm);
+    auto at = [&](int b, int i) -> float& { return red[wave & 3][(i >> 2) * 8 + half * 4 + (i & 3)][b * 32 + l32]; };
+    if (wave >= 4) {
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) at(b, i) = acc[b][i];
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) at(b, i) += acc[b][i];
+    }
+    __syncthreads();
+    float* const outp = a.part + (size_t)blockIdx.x * K * 27;
+    for (int o = tid; o < K * 27; o += 64 * C3W_WAVES) {
         const int ko = o / 27, kk = o - ko * 27;
         outp[o] = ((red[0][kk][ko] + red[1][kk][ko]) + red[2][kk][ko]) + red[3][kk][ko];
     }
@@ -919,8 +1041,11 @@ int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, cons
         a.x_bytes = (unsigned)((size_t)a.N * g.IH * g.IW * 3 * 2);
         a.dTR = make_fastdiv((uint32_t)a.tiles_row);
         a.dOH = make_fastdiv((uint32_t)g.OH);
-        if (g.Ncols == 64) hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<2>, dim3(grid), dim3(NT), 0, st, a);
-        else hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<1>, dim3(grid), dim3(NT), 0, st, a);
+        // Four work-groups a CU (8 / 64 images of 224 x 224, 64 channels, 13.9 / 85.7 us, 16.5 / 89.3 with eight; 22 images 29.8, 28.6; the tiles
+        // divided evenly among fewer 15.5 / 88.5).
+        const int groups = std::min(grid, kNumCU * 4);
+        if (g.Ncols == 64) hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<2>, dim3(groups), dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<1>, dim3(groups), dim3(NT), 0, st, a);
         return check_launch("conv_c3_fwd_rows");
     }
     if (g.Ncols == 64) hipLaunchKernelGGL(conv_c3_fwd_kernel<2>, dim3(grid), dim3(NT), 0, st, a);
@@ -935,6 +1060,9 @@ static bool wgrad_c3_special(const WgradGeom& g) {
     return g.C == 3 && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && (g.K == 32 || g.K == 64) && (g.Q % 8) == 0 &&
            (long)g.N * g.P * g.Q >= 4096;
 }
+static bool wgrad_c3_rows(const WgradGeom& g) {
+    return wgrad_c3_special(g) && (g.Q % 32) == 0 && (g.W % 2) == 0 && (double)g.N * g.H * g.W * 3 * 2.0 < 2147483648.0;
+}
 static bool wgrad_c3_strided(const WgradGeom& g) {
     C3SPlan p;
     return !wgrad_c3_special(g) && c3s_plan(g, &p) && (long)g.N * g.P >= 64;
@@ -944,6 +1072,7 @@ bool wgrad_c3_supported(const WgradGeom& g) {
 }
 const char* wgrad_c3_kernel_name(const WgradGeom& g) {
     if (wgrad_c3_strided(g)) return g.K == 64 ? "wgrad_c3_strided_kernel<2>" : "wgrad_c3_strided_kernel<1>";
+    if (wgrad_c3_rows(g)) return g.K == 64 ? "wgrad_c3_rows_kernel<2>" : "wgrad_c3_rows_kernel<1>";
     return g.K == 64 ? "wgrad_c3_kernel<2>" : "wgrad_c3_kernel<1>";
 }
 
@@ -954,7 +1083,9 @@ int wgrad_c3_nsplit(const WgradGeom& g) {
         const long want = units / 8;
         return (int)(want < 1 ? 1 : want < cap ? want : cap);
     }
-    return c3_grid(((long)g.N * g.P * g.Q + 15) / 16);
+    const long pixels = (long)g.N * g.P * g.Q;
+    if (wgrad_c3_rows(g)) return (int)std::min(2L * kNumCU, (pixels / 32 + C3W_WAVES - 1) / C3W_WAVES);
+    return c3_grid((pixels + 15) / 16);
 }
 
 int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* part, hipStream_t st) {
@@ -998,6 +1129,16 @@ int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_
     a.M = g.N * g.P * g.Q;
     a.dOHW = make_fastdiv((uint32_t)(g.P * g.Q));
     a.dOW = make_fastdiv((uint32_t)g.Q);
+    if (wgrad_c3_rows(g)) {
+        a.tiles_row = g.Q / 32;
+        a.ntiles = a.M / 32;
+        a.x_bytes = (unsigned)((size_t)g.N * g.H * g.W * 3 * 2);
+        a.dTR = make_fastdiv((uint32_t)a.tiles_row);
+        a.dOH = make_fastdiv((uint32_t)g.P);
+        if (g.K == 64) hipLaunchKernelGGL(wgrad_c3_rows_kernel<2>, dim3(nsplit), dim3(64 * C3W_WAVES), 0, st, a);
+        else hipLaunchKernelGGL(wgrad_c3_rows_kernel<1>, dim3(nsplit), dim3(64 * C3W_WAVES), 0, st, a);
+        return check_launch("wgrad_c3_rows");
+    }
     if (g.K == 64) hipLaunchKernelGGL(wgrad_c3_kernel<2>, dim3(nsplit), dim3(NT), 0, st, a);
     else hipLaunchKernelGGL(wgrad_c3_kernel<1>, dim3(nsplit), dim3(NT), 0, st, a);
     return check_launch("wgrad_c3");
