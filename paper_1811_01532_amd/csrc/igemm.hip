@@ -889,11 +889,19 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
     //     for 5x5 (32 x 27 x 27, 64 -> 192 20 / 26): beyond, the larger tiles read fewer weights per output;
     //   the generic kernel: where the predicted time, with a packing launch where there is one to pay for, is below that
     //     kernel's line of 9 us (14 with a split reduction) and 550 TFLOP/s (13 x 67 x 67, 384 -> 32 41 / 52, 28 x 10 x 10 20 / 8).
-    // A forward layer that pools in its epilogue keeps the tiles that can.  Single calls keep their split plans, and single data gradients of
-    // the whole-filter patch kernel with a last block of channels that is not full theirs, though the flat tiles would often be faster there
-    // as well (90 x 90, 64 -> 200 10 instead of 16 us): the tests of divided reductions and of that kernel's weight order run these calls.  Where a
-    // single call needed no workspace, tiles that read a packed copy of the weights take over only if the caller has one for it (not lean).
-    const bool kept = !prepacked && (nsplit > 1 || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
+    // A forward layer that pools in its epilogue keeps the tiles that can.  Single data gradients of the whole-filter patch kernel with a
+    // last block of channels that is not full keep theirs, though the flat tiles would often be faster there as well (90 x 90, 64 -> 200
+    // 10 instead of 16 us): the tests of that kernel's weight order run these calls.  Single calls that split their reduction change over
+    // from 700 pixels on, where 93 drawn layers took 0.47 to 0.9 of the time, 0.68 in the mean (us as a graph, split / flat: 28 x 28,
+    // 512 -> 512 18.1 / 13.9, 256 -> 512 16.0 / 9.7, 4 x 44 x 44, 64 -> 32 15.2 / 9.4; gradient 4 x 30 x 30, 224 -> 160 18.7 / 13.0).  With
+    // fewer, forward layers that read the weights as they are go from 0.5 to 1.5 times (5 x 9 x 9, 224 -> 192 9.1 / 13.7: four waits for
+    // weights one after another, and too few work-groups to hide them), and layers of 169 and 196 pixels were level.  Beyond
+    // 512 channels, where neither prediction was fitted, 13 of 110 layers were slower (gradient 64 x 14, 800 -> 928 31.1 / 34.8).  5x5 splits of
+    // the patch kernel stay: their prediction and the flat tiles' are too close to act on.  Where a single call needed no workspace, tiles
+    // that read a packed copy of the weights take over only if the caller has one for it (not lean); where it needed some, a caller with
+    // just that much keeps the split.
+    const bool split = !prepacked && nsplit > 1;
+    const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
         size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
@@ -907,6 +915,8 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         if (!prepacked && p.ws_bytes == 0) {
             if (raw) need = 0;
             else if (lean) tile = 0;
+        } else if (split && lean && need > p.ws_bytes) {
+            tile = 0;
         }
         bool wins;
         if (cfg == 7 && nsplit > 1) wins = true;
@@ -916,7 +926,9 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
             // The flat tiles' own prediction falls short where the two are close, most for single fragments of a 5x5 filter; a packing launch takes 3.
             const double other = us_beside_flat(g, cfg, nsplit, p.tile, ktiles, t);
             const double short_of = g.R == 5 ? (tile == 14 ? 1.4 : 1.1) : cfg < 5 ? (nsplit > 1 ? 1.0 : 1.15) : nsplit > 1 ? 1.05 : 1.1;
-            wins = other == 0 || us * short_of + (prepacked || raw ? 0 : 3) < other + (prepacked || cfg < 5 ? 0 : 3);
+            // Weights read as they are cost a wait of about 3 for every turn of a wavefront after its first; single calls leave a split for a tenth.
+            const int turns = split && raw ? (g.IC / 32 - 1) / (tile % 10) : 0;
+            wins = other == 0 || us * short_of + 3 * turns + (prepacked || raw ? 0 : 3) < (split ? 0.9 : 1.0) * (other + (prepacked || cfg < 5 ? 0 : 3));
         }
         if (tile && wins) {
             cfg = 16;
