@@ -286,8 +286,8 @@ __global__ __launch_bounds__(NT) void conv_wreg_kernel(const WArgsR a) {
 // A wavefront packs RUN steps of one channel block.  Bound by latency and address arithmetic, so what it packs is
 // found on the scalar unit and a lane has all its loads in flight: whole 128-byte lines of a row forward; for the data
 // gradient eight rows x 4 channels a lane, turned around in registers (byte permutes) instead of fetched 2 bytes at a time.
-// Every weight of a step, us, one vector a thread with 2-byte fetches / this: VGG-16 (118 MB) 33.4 / 28.6, AlexNet-style (20 MB)
-// 9.2 / 8.0.
+// Every weight of a step, us, one vector a thread with 2-byte fetches / this, a job for each copy: VGG-16 (118 MB)
+// 33.4 / 28.6, AlexNet-style (20 MB) 9.2 / 8.0.
 constexpr int PACK_RUN = 4;
 __host__ __device__ inline size_t pack_groups(int Ncols, int Kred, int run) {
     return (size_t)((Ncols + 31) / 32) * ((Kred / 16 + run - 1) / run);
@@ -343,6 +343,52 @@ __device__ __forceinline__ void pack_group(const bf16_t* __restrict__ w, u32x4* 
     }
 }
 
+// Both copies of a layer's weights from one reading: a wavefront takes 32 filters x 64 neighbouring elements of one tap, which are four steps
+// of one channel block forward and two steps of two blocks for the data gradient.  It loads whole lines of eight filters' rows (4 elements a
+// lane), turns them around in registers for the data gradient, and sends both copies through the LDS so that its stores are whole lines too (a
+// lane's own vectors lie 64 bytes apart).  Every weight of a step, us, a job for each copy / both with the forward fragments loaded again and
+// strided stores / stores through the LDS / this: VGG-16 (29 MB read, 59 written) at 8 images 29.8 / 23.7 / 21.1 / 20.2, at 22 30.5 / 26.0 / 23.1 / 20.2,
+// AlexNet-style 7.5 / 7.1 / 6.2 / 6.1 .. 7.1.
+constexpr int PACK_PITCH = 144;  // bytes of the LDS between two filters
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void pack_both(const bf16_t* __restrict__ w, u32x4* __restrict__ fwd, u32x4* __restrict__ back, int K, int C,
+                                          int taps, unsigned group, unsigned char* stage) {
+    const int lane = threadIdx.x & 63;
+    const unsigned runs = (unsigned)(taps * C) / 64, blk = group / runs, run = group - blk * runs;
+    const int k0 = blk * 32, tap = run * 64 / C, c0 = run * 64 - tap * C;
+    const size_t row = (size_t)taps * C, ksteps = (size_t)taps * K / 16;
+    const bf16_t* const src = w + k0 * row + run * 64;
+    u32x4* const of = fwd + ((size_t)blk * (row / 16) + run * 4) * 64;
+    u32x4* const ob = back + ((size_t)(c0 / 32) * ksteps + ((size_t)(taps - 1 - tap) * K + k0) / 16) * 64;
+    const int kg = lane >> 4, cl = (lane & 15) * 4;  // filters k0 + kg * 8 .. + 7, channels c0 + cl .. + 3
+    u32x2 h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = *reinterpret_cast<const u32x2*>(src + (kg * 8 + e) * row + cl);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) *reinterpret_cast<u32x2*>(stage + (kg * 8 + e) * PACK_PITCH + cl * 2) = h[e];
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        of[u * 64 + lane] = *reinterpret_cast<const u32x4*>(stage + (lane & 31) * PACK_PITCH + u * 32 + (lane >> 5) * 16);
+    wave_lds_sync();
+    u32x4* const turned = reinterpret_cast<u32x4*>(stage);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        u32x4 v;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            v[d] = __builtin_amdgcn_perm(h[2 * d + 1][j >> 1], h[2 * d][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+        turned[(cl >> 5) * 128 + (kg >> 1) * 64 + (kg & 1) * 32 + (cl & 31) + j] = v;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ob[(size_t)(i >> 1) * ksteps * 64 + (i & 1) * 64 + lane] = turned[i * 64 + lane];
+}
+
 constexpr int PACK_WAVES = 4;  // per work-group, each with a group of its own
 __device__ __forceinline__ unsigned pack_wave() {
     return blockIdx.x * PACK_WAVES + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -364,6 +410,12 @@ __global__ __launch_bounds__(64 * PACK_WAVES) void pack_weights_multi_kernel(con
     int j = 0;
     while (j + 1 < js.n && g >= js.first[j + 1]) ++j;
     const PackJob& b = js.job[j];
+    if (b.flip == 2) {
+        __shared__ __align__(16) unsigned char stage[PACK_WAVES][32 * PACK_PITCH];
+        pack_both(reinterpret_cast<const bf16_t*>(base + b.w_off), reinterpret_cast<u32x4*>(base + b.out_off),
+                  reinterpret_cast<u32x4*>(base + b.back_off), b.Ncols, b.IC, b.R * b.S, g - js.first[j], stage[threadIdx.x >> 6]);
+        return;
+    }
     pack_group<PACK_RUN>(reinterpret_cast<const bf16_t*>(base + b.w_off), reinterpret_cast<u32x4*>(base + b.out_off), b.Ncols, b.Kred, b.IC, b.R,
                b.S, b.flip, g - js.first[j]);
 }
@@ -384,9 +436,17 @@ bool wreg_supported(const GemmGeom& g) {
 size_t wreg_smem_bytes() { return (size_t)NSTAGE * A_STAGE; }
 
 void pack_jobs_add(PackJobs& js, const GemmGeom& g, bool flip, size_t w_off, size_t out_off) {
+    for (int j = 0; flip && j < js.n; ++j) {  // the same filters are packed for the forward pass: both from one reading
+        PackJob& f = js.job[j];
+        if (f.flip || f.w_off != w_off || f.Ncols != g.IC || f.IC != g.Ncols || f.R != g.R || f.S != g.S || f.IC % 64 != 0 || f.Ncols % 32 != 0) continue;
+        f.flip = 2;
+        f.back_off = out_off;
+        return;
+    }
     PackJob& b = js.job[js.n];
     b.w_off = w_off;
     b.out_off = out_off;
+    b.back_off = 0;
     b.Ncols = g.Ncols;
     b.Kred = g.Kred;
     b.IC = g.IC;

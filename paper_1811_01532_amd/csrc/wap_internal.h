@@ -261,8 +261,8 @@ inline size_t wreg_wt_bytes(const GemmGeom& g) { return (size_t)((g.Ncols + 31) 
 int launch_pack_weights(const GemmGeom& g, bool flip, const bf16_t* w, void* Wp, hipStream_t st);
 // All packing jobs of a launch list in one kernel (offsets are relative to one base pointer).
 struct PackJob {
-    size_t w_off, out_off;  // byte offsets of the source weights and of the packed copy
-    int Ncols, Kred, IC, R, S, flip;
+    size_t w_off, out_off, back_off;  // byte offsets of the source weights and of the packed copies (forward or data gradient; both: forward, data gradient)
+    int Ncols, Kred, IC, R, S, flip;  // flip: 0 forward, 1 data gradient, 2 both
 };
 constexpr int kMaxPackJobs = 32;
 struct PackJobs {
