@@ -898,8 +898,8 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
     // weights one after another, and too few work-groups to hide them), and layers of 169 and 196 pixels were level.  Beyond
     // 512 channels, where neither prediction was fitted, 13 of 110 layers were slower (gradient 64 x 14, 800 -> 928 31.1 / 34.8).  5x5 splits of
     // the patch kernel stay: their prediction and the flat tiles' are too close to act on.  Where a single call needed no workspace, tiles
-    // that read a packed copy of the weights take over only if the caller has one for it (not lean); where it needed some, a caller with
-    // just that much keeps the split.
+    // that read a packed copy of the weights take over only if the caller has one for it (not lean); where it needed some, only
+    // if that is enough (the two queries of a layer stay what they were).
     const bool split = !prepacked && nsplit > 1;
     const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
@@ -915,7 +915,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         if (!prepacked && p.ws_bytes == 0) {
             if (raw) need = 0;
             else if (lean) tile = 0;
-        } else if (split && lean && need > p.ws_bytes) {
+        } else if (split && need > p.ws_bytes) {
             tile = 0;
         }
         bool wins;

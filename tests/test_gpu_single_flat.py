@@ -1,6 +1,6 @@
-"""GPU parity of single convolutions whose divided reduction runs on the flat tiles: the least pixels that do so and one row fewer, channels past the rule, weights read as
-they are and packed, channels that are no block of 32, rows of odd length, no padding and more than the filter's half, the ReLU derivative and
-a max-pool in the data gradient; a workspace that holds only the partial sums keeps the divided plan."""
+"""GPU parity of single convolutions whose divided reduction runs on the flat tiles: the least pixels that do so and one row fewer,
+channels past the rule, weights read as they are and packed, channels that are no block of 32, rows of odd length, no padding and more than the filter's half, the ReLU derivative and
+a max-pool in the data gradient; filters that outgrow the partial sums' workspace keep the divided plan."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # N, H, W, C, K, filter, padding, forward / data gradient on flat tiles
 CASES = [(1, 28, 25, 128, 64, 3, 1, True, True), (1, 27, 25, 128, 64, 3, 1, False, False), (2, 19, 19, 96, 224, 3, 1, True, None), (1, 27, 27, 64, 192, 5, 2, False, None),
          (3, 17, 17, 256, 104, 3, 1, True, None), (3, 21, 17, 104, 256, 3, 0, None, True), (7, 9, 13, 64, 128, 3, 2, True, True), (3, 25, 25, 32, 192, 5, 2, True, None),
-         (3, 16, 16, 272, 32, 5, 2, None, True), (4, 30, 30, 160, 224, 3, 1, True, True), (1, 28, 25, 544, 64, 3, 1, False, None), (4, 26, 26, 408, 480, 5, 2, None, True)]
+         (3, 16, 16, 272, 32, 5, 2, None, True), (4, 30, 30, 160, 224, 3, 1, True, True), (1, 28, 25, 544, 64, 3, 1, False, None), (4, 26, 26, 408, 480, 5, 2, None, False)]
 
 
 def _flat(wap, d, p):
@@ -48,21 +48,17 @@ def test_single_calls_on_flat_tiles(orc, N, H, W, C, K, k, pad, fwd, dx):
     need = wap.wap_conv2d_workspace_bytes(d, wap.WAP_PASS_BWD_DATA)
     ref = orc.conv2d_bwd_data(g64, w64, (N, H, W, C), (1, 1), (pad, pad))
     out = torch.full((N * H * W * C + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
-    packed, part = 2 * (-(-C // 32) * 32) * K * k * k, 4 * N * H * W * C  # the packed weights, one split's sums
-    sizes = [need] + ([need - need % part] if need == packed and need >= 2 * part else [])
-    for n in sizes:
-        ws = gu.workspace(n)
-        wap.wap_conv2d_bwd_data(d, gd, wd, out, ws)
-        torch.cuda.synchronize()
-        assert torch.isnan(out[-8:].float()).all() and gu.rel_err(gu.host_f64(out[:-8]).reshape(ref.shape), ref) <= gu.TOL_BF16_OUT
-        wap.wap_conv2d_bwd_data_relu(d, gd, wd, xd, out, ws)
-        torch.cuda.synchronize()
-        assert gu.rel_err(gu.host_f64(out[:-8]).reshape(ref.shape), np.where(x64 > 0, ref, 0.0)) <= gu.TOL_BF16_OUT
-    assert len(sizes) == (2 if C == 408 else 1)
+    ws = gu.workspace(need)
+    wap.wap_conv2d_bwd_data(d, gd, wd, out, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[-8:].float()).all() and gu.rel_err(gu.host_f64(out[:-8]).reshape(ref.shape), ref) <= gu.TOL_BF16_OUT
+    wap.wap_conv2d_bwd_data_relu(d, gd, wd, xd, out, ws)
+    torch.cuda.synchronize()
+    assert gu.rel_err(gu.host_f64(out[:-8]).reshape(ref.shape), np.where(x64 > 0, ref, 0.0)) <= gu.TOL_BF16_OUT
     if d.P % 2 or d.Q % 2:
         return
-    gp, am = np.zeros((N, d.P // 2, d.Q // 2, K)), si.rng(985, K).integers(0, 4, (N, d.P // 2, d.Q // 2, K)).astype(np.uint8)
-    gpb = si.normal_bf16(si.rng(986, K), gp.shape)
+    am = si.rng(985, K).integers(0, 4, (N, d.P // 2, d.Q // 2, K)).astype(np.uint8)
+    gpb = si.normal_bf16(si.rng(986, K), am.shape)
     gp = orc.bf16_bits_to_f64(gpb)
     full = np.zeros((N, d.P, d.Q, K))
     for i in range(4):
