@@ -897,11 +897,12 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
     // fewer, forward layers that read the weights as they are go from 0.5 to 1.5 times (5 x 9 x 9, 224 -> 192 9.1 / 13.7: four waits for
     // weights one after another, and too few work-groups to hide them), and layers of 169 and 196 pixels were level.  Beyond
     // 512 channels, where neither prediction was fitted, 13 of 110 layers were slower (gradient 64 x 14, 800 -> 928 31.1 / 34.8).  5x5 splits of
-    // the patch kernel stay: their prediction and the flat tiles' are too close to act on.  Where a single call needed no workspace, tiles
+    // the patch kernel change over only with a reduction of 64 channels, where every wavefront has one turn, and a 32 x 32 block of outputs
+    // a CU at most (27 x 27, 64 -> 192 11.7 / 9.5, 55 x 55, 64 -> 64 11.9 / 9.3); with 96 channels they were 3 to 12 % ahead, with more up to half.  Where a single call needed no workspace, tiles
     // that read a packed copy of the weights take over only if the caller has one for it (not lean); where it needed some, only
     // if that is enough (the two queries of a layer stay what they were).
     const bool split = !prepacked && nsplit > 1;
-    const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
+    const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5 && (g.IC > 64 || (double)g.M * g.Ncols > 1024.0 * kNumCU)))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
         size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));
@@ -925,7 +926,7 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         if (tile && wins) {
             // The flat tiles' own prediction falls short where the two are close, most for single fragments of a 5x5 filter; a packing launch takes 3.
             const double other = us_beside_flat(g, cfg, nsplit, p.tile, ktiles, t);
-            const double short_of = g.R == 5 ? (tile == 14 ? 1.4 : 1.1) : cfg < 5 ? (nsplit > 1 ? 1.0 : 1.15) : nsplit > 1 ? 1.05 : 1.1;
+            const double short_of = g.R == 5 ? (tile == 14 && !(split && g.IC <= 64) ? 1.4 : 1.1) : cfg < 5 ? (nsplit > 1 ? 1.0 : 1.15) : nsplit > 1 ? 1.05 : 1.1;
             // Weights read as they are cost a wait of about 3 for every turn of a wavefront after its first; single calls leave a split for a tenth.
             const int turns = split && raw ? (g.IC / 32 - 1) / (tile % 10) : 0;
             wins = other == 0 || us * short_of + 3 * turns + (prepacked || raw ? 0 : 3) < (split ? 0.9 : 1.0) * (other + (prepacked || cfg < 5 ? 0 : 3));

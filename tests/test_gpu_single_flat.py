@@ -11,7 +11,7 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 # N, H, W, C, K, filter, padding, forward / data gradient on flat tiles
-CASES = [(1, 28, 25, 128, 64, 3, 1, True, True), (1, 27, 25, 128, 64, 3, 1, False, False), (2, 19, 19, 96, 224, 3, 1, True, None), (1, 27, 27, 64, 192, 5, 2, False, None),
+CASES = [(1, 28, 25, 128, 64, 3, 1, True, True), (1, 27, 25, 128, 64, 3, 1, False, False), (2, 19, 19, 96, 224, 3, 1, True, None), (1, 27, 27, 64, 192, 5, 2, True, None), (2, 27, 27, 64, 192, 5, 2, False, None), (1, 30, 30, 96, 64, 5, 2, False, None), (3, 20, 20, 192, 64, 5, 2, None, True),
          (3, 17, 17, 256, 104, 3, 1, True, None), (3, 21, 17, 104, 256, 3, 0, None, True), (7, 9, 13, 64, 128, 3, 2, True, True), (3, 25, 25, 32, 192, 5, 2, True, None),
          (3, 16, 16, 272, 32, 5, 2, None, True), (4, 30, 30, 160, 224, 3, 1, True, True), (1, 28, 25, 544, 64, 3, 1, False, None), (4, 26, 26, 408, 480, 5, 2, None, False)]
 
