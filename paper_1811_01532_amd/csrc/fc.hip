@@ -396,6 +396,15 @@ double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit) {
     return least;
 }
 
+// The plan of 17 to 64 rows that needs no workspace, whatever the generic product takes; false where the stream cannot run.
+bool fc_fwd_whole(const GemmGeom& g, GemmPlan* p) {
+    if (!is_fc(g) || g.M <= 16 || g.M > 64 || g.IC < 8 || !below_2g((double)g.M * g.IC) || !below_2g(16.0 * g.IC)) return false;
+    p->cfg = 10;
+    p->ws_bytes = 0;
+    fc_fwd_plan(g, true, &p->tile, &p->nsplit);
+    return true;
+}
+
 namespace {
 template <int NB>
 int launch_fwd(const FcArgs& a, dim3 grid, hipStream_t st) {

@@ -246,6 +246,7 @@ int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16
 bool fc_fwd_supported(const GemmGeom& g, bool in_step, bool lean);
 bool fc_dx_supported(const GemmGeom& g);
 double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
+bool fc_fwd_whole(const GemmGeom& g, GemmPlan* p);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);

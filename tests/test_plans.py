@@ -149,3 +149,29 @@ wap.wap_fc_fwd(wap.fc_desc(7, 25088, 500), m, m, None, m, Mem(6 * 4 * 7 * 500), 
 wap.wap_fc_fwd(wap.fc_desc(1, 9216, 512), m, m, None, m, Mem(2 * 4 * 512), stream=0)
 """))
     assert sum("wgrad_kernel" in c.kernel for c in calls) == 2 and sum("fc_fwd_kernel" in c.kernel for c in calls) == 2, calls
+
+
+# (inputs, outputs) with row counts whose query is less than what the generic product of fewer rows takes
+ROWS = [(1344, 500), (1088, 572), (1152, 500), (1088, 1000), (1472, 500), (1216, 512), (1536, 240), (2112, 512), (2816, 517), (6080, 1351), (4675, 616)]
+
+
+def test_a_workspace_for_more_rows_serves_fewer(so):
+    """Fully-connected forward passes of 17 to 64 rows in the workspace that the query gives for a larger count: the last, shorter batch.
+    Without any, layers whose larger counts all need one are refused as they are at those."""
+    recorded.run(so, f"""
+m = Mem(1 << 34)
+for i, o in {ROWS}:
+    need = {{n: wap.wap_fc_workspace_bytes(wap.fc_desc(n, i, o), wap.WAP_PASS_FWD) for n in range(17, 65)}}
+    for most in range(18, 65):
+        if any(need[n] > need[most] for n in range(17, most)):
+            for n in range(17, most):
+                wap.wap_fc_fwd(wap.fc_desc(n, i, o), m, m, None, m, Mem(need[most]) if need[most] else None, stream=0)
+for n in range(17, 65):
+    for ws in (None, Mem(1024)):
+        try:
+            wap.wap_fc_fwd(wap.fc_desc(n, 25088, 4096), m, m, None, m, ws, stream=0)
+        except wap.WapError as e:
+            assert e.status == wap.WAP_EWORKSPACE
+        else:
+            raise AssertionError(n)
+""")
