@@ -187,7 +187,7 @@ int wap_conv2d_workspace_bytes(const wap_conv_desc* d, int pass, size_t* bytes_o
     if (!bytes_out) return set_error(WAP_EINVAL, "bytes_out is NULL");
     if (pass == WAP_PASS_FWD) *bytes_out = plan_conv_fwd(geom_conv_fwd(*d)).ws_bytes;
     else if (pass == WAP_PASS_BWD_DATA) *bytes_out = plan_fwd_like(geom_conv_dgrad(*d), true).ws_bytes;
-    else if (pass == WAP_PASS_BWD_WEIGHT) *bytes_out = plan_wgrad(geom_conv_wgrad(*d)).ws_bytes;
+    else if (pass == WAP_PASS_BWD_WEIGHT) *bytes_out = wgrad_query_bytes(geom_conv_wgrad(*d));
     else return set_error(WAP_EINVAL, "unknown pass %d", pass);
     return WAP_OK;
 }

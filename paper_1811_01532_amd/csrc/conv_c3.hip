@@ -1088,6 +1088,13 @@ int wgrad_c3_nsplit(const WgradGeom& g) {
     return c3_grid((pixels + 15) / 16);
 }
 
+// The partial sums that a workspace query counts.  Of few tiles the rows kernel makes fewer than the kernel of conv_thin.hip makes of the
+// smaller minibatches that go there (8 x 32 -> 64 channels, 16 images 16, 15 images 30): a workspace for the larger one has to serve these.
+int wgrad_c3_query_splits(const WgradGeom& g) {
+    const int n = wgrad_c3_nsplit(g);
+    return wgrad_c3_rows(g) ? std::max(n, c3_grid(((long)g.N * g.P * g.Q + 15) / 16)) : n;
+}
+
 int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* part, hipStream_t st) {
     if (!wgrad_c3_supported(g)) return set_error(WAP_EINVAL, "internal: 3-channel weight-gradient kernel not applicable");
     if (wgrad_c3_strided(g)) {

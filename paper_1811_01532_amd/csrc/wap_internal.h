@@ -172,6 +172,7 @@ struct WgradPlan {
     size_t ws_bytes;
 };
 WgradPlan plan_wgrad(const WgradGeom& g, bool in_step = false, bool lean = false);  // lean: at least four reduction steps a split
+size_t wgrad_query_bytes(const WgradGeom& g);  // workspace query of a single call: what the plan needs, and no less than fewer images do
 // unpool_am: dy is the gradient of the 2x2 / stride-2 max-pooled output (N x P/2 x Q/2 x K) and unpool_am the pool's
 // argmax; only where wgrad_fuses_unpool() says so.
 // sgd: apply the update to the parameters instead of storing dW (dw may then be NULL); only where wgrad_fuses_sgd()
@@ -225,6 +226,7 @@ int launch_conv_c3_rows(const GemmGeom& g, const bf16_t* x, const bf16_t* w, con
 bool wgrad_c3_supported(const WgradGeom& g);
 const char* wgrad_c3_kernel_name(const WgradGeom& g);
 int wgrad_c3_nsplit(const WgradGeom& g);
+int wgrad_c3_query_splits(const WgradGeom& g);
 int launch_wgrad_c3(const WgradGeom& g, int nsplit, const bf16_t* x, const bf16_t* dy, float* part, hipStream_t st);
 
 // 1 .. 4 input channels, any filter and stride, output channels a multiple of 8 (conv_thin.hip)

@@ -526,6 +526,11 @@ WgradPlan plan_wgrad(const WgradGeom& g, bool in_step, bool lean) {
     return p;
 }
 
+size_t wgrad_query_bytes(const WgradGeom& g) {
+    const WgradPlan p = plan_wgrad(g);
+    return p.cfg == 4 ? (size_t)wgrad_c3_query_splits(g) * g.K * g.R * g.S * g.C * sizeof(float) : p.ws_bytes;
+}
+
 int launch_wgrad(const WgradGeom& g, const WgradPlan& plan, const bf16_t* x, const bf16_t* dy,
                  float* dw, void* ws, hipStream_t st, hipEvent_t ev_mid, const uint8_t* unpool_am,
                  const SgdFuse* sgd, int max_groups, bool once) {

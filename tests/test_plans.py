@@ -175,3 +175,18 @@ for n in range(17, 65):
         else:
             raise AssertionError(n)
 """)
+
+
+@pytest.mark.parametrize("H,W,K", [(14, 64, 32), (8, 32, 64), (16, 32, 64), (32, 32, 32), (20, 96, 64), (7, 160, 64)])
+def test_a_first_layer_workspace_for_more_images_serves_fewer(so, H, W, K):
+    """Weight gradient of a 3x3 first layer: below 4096 pixels another kernel takes it, in the workspace for any larger number of images."""
+    recorded.run(so, f"""
+m = Mem(1 << 34)
+first = -(-4096 // {H * W})
+for most in range(first, first + 70):
+    w = Mem(wap.wap_conv2d_workspace_bytes(wap.conv_desc(most, {H}, {W}, 3, {K}, 3, 3, 1, 1), wap.WAP_PASS_BWD_WEIGHT))
+    for n in range(1, most):
+        d = wap.conv_desc(n, {H}, {W}, 3, {K}, 3, 3, 1, 1)
+        wap.wap_conv2d_bwd_weight(d, m, m, m, w, stream=0)
+        wap.wap_conv2d_bwd_weight_sgd(d, m, m, m, m, 0.1, m, w, stream=0)
+""")
