@@ -225,7 +225,8 @@ __global__ __launch_bounds__(NT, 4) void conv_c3_fwd_rows_kernel(const C3Args a)
     for (int tile = blockIdx.x * 4 + wave; tile < a.ntiles; tile += gridDim.x * 4) {
 #pragma unroll
         for (int r = 0; r < 3; ++r) *reinterpret_cast<unsigned*>(xs + r * XROW + lane * 4) = xv[r];
-        load(tile + gridDim.x * 4);  // the rows of the next tile, while this one is made
+        // the rows of the next tile, while this one is made (asked for behind the last one as well, 1 x 64 x 64 took 3.50 instead of 3.38 us)
+        if (tile + (int)gridDim.x * 4 < a.ntiles) load(tile + gridDim.x * 4);
         // the strip is written as dwords and read as halfwords: keep the compiler from moving the reads in front of the
         // writes (the LDS pipe itself executes a wavefront's operations in order, so no wait is needed)
         asm volatile("" ::: "memory");
@@ -1041,8 +1042,9 @@ int launch_conv_c3_fwd(const GemmGeom& g, const bf16_t* x, const bf16_t* w, cons
         a.x_bytes = (unsigned)((size_t)a.N * g.IH * g.IW * 3 * 2);
         a.dTR = make_fastdiv((uint32_t)a.tiles_row);
         a.dOH = make_fastdiv((uint32_t)g.OH);
-        // Four work-groups a CU (8 / 64 images of 224 x 224, 64 channels, 13.9 / 85.7 us, 16.5 / 89.3 with eight; 22 images 29.8, 28.6; the tiles
-        // divided evenly among fewer 15.5 / 88.5).
+        // Four work-groups a CU.  us with four / eight, 224 x 224, 64 channels: 4 images 9.6 / 11.3, 8 13.4 / 15.5, 64 85.1 / 89.0, 128 174 / 179;
+        // from 16 to 48 images eight are up to 3 % ahead (22 29.1 / 28.8, 48 59.9 / 57.9), too little for a line of their own.  The tiles divided
+        // evenly among fewer: 8 images 15.5, 64 88.5.
         const int groups = std::min(grid, kNumCU * 4);
         if (g.Ncols == 64) hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<2>, dim3(groups), dim3(NT), 0, st, a);
         else hipLaunchKernelGGL(conv_c3_fwd_rows_kernel<1>, dim3(groups), dim3(NT), 0, st, a);
