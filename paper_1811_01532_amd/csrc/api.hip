@@ -360,7 +360,7 @@ static int bwd_weight_sgd(const WgradGeom& g, const void* x, const void* dy, flo
     if (!aligned16(dw_scratch)) return set_error(WAP_EINVAL, "dw_scratch is not 16-byte aligned");
     WAP_TRY(launch_wgrad(g, p, (const bf16_t*)x, (const bf16_t*)dy, dw_scratch, ws, st));
     const size_t n = (size_t)g.K * g.R * g.S * g.C;
-    return launch_sgd(n, w32, dw_scratch, lr, (bf16_t*)w_bf16, beyond_cache(10.0 * n), st);
+    return launch_sgd(n, w32, dw_scratch, lr, (bf16_t*)w_bf16, sgd_once(n, true), st);
 }
 
 int wap_conv2d_bwd_weight_sgd(const wap_conv_desc* d, const void* x, const void* dy, float* w32, void* w_bf16,
@@ -574,7 +574,7 @@ int wap_sgd_update(int64_t n, float* w32, const float* dw, float lr, void* w_bf1
     WAP_TRY(check_ptr(w32, "w32"));
     WAP_TRY(check_ptr(dw, "dw"));
     if (w_bf16 && !aligned16(w_bf16)) return set_error(WAP_EINVAL, "w_bf16 is not 16-byte aligned");
-    return launch_sgd((size_t)n, w32, dw, lr, (bf16_t*)w_bf16, beyond_cache(10.0 * n), (hipStream_t)stream);
+    return launch_sgd((size_t)n, w32, dw, lr, (bf16_t*)w_bf16, sgd_once((size_t)n, w_bf16 != nullptr), (hipStream_t)stream);
 }
 
 int wap_cast_f32_bf16(int64_t n, const float* src, void* dst, void* stream) {

@@ -950,8 +950,8 @@ int launch_bias_grad(size_t rows, int cols, const bf16_t* dy, float* db, float* 
 }
 
 int launch_relu_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dx, size_t n, hipStream_t st) {
-    // (in place the line is higher: 77 M elements, 308 MB, 60 through and 63.5 us past the cache, 268 M 360 and 255)
-    const bool once = beyond_cache((dy == dx ? 3.0 : 6.0) * n);
+    // (us through / past the cache: 46 M elements 39.7 / 42.4, 50 M 46.2 / 46.4, 56 M 56.3 / 52.1; in place 76 M 65.3 / 69.7, 88 M 82.3 / 80.1, 96 M 97 / 87)
+    const bool once = beyond_cache((dy == dx ? 3.0 : 5.35) * n);
     in_pieces(n, 8, [&](size_t at, size_t m, dim3 grid) {
         if (once) hipLaunchKernelGGL(relu_bwd_kernel<true>, grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
         else hipLaunchKernelGGL(relu_bwd_kernel<false>, grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
@@ -1032,6 +1032,10 @@ int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labe
     hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(kThreads), 0, st, LossMean{row_loss, loss, B});
     return check_launch("loss_mean");
 }
+
+// Update of a call of its own, us through / past the cache: 24 M weights 47.4 / 50.7, 32 M 64.7 / 67.2, 36 M 73.5 / 74.0, 40 M 93.5 / 83.8; without a
+// bf16 copy 28 M 46.5 / 51.6, 44 M 76.9 / 80.4, 46 M 87.4 / 84.0.
+bool sgd_once(size_t n, bool copy) { return beyond_cache((copy ? 7.4 : 5.95) * n); }
 
 int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, bool once, hipStream_t st) {
     in_pieces(n, 4, [&](size_t at, size_t m, dim3 grid) {

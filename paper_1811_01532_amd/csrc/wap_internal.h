@@ -57,8 +57,8 @@ constexpr int kNumCU = 256;
 constexpr int kNumXCD = 8;
 // Memory that a call or a step passes over once, in bytes: beyond the 256 MiB that the chip caches, what is kept there on the way
 // (non-temporal accesses do not) only drives out what is used again, and its dirty lines are written back when something else is
-// read.  Update of 16.8, 67.1 and 134 M weights (10 bytes each), one 16-byte group a thread, through / past the cache 29, 164, 321 /
-// 35, 127, 250 us.
+// read.  A kernel's line lies where its calls, repeated on the same tensors, take the same time both ways.  A good part of what is a little
+// larger than the cache is still found there, so some callers count less than their footprint.
 inline bool beyond_cache(double bytes) { return bytes > 268435456.0; }
 
 // ---- SGD update fused into the kernel that produces a weight gradient ----
@@ -352,6 +352,7 @@ int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_
 int maxpool_bwd_colsum_rows(int N, int H, int W, int C, int win, int stp);  // 0: the kernel has none
 int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labels, float* loss,  // loss == NULL: the rows' alone
                         float* row_loss, bf16_t* dz, hipStream_t st);
+bool sgd_once(size_t n, bool copy);  // whether a single update's fp32 operands pass the cache
 int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, bool once, hipStream_t st);
 int launch_cast(size_t n, const float* src, bf16_t* dst, hipStream_t st);
 

@@ -190,3 +190,13 @@ for most in range(first, first + 70):
         wap.wap_conv2d_bwd_weight(d, m, m, m, w, stream=0)
         wap.wap_conv2d_bwd_weight_sgd(d, m, m, m, m, 0.1, m, w, stream=0)
 """)
+
+
+def test_operands_pass_the_cache_only_where_that_is_faster(so):
+    """Elements around the sizes from which single updates and ReLU derivatives take the same time through and past the cache."""
+    def once(calls):
+        return [c.kernel.split("_kernel")[1].startswith("ILb1E") for c in recorded.launches(recorded.run(so, "m = Mem(1 << 40)\nm2 = Mem(1 << 40, 1 << 41)\n" + calls))]
+    assert once("for n in (24, 28, 34, 36, 38, 60): wap.wap_sgd_update(n * 10**6, m, m, 0.1, m, stream=0)") == [False] * 4 + [True] * 2
+    assert once("for n in (28, 34, 44, 46, 60): wap.wap_sgd_update(n * 10**6, m, m, 0.1, None, stream=0)") == [False] * 3 + [True] * 2
+    assert once("for n in (42, 46, 48, 52, 77): wap.wap_relu_bwd(m, m, m2, n * 10**6, stream=0)") == [False] * 3 + [True] * 2
+    assert once("for n in (52, 77, 84, 92): wap.wap_relu_bwd(m, m, m, n * 10**6, stream=0)") == [False] * 3 + [True]
