@@ -10,16 +10,19 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-CASES = [(17, 64, 16), (31, 512, 1000), (32, 4096, 1000), (33, 4096, 500), (48, 1000, 333), (63, 67, 41), (64, 9216, 512), (64, 515, 4096), (20, 1024, 8192),
-         (40, 22000, 80), (64, 8, 9)]
+# rows, inputs, outputs, and the stream's template arguments in the queried workspace (None: on the other side of the line, the generic kernel)
+CASES = [(17, 64, 16, (True, 2)), (31, 512, 1000, (True, 2)), (32, 4096, 1000, (True, 2)), (33, 4096, 500, (True, 4)), (48, 1000, 333, (True, 4)),
+         (63, 67, 41, (False, 4)), (64, 9216, 512, None), (64, 515, 4096, (False, 4)), (20, 1024, 8192, None), (40, 22000, 80, (True, 4)), (64, 8, 9, (True, 4)),
+         (18, 9, 24, (False, 2)), (20, 27, 40, (False, 2)), (25, 13, 700, (False, 2)), (29, 4099, 515, (False, 2)), (30, 5121, 200, (False, 2)),
+         (32, 1003, 1000, (False, 2)), (17, 11003, 90, (False, 2)), (64, 2107, 90, (False, 4)), (63, 1344, 500, None), (33, 2112, 512, None)]
+# rows that the generic kernel takes, in the workspace that is enough for more rows, bytes
+SHORT = [(63, 1344, 500, 0), (58, 1088, 572, 0), (33, 2112, 512, 409600), (61, 1152, 500, 0)]
 
 
-@pytest.mark.parametrize("B,n_in,n_out", CASES)
-def test_forward_stream_of_several_row_blocks(orc, B, n_in, n_out):
+@pytest.mark.parametrize("B,n_in,n_out,nws", [c[:3] + (None,) for c in CASES] + SHORT)
+def test_forward_stream_of_several_row_blocks(orc, B, n_in, n_out, nws):
+    """nws: bytes of workspace, None: what the query says.  (Which kernel each case runs is asserted without a GPU, in test_plans.py.)"""
     import paper_1811_01532_amd as wap
-    if wap.wap_fc_workspace_bytes(wap.fc_desc(B, n_in, n_out), wap.WAP_PASS_FWD) == 0:
-        name = wap.wap_conv2d_kernel_name(wap.conv_desc(B, 1, 1, n_in, n_out, 1, 1, 1, 0), wap.WAP_PASS_FWD)
-        assert name == ("fc_fwd_kernel<2>" if B <= 32 else "fc_fwd_kernel<4>")
     print(f"[case] fc fwd {B} x {n_in} -> {n_out}", flush=True)
     x = orc.bf16_bits_to_f64(si.normal_bf16(si.rng(960, B + n_in), (B, n_in)))
     x[x == 0] = 1.0
@@ -32,7 +35,8 @@ def test_forward_stream_of_several_row_blocks(orc, B, n_in, n_out):
         xd, Wd = (gu.dev_bf16(si.f32_to_bf16_bits(t.astype(np.float32))) for t in (x, W))
         for relu in (False, True):
             d = wap.fc_desc(B, n_in, n_out, relu=relu)
-            ws = gu.workspace(wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD))
+            nbytes = wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD) if nws is None else nws
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None
             ref = orc.fc_fwd(x, W, bias=bias.astype(np.float64), relu=relu)
             y = torch.full((B * n_out + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
             wap.wap_fc_fwd(d, xd, Wd, torch.from_numpy(bias).cuda(), y, ws)

@@ -2,6 +2,9 @@
 import pytest
 import torch
 
+from tests import gpu_util as gu
+from tests.test_gpu_step import _setup
+
 pytestmark = pytest.mark.gpu
 
 CACHE = 268435456
@@ -65,3 +68,29 @@ def test_fused_update_past_the_cache(B, n_in, n_out):
         wap.wap_sgd_update(n // 8, w2[at:at + n // 8], dw[at:at + n // 8], 0.05, wb2[at:at + n // 8])
     torch.cuda.synchronize()
     assert torch.equal(w32, w2) and torch.equal(wb.view(torch.int16), wb2.view(torch.int16))
+
+
+# networks of more than 26.8 M parameters, whose stored gradients pass the cache: rows that stream, and rows that the tiles take
+STEPS = [("alexnet", 33, 99), ("alexnet", 70, 99), ("vgg16", 129, 32), ("vgg16", 22, 32)]
+
+
+@pytest.mark.parametrize("net,B,image", STEPS)
+def test_stored_fully_connected_gradients(net, B, image):
+    """Each layer's stored weight gradient against the fp64 product of the very operands that the plan keeps, with and without a kept
+    copy of every intermediate."""
+    import paper_1811_01532_amd as wap
+    print(f"[case] stored gradients {net} B={B} image={image}", flush=True)
+    plan, ar, shapes, fcs, *_ = _setup(net, B, image, wap.WAP_STEP_KEEP_GRADS, 560)
+    plan.run(ar.buf)
+    torch.cuda.synchronize()
+    x = shapes[-1]["name"] + (".pool.y" if shapes[-1]["pool"] else ".y")
+    plan2, ar2, *_ = _setup(net, B, image, wap.WAP_STEP_STORE_GRADS, 560)
+    plan2.run(ar2.buf)
+    torch.cuda.synchronize()
+    for name, n_in, n_out, relu in fcs:
+        g = ar.bf16(("gm." if relu else "g.") + name + ".y", (B, n_out)).double()
+        ref = g.t().contiguous() @ ar.bf16(x, (B, n_in)).double()
+        for a in (ar, ar2):
+            e = (a.f32(name + ".dw", (n_out, n_in)).double() - ref).abs().max() / ref.abs().max()
+            assert ref.abs().max() > 0 and e <= gu.TOL_F32_OUT, (name, float(e))
+        x = name + ".y"

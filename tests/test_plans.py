@@ -200,3 +200,31 @@ def test_operands_pass_the_cache_only_where_that_is_faster(so):
     assert once("for n in (28, 34, 44, 46, 60): wap.wap_sgd_update(n * 10**6, m, m, 0.1, None, stream=0)") == [False] * 3 + [True] * 2
     assert once("for n in (42, 46, 48, 52, 77): wap.wap_relu_bwd(m, m, m2, n * 10**6, stream=0)") == [False] * 3 + [True] * 2
     assert once("for n in (52, 77, 84, 92): wap.wap_relu_bwd(m, m, m, n * 10**6, stream=0)") == [False] * 3 + [True]
+
+
+def test_kernels_of_the_forward_stream_cases(so):
+    """Every case that the GPU test of two and four blocks of rows runs, with the workspace it gives: the stream in its four forms, or the
+    generic kernel where the line to it is meant."""
+    from tests.test_gpu_fc_rows import CASES, SHORT
+    assert {c[3] for c in CASES} == {None, (True, 2), (False, 2), (True, 4), (False, 4)}
+    for case in CASES + SHORT:
+        calls = recorded.launches(recorded.run(so, f"""
+m, d = Mem(1 << 34), wap.fc_desc(*{case[:3]})
+need = {case[3] if case in SHORT else "wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD)"}
+wap.wap_fc_fwd(d, m, m, None, m, Mem(need) if need else None, stream=0)
+"""))
+        want = (case[1] % 8 == 0, 2 if case[0] <= 32 else 4) if case in SHORT else case[3]
+        assert ("igemm_kernel" if want is None else "fc_fwd_kernelILb%dELi%dE" % want) in calls[0].kernel, (case, calls)
+        assert len(calls) == 1 or case not in SHORT
+
+
+def test_stored_gradients_of_the_step_cases_pass_the_cache(so):
+    """The kernels behind the GPU test of stored gradients: the stream and the generic tiles in the form that passes the cache."""
+    from tests.test_gpu_past_cache import STEPS
+    for net, B, image in STEPS:
+        names = [c.kernel for c in recorded.launches(recorded.run(so, f"""
+p = wap.StepPlan("{net}", {B}, image={image}, flags=wap.WAP_STEP_STORE_GRADS)
+p.run(Mem(p.arena_bytes()), stream=0x10)
+"""))]
+        want = "Lb0ELb1EEE" if B <= 64 else "ILi128ELi128ELi2ELi2ELi0ELb1EEE"
+        assert any(("fc_dw_kernel" if B <= 64 else "wgrad_kernel") in n and want in n for n in names), (net, B, names)
