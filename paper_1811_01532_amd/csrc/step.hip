@@ -873,9 +873,9 @@ int wap_step_plan_create(const char* net, int32_t minibatch, int32_t image, floa
         Op op;
         op.kind = OP_PACK; op.name = "pack_weights";
         op.kernel = "pack_weights_multi_kernel";
-        for (int i = 0; i < p->packjobs.n; ++i) {  // each copy: read as they are, written in whole blocks of 32 channels
+        for (int i = 0; i < p->packjobs.n; ++i) {  // read as they are, once, and each copy written in whole blocks of 32 channels
             const PackJob& b = p->packjobs.job[i];
-            op.bytes += (b.flip == 2 ? 2.0 : 1.0) * 2.0 * b.Kred * ((double)b.Ncols + (b.Ncols + 31) / 32 * 32);
+            op.bytes += 2.0 * b.Kred * (b.Ncols + (b.flip == 2 ? 2.0 : 1.0) * ((b.Ncols + 31) / 32 * 32));
         }
         p->ops.insert(p->ops.begin(), op);
     }
