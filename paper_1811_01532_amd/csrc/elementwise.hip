@@ -868,7 +868,7 @@ __global__ __launch_bounds__(256) void colsum_finish_kernel(const ColsumJobs js,
     }
 }
 
-// up to 64 chunks of at least eight rows a thread
+// chunks of up to eight rows a thread, 64 of them at most (then of more rows)
 int colsum_chunks(int rows, int cols) {
     const int per = 8 * (256 / colsum_vpb(cols));
     return std::max(1, std::min(64, (rows + per - 1) / per));
