@@ -12,15 +12,16 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// One item a thread: work-groups in flight then walk the tensors together (max-pool of 64 x 224 x 224 x 64 forward / backward 107 / 125
-// us in 4096 work-groups that walk, 101 / 115 so).  The kernels loop, for tensors beyond a grid's threads.
-inline int grid_for(size_t work_items) {
-    size_t b = (work_items + kThreads - 1) / kThreads;
-    size_t cap = (size_t)1 << 22;
-    if (b > cap) b = cap;
-    if (b < 1) b = 1;
-    return (int)b;
+// One item a thread, up to `walk` items in 4096 work-groups at most, which walk the tensor.  More work-groups walk large tensors together (max-pool
+// of 64 x 224 x 224 x 64 forward / backward 107 / 125 us in 4096, 101 / 115 so), but their starts cost something: each launch has its line.
+inline int grid_for(size_t work_items, size_t walk = SIZE_MAX) {
+    const size_t cap = work_items <= walk ? (size_t)kNumCU * 16 : (size_t)1 << 22;
+    return (int)std::max((size_t)1, std::min((work_items + kThreads - 1) / kThreads, cap));
 }
+
+// of updates and ReLU derivatives that do not pass the cache, us walking / one vector a thread, same tensors again: ReLU derivative of 10.1 M elements
+// 10.2 / 10.7, in place 9.1 / 9.7, of 12.5 M level, of 22 M 20.5 / 20.1; update of 5.6 M weights without a copy 10.8 / 11.5, of 7 M level, of 15 M 26.9 / 26.0
+constexpr size_t kWalk = (size_t)3 << 19;
 
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -274,13 +275,26 @@ __global__ __launch_bounds__(1024) void bias_grad_kernel(const bf16_t* __restric
     }
 }
 
+// vector(i) for this thread's i < n, single(i - n) for the `rest` items behind them; with WALK for every one of its items
+template <bool WALK, typename V, typename S>
+__device__ __forceinline__ void walk_items(size_t n, size_t rest, V&& vector, S&& single) {
+    size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if constexpr (WALK)
+        for (const size_t stride = (size_t)gridDim.x * kThreads; i < n; i += stride) vector(i);
+    else if (i < n) {
+        vector(i);
+        return;
+    }
+    if (i - n < rest) single(i - n);
+}
+
 // ---- ReLU backward: bound by memory.  One 16-byte vector a thread; ONCE: the operands pass the cache (beyond_cache), what is
 // written, which the next kernels read, does not.  Walk of 4096 work-groups / this, us: 16.8 M elements 13.9 / 13.8, 67 M 78 / 56,
 // 77 M 89 / 63, 268 M 361 / 253 (6.4 TB/s). ----
-template <bool ONCE>
+template <bool ONCE, bool WALK>
 __global__ __launch_bounds__(kThreads) void relu_bwd_kernel(const bf16_t* dy, const bf16_t* __restrict__ y, bf16_t* dx, size_t n) {
-    const size_t n8 = n / 8, i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n8) {
+    const size_t n8 = n / 8;
+    walk_items<WALK>(n8, n & 7, [&](size_t i) {
         const u32x4 *gp = reinterpret_cast<const u32x4*>(dy) + i, *vp = reinterpret_cast<const u32x4*>(y) + i;
         u32x4 g, v;
         if constexpr (ONCE) {
@@ -297,10 +311,10 @@ __global__ __launch_bounds__(kThreads) void relu_bwd_kernel(const bf16_t* dy, co
             g[k] = lo | hi;
         }
         reinterpret_cast<u32x4*>(dx)[i] = g;
-    } else if (i - n8 < (n & 7)) {
-        const size_t j = n8 * 8 + (i - n8);
+    }, [&](size_t i) {
+        const size_t j = n8 * 8 + i;
         dx[j] = (bf2f(y[j]) > 0.f) ? dy[j] : (bf16_t)0;
-    }
+    });
 }
 
 // ---- max-pool forward: VEC channels of one window per thread, the window's loads issued together.  Bound by the input
@@ -644,11 +658,11 @@ __global__ __launch_bounds__(kThreads) void loss_mean_kernel(const LossMean m) {
 // threads, so that the work-groups in flight walk the tensors together (138 M weights, a walk of 4096 work-groups 465 us, 4.2 TB/s;
 // this 341); ONCE: gradient and master weights pass the cache (beyond_cache), the bf16 copy, which the next forward pass reads, does
 // not (308 us, 6.3 TB/s; in a VGG-16 step at 22 images 394 -> 290). ----
-template <bool ONCE>
+template <bool ONCE, bool WALK>
 __global__ __launch_bounds__(kThreads) void sgd_kernel(size_t n, float* __restrict__ w, const float* __restrict__ dw, float lr,
                                                        bf16_t* __restrict__ wb) {
-    const size_t n4 = n / 4, i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n4) {
+    const size_t n4 = n / 4;
+    walk_items<WALK>(n4, n & 3, [&](size_t i) {
         f32x4* const wp = reinterpret_cast<f32x4*>(w) + i;
         const f32x4* const gp = reinterpret_cast<const f32x4*>(dw) + i;
         f32x4 a, g;
@@ -669,12 +683,12 @@ __global__ __launch_bounds__(kThreads) void sgd_kernel(size_t n, float* __restri
             pk.y = (unsigned)f2bf(a[2]) | ((unsigned)f2bf(a[3]) << 16);
             reinterpret_cast<uint2*>(wb)[i] = pk;
         }
-    } else if (i - n4 < (n & 3)) {
-        const size_t j = n4 * 4 + (i - n4);
+    }, [&](size_t i) {
+        const size_t j = n4 * 4 + i;
         const float a = sgd_apply(w[j], dw[j], lr);
         w[j] = a;
         if (wb) wb[j] = f2bf(a);
-    }
+    });
 }
 
 __global__ void cast_kernel(size_t n, const float* __restrict__ src, bf16_t* __restrict__ dst) {
@@ -702,14 +716,15 @@ __global__ void fill_kernel(bf16_t* p, size_t n, uint32_t seed) {
     }
 }
 
-// n elements, a thread for every whole vector of `vec` and for every element behind them: launch(first, elements, grid), in pieces
-// of whole vectors where one grid (fewer than 2^32 threads) does not do.
+// n elements, an item for every whole vector of `vec` and for every element behind them: launch(first, elements, grid, whether it walks),
+// in pieces of whole vectors where one grid (fewer than 2^32 threads) does not do; `walk` as in grid_for.
 template <typename F>
-void in_pieces(size_t n, size_t vec, F&& launch) {
+void in_pieces(size_t n, size_t vec, size_t walk, F&& launch) {
     const size_t most = vec << 30;
     for (size_t at = 0; at < n; at += most) {
-        const size_t m = std::min(n - at, most);
-        launch(at, m, dim3((unsigned)((m / vec + m % vec + kThreads - 1) / kThreads)));
+        const size_t m = std::min(n - at, most), items = m / vec + m % vec;
+        const int groups = grid_for(items, walk);
+        launch(at, m, dim3((unsigned)groups), (size_t)groups * kThreads < items);
     }
 }
 
@@ -952,9 +967,10 @@ int launch_bias_grad(size_t rows, int cols, const bf16_t* dy, float* db, float* 
 int launch_relu_bwd(const bf16_t* dy, const bf16_t* y, bf16_t* dx, size_t n, hipStream_t st) {
     // (us through / past the cache: 46 M elements 39.7 / 42.4, 50 M 46.2 / 46.4, 56 M 56.3 / 52.1; in place 76 M 65.3 / 69.7, 88 M 82.3 / 80.1, 96 M 97 / 87)
     const bool once = beyond_cache((dy == dx ? 3.0 : 5.35) * n);
-    in_pieces(n, 8, [&](size_t at, size_t m, dim3 grid) {
-        if (once) hipLaunchKernelGGL(relu_bwd_kernel<true>, grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
-        else hipLaunchKernelGGL(relu_bwd_kernel<false>, grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
+    in_pieces(n, 8, once ? 0 : kWalk, [&](size_t at, size_t m, dim3 grid, bool walks) {
+        if (once) hipLaunchKernelGGL((relu_bwd_kernel<true, false>), grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
+        else if (walks) hipLaunchKernelGGL((relu_bwd_kernel<false, true>), grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
+        else hipLaunchKernelGGL((relu_bwd_kernel<false, false>), grid, dim3(kThreads), 0, st, dy + at, y + at, dx + at, m);
     });
     return check_launch("relu_bwd");
 }
@@ -976,7 +992,8 @@ int launch_maxpool_fwd(int N, int H, int W, int C, int win, int stp, const bf16_
                        uint8_t* am, hipStream_t st) {
     const int vec = (C & 7) == 0 ? 8 : 1;
     const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, (H - win) / stp + 1, (W - win) / stp + 1);
-    const dim3 grid(grid_for(a.items)), block(kThreads);
+    // (element by element they walk: 256 x 70 x 70 x 45, window 2, 34.4 us, 43.5 with an item a thread, 28 x 87 x 87 x 81, stride 1, 37.4 / 48.3)
+    const dim3 grid(grid_for(a.items, vec == 8 ? 0 : SIZE_MAX)), block(kThreads);
     if (win != 2 && win != 3) {
         if (vec == 8) hipLaunchKernelGGL(maxpool_fwd_any_kernel<8>, grid, block, 0, st, x, y, am, win, a);
         else hipLaunchKernelGGL(maxpool_fwd_any_kernel<1>, grid, block, 0, st, x, y, am, win, a);
@@ -1004,7 +1021,8 @@ int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_
     if ((colsum || mean) && !rows) return set_error(WAP_EINVAL, "internal: no column sums from this max-pool");
     if (stp == 2 && (win == 2 || win == 3)) {
         const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, (H + 1) / 2, (W + 1) / 2);
-        const dim3 grid((colsum ? rows : grid_for(a.items)) + (mean ? 1 : 0));
+        // (walking element by element as in the forward pass: 256 x 49 x 49 x 42, window 2, 35.0 / 38.8)
+        const dim3 grid((colsum ? rows : grid_for(a.items, vec == 8 ? 0 : SIZE_MAX)) + (mean ? 1 : 0));
         const dim3 threads(colsum ? pool_colsum_threads(C) : kThreads);
 #define WAP_POOL(VEC, WIN, COLSUM, MEAN) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<VEC, WIN, COLSUM, MEAN>), grid, threads, 0, st, dy, am, ry, dx, a, colsum, lm)
 #define WAP_POOL_WIN(VEC, COLSUM, MEAN) do { if (win == 2) WAP_POOL(VEC, 2, COLSUM, MEAN); else WAP_POOL(VEC, 3, COLSUM, MEAN); } while (0)
@@ -1018,7 +1036,7 @@ int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_
         return check_launch("maxpool_bwd");
     }
     const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, H, W);
-    const dim3 grid(grid_for(a.items));
+    const dim3 grid(grid_for(a.items, 0));
     if (vec == 8) hipLaunchKernelGGL(maxpool_bwd_kernel<8>, grid, block, 0, st, dy, am, ry, dx, win, a);
     else hipLaunchKernelGGL(maxpool_bwd_kernel<1>, grid, block, 0, st, dy, am, ry, dx, win, a);
     return check_launch("maxpool_bwd");
@@ -1038,16 +1056,18 @@ int launch_softmax_xent(int B, int classes, const bf16_t* z, const int32_t* labe
 bool sgd_once(size_t n, bool copy) { return beyond_cache((copy ? 7.4 : 5.95) * n); }
 
 int launch_sgd(size_t n, float* w, const float* dw, float lr, bf16_t* wb, bool once, hipStream_t st) {
-    in_pieces(n, 4, [&](size_t at, size_t m, dim3 grid) {
+    in_pieces(n, 4, once ? 0 : kWalk, [&](size_t at, size_t m, dim3 grid, bool walks) {
         bf16_t* const b = wb ? wb + at : nullptr;
-        if (once) hipLaunchKernelGGL(sgd_kernel<true>, grid, dim3(kThreads), 0, st, m, w + at, dw + at, lr, b);
-        else hipLaunchKernelGGL(sgd_kernel<false>, grid, dim3(kThreads), 0, st, m, w + at, dw + at, lr, b);
+        if (once) hipLaunchKernelGGL((sgd_kernel<true, false>), grid, dim3(kThreads), 0, st, m, w + at, dw + at, lr, b);
+        else if (walks) hipLaunchKernelGGL((sgd_kernel<false, true>), grid, dim3(kThreads), 0, st, m, w + at, dw + at, lr, b);
+        else hipLaunchKernelGGL((sgd_kernel<false, false>), grid, dim3(kThreads), 0, st, m, w + at, dw + at, lr, b);
     });
     return check_launch("sgd");
 }
 
 int launch_cast(size_t n, const float* src, bf16_t* dst, hipStream_t st) {
-    hipLaunchKernelGGL(cast_kernel, dim3(grid_for(n / 4 + 1)), dim3(kThreads), 0, st, n, src, dst);
+    // (us walking / one vector a thread: 8.7 M elements 11.8 / 12.6, 13.1 M 16.3 / 17.6, 52 M 48.8 / 52.5, 64 M 68 / 66, 103 M 118 / 106)
+    hipLaunchKernelGGL(cast_kernel, dim3(grid_for(n / 4 + 1, (size_t)15 << 20)), dim3(kThreads), 0, st, n, src, dst);
     return check_launch("cast");
 }
 

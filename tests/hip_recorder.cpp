@@ -23,9 +23,9 @@ thread_local dim3 cfg_grid, cfg_block;
 thread_local size_t cfg_smem;
 thread_local hipStream_t cfg_stream;
 
-void note(const char* fmt, const char* a, const void* b, long c, long d) {
+void note(const char* fmt, const char* a, const void* b, long c, long d, long e = 0) {
     char line[1024];
-    std::snprintf(line, sizeof line, fmt, a, b, c, d);
+    std::snprintf(line, sizeof line, fmt, a, b, c, d, e);
     lines.push_back(line);
 }
 void* handle() { return reinterpret_cast<void*>(0x1000 + 16 * ++handles); }
@@ -51,9 +51,9 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* smem, hipS
     *grid = cfg_grid; *block = cfg_block; *smem = cfg_smem; *st = cfg_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void**, size_t smem, hipStream_t st) {
+hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3, void**, size_t smem, hipStream_t st) {
     std::lock_guard<std::mutex> lock(mu);
-    note("launch %s %p %ld %ld", names[fn].c_str(), st, (long)smem, limits.count(fn) ? (long)limits[fn] : 65536L);
+    note("launch %s %p %ld %ld %ld", names[fn].c_str(), st, (long)smem, limits.count(fn) ? (long)limits[fn] : 65536L, (long)grid.x);
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute, int value) {

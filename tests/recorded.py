@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
-Launch = collections.namedtuple("Launch", "kernel stream smem limit")
+Launch = collections.namedtuple("Launch", "kernel stream smem limit groups")  # groups: along the grid's first axis
 
 PRELUDE = """
 import ctypes, sys
@@ -41,7 +41,7 @@ def build(folder):
 
 
 def run(so, code, printed=None):
-    """The calls that `code` (with `wap`, `Mem` and `rec` at hand) makes, as lists of words: launch kernel stream smem limit,
+    """The calls that `code` (with `wap`, `Mem` and `rec` at hand) makes, as lists of words: launch kernel stream smem limit groups,
     stream handle, record stream, wait stream.  What it prints, a word and a value a line, goes to printed[word]."""
     r = subprocess.run([sys.executable, "-c", PRELUDE + code + EPILOGUE, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
@@ -53,4 +53,4 @@ def run(so, code, printed=None):
 
 
 def launches(calls):
-    return [Launch(c[1], c[2], int(c[3]), int(c[4])) for c in calls if c[0] == "launch"]
+    return [Launch(c[1], c[2], int(c[3]), int(c[4]), int(c[5])) for c in calls if c[0] == "launch"]

@@ -9,10 +9,11 @@ pytestmark = pytest.mark.gpu
 
 CACHE = 268435456
 LINE = CACHE // 10  # up to this many parameters (fp32, gradient, bf16 copy) fit the cache
+GRID, WALK = 1 << 20, 3 << 19  # vectors from which on 4096 work-groups walk, and from which on a thread has one again
 LINES = [int(CACHE / 7.4), int(CACHE / 5.95)]  # from these on they pass it, with and without a bf16 copy
 
 
-@pytest.mark.parametrize("n", [1, 3, 4, 1023, 1027, LINE, LINE + 1, LINE + 6, LINES[0] - 2, LINES[0] + 3, LINES[1] - 2, LINES[1] + 7])
+@pytest.mark.parametrize("n", [1, 3, 4, 1023, 1027, 4 * GRID + 3, 4 * WALK - 1, 4 * WALK + 5, LINE, LINE + 1, LINE + 6, LINES[0] - 2, LINES[0] + 3, LINES[1] - 2, LINES[1] + 7])
 @pytest.mark.parametrize("copy", [True, False])
 def test_update_whole_and_in_pieces(n, copy):
     import paper_1811_01532_amd as wap
@@ -34,7 +35,7 @@ def test_update_whole_and_in_pieces(n, copy):
 
 
 @pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2049, 268435456 // 6, 268435456 // 6 + 5, int(CACHE / 5.35) - 3, int(CACHE / 5.35) + 5, 268435456 // 3 + 3])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2049, 8 * GRID + 7, 8 * WALK - 3, 8 * WALK + 5, 268435456 // 6, 268435456 // 6 + 5, int(CACHE / 5.35) - 3, int(CACHE / 5.35) + 5, 268435456 // 3 + 3])
 def test_relu_derivative(n, in_place):
     import paper_1811_01532_amd as wap
     print(f"[case] relu_bwd {n} {in_place}", flush=True)

@@ -228,3 +228,19 @@ p.run(Mem(p.arena_bytes()), stream=0x10)
 """))]
         want = "Lb0ELb1EEE" if B <= 64 else "ILi128ELi128ELi2ELi2ELi0ELb1EEE"
         assert any(("fc_dw_kernel" if B <= 64 else "wgrad_kernel") in n and want in n for n in names), (net, B, names)
+
+
+def test_work_groups_of_the_streams(so):
+    """4096 work-groups walk where that is the faster way: conversions to 63 M elements, updates and ReLU derivatives to 1.5 x 2^20 vectors,
+    max-pools of channel counts that are no multiple of 8.  Everything else has a thread for each item."""
+    def groups(calls):
+        return [c.groups for c in recorded.launches(recorded.run(so, "m = Mem(1 << 40)\nm2 = Mem(1 << 40, 1 << 41)\n" + calls))]
+    M = 10 ** 6
+    assert groups(f"for n in (1000, 4 * {M}, 10 * {M}, 62 * {M}, 64 * {M}): wap.wap_cast_f32_bf16(n, m, m2, stream=0)") == [1, 3907, 4096, 4096, 62501]
+    assert groups(f"for n in (1000, 8 * {M}, 12 * {M}, 13 * {M}, 80 * {M}): wap.wap_relu_bwd(m, m, m2, n, stream=0)") == [1, 3907, 4096, 6348, 39063]
+    assert groups(f"for n in (1000, 4 * {M}, 6 * {M}, 7 * {M}, 80 * {M}): wap.wap_sgd_update(n, m, m, 0.1, m2, stream=0)") == [1, 3907, 4096, 6836, 78125]
+    for C, want in ((44, 4096), (48, 256 * 35 * 35 * 6 // 256)):
+        assert groups(f"""
+wap.wap_maxpool_fwd(256, 70, 70, {C}, 2, 2, m, m2, m, stream=0)
+wap.wap_maxpool_bwd(256, 70, 70, {C}, 2, 2, m, m, m, m2, stream=0)
+""") == [want] * 2
