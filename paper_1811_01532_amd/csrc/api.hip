@@ -142,6 +142,10 @@ static GemmPlan plan_fc_fwd(const GemmGeom& g, const void* ws, size_t ws_bytes) 
     const size_t have = ws ? ws_bytes : 0;
     GemmPlan whole;
     if (p.ws_bytes <= have || g_force_fwd_cfg >= 0 || g_force_nsplit >= 0 || !fc_fwd_whole(g, &whole)) return p;
+    if (fc_fwd_supported(g, false, false)) {  // (odd rows that the generic kernel is faster on, in what their stream takes)
+        const GemmPlan s = plan_fc_stream(g, false);
+        if (s.ws_bytes <= have) return s;
+    }
     GemmGeom more = g;
     for (++more.M; more.M <= 64; ++more.M)
         if (plan_fwd_like(more, false).ws_bytes <= have) return whole;

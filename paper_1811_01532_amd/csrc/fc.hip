@@ -322,19 +322,34 @@ bool below_2g(double elems) { return elems * 2.0 < 2147483648.0; }
 // (rms error 12 %): 175 of them come here, all shapes take 0.75 of their time (geometric mean; 0.74 with the better kernel for each) and
 // only unaligned rows of a large Wt were slower (28 x 4387 -> 9504 91 instead of 52): these stay.  Steps, AlexNet-style at 32 and VGG-16 at
 // 22 images, 512.4 / 508.3 and 2783.5 / 2780.4.
+static double us_generic_rows(const GemmGeom& g) {
+    const double k = g.IC, mb = 2e-6 * k * g.Ncols;
+    return 7.6 + 0.13 * mb + 0.39e-3 * std::min(k, 16384.0) + 0.024 * g.M + ((g.IC % 64) == 0 ? 0.0 : 0.46 + 0.03 * mb) +
+           ((g.IC % 8) != 0 || (g.Ncols % 4) != 0 ? 2.0 : 0.0) + ((g.IC % 8) != 0 ? 0.33 * mb : 0.0);
+}
 bool fc_fwd_supported(const GemmGeom& g, bool in_step, bool lean) {
     if (!is_fc(g) || g.M > 64 || g.IC < 8 || !below_2g((double)g.M * g.IC) || !below_2g(16.0 * g.IC)) return false;
     const bool quick = (g.IC % 64) == 0;  // the generic kernel's fast mode
     if (g.M > 16) {
-        const double k = g.IC, mb = 2e-6 * k * g.Ncols;
-        if ((g.IC % 8) != 0 && mb > 40.0) return false;
-        const double generic = 7.6 + 0.13 * mb + 0.39e-3 * std::min(k, 16384.0) + 0.024 * g.M + (quick ? 0.0 : 0.46 + 0.03 * mb) +
-                               ((g.IC % 8) != 0 || (g.Ncols % 4) != 0 ? 2.0 : 0.0) + ((g.IC % 8) != 0 ? 0.33 * mb : 0.0);
+        if ((g.IC % 8) != 0 && 2e-6 * g.IC * g.Ncols > 40.0) return false;
         int feat, nsplit;
-        return fc_fwd_plan(g, lean, &feat, &nsplit) < 0.95 * generic + (in_step ? 2.0 : 0.0);  // (a step's next kernel waits for the second launch)
+        return fc_fwd_plan(g, lean, &feat, &nsplit) < 0.95 * us_generic_rows(g) + (in_step ? 2.0 : 0.0);  // (a step's next kernel waits for the second launch)
     }
     if (g.Ncols <= 4096) return !quick || g.M <= 6 || (double)g.IC * g.Ncols <= 50e6;
     return quick ? g.Ncols <= 8192 && g.IC >= 256 && g.IC <= 2048 : 25.0 * g.IC >= g.Ncols;
+}
+// Odd row lengths: a lane's 16 bytes begin between two dwords in every other row, and 512 of a row take 0.06 more for every batch row (rows of
+// even length, also where they are no whole vectors, take what fc_fwd_plan says).  us, generic kernel / stream, Wt cached: 47 x 4789 -> 4096
+// 28.7 / 49.2, 38 x 2013 -> 500 12.2 / 17.5, 64 x 6133 -> 1000 17.1 / 25.3; 43 x 7011 -> 512 17.4 / 15.6, 61 x 325 -> 174 13.4 / 7.8.  The generic kernel
+// is behind its line, too, while the rows are short or few.  Of 981 timings with odd rows, cached and from memory, 799 stay here, at 0.64 of
+// the generic kernel's time (6 of them more than 5 % slower, by 1.22 at most), and the other 182 took 1.14 of it.
+bool fc_fwd_odd_rows_slow(const GemmGeom& g, bool lean) {
+    if (g.M <= 16 || (g.IC & 1) == 0) return false;
+    int feat, nsplit;
+    const double us = fc_fwd_plan(g, lean, &feat, &nsplit);
+    const long rounds = ((long)((g.Ncols + feat - 1) / feat) * nsplit + kNumCU - 1) / kNumCU;
+    const bool behind = g.IC >= 256 && ((g.IC < 3000 && g.Ncols < 2000) || g.Ncols < 128);
+    return us + 0.06 * g.M * rounds * (g.IC / 512.0 / nsplit) >= 0.95 * (us_generic_rows(g) + (behind ? 2.5 : 0.0));
 }
 // The same for the data gradient, whose work-groups share the batch operand among 64 (or 32) columns: up to 32 rows, and
 // where the reduction is short (both kernels wait more than they stream) up to 128.  A work-group walks all rows of Wt with

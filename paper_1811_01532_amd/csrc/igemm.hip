@@ -776,7 +776,20 @@ double us_beside_flat(const GemmGeom& g, int cfg, int nsplit, int tile, int ktil
 
 }  // namespace
 
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) {
+GemmPlan plan_fc_stream(const GemmGeom& g, bool lean) {
+    GemmPlan p;
+    p.cfg = 10;
+    p.nsplit = 1;
+    fc_fwd_plan(g, lean, &p.tile, &p.nsplit);
+    if (g_force_nsplit >= 1) p.nsplit = g_force_nsplit;
+    const int steps = (g.IC + 31) / 32;
+    if (p.nsplit > steps) p.nsplit = steps;
+    p.nsplit = (steps + (steps + p.nsplit - 1) / p.nsplit - 1) / ((steps + p.nsplit - 1) / p.nsplit);  // none empty
+    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * g.M * g.Ncols * sizeof(float) : 0;
+    return p;
+}
+
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean, bool fc_stream) {
     GemmPlan p;
     if (!b_tr && (g_force_fwd_cfg < 0 || g_force_fwd_cfg == 8) && conv_c3_fwd_supported(g)) {
         p.cfg = 8;
@@ -796,18 +809,18 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean) 
         p.ws_bytes = 0;
         return p;
     }
-    if (g_force_fwd_cfg < 0 && (b_tr ? fc_dx_supported(g) : fc_fwd_supported(g, prepacked, lean))) {
-        p.cfg = b_tr ? 11 : 10;
+    if (g_force_fwd_cfg < 0 && b_tr && fc_dx_supported(g)) {
+        p.cfg = 11;
         p.nsplit = 1;
-        if (!b_tr) {
-            fc_fwd_plan(g, lean, &p.tile, &p.nsplit);
-            if (g_force_nsplit >= 1) p.nsplit = g_force_nsplit;
-        }
-        const int steps = (g.IC + 31) / 32;
-        if (p.nsplit > steps) p.nsplit = steps;
-        p.nsplit = (steps + (steps + p.nsplit - 1) / p.nsplit - 1) / ((steps + p.nsplit - 1) / p.nsplit);  // none empty
-        p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * g.M * g.Ncols * sizeof(float) : 0;
+        p.ws_bytes = 0;
         return p;
+    }
+    if (g_force_fwd_cfg < 0 && !b_tr && fc_stream && fc_fwd_supported(g, prepacked, lean)) {
+        if (fc_fwd_odd_rows_slow(g, lean)) {  // (calls that bring no workspace stream where the generic kernel needs one)
+            p = plan_fwd_like(g, b_tr, prepacked, lean, false);
+            if (!lean || p.ws_bytes == 0) return p;
+        }
+        return plan_fc_stream(g, lean);
     }
     int mode = classify_mode(g, b_tr);
     int ktiles = ((mode == 2 ? g.R * g.S * ((g.IC + 7) / 8 * 8) : g.Kred) + BK - 1) / BK;

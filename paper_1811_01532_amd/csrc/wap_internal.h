@@ -128,7 +128,8 @@ constexpr int kTileSplit64 = 1, kTileSplit192 = 3, kTileFill = 10, kTileStrips =
 //  TR : Bw[k][R-1-r][S-1-s][n]  (data gradient: reduction (r,s,k), k innermost): n contiguous
 // prepacked: the caller keeps the weights in packed order (a step plan); else a packing launch in front is part of the price.
 // lean: a single call that takes no workspace where the generic kernel needs none
-GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked = false, bool lean = false);
+GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked = false, bool lean = false, bool fc_stream = true);  // fc_stream: forward streams may be chosen
+GemmPlan plan_fc_stream(const GemmGeom& g, bool lean);  // where fc_fwd_supported
 int launch_fwd_like(const GemmGeom& g, bool b_tr, const GemmPlan& plan, const bf16_t* A,
                     const bf16_t* Bw, const float* bias, bool relu, bf16_t* out, void* ws,
                     hipStream_t st, hipEvent_t ev_mid = nullptr,  // ev_mid: recorded between kernel and split epilogue
@@ -246,6 +247,7 @@ int launch_dgrad_thin(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, bf16
 
 // fully-connected products with few rows as streams of the weights (fc.hip); geometries of geom_fc_fwd / geom_fc_dx
 bool fc_fwd_supported(const GemmGeom& g, bool in_step, bool lean);
+bool fc_fwd_odd_rows_slow(const GemmGeom& g, bool lean);  // of what is supported: the generic kernel is predicted ahead
 bool fc_dx_supported(const GemmGeom& g);
 double fc_fwd_plan(const GemmGeom& g, bool lean, int* feat, int* nsplit);
 bool fc_fwd_whole(const GemmGeom& g, GemmPlan* p);

@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 CASES = [(17, 64, 16, (True, 2)), (31, 512, 1000, (True, 2)), (32, 4096, 1000, (True, 2)), (33, 4096, 500, (True, 4)), (48, 1000, 333, (True, 4)),
          (63, 67, 41, (False, 4)), (64, 9216, 512, None), (64, 515, 4096, (False, 4)), (20, 1024, 8192, None), (40, 22000, 80, (True, 4)), (64, 8, 9, (True, 4)),
          (18, 9, 24, (False, 2)), (20, 27, 40, (False, 2)), (25, 13, 700, (False, 2)), (29, 4099, 515, (False, 2)), (30, 5121, 200, (False, 2)),
-         (32, 1003, 1000, (False, 2)), (17, 11003, 90, (False, 2)), (64, 2107, 90, (False, 4)), (63, 1344, 500, None), (33, 2112, 512, None)]
+         (32, 1003, 1000, (False, 2)), (17, 11003, 90, (False, 2)), (64, 2107, 90, (False, 4)), (63, 1344, 500, None), (33, 2112, 512, None),
+         (43, 7011, 512, (False, 4)), (45, 2014, 500, (False, 4)), (38, 2013, 500, None), (61, 325, 174, (False, 4)), (32, 4837, 1200, None)]
 # rows that the generic kernel takes, in the workspace that is enough for more rows, bytes
-SHORT = [(63, 1344, 500, 0), (58, 1088, 572, 0), (33, 2112, 512, 409600), (61, 1152, 500, 0)]
+SHORT = [(63, 1344, 500, 0), (58, 1088, 572, 0), (33, 2112, 512, 409600), (61, 1152, 500, 0), (49, 1933, 4096, 0)]
 
 
 @pytest.mark.parametrize("B,n_in,n_out,nws", [c[:3] + (None,) for c in CASES] + SHORT)

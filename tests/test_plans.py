@@ -244,3 +244,30 @@ def test_work_groups_of_the_streams(so):
 wap.wap_maxpool_fwd(256, 70, 70, {C}, 2, 2, m, m2, m, stream=0)
 wap.wap_maxpool_bwd(256, 70, 70, {C}, 2, 2, m, m, m, m2, stream=0)
 """) == [want] * 2
+
+
+def test_odd_rows_stream_only_where_that_is_faster(so):
+    """17 to 64 rows of odd length: beside what the GPU test runs, layers that were timed on either side of the line, and the next even length."""
+    def stream(B, i, o):
+        calls = recorded.launches(recorded.run(so, f"""
+m, d = Mem(1 << 34), wap.fc_desc({B}, {i}, {o})
+need = wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD)
+wap.wap_fc_fwd(d, m, m, None, m, Mem(need) if need else None, stream=0)
+"""))
+        return "fc_fwd_kernel" in calls[0].kernel
+    assert [stream(*c) for c in ((47, 4789, 4096), (64, 6133, 1000), (49, 3353, 4096), (52, 21501, 500), (32, 17215, 1000))] == [False] * 5
+    assert [stream(*c) for c in ((33, 7283, 500), (41, 7611, 9), (40, 693, 512), (21, 5991, 512), (47, 4790, 4096), (64, 6132, 1000), (52, 21502, 500))] == [True] * 7
+
+
+def test_odd_rows_run_in_what_their_stream_takes(so):
+    """Layers whose rows of odd length the generic kernel takes run without a workspace, or in that of the stream's partial sums, as well."""
+    recorded.run(so, """
+m = Mem(1 << 34)
+for B, i, o, splits in ((47, 4789, 4096, 1), (49, 3353, 4096, 1), (64, 6133, 1000, 4), (38, 2013, 500, 1), (52, 21501, 500, 7)):
+    d = wap.fc_desc(B, i, o)
+    have = 4 * splits * B * o if splits > 1 else 0
+    assert wap.wap_fc_workspace_bytes(d, wap.WAP_PASS_FWD) > have
+    wap.wap_fc_fwd(d, m, m, None, m, Mem(have) if have else None, stream=0)
+    c = wap.conv_desc(B, 1, 1, i, o, 1, 1, 1, 0)
+    assert wap.wap_conv2d_workspace_bytes(c, wap.WAP_PASS_FWD) == 0 or splits > 1
+""")
