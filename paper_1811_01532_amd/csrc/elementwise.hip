@@ -490,9 +490,8 @@ __device__ __forceinline__ void loss_mean(const LossMean m, float* sh) {
 // work-group takes the mean of the row losses; it waits for nothing here, and nothing for it.  (A flag of the launch instead, which every
 // work-group waits for: 12 x 29 x 29 x 200 5.1 -> 5.5 us.)
 template <int VEC, int WIN, bool COLSUM, bool MEAN>
-__global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
-                                                                  const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, const PoolArgs a,
-                                                                  float* __restrict__ colsum, const LossMean mean) {
+__device__ __forceinline__ void maxpool_bwd_s2(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am, const bf16_t* __restrict__ ry,
+                                               bf16_t* __restrict__ dx, const PoolArgs& a, uint32_t threads, float* __restrict__ colsum, const LossMean& mean) {
     __shared__ __align__(16) float red[COLSUM ? kThreads * VEC : MEAN ? kThreads : 4];
     const uint32_t groups = gridDim.x - (MEAN ? 1 : 0);
     if constexpr (MEAN) {
@@ -506,8 +505,8 @@ __global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* 
     for (int e = 0; e < VEC; ++e) cs[e] = 0.f;
     const uint32_t CV = a.C / VEC;
     const uint32_t WB = (a.W + 1) / 2, HB = (a.H + 1) / 2;
-    const uint32_t stride = groups * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.items; i += stride) {
+    const uint32_t stride = groups * threads;
+    for (uint32_t i = blockIdx.x * threads + threadIdx.x; i < a.items; i += stride) {
         const uint32_t t = fdiv(i, a.dCV);
         const uint32_t cv = i - t * CV;
         const uint32_t t2 = fdiv(t, a.dX);
@@ -543,7 +542,7 @@ __global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* 
             }
     }
     if constexpr (COLSUM) {  // the pixels of the work-group in order of a tree: fixed by the shape
-        const uint32_t np = blockDim.x / CV, px = threadIdx.x / CV;
+        const uint32_t np = threads / CV, px = threadIdx.x / CV;
         f32x4* const mine = reinterpret_cast<f32x4*>(red + threadIdx.x * VEC);
         auto put = [&]() {
 #pragma unroll
@@ -570,6 +569,20 @@ __global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* 
                 *reinterpret_cast<f32x4*>(colsum + (size_t)blockIdx.x * a.C + threadIdx.x * VEC + 4 * q) = f32x4{cs[4 * q], cs[4 * q + 1], cs[4 * q + 2], cs[4 * q + 3]};
         }
     }
+}
+
+// Alone, with work-groups of a constant size, and with what rides along: one kernel for both read the size and its longer arguments at every
+// work-group's start (31 x 19 x 19 x 200, window 3, 5.8 us, 5.5 so; 11 x 51 x 51 x 344, window 2, 9.7 / 9.3).
+template <int VEC, int WIN>
+__global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
+                                                                  const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, const PoolArgs a) {
+    maxpool_bwd_s2<VEC, WIN, false, false>(dy, am, ry, dx, a, kThreads, nullptr, LossMean{nullptr, nullptr, 0});
+}
+template <int WIN, bool COLSUM, bool MEAN>
+__global__ __launch_bounds__(kThreads) void maxpool_bwd_s2_sums_kernel(const bf16_t* __restrict__ dy, const uint8_t* __restrict__ am,
+                                                                       const bf16_t* __restrict__ ry, bf16_t* __restrict__ dx, const PoolArgs a,
+                                                                       uint32_t threads, float* __restrict__ colsum, const LossMean mean) {
+    maxpool_bwd_s2<8, WIN, COLSUM, MEAN>(dy, am, ry, dx, a, COLSUM ? threads : kThreads, colsum, mean);
 }
 
 // any other stride or window: a thread per input pixel walks the windows that cover it
@@ -1024,15 +1037,15 @@ int launch_maxpool_bwd(int N, int H, int W, int C, int win, int stp, const bf16_
         // (walking element by element as in the forward pass: 256 x 49 x 49 x 42, window 2, 35.0 / 38.8)
         const dim3 grid((colsum ? rows : grid_for(a.items, vec == 8 ? 0 : SIZE_MAX)) + (mean ? 1 : 0));
         const dim3 threads(colsum ? pool_colsum_threads(C) : kThreads);
-#define WAP_POOL(VEC, WIN, COLSUM, MEAN) hipLaunchKernelGGL((maxpool_bwd_s2_kernel<VEC, WIN, COLSUM, MEAN>), grid, threads, 0, st, dy, am, ry, dx, a, colsum, lm)
-#define WAP_POOL_WIN(VEC, COLSUM, MEAN) do { if (win == 2) WAP_POOL(VEC, 2, COLSUM, MEAN); else WAP_POOL(VEC, 3, COLSUM, MEAN); } while (0)
-        if (colsum && mean) WAP_POOL_WIN(8, true, true);
-        else if (colsum) WAP_POOL_WIN(8, true, false);
-        else if (mean) WAP_POOL_WIN(8, false, true);
-        else if (vec == 8) WAP_POOL_WIN(8, false, false);
-        else WAP_POOL_WIN(1, false, false);
-#undef WAP_POOL_WIN
-#undef WAP_POOL
+#define WAP_POOL_SUMS(COLSUM, MEAN)                                                                                                             \
+    hipLaunchKernelGGL((win == 2 ? maxpool_bwd_s2_sums_kernel<2, COLSUM, MEAN> : maxpool_bwd_s2_sums_kernel<3, COLSUM, MEAN>), grid, threads, 0, \
+                       st, dy, am, ry, dx, a, threads.x, colsum, lm)
+        if (colsum && mean) WAP_POOL_SUMS(true, true);
+        else if (colsum) WAP_POOL_SUMS(true, false);
+        else if (mean) WAP_POOL_SUMS(false, true);
+        else if (vec == 8) hipLaunchKernelGGL((win == 2 ? maxpool_bwd_s2_kernel<8, 2> : maxpool_bwd_s2_kernel<8, 3>), grid, threads, 0, st, dy, am, ry, dx, a);
+        else hipLaunchKernelGGL((win == 2 ? maxpool_bwd_s2_kernel<1, 2> : maxpool_bwd_s2_kernel<1, 3>), grid, threads, 0, st, dy, am, ry, dx, a);
+#undef WAP_POOL_SUMS
         return check_launch("maxpool_bwd");
     }
     const PoolArgs a = pool_args(N, H, W, C, win, stp, vec, H, W);

@@ -271,3 +271,16 @@ for B, i, o, splits in ((47, 4789, 4096, 1), (49, 3353, 4096, 1), (64, 6133, 100
     c = wap.conv_desc(B, 1, 1, i, o, 1, 1, 1, 0)
     assert wap.wap_conv2d_workspace_bytes(c, wap.WAP_PASS_FWD) == 0 or splits > 1
 """)
+
+
+def test_max_pools_backward_alone_and_with_sums(so):
+    """A call runs the kernel without the arguments of column sums and mean loss, the pools of a step with biases the one that has them."""
+    calls = [c.kernel for c in recorded.launches(recorded.run(so, """
+m = Mem(1 << 34)
+for win, C in ((2, 64), (3, 200), (2, 9), (3, 9)):
+    wap.wap_maxpool_bwd(31, 19, 19, C, win, 2, m, m, m, m, stream=0)
+p = wap.StepPlan("alexnet", 5, image=99, flags=wap.WAP_STEP_BIAS)
+p.run(Mem(p.arena_bytes()), stream=0x10)
+""")) if "maxpool_bwd" in c.kernel]
+    assert all("maxpool_bwd_s2_kernelILi%dELi%dEE" % (v, w) in c for (v, w), c in zip(((8, 2), (8, 3), (1, 2), (1, 3)), calls)), calls
+    assert len(calls) == 7 and all("maxpool_bwd_s2_sums_kernelILi3ELb1E" in c for c in calls[4:]), calls
