@@ -911,11 +911,14 @@ GemmPlan plan_fwd_like(const GemmGeom& g, bool b_tr, bool prepacked, bool lean, 
     // weights one after another, and too few work-groups to hide them), and layers of 169 and 196 pixels were level.  Beyond
     // 512 channels, where neither prediction was fitted, 13 of 110 layers were slower (gradient 64 x 14, 800 -> 928 31.1 / 34.8).  5x5 splits of
     // the patch kernel change over only with a reduction of 64 channels, where every wavefront has one turn, and a 32 x 32 block of outputs
-    // a CU at most (27 x 27, 64 -> 192 11.7 / 9.5, 55 x 55, 64 -> 64 11.9 / 9.3); with 96 channels they were 3 to 12 % ahead, with more up to half.  Where a single call needed no workspace, tiles
-    // that read a packed copy of the weights take over only if the caller has one for it (not lean); where it needed some, only
-    // if that is enough (the two queries of a layer stay what they were).
+    // a CU at most (27 x 27, 64 -> 192 11.7 / 9.5, 55 x 55, 64 -> 64 11.9 / 9.3); with 96 channels they were 3 to 12 % ahead, with more up to
+    // half.  5x5 splits of the generic kernel whose reduction has more than 256 channels change over from four pixels for each of them on (gradient
+    // 9 x 10 x 10, 384 -> 400 23.9 / 28.3, 30 x 6 x 6, 448 -> 432 27.9 / 32.7; 124 timings below that line 1.06 in the mean, 148 above it 0.90, none
+    // of them above 1.06).  Where a single call needed no workspace, tiles that read a packed copy of the weights take over only if the caller
+    // has one for it (not lean); where it needed some, only if that is enough (the two queries of a layer stay what they were).
     const bool split = !prepacked && nsplit > 1;
-    const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5 && (g.IC > 64 || (double)g.M * g.Ncols > 1024.0 * kNumCU)))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
+    const bool kept = !prepacked && ((nsplit > 1 && (g.M < 700 || std::max(g.IC, g.Ncols) > 512 || (cfg == 7 && g.R == 5 && (g.IC > 64 || (double)g.M * g.Ncols > 1024.0 * kNumCU)) ||
+                                                       (cfg < 5 && g.R == 5 && g.IC > 256 && g.M < 4 * g.IC))) || (cfg == 6 && b_tr && g.Ncols % 32 != 0));
     if (g_force_fwd_cfg < 0 && g_force_nsplit < 0 && (cfg < 5 || cfg == 6 || cfg == 7) && !kept) {
         const double flops = 2.0 * g.M * g.Ncols * g.Kred, blocks = (double)g.M * g.Ncols / 1024.0 / kNumCU;
         size_t need = std::max(p.ws_bytes, wreg_wt_bytes(g));

@@ -284,3 +284,16 @@ p.run(Mem(p.arena_bytes()), stream=0x10)
 """)) if "maxpool_bwd" in c.kernel]
     assert all("maxpool_bwd_s2_kernelILi%dELi%dEE" % (v, w) in c for (v, w), c in zip(((8, 2), (8, 3), (1, 2), (1, 3)), calls)), calls
     assert len(calls) == 7 and all("maxpool_bwd_s2_sums_kernelILi3ELb1E" in c for c in calls[4:]), calls
+
+
+def test_divided_5x5_calls_of_long_reductions(so):
+    """Single calls on either side of four pixels a channel: below, the divided reduction of the generic kernel; with up to 256 channels, the flat tiles."""
+    printed = {}
+    recorded.run(so, """
+for N, H, C, K in ((9, 10, 400, 384), (8, 11, 440, 384), (30, 6, 432, 448), (13, 10, 328, 512), (1, 33, 416, 384), (5, 22, 392, 384), (10, 13, 408, 512), (24, 10, 424, 256)):
+    print("dx", [N * H * H, K, wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, C, K, 5, 5, 1, 2), wap.WAP_PASS_BWD_DATA)])
+for N, H, C, K in ((19, 8, 320, 264), (23, 8, 448, 296), (2, 35, 384, 472), (5, 20, 320, 304), (29, 8, 256, 424), (20, 6, 256, 512)):
+    print("fwd", [N * H * H, C, wap.wap_conv2d_kernel_name(wap.conv_desc(N, H, H, C, K, 5, 5, 1, 2), wap.WAP_PASS_FWD)])
+""", printed)
+    for M, channels, name in printed["dx"] + printed["fwd"]:
+        assert name.startswith("igemm_kernel" if M < 4 * channels and channels > 256 else "conv_tile2d_flat_kernel"), (M, channels, name)
