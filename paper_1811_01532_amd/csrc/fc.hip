@@ -152,8 +152,9 @@ __global__ __launch_bounds__(64 * FW_WAVES) void fc_fwd_kernel(const FcArgs a) {
 
 constexpr int DX_WAVES = 8;
 
-// NB: blocks of 16 batch rows; CPL: columns of Wt per lane (a work-group owns 16 * CPL); VEC8: out % 8 == 0
-template <int NB, int CPL, bool VEC8>
+// NB: blocks of 16 batch rows; CPL: columns of Wt per lane (a work-group owns 16 * CPL); VEC8: out % 8 == 0; SUM: column sums as well (as a flag of
+// the launch they cost those without them 0.25 us: 96 x 500 -> 4096 7.50 / 7.76)
+template <int NB, int CPL, bool VEC8, bool SUM>
 __global__ __launch_bounds__(64 * DX_WAVES) void fc_dx_kernel(const FcArgs a) {
     constexpr int U = NB * CPL <= 4 ? 2 : 1;  // 32-deep steps per register set
     __shared__ f32x4_t red[DX_WAVES][CPL][64];
@@ -281,13 +282,13 @@ __global__ __launch_bounds__(64 * DX_WAVES) void fc_dx_kernel(const FcArgs a) {
                             (unsigned)f2bf(s[2]) | ((unsigned)f2bf(s[3]) << 16)};
                 __builtin_memcpy(reinterpret_cast<bf16_t*>(a.res) + e, &pk, 8);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) cs[t] += __uint_as_float((t & 1) ? pk[t >> 1] & 0xffff0000u : pk[t >> 1] << 16);
+                for (int t = 0; SUM && t < 4; ++t) cs[t] += __uint_as_float((t & 1) ? pk[t >> 1] & 0xffff0000u : pk[t >> 1] << 16);
             }
         }
         __syncthreads();
     }
     // the work-group has all rows of its columns: their sums are the bias gradient of the layer below
-    if (a.colsum && tid < 64 * CPL) {
+    if (SUM && tid < 64 * CPL) {
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1)
 #pragma unroll
@@ -440,17 +441,19 @@ int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, cons
 }
 
 namespace {
-template <int CPL, bool VEC8>
+template <int CPL, bool VEC8, bool SUM = false>
 int launch_dx(const FcArgs& a, hipStream_t st) {
     const dim3 grid((a.in + 16 * CPL - 1) / (16 * CPL)), block(64 * DX_WAVES);
-    if (a.B <= 16) hipLaunchKernelGGL((fc_dx_kernel<1, CPL, VEC8>), grid, block, 0, st, a);
-    else if (a.B <= 32) hipLaunchKernelGGL((fc_dx_kernel<2, CPL, VEC8>), grid, block, 0, st, a);
-    else if (a.B <= 64) hipLaunchKernelGGL((fc_dx_kernel<4, CPL, VEC8>), grid, block, 0, st, a);
-    else if constexpr (CPL == 2) hipLaunchKernelGGL((fc_dx_kernel<8, 2, VEC8>), grid, block, 0, st, a);
+    if (a.B <= 16) hipLaunchKernelGGL((fc_dx_kernel<1, CPL, VEC8, SUM>), grid, block, 0, st, a);
+    else if (a.B <= 32) hipLaunchKernelGGL((fc_dx_kernel<2, CPL, VEC8, SUM>), grid, block, 0, st, a);
+    else if (a.B <= 64) hipLaunchKernelGGL((fc_dx_kernel<4, CPL, VEC8, SUM>), grid, block, 0, st, a);
+    else if constexpr (CPL == 2) hipLaunchKernelGGL((fc_dx_kernel<8, 2, VEC8, SUM>), grid, block, 0, st, a);
     else return set_error(WAP_EINVAL, "internal: more than 64 batch rows need two columns per lane");
     return check_launch("fc_dx");
 }
 }  // namespace
+
+bool fc_dx_sums(const GemmGeom& g) { return (g.IC % 8) == 0 && (g.Ncols % 64) == 0; }  // whole work-groups of columns
 
 // Four columns per lane read whole 128-byte lines of a row.  Where that gives fewer than 96 work-groups (4096 columns at
 // 8 rows: 12.7 us), or the sums of more than 64 batch rows would not fit the registers, two columns per lane (10.7 us;
@@ -458,6 +461,10 @@ int launch_dx(const FcArgs& a, hipStream_t st) {
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, float* colsum, hipStream_t st) {
     const FcArgs a = {dy, w, nullptr, mask, dx, g.M, g.Ncols, g.IC, 0, 0, 0, 0, colsum};
     const bool wide = g.Ncols >= 96 * 64 && g.M <= 64, vec8 = (g.IC % 8) == 0;
+    if (colsum) {
+        if (!fc_dx_sums(g)) return set_error(WAP_EINVAL, "internal: no column sums from this fully-connected data gradient");
+        return wide ? launch_dx<4, true, true>(a, st) : launch_dx<2, true, true>(a, st);
+    }
     if (wide) return vec8 ? launch_dx<4, true>(a, st) : launch_dx<4, false>(a, st);
     return vec8 ? launch_dx<2, true>(a, st) : launch_dx<2, false>(a, st);
 }

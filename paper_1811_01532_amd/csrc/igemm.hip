@@ -1129,7 +1129,7 @@ bool fwd_like_fuses_unpool(const GemmGeom& g, const GemmPlan& plan) {
 }
 int fwd_like_colsum_rows(const GemmGeom& g, const GemmPlan& plan) {
     if (plan.nsplit > 1 && plan.cfg != 10) return reduce_bf16_colsum_rows(g.M, g.Ncols);
-    if (plan.cfg == 11) return 1;
+    if (plan.cfg == 11) return fc_dx_sums(g) ? 1 : 0;
     if (plan.cfg == 16) return flat_colsum_rows(g, plan.tile);
     return plan.cfg == 7 && (g.Ncols % 8) == 0 ? tile2d_colsum_rows(g, plan.tile) : 0;
 }

@@ -254,6 +254,7 @@ bool fc_fwd_whole(const GemmGeom& g, GemmPlan* p);
 // out: bf16 [B][out] with bias / ReLU applied, or fp32 partial sums [nsplit][B][out] for nsplit > 1
 int launch_fc_fwd(const GemmGeom& g, int nsplit, int feat, const bf16_t* x, const bf16_t* w, const float* bias, bool relu, void* out,
                   hipStream_t st);
+bool fc_dx_sums(const GemmGeom& g);  // whether launch_fc_dx can leave column sums
 int launch_fc_dx(const GemmGeom& g, const bf16_t* dy, const bf16_t* w, const bf16_t* mask, bf16_t* dx, float* colsum, hipStream_t st);
 
 // fully-connected weight gradient with few batch rows as a stream of the weights (fc_dw.hip); sgd, max_groups, once: as launch_wgrad

@@ -273,6 +273,18 @@ for B, i, o, splits in ((47, 4789, 4096, 1), (49, 3353, 4096, 1), (64, 6133, 100
 """)
 
 
+def test_fully_connected_data_gradients_alone_and_with_sums(so):
+    """A call runs the kernel without column sums, the layers of a step with biases the one that leaves them."""
+    calls = [c.kernel for c in recorded.launches(recorded.run(so, """
+m = Mem(1 << 34)
+for B, i, o in ((96, 4096, 500), (8, 9216, 1000), (16, 4100, 333)):
+    wap.wap_fc_bwd(wap.fc_desc(B, i, o), m, m, m, m, None, None, stream=0)
+p = wap.StepPlan("alexnet", 5, image=99, flags=wap.WAP_STEP_BIAS)
+p.run(Mem(p.arena_bytes()), stream=0x10)
+""")) if "fc_dx_kernel" in c.kernel]
+    assert [("Lb0EEE" in c, "Lb1EEE" in c) for c in calls] == [(True, False)] * 3 + [(False, True)] * 2 + [(True, False)], calls
+
+
 def test_max_pools_backward_alone_and_with_sums(so):
     """A call runs the kernel without the arguments of column sums and mean loss, the pools of a step with biases the one that has them."""
     calls = [c.kernel for c in recorded.launches(recorded.run(so, """
